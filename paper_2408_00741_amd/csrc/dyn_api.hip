@@ -966,7 +966,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
 }
 
 namespace {
-struct PathWs { size_t layout, order, seg, transition, pred, kend, min_cost, min_k, exits, total; };
+struct PathWs { size_t layout, order, seg, transition, pred, kend, end_total, min_cost, min_k, exits, total; };
 PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) {
   PathWs w;
   size_t off = 0;
@@ -976,6 +976,7 @@ PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) 
   w.transition = off; off += align256((size_t)n_layout * n_layout * sizeof(double));
   w.pred = off; off += align256((size_t)G * n_window * n_layout * sizeof(int32_t));
   w.kend = off; off += align256((size_t)G * n_window * sizeof(int32_t));
+  w.end_total = off; off += align256(n_layout <= DYN_WAVE ? (size_t)G * n_window * sizeof(double) : 0);
   const size_t per_layout = n_layout <= DYN_WAVE ? (size_t)G * n_window * n_layout : 0;   // the wave-per-class route only
   w.min_cost = off; off += align256(per_layout * sizeof(double));
   w.min_k = off; off += align256(per_layout * sizeof(int32_t));
@@ -1044,7 +1045,7 @@ int dyn_select_path(dyn_profile* p, const dyn_space* space, const dyn_config* cf
   a.G = p->G; a.n_tp_f = p->n_tp * p->n_f; a.n_window = n_window; a.window_s = window_s; a.idle_w = o->idle_cost_weight;
   a.n_layout = tr->n_layout; a.layout = p->d_path_layout; a.transition = p->d_path_trans;
   a.order = p->d_path_order; a.seg_start = p->d_path_seg;
-  a.pred = (int32_t*)(base + w.pred); a.kend = (int32_t*)(base + w.kend);
+  a.pred = (int32_t*)(base + w.pred); a.kend = (int32_t*)(base + w.kend); a.end_total = (double*)(base + w.end_total);
   a.min_cost = (double*)(base + w.min_cost); a.min_k = (int32_t*)(base + w.min_k); a.exits = (int32_t*)(base + w.exits);
   a.sel = out->sel; a.sel_energy = out->sel_energy_j; a.path_cost = out->path_cost;
   if (!hip_ok(dyn_launch_path(a, s), "path launch")) return DYN_E_DEVICE;
@@ -1212,7 +1213,7 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     // one candidate per layout: the layout map, the sorted order and the segment starts are all the identity
     pa.n_layout = c->n_layout; pa.layout = p->d_ident; pa.transition = p->d_hier_trans;
     pa.order = p->d_ident; pa.seg_start = p->d_ident;
-    pa.pred = (int32_t*)(pb + pw.pred); pa.kend = (int32_t*)(pb + pw.kend);
+    pa.pred = (int32_t*)(pb + pw.pred); pa.kend = (int32_t*)(pb + pw.kend); pa.end_total = (double*)(pb + pw.end_total);
     pa.min_cost = (double*)(pb + pw.min_cost); pa.min_k = (int32_t*)(pb + pw.min_k); pa.exits = (int32_t*)(pb + pw.exits);
     pa.sel = out->layout_sel; pa.sel_energy = (double*)(base + w.sel_energy); pa.path_cost = out->path_cost;
     if (!hip_ok(dyn_launch_path(pa, s), "path launch")) return DYN_E_DEVICE;

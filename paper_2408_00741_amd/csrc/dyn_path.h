@@ -20,6 +20,7 @@ struct PathArgs {
   const double* transition;     // DEVICE [n_layout][n_layout] (from, to)
   int32_t* pred;                // workspace [G][n_window][n_layout]
   int32_t* kend;                // workspace [G][n_window]
+  double* end_total;            // workspace [G][n_window] (n_layout <= 64): total of the sequence that ends in the window, +inf where none does
   double* min_cost;             // workspace [cells][n_layout] (n_layout <= 64): least cost of a layout's candidates, then least total of the sequences ending there
   int32_t* min_k;               // workspace [cells][n_layout]: the candidate that has it
   int32_t* exits;               // workspace [G][runs][DYN_PATH_STATES] (n_layout <= 64): state a run of windows is left with, by the state it is entered with

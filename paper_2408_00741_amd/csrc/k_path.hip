@@ -21,6 +21,7 @@
 #include <algorithm>
 
 #include "dyn_path.h"
+#include "dyn_device.h"
 static_assert(DYN_PATH_MAX_CONFIGS == 256 * 8, "candidates are held in registers, a fixed number per thread");
 
 namespace {
@@ -226,17 +227,12 @@ __global__ __launch_bounds__(kThreads) void path_kernel(PathArgs a) {
 // candidate that has it (adding a layout's arrival total to its candidates' costs keeps their
 // order: rounded addition is monotone).  Those are independent of the recurrence:
 // path_min_kernel takes them for all windows at once.  The recurrence itself only needs minima:
-// path_chain_kernel walks the windows with one lane per layout and keeps, per (window, layout), the
-// least total of the sequences that end there.  Which source and candidate reach a minimum is not part
+// path_chain_kernel walks the windows and keeps, per (window, layout), the least total of the
+// sequences that end there.  Which source and candidate reach a minimum is not part
 // of the recurrence; path_pred_kernel recomputes the same rounded sums from the stored totals for all
 // windows in parallel and records the predecessors (least total, then lowest candidate), and
-// the two path_trace kernels follow them back, all runs of windows at once.  What the walk costs is the instructions one window's step takes
-// in the block's waves (they share the four SIMDs of one compute unit), so the step holds nothing else:
-// global memory is touched a chunk of windows at a time and a source's total is a lane read.
-constexpr int kChainChunk = 16;                            // windows per visit to global memory
-constexpr int kChainWaves = 8;                             // measured on a day of windows and 48 layouts: 4 waves 811 us, 8 waves 740 us, 16 waves 788 us for the whole selection
-constexpr int kEndMark = -2;                               // kend: a sequence ends in this window (before path_pred_kernel fills in its best end)
-
+// the two path_trace kernels follow them back, all runs of windows at once.  Where sequences end, and the classes'
+// totals, come out of those kernels too.  What the walk costs is the latency of one window's step, so the step holds nothing else.
 // thread = (cell, layout): least cost among the layout's candidates, lowest candidate among equals
 __global__ __launch_bounds__(256) void path_min_kernel(PathArgs a) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -272,94 +268,118 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {   // lane m
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// One block of WAVES waves per class; lane = destination layout in every wave, and wave q owns the source
-// layouts [q * LMAX/WAVES, (q + 1) * LMAX/WAVES) with its lanes' entries of those rows of the table in registers.
-// Per window every wave forms the window's totals itself (all waves carry the same state), takes the least
-// arrival total over its sources; the waves' partial minima meet in LDS (atomic minimum per destination)
-// behind the window's only block barrier.  min_cost[window][layout] is overwritten by the least total
-// of the sequences that end there (+inf: none); kend[window] = -1: no feasible candidate, kEndMark: a
-// sequence ends here, 0 otherwise.
-template <int LMAX, int WAVES>
-__global__ __launch_bounds__(WAVES* DYN_WAVE) void path_chain_kernel(PathArgs a) {
-  constexpr int SPW = LMAX / WAVES;                          // sources per wave
-  __shared__ double s_c[(kChainChunk + 1) * DYN_WAVE];       // the chunk's least costs by (window, layout), one window more; totals once a window is done
-  __shared__ int32_t s_ke[kChainChunk];
-  __shared__ double s_best[3][DYN_WAVE];                     // least arrival total per destination: the waves' partial minima meet here (LDS atomic minimum); three buffers in turn
-  const int g = blockIdx.x, lane = threadIdx.x & (DYN_WAVE - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
+// Lane Q of each row of 16 lanes, in all of the row's lanes.
+template <int Q>
+__device__ __forceinline__ double row_lane_f64(double v) {
+  return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, __double_as_longlong(v), 0x150 + Q, 0xF, 0xF, true));   // row_newbcast
+}
+// Smaller of two values that are not NaN, for a lane exchange right after it: the wait states that an exchange of a just
+// written register needs are part of the block (the compiler would quiet both operands first).
+__device__ __forceinline__ double min_then_swap(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// Least value over the four rows of 16 lanes, position by position, in all rows.
+__device__ __forceinline__ double rows_min_f64(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  const double m = min_then_swap(__longlong_as_double((long long)(((uint64_t)h16[0] << 32) | l16[0])),
+                                 __longlong_as_double((long long)(((uint64_t)h16[1] << 32) | l16[1])));
+  const uint64_t x = (uint64_t)__double_as_longlong(m);
+  const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+  return min_then_swap(__longlong_as_double((long long)(((uint64_t)h32[0] << 32) | l32[0])),
+                       __longlong_as_double((long long)(((uint64_t)h32[1] << 32) | l32[1])));
+}
+// m[q] = (lane q of the row's v) + t[q], q = Q .. N - 1
+template <int Q, int N>
+__device__ __forceinline__ void add_sources(double v, const double (&t)[N], double (&m)[N]) {
+  if constexpr (Q < N) {
+    m[Q] = row_lane_f64<Q>(v) + t[Q];
+    add_sources<Q + 1, N>(v, t, m);
+  }
+}
+
+// The walk.  One block per class, a wave per 16 destination layouts; each of its four rows of 16 lanes takes a quarter of
+// the source layouts (SPL = LMAX / 4), lane p of a row the destination p of the wave, with its SPL entries of the overhead
+// table in registers.  Per window a lane reads one total of the window before from LDS (lane q of row r: source
+// r * SPL + q), the row's totals reach all its lanes by DPP broadcasts, and the rows' partial minima meet by lane swaps.
+// Row i holds the least costs of window i of a run of four, adds them when it is that window's turn and writes the new
+// totals to the other LDS buffer: one block barrier per window and nothing else between the waves.  Costs are loaded
+// three runs ahead, totals stored once per run, a window per row.
+// Bound: the latency of one window's chain (LDS read, SPL broadcasts and additions, minima, LDS write, barrier), 1440
+// times in a row on the one-day workload; nothing of the chip's rates applies.  Sources split over waves, their totals
+// by lane reads and the partial minima through LDS atomics: 0.41 us a window; sources read from LDS by every lane
+// (n_layout^2 values a window through the LDS port): 0.27 us; this, with 48 layouts: 0.22 us (596 to 323 us for the day).
+// min_cost[window][layout] is overwritten by the least total of the sequences that end there (+inf: none).
+template <int LMAX>
+__global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
+  constexpr int SPL = LMAX / 4;                              // sources per row
+  static_assert(LMAX % 16 == 0 && LMAX <= 64, "a row of 16 lanes broadcasts its sources");
+  __shared__ double s_v[2][LMAX];                            // least totals of the window before, two buffers in turn
+  __shared__ double s_dump[LMAX * 4];
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const int g = blockIdx.x, r = lane >> 4, p = lane & 15, d = (int)(threadIdx.x / DYN_WAVE) * 16 + p;   // row, place in it, destination
+  const int src = r * SPL + min(p, SPL - 1);                 // the source whose total this lane reads
   const int NL = a.n_layout, NW = a.n_window, G = a.G;
   const double inf = __builtin_inf();
-  const bool on = lane < NL;
-  double t[SPW];                                             // overhead of going from this wave's source q to this lane's layout
+  const bool on = d < NL;
+  double t[SPL];                                             // overhead of going from the row's source q to this lane's destination
 #pragma unroll
-  for (int q = 0; q < SPW; ++q) {
-    const int ls = wave * SPW + q;
-    t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + lane] : inf;   // layouts beyond NL never win
+  for (int q = 0; q < SPL; ++q) {
+    const int ls = r * SPL + q;
+    t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + d] : inf;   // layouts beyond NL never win
   }
-  int32_t* kend = a.kend + (size_t)g * NW;
-  auto row = [&](int w) { return ((size_t)w * G + g) * NL + lane; };
-
-  double total = 0.0, arrive = inf;                          // the same in every wave
-  bool first = true;
-  int buf = 0;
-  if (wave == 0) s_best[0][lane] = inf;                      // ordered before its first use by the chunk loop's barriers
+  double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);  // this destination in window w: col[w * step]
+  const size_t step = (size_t)G * NL;
+  // loaded by every lane, from the last window beyond the end: behind a branch the waits would take in later loads too
+  auto cost = [&](int w) { return col[(size_t)min(w, NW - 1) * step]; };
+  constexpr int kRuns = 4;                                   // runs per loop pass: their costs sit in registers of their own, since
+  double c[kRuns];                                           // handing a value on that is still being loaded would wait for it
+#pragma unroll
+  for (int u = 0; u + 1 < kRuns; ++u) c[u] = cost(4 * u + r);
+  double* put[4];                                            // where a lane writes in window i of a run: no branch in the walk
+#pragma unroll
+  for (int i = 0; i < 4; ++i) put[i] = r == i ? &s_v[(i & 1) ^ 1][d] : &s_dump[threadIdx.x];
+  if (r == 0) s_v[0][d] = inf;                               // before the first window: as after a window without a feasible candidate
+  __syncthreads();
 #pragma unroll 1
-  for (int w0 = 0; w0 < NW; w0 += kChainChunk) {
-    __syncthreads();                                         // the previous chunk's flush has read s_c / s_ke
+  for (int w0 = 0; w0 < NW; w0 += 4 * kRuns) {
 #pragma unroll
-    for (int j = 0; j < (kChainChunk + 1 + WAVES - 1) / WAVES; ++j) {
-      const int i = j * WAVES + wave;                        // row of the chunk this wave loads
-      if (i <= kChainChunk) s_c[i * DYN_WAVE + lane] = (on && w0 + i < NW) ? a.min_cost[row(w0 + i)] : inf;
-    }
-    __syncthreads();
-    const int n = NW - w0 < kChainChunk ? NW - w0 : kChainChunk;
-    double c_nxt = s_c[lane];
-#pragma unroll 1
-    for (int i = 0; i < n; ++i) {
-      const double c_cur = c_nxt;
-      c_nxt = s_c[(i + 1) * DYN_WAVE + lane];                // read a window ahead, before this row is overwritten
-      // least total of the sequences that end in this window in this lane's layout
-      const double v = (first || !(c_cur < inf)) ? c_cur : arrive + c_cur;
-      const bool gap = __ballot(v < inf) == 0;               // no feasible candidate in this window
-      double m[SPW];                                         // sums are never NaN here: plain minima
+    for (int u = 0; u < kRuns; ++u) {
+      const int w = w0 + 4 * u + r;                          // this row's window
+      c[(u + kRuns - 1) % kRuns] = cost(w + 4 * (kRuns - 1));
+      const bool has = on && w < NW;
+      const double cw = has ? c[u] : inf;
+      double keep = inf;
 #pragma unroll
-      for (int q = 0; q < SPW; ++q) m[q] = readlane_f64(v, wave * SPW + q) + t[q];
+      for (int i = 0; i < 4; ++i) {
+        const double v = s_v[i & 1][src];
+        const bool alive = __ballot((int)(__double_as_longlong(v) >> 32) < 0x7FF00000) != 0;   // any total below +inf (the wave holds all of them)
+        double m[SPL];
+        add_sources<0, SPL>(v, t, m);
 #pragma unroll
-      for (int d = 1; d < SPW; d *= 2)
+        for (int k = 1; k < SPL; k *= 2)
 #pragma unroll
-        for (int q = 0; q + d < SPW; q += 2 * d) m[q] = fmin(m[q], m[q + d]);
-      __hip_atomic_fetch_min(&s_best[buf][lane], m[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const int nxt = buf == 2 ? 0 : buf + 1;
-      // the next window's buffer: last read two windows ago, behind the previous window's barrier for every wave
-      if (wave == WAVES - 1) s_best[nxt][lane] = inf;
-      lds_barrier();                                         // the window's only block barrier
-      if (wave == 0) s_c[i * DYN_WAVE + lane] = v;           // every wave has taken this row's costs before the barrier
-      const double bv = s_best[buf][lane];
-      buf = nxt;
-      // a sequence ends here if the next window has no feasible candidate (its costs are all +inf) or does not exist
-      const bool ends = !gap && (w0 + i + 1 >= NW || __ballot(c_nxt < inf) == 0);
-      if (ends) {                                            // wave-uniform
-        double ev = v;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) ev = fmin(ev, __shfl_xor(ev, d, DYN_WAVE));
-        total += ev;                                         // the sequences' totals in time order
+          for (int q = 0; q + k < SPL; q += 2 * k) m[q] = __builtin_fmin(m[q], m[q + k]);   // sums are never NaN here
+        const double arrive = rows_min_f64(m[0]);
+        // least total of the sequences that end in this window in this destination (row i: its window)
+        const double now = (!alive || !(cw < inf)) ? cw : arrive + cw;
+        *put[i] = now;                                       // the other rows' lanes write to a place of their own that nobody reads
+        keep = r == i ? now : keep;
+        lds_barrier();                                       // the window's only block barrier
       }
-      if (threadIdx.x == 0) s_ke[i] = gap ? -1 : (ends ? kEndMark : 0);
-      arrive = bv;
-      first = gap;
+      if (has) col[(size_t)w * step] = keep;
     }
-    __syncthreads();
-    for (int i = wave; i < n; i += WAVES)
-      if (on) a.min_cost[row(w0 + i)] = s_c[i * DYN_WAVE + lane];
-    if (threadIdx.x < n) kend[w0 + threadIdx.x] = s_ke[threadIdx.x];
   }
-  if (threadIdx.x == 0) a.path_cost[g] = total;
 }
 
 // One wave per (window, class), lane = destination layout, the lane's column of the table in registers: where
 // the cheapest arrival in every layout of the next window comes from (least total + overhead, then the lowest
-// candidate among the sources that reach it), as (candidate << 6) | its layout, -1: none; and the best end of a
-// sequence that ends in this window.  The sums are those of the walk, from the same operands.
+// candidate among the sources that reach it), as (candidate << 6) | its layout, -1: none; and the best end and the total
+// of a sequence that ends in this window.  The sums are those of the walk, from the same operands.
 template <int LMAX>
 __global__ __launch_bounds__(256) void path_pred_kernel(PathArgs a) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
@@ -376,15 +396,22 @@ __global__ __launch_bounds__(256) void path_pred_kernel(PathArgs a) {
     const double v = on ? a.min_cost[(size_t)cell * NL + lane] : inf;
     const int k = on ? a.min_k[(size_t)cell * NL + lane] : 0;
     const uint32_t pk = (v < inf) ? (((uint32_t)k << 6) | (uint32_t)lane) : 0xFFFFFFFFu;
-    int32_t* kend = a.kend + (size_t)g * NW + w;
-    if (*kend == kEndMark) {                                 // wave-uniform
-      double ev = v;
+    const double nv = (on && w + 1 < NW) ? a.min_cost[((size_t)cell + G) * NL + lane] : inf;
+    const bool gap = __ballot(v < inf) == 0;                 // no feasible candidate in this window
+    const bool ends = !gap && __ballot(nv < inf) == 0;       // the next window has none, or does not exist
+    double ev = inf;
+    uint32_t ep = gap ? 0xFFFFFFFFu : 0u;
+    if (ends) {                                              // wave-uniform
+      ev = v;
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) ev = fmin(ev, __shfl_xor(ev, d, DYN_WAVE));
-      uint32_t ep = (v == ev) ? pk : 0xFFFFFFFFu;
+      ep = (v == ev) ? pk : 0xFFFFFFFFu;
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) ep = min(ep, (uint32_t)__shfl_xor((int)ep, d, DYN_WAVE));
-      if (lane == 0) *kend = (int32_t)ep;
+    }
+    if (lane == 0) {
+      a.kend[(size_t)g * NW + w] = (int32_t)ep;              // -1 gap, the best end where a sequence ends, 0 otherwise
+      a.end_total[(size_t)g * NW + w] = ev;                  // +inf where none ends
     }
     if (w + 1 >= NW) continue;
     double m = inf;
@@ -425,11 +452,37 @@ __device__ __forceinline__ void trace_stage(const PathArgs& a, int g, int lo, in
   __syncthreads();
 }
 
-// grid (runs, classes), 128 threads: thread s < DYN_PATH_STATES follows the run back from entry state s.
+// A class's total: its sequences' totals added in time order (one wave; the loads of a chunk of windows are in flight together: a day is one round).
+__device__ __forceinline__ void class_total(const PathArgs& a, int g) {
+  const int NW = a.n_window, lane = threadIdx.x;
+  const double inf = __builtin_inf();
+  const double* end_total = a.end_total + (size_t)g * NW;
+  constexpr int kAhead = 24;
+  double total = 0.0;
+  for (int w0 = 0; w0 < NW; w0 += kAhead * DYN_WAVE) {
+    double v[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int w = w0 + j * DYN_WAVE + lane;
+      v[j] = w < NW ? end_total[w] : inf;
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+      for (uint64_t at = __ballot(v[j] < inf); at != 0; at &= at - 1) total += readlane_f64(v[j], __builtin_ctzll(at));
+  }
+  if (lane == 0) a.path_cost[g] = total;
+}
+
+// grid (runs + 1, classes), 128 threads: thread s < DYN_PATH_STATES follows the run back from entry state s; the blocks
+// beyond the runs add up the classes' totals.
 __global__ __launch_bounds__(128) void path_trace_runs_kernel(PathArgs a) {
   __shared__ int32_t s_bp[DYN_PATH_RUN * DYN_WAVE];
   __shared__ int32_t s_ke[DYN_PATH_RUN];
-  const int r = blockIdx.x, g = blockIdx.y;
+  const int r = blockIdx.x, g = blockIdx.y, n_run = gridDim.x - 1;
+  if (r == n_run) {                                          // block-uniform
+    if (threadIdx.x < DYN_WAVE) class_total(a, g);
+    return;
+  }
   const int lo = r * DYN_PATH_RUN, hi = min(a.n_window, lo + DYN_PATH_RUN);
   trace_stage(a, g, lo, hi, s_bp, s_ke);
   int state = threadIdx.x;
@@ -439,7 +492,7 @@ __global__ __launch_bounds__(128) void path_trace_runs_kernel(PathArgs a) {
     const int rec = trace_step(s_ke[i], state, s_bp, i, a.n_layout);
     state = rec < 0 ? DYN_PATH_STATES - 1 : (rec & 63);
   }
-  a.exits[((size_t)g * gridDim.x + r) * DYN_PATH_STATES + threadIdx.x] = state;
+  a.exits[((size_t)g * n_run + r) * DYN_PATH_STATES + threadIdx.x] = state;
 }
 
 // grid (runs, classes), 64 threads.
@@ -490,11 +543,11 @@ void launch_layout_route(const PathArgs& a, hipStream_t s) {
   const int64_t cells = (int64_t)a.n_window * a.G;
   const int64_t n = cells * a.n_layout;
   hipLaunchKernelGGL(path_min_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL((path_chain_kernel<LMAX, kChainWaves>), dim3((unsigned)a.G), dim3(kChainWaves * DYN_WAVE), 0, s, a);
+  hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
   const int64_t pred_blocks = std::min<int64_t>((cells + 3) / 4, 2048);
   hipLaunchKernelGGL(path_pred_kernel<LMAX>, dim3((unsigned)pred_blocks), dim3(256), 0, s, a);
   const dim3 runs((unsigned)dyn_path_runs(a.n_window), (unsigned)a.G);
-  hipLaunchKernelGGL(path_trace_runs_kernel, runs, dim3(128), 0, s, a);
+  hipLaunchKernelGGL(path_trace_runs_kernel, dim3(runs.x + 1, runs.y), dim3(128), 0, s, a);
   hipLaunchKernelGGL(path_trace_write_kernel, runs, dim3(DYN_WAVE), 0, s, a);
 }
 

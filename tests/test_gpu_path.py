@@ -326,3 +326,39 @@ def test_tiny_spaces_against_every_sequence(dyn, seed):
             assert tuple(int(sel[(x + i) * G + g]) for i in range(e - x)) in best_seq
             x = e
         assert pc[g] == total
+
+
+@pytest.mark.parametrize("NW,NL", [(1, 1), (2, 16), (3, 17), (4, 48), (5, 64), (12, 33), (15, 15), (16, 32), (17, 49), (31, 2), (33, 48), (1537, 3)])
+def test_walk_at_the_edges_of_its_runs(dyn, NW, NL):
+    """The walk takes windows in runs of four, four runs per pass, and the totals of a class are added 1536 windows at a
+    time: window counts around those, a sequence that ends in every third window, overheads that overflow when added."""
+    rng = np.random.default_rng(NW * 100 + NL)
+    w = make(SPECS[0])
+    G, K = w["n_class"], NL + 3
+    cfg = {"n_inst": np.ones(K, np.int32), "tp_index": np.zeros(K, np.int32), "f_mhz": np.full(K, w["profile"]["f_mhz"][0])}
+    energy = np.round(rng.uniform(1, 50, (NW * G, K)), 3)
+    flags = np.where(rng.uniform(0, 1, (NW * G, K)) < 0.7, 1, 4).astype(np.uint8)
+    if NW > 2:
+        for g in range(0, G, 2):
+            flags.reshape(NW, G, K)[2::3, g] = 8
+    lay = (np.arange(K) % NL).astype(np.int32)
+    tr = np.round(rng.uniform(0, 6, (NL, NL)), 3)
+    feas = (flags & 1).astype(np.uint8)
+    o_sel, o_pc = oracle.select_path(energy, feas, NW, G, lay, tr)
+    prof = dyn.dyn_profile_load(w["profile"])
+    plan = dyn.Plan(cfg, w["slos"], w["pct"], None, 0.0)
+    g = run_path(dyn, prof, plan, energy, flags, NW, 60.0, lay, tr)
+    assert check(g, o_sel, o_pc, energy, feas, energy, lay, tr, NW, G) == G
+    if NL > 1 and NW > 1:                                   # a forbidden change: two of them overflow, none is taken
+        tr = np.full((NL, NL), 1.7e308)
+        tr[np.diag_indices(NL)] = 0.0
+        flags[:] = 4
+        for g in range(G):
+            flags.reshape(NW, G, K)[:, g, g % NL] = 1      # one layout can run all windows
+            flags.reshape(NW, G, K)[::2, g] = 1
+        feas = (flags & 1).astype(np.uint8)
+        o_sel, o_pc = oracle.select_path(energy, feas, NW, G, lay, tr)
+        g = run_path(dyn, prof, plan, energy, flags, NW, 60.0, lay, tr)
+        np.testing.assert_array_equal(g["path_cost"], o_pc)
+        np.testing.assert_array_equal(g["sel"], o_sel)
+    prof.free()
