@@ -8,14 +8,8 @@
 // writes where every window starts), and one block per window then counts its requests by class
 // and moves them, stably, to their cells (window_sort_kernel).  Any other trace takes the radix
 // sort.  The host does not read the flag: both routes are enqueued and the kernels of the route
-// not taken return at their first instruction.  The general sort is one launch of a grid the device
-// holds at once, with grid-wide barriers between the phases, so the route not taken costs one empty
-// launch; where the device does not tell what it holds it is the separate kernels below.
-//
-// One radix pass = per-block digit histogram -> exclusive scan of the (digit, block)
-// counters -> stable scatter.  Inside a block every wave owns a contiguous run of rows of
-// 64 requests and walks them in order; the position of a request among the requests of
-// its row with the same digit comes from wave ballots, so arrival order is preserved.
+// not taken return at their first instruction.  The general sort is one launch with grid-wide
+// barriers between the phases, so the route not taken costs one empty launch.
 #include <string.h>
 
 #include <algorithm>
@@ -29,7 +23,6 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kRows = 32;                              // rows of 64 requests per wave
 constexpr int kTile = kWaves * kRows * DYN_WAVE;       // 8192 requests per block
-constexpr int kScanChunk = 4096;                       // counters per block of the scan kernels
 
 constexpr int kKeyRows = 4;                            // requests per thread of the key kernel (rows of 256)
 
@@ -138,233 +131,70 @@ __global__ void edge_store_kernel(EdgePack p, int n_a, int32_t* __restrict__ dst
     header->kind = DYN_WS_KIND_WORD;
     header->cells = 0;
     ((uint32_t*)header)[DYN_WS_HEADER_ORDER_WORD] = order_word;
-    ((uint32_t*)header)[DYN_WS_HEADER_BARRIER_WORD] = 0u;
+    for (int q = 0; q < 3; ++q) ((uint32_t*)header)[DYN_WS_HEADER_BARRIER_WORD + q] = 0u;
   }
-}
-
-// digit counts of one tile -> block_hist[digit * n_block + tile]; `cnt` is DYN_INGEST_MAX_BINS words of LDS
-__device__ __forceinline__ void hist_tile(int64_t tile, const uint32_t* keys, int64_t n, int shift, int bits,
-                                          uint32_t* block_hist, int64_t n_block, uint32_t* cnt) {
-  const int nbins = 1 << bits;
-  const uint32_t mask = (uint32_t)nbins - 1u;
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) cnt[b] = 0;
-  __syncthreads();
-  const int64_t base = tile * kTile;
-  for (int r = 0; r < kTile / (kWaves * DYN_WAVE); ++r) {
-    const int64_t idx = base + (int64_t)r * (kWaves * DYN_WAVE) + threadIdx.x;
-    if (idx < n) atomicAdd(&cnt[(keys[idx] >> shift) & mask], 1u);
-  }
-  __syncthreads();
-  for (int b = threadIdx.x; b < nbins; b += blockDim.x) block_hist[(size_t)b * n_block + tile] = cnt[b];
-}
-
-__global__ __launch_bounds__(kWaves* DYN_WAVE) void hist_kernel(const uint32_t* __restrict__ keys, int64_t n,
-                                                                int shift, int bits, uint32_t* __restrict__ block_hist,
-                                                                int64_t n_block, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  __shared__ uint32_t cnt[DYN_INGEST_MAX_BINS];
-  hist_tile(blockIdx.x, keys, n, shift, bits, block_hist, n_block, cnt);
-}
-
-// ---- exclusive scan of `count` uint32 counters in three small kernels --------------------
-__device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_t* total, uint32_t* s_wave) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t incl = v;
-#pragma unroll
-  for (int d = 1; d < DYN_WAVE; d <<= 1) {
-    const uint32_t up = __shfl_up(incl, d, DYN_WAVE);
-    if (lane >= d) incl += up;
-  }
-  if (lane == 63) s_wave[wave] = incl;
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) off += s_wave[w];
-    tot += s_wave[w];
-  }
-  __syncthreads();
-  *total = tot;
-  return off + incl - v;
-}
-
-__device__ __forceinline__ void scan_reduce_chunk(int64_t chunk, const uint32_t* x, int64_t count, uint32_t* partial, uint32_t* s_wave) {
-  const int64_t base = chunk * kScanChunk;
-  uint32_t v = 0;
-  for (int q = 0; q < kScanChunk / 256; ++q) {
-    const int64_t i = base + q * 256 + threadIdx.x;
-    if (i < count) v += x[i];
-  }
-  uint32_t tot;
-  block_exclusive_scan_256(v, &tot, s_wave);
-  if (threadIdx.x == 0) partial[chunk] = tot;
-}
-
-__device__ __forceinline__ void scan_partials_all(uint32_t* partial, int64_t n_partial, uint32_t* s_wave) {
-  uint32_t carry = 0;
-  for (int64_t base = 0; base < n_partial; base += 256) {
-    const int64_t i = base + threadIdx.x;
-    const uint32_t v = i < n_partial ? partial[i] : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_exclusive_scan_256(v, &tot, s_wave);
-    if (i < n_partial) partial[i] = carry + ex;
-    carry += tot;
-  }
-}
-
-__device__ __forceinline__ void scan_apply_chunk(int64_t chunk, uint32_t* x, int64_t count, const uint32_t* partial, uint32_t* s_wave) {
-  // thread t owns 16 consecutive counters of the chunk
-  constexpr int per = kScanChunk / 256;
-  const int64_t base = chunk * kScanChunk + (int64_t)threadIdx.x * per;
-  uint32_t v[per], sum = 0;
-#pragma unroll
-  for (int q = 0; q < per; ++q) {
-    v[q] = (base + q < count) ? x[base + q] : 0u;
-    sum += v[q];
-  }
-  uint32_t tot;
-  uint32_t run = partial[chunk] + block_exclusive_scan_256(sum, &tot, s_wave);
-#pragma unroll
-  for (int q = 0; q < per; ++q) {
-    if (base + q < count) x[base + q] = run;
-    run += v[q];
-  }
-}
-
-__global__ __launch_bounds__(256) void scan_reduce_kernel(const uint32_t* __restrict__ x, int64_t count,
-                                                          uint32_t* __restrict__ partial, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  __shared__ uint32_t s_wave[4];
-  scan_reduce_chunk(blockIdx.x, x, count, partial, s_wave);
-}
-
-__global__ __launch_bounds__(256) void scan_partials_kernel(uint32_t* __restrict__ partial, int64_t n_partial, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  __shared__ uint32_t s_wave[4];
-  scan_partials_all(partial, n_partial, s_wave);
-}
-
-__global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t* __restrict__ x, int64_t count,
-                                                         const uint32_t* __restrict__ partial, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  __shared__ uint32_t s_wave[4];
-  scan_apply_chunk(blockIdx.x, x, count, partial, s_wave);
-}
-
-// ---- stable scatter of one radix pass -----------------------------------------------------
-__device__ __forceinline__ void scatter_tile(int64_t tile, const uint32_t* keys_in, const int32_t* in_in, const int32_t* out_in,
-                                             uint32_t* keys_out, int32_t* in_out, int32_t* out_out, int64_t n, int shift, int bits,
-                                             const uint32_t* scanned, int64_t n_block, uint32_t (*wcnt)[DYN_INGEST_MAX_BINS]) {
-  const int nbins = 1 << bits;
-  const uint32_t mask = (uint32_t)nbins - 1u;
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
-  const int wave = threadIdx.x / DYN_WAVE;
-  for (int b = threadIdx.x; b < kWaves * DYN_INGEST_MAX_BINS; b += blockDim.x) (&wcnt[0][0])[b] = 0;
-  __syncthreads();
-
-  // phase 1: digit counts of each wave's run of rows
-  const int64_t wbase = tile * kTile + (int64_t)wave * (kRows * DYN_WAVE);
-  uint32_t key[kRows];
-  int32_t vin[kRows], vout[kRows];                       // the payload, loaded with the keys: not one row at a time later
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = wbase + r * DYN_WAVE + lane;
-    key[r] = idx < n ? keys_in[idx] : 0u;
-    vin[r] = idx < n ? in_in[idx] : 0;
-    vout[r] = idx < n ? out_in[idx] : 0;
-    if (idx < n) atomicAdd(&wcnt[wave][(key[r] >> shift) & mask], 1u);
-  }
-  __syncthreads();
-  // phase 2: per digit, the first output position of each wave's requests
-  for (int d = threadIdx.x; d < nbins; d += blockDim.x) {
-    uint32_t run = scanned[(size_t)d * n_block + tile];
-    for (int w = 0; w < kWaves; ++w) {
-      const uint32_t c = wcnt[w][d];
-      wcnt[w][d] = run;
-      run += c;
-    }
-  }
-  __syncthreads();
-  // phase 3: rows in order; inside a row, rank among the lanes with the same digit
-  uint32_t* my = wcnt[wave];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = wbase + r * DYN_WAVE + lane;
-    const bool valid = idx < n;
-    if (__ballot(valid) == 0) break;                     // wave-uniform: nothing left in this run
-    const uint32_t d = (key[r] >> shift) & mask;
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < bits; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t bal = __ballot(bit);
-      peers &= bit ? bal : ~bal;
-    }
-    const int before = __popcll(peers & ((1ull << lane) - 1ull));
-    const int group = __popcll(peers);
-    uint32_t pos = 0;
-    if (valid) pos = my[d] + (uint32_t)before;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (valid && before == group - 1) my[d] += (uint32_t)group;   // one lane per digit advances it
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (valid) {
-      if (keys_out) keys_out[pos] = key[r];
-      in_out[pos] = vin[r];
-      out_out[pos] = vout[r];
-    }
-  }
-}
-
-__global__ __launch_bounds__(kWaves* DYN_WAVE) void scatter_kernel(
-    const uint32_t* __restrict__ keys_in, const int32_t* __restrict__ in_in, const int32_t* __restrict__ out_in,
-    uint32_t* __restrict__ keys_out, int32_t* __restrict__ in_out, int32_t* __restrict__ out_out, int64_t n,
-    int shift, int bits, const uint32_t* __restrict__ scanned, int64_t n_block, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  __shared__ uint32_t wcnt[kWaves][DYN_INGEST_MAX_BINS];
-  scatter_tile(blockIdx.x, keys_in, in_in, out_in, keys_out, in_out, out_out, n, shift, bits, scanned, n_block, wcnt);
 }
 
 // cell_off[c] = number of requests with key < c, read off the sorted keys
-__device__ __forceinline__ void offsets_at(int64_t i, const uint32_t* keys, int64_t n, int64_t cells, int64_t* cell_off) {
-  if (i > n) return;
-  const int64_t prev = i == 0 ? -1 : (int64_t)keys[i - 1];
-  int64_t cur = i == n ? cells : (int64_t)keys[i];
-  if (cur > cells) cur = cells;
+__device__ __forceinline__ void offsets_at(int64_t i, int64_t prev, int64_t cur, int64_t n, int64_t cells, int64_t* cell_off) {
+  if (i == n || cur > cells) cur = cells;
   for (int64_t c = prev + 1; c <= cur; ++c) cell_off[c] = i;
 }
 
-__global__ __launch_bounds__(256) void offsets_kernel(const uint32_t* __restrict__ keys, int64_t n, int64_t cells,
-                                                      int64_t* __restrict__ cell_off, const uint32_t* __restrict__ order) {
-  if (!sort_route(order)) return;
-  offsets_at((int64_t)blockIdx.x * blockDim.x + threadIdx.x, keys, n, cells, cell_off);
-}
-
-// The whole general sort in one launch: a grid that the device holds at once walks the tiles of every phase, with a
-// grid-wide barrier between the phases.  A trace in window order costs this one launch that returns at its first
-// instruction (eleven gated launches otherwise).  The barrier: an arrival counter in the workspace header, zeroed with
-// the header; barrier number k is passed when the counter reaches k * blocks.  The grid is a fraction of what the
-// device holds at once (occupancy query), so every block is running when the first one waits; if other work keeps
-// part of the device for seconds the wait is given up (every block leaves, DYN_WS_SORT_ABANDONED is raised).
-// A barrier costs a write-back of the block's cache level per block, which is why the grid is kept small.
+// ---- the general sort ----------------------------------------------------------------------
+// All radix passes and the offsets in one launch, with barriers between the phases that all its blocks pass: a trace in
+// window order costs this one launch, which returns at its first instruction.  Every block owns a contiguous run of tiles.  A
+// pass is: digit counts of every block's run -> barrier -> one wave per digit turns the blocks' counts into
+// inclusive sums -> barrier -> every block moves its run, a tile at a time -> barrier.
+//
+// What bounds it: bytes through the last-level cache (a request is read and written once a pass, its key once more)
+// and the barriers.  Measured at 6 M requests and 51 840 cells (two passes of 8 bits):
+// - A cache write-back or invalidation is done once per block, by the thread that waits, not by every wave of it: an acquiring
+//   fence by all 8 waves of 256 blocks costs 17 us a barrier, by one wave 2.  Data for other blocks is stored
+//   through the L2 (put), so the write-back finds it clean; scattered runs cost the same either way.
+// - A tile is ordered by digit in LDS before it is written, so that a digit's requests leave as one run: 8 M single words
+//   scattered cost 93 us, runs of 16 words 13 us, of 32 words 9.5 us.  So the tile is 8192 requests: 32 to a digit.
+// - All loads of a thread's eight requests are in flight together, also where only keys are counted or compared.
+// 523 us with separate scan phases, all waves fencing and single words scattered; 225 us so.
+//
+// The barrier: an arrival counter in the workspace header, zeroed with the header; barrier number k is passed when
+// the counter reaches k * blocks.  Only blocks that run take part (join_team), so other work on the device can
+// delay a barrier but not stop it; if it takes seconds all the same, the wait is given up (every block leaves,
+// DYN_WS_SORT_ABANDONED is raised).
 struct RadixArgs {
   const uint32_t* order;
-  uint32_t* barrier; uint32_t* status;
+  uint32_t* barrier; uint32_t* join; uint32_t* members; uint32_t* status;
   uint32_t* key_a; uint32_t* key_b;
   const int32_t* in_tok; const int32_t* out_tok;
   int32_t* in_sorted; int32_t* out_sorted; int32_t* in_tmp; int32_t* out_tmp;
-  uint32_t* block_hist; int64_t n_block;
+  uint32_t* hist;                                // [digit][block]
   int64_t n, cells; int64_t* cell_off;
   int32_t passes, bits;
 };
 
-constexpr int kRadixGridShare = 4;               // the grid is this fraction of what the device holds at once
 constexpr uint32_t kBarrierSpins = 1u << 22;     // x about a microsecond per look: seconds
+// The blocks that sort together: those that run when the first one has waited for them.
+struct RadixTeam { int blocks, block; };
+constexpr uint32_t kTeamClosed = 1u << 31;
+constexpr uint32_t kTeamSpins = 256;             // x a third of a microsecond: the leader's wait for blocks that do not run yet
+constexpr int kRadixWaves = 16;
+constexpr int kRadixThreads = kRadixWaves * DYN_WAVE;
+constexpr int kRadixItems = 8;                   // requests per thread and tile
+constexpr int kRadixTile = kRadixThreads * kRadixItems;
+constexpr int kRadixOwn = DYN_INGEST_MAX_BINS / kRadixThreads;   // digits a thread owns in the scans
+static_assert(kRadixTile * sizeof(uint32_t) == kRadixWaves * DYN_INGEST_MAX_BINS * sizeof(uint16_t), "the wave counters become the second move buffer");
 
-// false: given up (block-uniform).  All writes of the block before the call are visible to every block after it.
-// The waiting thread looks at the counter with relaxed loads (acquiring loads would invalidate caches all over the
-// device for as long as anyone waits) and acquires once at the end.
+// a store that other blocks read after the next barrier
+template <typename T>
+__device__ __forceinline__ void put(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// false: given up (block-uniform).  All writes of the block before the call are visible to every block after it: every
+// wave waits for its own stores, and the waiting thread releases before it arrives and acquires after it has seen
+// the others (the block's other waves share its caches and follow it through the block barrier).
 __device__ __forceinline__ bool grid_barrier(uint32_t* counter, uint32_t target, uint32_t* s_flag) {
-  __syncthreads();                                // the block's stores have been issued and acknowledged
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -372,66 +202,320 @@ __device__ __forceinline__ bool grid_barrier(uint32_t* counter, uint32_t target,
     bool ok = true;
     while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
       if (++spins > kBarrierSpins) { ok = false; break; }
-      __builtin_amdgcn_s_sleep(20);
+      __builtin_amdgcn_s_sleep(8);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     *s_flag = ok ? 1u : 0u;
   }
   __syncthreads();
-  const bool ok = *s_flag != 0u;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // later reads see the other blocks' writes
-  return ok;
+  return *s_flag != 0u;
 }
 
-__global__ __launch_bounds__(kWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void radix_route_kernel(RadixArgs a) {
+// LDS of a block: the wave counters of a tile are done with when its requests' places are known, and are then the
+// second buffer of the move.
+struct RadixLds {
+  uint32_t move[kRadixTile];
+  union {
+    uint16_t wcnt[kRadixWaves][DYN_INGEST_MAX_BINS];
+    uint32_t cnt[4][DYN_INGEST_MAX_BINS];        // digit counts of the block's run, four copies
+    uint32_t move2[kRadixTile];
+  };
+  uint32_t to[DYN_INGEST_MAX_BINS];              // output position of a digit's first request of the tile, less its place in the tile
+  uint32_t wave_sum[kRadixWaves];
+  uint32_t flag;
+};
+
+// Which of the sorting blocks this one is, and how many there are ({0, 0}: it came too late, or the wait was given up).  The
+// first block to arrive waits a moment for the rest of the grid and then closes the team; a block that arrives later leaves.
+// So every block that the barriers wait for is running, whatever else the device is busy with.
+__device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members, uint32_t* status, RadixLds& s) {
+  if (threadIdx.x == 0) {
+    const uint32_t ticket = atomicAdd(join, 1u);
+    uint32_t n = 0;
+    if (ticket == 0) {
+      for (uint32_t spins = 0; spins < kTeamSpins && __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x; ++spins) __builtin_amdgcn_s_sleep(4);
+      n = atomicOr(join, kTeamClosed);
+      put(members, n);
+    } else if (ticket < kTeamClosed) {
+      for (uint32_t spins = 0; n == 0 && spins < kBarrierSpins; ++spins) {
+        n = __hip_atomic_load(members, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (n == 0) __builtin_amdgcn_s_sleep(4);
+      }
+      if (n == 0) atomicOr(status, DYN_WS_SORT_ABANDONED);
+    }
+    s.flag = n;
+    s.wave_sum[0] = ticket;
+  }
+  __syncthreads();
+  const RadixTeam m = {__builtin_amdgcn_readfirstlane((int)s.flag), __builtin_amdgcn_readfirstlane((int)s.wave_sum[0])};
+  __syncthreads();
+  return m;
+}
+
+// Digit counts of the keys [beg, end) -> hist[digit][block].  In runs of equal digits (the keys of a later pass) a wave
+// adds once for all its lanes; else lanes add to one of four copies, which shortens the queues of equal digits.
+__device__ __forceinline__ void radix_count(const uint32_t* keys, int64_t beg, int64_t end, int shift, int bits, uint32_t* hist, RadixTeam m, RadixLds& s) {
+  const int nbins = 1 << bits;
+  const uint32_t mask = (uint32_t)nbins - 1u;
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  for (int b = threadIdx.x; b < 4 * DYN_INGEST_MAX_BINS; b += kRadixThreads) (&s.cnt[0][0])[b] = 0;
+  __syncthreads();
+  uint32_t* mine = s.cnt[lane & 3];
+  for (int64_t at = beg; at < end; at += kRadixTile) {
+    uint32_t key[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      key[r] = keys[i < end ? i : end - 1];
+    }
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+      const bool in = at + r * kRadixThreads + threadIdx.x < end;
+      const uint32_t d = (key[r] >> shift) & mask;
+      const uint64_t there = __ballot(in);
+      if (there == 0) continue;
+      const uint32_t first = __builtin_amdgcn_readfirstlane(d);   // lanes that are in are a prefix of the wave
+      if (__ballot(in && d != first) == 0) {
+        if (lane == 0) atomicAdd(&mine[first], (uint32_t)__popcll(there));
+      } else if (in) {
+        atomicAdd(&mine[d], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < nbins; b += kRadixThreads)
+    put(&hist[(size_t)b * m.blocks + m.block], s.cnt[0][b] + s.cnt[1][b] + s.cnt[2][b] + s.cnt[3][b]);
+}
+
+// hist[d][0 .. blocks) -> inclusive sums, one wave per digit
+__device__ __forceinline__ void radix_scan(uint32_t* hist, int bits, RadixTeam m) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const int n = m.blocks;
+  for (int d = (int)(threadIdx.x / DYN_WAVE) * n + m.block; d < (1 << bits); d += kRadixWaves * n) {
+    uint32_t* row = hist + (size_t)d * n;
+    uint32_t carry = 0;
+    for (int base = 0; base < n; base += 4 * DYN_WAVE) {
+      uint32_t v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = row[min(base + q * DYN_WAVE + lane, n - 1)];   // past the end: not written
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int k = 1; k < DYN_WAVE; k <<= 1) {
+          const uint32_t up = __shfl_up(v[q], k, DYN_WAVE);
+          if (lane >= k) v[q] += up;
+        }
+        v[q] += carry;
+        carry = __shfl(v[q], DYN_WAVE - 1, DYN_WAVE);
+        if (base + q * DYN_WAVE + lane < n) put(&row[base + q * DYN_WAVE + lane], v[q]);
+      }
+    }
+  }
+}
+
+// exclusive sum over the block's threads
+__device__ __forceinline__ uint32_t radix_block_scan(uint32_t v, RadixLds& s) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t incl = v;
+#pragma unroll
+  for (int k = 1; k < DYN_WAVE; k <<= 1) {
+    const uint32_t up = __shfl_up(incl, k, DYN_WAVE);
+    if (lane >= k) incl += up;
+  }
+  if (lane == DYN_WAVE - 1) s.wave_sum[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += s.wave_sum[w];
+  __syncthreads();
+  return before + incl - v;
+}
+
+// Stable move of one tile of `count` requests (FULL: kRadixTile).  What is missing to kRadixTile takes part as requests of
+// the last digit, behind all others, and is not written.  Every wave owns a contiguous run of rows of 64 requests and
+// walks them in order; a request's rank among the row's requests with its digit comes from wave ballots.  `next`: output
+// position of the next request of each digit that the thread owns (threadIdx.x * kRadixOwn ...), moved on.
+template <bool FULL>
+__device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_t* in_in, const int32_t* out_in, uint32_t* keys_out,
+                                           int32_t* in_out, int32_t* out_out, int count, int shift, int bits, uint32_t* next, RadixLds& s) {
+  const int nbins = 1 << bits;
+  const uint32_t mask = (uint32_t)nbins - 1u;
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  const int at = wave * (kRadixItems * DYN_WAVE) + lane;
+  uint32_t key[kRadixItems], pos[kRadixItems];
+  int32_t vin[kRadixItems], vout[kRadixItems];
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = FULL ? at + r * DYN_WAVE : min(at + r * DYN_WAVE, count - 1);
+    key[r] = keys_in[i];
+    vin[r] = in_in[i];
+    vout[r] = out_in[i];
+    if (!FULL && at + r * DYN_WAVE >= count) key[r] = ~0u;
+  }
+#pragma unroll
+  for (int q = 0; q < kRadixItems; ++q) s.move2[q * kRadixThreads + threadIdx.x] = 0;   // the wave counters
+  __syncthreads();
+  uint16_t* my = s.wcnt[wave];
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const uint32_t d = (key[r] >> shift) & mask;
+    uint64_t peers = ~0ull;
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (d >> b) & 1u;
+      const uint64_t bal = __ballot(bit);
+      peers &= bit ? bal : ~bal;
+    }
+    const uint32_t before = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull)), group = (uint32_t)__popcll(peers);
+    pos[r] = my[d] + before;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (before == group - 1) my[d] = (uint16_t)(pos[r] + 1);   // one lane per digit advances it
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  // per digit: where its requests start in the tile, and where each wave's among them do
+  uint32_t total[kRadixOwn], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kRadixOwn; ++q) {
+    total[q] = 0;
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) total[q] += s.wcnt[w][threadIdx.x * kRadixOwn + q];
+    sum += total[q];
+  }
+  uint32_t start = radix_block_scan(sum, s);
+#pragma unroll
+  for (int q = 0; q < kRadixOwn; ++q) {
+    const int d = threadIdx.x * kRadixOwn + q;
+    s.to[d] = next[q] - start;
+    next[q] += total[q];
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) {
+      const uint32_t c = s.wcnt[w][d];
+      s.wcnt[w][d] = (uint16_t)start;
+      start += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) pos[r] += my[(key[r] >> shift) & mask];
+  __syncthreads();                               // the wave counters are done with
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    s.move[pos[r]] = key[r];
+    s.move2[pos[r]] = (uint32_t)vin[r];
+  }
+  __syncthreads();
+  uint32_t dst[kRadixItems];
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = r * kRadixThreads + threadIdx.x;
+    const uint32_t k = s.move[i];
+    dst[r] = s.to[(k >> shift) & mask] + (uint32_t)i;
+    if (FULL || i < count) {
+      put(keys_out + dst[r], k);
+      put(in_out + dst[r], (int32_t)s.move2[i]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) s.move[pos[r]] = (uint32_t)vout[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRadixItems; ++r) {
+    const int i = r * kRadixThreads + threadIdx.x;
+    if (FULL || i < count) put(out_out + dst[r], (int32_t)s.move[i]);
+  }
+}
+
+// Stable move of the requests [beg, end).
+__device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_t* in_in, const int32_t* out_in, uint32_t* keys_out,
+                                           int32_t* in_out, int32_t* out_out, int64_t beg, int64_t end, int shift, int bits,
+                                           const uint32_t* hist, RadixTeam m, RadixLds& s) {
+  const int nbins = 1 << bits;
+  uint32_t next[kRadixOwn];                             // output position of the next request of each owned digit
+  {
+    uint32_t total[kRadixOwn], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kRadixOwn; ++q) {
+      const int d = threadIdx.x * kRadixOwn + q;
+      const uint32_t* row = hist + (size_t)d * m.blocks;
+      total[q] = d < nbins ? row[m.blocks - 1] : 0u;
+      next[q] = d < nbins && m.block > 0 ? row[m.block - 1] : 0u;
+      sum += total[q];
+    }
+    uint32_t base = radix_block_scan(sum, s);
+#pragma unroll
+    for (int q = 0; q < kRadixOwn; ++q) {
+      next[q] += base;
+      base += total[q];
+    }
+  }
+  int64_t at = beg;
+  for (; at + kRadixTile <= end; at += kRadixTile)
+    radix_tile<true>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, kRadixTile, shift, bits, next, s);
+  if (at < end) radix_tile<false>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, (int)(end - at), shift, bits, next, s);
+}
+
+__global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs a) {
   if (!sort_route(a.order)) return;              // the same word for every block: all leave, or none
-  __shared__ uint32_t wcnt[kWaves][DYN_INGEST_MAX_BINS];
-  __shared__ uint32_t s_wave[4];
-  __shared__ uint32_t s_flag;
+  __shared__ RadixLds s;
+  const RadixTeam m = join_team(a.join, a.members, a.status, s);
+  if (m.blocks == 0) return;
   uint32_t passed = 0;                           // barriers behind this block
   auto sync = [&]() {
     ++passed;
-    return grid_barrier(a.barrier, passed * gridDim.x, &s_flag);
+    const bool ok = grid_barrier(a.barrier, passed * (uint32_t)m.blocks, &s.flag);
+    if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
+    return ok;
   };
-  auto give_up = [&]() {
-    if (threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
-  };
+  const int n_tile = (int)((a.n + kRadixTile - 1) / kRadixTile);
+  const int tiles = n_tile / m.blocks, more = n_tile % m.blocks;   // the first `more` blocks take one tile more
+  const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kRadixTile;
+  const int64_t end = std::min<int64_t>(a.n, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
   const uint32_t* k_src = a.key_a;
   uint32_t* k_dst = a.key_b;
   const int32_t *i_src = a.in_tok, *o_src = a.out_tok;
-  const uint32_t* sorted_keys = a.key_a;
-  uint32_t* partial = a.block_hist + (size_t)DYN_INGEST_MAX_BINS * a.n_block;
   for (int p = 0; p < a.passes; ++p) {
     const bool to_final = ((a.passes - 1 - p) % 2) == 0;   // ping-pong so that the last pass lands in the caller's arrays
     int32_t* i_dst = to_final ? a.in_sorted : a.in_tmp;
     int32_t* o_dst = to_final ? a.out_sorted : a.out_tmp;
     const int shift = p * a.bits;
-    const int64_t count = (int64_t)(1 << a.bits) * a.n_block;
-    const int64_t n_part = (count + kScanChunk - 1) / kScanChunk;
-    for (int64_t t = blockIdx.x; t < a.n_block; t += gridDim.x) {
-      hist_tile(t, k_src, a.n, shift, a.bits, a.block_hist, a.n_block, wcnt[0]);
-      __syncthreads();
-    }
-    if (!sync()) { give_up(); return; }
-    for (int64_t c = blockIdx.x; c < n_part; c += gridDim.x) scan_reduce_chunk(c, a.block_hist, count, partial, s_wave);
-    if (!sync()) { give_up(); return; }
-    if (blockIdx.x == 0) scan_partials_all(partial, n_part, s_wave);
-    if (!sync()) { give_up(); return; }
-    for (int64_t c = blockIdx.x; c < n_part; c += gridDim.x) scan_apply_chunk(c, a.block_hist, count, partial, s_wave);
-    if (!sync()) { give_up(); return; }
-    for (int64_t t = blockIdx.x; t < a.n_block; t += gridDim.x) {
-      scatter_tile(t, k_src, i_src, o_src, k_dst, i_dst, o_dst, a.n, shift, a.bits, a.block_hist, a.n_block, wcnt);
-      __syncthreads();
-    }
-    if (!sync()) { give_up(); return; }
-    sorted_keys = k_dst;
+    radix_count(k_src, beg, end, shift, a.bits, a.hist, m, s);
+    if (!sync()) return;
+    radix_scan(a.hist, a.bits, m);
+    if (!sync()) return;
+    radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, a.bits, a.hist, m, s);
+    if (!sync()) return;
     i_src = i_dst;
     o_src = o_dst;
-    uint32_t* old_src = const_cast<uint32_t*>(k_src);
+    uint32_t* old_src = const_cast<uint32_t*>(k_src);      // both key buffers live in the workspace
     k_src = k_dst;
     k_dst = old_src;
   }
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= a.n; i += (int64_t)gridDim.x * blockDim.x)
-    offsets_at(i, sorted_keys, a.n, a.cells, a.cell_off);
+  if (a.n == 0)
+    for (int64_t c = threadIdx.x; c <= a.cells; c += kRadixThreads) a.cell_off[c] = 0;
+  // the offsets: a block goes over its run of the sorted keys, every key beside the one before it
+  for (int64_t at = beg; at < end; at += kRadixTile) {
+    uint32_t key[kRadixItems], left[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
+      key[r] = k_src[i];
+      left[r] = k_src[i > 0 ? i - 1 : 0];
+    }
+#pragma unroll 1
+    for (int r = 0; r < kRadixItems; ++r) {
+      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      uint32_t k = key[0], l = left[0];
+#pragma unroll
+      for (int q = 1; q < kRadixItems; ++q) {
+        k = r == q ? key[q] : k;
+        l = r == q ? left[q] : l;
+      }
+      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n, a.cells, a.cell_off);
+      if (i == a.n - 1) offsets_at(a.n, k, a.cells, a.n, a.cells, a.cell_off);
+    }
+  }
 }
 
 // ---- a trace in window order ----------------------------------------------------------------
@@ -593,66 +677,28 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   }
   const int passes = a.key_bits <= 0 ? 1 : (a.key_bits + 9) / 10;
   const int bits = a.key_bits <= 0 ? 1 : (a.key_bits + passes - 1) / passes;
-  {
-    // one launch of a resident grid when the device tells what it holds; else the launches below
-    // what the device holds at once, asked once per device (0: not asked yet, -1: unknown: the separate kernels below)
-    static std::atomic<int> resident[64];
-    int dev = 0;
-    int fit = 0;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
-      fit = resident[dev].load(std::memory_order_relaxed);
-      if (fit == 0) {
-        int n_cu = 0, per_cu = 0;
-        fit = -1;
-        if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, radix_route_kernel, kWaves * DYN_WAVE, 0) == hipSuccess && per_cu > 0)
-          fit = std::max(1, per_cu * n_cu / kRadixGridShare);
-        (void)hipGetLastError();
-        resident[dev].store(fit, std::memory_order_relaxed);
-      }
-    }
-    if (fit > 0) {
-      RadixArgs r;
-      r.order = a.unsorted; r.barrier = a.unsorted + (DYN_WS_HEADER_BARRIER_WORD - DYN_WS_HEADER_ORDER_WORD); r.status = a.status;
-      r.key_a = a.key_a; r.key_b = a.key_b; r.in_tok = a.in_tok; r.out_tok = a.out_tok;
-      r.in_sorted = a.in_sorted; r.out_sorted = a.out_sorted; r.in_tmp = a.in_tmp; r.out_tmp = a.out_tmp;
-      r.block_hist = a.block_hist; r.n_block = a.n_block; r.n = n; r.cells = cells; r.cell_off = a.cell_off;
-      r.passes = passes; r.bits = bits;
-      const int64_t useful = std::max<int64_t>(a.n_block, 1);
-      const unsigned blocks = (unsigned)std::min<int64_t>((int64_t)fit, useful);
-      hipLaunchKernelGGL(radix_route_kernel, dim3(blocks), dim3(kWaves * DYN_WAVE), 0, s, r);
-      return hipGetLastError();
+  // one block per compute unit (asked once per device)
+  static std::atomic<int> units[64];
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
+    n_cu = units[dev].load(std::memory_order_relaxed);
+    if (n_cu == 0) {
+      if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1) n_cu = 1;
+      units[dev].store(n_cu, std::memory_order_relaxed);
     }
   }
-  // ping-pong so that the last pass lands in the caller's arrays
-  const uint32_t* k_src = a.key_a;
-  uint32_t* k_dst = a.key_b;
-  const int32_t *i_src = a.in_tok, *o_src = a.out_tok;
-  const uint32_t* sorted_keys = a.key_a;
-  for (int p = 0; p < passes; ++p) {
-    const bool to_final = ((passes - 1 - p) % 2) == 0;
-    int32_t* i_dst = to_final ? a.in_sorted : a.in_tmp;
-    int32_t* o_dst = to_final ? a.out_sorted : a.out_tmp;
-    const int shift = p * bits;
-    const int64_t count = (int64_t)(1 << bits) * a.n_block;
-    const int64_t n_part = (count + kScanChunk - 1) / kScanChunk;
-    uint32_t* partial = a.block_hist + (size_t)DYN_INGEST_MAX_BINS * a.n_block;
-    hipLaunchKernelGGL(hist_kernel, dim3((unsigned)a.n_block), dim3(kWaves * DYN_WAVE), 0, s, k_src, n, shift,
-                       bits, a.block_hist, a.n_block, a.unsorted);
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)n_part), dim3(256), 0, s, a.block_hist, count, partial, a.unsorted);
-    hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(256), 0, s, partial, n_part, a.unsorted);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)n_part), dim3(256), 0, s, a.block_hist, count, partial, a.unsorted);
-    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)a.n_block), dim3(kWaves * DYN_WAVE), 0, s, k_src, i_src,
-                       o_src, k_dst, i_dst, o_dst, n, shift, bits, a.block_hist, a.n_block, a.unsorted);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    sorted_keys = k_dst;
-    i_src = i_dst;
-    o_src = o_dst;
-    uint32_t* old_src = const_cast<uint32_t*>(k_src);   // both key buffers live in the workspace
-    k_src = k_dst;
-    k_dst = old_src;
-  }
-  hipLaunchKernelGGL(offsets_kernel, dim3((unsigned)((n + 1 + 255) / 256)), dim3(256), 0, s, sorted_keys, n, cells,
-                     a.cell_off, a.unsorted);
+  (void)hipGetLastError();
+  RadixArgs r;
+  r.order = a.unsorted; r.barrier = a.unsorted + (DYN_WS_HEADER_BARRIER_WORD - DYN_WS_HEADER_ORDER_WORD); r.status = a.status;
+  r.join = r.barrier + 1; r.members = r.barrier + 2;
+  r.key_a = a.key_a; r.key_b = a.key_b; r.in_tok = a.in_tok; r.out_tok = a.out_tok;
+  r.in_sorted = a.in_sorted; r.out_sorted = a.out_sorted; r.in_tmp = a.in_tmp; r.out_tmp = a.out_tmp;
+  r.hist = a.block_hist; r.n = n; r.cells = cells; r.cell_off = a.cell_off;
+  r.passes = passes; r.bits = bits;
+  // a block for every tile, as far as they fit the device and the digit counts (a word per digit and block) the workspace
+  const int64_t room = ((int64_t)DYN_INGEST_MAX_BINS * a.n_block) >> bits;
+  const int64_t n_tile = (n + kRadixTile - 1) / kRadixTile;
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({(int64_t)n_cu, n_tile, room}));
+  hipLaunchKernelGGL(radix_route_kernel, dim3((unsigned)blocks), dim3(kRadixThreads), 0, s, r);
   return hipGetLastError();
 }

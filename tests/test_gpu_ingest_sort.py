@@ -1,0 +1,73 @@
+"""The orders a request log can come in, each through the route it takes, at the sizes where tiles and runs end."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+TILE = 8192          # requests a block of the general sort moves at a time
+
+
+@pytest.fixture(scope="module")
+def dyn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2408_00741_amd as d
+    return d
+
+
+def _edges(n_in, n_out):
+    return {"in_edge": np.linspace(100, 8000, n_in - 1).astype(np.int32)[None, :], "out_edge": np.linspace(90, 7900, n_out - 1).astype(np.int32)[None, :]}
+
+
+def _log(seed, n, horizon):
+    rng = np.random.default_rng(seed)
+    return {"t_s": rng.uniform(0, horizon, n), "in_tok": rng.integers(1, 8193, n).astype(np.int32),
+            "out_tok": rng.integers(1, 8193, n).astype(np.int32), "model": np.zeros(n, np.int32)}
+
+
+def _call(dyn, tr, edges, n_window, window_s, **kw):
+    d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
+    return dyn.dyn_trace_ingest(*d, None, edges, n_window, window_s, **kw)
+
+
+def _check(got, tr, edges, n_window, window_s):
+    want = oracle.ingest(tr, edges, n_window, window_s)
+    np.testing.assert_array_equal(got[2].cpu().numpy(), want["cell_off"])
+    np.testing.assert_array_equal(got[0].cpu().numpy(), want["in_tok"])
+    np.testing.assert_array_equal(got[1].cpu().numpy(), want["out_tok"])
+
+
+# one, two and three passes; digits of 1 to 10 bits; less than a wave, a tile and one more, many tiles a block
+@pytest.mark.parametrize("n,n_window,n_in,n_out", [(1, 1, 1, 1), (2, 2, 1, 1), (63, 5, 2, 2), (TILE - 1, 9, 5, 5), (TILE, 40, 5, 5), (TILE + 1, 41, 5, 5),
+                                                   (2 * TILE + 65, 1000, 5, 5), (100_000, 3, 40, 30), (300_001, 2000, 16, 20), (2_500_000, 1440, 5, 5)])
+def test_general_sort_is_stable(dyn, n, n_window, n_in, n_out):
+    edges = _edges(n_in, n_out)
+    tr = _log(n, n, n_window * 10.0)
+    got = _call(dyn, tr, edges, n_window, 10.0)
+    assert dyn.dyn_workspace_status(got[3]) == 0
+    _check(got, tr, edges, n_window, 10.0)
+
+
+def test_no_requests_and_more_classes_than_the_window_route_counts(dyn):
+    edges = _edges(40, 30)
+    got = _call(dyn, _log(0, 0, 1.0), edges, 3, 10.0)
+    assert got[2].cpu().numpy().tolist() == [0] * (3 * 1200 + 1)
+
+
+def test_sorts_on_eight_streams_at_once(dyn):
+    """More sorts than the device holds whole: every one forms its team from the blocks that run."""
+    edges = _edges(5, 5)
+    logs = [_log(q, 400_000 + q, 3600.0) for q in range(8)]
+    streams = [torch.cuda.Stream() for _ in logs]
+    got = []
+    for tr, st in zip(logs, streams):
+        with torch.cuda.stream(st):
+            got.append(_call(dyn, tr, edges, 60, 60.0))
+    torch.cuda.synchronize()
+    for tr, g in zip(logs, got):
+        assert dyn.dyn_workspace_status(g[3]) == 0
+        _check(g, tr, edges, 60, 60.0)
