@@ -20,12 +20,6 @@
 
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kRows = 32;                              // rows of 64 requests per wave
-constexpr int kTile = kWaves * kRows * DYN_WAVE;       // 8192 requests per block
-
-constexpr int kKeyRows = 4;                            // requests per thread of the key kernel (rows of 256)
-
 // Window of a timestamp: floor(t / window_s), the quotient formed from RN(1 / window_s) by div_by (correctly rounded
 // for timestamps whose quotient is a normal number; a handful of multiply-adds instead of a division).  Quotients that are
 // not finite, and tiny ones (below 2^-900, where a residual could underflow), take the IEEE division; clamped, out-of-range flagged.
@@ -38,73 +32,93 @@ __device__ __forceinline__ double window_of(double t, double window_s, double r_
   return wq;
 }
 
-// A block takes kKeyRows rows of 256 consecutive requests (all loads of a thread in flight together); the class
-// edges sit in LDS when they fit (lds_edges != 0).
-__global__ __launch_bounds__(256) void key_kernel(IngestArgs a, double r_window, int lds_edges) {
-  extern __shared__ int32_t s_edge[];                  // [n_model][n_in_bin - 1] then [n_model][n_out_bin - 1]
+// The classes' edges in LDS where they fit (`room` ints), else where they are.  A barrier is due before they are read.
+struct ClassEdges { const int32_t* in; const int32_t* out; };
+__device__ __forceinline__ ClassEdges stage_edges(const IngestArgs& a, int32_t* lds, int room) {
+  const int n_in = a.n_model * (a.n_in_bin - 1), n_out = a.n_model * (a.n_out_bin - 1);
+  if (n_in + n_out > room) return {a.d_in_edge, a.d_out_edge};
+  for (int q = threadIdx.x; q < n_in; q += blockDim.x) lds[q] = a.d_in_edge[q];
+  for (int q = threadIdx.x; q < n_out; q += blockDim.x) lds[n_in + q] = a.d_out_edge[q];
+  return {lds, lds + n_in};
+}
+
+// Classes of N requests (input and output tokens, model; a bad model index is clamped and flagged).  One model: an edge is
+// read once for all of them.
+template <int N>
+__device__ __forceinline__ void classes_of(const IngestArgs& a, const ClassEdges& e, const int32_t* x, const int32_t* y, const int32_t* mdl, uint32_t* cls, uint32_t* bad) {
   const int n_ie = a.n_in_bin - 1, n_oe = a.n_out_bin - 1;
-  const int32_t* in_edge = a.d_in_edge;
-  const int32_t* out_edge = a.d_out_edge;
-  if (lds_edges) {
-    for (int q = threadIdx.x; q < a.n_model * n_ie; q += blockDim.x) s_edge[q] = a.d_in_edge[q];
-    for (int q = threadIdx.x; q < a.n_model * n_oe; q += blockDim.x) s_edge[a.n_model * n_ie + q] = a.d_out_edge[q];
-    __syncthreads();
-    in_edge = s_edge;
-    out_edge = s_edge + a.n_model * n_ie;
-  }
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
-  const int64_t base = (int64_t)blockIdx.x * (kKeyRows * 256) + threadIdx.x;
-  double t[kKeyRows], tp[kKeyRows];
-  int32_t x[kKeyRows], y[kKeyRows], md[kKeyRows];
+  int m[N], bi[N], bo[N];
 #pragma unroll
-  for (int r = 0; r < kKeyRows; ++r) {
-    const int64_t i = base + r * 256;
-    const bool in = i < a.n_req;
-    t[r] = in ? a.t_s[i] : 0.0;
-    tp[r] = (in && lane == 0 && i > 0) ? a.t_s[i - 1] : 0.0;   // the request before a wave's first
-    x[r] = in ? a.in_tok[i] : 0;
-    y[r] = in ? a.out_tok[i] : 0;
-    md[r] = (in && a.model) ? a.model[i] : 0;
+  for (int r = 0; r < N; ++r) {
+    m[r] = 0; bi[r] = 0; bo[r] = 0;
+    if (a.model) {
+      m[r] = mdl[r];
+      if (m[r] < 0 || m[r] >= a.n_model) { *bad = DYN_WS_BAD_REQUEST; m[r] = 0; }
+    }
   }
-  const int64_t G = (int64_t)a.n_model * a.n_in_bin * a.n_out_bin;
-  uint32_t bad = 0;
+  if (a.model) {
+    for (int q = 0; q < n_ie; ++q) {
+#pragma unroll
+      for (int r = 0; r < N; ++r) bi[r] += x[r] >= e.in[m[r] * n_ie + q] ? 1 : 0;
+    }
+    for (int q = 0; q < n_oe; ++q) {
+#pragma unroll
+      for (int r = 0; r < N; ++r) bo[r] += y[r] >= e.out[m[r] * n_oe + q] ? 1 : 0;
+    }
+  } else {
+    for (int q = 0; q < n_ie; ++q) {
+      const int32_t edge = e.in[q];
+#pragma unroll
+      for (int r = 0; r < N; ++r) bi[r] += x[r] >= edge ? 1 : 0;
+    }
+    for (int q = 0; q < n_oe; ++q) {
+      const int32_t edge = e.out[q];
+#pragma unroll
+      for (int r = 0; r < N; ++r) bo[r] += y[r] >= edge ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < N; ++r) cls[r] = (uint32_t)((m[r] * a.n_in_bin + bi[r]) * a.n_out_bin + bo[r]);
+}
+
+// Is the trace in window order, and where does every window start?  Only the timestamps are read (8 bytes a request): the
+// routes compute classes from the tokens that they move anyway.  A wave takes kOrderRows rows of 64 consecutive
+// requests, all loads in flight together.
+constexpr int kOrderRows = 8;
+__global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_window) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  if (a.n_req == 0) {
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w <= a.n_window; w += (int64_t)gridDim.x * blockDim.x) a.win_off[w] = 0;
+    return;
+  }
+  const int64_t base = ((int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane)) * kOrderRows;   // the wave's first request
+  if (base >= a.n_req) return;
+  double t[kOrderRows];
+#pragma unroll
+  for (int r = 0; r < kOrderRows; ++r) t[r] = a.t_s[std::min<int64_t>(base + r * DYN_WAVE + lane, a.n_req - 1)];
+  uint32_t bad = 0, ignore = 0;
+  // the window of the request before the wave's first
+  double left = base > 0 ? window_of(a.t_s[base - 1], a.window_s, r_window, a.n_window, &ignore) : -1.0;
   bool dis = false;
 #pragma unroll
-  for (int r = 0; r < kKeyRows; ++r) {
-    const int64_t i = base + r * 256;
-    const bool in = i < a.n_req;                       // the lanes that are in are a prefix of the wave: lane - 1 is among them
-    uint32_t bad_r = 0;
-    const double wq = window_of(t[r], a.window_s, r_window, a.n_window, &bad_r);
-    int32_t mdl = md[r];
-    if (mdl < 0 || mdl >= a.n_model) { bad_r = DYN_WS_BAD_REQUEST; mdl = 0; }
-    const int32_t* ie = in_edge + (size_t)mdl * n_ie;
-    const int32_t* oe = out_edge + (size_t)mdl * n_oe;
-    int bi = 0, bo = 0;
-    for (int e = 0; e < n_ie; ++e) bi += (x[r] >= ie[e]) ? 1 : 0;
-    for (int e = 0; e < n_oe; ++e) bo += (y[r] >= oe[e]) ? 1 : 0;
-    const int64_t g = ((int64_t)mdl * a.n_in_bin + bi) * a.n_out_bin + bo;
-    // Window order: compare with the request before (the neighbouring lane; the first lane of a wave recomputes it).
-    // Where the window changes the boundaries are written: in a trace in window order win_off[w] = number of
-    // requests in windows before w (the values are not used otherwise).
+  for (int r = 0; r < kOrderRows; ++r) {
+    const int64_t i = base + r * DYN_WAVE + lane;
+    const bool in = i < a.n_req;                       // past the end: the last request again
+    const double wq = window_of(t[r], a.window_s, r_window, a.n_window, &bad);
+    // Window order: compare with the request before.  Where the window changes the boundaries are written: in a trace in
+    // window order win_off[w] = number of requests in windows before w (the values are not used otherwise).
     double wp = __shfl_up(wq, 1, DYN_WAVE);
-    if (lane == 0) {
-      uint32_t ignore = 0;
-      wp = window_of(tp[r], a.window_s, r_window, a.n_window, &ignore);
-    }
-    if (i == 0) wp = -1.0;
+    if (lane == 0) wp = left;
+    left = __shfl(wq, DYN_WAVE - 1, DYN_WAVE);
     // The boundaries only matter to the window route: a wave that sees a request out of order, or finds the flag
     // raised already, writes none (on a shuffled trace every request would otherwise fill hundreds of them).
     const bool back = in && wp > wq;
-    const bool fill = __ballot(back) == 0 && __hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
-    if (in) {
-      a.key_a[i] = (uint32_t)((int64_t)wq * G + g);
-      bad |= bad_r;
-      dis = dis || back;
-      if (fill) {
-        for (int64_t w = (int64_t)wp + 1; w <= (int64_t)wq; ++w) a.win_off[w] = i;
-        if (i == a.n_req - 1)
-          for (int64_t w = (int64_t)wq + 1; w <= a.n_window; ++w) a.win_off[w] = a.n_req;
-      }
+    dis = dis || back;
+    if (__ballot(in && (wp != wq || i == a.n_req - 1)) == 0) continue;
+    if (__ballot(back) == 0 && __hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && in) {
+      for (int64_t w = (int64_t)wp + 1; w <= (int64_t)wq; ++w) a.win_off[w] = i;
+      if (i == a.n_req - 1)
+        for (int64_t w = (int64_t)wq + 1; w <= a.n_window; ++w) a.win_off[w] = a.n_req;
     }
   }
   if (bad) atomicOr(a.status, bad);
@@ -114,7 +128,7 @@ __global__ __launch_bounds__(256) void key_kernel(IngestArgs a, double r_window,
 }
 
 // The route is chosen on the device: every kernel of the two routes is launched and the kernels of the route that
-// is not taken return at once.  `order` is the flag word the key kernel leaves: 0 = every request's window is at
+// is not taken return at once.  `order` is the flag word the order kernel leaves: 0 = every request's window is at
 // or after the window of the request before it (the trace is moved window by window), else the general sort runs.
 __device__ __forceinline__ bool sort_route(const uint32_t* order) { return *order != 0u; }
 
@@ -141,6 +155,23 @@ __device__ __forceinline__ void offsets_at(int64_t i, int64_t prev, int64_t cur,
   for (int64_t c = prev + 1; c <= cur; ++c) cell_off[c] = i;
 }
 
+// exclusive sum over the block's threads; `wave_sum`: a word of LDS per wave
+__device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wave_sum) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t incl = v;
+#pragma unroll
+  for (int k = 1; k < DYN_WAVE; k <<= 1) {
+    const uint32_t up = __shfl_up(incl, k, DYN_WAVE);
+    if (lane >= k) incl += up;
+  }
+  if (lane == DYN_WAVE - 1) wave_sum[wave] = incl;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += wave_sum[w];
+  __syncthreads();
+  return before + incl - v;
+}
+
 // ---- the general sort ----------------------------------------------------------------------
 // All radix passes and the offsets in one launch, with barriers between the phases that all its blocks pass: a trace in
 // window order costs this one launch, which returns at its first instruction.  Every block owns a contiguous run of tiles.  A
@@ -162,13 +193,10 @@ __device__ __forceinline__ void offsets_at(int64_t i, int64_t prev, int64_t cur,
 // delay a barrier but not stop it; if it takes seconds all the same, the wait is given up (every block leaves,
 // DYN_WS_SORT_ABANDONED is raised).
 struct RadixArgs {
-  const uint32_t* order;
-  uint32_t* barrier; uint32_t* join; uint32_t* members; uint32_t* status;
-  uint32_t* key_a; uint32_t* key_b;
-  const int32_t* in_tok; const int32_t* out_tok;
-  int32_t* in_sorted; int32_t* out_sorted; int32_t* in_tmp; int32_t* out_tmp;
-  uint32_t* hist;                                // [digit][block]
-  int64_t n, cells; int64_t* cell_off;
+  IngestArgs t;
+  double r_window;
+  uint32_t* barrier; uint32_t* join; uint32_t* members;
+  int64_t cells;
   int32_t passes, bits;
 };
 
@@ -252,6 +280,37 @@ __device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members
   return m;
 }
 
+// Keys of the requests [beg, end): cell = window * classes + class.
+__device__ __forceinline__ void radix_keys(const IngestArgs& a, double r_window, int64_t beg, int64_t end, RadixLds& s) {
+  const ClassEdges edges = stage_edges(a, (int32_t*)s.move, kRadixTile);
+  __syncthreads();
+  const uint32_t G = (uint32_t)(a.n_model * a.n_in_bin * a.n_out_bin);
+  uint32_t bad = 0;
+  constexpr int N = 4;
+  for (int64_t at = beg; at < end; at += N * kRadixThreads) {
+    double t[N];
+    int32_t x[N], y[N], mdl[N];
+    uint32_t cls[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
+      t[r] = a.t_s[i];
+      x[r] = a.in_tok[i];
+      y[r] = a.out_tok[i];
+      mdl[r] = a.model ? a.model[i] : 0;
+    }
+    classes_of<N>(a, edges, x, y, mdl, cls, &bad);
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      const uint32_t w = (uint32_t)window_of(t[r], a.window_s, r_window, a.n_window, &bad);
+      if (i < end) put(a.key_a + i, w * G + cls[r]);
+    }
+  }
+  if (bad) atomicOr(a.status, bad);
+  __syncthreads();
+}
+
 // Digit counts of the keys [beg, end) -> hist[digit][block].  In runs of equal digits (the keys of a later pass) a wave
 // adds once for all its lanes; else lanes add to one of four copies, which shortens the queues of equal digits.
 __device__ __forceinline__ void radix_count(const uint32_t* keys, int64_t beg, int64_t end, int shift, int bits, uint32_t* hist, RadixTeam m, RadixLds& s) {
@@ -313,23 +372,6 @@ __device__ __forceinline__ void radix_scan(uint32_t* hist, int bits, RadixTeam m
   }
 }
 
-// exclusive sum over the block's threads
-__device__ __forceinline__ uint32_t radix_block_scan(uint32_t v, RadixLds& s) {
-  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
-  uint32_t incl = v;
-#pragma unroll
-  for (int k = 1; k < DYN_WAVE; k <<= 1) {
-    const uint32_t up = __shfl_up(incl, k, DYN_WAVE);
-    if (lane >= k) incl += up;
-  }
-  if (lane == DYN_WAVE - 1) s.wave_sum[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0;
-  for (int w = 0; w < wave; ++w) before += s.wave_sum[w];
-  __syncthreads();
-  return before + incl - v;
-}
-
 // Stable move of one tile of `count` requests (FULL: kRadixTile).  What is missing to kRadixTile takes part as requests of
 // the last digit, behind all others, and is not written.  Every wave owns a contiguous run of rows of 64 requests and
 // walks them in order; a request's rank among the row's requests with its digit comes from wave ballots.  `next`: output
@@ -382,7 +424,7 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
     for (int w = 0; w < kRadixWaves; ++w) total[q] += s.wcnt[w][threadIdx.x * kRadixOwn + q];
     sum += total[q];
   }
-  uint32_t start = radix_block_scan(sum, s);
+  uint32_t start = block_exclusive_sum(sum, s.wave_sum);
 #pragma unroll
   for (int q = 0; q < kRadixOwn; ++q) {
     const int d = threadIdx.x * kRadixOwn + q;
@@ -443,7 +485,7 @@ __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_
       next[q] = d < nbins && m.block > 0 ? row[m.block - 1] : 0u;
       sum += total[q];
     }
-    uint32_t base = radix_block_scan(sum, s);
+    uint32_t base = block_exclusive_sum(sum, s.wave_sum);
 #pragma unroll
     for (int q = 0; q < kRadixOwn; ++q) {
       next[q] += base;
@@ -456,35 +498,37 @@ __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_
   if (at < end) radix_tile<false>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, (int)(end - at), shift, bits, next, s);
 }
 
-__global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs a) {
-  if (!sort_route(a.order)) return;              // the same word for every block: all leave, or none
+__global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs g) {
+  const IngestArgs& a = g.t;
+  if (!sort_route(a.unsorted)) return;              // the same word for every block: all leave, or none
   __shared__ RadixLds s;
-  const RadixTeam m = join_team(a.join, a.members, a.status, s);
+  const RadixTeam m = join_team(g.join, g.members, a.status, s);
   if (m.blocks == 0) return;
   uint32_t passed = 0;                           // barriers behind this block
   auto sync = [&]() {
     ++passed;
-    const bool ok = grid_barrier(a.barrier, passed * (uint32_t)m.blocks, &s.flag);
+    const bool ok = grid_barrier(g.barrier, passed * (uint32_t)m.blocks, &s.flag);
     if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
     return ok;
   };
-  const int n_tile = (int)((a.n + kRadixTile - 1) / kRadixTile);
+  const int n_tile = (int)((a.n_req + kRadixTile - 1) / kRadixTile);
   const int tiles = n_tile / m.blocks, more = n_tile % m.blocks;   // the first `more` blocks take one tile more
   const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kRadixTile;
-  const int64_t end = std::min<int64_t>(a.n, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
+  const int64_t end = std::min<int64_t>(a.n_req, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
+  radix_keys(a, g.r_window, beg, end, s);
   const uint32_t* k_src = a.key_a;
   uint32_t* k_dst = a.key_b;
   const int32_t *i_src = a.in_tok, *o_src = a.out_tok;
-  for (int p = 0; p < a.passes; ++p) {
-    const bool to_final = ((a.passes - 1 - p) % 2) == 0;   // ping-pong so that the last pass lands in the caller's arrays
+  for (int p = 0; p < g.passes; ++p) {
+    const bool to_final = ((g.passes - 1 - p) % 2) == 0;   // ping-pong so that the last pass lands in the caller's arrays
     int32_t* i_dst = to_final ? a.in_sorted : a.in_tmp;
     int32_t* o_dst = to_final ? a.out_sorted : a.out_tmp;
-    const int shift = p * a.bits;
-    radix_count(k_src, beg, end, shift, a.bits, a.hist, m, s);
+    const int shift = p * g.bits;
+    radix_count(k_src, beg, end, shift, g.bits, a.block_hist, m, s);
     if (!sync()) return;
-    radix_scan(a.hist, a.bits, m);
+    radix_scan(a.block_hist, g.bits, m);
     if (!sync()) return;
-    radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, a.bits, a.hist, m, s);
+    radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, g.bits, a.block_hist, m, s);
     if (!sync()) return;
     i_src = i_dst;
     o_src = o_dst;
@@ -492,8 +536,8 @@ __global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs a)
     k_src = k_dst;
     k_dst = old_src;
   }
-  if (a.n == 0)
-    for (int64_t c = threadIdx.x; c <= a.cells; c += kRadixThreads) a.cell_off[c] = 0;
+  if (a.n_req == 0)
+    for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
   // the offsets: a block goes over its run of the sorted keys, every key beside the one before it
   for (int64_t at = beg; at < end; at += kRadixTile) {
     uint32_t key[kRadixItems], left[kRadixItems];
@@ -512,126 +556,224 @@ __global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs a)
         k = r == q ? key[q] : k;
         l = r == q ? left[q] : l;
       }
-      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n, a.cells, a.cell_off);
-      if (i == a.n - 1) offsets_at(a.n, k, a.cells, a.n, a.cells, a.cell_off);
+      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n_req, g.cells, a.cell_off);
+      if (i == a.n_req - 1) offsets_at(a.n_req, k, g.cells, a.n_req, g.cells, a.cell_off);
     }
   }
 }
 
 // ---- a trace in window order ----------------------------------------------------------------
-// win_off[w] = number of requests in windows before w, read off the keys (window = key / G)
-__global__ __launch_bounds__(256) void window_offsets_kernel(const uint32_t* __restrict__ keys, int64_t n, uint32_t G,
-                                                             int32_t n_window, int64_t* __restrict__ win_off) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > n) return;
-  const int64_t prev = i == 0 ? -1 : (int64_t)(keys[i - 1] / G);
-  int64_t cur = i == n ? n_window : (int64_t)(keys[i] / G);
-  if (cur > n_window) cur = n_window;
-  for (int64_t w = prev + 1; w <= cur; ++w) win_off[w] = i;
+// One block per window.  The requests are ranked by class as in the general sort (a wave walks rows of 64 in order, ranks
+// inside a row from ballots), put in class order in LDS and written from there: the window's part of the output is one
+// run.  A window of more than a tile counts its classes first and then goes tile by tile.
+// What bounds it: vector instructions (ranking and classes, 100 a row of 64 requests: 26 us of ten million requests) and
+// bytes (16 a request: 30 us).  The tile is the largest that lets two blocks share a compute unit (76 KB of LDS, 24 requests
+// a thread): a window of one tile needs no counting and no look-up of where a class goes.  Ten million requests in 1440
+// windows: 47 us; 62 with 16 requests a thread, 75 with 8; 72 with keys read twice and single words scattered (and
+// 53 us for the kernel that wrote the keys, where order_kernel takes 19).
+constexpr int kWinWaves = 8;
+constexpr int kWinThreads = kWinWaves * DYN_WAVE;
+constexpr int kWinItems = 24;                    // requests per thread and tile
+constexpr int kWinTile = kWinThreads * kWinItems;
+constexpr int kWinOwn = DYN_INGEST_MAX_BINS / kWinThreads;   // classes a thread owns
+constexpr size_t kWinEdges = 2048;               // class edges that a block stages in LDS
+
+struct WinLds {
+  uint32_t move[kWinTile];
+  union {
+    uint16_t wcnt[kWinWaves][DYN_INGEST_MAX_BINS];
+    uint32_t cnt[DYN_INGEST_MAX_BINS];           // class totals of a long window
+    uint16_t cls[kWinTile];                      // of a long window's tile in class order
+  };
+  uint32_t to[DYN_INGEST_MAX_BINS];              // place in a long window of a class's first request of the tile, less its place in the tile
+  uint32_t wave_sum[kWinWaves];
+};
+
+// Element i of a run of 4-byte values, i * 4 < 2^32: one 32-bit offset instead of a 64-bit address.
+template <typename T>
+__device__ __forceinline__ T& at32(T* p, uint32_t i) { return *(T*)((char*)p + (i << 2)); }
+
+// One tile of `count` requests; LONG: of a window of several tiles.  `next`: place in the window of the next request of each
+// class that the thread owns (set here for a window of one tile).  `off`: the window's cell offsets, written by its first tile.
+template <bool LONG>
+__device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdges& edges, const int32_t* in_in, const int32_t* out_in, const int32_t* model,
+                                            int32_t* in_out, int32_t* out_out, int count, int bits, int G, int64_t beg, int64_t* off, uint32_t* next, uint32_t* bad, WinLds& s) {
+  constexpr int N = 8;                             // rows loaded together
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  const int rows = (count + kWinThreads - 1) / kWinThreads;   // rows per wave: a short tile is shared by all waves
+  const int at = wave * rows * DYN_WAVE + lane;
+  uint32_t place[kWinItems];                       // class << 16 | rank in the wave, later the place in the tile
+  int32_t vin[kWinItems], vout[kWinItems];
+#pragma unroll
+  for (int r = 0; r < kWinItems; ++r)
+    if (r / N * N < rows) {
+      const uint32_t i = (uint32_t)min(at + r * DYN_WAVE, count - 1);
+      vin[r] = at32(in_in, i);
+      vout[r] = at32(out_in, i);
+    }
+  for (int b = threadIdx.x; b < kWinWaves * DYN_INGEST_MAX_BINS / 2; b += kWinThreads) ((uint32_t*)s.wcnt)[b] = 0;
+  __syncthreads();
+  uint16_t* my = s.wcnt[wave];
+  // what is missing to the rows takes part as requests of the last class, behind all others, and is not written
+  const uint32_t last = (1u << bits) - 1u;
+#pragma unroll
+  for (int g = 0; g < kWinItems; g += N) {
+    if (g >= rows) continue;                       // the same for the whole block
+    int32_t mdl[N];
+    uint32_t cls[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) mdl[r] = model ? at32(model, (uint32_t)min(at + (g + r) * DYN_WAVE, count - 1)) : 0;
+    classes_of<N>(a, edges, vin + g, vout + g, mdl, cls, bad);
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      if (g + r >= rows) continue;
+      const uint32_t c = at + (g + r) * DYN_WAVE < count ? cls[r] : last;
+      uint32_t lo = ~0u, hi = ~0u;
+      for (int b = 0; b < bits; ++b) {
+        const int bit = __builtin_amdgcn_sbfe((int)c, b, 1);   // 0 or -1
+        const uint64_t bal = __ballot(bit != 0);
+        lo &= ~((uint32_t)bal ^ (uint32_t)bit);
+        hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)bit);
+      }
+      const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+      const uint32_t group = (uint32_t)__popc(lo) + (uint32_t)__popc(hi);
+      const uint32_t rank = my[c] + before;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (before == group - 1) my[c] = (uint16_t)(rank + 1);   // one lane per class advances it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      place[g + r] = c << 16 | rank;
+    }
+  }
+  __syncthreads();
+  // per class: where its requests start in the tile, and where each wave's among them do
+  uint32_t total[kWinOwn], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kWinOwn; ++q) {
+    total[q] = 0;
+#pragma unroll
+    for (int v = 0; v < kWinWaves; ++v) total[q] += s.wcnt[v][threadIdx.x * kWinOwn + q];
+    sum += total[q];
+  }
+  uint32_t start = block_exclusive_sum(sum, s.wave_sum);
+#pragma unroll
+  for (int q = 0; q < kWinOwn; ++q) {
+    const int d = threadIdx.x * kWinOwn + q;
+    if (!LONG) next[q] = start;
+    if (off && d < G) off[d] = beg + next[q];
+    if (LONG) {
+      s.to[d] = next[q] - start;
+      next[q] += total[q];
+    }
+#pragma unroll
+    for (int v = 0; v < kWinWaves; ++v) {
+      const uint32_t c = s.wcnt[v][d];
+      s.wcnt[v][d] = (uint16_t)start;
+      start += c;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kWinItems; ++r)
+    if (r < rows) place[r] += my[place[r] >> 16];
+  if (LONG) {
+    __syncthreads();                               // the wave counters are done with
+#pragma unroll
+    for (int r = 0; r < kWinItems; ++r)
+      if (r < rows) s.cls[place[r] & 0xFFFFu] = (uint16_t)(place[r] >> 16);
+  }
+#pragma unroll
+  for (int r = 0; r < kWinItems; ++r)
+    if (r < rows) s.move[place[r] & 0xFFFFu] = (uint32_t)vin[r];
+  __syncthreads();
+  auto write = [&](int32_t* out) {
+    auto one = [&](uint32_t i) {
+      if (LONG) out[s.to[s.cls[i]] + i] = (int32_t)s.move[i];
+      else at32(out, i) = (int32_t)s.move[i];
+    };
+    int i = threadIdx.x;
+    for (; i + 3 * kWinThreads < count; i += 4 * kWinThreads) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) one((uint32_t)(i + q * kWinThreads));
+    }
+    for (; i < count; i += kWinThreads) one((uint32_t)i);
+  };
+  write(in_out);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kWinItems; ++r)
+    if (r < rows) s.move[place[r] & 0xFFFFu] = (uint32_t)vout[r];
+  __syncthreads();
+  write(out_out);
 }
 
-// One block per window: class totals of the window, their exclusive prefix (the window's cell offsets),
-// then a stable move tile by tile: every wave owns a contiguous run of rows of a tile and walks them in
-// order, a request's position = start of its class + requests of the class in earlier tiles and earlier
-// waves' runs + its rank among the lanes of its row with the same class (wave ballots).
-__global__ __launch_bounds__(kWaves* DYN_WAVE) void window_sort_kernel(
-    const uint32_t* __restrict__ keys, const int32_t* __restrict__ in_in, const int32_t* __restrict__ out_in,
-    int32_t* __restrict__ in_out, int32_t* __restrict__ out_out, const int64_t* __restrict__ win_off, int32_t G,
-    int32_t n_window, int64_t n, int64_t* __restrict__ cell_off, const uint32_t* __restrict__ order) {
-  if (sort_route(order)) return;
-  __shared__ uint32_t wcnt[kWaves][DYN_INGEST_MAX_BINS];
-  __shared__ uint32_t run[DYN_INGEST_MAX_BINS];          // next output position of every class, relative to the window's start
+__global__ __launch_bounds__(kWinThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void window_sort_kernel(IngestArgs a, int edge_room) {
+  if (sort_route(a.unsorted)) return;
+  __shared__ WinLds s;
+  extern __shared__ int32_t s_edge[];
+  const int32_t G = a.n_model * a.n_in_bin * a.n_out_bin;
   const int w = blockIdx.x;
-  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
-  const int64_t beg = win_off[w], end = win_off[w + 1];
-  const uint32_t key0 = (uint32_t)w * (uint32_t)G;
+  const int64_t beg = a.win_off[w];
+  const int len = (int)(a.win_off[w + 1] - beg);
+  int64_t* off = a.cell_off + (int64_t)w * G;
+  if (w == a.n_window - 1 && threadIdx.x == 0) off[G] = a.n_req;
+  if (len <= 0) {
+    for (int d = threadIdx.x; d < G; d += kWinThreads) off[d] = beg;
+    return;
+  }
+  const int32_t* in_in = a.in_tok + beg;
+  const int32_t* out_in = a.out_tok + beg;
+  const int32_t* model = a.model ? a.model + beg : nullptr;
+  int32_t* in_out = a.in_sorted + beg;
+  int32_t* out_out = a.out_sorted + beg;
+  const ClassEdges edges = stage_edges(a, s_edge, edge_room);
+  uint32_t bad = 0;
   int bits = 0;
   while ((1 << bits) < G) ++bits;
-  for (int d = threadIdx.x; d < G; d += blockDim.x) run[d] = 0;
-  __syncthreads();
-  {                                                      // class totals of the window, four loads per thread in flight
-    int64_t i = beg + threadIdx.x;
-    for (; i + 3 * (int64_t)blockDim.x < end; i += 4 * (int64_t)blockDim.x) {
-      const uint32_t k0 = keys[i], k1 = keys[i + blockDim.x], k2 = keys[i + 2 * blockDim.x], k3 = keys[i + 3 * blockDim.x];
-      atomicAdd(&run[k0 - key0], 1u); atomicAdd(&run[k1 - key0], 1u); atomicAdd(&run[k2 - key0], 1u); atomicAdd(&run[k3 - key0], 1u);
-    }
-    for (; i < end; i += blockDim.x) atomicAdd(&run[keys[i] - key0], 1u);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {                                // exclusive prefix over the classes
-    uint32_t acc = 0;
-    for (int d = 0; d < G; ++d) {
-      const uint32_t c = run[d];
-      run[d] = acc;
-      acc += c;
-    }
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < G; d += blockDim.x) cell_off[(int64_t)w * G + d] = beg + run[d];
-  if (w == n_window - 1 && threadIdx.x == 0) cell_off[(int64_t)n_window * G] = n;
-
-  for (int64_t tile = beg; tile < end; tile += kTile) {
-    for (int b = threadIdx.x; b < kWaves * G; b += blockDim.x) wcnt[b / G][b % G] = 0;
+  uint32_t next[kWinOwn];
+  if (len <= kWinTile) {
+    window_tile<false>(a, edges, in_in, out_in, model, in_out, out_out, len, bits, G, beg, off, next, &bad, s);
+  } else {
+    for (int d = threadIdx.x; d < DYN_INGEST_MAX_BINS; d += kWinThreads) s.cnt[d] = 0;
     __syncthreads();
-    // phase 1: class counts of each wave's run of rows
-    const int64_t wbase = tile + (int64_t)wave * (kRows * DYN_WAVE);
-    uint32_t cls[kRows];
-    int32_t vin[kRows], vout[kRows];                     // the payload, loaded with the keys: not one row at a time later
+    for (int at = 0; at < len; at += 4 * kWinThreads) {
+      int32_t x[4], y[4], mdl[4];
+      uint32_t d[4];
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t idx = wbase + r * DYN_WAVE + lane;
-      cls[r] = idx < end ? keys[idx] - key0 : 0u;
-      vin[r] = idx < end ? in_in[idx] : 0;
-      vout[r] = idx < end ? out_in[idx] : 0;
-      if (idx < end) atomicAdd(&wcnt[wave][cls[r]], 1u);
-    }
-    __syncthreads();
-    // phase 2: per class, the first output position of each wave's requests
-    for (int d = threadIdx.x; d < G; d += blockDim.x) {
-      uint32_t pos = run[d];
-      for (int q = 0; q < kWaves; ++q) {
-        const uint32_t c = wcnt[q][d];
-        wcnt[q][d] = pos;
-        pos += c;
+      for (int r = 0; r < 4; ++r) {
+        const int i = min(at + r * kWinThreads + (int)threadIdx.x, len - 1);
+        x[r] = in_in[i];
+        y[r] = out_in[i];
+        mdl[r] = model ? model[i] : 0;
       }
-      run[d] = pos;
-    }
-    __syncthreads();
-    // phase 3: rows in order; inside a row, rank among the lanes with the same class
-    uint32_t* my = wcnt[wave];
+      classes_of<4>(a, edges, x, y, mdl, d, &bad);
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t idx = wbase + r * DYN_WAVE + lane;
-      const bool valid = idx < end;
-      if (__ballot(valid) == 0) break;                   // wave-uniform: nothing left in this run
-      const uint32_t d = cls[r];
-      uint64_t peers = __ballot(valid);
-      for (int b = 0; b < bits; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        peers &= bit ? bal : ~bal;
-      }
-      const int before = __popcll(peers & ((1ull << lane) - 1ull));
-      const int group = __popcll(peers);
-      uint32_t pos = 0;
-      if (valid) pos = my[d] + (uint32_t)before;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      if (valid && before == group - 1) my[d] += (uint32_t)group;   // one lane per class advances it
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      if (valid) {
-        in_out[beg + pos] = vin[r];
-        out_out[beg + pos] = vout[r];
-      }
+      for (int r = 0; r < 4; ++r)
+        if (at + r * kWinThreads + (int)threadIdx.x < len) atomicAdd(&s.cnt[d[r]], 1u);
     }
     __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kWinOwn; ++q) sum += s.cnt[threadIdx.x * kWinOwn + q];
+    uint32_t base = block_exclusive_sum(sum, s.wave_sum);
+#pragma unroll
+    for (int q = 0; q < kWinOwn; ++q) {
+      next[q] = base;
+      base += s.cnt[threadIdx.x * kWinOwn + q];
+    }
+    for (int tile = 0; tile < len; tile += kWinTile) {
+      __syncthreads();                             // what the counts or the last tile left in LDS has been read
+      window_tile<true>(a, edges, in_in + tile, out_in + tile, model ? model + tile : nullptr, in_out, out_out, min(kWinTile, len - tile), bits, G, beg,
+                        tile == 0 ? off : nullptr, next, &bad, s);
+    }
   }
+  if (bad) atomicOr(a.status, bad);
 }
 
 }  // namespace
 
-int64_t dyn_ingest_blocks(int64_t n_req) { return n_req > 0 ? (n_req + kTile - 1) / kTile : 1; }
+int64_t dyn_ingest_blocks(int64_t n_req) { return n_req > 0 ? (n_req + kRadixTile - 1) / kRadixTile : 1; }
 
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
                             int32_t* d_out, WsHeader* header, uint32_t order_word, hipStream_t s) {
@@ -658,20 +800,16 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   const int32_t G = a.n_model * a.n_in_bin * a.n_out_bin;
   const int64_t cells = (int64_t)a.n_window * G;
   hipError_t e;
-  // Keys, and whether the trace is in window order already: the key kernel ORs into the flag word, which the header
-  // kernel before it set to 0, or to 1 when the general sort is forced (more classes than the window route counts).
-  if (n > 0) {
-    const size_t edge_bytes = (size_t)a.n_model * ((a.n_in_bin - 1) + (a.n_out_bin - 1)) * sizeof(int32_t);
-    const int lds_edges = edge_bytes <= 32 * 1024 ? 1 : 0;
-    hipLaunchKernelGGL(key_kernel, dim3((unsigned)((n + kKeyRows * 256 - 1) / (kKeyRows * 256))), dim3(256), lds_edges ? edge_bytes : 0, s, a,
-                       1.0 / a.window_s, lds_edges);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else {
-    hipLaunchKernelGGL(window_offsets_kernel, dim3(1), dim3(256), 0, s, a.key_a, n, (uint32_t)G, a.n_window, a.win_off);
-  }
+  // The order kernel ORs into the flag word, which the header kernel before it set to 0, or to 1 when the general sort
+  // is forced (more classes than the window route counts).
+  const double r_window = 1.0 / a.window_s;
+  const int64_t per_block = 256 * kOrderRows;
+  hipLaunchKernelGGL(order_kernel, dim3((unsigned)std::max<int64_t>(1, (n + per_block - 1) / per_block)), dim3(256), 0, s, a, r_window);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!a.force_sort) {        // in window order: one block per window moves its requests to their cells
-    hipLaunchKernelGGL(window_sort_kernel, dim3((unsigned)a.n_window), dim3(kWaves * DYN_WAVE), 0, s, a.key_a, a.in_tok,
-                       a.out_tok, a.in_sorted, a.out_sorted, a.win_off, G, a.n_window, n, a.cell_off, a.unsorted);
+    const size_t n_edge = (size_t)a.n_model * ((a.n_in_bin - 1) + (a.n_out_bin - 1));
+    const size_t room = n_edge <= kWinEdges ? n_edge : 0;
+    hipLaunchKernelGGL(window_sort_kernel, dim3((unsigned)a.n_window), dim3(kWinThreads), room * sizeof(int32_t), s, a, (int)room);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (n == 0) return hipSuccess;   // nothing to sort: the flag word stays 0
   }
@@ -689,12 +827,8 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   }
   (void)hipGetLastError();
   RadixArgs r;
-  r.order = a.unsorted; r.barrier = a.unsorted + (DYN_WS_HEADER_BARRIER_WORD - DYN_WS_HEADER_ORDER_WORD); r.status = a.status;
-  r.join = r.barrier + 1; r.members = r.barrier + 2;
-  r.key_a = a.key_a; r.key_b = a.key_b; r.in_tok = a.in_tok; r.out_tok = a.out_tok;
-  r.in_sorted = a.in_sorted; r.out_sorted = a.out_sorted; r.in_tmp = a.in_tmp; r.out_tmp = a.out_tmp;
-  r.hist = a.block_hist; r.n = n; r.cells = cells; r.cell_off = a.cell_off;
-  r.passes = passes; r.bits = bits;
+  r.t = a; r.r_window = r_window; r.cells = cells; r.passes = passes; r.bits = bits;
+  r.barrier = a.unsorted + (DYN_WS_HEADER_BARRIER_WORD - DYN_WS_HEADER_ORDER_WORD); r.join = r.barrier + 1; r.members = r.barrier + 2;
   // a block for every tile, as far as they fit the device and the digit counts (a word per digit and block) the workspace
   const int64_t room = ((int64_t)DYN_INGEST_MAX_BINS * a.n_block) >> bits;
   const int64_t n_tile = (n + kRadixTile - 1) / kRadixTile;

@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 TILE = 8192          # requests a block of the general sort moves at a time
+WINDOW = 12288       # requests a block of the window route moves at a time
 
 
 @pytest.fixture(scope="module")
@@ -19,19 +20,20 @@ def dyn():
     return d
 
 
-def _edges(n_in, n_out):
-    return {"in_edge": np.linspace(100, 8000, n_in - 1).astype(np.int32)[None, :], "out_edge": np.linspace(90, 7900, n_out - 1).astype(np.int32)[None, :]}
+def _edges(n_in, n_out, n_model=1):
+    tile = lambda e: np.tile(e.astype(np.int32), (n_model, 1)).reshape(n_model, e.size) + 7 * np.arange(n_model, dtype=np.int32)[:, None]
+    return {"in_edge": tile(np.linspace(100, 8000, n_in - 1)), "out_edge": tile(np.linspace(90, 7900, n_out - 1))}
 
 
-def _log(seed, n, horizon):
+def _log(seed, n, horizon, n_model=1):
     rng = np.random.default_rng(seed)
     return {"t_s": rng.uniform(0, horizon, n), "in_tok": rng.integers(1, 8193, n).astype(np.int32),
-            "out_tok": rng.integers(1, 8193, n).astype(np.int32), "model": np.zeros(n, np.int32)}
+            "out_tok": rng.integers(1, 8193, n).astype(np.int32), "model": rng.integers(0, n_model, n).astype(np.int32)}
 
 
 def _call(dyn, tr, edges, n_window, window_s, **kw):
-    d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
-    return dyn.dyn_trace_ingest(*d, None, edges, n_window, window_s, **kw)
+    d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok", "model")]
+    return dyn.dyn_trace_ingest(*d[:3], d[3] if len(edges["in_edge"]) > 1 else None, edges, n_window, window_s, **kw)
 
 
 def _check(got, tr, edges, n_window, window_s):
@@ -50,6 +52,29 @@ def test_general_sort_is_stable(dyn, n, n_window, n_in, n_out):
     got = _call(dyn, tr, edges, n_window, 10.0)
     assert dyn.dyn_workspace_status(got[3]) == 0
     _check(got, tr, edges, n_window, 10.0)
+
+
+# a window of one request, of a wave, of a tile, of one more and of several tiles; empty windows; one class, and the most
+# that the route takes; several models; edges that stay in global memory
+@pytest.mark.parametrize("n,n_window,n_in,n_out,n_model", [(1, 1, 1, 1, 1), (64, 1, 2, 2, 1), (WINDOW, 1, 5, 5, 1), (WINDOW + 1, 1, 5, 5, 1), (4 * WINDOW - 3, 1, 32, 32, 1),
+                                                           (3 * WINDOW, 2, 8, 8, 4), (513, 1000, 5, 5, 1), (200_000, 31, 3, 3, 4), (100_000, 7, 2, 2, 256)])
+def test_log_in_time_order(dyn, n, n_window, n_in, n_out, n_model):
+    edges = _edges(n_in, n_out, n_model)
+    tr = _log(n, n, n_window * 10.0, n_model)
+    tr["t_s"].sort()
+    got = _call(dyn, tr, edges, n_window, 10.0)
+    assert dyn.dyn_workspace_status(got[3]) == 0
+    _check(got, tr, edges, n_window, 10.0)
+
+
+def test_edges_that_stay_in_global_memory(dyn):
+    """One class axis of 900 bins and three models: 2697 edges, more than a block stages (and more classes than the window route)."""
+    edges = _edges(900, 1, 3)
+    for order in (True, False):
+        tr = _log(5, 50_000, 30.0, 3)
+        if order:
+            tr["t_s"].sort()
+        _check(_call(dyn, tr, edges, 3, 10.0), tr, edges, 3, 10.0)
 
 
 def test_no_requests_and_more_classes_than_the_window_route_counts(dyn):
