@@ -651,12 +651,12 @@ int dyn_trace_ingest(const double* t_s, const int32_t* in_tok, const int32_t* ou
   a.in_tmp = (int32_t*)(base + w.in_tmp); a.out_tmp = (int32_t*)(base + w.out_tmp);
   a.block_hist = (uint32_t*)(base + w.hist);
   a.unsorted = (uint32_t*)(base + w.status) + DYN_WS_HEADER_ORDER_WORD;
-  a.force_sort = G > DYN_INGEST_MAX_BINS ? 1 : 0;   // the window route keeps one counter per class in LDS
   a.win_off = (int64_t*)(base + w.win_off);
   a.n_block = dyn_ingest_blocks(n_req);
   int bits = 0;
   while (((int64_t)1 << bits) < cells) ++bits;
   a.key_bits = bits;
+  a.force_sort = dyn_ingest_always_sorts(n_req, n_window, G, bits) ? 1 : 0;
   // the workspace header (status 0, order word = "general sort forced") and the edge lists, which travel in a kernel's
   // arguments: the host arrays are free on return and nothing waits for the stream
   if (!hip_ok(dyn_launch_edges(e->in_edge, (size_t)e->n_model * (e->n_in_bin - 1), e->out_edge, (size_t)e->n_model * (e->n_out_bin - 1),

@@ -180,6 +180,7 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s);
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
                             int32_t* d_out, WsHeader* header, uint32_t order_word, hipStream_t s);
 int64_t dyn_ingest_blocks(int64_t n_req);
+bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, int32_t key_bits);
 #define DYN_INGEST_MAX_BINS 1024
 
 void dyn_set_error(const char* fmt, ...);

@@ -156,6 +156,7 @@ __device__ __forceinline__ void offsets_at(int64_t i, int64_t prev, int64_t cur,
 }
 
 // exclusive sum over the block's threads; `wave_sum`: a word of LDS per wave
+template <int WAVES>
 __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wave_sum) {
   const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
   uint32_t incl = v;
@@ -164,10 +165,12 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wa
     const uint32_t up = __shfl_up(incl, k, DYN_WAVE);
     if (lane >= k) incl += up;
   }
+  if (WAVES == 1) return incl - v;
   if (lane == DYN_WAVE - 1) wave_sum[wave] = incl;
   __syncthreads();
   uint32_t before = 0;
-  for (int w = 0; w < wave; ++w) before += wave_sum[w];
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) before += w < wave ? wave_sum[w] : 0u;
   __syncthreads();
   return before + incl - v;
 }
@@ -424,7 +427,7 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
     for (int w = 0; w < kRadixWaves; ++w) total[q] += s.wcnt[w][threadIdx.x * kRadixOwn + q];
     sum += total[q];
   }
-  uint32_t start = block_exclusive_sum(sum, s.wave_sum);
+  uint32_t start = block_exclusive_sum<kRadixWaves>(sum, s.wave_sum);
 #pragma unroll
   for (int q = 0; q < kRadixOwn; ++q) {
     const int d = threadIdx.x * kRadixOwn + q;
@@ -485,7 +488,7 @@ __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_
       next[q] = d < nbins && m.block > 0 ? row[m.block - 1] : 0u;
       sum += total[q];
     }
-    uint32_t base = block_exclusive_sum(sum, s.wave_sum);
+    uint32_t base = block_exclusive_sum<kRadixWaves>(sum, s.wave_sum);
 #pragma unroll
     for (int q = 0; q < kRadixOwn; ++q) {
       next[q] += base;
@@ -571,22 +574,21 @@ __global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs g)
 // a thread): a window of one tile needs no counting and no look-up of where a class goes.  Ten million requests in 1440
 // windows: 47 us; 62 with 16 requests a thread, 75 with 8; 72 with keys read twice and single words scattered (and
 // 53 us for the kernel that wrote the keys, where order_kernel takes 19).
-constexpr int kWinWaves = 8;
-constexpr int kWinThreads = kWinWaves * DYN_WAVE;
-constexpr int kWinItems = 24;                    // requests per thread and tile
-constexpr int kWinTile = kWinThreads * kWinItems;
-constexpr int kWinOwn = DYN_INGEST_MAX_BINS / kWinThreads;   // classes a thread owns
 constexpr size_t kWinEdges = 2048;               // class edges that a block stages in LDS
 
+template <int WAVES, int ITEMS>
 struct WinLds {
-  uint32_t move[kWinTile];
+  static constexpr int kThreads = WAVES * DYN_WAVE;
+  static constexpr int kTile = kThreads * ITEMS;   // ITEMS requests per thread and tile
+  static constexpr int kOwn = DYN_INGEST_MAX_BINS / kThreads;   // classes a thread owns at most
+  uint32_t move[kTile];
   union {
-    uint16_t wcnt[kWinWaves][DYN_INGEST_MAX_BINS];
+    uint16_t wcnt[WAVES][DYN_INGEST_MAX_BINS];
     uint32_t cnt[DYN_INGEST_MAX_BINS];           // class totals of a long window
-    uint16_t cls[kWinTile];                      // of a long window's tile in class order
+    uint16_t cls[kTile];                         // of a long window's tile in class order
   };
   uint32_t to[DYN_INGEST_MAX_BINS];              // place in a long window of a class's first request of the tile, less its place in the tile
-  uint32_t wave_sum[kWinWaves];
+  uint32_t wave_sum[WAVES];
 };
 
 // Element i of a run of 4-byte values, i * 4 < 2^32: one 32-bit offset instead of a 64-bit address.
@@ -595,29 +597,33 @@ __device__ __forceinline__ T& at32(T* p, uint32_t i) { return *(T*)((char*)p + (
 
 // One tile of `count` requests; LONG: of a window of several tiles.  `next`: place in the window of the next request of each
 // class that the thread owns (set here for a window of one tile).  `off`: the window's cell offsets, written by its first tile.
-template <bool LONG>
+template <int WAVES, int ITEMS, bool LONG>
 __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdges& edges, const int32_t* in_in, const int32_t* out_in, const int32_t* model,
-                                            int32_t* in_out, int32_t* out_out, int count, int bits, int G, int64_t beg, int64_t* off, uint32_t* next, uint32_t* bad, WinLds& s) {
-  constexpr int N = 8;                             // rows loaded together
+                                            int32_t* in_out, int32_t* out_out, int count, int bits, int G, int64_t beg, int64_t* off, uint32_t* next, uint32_t* bad, WinLds<WAVES, ITEMS>& s) {
+  constexpr int kThreads = WAVES * DYN_WAVE, kOwn = WinLds<WAVES, ITEMS>::kOwn;
+  constexpr int N = 8;                             // rows whose classes are computed together
+  const int nbins = 1 << bits, own = (nbins + kThreads - 1) / kThreads;   // classes, and those a thread owns: threadIdx.x * own ...
   const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
-  const int rows = (count + kWinThreads - 1) / kWinThreads;   // rows per wave: a short tile is shared by all waves
+  const int rows = (count + kThreads - 1) / kThreads;   // rows per wave: a short tile is shared by all waves
   const int at = wave * rows * DYN_WAVE + lane;
-  uint32_t place[kWinItems];                       // class << 16 | rank in the wave, later the place in the tile
-  int32_t vin[kWinItems], vout[kWinItems];
+  uint32_t place[ITEMS];                       // class << 16 | rank in the wave, later the place in the tile
+  int32_t vin[ITEMS], vout[ITEMS];
 #pragma unroll
-  for (int r = 0; r < kWinItems; ++r)
+  for (int r = 0; r < ITEMS; ++r)
     if (r / N * N < rows) {
       const uint32_t i = (uint32_t)min(at + r * DYN_WAVE, count - 1);
       vin[r] = at32(in_in, i);
       vout[r] = at32(out_in, i);
     }
-  for (int b = threadIdx.x; b < kWinWaves * DYN_INGEST_MAX_BINS / 2; b += kWinThreads) ((uint32_t*)s.wcnt)[b] = 0;
+#pragma unroll
+  for (int v = 0; v < WAVES; ++v)
+    for (int b = threadIdx.x; b < nbins; b += kThreads) s.wcnt[v][b] = 0;
   __syncthreads();
   uint16_t* my = s.wcnt[wave];
   // what is missing to the rows takes part as requests of the last class, behind all others, and is not written
   const uint32_t last = (1u << bits) - 1u;
 #pragma unroll
-  for (int g = 0; g < kWinItems; g += N) {
+  for (int g = 0; g < ITEMS; g += N) {
     if (g >= rows) continue;                       // the same for the whole block
     int32_t mdl[N];
     uint32_t cls[N];
@@ -648,18 +654,22 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
   }
   __syncthreads();
   // per class: where its requests start in the tile, and where each wave's among them do
-  uint32_t total[kWinOwn], sum = 0;
+  uint32_t total[kOwn], sum = 0;
 #pragma unroll
-  for (int q = 0; q < kWinOwn; ++q) {
+  for (int q = 0; q < kOwn; ++q) {
     total[q] = 0;
+    const int d = threadIdx.x * own + q;
+    if (q < own && d < nbins) {
 #pragma unroll
-    for (int v = 0; v < kWinWaves; ++v) total[q] += s.wcnt[v][threadIdx.x * kWinOwn + q];
-    sum += total[q];
+      for (int v = 0; v < WAVES; ++v) total[q] += s.wcnt[v][d];
+      sum += total[q];
+    }
   }
-  uint32_t start = block_exclusive_sum(sum, s.wave_sum);
+  uint32_t start = block_exclusive_sum<WAVES>(sum, s.wave_sum);
 #pragma unroll
-  for (int q = 0; q < kWinOwn; ++q) {
-    const int d = threadIdx.x * kWinOwn + q;
+  for (int q = 0; q < kOwn; ++q) {
+    const int d = threadIdx.x * own + q;
+    if (q >= own || d >= nbins) continue;
     if (!LONG) next[q] = start;
     if (off && d < G) off[d] = beg + next[q];
     if (LONG) {
@@ -667,7 +677,7 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
       next[q] += total[q];
     }
 #pragma unroll
-    for (int v = 0; v < kWinWaves; ++v) {
+    for (int v = 0; v < WAVES; ++v) {
       const uint32_t c = s.wcnt[v][d];
       s.wcnt[v][d] = (uint16_t)start;
       start += c;
@@ -675,16 +685,16 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kWinItems; ++r)
+  for (int r = 0; r < ITEMS; ++r)
     if (r < rows) place[r] += my[place[r] >> 16];
   if (LONG) {
     __syncthreads();                               // the wave counters are done with
 #pragma unroll
-    for (int r = 0; r < kWinItems; ++r)
+    for (int r = 0; r < ITEMS; ++r)
       if (r < rows) s.cls[place[r] & 0xFFFFu] = (uint16_t)(place[r] >> 16);
   }
 #pragma unroll
-  for (int r = 0; r < kWinItems; ++r)
+  for (int r = 0; r < ITEMS; ++r)
     if (r < rows) s.move[place[r] & 0xFFFFu] = (uint32_t)vin[r];
   __syncthreads();
   auto write = [&](int32_t* out) {
@@ -693,24 +703,26 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
       else at32(out, i) = (int32_t)s.move[i];
     };
     int i = threadIdx.x;
-    for (; i + 3 * kWinThreads < count; i += 4 * kWinThreads) {
+    for (; i + 3 * kThreads < count; i += 4 * kThreads) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) one((uint32_t)(i + q * kWinThreads));
+      for (int q = 0; q < 4; ++q) one((uint32_t)(i + q * kThreads));
     }
-    for (; i < count; i += kWinThreads) one((uint32_t)i);
+    for (; i < count; i += kThreads) one((uint32_t)i);
   };
   write(in_out);
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kWinItems; ++r)
+  for (int r = 0; r < ITEMS; ++r)
     if (r < rows) s.move[place[r] & 0xFFFFu] = (uint32_t)vout[r];
   __syncthreads();
   write(out_out);
 }
 
-__global__ __launch_bounds__(kWinThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void window_sort_kernel(IngestArgs a, int edge_room) {
+template <int WAVES, int ITEMS, int PER_SIMD>
+__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD))) void window_sort_kernel(IngestArgs a, int edge_room) {
   if (sort_route(a.unsorted)) return;
-  __shared__ WinLds s;
+  constexpr int kThreads = WAVES * DYN_WAVE, kTile = kThreads * ITEMS, kOwn = WinLds<WAVES, ITEMS>::kOwn;
+  __shared__ WinLds<WAVES, ITEMS> s;
   extern __shared__ int32_t s_edge[];
   const int32_t G = a.n_model * a.n_in_bin * a.n_out_bin;
   const int w = blockIdx.x;
@@ -719,7 +731,7 @@ __global__ __launch_bounds__(kWinThreads) __attribute__((amdgpu_waves_per_eu(4, 
   int64_t* off = a.cell_off + (int64_t)w * G;
   if (w == a.n_window - 1 && threadIdx.x == 0) off[G] = a.n_req;
   if (len <= 0) {
-    for (int d = threadIdx.x; d < G; d += kWinThreads) off[d] = beg;
+    for (int d = threadIdx.x; d < G; d += kThreads) off[d] = beg;
     return;
   }
   const int32_t* in_in = a.in_tok + beg;
@@ -731,18 +743,18 @@ __global__ __launch_bounds__(kWinThreads) __attribute__((amdgpu_waves_per_eu(4, 
   uint32_t bad = 0;
   int bits = 0;
   while ((1 << bits) < G) ++bits;
-  uint32_t next[kWinOwn];
-  if (len <= kWinTile) {
-    window_tile<false>(a, edges, in_in, out_in, model, in_out, out_out, len, bits, G, beg, off, next, &bad, s);
+  uint32_t next[kOwn];
+  if (len <= kTile) {
+    window_tile<WAVES, ITEMS, false>(a, edges, in_in, out_in, model, in_out, out_out, len, bits, G, beg, off, next, &bad, s);
   } else {
-    for (int d = threadIdx.x; d < DYN_INGEST_MAX_BINS; d += kWinThreads) s.cnt[d] = 0;
+    for (int d = threadIdx.x; d < DYN_INGEST_MAX_BINS; d += kThreads) s.cnt[d] = 0;
     __syncthreads();
-    for (int at = 0; at < len; at += 4 * kWinThreads) {
+    for (int at = 0; at < len; at += 4 * kThreads) {
       int32_t x[4], y[4], mdl[4];
       uint32_t d[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = min(at + r * kWinThreads + (int)threadIdx.x, len - 1);
+        const int i = min(at + r * kThreads + (int)threadIdx.x, len - 1);
         x[r] = in_in[i];
         y[r] = out_in[i];
         mdl[r] = model ? model[i] : 0;
@@ -750,21 +762,23 @@ __global__ __launch_bounds__(kWinThreads) __attribute__((amdgpu_waves_per_eu(4, 
       classes_of<4>(a, edges, x, y, mdl, d, &bad);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (at + r * kWinThreads + (int)threadIdx.x < len) atomicAdd(&s.cnt[d[r]], 1u);
+        if (at + r * kThreads + (int)threadIdx.x < len) atomicAdd(&s.cnt[d[r]], 1u);
     }
     __syncthreads();
+    const int own = ((1 << bits) + kThreads - 1) / kThreads;
     uint32_t sum = 0;
 #pragma unroll
-    for (int q = 0; q < kWinOwn; ++q) sum += s.cnt[threadIdx.x * kWinOwn + q];
-    uint32_t base = block_exclusive_sum(sum, s.wave_sum);
+    for (int q = 0; q < kOwn; ++q)
+      if (q < own && (int)threadIdx.x * own + q < DYN_INGEST_MAX_BINS) sum += s.cnt[threadIdx.x * own + q];
+    uint32_t base = block_exclusive_sum<WAVES>(sum, s.wave_sum);
 #pragma unroll
-    for (int q = 0; q < kWinOwn; ++q) {
+    for (int q = 0; q < kOwn; ++q) {
       next[q] = base;
-      base += s.cnt[threadIdx.x * kWinOwn + q];
+      if (q < own && (int)threadIdx.x * own + q < DYN_INGEST_MAX_BINS) base += s.cnt[threadIdx.x * own + q];
     }
-    for (int tile = 0; tile < len; tile += kWinTile) {
+    for (int tile = 0; tile < len; tile += kTile) {
       __syncthreads();                             // what the counts or the last tile left in LDS has been read
-      window_tile<true>(a, edges, in_in + tile, out_in + tile, model ? model + tile : nullptr, in_out, out_out, min(kWinTile, len - tile), bits, G, beg,
+      window_tile<WAVES, ITEMS, true>(a, edges, in_in + tile, out_in + tile, model ? model + tile : nullptr, in_out, out_out, min(kTile, len - tile), bits, G, beg,
                         tile == 0 ? off : nullptr, next, &bad, s);
     }
   }
@@ -795,25 +809,44 @@ hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* 
   return hipGetLastError();
 }
 
+static int sort_passes(int32_t key_bits) { return key_bits <= 0 ? 1 : (key_bits + 9) / 10; }
+
+// Whether to sort whatever the order: more classes than the window route counts, or windows so long that one block each
+// takes longer than the whole sort.  Measured: the window route 2 us per thousand requests of a window, the sort
+// 30 us and 12 to 16 us a pass and million.  10 M requests in 20, 60, 120 windows: 1041, 384, 225 us by window, 216, 333,
+// 334 sorted; 1 M in 5, 20, 60: 405, 120, 55 and 50, 56, 81; one window of 10 000, 30 000: 26, 76 and 34, 35.
+bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, int32_t key_bits) {
+  if (n_class > DYN_INGEST_MAX_BINS) return true;
+  return 2e-3 * (double)n_req / n_window > 30.0 + 15e-6 * sort_passes(key_bits) * (double)n_req;
+}
+
 hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   const int64_t n = a.n_req;
   const int32_t G = a.n_model * a.n_in_bin * a.n_out_bin;
   const int64_t cells = (int64_t)a.n_window * G;
   hipError_t e;
-  // The order kernel ORs into the flag word, which the header kernel before it set to 0, or to 1 when the general sort
-  // is forced (more classes than the window route counts).
   const double r_window = 1.0 / a.window_s;
-  const int64_t per_block = 256 * kOrderRows;
-  hipLaunchKernelGGL(order_kernel, dim3((unsigned)std::max<int64_t>(1, (n + per_block - 1) / per_block)), dim3(256), 0, s, a, r_window);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!a.force_sort) {        // in window order: one block per window moves its requests to their cells
+    // the order kernel ORs into the flag word, which the header kernel before it set to 0
+    const int64_t per_block = 256 * kOrderRows;
+    hipLaunchKernelGGL(order_kernel, dim3((unsigned)std::max<int64_t>(1, (n + per_block - 1) / per_block)), dim3(256), 0, s, a, r_window);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     const size_t n_edge = (size_t)a.n_model * ((a.n_in_bin - 1) + (a.n_out_bin - 1));
     const size_t room = n_edge <= kWinEdges ? n_edge : 0;
-    hipLaunchKernelGGL(window_sort_kernel, dim3((unsigned)a.n_window), dim3(kWinThreads), room * sizeof(int32_t), s, a, (int)room);
+    // The smallest tile that holds a window of 1.75 times the mean (traffic is not even).  Measured (us, by mean requests per
+    // window; 1440 to 2016 windows, 17 280 for 579), tiles of 512, 2048, 4096 and 12 288: 10: 7, 12, 13, 27; 198: 9, 13, 15, 28;
+    // 579: 78, 69, 102, 207; 694: 27, 11, 16, 23; 1389: 45, 22, 15, 26; 2778: 81, 33, 31, 29; 6944: 189, 65, 61, 45.
+    const dim3 grid((unsigned)a.n_window);
+    const size_t lds = room * sizeof(int32_t);
+    const double peak = 1.75 * (double)n / a.n_window;
+    if (peak <= 512) hipLaunchKernelGGL((window_sort_kernel<1, 8, 4>), grid, dim3(DYN_WAVE), lds, s, a, (int)room);
+    else if (peak <= 2048) hipLaunchKernelGGL((window_sort_kernel<4, 8, 6>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room);
+    else if (peak <= 4096) hipLaunchKernelGGL((window_sort_kernel<4, 16, 4>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room);
+    else hipLaunchKernelGGL((window_sort_kernel<8, 24, 4>), grid, dim3(8 * DYN_WAVE), lds, s, a, (int)room);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (n == 0) return hipSuccess;   // nothing to sort: the flag word stays 0
   }
-  const int passes = a.key_bits <= 0 ? 1 : (a.key_bits + 9) / 10;
+  const int passes = sort_passes(a.key_bits);
   const int bits = a.key_bits <= 0 ? 1 : (a.key_bits + passes - 1) / passes;
   // one block per compute unit (asked once per device)
   static std::atomic<int> units[64];

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 TILE = 8192          # requests a block of the general sort moves at a time
-WINDOW = 12288       # requests a block of the window route moves at a time
+WINDOW = 12288       # requests a block of the window route moves at a time (512, 2048 or 4096 where windows are short)
 
 
 @pytest.fixture(scope="module")
@@ -56,11 +56,15 @@ def test_general_sort_is_stable(dyn, n, n_window, n_in, n_out):
 
 # a window of one request, of a wave, of a tile, of one more and of several tiles; empty windows; one class, and the most
 # that the route takes; several models; edges that stay in global memory
-@pytest.mark.parametrize("n,n_window,n_in,n_out,n_model", [(1, 1, 1, 1, 1), (64, 1, 2, 2, 1), (WINDOW, 1, 5, 5, 1), (WINDOW + 1, 1, 5, 5, 1), (4 * WINDOW - 3, 1, 32, 32, 1),
-                                                           (3 * WINDOW, 2, 8, 8, 4), (513, 1000, 5, 5, 1), (200_000, 31, 3, 3, 4), (100_000, 7, 2, 2, 256)])
-def test_log_in_time_order(dyn, n, n_window, n_in, n_out, n_model):
+@pytest.mark.parametrize("n,n_window,n_in,n_out,n_model", [(1, 1, 1, 1, 1), (64, 1, 2, 2, 1), (WINDOW, 1, 5, 5, 1), (WINDOW + 1, 1, 5, 5, 1), (50_000, 7, 32, 32, 1),
+                                                           (3 * WINDOW, 2, 8, 8, 4), (513, 1000, 5, 5, 1), (200_000, 31, 3, 3, 4), (100_000, 7, 2, 2, 256),
+                                                           (20_000, 70, 5, 5, 1), (60_000, 70, 5, 5, 2), (120_000, 70, 32, 32, 1), (400_000, 3, 5, 5, 1)])
+@pytest.mark.parametrize("skewed", [False, True])
+def test_log_in_time_order(dyn, n, n_window, n_in, n_out, n_model, skewed):
     edges = _edges(n_in, n_out, n_model)
     tr = _log(n, n, n_window * 10.0, n_model)
+    if skewed:           # half of the requests in the last tenth: windows of several tiles beside short ones
+        tr["t_s"][::2] = n_window * 9.0 + 0.1 * tr["t_s"][::2]
     tr["t_s"].sort()
     got = _call(dyn, tr, edges, n_window, 10.0)
     assert dyn.dyn_workspace_status(got[3]) == 0
