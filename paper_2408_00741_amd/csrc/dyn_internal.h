@@ -117,6 +117,8 @@ struct WsHeader {
 };
 #define DYN_WS_HEADER_ORDER_WORD 8   // 32-bit word of a 256-byte header region used by the ingestion kernels
 #define DYN_WS_HEADER_BARRIER_WORD 9 // arrivals at the general sort's barriers, blocks that came to sort, blocks that sort (3 words, zeroed with the header)
+#define DYN_WS_HEADER_BREAK_WORD 16  // where the trace's runs after the first start, as far as there are at most DYN_WS_MAX_BREAKS
+#define DYN_WS_MAX_BREAKS 48u
 #define DYN_WS_KIND_WORD 1u
 #define DYN_WS_KIND_CELLS 2u
 
@@ -171,8 +173,8 @@ struct IngestArgs {
   int32_t* in_sorted; int32_t* out_sorted; int64_t* cell_off;
   uint32_t* status; uint32_t* key_a; uint32_t* key_b; int32_t* in_tmp; int32_t* out_tmp;
   uint32_t* block_hist; int64_t n_block; int32_t key_bits;
-  uint32_t* unsorted;      // word in the workspace header: 0 while every request's window is >= the one before
-  int32_t force_sort;      // != 0: take the general sort whatever the order (the word then starts at 1)
+  uint32_t* unsorted;      // word in the workspace header: how many requests are in a window before that of the request before them
+  int32_t force_sort;      // != 0: take the general sort whatever the order (the word then starts past DYN_WS_MAX_BREAKS)
   int64_t* win_off;        // workspace [n_window + 1]
 };
 hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s);

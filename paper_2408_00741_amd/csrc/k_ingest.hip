@@ -1,15 +1,14 @@
-// Trace ingestion: every request gets the key of its cell (window from the timestamp,
-// class from the input/output length bins of Table IV's convention), then a stable
-// least-significant-digit radix sort by key moves (input tokens, output tokens) into cell
-// order, and the cell offsets are read off the sorted keys.
+// Trace ingestion: every request goes to its cell (window from the timestamp,
+// class from the input/output length bins of Table IV's convention): (input tokens, output tokens)
+// in cell order, stably, and the cell offsets.  In general that is a least-significant-digit radix sort.
 //
 // A trace that is already in window order (a request log is in time order) does not need the
-// general sort: the key kernel notices it (a flag word in the workspace header stays 0; it also
-// writes where every window starts), and one block per window then counts its requests by class
-// and moves them, stably, to their cells (window_sort_kernel).  Any other trace takes the radix
-// sort.  The host does not read the flag: both routes are enqueued and the kernels of the route
-// not taken return at their first instruction.  The general sort is one launch with grid-wide
-// barriers between the phases, so the route not taken costs one empty launch.
+// general sort: the order kernel notices it (a word in the workspace header stays 0; it also
+// writes where every window starts), and one block per window then moves its requests, stably,
+// to their cells (window_sort_kernel).  So does a trace of a few such runs.  Any other trace takes
+// the radix sort.  The host does not read the word: all routes are enqueued and the kernels of a
+// route not taken return at their first instruction.  Runs and the general sort are one launch, so
+// what is not taken costs one empty launch.
 #include <string.h>
 
 #include <algorithm>
@@ -99,7 +98,6 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
   uint32_t bad = 0, ignore = 0;
   // the window of the request before the wave's first
   double left = base > 0 ? window_of(a.t_s[base - 1], a.window_s, r_window, a.n_window, &ignore) : -1.0;
-  bool dis = false;
 #pragma unroll
   for (int r = 0; r < kOrderRows; ++r) {
     const int64_t i = base + r * DYN_WAVE + lane;
@@ -113,28 +111,49 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
     // The boundaries only matter to the window route: a wave that sees a request out of order, or finds the flag
     // raised already, writes none (on a shuffled trace every request would otherwise fill hundreds of them).
     const bool back = in && wp > wq;
-    dis = dis || back;
     if (__ballot(in && (wp != wq || i == a.n_req - 1)) == 0) continue;
-    if (__ballot(back) == 0 && __hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && in) {
+    const uint64_t any = __ballot(back);
+    if (any != 0) {                                    // a request out of order: a run starts here
+      if (__hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= DYN_WS_MAX_BREAKS) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(a.unsorted, (uint32_t)__popcll(any));
+        at = __shfl(at, 0, DYN_WAVE) + (uint32_t)__popcll(any & ((1ull << lane) - 1ull));
+        if (back && at < DYN_WS_MAX_BREAKS) a.unsorted[DYN_WS_HEADER_BREAK_WORD - DYN_WS_HEADER_ORDER_WORD + at] = (uint32_t)i;
+      }
+      continue;
+    }
+    if (__hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && in) {
       for (int64_t w = (int64_t)wp + 1; w <= (int64_t)wq; ++w) a.win_off[w] = i;
       if (i == a.n_req - 1)
         for (int64_t w = (int64_t)wq + 1; w <= a.n_window; ++w) a.win_off[w] = a.n_req;
     }
   }
   if (bad) atomicOr(a.status, bad);
-  const uint64_t any = __ballot(dis);
-  if (any && lane == __builtin_ctzll(any) && __hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-    atomicOr(a.unsorted, 1u);
 }
 
-// The route is chosen on the device: every kernel of the two routes is launched and the kernels of the route that
-// is not taken return at once.  `order` is the flag word the order kernel leaves: 0 = every request's window is at
-// or after the window of the request before it (the trace is moved window by window), else the general sort runs.
-__device__ __forceinline__ bool sort_route(const uint32_t* order) { return *order != 0u; }
+// The route is chosen on the device: the kernels of all routes are launched and those of a route that is not taken return
+// at once.  The order word is the number of requests whose window is before that of the request before them, as the order
+// kernel left it (counted no further than past DYN_WS_MAX_BREAKS):
+//   0      the trace is moved window by window;
+//   a few  it is a few runs, each in window order (the logs of several front ends, one after the other): moved window by
+//          window too, a window being a piece of every run, which its block finds by bisection;
+//   more   the general sort.
+// Where the line lies: a window of runs costs its block 8 us and 0.3 us a run (finding the pieces, the barriers of a tile)
+// and 4 us a million requests, the sort 50 us and 30 us a million (two passes).  Measured (us by runs, sorted): 6 M requests in
+// 1440 windows and 6 runs 89, 252; 1 M in 1000 and 6: 44, 78; 50 000 in 100 and 6: 13, 50; 9 M in 6000 and 6: 243, 371;
+// 9 M in 2016 and 48: 228, 344; 300 000 in 2016 and 40: 171, 63; 9 M in 20 000 and 9: 836, 414.
+enum Route { kByWindow, kByRuns, kSort };
+__device__ __forceinline__ Route route_of(const IngestArgs& a) {
+  const uint32_t breaks = *a.unsorted;
+  if (breaks == 0) return kByWindow;
+  if (breaks > DYN_WS_MAX_BREAKS) return kSort;
+  const int64_t rounds = (a.n_window + (int64_t)gridDim.x - 1) / gridDim.x;   // of the unordered kernel (the other only asks for kByWindow)
+  return rounds * (80 + 3 * (int64_t)breaks) < 500 + a.n_req * 26 / 100000 ? kByRuns : kSort;
+}
 
 // Class edges from the kernel's arguments into the workspace (a few hundred values at most per launch): the host
 // arrays are free when the call returns and nothing waits for the stream.  The first launch also writes the
-// workspace header: status 0, the order word (1 when the general sort is forced).
+// workspace header: status 0, the order word (past DYN_WS_MAX_BREAKS when the general sort is forced).
 struct EdgePack { int32_t v[DYN_EDGE_PACK]; };
 __global__ void edge_store_kernel(EdgePack p, int n_a, int32_t* __restrict__ dst_a, int n_b, int32_t* __restrict__ dst_b,
                                   WsHeader* header, uint32_t order_word) {
@@ -201,6 +220,7 @@ struct RadixArgs {
   uint32_t* barrier; uint32_t* join; uint32_t* members;
   int64_t cells;
   int32_t passes, bits;
+  int32_t blocks;                                // that sort (the grid may have more, for the runs)
 };
 
 constexpr uint32_t kBarrierSpins = 1u << 22;     // x about a microsecond per look: seconds
@@ -257,14 +277,14 @@ struct RadixLds {
 };
 
 // Which of the sorting blocks this one is, and how many there are ({0, 0}: it came too late, or the wait was given up).  The
-// first block to arrive waits a moment for the rest of the grid and then closes the team; a block that arrives later leaves.
+// first block to arrive waits a moment for the rest of `all` and then closes the team; a block that arrives later leaves.
 // So every block that the barriers wait for is running, whatever else the device is busy with.
-__device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members, uint32_t* status, RadixLds& s) {
+__device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members, uint32_t all, uint32_t* status, RadixLds& s) {
   if (threadIdx.x == 0) {
     const uint32_t ticket = atomicAdd(join, 1u);
     uint32_t n = 0;
     if (ticket == 0) {
-      for (uint32_t spins = 0; spins < kTeamSpins && __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < gridDim.x; ++spins) __builtin_amdgcn_s_sleep(4);
+      for (uint32_t spins = 0; spins < kTeamSpins && __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all; ++spins) __builtin_amdgcn_s_sleep(4);
       n = atomicOr(join, kTeamClosed);
       put(members, n);
     } else if (ticket < kTeamClosed) {
@@ -501,70 +521,6 @@ __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_
   if (at < end) radix_tile<false>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, (int)(end - at), shift, bits, next, s);
 }
 
-__global__ __launch_bounds__(kRadixThreads) void radix_route_kernel(RadixArgs g) {
-  const IngestArgs& a = g.t;
-  if (!sort_route(a.unsorted)) return;              // the same word for every block: all leave, or none
-  __shared__ RadixLds s;
-  const RadixTeam m = join_team(g.join, g.members, a.status, s);
-  if (m.blocks == 0) return;
-  uint32_t passed = 0;                           // barriers behind this block
-  auto sync = [&]() {
-    ++passed;
-    const bool ok = grid_barrier(g.barrier, passed * (uint32_t)m.blocks, &s.flag);
-    if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
-    return ok;
-  };
-  const int n_tile = (int)((a.n_req + kRadixTile - 1) / kRadixTile);
-  const int tiles = n_tile / m.blocks, more = n_tile % m.blocks;   // the first `more` blocks take one tile more
-  const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kRadixTile;
-  const int64_t end = std::min<int64_t>(a.n_req, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
-  radix_keys(a, g.r_window, beg, end, s);
-  const uint32_t* k_src = a.key_a;
-  uint32_t* k_dst = a.key_b;
-  const int32_t *i_src = a.in_tok, *o_src = a.out_tok;
-  for (int p = 0; p < g.passes; ++p) {
-    const bool to_final = ((g.passes - 1 - p) % 2) == 0;   // ping-pong so that the last pass lands in the caller's arrays
-    int32_t* i_dst = to_final ? a.in_sorted : a.in_tmp;
-    int32_t* o_dst = to_final ? a.out_sorted : a.out_tmp;
-    const int shift = p * g.bits;
-    radix_count(k_src, beg, end, shift, g.bits, a.block_hist, m, s);
-    if (!sync()) return;
-    radix_scan(a.block_hist, g.bits, m);
-    if (!sync()) return;
-    radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, g.bits, a.block_hist, m, s);
-    if (!sync()) return;
-    i_src = i_dst;
-    o_src = o_dst;
-    uint32_t* old_src = const_cast<uint32_t*>(k_src);      // both key buffers live in the workspace
-    k_src = k_dst;
-    k_dst = old_src;
-  }
-  if (a.n_req == 0)
-    for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
-  // the offsets: a block goes over its run of the sorted keys, every key beside the one before it
-  for (int64_t at = beg; at < end; at += kRadixTile) {
-    uint32_t key[kRadixItems], left[kRadixItems];
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
-      key[r] = k_src[i];
-      left[r] = k_src[i > 0 ? i - 1 : 0];
-    }
-#pragma unroll 1
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int64_t i = at + r * kRadixThreads + threadIdx.x;
-      uint32_t k = key[0], l = left[0];
-#pragma unroll
-      for (int q = 1; q < kRadixItems; ++q) {
-        k = r == q ? key[q] : k;
-        l = r == q ? left[q] : l;
-      }
-      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n_req, g.cells, a.cell_off);
-      if (i == a.n_req - 1) offsets_at(a.n_req, k, g.cells, a.n_req, g.cells, a.cell_off);
-    }
-  }
-}
-
 // ---- a trace in window order ----------------------------------------------------------------
 // One block per window.  The requests are ranked by class as in the general sort (a wave walks rows of 64 in order, ranks
 // inside a row from ballots), put in class order in LDS and written from there: the window's part of the output is one
@@ -591,15 +547,84 @@ struct WinLds {
   uint32_t wave_sum[WAVES];
 };
 
+// The window's pieces in a trace of several runs: where the run starts, the piece's bounds; then the piece's end in the
+// window, what to add to a place in the window to have the request's index, and the window's first output position and length.
+struct RunLds {
+  uint32_t run_start[DYN_WS_MAX_BREAKS + 2], bound[2 * (DYN_WS_MAX_BREAKS + 1)];
+  int32_t piece_end[DYN_WS_MAX_BREAKS + 1];
+  uint32_t piece_add[DYN_WS_MAX_BREAKS + 1];
+  uint32_t out[2];
+};
+constexpr int kRunEdges = 2048;
+
 // Element i of a run of 4-byte values, i * 4 < 2^32: one 32-bit offset instead of a 64-bit address.
 template <typename T>
 __device__ __forceinline__ T& at32(T* p, uint32_t i) { return *(T*)((char*)p + (i << 2)); }
 
+// Index of the request at place j of the window; `piece`: that of a place before it.
+__device__ __forceinline__ uint32_t window_request(const RunLds& s, uint32_t j, int& piece) {
+  while ((int)j >= s.piece_end[piece]) ++piece;
+  return s.piece_add[piece] + j;
+}
+
+// The pieces of window w in a trace of several runs (the breaks come in any order).
+template <int THREADS>
+__device__ __forceinline__ void find_pieces(const IngestArgs& a, double r_window, int w, RunLds& s) {
+  const uint32_t* breaks = a.unsorted + (DYN_WS_HEADER_BREAK_WORD - DYN_WS_HEADER_ORDER_WORD);
+  const int n_break = (int)*a.unsorted, n_run = n_break + 1, lane = threadIdx.x;
+  if (lane < n_break) {
+    const uint32_t mine = breaks[lane];
+    int rank = 1;
+    for (int q = 0; q < n_break; ++q) rank += breaks[q] < mine ? 1 : 0;
+    s.run_start[rank] = mine;
+  }
+  if (lane == 0) {
+    s.run_start[0] = 0;
+    s.run_start[n_run] = (uint32_t)a.n_req;
+  }
+  __syncthreads();
+  // first request of the run in window w (q even) or after it: a wave per question, 64 probes a step
+  for (int q = threadIdx.x / DYN_WAVE; q < 2 * n_run; q += THREADS / DYN_WAVE) {
+    uint32_t lo = s.run_start[q >> 1], hi = s.run_start[(q >> 1) + 1], ignore = 0;
+    const double at = (double)(w + (q & 1));
+    while (lo < hi) {                              // requests before lo lie in earlier windows, those from hi on do not
+      const uint32_t step = (hi - lo + DYN_WAVE - 1) / DYN_WAVE;
+      const uint64_t mine = (uint64_t)lo + (uint64_t)(threadIdx.x & (DYN_WAVE - 1)) * step + (step - 1);   // the last of the lane's share
+      const bool early = mine < hi && window_of(a.t_s[mine < hi ? mine : hi - 1], a.window_s, r_window, a.n_window, &ignore) < at;
+      const uint32_t shares = (uint32_t)__popcll(__ballot(early));
+      const uint64_t next = (uint64_t)lo + (uint64_t)shares * step;
+      lo = next < hi ? (uint32_t)next : hi;
+      if (next + step - 1 < hi) hi = (uint32_t)(next + step - 1);
+    }
+    if ((threadIdx.x & (DYN_WAVE - 1)) == 0) s.bound[q] = lo;
+  }
+  __syncthreads();
+  if (lane < DYN_WAVE) {
+    const uint32_t from = lane < n_run ? s.bound[2 * lane] : 0u, len = lane < n_run ? s.bound[2 * lane + 1] - from : 0u;
+    uint32_t end = len, before = lane < n_run ? from - s.run_start[lane] : 0u;
+#pragma unroll
+    for (int k = 1; k < DYN_WAVE; k <<= 1) {
+      const uint32_t up = __shfl_up(end, k, DYN_WAVE);
+      before += __shfl_xor(before, k, DYN_WAVE);
+      if (lane >= k) end += up;
+    }
+    if (lane < n_run) {
+      s.piece_end[lane] = (int32_t)end;
+      s.piece_add[lane] = from - (end - len);
+    }
+    if (lane == DYN_WAVE - 1) {
+      s.out[0] = before;
+      s.out[1] = end;
+    }
+  }
+  __syncthreads();
+}
+
 // One tile of `count` requests; LONG: of a window of several tiles.  `next`: place in the window of the next request of each
 // class that the thread owns (set here for a window of one tile).  `off`: the window's cell offsets, written by its first tile.
-template <int WAVES, int ITEMS, bool LONG>
+template <int WAVES, int ITEMS, bool LONG, bool RUNS>
 __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdges& edges, const int32_t* in_in, const int32_t* out_in, const int32_t* model,
-                                            int32_t* in_out, int32_t* out_out, int count, int bits, int G, int64_t beg, int64_t* off, uint32_t* next, uint32_t* bad, WinLds<WAVES, ITEMS>& s) {
+                                            int32_t* in_out, int32_t* out_out, int tile, int count, int bits, int G, int64_t beg, int64_t* off, uint32_t* next, uint32_t* bad, WinLds<WAVES, ITEMS>& s, const RunLds* p) {
   constexpr int kThreads = WAVES * DYN_WAVE, kOwn = WinLds<WAVES, ITEMS>::kOwn;
   constexpr int N = 8;                             // rows whose classes are computed together
   const int nbins = 1 << bits, own = (nbins + kThreads - 1) / kThreads;   // classes, and those a thread owns: threadIdx.x * own ...
@@ -608,13 +633,21 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
   const int at = wave * rows * DYN_WAVE + lane;
   uint32_t place[ITEMS];                       // class << 16 | rank in the wave, later the place in the tile
   int32_t vin[ITEMS], vout[ITEMS];
+  int piece = 0;                                   // the lane's places only grow
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r)
     if (r / N * N < rows) {
       const uint32_t i = (uint32_t)min(at + r * DYN_WAVE, count - 1);
-      vin[r] = at32(in_in, i);
-      vout[r] = at32(out_in, i);
+      if (RUNS) {
+        const uint32_t j = window_request(*p, (uint32_t)tile + i, piece);
+        vin[r] = in_in[j];
+        vout[r] = out_in[j];
+      } else {
+        vin[r] = at32(in_in, i);
+        vout[r] = at32(out_in, i);
+      }
     }
+  piece = 0;
 #pragma unroll
   for (int v = 0; v < WAVES; ++v)
     for (int b = threadIdx.x; b < nbins; b += kThreads) s.wcnt[v][b] = 0;
@@ -628,7 +661,11 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
     int32_t mdl[N];
     uint32_t cls[N];
 #pragma unroll
-    for (int r = 0; r < N; ++r) mdl[r] = model ? at32(model, (uint32_t)min(at + (g + r) * DYN_WAVE, count - 1)) : 0;
+    for (int r = 0; r < N; ++r) {
+      const uint32_t i = (uint32_t)min(at + (g + r) * DYN_WAVE, count - 1);
+      mdl[r] = 0;
+      if (model) mdl[r] = RUNS ? model[window_request(*p, (uint32_t)tile + i, piece)] : at32(model, i);
+    }
     classes_of<N>(a, edges, vin + g, vout + g, mdl, cls, bad);
 #pragma unroll
     for (int r = 0; r < N; ++r) {
@@ -718,43 +755,39 @@ __device__ __forceinline__ void window_tile(const IngestArgs& a, const ClassEdge
   write(out_out);
 }
 
-template <int WAVES, int ITEMS, int PER_SIMD>
-__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD))) void window_sort_kernel(IngestArgs a, int edge_room) {
-  if (sort_route(a.unsorted)) return;
+// A window: `len` requests whose output starts at `beg`.
+template <int WAVES, int ITEMS, bool RUNS>
+__device__ __forceinline__ void window_move(const IngestArgs& a, int w, int64_t beg, int len, const ClassEdges& edges, WinLds<WAVES, ITEMS>& s, const RunLds* p = nullptr) {
   constexpr int kThreads = WAVES * DYN_WAVE, kTile = kThreads * ITEMS, kOwn = WinLds<WAVES, ITEMS>::kOwn;
-  __shared__ WinLds<WAVES, ITEMS> s;
-  extern __shared__ int32_t s_edge[];
   const int32_t G = a.n_model * a.n_in_bin * a.n_out_bin;
-  const int w = blockIdx.x;
-  const int64_t beg = a.win_off[w];
-  const int len = (int)(a.win_off[w + 1] - beg);
   int64_t* off = a.cell_off + (int64_t)w * G;
-  if (w == a.n_window - 1 && threadIdx.x == 0) off[G] = a.n_req;
   if (len <= 0) {
     for (int d = threadIdx.x; d < G; d += kThreads) off[d] = beg;
     return;
   }
-  const int32_t* in_in = a.in_tok + beg;
-  const int32_t* out_in = a.out_tok + beg;
-  const int32_t* model = a.model ? a.model + beg : nullptr;
+  const int64_t from = RUNS ? 0 : beg;             // what the requests are counted from
+  const int32_t* in_in = a.in_tok + from;
+  const int32_t* out_in = a.out_tok + from;
+  const int32_t* model = a.model ? a.model + from : nullptr;
   int32_t* in_out = a.in_sorted + beg;
   int32_t* out_out = a.out_sorted + beg;
-  const ClassEdges edges = stage_edges(a, s_edge, edge_room);
   uint32_t bad = 0;
   int bits = 0;
   while ((1 << bits) < G) ++bits;
   uint32_t next[kOwn];
   if (len <= kTile) {
-    window_tile<WAVES, ITEMS, false>(a, edges, in_in, out_in, model, in_out, out_out, len, bits, G, beg, off, next, &bad, s);
+    window_tile<WAVES, ITEMS, false, RUNS>(a, edges, in_in, out_in, model, in_out, out_out, 0, len, bits, G, beg, off, next, &bad, s, p);
   } else {
     for (int d = threadIdx.x; d < DYN_INGEST_MAX_BINS; d += kThreads) s.cnt[d] = 0;
     __syncthreads();
+    int piece = 0;
     for (int at = 0; at < len; at += 4 * kThreads) {
       int32_t x[4], y[4], mdl[4];
       uint32_t d[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = min(at + r * kThreads + (int)threadIdx.x, len - 1);
+        uint32_t i = (uint32_t)min(at + r * kThreads + (int)threadIdx.x, len - 1);
+        if (RUNS) i = window_request(*p, i, piece);
         x[r] = in_in[i];
         y[r] = out_in[i];
         mdl[r] = model ? model[i] : 0;
@@ -778,11 +811,115 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
     }
     for (int tile = 0; tile < len; tile += kTile) {
       __syncthreads();                             // what the counts or the last tile left in LDS has been read
-      window_tile<WAVES, ITEMS, true>(a, edges, in_in + tile, out_in + tile, model ? model + tile : nullptr, in_out, out_out, min(kTile, len - tile), bits, G, beg,
-                        tile == 0 ? off : nullptr, next, &bad, s);
+      const int skip = RUNS ? 0 : tile;
+      window_tile<WAVES, ITEMS, true, RUNS>(a, edges, in_in + skip, out_in + skip, model ? model + skip : nullptr, in_out, out_out, tile, min(kTile, len - tile), bits, G,
+                                            beg, tile == 0 ? off : nullptr, next, &bad, s, p);
     }
   }
   if (bad) atomicOr(a.status, bad);
+}
+
+template <int WAVES, int ITEMS, int PER_SIMD>
+__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD))) void window_sort_kernel(IngestArgs a, int edge_room) {
+  if (route_of(a) != kByWindow) return;
+  __shared__ WinLds<WAVES, ITEMS> s;
+  extern __shared__ int32_t s_edge[];
+  const int w = blockIdx.x;
+  const int64_t beg = a.win_off[w];
+  const int len = (int)(a.win_off[w + 1] - beg);
+  if (w == a.n_window - 1 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
+  const ClassEdges edges = stage_edges(a, s_edge, edge_room);
+  window_move<WAVES, ITEMS, false>(a, w, beg, len, edges, s);
+}
+
+// A trace of a few runs, window by window; the blocks share the windows.
+__device__ __forceinline__ void runs_route(const IngestArgs& a, double r_window, WinLds<kRadixWaves, kRadixItems>& s, RunLds& p, int32_t* s_edge) {
+  const ClassEdges edges = stage_edges(a, s_edge, kRunEdges);
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
+  for (int w = blockIdx.x; w < a.n_window; w += gridDim.x) {
+    find_pieces<kRadixThreads>(a, r_window, w, p);
+    window_move<kRadixWaves, kRadixItems, true>(a, w, p.out[0], (int)p.out[1], edges, s, &p);
+    __syncthreads();
+  }
+}
+
+// A trace that is not in window order.
+__global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
+  const IngestArgs& a = g.t;
+  const Route route = route_of(a);               // the same for every block
+  if (route == kByWindow) return;
+  __shared__ union {
+    RadixLds radix;
+    struct {
+      WinLds<kRadixWaves, kRadixItems> win;
+      RunLds run;
+      int32_t edge[kRunEdges];
+    } runs;
+  } lds;
+  if (route == kByRuns) {
+    runs_route(a, g.r_window, lds.runs.win, lds.runs.run, lds.runs.edge);
+    return;
+  }
+  if ((int)blockIdx.x >= g.blocks) return;
+  RadixLds& s = lds.radix;
+  const RadixTeam m = join_team(g.join, g.members, (uint32_t)g.blocks, a.status, s);
+  if (m.blocks == 0) return;
+  uint32_t passed = 0;                           // barriers behind this block
+  auto sync = [&]() {
+    ++passed;
+    const bool ok = grid_barrier(g.barrier, passed * (uint32_t)m.blocks, &s.flag);
+    if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
+    return ok;
+  };
+  const int n_tile = (int)((a.n_req + kRadixTile - 1) / kRadixTile);
+  const int tiles = n_tile / m.blocks, more = n_tile % m.blocks;   // the first `more` blocks take one tile more
+  const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kRadixTile;
+  const int64_t end = std::min<int64_t>(a.n_req, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
+  radix_keys(a, g.r_window, beg, end, s);
+  const uint32_t* k_src = a.key_a;
+  uint32_t* k_dst = a.key_b;
+  const int32_t *i_src = a.in_tok, *o_src = a.out_tok;
+  for (int p = 0; p < g.passes; ++p) {
+    const bool to_final = ((g.passes - 1 - p) % 2) == 0;   // ping-pong so that the last pass lands in the caller's arrays
+    int32_t* i_dst = to_final ? a.in_sorted : a.in_tmp;
+    int32_t* o_dst = to_final ? a.out_sorted : a.out_tmp;
+    const int shift = p * g.bits;
+    radix_count(k_src, beg, end, shift, g.bits, a.block_hist, m, s);
+    if (!sync()) return;
+    radix_scan(a.block_hist, g.bits, m);
+    if (!sync()) return;
+    radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, g.bits, a.block_hist, m, s);
+    if (!sync()) return;
+    i_src = i_dst;
+    o_src = o_dst;
+    uint32_t* old_src = const_cast<uint32_t*>(k_src);      // both key buffers live in the workspace
+    k_src = k_dst;
+    k_dst = old_src;
+  }
+  if (a.n_req == 0)
+    for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
+  // the offsets: a block goes over its run of the sorted keys, every key beside the one before it
+  for (int64_t at = beg; at < end; at += kRadixTile) {
+    uint32_t key[kRadixItems], left[kRadixItems];
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) {
+      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
+      key[r] = k_src[i];
+      left[r] = k_src[i > 0 ? i - 1 : 0];
+    }
+#pragma unroll 1
+    for (int r = 0; r < kRadixItems; ++r) {
+      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      uint32_t k = key[0], l = left[0];
+#pragma unroll
+      for (int q = 1; q < kRadixItems; ++q) {
+        k = r == q ? key[q] : k;
+        l = r == q ? left[q] : l;
+      }
+      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n_req, g.cells, a.cell_off);
+      if (i == a.n_req - 1) offsets_at(a.n_req, k, g.cells, a.n_req, g.cells, a.cell_off);
+    }
+  }
 }
 
 }  // namespace
@@ -866,6 +1003,8 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   const int64_t room = ((int64_t)DYN_INGEST_MAX_BINS * a.n_block) >> bits;
   const int64_t n_tile = (n + kRadixTile - 1) / kRadixTile;
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({(int64_t)n_cu, n_tile, room}));
-  hipLaunchKernelGGL(radix_route_kernel, dim3((unsigned)blocks), dim3(kRadixThreads), 0, s, r);
+  r.blocks = (int32_t)blocks;
+  const int64_t grid = a.force_sort ? blocks : std::max<int64_t>(blocks, std::min<int64_t>(n_cu, a.n_window));
+  hipLaunchKernelGGL(unordered_kernel, dim3((unsigned)grid), dim3(kRadixThreads), 0, s, r);
   return hipGetLastError();
 }

@@ -71,6 +71,26 @@ def test_log_in_time_order(dyn, n, n_window, n_in, n_out, n_model, skewed):
     _check(got, tr, edges, n_window, 10.0)
 
 
+# the logs of several front ends, one after the other: fewer and more runs than the route takes, a run of one request, runs
+# of different parts of the day, windows of several tiles, and (2000 windows of 30 000 requests) the sort all the same
+@pytest.mark.parametrize("n,n_window,n_run,n_model", [(2, 2, 2, 1), (5_000, 5, 5, 1), (100_000, 100, 48, 1), (100_000, 100, 49, 4), (100_000, 100, 50, 1), (100_000, 60, 300, 1),
+                                                      (30_000, 2000, 9, 1), (900_000, 45, 7, 4), (1_500_000, 60, 3, 1)])
+@pytest.mark.parametrize("apart", [False, True])
+def test_log_of_several_runs(dyn, n, n_window, n_run, n_model, apart):
+    edges = _edges(5, 5, n_model)
+    tr = _log(n, n, n_window * 10.0, n_model)
+    cut = [n * r // n_run for r in range(n_run + 1)]
+    if n_run > 2:
+        cut[1] = 1
+    for r, (a, b) in enumerate(zip(cut[:-1], cut[1:])):
+        if apart:        # a run covers a part of the windows: others have no piece of it
+            tr["t_s"][a:b] = n_window * 10.0 * (r % 3 + tr["t_s"][a:b] / (n_window * 10.0)) / 3.0
+        tr["t_s"][a:b] = np.sort(tr["t_s"][a:b])
+    got = _call(dyn, tr, edges, n_window, 10.0)
+    assert dyn.dyn_workspace_status(got[3]) == 0
+    _check(got, tr, edges, n_window, 10.0)
+
+
 def test_edges_that_stay_in_global_memory(dyn):
     """One class axis of 900 bins and three models: 2697 edges, more than a block stages (and more classes than the window route)."""
     edges = _edges(900, 1, 3)
