@@ -8,7 +8,9 @@
 // input length x a non-negative constant, so the cell's j-th largest TTFT (j = m - rank + 1)
 // is among the j largest input lengths of each tick scaled by that tick's prefill time.
 // The request stream is read once, independent of the configurations:
-//   tick_cell_kernel   per cell every tick's load, its min(j, count) largest input lengths in
+//   tick_tight_kernel, tick_tight_block_kernel  the cells whose percentile is settled without lists (below), and the lists
+//                      of long cells and of few ones;
+//   tick_cell_kernel   of the cells left, per cell every tick's load, its min(j, count) largest input lengths in
 //                      descending order (j <= 64: kept sorted in a wave's lanes) and the cell's
 //                      j-th largest input length x_j; what the later kernels do with the cell;
 //   tick_deep_kernel   the same lists and x_j for the cells with j > 64 (a block per cell:
@@ -69,6 +71,11 @@ __device__ __forceinline__ uint32_t tbt_route(int32_t cnt_l, int64_t j64, int la
   }
   if (all_in || s4 >= j64) flags |= DYN_TP_SMALL;
   return flags;
+}
+
+// The walk kernel keeps a register list of 16 candidates beside the largest tick TBT, of 8 beside the four largest.
+__device__ __forceinline__ bool walks_with_lists(uint32_t flags, int64_t j64) {
+  return ((flags & DYN_TP_DENSE) && j64 <= kFastDepth) || ((flags & DYN_TP_SMALL) && j64 <= kFastDepth / 2);
 }
 
 // ---- cells settled by their ties at x_j ----------------------------------------------------------
@@ -328,8 +335,9 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 #define DYN_LIST_DONE 0xFFFFFFFFu
 constexpr int kTightBlocks = 1024;
 
+enum BlockCell { kNotTaken, kSettled, kBoundFails };   // kBoundFails: token sums and x_j are known, the ticks' lists are needed
 template <int P>   // P registers = 2P rows per wave
-__device__ __forceinline__ bool tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
+__device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
                                                  int64_t beg_l, int32_t cnt_l, int T, int rpt, int m, int rank, float theta,
                                                  int lane, int wave, uint32_t* s_x /* [2][kWavesPerBlock] */,
                                                  uint32_t* s_m /* [4 * kWavesPerBlock] */, TightCell* res) {
@@ -405,7 +413,7 @@ __device__ __forceinline__ bool tight_cell_block(const int32_t* __restrict__ in,
   };
   const uint32_t all_or = block_or(wave_or_u32(orv));
   const uint32_t top = block_max(wave_max_u32(vmax));
-  if (all_or >= (1u << 16) || top == 0xFFFFu) return false;   // block-uniform; 0xFFFF is the padding value
+  if (all_or >= (1u << 16) || top == 0xFFFFu) return kNotTaken;   // block-uniform; 0xFFFF is the padding value
   uint32_t xj = top;
   const int j = m - rank + 1;
   if (rank != m) {
@@ -423,7 +431,9 @@ __device__ __forceinline__ bool tight_cell_block(const int32_t* __restrict__ in,
     }
     xj = d;
   }
-  if (!((double)theta * ((double)xj + 1.0) > (double)xj)) return false;
+  res->tok_l = tok_l;                    // lanes q with q % 4 == wave
+  res->xj = xj;
+  if (!((double)theta * ((double)xj + 1.0) > (double)xj)) return kBoundFails;
   int n_gt = 0, n_eq = 0, eq_acc = 0;      // the padding (0xFFFF) counts as longer: taken off after the block's sum
   uint32_t eq_l = 0;
   q = wave; r = 0;
@@ -471,16 +481,80 @@ __device__ __forceinline__ bool tight_cell_block(const int32_t* __restrict__ in,
     place = (uint32_t)(n_eq - need + 1) | DYN_TIGHT_FROM_BELOW;
   }
   res->need = (uint32_t)need;
-  res->tok_l = tok_l;                    // lanes q with q % 4 == wave
   res->eq_l = eq_l;
-  res->xj = xj;
   res->place = place;
-  return true;
+  return kSettled;
 }
 
-__global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_tight_block_kernel(TickCellArgs a) {
+// The n_top largest of a tick's `cnt` input lengths (all below 2^16, cnt <= kListTick) in descending order to dst, by one
+// wave in LDS: the n_top-th largest by a bit-wise search, what is above it gathered in place, the rest of the places
+// filled with it, a bitonic sort of that many.
+constexpr int kListTick = 2048;
+__device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int cnt, int n_top, int32_t* dst, int32_t* buf, int lane) {
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  int32_t mx = 0;
+  for (int i0 = 0; i0 < cnt; i0 += 8 * DYN_WAVE) {
+    int32_t x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = src[min(i0 + u * DYN_WAVE + lane, cnt - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      mx = max(mx, x[u]);
+      if (i0 + u * DYN_WAVE + lane < cnt) buf[i0 + u * DYN_WAVE + lane] = x[u];
+    }
+  }
+  wave_sync();
+  if (n_top < cnt) {
+    int32_t thr = 0;
+    for (int b = 31 - __builtin_clz((uint32_t)wave_max_i32(mx) | 1u); b >= 0; --b) {
+      const int32_t cand = thr | (1 << b);
+      int above = 0;
+      for (int i0 = 0; i0 < cnt; i0 += 4 * DYN_WAVE) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = i0 + u * DYN_WAVE + lane;
+          above += __popcll(__ballot(i < cnt && buf[min(i, cnt - 1)] >= cand));
+        }
+      }
+      if (above >= n_top) thr = cand;
+    }
+    int got = 0;                                   // fewer than n_top values are above thr
+    for (int i0 = 0; i0 < cnt; i0 += DYN_WAVE) {
+      const int32_t x = i0 + lane < cnt ? buf[i0 + lane] : 0;
+      const bool take = i0 + lane < cnt && x > thr;
+      const uint64_t who = __ballot(take);
+      wave_sync();                                 // the row is read before places in it are written
+      if (take) buf[got + __popcll(who & ((1ull << lane) - 1ull))] = x;
+      got += __popcll(who);
+    }
+    wave_sync();
+    for (int i = got + lane; i < n_top; i += DYN_WAVE) buf[i] = thr;
+  }
+  int n2 = 2;
+  while (n2 < n_top) n2 <<= 1;                     // at most kListTick
+  for (int i = n_top + lane; i < n2; i += DYN_WAVE) buf[i] = -1;
+  wave_sync();
+  for (int k = 2; k <= n2; k <<= 1)
+    for (int d = k >> 1; d > 0; d >>= 1) {
+      for (int p = lane; p < n2 / 2; p += DYN_WAVE) {
+        const int i = ((p & ~(d - 1)) << 1) | (p & (d - 1)), o = i | d;   // the pair's places
+        const int32_t u = buf[i], v = buf[o];
+        const bool down = (i & k) == 0;            // descending runs first: the whole ends descending
+        if (down ? u < v : u > v) { buf[i] = v; buf[o] = u; }
+      }
+      wave_sync();
+    }
+  for (int i = lane; i < n_top; i += DYN_WAVE) dst[i] = buf[i];
+  wave_sync();                                     // buf is reused
+}
+
+__global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_tight_block_kernel(TickCellArgs a) {
   __shared__ uint32_t s_x[2 * kWavesPerBlock];
   __shared__ uint32_t s_m[4 * kWavesPerBlock];
+  __shared__ int32_t s_list[kWavesPerBlock][kListTick];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int T = a.n_tick, G = a.G;
@@ -506,7 +580,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_tight_block_ker
     const int rows = ((T + kWavesPerBlock - 1) / kWavesPerBlock) * rpt;   // rows of the wave with most ticks
     TightCell tc;
     tc.tok_l = 0; tc.eq_l = 0; tc.xj = 0; tc.place = 0; tc.need = 0; tc.walk = true;
-    bool done = false;                           // block-uniform from here on
+    BlockCell done = kNotTaken;                  // block-uniform from here on
     if (m_cell > 0 && m_cell < (1 << 24) && rows <= 128) {
       const float theta = a.theta[g];
       const int m = (int)m_cell, rk = (int)rank;
@@ -515,11 +589,27 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_tight_block_ker
       else done = tight_cell_block<64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
     }
     __syncthreads();                             // s_x is reused by the next item
-    if (!done) continue;
-    uint32_t flags = tbt_route(cnt_l, j64, lane) | DYN_TP_TIGHT;
-    if (!tc.walk || !(flags & (DYN_TP_DENSE | DYN_TP_SMALL))) {
-      flags |= DYN_TP_GENERAL;
-      tc.place = tc.need;
+    if (done == kNotTaken) continue;
+    uint32_t flags = tbt_route(cnt_l, j64, lane);
+    if (done == kSettled) {
+      flags |= DYN_TP_TIGHT;
+      if (!tc.walk || !(flags & (DYN_TP_DENSE | DYN_TP_SMALL))) {
+        flags |= DYN_TP_GENERAL;
+        tc.place = tc.need;
+      }
+    } else {
+      // Its lists, a tick per wave at a time, where that is better than what follows: few cells on the whole device, or a
+      // list beyond the 64 entries that one wave keeps sorted (a block per cell, tick after tick).  540 cells of up to
+      // 6800 requests and 12 ticks: 84 us in this kernel; 26, then 227 in tick_cell_kernel and 462 in tick_deep_kernel without.
+      if (!(a.few_cells || j64 > DYN_TICK_WAVE) || j64 > DYN_TICK_DEPTH || wave_max_u32((uint32_t)cnt_l) > kListTick) continue;
+      for (int q = wave; q < T; q += kWavesPerBlock) {
+        const int64_t beg_q = readlane_i64(beg_l, q);
+        const int cnt_q = __builtin_amdgcn_readlane(cnt_l, q);
+        if (cnt_q > 0) tick_list(a.in + beg_q, cnt_q, j64 < cnt_q ? (int)j64 : cnt_q, a.top + beg_q, s_list[wave], lane);
+      }
+      if (j64 > DYN_TICK_WAVE) flags |= DYN_TP_DEEP;
+      flags |= walks_with_lists(flags, j64) ? 0u : DYN_TP_GENERAL;
+      tc.eq_l = (uint32_t)beg_l;                 // where the tick's list is (n_req < 2^31)
     }
     if (lane < T && (lane % kWavesPerBlock) == wave) {   // the wave that walked the tick
       TickRec r;
@@ -537,6 +627,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_tight_block_ker
       p.place = tc.place;
       a.plan[c] = p;
       if (flags & DYN_TP_GENERAL) a.slow_list[atomicAdd(&a.counters[1], 1u)] = (uint32_t)c;
+      else if (done == kBoundFails) atomicAdd(&a.counters[3], 1u);   // a cell the walk takes with its lists
       a.list_cells[item] = DYN_LIST_DONE;
     }
   }
@@ -587,9 +678,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_cell_kernel(Tic
   uint32_t flags = raw ? DYN_TP_RAW : (deep ? DYN_TP_DEEP : 0u);
   if (m_cell > 0) {
     flags |= tbt_route(cnt_l, j64, lane);
-    // the walk kernel keeps a register list of 16 candidates beside the largest tick TBT, of 8 beside the four largest
-    const bool walk = ((flags & DYN_TP_DENSE) && j64 <= kFastDepth) || ((flags & DYN_TP_SMALL) && j64 <= kFastDepth / 2);
-    if (raw || !walk) flags |= DYN_TP_GENERAL;
+    if (raw || !walks_with_lists(flags, j64)) flags |= DYN_TP_GENERAL;
   }
 
   int32_t* buf = s_buf[wave];

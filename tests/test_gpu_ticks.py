@@ -203,6 +203,23 @@ def test_deep_percentiles_with_load_dependent_prefill(dyn, n_req, NW, T, crowd):
     assert j.max() > 16
 
 
+@pytest.mark.parametrize("n_req,NW,T,crowd", [(2048, 1, 1, None), (2049, 1, 1, None), (2047 * 3, 1, 3, None), (6600, 1, 3, 2300), (64 * 12, 1, 12, None), (13_000, 1, 12, None), (130, 2, 5, None)])
+@pytest.mark.parametrize("pct", [(99, 100), (1, 2), (1, 100), (1, 1)])
+def test_lists_of_a_few_cells(dyn, n_req, NW, T, crowd, pct):
+    """Cells whose lists a block builds, a tick per wave: ticks of up to 2048 requests and one more, lists of whole ticks, of
+    one entry, of more entries than a tick holds, more and fewer ticks than waves; a prefill time that rises with the load."""
+    w = _one_class(make(SPECS[1].scaled(n_req, NW)))
+    r = w["profile"]["rho"]
+    w["profile"]["prefill_ms_per_tok"] = w["profile"]["prefill_ms_per_tok"] * (1.0 + 0.8 * r * r)
+    if crowd:
+        w["trace"]["t_s"][:crowd] = 0.25 * w["window_s"] / T
+        w["trace"]["t_s"].sort()
+    w["configs"] = {k: v[::7].copy() for k, v in w["configs"].items()}
+    g, fine = gpu_ticks(dyn, w, T, pct=pct)
+    assert g["status"] == 0
+    assert_same(w, g, ora_ticks(w, fine, T, pct=pct))
+
+
 @pytest.mark.parametrize("kind", ["flat", "zero", "narrow", "wide"])
 @pytest.mark.parametrize("pct", [(99, 100), (9, 10)])
 def test_walk_lists_pruned_by_the_prefill_spread(dyn, kind, pct):
