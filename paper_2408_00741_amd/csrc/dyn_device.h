@@ -111,16 +111,12 @@ __device__ __forceinline__ double min_num(double a, double b) {
   return r;
 }
 
-// Tables at (f, min(rho, rho_max)) for load `load` (>= 0): the window-level kernel's arithmetic.
 // SINGLE: every bucket of the load axis holds at most one interior grid point, so the bracket
 // is the bucket's start index plus one comparison; otherwise the bracket is searched from the
-// bucket's index.  TWO: both frequency rows are combined (weight 0 on the upper row leaves
-// the lower row's value unchanged, so lanes with a profiled frequency may run it too).
-template <bool SINGLE, bool TWO>
-__device__ __forceinline__ bool table_lookup(const Lookup& L, double load, double* pf, double* tb, double* pw) {
-  const double rho = div_by(load, L.den, L.rden);
-  const bool ov = rho > L.rho_max;
-  const double rc = ov ? L.rho_max : rho;
+// bucket's index.
+// The bracket of the load axis that rc = min(rho, rho_max) lies in, and its weight there.
+template <bool SINGLE>
+__device__ __forceinline__ int table_bracket(const Lookup& L, double rc, double* t) {
   int jj;
   if (SINGLE) {
     const int b = (int)(rc * L.bucket_scale);
@@ -131,7 +127,19 @@ __device__ __forceinline__ bool table_lookup(const Lookup& L, double load, doubl
     while (jj < L.n_rho - 2 && L.rgp[jj + 2] <= rc) ++jj;
   }
   const double r0 = L.rgp[jj + 1], r1 = L.rgp[jj + 2];
-  const double t = div_by(rc - r0, r1 - r0, L.rinv[jj + 1]);
+  *t = div_by(rc - r0, r1 - r0, L.rinv[jj + 1]);
+  return jj;
+}
+
+// Tables at (f, min(rho, rho_max)) for load `load` (>= 0): the window-level kernel's arithmetic.
+// TWO: both frequency rows are combined (weight 0 on the upper row leaves
+// the lower row's value unchanged, so lanes with a profiled frequency may run it too).
+template <bool SINGLE, bool TWO>
+__device__ __forceinline__ bool table_lookup(const Lookup& L, double load, double* pf, double* tb, double* pw) {
+  const double rho = div_by(load, L.den, L.rden);
+  const bool ov = rho > L.rho_max;
+  double t;
+  const int jj = table_bracket<SINGLE>(L, ov ? L.rho_max : rho, &t);
   const double omt = 1.0 - t;
   const int n_rho = L.n_rho;
   double x_pf = omt * L.lo[jj] + t * L.lo[jj + 1];

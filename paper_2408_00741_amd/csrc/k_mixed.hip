@@ -190,15 +190,20 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
     double best = __builtin_inf();
     int bf = -1;
     for (int f = 0; f < n_f; ++f) {                              // ascending: the lowest frequency wins equal energies
-      L.den = den[f];
-      L.rden = rden[f];
-      L.lo = s_tab + (size_t)f * row_stride;
-      L.hi = L.lo;
-      double pf, tb, pw;
-      const bool ov = table_lookup<SINGLE, false>(L, ls, &pf, &tb, &pw);
-      const double en = (nd * pw) * a.window_s;
-      const bool ok = !ov && !(rec.xp99 * pf > slo_ttft) && !(tb * rec.nonempty > slo_tbt);
-      if (ok && en < best) { best = en; bf = f; }
+      // table_lookup's arithmetic, in the order that lets a wave stop early: its lanes hold neighbouring entries, which
+      // are overloaded at much the same frequencies and rarely find less energy above the first admissible one
+      const double rho = div_by(ls, den[f], rden[f]);
+      bool live = !(rho > L.rho_max);
+      if (__ballot(live) == 0) continue;
+      double t;
+      const int jj = table_bracket<SINGLE>(L, live ? rho : L.rho_max, &t);
+      const double omt = 1.0 - t;
+      const double* tab = s_tab + (size_t)f * row_stride + jj;
+      const double en = (nd * (omt * tab[2 * n_rho] + t * tab[2 * n_rho + 1])) * a.window_s;
+      live = live && en < best;
+      if (__ballot(live) == 0) continue;
+      const double pf = omt * tab[0] + t * tab[1], tb = omt * tab[n_rho] + t * tab[n_rho + 1];
+      if (live && !(rec.xp99 * pf > slo_ttft) && !(tb * rec.nonempty > slo_tbt)) { best = en; bf = f; }
     }
     const size_t o = ((size_t)(w0 + dw) * a.G + g) * n_entry + a.types.off[i] + e;
     a.type_energy[o] = best;
@@ -206,7 +211,9 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
   }
 }
 
-// One wave per cell.  LDS: [E_i(n, a) of the cell, n_entry] [D of the previous type] [D of this type]
+// One wave per cell.  What bounds it: vector instructions, 8 a candidate (prefix state, instances, shares).  The first type has
+// one candidate a state and the last one U + 1 states; going over all of both cost three times the candidates
+// (36 000 cells, 8 shares, 16 units of GPUs, three types: 276 us, 124 us so).  LDS: [E_i(n, a) of the cell, n_entry] [D of the previous type] [D of this type]
 // [choice per type and state (16-bit: n << 8 | a)], states = (units of GPUs 0..U) x (shares 0..S).
 // SMAX >= n_share bounds the unrolled loop over the shares given to a type: the loads of one
 // (state, n) are issued together and the running minimum is the only dependence.
@@ -228,7 +235,8 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_combine_kernel(MixedCombineArg
   const double inf = __builtin_inf();
 
   for (int q = threadIdx.x; q < n_entry; q += DYN_WAVE) s_c[q] = a.type_energy[cell * n_entry + q];
-  for (int q = threadIdx.x; q < n_state; q += DYN_WAVE) s_d0[q] = q == 0 ? 0.0 : inf;   // nothing used: 0 J
+  // D_0 is 0 J with nothing used and +inf elsewhere, so D_1 is the first type's own energies; of the last type's states only
+  // those with all shares assigned are asked for
   double* prev = s_d0;
   double* next = s_d1;
   for (int i = 0; i < n_tp; ++i) {
@@ -236,8 +244,25 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_combine_kernel(MixedCombineArg
     const int units = a.types.units[i], n_max = a.types.n_max[i];
     const double* ci = s_c + a.types.off[i];
     uint16_t* ch = s_ch + (size_t)i * n_state_max;
-    for (int st = threadIdx.x; st < n_state; st += DYN_WAVE) {
-      const int u = st / S1, sh = st - u * S1;
+    const bool last = i == n_tp - 1;
+    if (i == 0) {
+      for (int q = threadIdx.x; q < n_state; q += DYN_WAVE) {
+        const int u = q / S1, sh = q - u * S1, n = u / units;
+        double best = q == 0 ? 0.0 : inf;
+        uint32_t bc = 0;
+        if (n >= 1 && n <= n_max && n * units == u && sh >= 1) {
+          const double cand = 0.0 + ci[(n - 1) * S + sh - 1];
+          if (cand < best) { best = cand; bc = ((uint32_t)n << 8) | (uint32_t)sh; }
+        }
+        next[q] = best;
+        ch[q] = (uint16_t)bc;
+      }
+      double* t = prev; prev = next; next = t;
+      continue;
+    }
+    for (int q = threadIdx.x; q < (last ? U + 1 : n_state); q += DYN_WAVE) {
+      const int st = last ? q * S1 + S : q;
+      const int u = last ? q : st / S1, sh = st - u * S1;
       double best = prev[st];                          // the type stays unused
       uint32_t bc = 0;
       for (int n = 1; n <= n_max && n * units <= u; ++n) {
@@ -257,13 +282,19 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_combine_kernel(MixedCombineArg
     double* t = prev; prev = next; next = t;
   }
   __syncthreads();
+  double best = inf;                                   // the least energy, the fewest GPUs among equals
+  int bu = -1;
+  for (int u = threadIdx.x; u <= U; u += DYN_WAVE) {
+    const double v = prev[u * S1 + S];
+    if (v < best) { best = v; bu = u; }
+  }
+#pragma unroll
+  for (int d = 1; d < DYN_WAVE; d <<= 1) {
+    const double ov = __shfl_xor(best, d, DYN_WAVE);
+    const int ou = __shfl_xor(bu, d, DYN_WAVE);
+    if (ov < best || (ov == best && (uint32_t)ou < (uint32_t)bu)) { best = ov; bu = ou; }
+  }
   if (threadIdx.x == 0) {
-    double best = inf;
-    int bu = -1;
-    for (int u = 0; u <= U; ++u) {
-      const double v = prev[u * S1 + S];
-      if (v < best) { best = v; bu = u; }
-    }
     a.energy[cell] = best;
     a.ok[cell] = bu >= 0 ? 0 : -1;
     int st = bu >= 0 ? bu * S1 + S : 0;
