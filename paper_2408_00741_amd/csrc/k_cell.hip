@@ -143,12 +143,13 @@ __device__ __forceinline__ void group_sync() {
 
 // Large cell, by a group of WAVES waves (the whole block, or one wave on its own): the group streams the cell from
 // global memory once for the sums and once per 10-bit digit of the selection (radix select through one LDS histogram).
-// Every thread returns the same result.  `hist` (kHistBins counters) and `xch` (16 words) are LDS scratch of the
+// Every thread returns the same result.  `hist` (kHistBins counters) and `xch` (kXchWords) are LDS scratch of the
 // group; the caller guarantees nobody else uses them.
+constexpr int kXchWords = 24;
 template <int U, int WAVES>   // U independent loads per array in flight
 __device__ __forceinline__ CellOut cell_by_group(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg,
                                  int64_t m, int64_t rank, uint32_t* hist, int64_t* xch) {
-  static_assert(WAVES == 1 || WAVES == kWavesPerBlock, "one wave or the block");
+  static_assert(WAVES * 3 <= kXchWords, "one wave or the block");
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int tid = WAVES == 1 ? lane : (int)threadIdx.x, wave = tid / DYN_WAVE;
   constexpr int nthr = WAVES * DYN_WAVE;
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat,
     WsHeader* __restrict__ header) {
   __shared__ uint32_t s_hist[kWavesPerBlock][kHistBins];
-  __shared__ int64_t s_xch[kWavesPerBlock][16];
+  __shared__ int64_t s_xch[kWavesPerBlock][kXchWords];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int64_t c0 = (int64_t)blockIdx.x * kWavesPerBlock;
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
   __shared__ int64_t s_off[kWavesPerBlock][kTinyCells + 1];
   __shared__ uint32_t s_big[kWavesPerBlock];
   __shared__ uint32_t s_hist[kHistBins];
-  __shared__ int64_t s_xch[16];
+  __shared__ int64_t s_xch[kXchWords];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int64_t c0 = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kTinyCells;
@@ -575,6 +576,110 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     }
 }
 
+// ---- few cells: a block per cell --------------------------------------------------------------
+// With no more cells than compute units hold blocks, a wave per cell leaves most of the device idle while the longest cell
+// decides the time.  Here eight waves share a cell: up to kBlockRows values in each thread's registers, the bit-wise search with
+// the waves' counts added up through LDS (a barrier a bit); longer cells are streamed.  What bounds it is latency: offsets,
+// requests, the bits of the search.  Measured (us, a wave per cell and a block): 9 cells of 10 000 requests together 12.4, 11.4;
+// 540 of 1 M 18.8, 13.1; 1000 of 20 000 10.5, 6.2; 1000 of 10 M 105, 40.  Beyond the cells that are resident at once a wave per cell
+// is better unless cells are long: 2500 of 1 M 7.3, 21.6; of 10 M 61, 45; 36 000 of 20 M 34, 271.
+constexpr int kBlockWaves = 8;
+constexpr int kBlockRows = 16;                     // register path: m <= 512 * kBlockRows
+constexpr int64_t kBlockCells = 1024;              // cells that the device holds at once this way
+
+template <int R>
+__device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int m, int rank, int64_t* xch, uint32_t* s_n) {
+  constexpr int kThreads = kBlockWaves * DYN_WAVE;
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t v[R], b[R], orv = 0, top = 0;
+  int64_t sin = 0, sout = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int at = min(i * kThreads + (int)threadIdx.x, m - 1);
+    v[i] = (uint32_t)in[at];
+    b[i] = (uint32_t)out[at];
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const bool ok = i * kThreads + (int)threadIdx.x < m;
+    sin += ok ? (int32_t)v[i] : 0;
+    sout += ok ? (int32_t)b[i] : 0;
+    orv |= v[i] | b[i];                            // beyond m: the last request again
+    top = max(top, v[i]);
+    v[i] = ok ? v[i] : 0xFFFFFFFFu;                // padding is never below a candidate value
+  }
+  sin = wave_sum_i64(sin);
+  sout = wave_sum_i64(sout);
+  orv = wave_or_u32(orv);
+  top = wave_max_u32(top);
+  if (lane == 0) {
+    xch[wave * 3 + 0] = sin;
+    xch[wave * 3 + 1] = sout;
+    xch[wave * 3 + 2] = (int64_t)(((uint64_t)top << 32) | orv);
+  }
+  __syncthreads();
+  CellOut r;
+  r.tin = r.tout = 0;
+  r.orv = top = 0;
+#pragma unroll
+  for (int w = 0; w < kBlockWaves; ++w) {
+    r.tin += xch[w * 3 + 0];
+    r.tout += xch[w * 3 + 1];
+    r.orv |= (uint32_t)xch[w * 3 + 2];
+    top = max(top, (uint32_t)((uint64_t)xch[w * 3 + 2] >> 32));
+  }
+  r.p99 = top;
+  if (rank == m) return r;
+  uint32_t d = 0;
+  int turn = 0;                                    // two buffers: a wave may be a barrier ahead of the slowest reader
+  for (int bit = 31 - __builtin_clz(top | 1u); bit >= 0; --bit) {
+    const uint32_t cand = d | (1u << bit);
+    int below = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) below += __popcll(__ballot(v[i] < cand));
+    if (lane == 0) s_n[turn * kBlockWaves + wave] = (uint32_t)below;
+    __syncthreads();
+    uint32_t all = 0;
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) all += s_n[turn * kBlockWaves + w];
+    if ((int)all < rank) d = cand;
+    turn ^= 1;
+  }
+  r.p99 = d;
+  return r;
+}
+
+__global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_aggregate_block_kernel(
+    const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells,
+    double window_s, double r_window, int32_t pct_num, int32_t pct_den, int64_t* __restrict__ tin, int64_t* __restrict__ tout,
+    int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header) {
+  __shared__ uint32_t s_hist[kHistBins];
+  __shared__ int64_t s_xch[kXchWords];
+  __shared__ uint32_t s_n[2 * kBlockWaves];
+  const int64_t c = blockIdx.x;
+  int64_t beg = cell_off[c], end = cell_off[c + 1];
+  uint32_t bad = (beg < 0 || end < beg || end > n_req) ? DYN_WS_BAD_OFFSETS : 0u;
+  if (bad) beg = end = 0;                          // never read outside the trace
+  const int64_t m = end - beg;
+  CellOut r;
+  r.tin = r.tout = 0;
+  r.p99 = 0;
+  r.orv = 0;
+  if (m > 0) {
+    const int64_t rank = ((int64_t)pct_num * m + pct_den - 1) / pct_den;
+    constexpr int kThreads = kBlockWaves * DYN_WAVE;
+    const int32_t *ci = in + beg, *co = out + beg;
+    if (m <= kThreads) r = cell_by_block<1>(ci, co, (int)m, (int)rank, s_xch, s_n);
+    else if (m <= 2 * kThreads) r = cell_by_block<2>(ci, co, (int)m, (int)rank, s_xch, s_n);
+    else if (m <= 4 * kThreads) r = cell_by_block<4>(ci, co, (int)m, (int)rank, s_xch, s_n);
+    else if (m <= 8 * kThreads) r = cell_by_block<8>(ci, co, (int)m, (int)rank, s_xch, s_n);
+    else if (m <= kBlockRows * kThreads) r = cell_by_block<kBlockRows>(ci, co, (int)m, (int)rank, s_xch, s_n);
+    else r = cell_by_group<8, kBlockWaves>(in, out, beg, m, rank, s_hist, s_xch);
+    if (r.orv >> 31) bad |= DYN_WS_BAD_REQUEST;    // a negative token count
+  }
+  if (threadIdx.x == 0) write_cell(c, r, m, bad, window_s, r_window, cells, tin, tout, in_p99, rec, cstat, header);
+}
+
 }  // namespace
 
 hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_tok,
@@ -583,6 +688,11 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                                      int64_t* tin, int64_t* tout, int32_t* in_p99, CellRec* rec,
                                      uint8_t* cstat, WsHeader* header, hipStream_t s) {
   DynTimed timed(DYN_K_CELL, s);
+  if (cells <= kBlockCells) {
+    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)cells), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
+                       window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header);
+    return hipGetLastError();
+  }
   if (n_req / 48 <= cells) {                     // a few dozen requests per cell on average
     const int64_t per = kWavesPerBlock * kTinyCells;
     hipLaunchKernelGGL(cell_aggregate_tiny_kernel, dim3((unsigned)((cells + per - 1) / per)),

@@ -1,0 +1,52 @@
+"""Token sums and percentile length of single cells at the sizes where the reduction changes its form, in few cells (a block each)
+and in many (a wave each)."""
+import numpy as np
+import pytest
+
+from workloads import SPECS, make
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dyn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2408_00741_amd as d
+    return d
+
+
+SIZES = [0, 1, 2, 63, 64, 65, 100, 101, 256, 511, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 20_001, 0, 3]
+
+
+@pytest.mark.parametrize("cells", [len(SIZES), 1024, 1025, 3000])
+@pytest.mark.parametrize("pct", [(99, 100), (1, 2), (1, 1000), (1, 1)])
+@pytest.mark.parametrize("kind", ["tokens", "equal", "wide", "negative"])
+def test_cell_statistics(dyn, cells, pct, kind):
+    rng = np.random.default_rng(cells + pct[0])
+    m = np.concatenate([SIZES, rng.integers(0, 5 if cells < 2000 else 400, cells - len(SIZES))]).astype(np.int64)
+    off = np.concatenate([[0], np.cumsum(m)])
+    n = int(off[-1])
+    x, y = (rng.integers(0, {"tokens": 8193, "equal": 3, "wide": 1 << 31, "negative": 8193}[kind], n).astype(np.int32) for _ in range(2))
+    if kind == "negative":
+        x[off[20]] = -5                            # cell 20 holds one: its sums count it, its status says so
+    w = make(SPECS[1].scaled(1000, 2))
+    G = 1
+    prof = dyn.dyn_profile_load({k: (v[:G] if v.ndim >= 3 else v) for k, v in w["profile"].items()})
+    plan = dyn.Plan({k: v[:3] for k, v in w["configs"].items()}, {k: v[:G] for k, v in w["slos"].items()}, pct, None, 0.0)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    _, ws = dyn.dyn_eval_space(prof, dev(x), dev(y), dev(off), cells, 60.0, plan)
+    tin, tout, p99 = (t.cpu().numpy() for t in dyn.dyn_cell_stats(ws, cells, G))
+    assert dyn.dyn_workspace_status(ws) == (dyn.DYN_WS_BAD_REQUEST if kind == "negative" else 0)
+    sums = lambda a: np.concatenate([[0], np.cumsum(a.astype(np.int64))])
+    np.testing.assert_array_equal(tin, sums(x)[off[1:]] - sums(x)[off[:-1]])
+    np.testing.assert_array_equal(tout, sums(y)[off[1:]] - sums(y)[off[:-1]])
+    for c in range(cells):
+        if kind == "negative" and c == 20:
+            continue
+        v = np.sort(x[off[c]:off[c + 1]])
+        rank = -(-pct[0] * v.size // pct[1])
+        assert p99[c] == (v[rank - 1] if v.size else 0), (c, v.size)
+    prof.free()
