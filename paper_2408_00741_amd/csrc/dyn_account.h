@@ -10,8 +10,8 @@ struct AccountArgs {
   double gpu_hour_price, kwh_price; int32_t gpus_per_server;
   int64_t* gpus; double* gpu_cost; double* energy_cost; double* carbon_g; double* totals;
   double* hours; double* servers;   // workspace [n_window] each
-  uint32_t* status;                 // workspace word, zeroed by the caller of the kernels
+  uint32_t* status;                 // the workspace header's, written by the launch
 };
-hipError_t dyn_launch_account(const AccountArgs& a, hipStream_t s);
+hipError_t dyn_launch_account(const AccountArgs& a, WsHeader* header, hipStream_t s);
 
 #endif  // DYN_ACCOUNT_H_

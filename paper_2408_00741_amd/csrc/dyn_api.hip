@@ -29,14 +29,6 @@ bool hip_ok(hipError_t e, const char* what) {
   return false;
 }
 
-__global__ void init_word_header_kernel(WsHeader* h, uint32_t order_word) {   // header regions are 256 bytes
-  h->status = 0u;
-  h->kind = DYN_WS_KIND_WORD;
-  h->cells = 0;
-  ((uint32_t*)h)[DYN_WS_HEADER_ORDER_WORD] = order_word;   // ingestion: "not in window order" flag
-  ((uint32_t*)h)[DYN_WS_HEADER_BARRIER_WORD] = 0u;
-}
-
 // Lengths of windows and ticks, capacities and grid spacings are kept inside this range so that the
 // reciprocal-based division of the kernels never meets a subnormal or infinite intermediate.
 constexpr double kMinScale = 1e-100, kMaxScale = 1e100;
@@ -1076,8 +1068,6 @@ int dyn_account(dyn_profile* p, const int32_t* sel, const double* window_energy_
   hipStream_t s = (hipStream_t)hip_stream;
   if ((rc = prepare_configs(p, cfg, K, s)) != DYN_OK) return rc;
   char* base = (char*)workspace;
-  hipLaunchKernelGGL(init_word_header_kernel, dim3(1), dim3(1), 0, s, (WsHeader*)base, 0u);
-  if (!hip_ok(hipGetLastError(), "launch")) return DYN_E_DEVICE;
   AccountArgs a;
   a.sel = sel; a.window_energy = window_energy_j; a.carbon = r->carbon_g_per_kwh;
   a.cfg = p->d_cfg; a.K = K; a.G = p->G; a.n_window = n_window; a.window_s = window_s;
@@ -1085,7 +1075,7 @@ int dyn_account(dyn_profile* p, const int32_t* sel, const double* window_energy_
   a.gpus = out->gpus; a.gpu_cost = out->gpu_cost; a.energy_cost = out->energy_cost; a.carbon_g = out->carbon_g; a.totals = out->totals;
   a.hours = (double*)(base + 256); a.servers = (double*)(base + 256 + per);
   a.status = &((WsHeader*)base)->status;
-  if (!hip_ok(dyn_launch_account(a, s), "account launch")) return DYN_E_DEVICE;
+  if (!hip_ok(dyn_launch_account(a, (WsHeader*)base, s), "account launch")) return DYN_E_DEVICE;
   return DYN_OK;
 }
 

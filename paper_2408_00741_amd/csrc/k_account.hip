@@ -27,24 +27,127 @@ __global__ __launch_bounds__(128) void account_kernel(AccountArgs a) {
   if (bad) atomicOr(a.status, DYN_WS_BAD_REQUEST);
 }
 
-// Totals in window order from 0 (one lane per total: five independent sequential sums).
-__global__ __launch_bounds__(64) void account_totals_kernel(AccountArgs a) {
-  const double* src[5] = {a.hours, a.gpu_cost, a.energy_cost, a.carbon_g, a.servers};
-  if (threadIdx.x < 5) {
-    const double* x = src[threadIdx.x];
-    double t = 0.0;
-    for (int w = 0; w < a.n_window; ++w) t += x[w];
-    a.totals[threadIdx.x] = t;
+// t + x[0] + x[1] + ... in order; x in LDS, readable up to the next multiple of 16.  16 values in flight while 16 are added.
+__device__ __forceinline__ double add_in_order(double t, const double* x, int n) {
+  constexpr int N = 16;
+  double v[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) v[q] = x[q];
+  int at = 0;
+  for (; at + N < n; at += N) {
+    double next[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) next[q] = x[at + N + q];
+#pragma unroll
+    for (int q = 0; q < N; ++q) t += v[q];
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] = next[q];
   }
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    if (at + q < n) t += v[q];
+  return t;
+}
+
+// Totals in window order from 0: a wave per total, five independent sequential sums.  The chain of additions bounds it; the values
+// come through LDS, the next while these are added (one at a time from memory they cost 82 ns a window).
+constexpr int kTotalsChunk = 512;
+__global__ __launch_bounds__(5 * DYN_WAVE) void account_totals_kernel(AccountArgs a) {
+  __shared__ double s_x[5][kTotalsChunk];
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  const double* x = wave == 0 ? a.hours : wave == 1 ? a.gpu_cost : wave == 2 ? a.energy_cost : wave == 3 ? a.carbon_g : a.servers;
+  constexpr int kEach = kTotalsChunk / DYN_WAVE;
+  double v[kEach], t = 0.0;
+  auto load = [&](int w0) {
+#pragma unroll
+    for (int r = 0; r < kEach; ++r) v[r] = x[min(w0 + r * DYN_WAVE + lane, a.n_window - 1)];
+  };
+  load(0);
+  for (int w = 0; w < a.n_window; w += kTotalsChunk) {
+#pragma unroll
+    for (int r = 0; r < kEach; ++r) s_x[wave][r * DYN_WAVE + lane] = v[r];
+    __syncthreads();
+    load(min(w + kTotalsChunk, a.n_window - 1));
+    t = add_in_order(t, s_x[wave], min(kTotalsChunk, a.n_window - w));
+    __syncthreads();
+  }
+  if (lane == 0) a.totals[wave] = t;
+}
+
+// Everything in one block, header included, where the cells are few: the launches would cost more than the work.  487 windows of
+// 15 classes: 13 us in one launch, 50 in three.
+constexpr int kOneBlock = 1024;                  // threads, and windows at a time
+constexpr int64_t kOneBlockCells = 16384;
+__global__ __launch_bounds__(kOneBlock) void account_one_kernel(AccountArgs a, WsHeader* header) {
+  __shared__ unsigned long long s_used[kOneBlock];
+  __shared__ double s_v[5][kOneBlock];
+  __shared__ uint32_t s_bad;
+  const int tid = threadIdx.x, lane = tid & (DYN_WAVE - 1), wave = tid / DYN_WAVE;
+  if (tid == 0) s_bad = 0u;
+  double t = 0.0;
+  for (int w0 = 0; w0 < a.n_window; w0 += kOneBlock) {
+    const int n = min(kOneBlock, a.n_window - w0), cells = n * a.G;
+    __syncthreads();
+    s_used[tid] = 0ull;
+    __syncthreads();
+    const int32_t* sel = a.sel + (size_t)w0 * a.G;
+    for (int c0 = tid; c0 < cells; c0 += 8 * kOneBlock) {
+      int32_t k[8], gpus[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) k[q] = sel[min(c0 + q * kOneBlock, cells - 1)];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) gpus[q] = a.cfg[k[q] >= 0 && k[q] < a.K ? k[q] : 0].gpus;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int c = c0 + q * kOneBlock;
+        if (c >= cells) continue;
+        if (k[q] >= a.K) s_bad = 1u;               // not a candidate of the list: counted as no selection
+        else if (k[q] >= 0) atomicAdd(&s_used[c / a.G], (unsigned long long)gpus[q]);
+      }
+    }
+    __syncthreads();
+    if (tid < n) {
+      const int w = w0 + tid;
+      const int64_t used = (int64_t)s_used[tid];
+      const double hours = ((double)used * a.window_s) / 3600.0;
+      const double kwh = a.window_energy[w] / 3.6e6;
+      a.gpus[w] = used;
+      a.gpu_cost[w] = s_v[1][tid] = hours * a.gpu_hour_price;
+      a.energy_cost[w] = s_v[2][tid] = kwh * a.kwh_price;
+      a.carbon_g[w] = s_v[3][tid] = kwh * a.carbon[w];
+      s_v[0][tid] = hours;
+      s_v[4][tid] = (double)((used + a.gpus_per_server - 1) / a.gpus_per_server);
+    }
+    __syncthreads();
+    if (wave < 5) t = add_in_order(t, s_v[wave], n);
+  }
+  if (wave < 5 && lane == 0) a.totals[wave] = t;
+  if (tid == 0) {
+    header->status = s_bad ? DYN_WS_BAD_REQUEST : 0u;
+    header->kind = DYN_WS_KIND_WORD;
+    header->cells = 0;
+  }
+}
+
+__global__ void account_header_kernel(WsHeader* header) {
+  header->status = 0u;
+  header->kind = DYN_WS_KIND_WORD;
+  header->cells = 0;
 }
 
 }  // namespace
 
-hipError_t dyn_launch_account(const AccountArgs& a, hipStream_t s) {
+hipError_t dyn_launch_account(const AccountArgs& a, WsHeader* header, hipStream_t s) {
   DynTimed timed(DYN_K_TOTALS, s);
-  hipLaunchKernelGGL(account_kernel, dim3((unsigned)((a.n_window + 127) / 128)), dim3(128), 0, s, a);
+  if ((int64_t)a.n_window * a.G <= kOneBlockCells) {
+    hipLaunchKernelGGL(account_one_kernel, dim3(1), dim3(kOneBlock), 0, s, a, header);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(account_header_kernel, dim3(1), dim3(1), 0, s, header);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(account_totals_kernel, dim3(1), dim3(64), 0, s, a);
+  hipLaunchKernelGGL(account_kernel, dim3((unsigned)((a.n_window + 127) / 128)), dim3(128), 0, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(account_totals_kernel, dim3(1), dim3(5 * DYN_WAVE), 0, s, a);
   return hipGetLastError();
 }

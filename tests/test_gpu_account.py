@@ -54,3 +54,21 @@ def test_account_matches_oracle(dyn, idx, n_req, n_win):
         dyn.dyn_account(prof, sel["sel"], sel["window_energy_j"], plan, NW, W, 1.0, 0.1, _dev(ci), 0)
     assert e.value.status == -2
     prof.free()
+
+
+@pytest.mark.parametrize("n_win", [1, 2, 63, 64, 65, 546, 547, 1024, 1025, 2049])
+@pytest.mark.parametrize("G", [1, 9, 30])
+def test_totals_in_window_order(dyn, n_win, G):
+    """One block (up to 16 384 cells, 1024 windows at a time) and several, with windows that end inside a group of 64."""
+    w = make(SPECS[2].scaled(1000, 2))
+    prof = dyn.dyn_profile_load({k: (np.repeat(v[:1], G, axis=0) if v.ndim >= 3 else v) for k, v in w["profile"].items()})
+    plan = dyn.Plan(w["configs"], {k: np.repeat(v[:1], G) for k, v in w["slos"].items()}, w["pct"], None, 0.0)
+    rng = np.random.default_rng(n_win + G)
+    sel = rng.integers(-1, w["configs"]["n_inst"].size, n_win * G).astype(np.int32)
+    e, ci = rng.uniform(0.0, 1e9, n_win), rng.uniform(80.0, 700.0, n_win)
+    out, ws = dyn.dyn_account(prof, _dev(sel), _dev(e), plan, n_win, 300.0, 11.06, 0.0832, _dev(ci), 8)
+    assert dyn.dyn_workspace_status(ws) == 0
+    o = oracle.account(w["configs"], w["profile"]["tp"], sel, e, n_win, G, 300.0, 11.06, 0.0832, ci, 8)
+    for k in ("gpus", "gpu_cost", "energy_cost", "carbon_g", "totals"):
+        np.testing.assert_array_equal(out[k].cpu().numpy(), o[k], err_msg=k)
+    prof.free()
