@@ -241,7 +241,7 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_combine_kernel(MixedCombineArg
   double* next = s_d1;
   for (int i = 0; i < n_tp; ++i) {
     __syncthreads();
-    const int units = a.types.units[i], n_max = a.types.n_max[i];
+    const int units = max(a.types.units[i], 1), n_max = a.types.n_max[i];   // 0: a type of no instances
     const double* ci = s_c + a.types.off[i];
     uint16_t* ch = s_ch + (size_t)i * n_state_max;
     const bool last = i == n_tp - 1;
@@ -309,6 +309,130 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_combine_kernel(MixedCombineArg
   }
 }
 
+// The same programme with the shares in registers: a lane holds one count of GPUs of one cell, its D over all shares; 63 / (U + 1)
+// cells to a wave (lane 63 stays free of them).  For every number of instances the lane reads the row that many GPUs below from LDS
+// once, and every (shares before, shares given) pair of it costs an addition and a minimum.  Nothing else is kept: the
+// choices are found again on the way back, at the n_tp states of the best assignment, as the first candidate in the order
+// above whose sum is the state's value.
+// What bounds it: vector instructions, 2 a candidate and the lanes without one; the row reads.  36 000 cells, 8 shares, 16 units,
+// three types: 73 us; 122 us by the kernel above, which stays for more than 62 units of GPUs.
+// The shares are numbered from the top (t = s + SMAX - S), so that all of them assigned is t = SMAX whatever S is.
+// LDS: [row SMAX + 1 of D per lane, and one of +inf before them; per type after the first] [least total per lane]
+constexpr int kRowLanes = DYN_WAVE + 1;
+template <int SMAX>
+__global__ __launch_bounds__(DYN_WAVE) void mixed_rows_kernel(MixedCombineArgs a) {
+  extern __shared__ double smem[];
+  constexpr int W = SMAX + 1;
+  const double inf = __builtin_inf();
+  const int S = a.n_share, skip = SMAX - S, n_tp = a.types.n_tp, n_entry = a.types.off[n_tp];
+  const int lane = threadIdx.x, U1 = a.u_max + 1, per_wave = (DYN_WAVE - 1) / U1;
+  const int grp = lane / U1, u = lane - grp * U1;
+  const int64_t cell = (int64_t)blockIdx.x * per_wave + grp;
+  const bool live = grp < per_wave && cell < a.cells;
+  const double* te = a.type_energy + (live ? cell : 0) * n_entry;
+  double* s_v = smem + (size_t)(n_tp - 1) * kRowLanes * W;       // [DYN_WAVE]
+
+  double cur[W];                                 // D_1: the first type's own energies
+  {
+    const int units = max(a.types.units[0], 1), n = u / units;   // 0: a type of no instances
+    const bool some = live && n >= 1 && n <= a.types.n_max[0] && n * units == u;
+    const double* c = te + (some ? (n - 1) * S : 0);
+#pragma unroll
+    for (int t = 0; t < W; ++t) {
+      cur[t] = inf;
+      if (t > skip && some) cur[t] = 0.0 + c[t - skip - 1];
+      if (t == skip && live && u == 0) cur[t] = 0.0;             // nothing used
+    }
+  }
+  for (int i = 1; i < n_tp; ++i) {
+    double* rows = smem + (size_t)(i - 1) * kRowLanes * W;       // row 0: what cannot be done; row 1 + lane
+    const int units = max(a.types.units[i], 1), n_end = min(a.types.n_max[i], a.u_max / units);
+    const double* ci = te + a.types.off[i];
+    const bool last = i == n_tp - 1;
+#pragma unroll
+    for (int t = 0; t < W; ++t) rows[(1 + lane) * W + t] = cur[t];
+    if (lane < W) rows[lane] = inf;
+    __syncthreads();
+    double c[SMAX];                              // c[x - 1]: the energy of n instances with x shares; the next n's in flight
+#pragma unroll
+    for (int x = 0; x < SMAX; ++x) c[x] = n_end >= 1 && x < S ? ci[x] : inf;
+    for (int n = 1; n <= n_end; ++n) {
+      double cn[SMAX], row[SMAX];
+      const double* cnext = ci + (size_t)(n < n_end ? n : 0) * S;
+#pragma unroll
+      for (int x = 0; x < SMAX; ++x) cn[x] = x < S ? cnext[x] : inf;
+      const double* from = rows + (size_t)(live && u >= n * units ? 1 + lane - n * units : 0) * W;
+#pragma unroll
+      for (int t = 0; t < SMAX; ++t) row[t] = from[t];
+      if (last) {
+#pragma unroll
+        for (int x = 1; x <= SMAX; ++x) cur[SMAX] = min_num(cur[SMAX], row[SMAX - x] + c[x - 1]);
+      } else {
+#pragma unroll
+        for (int t = 1; t <= SMAX; ++t) {
+#pragma unroll
+          for (int x = 1; x <= t; ++x) cur[t] = min_num(cur[t], row[t - x] + c[x - 1]);
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < SMAX; ++x) c[x] = cn[x];
+    }
+  }
+  s_v[lane] = cur[SMAX];
+  __syncthreads();
+  // the least energy and the fewest GPUs that have it: every lane of a cell goes over its cell's values
+  const int32_t bud = a.budget[live ? (int)(cell % a.G) : 0];
+  const int U = bud > 0 ? min(bud / a.unit, a.u_max) : a.u_max;
+  double best = inf;
+  int bu = -1;
+  for (int q = 0; q <= U; ++q) {
+    const double v = s_v[live ? grp * U1 + q : DYN_WAVE - 1];
+    if (v < best) { best = v; bu = q; }
+  }
+  const bool lead = live && u == 0;
+  if (lead) {
+    a.energy[cell] = best;
+    a.ok[cell] = bu >= 0 ? 0 : -1;
+  }
+  const uint64_t mine = live ? ((1ull << U1) - 1ull) << (grp * U1) : 0ull;   // the cell's lanes
+  int su = bu >= 0 ? bu : 0, st = bu >= 0 ? SMAX : skip;         // the state on the way back
+  double val = best;
+  for (int i = n_tp - 1; i >= 0; --i) {
+    const int units = max(a.types.units[i], 1);
+    int n = 0, x = 0;
+    if (i == 0) {
+      if (bu >= 0 && su > 0) { n = su / units; x = st - skip; }
+    } else {
+      const double* rows = smem + (size_t)(i - 1) * kRowLanes * W;
+      const double* at = rows + (size_t)(live ? 1 + grp * U1 + su : 0) * W;
+      const int n_cand = min(a.types.n_max[i], a.u_max / units) * S;
+      bool open = live && bu >= 0 && at[st] != val;              // else the type is not used
+      for (int f0 = 0; f0 < n_cand && __ballot(open) != 0; f0 += U1) {
+        const int f = f0 + u, fn = f / S + 1, fx = f - (fn - 1) * S + 1;
+        const bool can = open && f < n_cand && fn * units <= su && fx <= st - skip;
+        const bool hit = can && at[-fn * units * W + st - fx] + te[a.types.off[i] + f] == val;
+        const uint64_t who = __ballot(hit) & mine;
+        if (open && who != 0) {
+          const int ff = f0 + (int)__builtin_ctzll(who) - grp * U1;
+          n = ff / S + 1;
+          x = ff - (n - 1) * S + 1;
+          open = false;
+        }
+      }
+      if (n > 0) {
+        val = at[-n * units * W + st - x];
+        su -= n * units;
+        st -= x;
+      }
+    }
+    if (lead) {
+      a.n_inst[cell * n_tp + i] = n;
+      a.share[cell * n_tp + i] = x;
+      a.f_index[cell * n_tp + i] = n > 0 ? (int32_t)a.type_f[cell * n_entry + a.types.off[i] + (n - 1) * S + (x - 1)] : -1;
+    }
+  }
+}
+
 size_t type_lds(const MixedTypeArgs& a, bool single) {
   return ((size_t)a.n_f * ((3 * a.n_rho) | 1) + 2 * a.n_rho + 3 + (single ? a.n_bucket + 1 : 0)) * sizeof(double) +
          (size_t)a.win_per_block * sizeof(CellRec) + ((size_t)a.n_bucket + 1) * sizeof(uint16_t) + 8;
@@ -345,10 +469,21 @@ hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, bool single_point, hip
   return hipGetLastError();
 }
 
+template <int SMAX>
+bool launch_rows(const MixedCombineArgs& a, hipStream_t s) {   // false: the shape is not for it
+  const int U1 = a.u_max + 1;
+  const size_t lds = ((size_t)(a.types.n_tp - 1) * kRowLanes * (SMAX + 1) + DYN_WAVE) * sizeof(double);
+  if (U1 > DYN_WAVE - 1 || lds > DYN_LDS_BUDGET) return false;
+  const int64_t per_wave = (DYN_WAVE - 1) / U1;
+  hipLaunchKernelGGL(mixed_rows_kernel<SMAX>, dim3((unsigned)((a.cells + per_wave - 1) / per_wave)), dim3(DYN_WAVE), lds, s, a);
+  return true;
+}
+
 hipError_t dyn_launch_mixed_combine(const MixedCombineArgs& a, hipStream_t s) {
   const size_t lds = dyn_mixed_combine_lds(a.types.n_tp, a.types.off[a.types.n_tp], a.u_max, a.n_share);
   if (lds > DYN_LDS_BUDGET) return hipErrorInvalidValue;
   DynTimed timed(DYN_K_MIXED_COMBINE, s);
+  if (a.n_share <= 4 ? launch_rows<4>(a, s) : a.n_share <= 8 ? launch_rows<8>(a, s) : launch_rows<DYN_MIXED_MAX_SHARES>(a, s)) return hipGetLastError();
   const dim3 grid((unsigned)a.cells), block(DYN_WAVE);
   if (a.n_share <= 4) hipLaunchKernelGGL(mixed_combine_kernel<4>, grid, block, lds, s, a);
   else if (a.n_share <= 8) hipLaunchKernelGGL(mixed_combine_kernel<8>, grid, block, lds, s, a);

@@ -120,6 +120,19 @@ def test_many_instances_of_one_type(dyn):
     assert rep[0] > 0
 
 
+@pytest.mark.parametrize("S,n_max,budget", [(1, [1, 1, 1], None), (4, [3, 0, 2], None), (5, [0, 3, 2], None), (8, [2, 2, 0], None), (9, [4, 2, 1], None),
+                                            (16, [3, 2, 1], None), (2, [30, 15, 0], None), (2, [62, 0, 0], None), (3, [63, 0, 0], None), (8, [16, 8, 4], 4),
+                                            (2, [20, 10, 5], 124), (2, [21, 10, 5], 126), (1, [255, 2, 2], 20)])
+def test_programme_by_rows_and_beyond(dyn, S, n_max, budget):
+    """Shares up to and one past what the register rows are made for, types without instances (the first and the last of them
+    too), one cell to a wave and many, and 62 units of GPUs, 63 (the kernel without rows) and more."""
+    w = make(SPECS[2].scaled(3000, 3))
+    budget = None if budget is None else np.full(w["n_class"], budget, np.int32)
+    g, st = gpu_mixed(dyn, w, S, n_max, budget)
+    o = oracle.mixed(w["profile"], st, w["n_window"], w["window_s"], S, n_max, w["slos"], w["pct"], budget, want_types=True)
+    check(w, g, o, S, n_max, budget)
+
+
 def _random_case(seed):
     rng = np.random.default_rng(1100 + seed)
     n_tp, n_f, n_rho, G = int(rng.integers(1, 5)), int(rng.integers(1, 7)), int(rng.integers(2, 9)), 3
