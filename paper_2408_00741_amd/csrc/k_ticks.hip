@@ -330,17 +330,18 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 }
 
 // The same for the listed cells whose ticks do not fit one wave's registers: a block per cell, wave w takes the ticks
-// w, w + 4, ...; x_j by the bit-wise search with the waves' counts added up through LDS (one barrier per bit).  A cell
+// w, w + 8, ...; x_j by the bit-wise search with the waves' counts added up through LDS (one barrier per bit).  A cell
 // it settles is taken off the list (its entry becomes DYN_LIST_DONE).
 #define DYN_LIST_DONE 0xFFFFFFFFu
-constexpr int kTightBlocks = 1024;
+constexpr int kTightWaves = 8;
+constexpr int kTightBlocks = 512;              // what the device holds at once (registers: two to a compute unit)
 
 enum BlockCell { kNotTaken, kSettled, kBoundFails };   // kBoundFails: token sums and x_j are known, the ticks' lists are needed
 template <int P>   // P registers = 2P rows per wave
 __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
                                                  int64_t beg_l, int32_t cnt_l, int T, int rpt, int m, int rank, float theta,
-                                                 int lane, int wave, uint32_t* s_x /* [2][kWavesPerBlock] */,
-                                                 uint32_t* s_m /* [4 * kWavesPerBlock] */, TightCell* res) {
+                                                 int lane, int wave, uint32_t* s_x /* [2][kTightWaves] */,
+                                                 uint32_t* s_m /* [4 * kTightWaves] */, TightCell* res) {
   uint32_t v[P];
   uint32_t orv = 0, vmax = 0, tok_acc = 0, tok_l = 0;
   constexpr int CH = 4;
@@ -365,7 +366,7 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
       const int64_t row_q = beg_q + (int64_t)(r * DYN_WAVE);   // one scalar offset for both arrays
       a[u] = ok ? (uint32_t)in[row_q + lane] : 0u;
       b[u] = ok ? (uint32_t)out[row_q + lane] : 0u;
-      if (++r == rpt) { r = 0; q += kWavesPerBlock; }
+      if (++r == rpt) { r = 0; q += kTightWaves; }
     }
 #pragma unroll
     for (int u = 0; u < 2 * CH; ++u) {
@@ -385,29 +386,29 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
     asm volatile("" : "+v"(tok_acc), "+v"(tok_l), "+v"(orv), "+v"(vmax), "+v"(v[p0]), "+v"(v[p0 + 1]), "+v"(v[p0 + 2]),
                  "+v"(v[p0 + 3])::"memory");
   }
-  // sums over the block: every wave writes its word, a barrier, every wave reads all four (two buffers in turn)
+  // sums over the block: every wave writes its word, a barrier, every wave reads all of them (two buffers in turn)
   int turn = 0;
   auto block_or = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kWavesPerBlock + wave] = x;
+    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kWavesPerBlock; ++w) all |= s_x[turn * kWavesPerBlock + w];
+    for (int w = 0; w < kTightWaves; ++w) all |= s_x[turn * kTightWaves + w];
     turn ^= 1;
     return all;
   };
   auto block_max = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kWavesPerBlock + wave] = x;
+    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kWavesPerBlock; ++w) all = max(all, s_x[turn * kWavesPerBlock + w]);
+    for (int w = 0; w < kTightWaves; ++w) all = max(all, s_x[turn * kTightWaves + w]);
     turn ^= 1;
     return all;
   };
   auto block_sum = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kWavesPerBlock + wave] = x;
+    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kWavesPerBlock; ++w) all += s_x[turn * kWavesPerBlock + w];
+    for (int w = 0; w < kTightWaves; ++w) all += s_x[turn * kTightWaves + w];
     turn ^= 1;
     return all;
   };
@@ -431,7 +432,7 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
     }
     xj = d;
   }
-  res->tok_l = tok_l;                    // lanes q with q % 4 == wave
+  res->tok_l = tok_l;                    // lanes q with q % 8 == wave
   res->xj = xj;
   if (!((double)theta * ((double)xj + 1.0) > (double)xj)) return kBoundFails;
   int n_gt = 0, n_eq = 0, eq_acc = 0;      // the padding (0xFFFF) counts as longer: taken off after the block's sum
@@ -448,24 +449,24 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
         if (lane == q) eq_l = (uint32_t)eq_acc;
         n_eq += eq_acc;
         eq_acc = 0;
-        r = 0; q += kWavesPerBlock;
+        r = 0; q += kTightWaves;
       }
     }
   }
-  n_gt = (int)block_sum((uint32_t)n_gt) - (2 * P * DYN_WAVE * kWavesPerBlock - m);
+  n_gt = (int)block_sum((uint32_t)n_gt) - (2 * P * DYN_WAVE * kTightWaves - m);
   n_eq = (int)block_sum((uint32_t)n_eq);
   const int need = j - n_gt;
   uint32_t place = (uint32_t)need;
   res->walk = true;
   if (need > 4 && n_eq - need + 1 > 4) {   // block-uniform
-    // every wave's four smallest positive counts meet in LDS; the four smallest of the sixteen are the block's
+    // every wave's four smallest positive counts meet in LDS; the four smallest of them are the block's
     uint32_t m4[4];
     const int npos_w = smallest_four(eq_l, lane, m4);
     const int npos = (int)block_sum((uint32_t)npos_w);
     if (lane < 4) s_m[wave * 4 + lane] = lane == 0 ? m4[0] : lane == 1 ? m4[1] : lane == 2 ? m4[2] : m4[3];
     __syncthreads();
     uint32_t best[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-    for (int i = 0; i < 4 * kWavesPerBlock; ++i) {
+    for (int i = 0; i < 4 * kTightWaves; ++i) {
       uint32_t x = s_m[i];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {        // insertion into the ascending four
@@ -551,10 +552,10 @@ __device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int c
   wave_sync();                                     // buf is reused
 }
 
-__global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_tight_block_kernel(TickCellArgs a) {
-  __shared__ uint32_t s_x[2 * kWavesPerBlock];
-  __shared__ uint32_t s_m[4 * kWavesPerBlock];
-  __shared__ int32_t s_list[kWavesPerBlock][kListTick];
+__global__ __launch_bounds__(kTightWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_tight_block_kernel(TickCellArgs a) {
+  __shared__ uint32_t s_x[2 * kTightWaves];
+  __shared__ uint32_t s_m[4 * kTightWaves];
+  __shared__ int32_t s_list[kTightWaves][kListTick];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int T = a.n_tick, G = a.G;
@@ -577,14 +578,15 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     const int64_t rank = (a.pct_num * m_cell + a.pct_den - 1) / a.pct_den;
     const int64_t j64 = m_cell > 0 ? m_cell - rank + 1 : 0;
     const int rpt = ((int)wave_max_u32((uint32_t)cnt_l) + DYN_WAVE - 1) / DYN_WAVE;
-    const int rows = ((T + kWavesPerBlock - 1) / kWavesPerBlock) * rpt;   // rows of the wave with most ticks
+    const int rows = ((T + kTightWaves - 1) / kTightWaves) * rpt;   // rows of the wave with most ticks
     TightCell tc;
     tc.tok_l = 0; tc.eq_l = 0; tc.xj = 0; tc.place = 0; tc.need = 0; tc.walk = true;
     BlockCell done = kNotTaken;                  // block-uniform from here on
     if (m_cell > 0 && m_cell < (1 << 24) && rows <= 128) {
       const float theta = a.theta[g];
       const int m = (int)m_cell, rk = (int)rank;
-      if (rows <= 32) done = tight_cell_block<16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      if (rows <= 16) done = tight_cell_block<8>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      else if (rows <= 32) done = tight_cell_block<16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
       else if (rows <= 64) done = tight_cell_block<32>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
       else done = tight_cell_block<64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
     }
@@ -600,9 +602,9 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     } else {
       // Its lists, a tick per wave at a time, where that is better than what follows: few cells on the whole device, or a
       // list beyond the 64 entries that one wave keeps sorted (a block per cell, tick after tick).  540 cells of up to
-      // 6800 requests and 12 ticks: 84 us in this kernel; 26, then 227 in tick_cell_kernel and 462 in tick_deep_kernel without.
+      // 6800 requests and 12 ticks: 73 us in this kernel (84 with four waves a block); 26, then 227 in tick_cell_kernel and 462 in tick_deep_kernel without.
       if (!(a.few_cells || j64 > DYN_TICK_WAVE) || j64 > DYN_TICK_DEPTH || wave_max_u32((uint32_t)cnt_l) > kListTick) continue;
-      for (int q = wave; q < T; q += kWavesPerBlock) {
+      for (int q = wave; q < T; q += kTightWaves) {
         const int64_t beg_q = readlane_i64(beg_l, q);
         const int cnt_q = __builtin_amdgcn_readlane(cnt_l, q);
         if (cnt_q > 0) tick_list(a.in + beg_q, cnt_q, j64 < cnt_q ? (int)j64 : cnt_q, a.top + beg_q, s_list[wave], lane);
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
       flags |= walks_with_lists(flags, j64) ? 0u : DYN_TP_GENERAL;
       tc.eq_l = (uint32_t)beg_l;                 // where the tick's list is (n_req < 2^31)
     }
-    if (lane < T && (lane % kWavesPerBlock) == wave) {   // the wave that walked the tick
+    if (lane < T && (lane % kTightWaves) == wave) {   // the wave that walked the tick
       TickRec r;
       r.load = div_by((double)tc.tok_l, a.tick_s, a.r_tick);
       r.off = tc.eq_l;
@@ -1727,7 +1729,7 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   DynTimed timed(DYN_K_TICK_TOP, s);
   hipLaunchKernelGGL(tick_init_kernel, dim3(1), dim3(1), 0, s, a.counters);
   hipLaunchKernelGGL(tick_tight_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
-  hipLaunchKernelGGL(tick_tight_block_kernel, dim3(kTightBlocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
+  hipLaunchKernelGGL(tick_tight_block_kernel, dim3(kTightBlocks), dim3(kTightWaves * DYN_WAVE), 0, s, a);
   hipLaunchKernelGGL(tick_cell_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
   hipLaunchKernelGGL(tick_deep_kernel, dim3(kDeepBlocks), dim3(256), 0, s, a);
   return hipGetLastError();
