@@ -580,12 +580,14 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 // With no more cells than compute units hold blocks, a wave per cell leaves most of the device idle while the longest cell
 // decides the time.  Here eight waves share a cell: up to kBlockRows values in each thread's registers, the bit-wise search with
 // the waves' counts added up through LDS (a barrier a bit); longer cells are streamed.  What bounds it is latency: offsets,
-// requests, the bits of the search.  Measured (us, a wave per cell and a block): 9 cells of 10 000 requests together 12.4, 11.4;
-// 540 of 1 M 18.8, 13.1; 1000 of 20 000 10.5, 6.2; 1000 of 10 M 105, 40.  Beyond the cells that are resident at once a wave per cell
-// is better unless cells are long: 2500 of 1 M 7.3, 21.6; of 10 M 61, 45; 36 000 of 20 M 34, 271.
+// requests, the bits of the search.  It pays where the longest cell is beyond a wave's plain registers (2048 requests), which
+// classes of uneven traffic reach at a mean of about 1000.  Measured (us, a wave per cell and a block): 9 cells of 10 000 requests
+// together 12.4, 9.4; 540 of 1 M 18.8, 13.1; 1000 of 10 M 105, 40; but 40 even ones of 100 000 7.3, 9.0; 1000 of 100 000 3.8, 13.6;
+// and beyond the cells that are resident at once 2500 of 1 M 7.3, 21.6; 36 000 of 20 M 34, 271.
 constexpr int kBlockWaves = 8;
 constexpr int kBlockRows = 16;                     // register path: m <= 512 * kBlockRows
 constexpr int64_t kBlockCells = 1024;              // cells that the device holds at once this way
+constexpr int64_t kBlockMean = 1000;               // requests per cell
 
 template <int R>
 __device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int m, int rank, int64_t* xch, uint32_t* s_n) {
@@ -688,7 +690,7 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                                      int64_t* tin, int64_t* tout, int32_t* in_p99, CellRec* rec,
                                      uint8_t* cstat, WsHeader* header, hipStream_t s) {
   DynTimed timed(DYN_K_CELL, s);
-  if (cells <= kBlockCells) {
+  if (cells <= kBlockCells && n_req > kBlockMean * cells) {
     hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)cells), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
                        window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header);
     return hipGetLastError();
