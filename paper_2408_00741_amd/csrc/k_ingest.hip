@@ -168,12 +168,6 @@ __global__ void edge_store_kernel(EdgePack p, int n_a, int32_t* __restrict__ dst
   }
 }
 
-// cell_off[c] = number of requests with key < c, read off the sorted keys
-__device__ __forceinline__ void offsets_at(int64_t i, int64_t prev, int64_t cur, int64_t n, int64_t cells, int64_t* cell_off) {
-  if (i == n || cur > cells) cur = cells;
-  for (int64_t c = prev + 1; c <= cur; ++c) cell_off[c] = i;
-}
-
 // exclusive sum over the block's threads; `wave_sum`: a word of LDS per wave
 template <int WAVES>
 __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wave_sum) {
@@ -898,28 +892,35 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
   }
   if (a.n_req == 0)
     for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
-  // the offsets: a block goes over its run of the sorted keys, every key beside the one before it
+  // The offsets (cell_off[c] = number of requests with key < c), a tile of sorted keys in LDS at a time: a request's thread fills
+  // the cells from the key before it on, a few of them by itself, and its wave the others (the 35 000 empty cells before
+  // the log of a grid's last minutes took one thread 1.1 ms).  What is left behind the last request is its block's.
+  constexpr int kOwnCells = 16;
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  uint32_t left = 0;                             // one more than the key before the tile
   for (int64_t at = beg; at < end; at += kRadixTile) {
-    uint32_t key[kRadixItems], left[kRadixItems];
+    const int count = (int)std::min<int64_t>(kRadixTile, end - at);
+    left = at > 0 ? __hip_atomic_load(k_src + at - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u : 0u;
 #pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
-      key[r] = k_src[i];
-      left[r] = k_src[i > 0 ? i - 1 : 0];
-    }
+    for (int r = 0; r < kRadixItems; ++r) s.move[r * kRadixThreads + threadIdx.x] = k_src[std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1)];
+    __syncthreads();
 #pragma unroll 1
-    for (int r = 0; r < kRadixItems; ++r) {
-      const int64_t i = at + r * kRadixThreads + threadIdx.x;
-      uint32_t k = key[0], l = left[0];
-#pragma unroll
-      for (int q = 1; q < kRadixItems; ++q) {
-        k = r == q ? key[q] : k;
-        l = r == q ? left[q] : l;
+    for (int i = threadIdx.x; i - (int)threadIdx.x < count; i += kRadixThreads) {
+      uint32_t c = i > 0 ? s.move[min(i, count) - 1] + 1u : left;
+      const uint32_t to = s.move[min(i, count - 1)] + 1u;        // beyond the tile: c == to
+      for (int q = 0; q < kOwnCells && c < to; ++q) a.cell_off[c++] = at + i;
+      for (uint64_t more = __ballot(c < to); more != 0; more &= more - 1) {
+        const int who = __builtin_ctzll(more);
+        const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)to, who);
+        const int64_t off = at + __builtin_amdgcn_readlane(i, who);
+        for (uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)c, who) + lane; b < upto; b += DYN_WAVE) a.cell_off[b] = off;
       }
-      if (i < end && (k != l || i == 0)) offsets_at(i, i == 0 ? -1 : (int64_t)l, k, a.n_req, g.cells, a.cell_off);
-      if (i == a.n_req - 1) offsets_at(a.n_req, k, g.cells, a.n_req, g.cells, a.cell_off);
     }
+    left = s.move[count - 1] + 1u;
+    __syncthreads();
   }
+  if (end == a.n_req && beg < end)
+    for (int64_t c = (int64_t)left + threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = a.n_req;
 }
 
 }  // namespace

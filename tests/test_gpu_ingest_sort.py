@@ -120,3 +120,50 @@ def test_sorts_on_eight_streams_at_once(dyn):
     for tr, g in zip(logs, got):
         assert dyn.dyn_workspace_status(g[3]) == 0
         _check(g, tr, edges, 60, 60.0)
+
+
+def _squeezed(seed, n, n_window, first, used, n_model=1):
+    """A log whose requests lie in `used` windows of 10 s from window `first` on."""
+    tr = _log(seed, n, used * 10.0, n_model)
+    tr["t_s"] += first * 10.0
+    return tr
+
+
+def _us(call):
+    """Least time of a few calls on the GPU, in microseconds."""
+    call()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+# the sort where most cells are empty: before the first request, between two tiles, behind the last (1200 classes force the
+# sort, so a log of one request takes it too)
+@pytest.mark.parametrize("n", [1, 63, 64, 65, TILE, TILE + 1, 3 * TILE + 5])
+@pytest.mark.parametrize("first", [0, 17, 39])
+@pytest.mark.parametrize("n_in,n_out", [(5, 5), (40, 30)])
+def test_sort_of_a_log_in_a_small_part_of_the_grid(dyn, n, first, n_in, n_out):
+    edges = _edges(n_in, n_out)
+    tr = _squeezed(n, n, 40, first, 1)
+    if n > 1:
+        tr["t_s"][-1], tr["t_s"][0] = 10.0 * first, 399.0       # out of order also where all lie in one window
+    got = _call(dyn, tr, edges, 40, 10.0)
+    _check(got, tr, edges, 40, 10.0)
+
+
+def test_sort_is_as_quick_where_most_cells_are_empty(dyn):
+    """A day's log of the last minute, unordered: its empty cells before it are filled by all threads (one thread: 13 times as long)."""
+    edges = _edges(5, 5)
+    us = []
+    for used in (2000, 1):
+        tr = _squeezed(7, 300_000, 2000, 2000 - used, used)
+        tr["t_s"][1000::1000] = 0.0                             # more breaks than the runs route takes
+        d = [torch.from_numpy(tr[k]).cuda() for k in ("t_s", "in_tok", "out_tok")]
+        us.append(_us(lambda: dyn.dyn_trace_ingest(*d, None, edges, 2000, 10.0)))
+    assert us[1] < 4.0 * us[0], us
