@@ -117,8 +117,10 @@ struct WsHeader {
 };
 #define DYN_WS_HEADER_ORDER_WORD 8   // 32-bit word of a 256-byte header region used by the ingestion kernels
 #define DYN_WS_HEADER_BARRIER_WORD 9 // arrivals at the general sort's barriers, blocks that came to sort, blocks that sort (3 words, zeroed with the header)
+#define DYN_WS_HEADER_LEFT_WORD 12   // windows that the window route left to larger blocks (zeroed with the header)
 #define DYN_WS_HEADER_BREAK_WORD 16  // where the trace's runs after the first start, as far as there are at most DYN_WS_MAX_BREAKS
 #define DYN_WS_MAX_BREAKS 48u
+#define DYN_INGEST_COUNTERS 1024     // of the sampled requests per window (the first words of block_hist, zeroed with the header)
 #define DYN_WS_KIND_WORD 1u
 #define DYN_WS_KIND_CELLS 2u
 
@@ -176,12 +178,14 @@ struct IngestArgs {
   uint32_t* unsorted;      // word in the workspace header: how many requests are in a window before that of the request before them
   int32_t force_sort;      // != 0: take the general sort whatever the order (the word then starts past DYN_WS_MAX_BREAKS)
   int64_t* win_off;        // workspace [n_window + 1]
+  uint32_t many;           // samples of one window after which the log is sorted, 0: not asked (dyn_ingest_many)
 };
 hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s);
 #define DYN_EDGE_PACK 960   // class edges that travel in one kernel's arguments
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
-                            int32_t* d_out, WsHeader* header, uint32_t order_word, hipStream_t s);
+                            int32_t* d_out, WsHeader* header, uint32_t order_word, uint32_t* counters, hipStream_t s);
 int64_t dyn_ingest_blocks(int64_t n_req);
+uint32_t dyn_ingest_many(int64_t n_req, int32_t key_bits);
 bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, int32_t key_bits);
 #define DYN_INGEST_MAX_BINS 1024
 

@@ -80,10 +80,33 @@ __device__ __forceinline__ void classes_of(const IngestArgs& a, const ClassEdges
   for (int r = 0; r < N; ++r) cls[r] = (uint32_t)((m[r] * a.n_in_bin + bi[r]) * a.n_out_bin + bo[r]);
 }
 
+// dst[from .. to) = value, a run of every lane (empty: from >= to): the lane writes a few, its wave the others.  All lanes call it.
+__device__ __forceinline__ void fill_runs(int64_t* dst, uint32_t from, uint32_t to, int64_t value) {
+  constexpr int kOwn = 16;
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  if (from < to) dst[from++] = value;              // as a rule the only one
+  if (__ballot(from < to) == 0) return;
+#pragma unroll 1
+  for (int q = 1; q < kOwn && from < to; ++q) dst[from++] = value;
+#pragma unroll 1
+  for (uint64_t more = __ballot(from < to); more != 0; more &= more - 1) {
+    const int who = __builtin_ctzll(more);
+    const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)to, who);
+    const int64_t v = readlane_i64(value, who);
+    for (uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)from, who) + lane; at < end; at += DYN_WAVE) dst[at] = v;
+  }
+}
+
 // Is the trace in window order, and where does every window start?  Only the timestamps are read (8 bytes a request): the
 // routes compute classes from the tokens that they move anyway.  A wave takes kOrderRows rows of 64 consecutive
-// requests, all loads in flight together.
+// requests, all loads in flight together.  Windows without requests are filled by whole waves (a thread per request with 2000
+// of them before the log's first one took 50 us).
+// A log's requests can also lie in a few windows of its grid.  A window is one block's work on both window routes, so a log
+// with a window that alone takes longer than the sort of all is sorted (a.many).  One wave in 16 counts for
+// this: one sample of its window if all its requests lie in one.  Neighbouring windows have counters of their own, and a mean
+// window that long never comes here (dyn_ingest_always_sorts), so windows that share one matter little.
 constexpr int kOrderRows = 8;
+constexpr int kSampleStep = 16 * kOrderRows * DYN_WAVE;   // requests a sample stands for: those of four blocks
 __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_window) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   if (a.n_req == 0) {
@@ -98,6 +121,12 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
   uint32_t bad = 0, ignore = 0;
   // the window of the request before the wave's first
   double left = base > 0 ? window_of(a.t_s[base - 1], a.window_s, r_window, a.n_window, &ignore) : -1.0;
+  if (a.many != 0 && (blockIdx.x & 3) == 0 && threadIdx.x == 0 && base + kOrderRows * DYN_WAVE <= a.n_req) {
+    const double first = window_of(t[0], a.window_s, r_window, a.n_window, &ignore);
+    if (first == window_of(a.t_s[base + kOrderRows * DYN_WAVE - 1], a.window_s, r_window, a.n_window, &ignore) &&
+        atomicAdd(&a.block_hist[(uint32_t)first % DYN_INGEST_COUNTERS], 1u) + 1u == a.many)
+      atomicAdd(a.unsorted, DYN_WS_MAX_BREAKS + 1u);
+  }
 #pragma unroll
   for (int r = 0; r < kOrderRows; ++r) {
     const int64_t i = base + r * DYN_WAVE + lane;
@@ -122,10 +151,9 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
       }
       continue;
     }
-    if (__hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u && in) {
-      for (int64_t w = (int64_t)wp + 1; w <= (int64_t)wq; ++w) a.win_off[w] = i;
-      if (i == a.n_req - 1)
-        for (int64_t w = (int64_t)wq + 1; w <= a.n_window; ++w) a.win_off[w] = a.n_req;
+    if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(a.unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u) {
+      fill_runs(a.win_off, (uint32_t)((int)wp + 1), in ? (uint32_t)((int)wq + 1) : 0u, i);
+      if (__ballot(i == a.n_req - 1) != 0) fill_runs(a.win_off, (uint32_t)((int)wq + 1), i == a.n_req - 1 ? (uint32_t)a.n_window + 1u : 0u, a.n_req);
     }
   }
   if (bad) atomicOr(a.status, bad);
@@ -156,7 +184,7 @@ __device__ __forceinline__ Route route_of(const IngestArgs& a) {
 // workspace header: status 0, the order word (past DYN_WS_MAX_BREAKS when the general sort is forced).
 struct EdgePack { int32_t v[DYN_EDGE_PACK]; };
 __global__ void edge_store_kernel(EdgePack p, int n_a, int32_t* __restrict__ dst_a, int n_b, int32_t* __restrict__ dst_b,
-                                  WsHeader* header, uint32_t order_word) {
+                                  WsHeader* header, uint32_t order_word, uint32_t* counters) {
   for (int i = threadIdx.x; i < n_a; i += blockDim.x) dst_a[i] = p.v[i];
   for (int i = threadIdx.x; i < n_b; i += blockDim.x) dst_b[i] = p.v[n_a + i];
   if (header && threadIdx.x == 0) {
@@ -165,7 +193,10 @@ __global__ void edge_store_kernel(EdgePack p, int n_a, int32_t* __restrict__ dst
     header->cells = 0;
     ((uint32_t*)header)[DYN_WS_HEADER_ORDER_WORD] = order_word;
     for (int q = 0; q < 3; ++q) ((uint32_t*)header)[DYN_WS_HEADER_BARRIER_WORD + q] = 0u;
+    ((uint32_t*)header)[DYN_WS_HEADER_LEFT_WORD] = 0u;
   }
+  if (header && counters)
+    for (int q = threadIdx.x; q < DYN_INGEST_COUNTERS; q += blockDim.x) counters[q] = 0u;
 }
 
 // exclusive sum over the block's threads; `wave_sum`: a word of LDS per wave
@@ -814,7 +845,7 @@ __device__ __forceinline__ void window_move(const IngestArgs& a, int w, int64_t 
 }
 
 template <int WAVES, int ITEMS, int PER_SIMD>
-__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD))) void window_sort_kernel(IngestArgs a, int edge_room) {
+__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(PER_SIMD, PER_SIMD))) void window_sort_kernel(IngestArgs a, int edge_room, int longest) {
   if (route_of(a) != kByWindow) return;
   __shared__ WinLds<WAVES, ITEMS> s;
   extern __shared__ int32_t s_edge[];
@@ -822,26 +853,39 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
   const int64_t beg = a.win_off[w];
   const int len = (int)(a.win_off[w + 1] - beg);
   if (w == a.n_window - 1 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
+  if (len > longest) {                             // for the larger blocks of the kernel after this one
+    if (threadIdx.x == 0) a.key_a[atomicAdd(a.unsorted + (DYN_WS_HEADER_LEFT_WORD - DYN_WS_HEADER_ORDER_WORD), 1u)] = (uint32_t)w;
+    return;
+  }
   const ClassEdges edges = stage_edges(a, s_edge, edge_room);
   window_move<WAVES, ITEMS, false>(a, w, beg, len, edges, s);
 }
 
-// A trace of a few runs, window by window; the blocks share the windows.
-__device__ __forceinline__ void runs_route(const IngestArgs& a, double r_window, WinLds<kRadixWaves, kRadixItems>& s, RunLds& p, int32_t* s_edge) {
+// The windows of a trace of a few runs (RUNS), or the `n` windows that window_sort_kernel left: a list, each of them one
+// piece.  The blocks share them.
+template <bool RUNS>
+__device__ __forceinline__ void shared_windows(const IngestArgs& a, double r_window, int n, WinLds<kRadixWaves, kRadixItems>& s, RunLds& p, int32_t* s_edge) {
   const ClassEdges edges = stage_edges(a, s_edge, kRunEdges);
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
-  for (int w = blockIdx.x; w < a.n_window; w += gridDim.x) {
-    find_pieces<kRadixThreads>(a, r_window, w, p);
-    window_move<kRadixWaves, kRadixItems, true>(a, w, p.out[0], (int)p.out[1], edges, s, &p);
+  if (RUNS && blockIdx.x == 0 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
+  for (int i = blockIdx.x; i < n; i += gridDim.x) {
+    if (RUNS) {
+      find_pieces<kRadixThreads>(a, r_window, i, p);
+      window_move<kRadixWaves, kRadixItems, true>(a, i, p.out[0], (int)p.out[1], edges, s, &p);
+    } else {
+      const int w = (int)a.key_a[i];
+      const int64_t beg = a.win_off[w];
+      window_move<kRadixWaves, kRadixItems, false>(a, w, beg, (int)(a.win_off[w + 1] - beg), edges, s);
+    }
     __syncthreads();
   }
 }
 
-// A trace that is not in window order.
+// A trace that is not in window order, and the long windows of one that is.
 __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
   const IngestArgs& a = g.t;
   const Route route = route_of(a);               // the same for every block
-  if (route == kByWindow) return;
+  const int n_left = route == kByWindow ? (int)a.unsorted[DYN_WS_HEADER_LEFT_WORD - DYN_WS_HEADER_ORDER_WORD] : 0;
+  if (route == kByWindow && (int)blockIdx.x >= n_left) return;
   __shared__ union {
     RadixLds radix;
     struct {
@@ -850,8 +894,12 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
       int32_t edge[kRunEdges];
     } runs;
   } lds;
+  if (route == kByWindow) {
+    shared_windows<false>(a, g.r_window, n_left, lds.runs.win, lds.runs.run, lds.runs.edge);
+    return;
+  }
   if (route == kByRuns) {
-    runs_route(a, g.r_window, lds.runs.win, lds.runs.run, lds.runs.edge);
+    shared_windows<true>(a, g.r_window, a.n_window, lds.runs.win, lds.runs.run, lds.runs.edge);
     return;
   }
   if ((int)blockIdx.x >= g.blocks) return;
@@ -892,11 +940,9 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
   }
   if (a.n_req == 0)
     for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
-  // The offsets (cell_off[c] = number of requests with key < c), a tile of sorted keys in LDS at a time: a request's thread fills
-  // the cells from the key before it on, a few of them by itself, and its wave the others (the 35 000 empty cells before
-  // the log of a grid's last minutes took one thread 1.1 ms).  What is left behind the last request is its block's.
-  constexpr int kOwnCells = 16;
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  // The offsets (cell_off[c] = number of requests with key < c), a tile of sorted keys in LDS at a time: a request fills
+  // the cells from the key before it on (by one thread the 35 000 empty cells before the log of a grid's last minutes took 1.1 ms).
+  // What is left behind the last request is its block's.
   uint32_t left = 0;                             // one more than the key before the tile
   for (int64_t at = beg; at < end; at += kRadixTile) {
     const int count = (int)std::min<int64_t>(kRadixTile, end - at);
@@ -906,15 +952,8 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
     __syncthreads();
 #pragma unroll 1
     for (int i = threadIdx.x; i - (int)threadIdx.x < count; i += kRadixThreads) {
-      uint32_t c = i > 0 ? s.move[min(i, count) - 1] + 1u : left;
-      const uint32_t to = s.move[min(i, count - 1)] + 1u;        // beyond the tile: c == to
-      for (int q = 0; q < kOwnCells && c < to; ++q) a.cell_off[c++] = at + i;
-      for (uint64_t more = __ballot(c < to); more != 0; more &= more - 1) {
-        const int who = __builtin_ctzll(more);
-        const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)to, who);
-        const int64_t off = at + __builtin_amdgcn_readlane(i, who);
-        for (uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)c, who) + lane; b < upto; b += DYN_WAVE) a.cell_off[b] = off;
-      }
+      const uint32_t from = i > 0 ? s.move[min(i, count) - 1] + 1u : left, to = s.move[min(i, count - 1)] + 1u;   // beyond the tile: equal
+      fill_runs(a.cell_off, from, to, at + i);
     }
     left = s.move[count - 1] + 1u;
     __syncthreads();
@@ -928,21 +967,21 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
 int64_t dyn_ingest_blocks(int64_t n_req) { return n_req > 0 ? (n_req + kRadixTile - 1) / kRadixTile : 1; }
 
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
-                            int32_t* d_out, WsHeader* header, uint32_t order_word, hipStream_t s) {
+                            int32_t* d_out, WsHeader* header, uint32_t order_word, uint32_t* counters, hipStream_t s) {
   EdgePack p;
   if (n_in + n_out <= DYN_EDGE_PACK) {          // the usual case: header and both lists in one launch
     if (n_in) memcpy(p.v, in_edge, n_in * sizeof(int32_t));
     if (n_out) memcpy(p.v + n_in, out_edge, n_out * sizeof(int32_t));
-    hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(256), 0, s, p, (int)n_in, d_in, (int)n_out, d_out, header, order_word);
+    hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(256), 0, s, p, (int)n_in, d_in, (int)n_out, d_out, header, order_word, counters);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(64), 0, s, p, 0, d_in, 0, d_out, header, order_word);
+  hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(64), 0, s, p, 0, d_in, 0, d_out, header, order_word, counters);
   const struct { const int32_t* src; size_t n; int32_t* dst; } parts[2] = {{in_edge, n_in, d_in}, {out_edge, n_out, d_out}};
   for (const auto& part : parts)
     for (size_t at = 0; at < part.n; at += DYN_EDGE_PACK) {
       const int n = (int)std::min<size_t>(DYN_EDGE_PACK, part.n - at);
       memcpy(p.v, part.src + at, (size_t)n * sizeof(int32_t));
-      hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(256), 0, s, p, n, part.dst + at, 0, part.dst, (WsHeader*)nullptr, 0u);
+      hipLaunchKernelGGL(edge_store_kernel, dim3(1), dim3(256), 0, s, p, n, part.dst + at, 0, part.dst, (WsHeader*)nullptr, 0u, (uint32_t*)nullptr);
     }
   return hipGetLastError();
 }
@@ -956,6 +995,15 @@ static int sort_passes(int32_t key_bits) { return key_bits <= 0 ? 1 : (key_bits 
 bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, int32_t key_bits) {
   if (n_class > DYN_INGEST_MAX_BINS) return true;
   return 2e-3 * (double)n_req / n_window > 30.0 + 15e-6 * sort_passes(key_bits) * (double)n_req;
+}
+
+// Samples of one window (order_kernel) after which the log is sorted: those of the longest window that one block moves while
+// the device sorts everything.  The block 8 us and 1.5 us a thousand requests, the sort 50 us and 16 us a pass and million.
+// Measured (us; the window routes and the sort): ordered, 10 M requests in 3 of 2016 windows 6750, 378; 6 M in 10 of
+// 1440 1266, 276; 500 000 in 5 of 2016 (by 64 threads) 1575, 102; six runs, 10 M in 3 of 2016 5100, 373.
+uint32_t dyn_ingest_many(int64_t n_req, int32_t key_bits) {
+  const double longest = (42.0 + 16e-6 * sort_passes(key_bits) * (double)n_req) / 1.5e-3;
+  return (double)n_req > longest ? (uint32_t)(longest / kSampleStep) + 1u : 0u;
 }
 
 hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
@@ -974,13 +1022,18 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
     // The smallest tile that holds a window of 1.75 times the mean (traffic is not even).  Measured (us, by mean requests per
     // window; 1440 to 2016 windows, 17 280 for 579), tiles of 512, 2048, 4096 and 12 288: 10: 7, 12, 13, 27; 198: 9, 13, 15, 28;
     // 579: 78, 69, 102, 207; 694: 27, 11, 16, 23; 1389: 45, 22, 15, 26; 2778: 81, 33, 31, 29; 6944: 189, 65, 61, 45.
+    // A longer window than the tile goes to the 16-wave blocks of the next kernel, which ran empty before: 1.5 us a thousand
+    // requests, where these take 15, 4.1, 3.1 and 2.0.  Of the largest tile only what is far longer than four tiles
+    // and than the others: where all are long these blocks, twice as many, are as quick.  Measured (us; all here, and left):
+    // 500 000 requests in 50 of 2016 windows 221, 36; 200 000 in 20 of 1440 207, 35; 1000 in 1 of 60 31, 16; 580 000 in 1000 of
+    // 2016 54, 53; 20 M in 100 of 2016 519, 365; evenly, 580 000 and 2.3 M in 2016 28, 26 and 32, 32.
     const dim3 grid((unsigned)a.n_window);
     const size_t lds = room * sizeof(int32_t);
     const double peak = 1.75 * (double)n / a.n_window;
-    if (peak <= 512) hipLaunchKernelGGL((window_sort_kernel<1, 8, 4>), grid, dim3(DYN_WAVE), lds, s, a, (int)room);
-    else if (peak <= 2048) hipLaunchKernelGGL((window_sort_kernel<4, 8, 6>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room);
-    else if (peak <= 4096) hipLaunchKernelGGL((window_sort_kernel<4, 16, 4>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room);
-    else hipLaunchKernelGGL((window_sort_kernel<8, 24, 4>), grid, dim3(8 * DYN_WAVE), lds, s, a, (int)room);
+    if (peak <= 512) hipLaunchKernelGGL((window_sort_kernel<1, 8, 4>), grid, dim3(DYN_WAVE), lds, s, a, (int)room, 512);
+    else if (peak <= 2048) hipLaunchKernelGGL((window_sort_kernel<4, 8, 6>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room, 2048);
+    else if (peak <= 4096) hipLaunchKernelGGL((window_sort_kernel<4, 16, 4>), grid, dim3(4 * DYN_WAVE), lds, s, a, (int)room, 4096);
+    else hipLaunchKernelGGL((window_sort_kernel<8, 24, 4>), grid, dim3(8 * DYN_WAVE), lds, s, a, (int)room, std::max(4 * 12288, (int)(4 * n / a.n_window)));
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (n == 0) return hipSuccess;   // nothing to sort: the flag word stays 0
   }

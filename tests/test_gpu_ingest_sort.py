@@ -167,3 +167,46 @@ def test_sort_is_as_quick_where_most_cells_are_empty(dyn):
         d = [torch.from_numpy(tr[k]).cuda() for k in ("t_s", "in_tok", "out_tok")]
         us.append(_us(lambda: dyn.dyn_trace_ingest(*d, None, edges, 2000, 10.0)))
     assert us[1] < 4.0 * us[0], us
+
+
+def _counted(seed, counts, n_run=1, n_model=1):
+    """A log with counts[w] requests in window w of 10 s: in time order, or as n_run ordered runs that each take part in every window."""
+    n = int(np.sum(counts))
+    tr = _log(seed, n, 1.0, n_model)
+    tr["t_s"] = np.repeat(10.0 * np.arange(len(counts)), counts) + 9.0 * tr["t_s"]
+    tr["t_s"].sort()
+    if n_run > 1:
+        for k in tr:
+            tr[k] = np.concatenate([tr[k][r::n_run] for r in range(n_run)])
+    return tr
+
+
+# uneven logs: a window longer than the tile that the mean window asks for is left to larger blocks (512, 2048, 4096 and
+# 4 x 12 288 requests, and one more; several of them; all but one), one that alone takes longer than the sort has the log sorted
+@pytest.mark.parametrize("counts,n_run,left,sorts", [
+    ([512, 513] + [100] * 20, 1, 1, False), ([500] * 20 + [2048, 2049], 1, 1, False), ([1500] * 20 + [4097, 4096], 1, 1, False),
+    ([6000] * 400 + [4 * WINDOW + 1, 4 * WINDOW], 1, 1, False), ([4000] * 20 + [4 * WINDOW], 1, None, True), ([0] * 600 + [520] * 300, 1, 300, False), ([0] * 99 + [25_000], 1, 1, False),
+    ([200] * 2000 + [20_000, 100], 1, 1, False), ([200] * 2000 + [60_000, 100], 1, None, True), ([0] * 2000 + [90_000] * 2, 1, None, True),
+    ([200] * 2000 + [60_000, 100], 2, None, True), ([0] * 2000 + [90_000] * 2, 6, None, True), ([200] * 200 + [15_000, 100], 6, 0, False)])
+@pytest.mark.parametrize("n_model", [1, 4])
+def test_uneven_log(dyn, counts, n_run, left, sorts, n_model):
+    edges = _edges(5, 5, n_model)
+    tr = _counted(len(counts), counts, n_run, n_model)
+    got = _call(dyn, tr, edges, len(counts), 10.0)
+    assert dyn.dyn_workspace_status(got[3]) == 0
+    _check(got, tr, edges, len(counts), 10.0)
+    words = got[3][:256].view(torch.int32).cpu().numpy()        # 8: breaks, or past 48 where the log is sorted; 12: windows left
+    assert (words[8] > 48) == sorts and (sorts or words[8] == n_run - 1)
+    assert sorts or words[12] == left
+
+
+@pytest.mark.parametrize("n_run", [1, 6])
+def test_log_of_a_few_long_windows_is_as_quick_as_an_even_one(dyn, n_run):
+    """Three million requests in three of 2016 windows (by window one block each: 19 and 14 times as long)."""
+    edges = _edges(5, 5)
+    us = []
+    for counts in ([1488] * 2016, [0] * 2013 + [1_000_000] * 3):
+        tr = _counted(3, counts, n_run)
+        d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
+        us.append(_us(lambda: dyn.dyn_trace_ingest(*d, None, edges, 2016, 10.0)))
+    assert us[1] < 8.0 * us[0], us
