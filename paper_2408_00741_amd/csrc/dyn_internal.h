@@ -118,7 +118,7 @@ struct WsHeader {
 #define DYN_WS_HEADER_ORDER_WORD 8   // 32-bit word of a 256-byte header region used by the ingestion kernels
 #define DYN_WS_HEADER_BARRIER_WORD 9 // arrivals at the general sort's barriers, blocks that came to sort, blocks that sort (3 words, zeroed with the header)
 #define DYN_WS_HEADER_LEFT_WORD 12   // windows that the window route left to larger blocks (zeroed with the header)
-#define DYN_WS_HEADER_BREAK_WORD 16  // where the trace's runs after the first start, as far as there are at most DYN_WS_MAX_BREAKS
+#define DYN_WS_HEADER_BREAK_WORD 16  // where the trace's runs after the first start, as far as there are at most DYN_WS_MAX_BREAKS; the last of them: the sort's barriers passed
 #define DYN_WS_MAX_BREAKS 48u
 #define DYN_INGEST_COUNTERS 1024     // of the sampled requests per window (the first words of block_hist, zeroed with the header)
 #define DYN_WS_KIND_WORD 1u

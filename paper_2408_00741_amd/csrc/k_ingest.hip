@@ -236,13 +236,14 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wa
 // 523 us with separate scan phases, all waves fencing and single words scattered; 225 us so.
 //
 // The barrier: an arrival counter in the workspace header, zeroed with the header; barrier number k is passed when
-// the counter reaches k * blocks.  Only blocks that run take part (join_team), so other work on the device can
+// the counter reaches k * blocks.  The block that arrives last says so in a word of its own, which the others watch: watching the
+// counter they held up the arrivals (six million requests 335 us, 280 so).  Only blocks that run take part (join_team), so other work on the device can
 // delay a barrier but not stop it; if it takes seconds all the same, the wait is given up (every block leaves,
 // DYN_WS_SORT_ABANDONED is raised).
 struct RadixArgs {
   IngestArgs t;
   double r_window;
-  uint32_t* barrier; uint32_t* join; uint32_t* members;
+  uint32_t* barrier; uint32_t* join; uint32_t* members; uint32_t* passed;
   int64_t cells;
   int32_t passes, bits;
   int32_t blocks;                                // that sort (the grid may have more, for the runs)
@@ -252,7 +253,7 @@ constexpr uint32_t kBarrierSpins = 1u << 22;     // x about a microsecond per lo
 // The blocks that sort together: those that run when the first one has waited for them.
 struct RadixTeam { int blocks, block; };
 constexpr uint32_t kTeamClosed = 1u << 31;
-constexpr uint32_t kTeamSpins = 256;             // x a third of a microsecond: the leader's wait for blocks that do not run yet
+constexpr uint32_t kTeamSpins = 256, kTeamMaxSpins = 1u << 15;   // x a third of a microsecond: the leader's wait for blocks that do not run yet
 constexpr int kRadixWaves = 16;
 constexpr int kRadixThreads = kRadixWaves * DYN_WAVE;
 constexpr int kRadixItems = 8;                   // requests per thread and tile
@@ -267,18 +268,21 @@ __device__ __forceinline__ void put(T* p, T v) { __hip_atomic_store(p, v, __ATOM
 // false: given up (block-uniform).  All writes of the block before the call are visible to every block after it: every
 // wave waits for its own stores, and the waiting thread releases before it arrives and acquires after it has seen
 // the others (the block's other waves share its caches and follow it through the block barrier).
-__device__ __forceinline__ bool grid_barrier(uint32_t* counter, uint32_t target, uint32_t* s_flag) {
+__device__ __forceinline__ bool grid_barrier(uint32_t* counter, uint32_t* passed, uint32_t number, uint32_t blocks, uint32_t* s_flag) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t spins = 0;
     bool ok = true;
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (++spins > kBarrierSpins) { ok = false; break; }
-      __builtin_amdgcn_s_sleep(8);
+    if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == number * blocks) {
+      put(passed, number);
+    } else {
+      while (__hip_atomic_load(passed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < number) {
+        if (++spins > kBarrierSpins) { ok = false; break; }
+        __builtin_amdgcn_s_sleep(8);
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     *s_flag = ok ? 1u : 0u;
@@ -302,15 +306,24 @@ struct RadixLds {
 };
 
 // Which of the sorting blocks this one is, and how many there are ({0, 0}: it came too late, or the wait was given up).  The
-// first block to arrive waits a moment for the rest of `all` and then closes the team; a block that arrives later leaves.
-// So every block that the barriers wait for is running, whatever else the device is busy with.
-__device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members, uint32_t all, uint32_t* status, RadixLds& s) {
+// first block to arrive waits for the rest of `all` and then closes the team; a block that arrives later leaves.  So every
+// block that the barriers wait for is running, whatever else the device is busy with.  It waits as long as the sort would take
+// longer with the blocks that are there than with all (`work`: looks that one block alone takes for the sort), but at
+// least a moment and at most some milliseconds.  After a moment only, 20 M requests beside an evaluation were at times left to a few
+// blocks for 23 ms.
+__device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members, uint32_t* passed, uint32_t all, float work, uint32_t* status, uint32_t* s_ticket, uint32_t* s_members) {
   if (threadIdx.x == 0) {
     const uint32_t ticket = atomicAdd(join, 1u);
     uint32_t n = 0;
     if (ticket == 0) {
-      for (uint32_t spins = 0; spins < kTeamSpins && __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all; ++spins) __builtin_amdgcn_s_sleep(4);
+      for (uint32_t spins = 0; spins < kTeamMaxSpins; ++spins) {
+        const uint32_t here = __hip_atomic_load(join, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (here >= all || (spins >= kTeamSpins && (float)spins > work / (float)here - work / (float)all)) break;
+        __builtin_amdgcn_s_sleep(4);
+      }
       n = atomicOr(join, kTeamClosed);
+      put(passed, 0u);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       put(members, n);
     } else if (ticket < kTeamClosed) {
       for (uint32_t spins = 0; n == 0 && spins < kBarrierSpins; ++spins) {
@@ -319,11 +332,11 @@ __device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members
       }
       if (n == 0) atomicOr(status, DYN_WS_SORT_ABANDONED);
     }
-    s.flag = n;
-    s.wave_sum[0] = ticket;
+    *s_members = n;
+    *s_ticket = ticket;
   }
   __syncthreads();
-  const RadixTeam m = {__builtin_amdgcn_readfirstlane((int)s.flag), __builtin_amdgcn_readfirstlane((int)s.wave_sum[0])};
+  const RadixTeam m = {__builtin_amdgcn_readfirstlane((int)*s_members), __builtin_amdgcn_readfirstlane((int)*s_ticket)};
   __syncthreads();
   return m;
 }
@@ -904,12 +917,12 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
   }
   if ((int)blockIdx.x >= g.blocks) return;
   RadixLds& s = lds.radix;
-  const RadixTeam m = join_team(g.join, g.members, (uint32_t)g.blocks, a.status, s);
+  const RadixTeam m = join_team(g.join, g.members, g.passed, (uint32_t)g.blocks, (float)a.n_req * 0.012f * (float)g.passes, a.status, &s.wave_sum[0], &s.flag);
   if (m.blocks == 0) return;
   uint32_t passed = 0;                           // barriers behind this block
   auto sync = [&]() {
     ++passed;
-    const bool ok = grid_barrier(g.barrier, passed * (uint32_t)m.blocks, &s.flag);
+    const bool ok = grid_barrier(g.barrier, g.passed, passed, (uint32_t)m.blocks, &s.flag);
     if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
     return ok;
   };
@@ -1053,6 +1066,7 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   RadixArgs r;
   r.t = a; r.r_window = r_window; r.cells = cells; r.passes = passes; r.bits = bits;
   r.barrier = a.unsorted + (DYN_WS_HEADER_BARRIER_WORD - DYN_WS_HEADER_ORDER_WORD); r.join = r.barrier + 1; r.members = r.barrier + 2;
+  r.passed = a.unsorted + (DYN_WS_HEADER_BREAK_WORD + DYN_WS_MAX_BREAKS - 1 - DYN_WS_HEADER_ORDER_WORD);   // the last break's word: a log that is sorted needs no breaks
   // a block for every tile, as far as they fit the device and the digit counts (a word per digit and block) the workspace
   const int64_t room = ((int64_t)DYN_INGEST_MAX_BINS * a.n_block) >> bits;
   const int64_t n_tile = (n + kRadixTile - 1) / kRadixTile;

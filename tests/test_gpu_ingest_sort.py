@@ -210,3 +210,21 @@ def test_log_of_a_few_long_windows_is_as_quick_as_an_even_one(dyn, n_run):
         d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
         us.append(_us(lambda: dyn.dyn_trace_ingest(*d, None, edges, 2016, 10.0)))
     assert us[1] < 8.0 * us[0], us
+
+
+def test_sort_beside_another_kernel_is_not_left_to_a_few_blocks(dyn):
+    """The device is full when the sort starts: its first block waits for the others as long as that pays."""
+    edges = _edges(5, 5)
+    tr = _log(20, 4_000_000, 14400.0)
+    d = [torch.from_numpy(tr[k]).cuda() for k in ("t_s", "in_tok", "out_tok")]
+    full = torch.rand(1 << 28, device="cuda")
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(12):
+            torch.erfinv(full, out=full)
+    got = dyn.dyn_trace_ingest(*d, None, edges, 1440, 10.0)
+    torch.cuda.synchronize()
+    assert dyn.dyn_workspace_status(got[3]) == 0
+    _check(got, tr, edges, 1440, 10.0)
+    assert int(got[3][:256].view(torch.int32)[11]) >= 64         # blocks that sorted
