@@ -649,7 +649,7 @@ int dyn_trace_ingest(const double* t_s, const int32_t* in_tok, const int32_t* ou
   while (((int64_t)1 << bits) < cells) ++bits;
   a.key_bits = bits;
   a.force_sort = dyn_ingest_always_sorts(n_req, n_window, G, bits) ? 1 : 0;
-  a.many = a.force_sort ? 0u : dyn_ingest_many(n_req, bits);
+  a.many = a.force_sort ? 0u : dyn_ingest_many(n_req, n_window, bits);
   // the workspace header (status 0, order word = "general sort forced") and the edge lists, which travel in a kernel's
   // arguments: the host arrays are free on return and nothing waits for the stream
   if (!hip_ok(dyn_launch_edges(e->in_edge, (size_t)e->n_model * (e->n_in_bin - 1), e->out_edge, (size_t)e->n_model * (e->n_out_bin - 1),

@@ -120,7 +120,7 @@ struct WsHeader {
 #define DYN_WS_HEADER_LEFT_WORD 12   // windows that the window route left to larger blocks (zeroed with the header)
 #define DYN_WS_HEADER_BREAK_WORD 16  // where the trace's runs after the first start, as far as there are at most DYN_WS_MAX_BREAKS; the last of them: the sort's barriers passed
 #define DYN_WS_MAX_BREAKS 48u
-#define DYN_INGEST_COUNTERS 1024     // of the sampled requests per window (the first words of block_hist, zeroed with the header)
+#define DYN_INGEST_COUNTERS 256      // of the sampled requests per window (the first words of block_hist, zeroed with the header)
 #define DYN_WS_KIND_WORD 1u
 #define DYN_WS_KIND_CELLS 2u
 
@@ -185,7 +185,7 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s);
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
                             int32_t* d_out, WsHeader* header, uint32_t order_word, uint32_t* counters, hipStream_t s);
 int64_t dyn_ingest_blocks(int64_t n_req);
-uint32_t dyn_ingest_many(int64_t n_req, int32_t key_bits);
+uint32_t dyn_ingest_many(int64_t n_req, int32_t n_window, int32_t key_bits);
 bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, int32_t key_bits);
 #define DYN_INGEST_MAX_BINS 1024
 

@@ -106,8 +106,8 @@ __device__ __forceinline__ void fill_runs(int64_t* dst, uint32_t from, uint32_t 
 // this: one sample of its window if all its requests lie in one.  Neighbouring windows have counters of their own, and a mean
 // window that long never comes here (dyn_ingest_always_sorts), so windows that share one matter little.
 constexpr int kOrderRows = 8;
-constexpr int kSampleStep = 16 * kOrderRows * DYN_WAVE;   // requests a sample stands for: those of four blocks
-__global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_window) {
+constexpr int kSampleStep = 4 * kOrderRows * DYN_WAVE;   // requests a sample stands for: those of a block, of a large log those of four
+__global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_window, uint32_t sparse) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   if (a.n_req == 0) {
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w <= a.n_window; w += (int64_t)gridDim.x * blockDim.x) a.win_off[w] = 0;
@@ -121,12 +121,7 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
   uint32_t bad = 0, ignore = 0;
   // the window of the request before the wave's first
   double left = base > 0 ? window_of(a.t_s[base - 1], a.window_s, r_window, a.n_window, &ignore) : -1.0;
-  if (a.many != 0 && (blockIdx.x & 3) == 0 && threadIdx.x == 0 && base + kOrderRows * DYN_WAVE <= a.n_req) {
-    const double first = window_of(t[0], a.window_s, r_window, a.n_window, &ignore);
-    if (first == window_of(a.t_s[base + kOrderRows * DYN_WAVE - 1], a.window_s, r_window, a.n_window, &ignore) &&
-        atomicAdd(&a.block_hist[(uint32_t)first % DYN_INGEST_COUNTERS], 1u) + 1u == a.many)
-      atomicAdd(a.unsorted, DYN_WS_MAX_BREAKS + 1u);
-  }
+  double first = 0.0;                              // the wave's first window, in its first lane
 #pragma unroll
   for (int r = 0; r < kOrderRows; ++r) {
     const int64_t i = base + r * DYN_WAVE + lane;
@@ -134,6 +129,7 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
     const double wq = window_of(t[r], a.window_s, r_window, a.n_window, &bad);
     // Window order: compare with the request before.  Where the window changes the boundaries are written: in a trace in
     // window order win_off[w] = number of requests in windows before w (the values are not used otherwise).
+    if (r == 0) first = wq;
     double wp = __shfl_up(wq, 1, DYN_WAVE);
     if (lane == 0) wp = left;
     left = __shfl(wq, DYN_WAVE - 1, DYN_WAVE);
@@ -156,6 +152,8 @@ __global__ __launch_bounds__(256) void order_kernel(IngestArgs a, double r_windo
       if (__ballot(i == a.n_req - 1) != 0) fill_runs(a.win_off, (uint32_t)((int)wq + 1), i == a.n_req - 1 ? (uint32_t)a.n_window + 1u : 0u, a.n_req);
     }
   }
+  if (a.many != 0 && (blockIdx.x & sparse) == 0 && threadIdx.x == 0 && base + kOrderRows * DYN_WAVE <= a.n_req && first == left)
+    if (atomicAdd(&a.block_hist[(uint32_t)first % DYN_INGEST_COUNTERS], 1u) + 1u == a.many) atomicAdd(a.unsorted, DYN_WS_MAX_BREAKS + 1u);
   if (bad) atomicOr(a.status, bad);
 }
 
@@ -254,12 +252,8 @@ constexpr uint32_t kBarrierSpins = 1u << 22;     // x about a microsecond per lo
 struct RadixTeam { int blocks, block; };
 constexpr uint32_t kTeamClosed = 1u << 31;
 constexpr uint32_t kTeamSpins = 256, kTeamMaxSpins = 1u << 15;   // x a third of a microsecond: the leader's wait for blocks that do not run yet
-constexpr int kRadixWaves = 16;
-constexpr int kRadixThreads = kRadixWaves * DYN_WAVE;
 constexpr int kRadixItems = 8;                   // requests per thread and tile
-constexpr int kRadixTile = kRadixThreads * kRadixItems;
-constexpr int kRadixOwn = DYN_INGEST_MAX_BINS / kRadixThreads;   // digits a thread owns in the scans
-static_assert(kRadixTile * sizeof(uint32_t) == kRadixWaves * DYN_INGEST_MAX_BINS * sizeof(uint16_t), "the wave counters become the second move buffer");
+constexpr int kLargeWaves = 16, kSmallWaves = 4; // of a block: dyn_launch_ingest says where the line lies
 
 // a store that other blocks read after the next barrier
 template <typename T>
@@ -293,15 +287,20 @@ __device__ __forceinline__ bool grid_barrier(uint32_t* counter, uint32_t* passed
 
 // LDS of a block: the wave counters of a tile are done with when its requests' places are known, and are then the
 // second buffer of the move.
+template <int WAVES>
 struct RadixLds {
-  uint32_t move[kRadixTile];
+  static constexpr int kThreads = WAVES * DYN_WAVE, kTile = kThreads * kRadixItems;
+  static constexpr int kOwn = DYN_INGEST_MAX_BINS / kThreads;   // digits a thread owns in the scans
+  static constexpr int kCopies = WAVES >= 8 ? 4 : 2;
+  static_assert(kTile * sizeof(uint32_t) == WAVES * DYN_INGEST_MAX_BINS * sizeof(uint16_t), "the wave counters become the second move buffer");
+  uint32_t move[kTile];
   union {
-    uint16_t wcnt[kRadixWaves][DYN_INGEST_MAX_BINS];
-    uint32_t cnt[4][DYN_INGEST_MAX_BINS];        // digit counts of the block's run, four copies
-    uint32_t move2[kRadixTile];
+    uint16_t wcnt[WAVES][DYN_INGEST_MAX_BINS];
+    uint32_t cnt[kCopies][DYN_INGEST_MAX_BINS];  // digit counts of the block's run, a few copies
+    uint32_t move2[kTile];
   };
   uint32_t to[DYN_INGEST_MAX_BINS];              // output position of a digit's first request of the tile, less its place in the tile
-  uint32_t wave_sum[kRadixWaves];
+  uint32_t wave_sum[WAVES];
   uint32_t flag;
 };
 
@@ -342,19 +341,21 @@ __device__ __forceinline__ RadixTeam join_team(uint32_t* join, uint32_t* members
 }
 
 // Keys of the requests [beg, end): cell = window * classes + class.
-__device__ __forceinline__ void radix_keys(const IngestArgs& a, double r_window, int64_t beg, int64_t end, RadixLds& s) {
-  const ClassEdges edges = stage_edges(a, (int32_t*)s.move, kRadixTile);
+template <int WAVES>
+__device__ __forceinline__ void radix_keys(const IngestArgs& a, double r_window, int64_t beg, int64_t end, RadixLds<WAVES>& s) {
+  constexpr int kThreads = RadixLds<WAVES>::kThreads;
+  const ClassEdges edges = stage_edges(a, (int32_t*)s.move, RadixLds<WAVES>::kTile);
   __syncthreads();
   const uint32_t G = (uint32_t)(a.n_model * a.n_in_bin * a.n_out_bin);
   uint32_t bad = 0;
   constexpr int N = 4;
-  for (int64_t at = beg; at < end; at += N * kRadixThreads) {
+  for (int64_t at = beg; at < end; at += N * kThreads) {
     double t[N];
     int32_t x[N], y[N], mdl[N];
     uint32_t cls[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) {
-      const int64_t i = std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1);
+      const int64_t i = std::min<int64_t>(at + r * kThreads + threadIdx.x, end - 1);
       t[r] = a.t_s[i];
       x[r] = a.in_tok[i];
       y[r] = a.out_tok[i];
@@ -363,7 +364,7 @@ __device__ __forceinline__ void radix_keys(const IngestArgs& a, double r_window,
     classes_of<N>(a, edges, x, y, mdl, cls, &bad);
 #pragma unroll
     for (int r = 0; r < N; ++r) {
-      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      const int64_t i = at + r * kThreads + threadIdx.x;
       const uint32_t w = (uint32_t)window_of(t[r], a.window_s, r_window, a.n_window, &bad);
       if (i < end) put(a.key_a + i, w * G + cls[r]);
     }
@@ -374,23 +375,25 @@ __device__ __forceinline__ void radix_keys(const IngestArgs& a, double r_window,
 
 // Digit counts of the keys [beg, end) -> hist[digit][block].  In runs of equal digits (the keys of a later pass) a wave
 // adds once for all its lanes; else lanes add to one of four copies, which shortens the queues of equal digits.
-__device__ __forceinline__ void radix_count(const uint32_t* keys, int64_t beg, int64_t end, int shift, int bits, uint32_t* hist, RadixTeam m, RadixLds& s) {
+template <int WAVES>
+__device__ __forceinline__ void radix_count(const uint32_t* keys, int64_t beg, int64_t end, int shift, int bits, uint32_t* hist, RadixTeam m, RadixLds<WAVES>& s) {
+  constexpr int kThreads = RadixLds<WAVES>::kThreads, kTile = RadixLds<WAVES>::kTile, kCopies = RadixLds<WAVES>::kCopies;
   const int nbins = 1 << bits;
   const uint32_t mask = (uint32_t)nbins - 1u;
   const int lane = threadIdx.x & (DYN_WAVE - 1);
-  for (int b = threadIdx.x; b < 4 * DYN_INGEST_MAX_BINS; b += kRadixThreads) (&s.cnt[0][0])[b] = 0;
+  for (int b = threadIdx.x; b < kCopies * DYN_INGEST_MAX_BINS; b += kThreads) (&s.cnt[0][0])[b] = 0;
   __syncthreads();
-  uint32_t* mine = s.cnt[lane & 3];
-  for (int64_t at = beg; at < end; at += kRadixTile) {
+  uint32_t* mine = s.cnt[lane & (kCopies - 1)];
+  for (int64_t at = beg; at < end; at += kTile) {
     uint32_t key[kRadixItems];
 #pragma unroll
     for (int r = 0; r < kRadixItems; ++r) {
-      const int64_t i = at + r * kRadixThreads + threadIdx.x;
+      const int64_t i = at + r * kThreads + threadIdx.x;
       key[r] = keys[i < end ? i : end - 1];
     }
 #pragma unroll
     for (int r = 0; r < kRadixItems; ++r) {
-      const bool in = at + r * kRadixThreads + threadIdx.x < end;
+      const bool in = at + r * kThreads + threadIdx.x < end;
       const uint32_t d = (key[r] >> shift) & mask;
       const uint64_t there = __ballot(in);
       if (there == 0) continue;
@@ -403,15 +406,27 @@ __device__ __forceinline__ void radix_count(const uint32_t* keys, int64_t beg, i
     }
   }
   __syncthreads();
-  for (int b = threadIdx.x; b < nbins; b += kRadixThreads)
-    put(&hist[(size_t)b * m.blocks + m.block], s.cnt[0][b] + s.cnt[1][b] + s.cnt[2][b] + s.cnt[3][b]);
+  for (int b = threadIdx.x; b < nbins; b += kThreads) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int q = 0; q < kCopies; ++q) n += s.cnt[q][b];
+    put(&hist[(size_t)b * m.blocks + m.block], n);
+  }
 }
 
-// hist[d][0 .. blocks) -> inclusive sums, one wave per digit
+// hist[d][0 .. blocks) -> inclusive sums, one wave per digit where the blocks are many
+template <int WAVES>
 __device__ __forceinline__ void radix_scan(uint32_t* hist, int bits, RadixTeam m) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int n = m.blocks;
-  for (int d = (int)(threadIdx.x / DYN_WAVE) * n + m.block; d < (1 << bits); d += kRadixWaves * n) {
+  if (n <= 8) {                                  // a few counts: a thread per digit
+    for (int d = m.block * WAVES * DYN_WAVE + threadIdx.x; d < (1 << bits); d += n * WAVES * DYN_WAVE) {
+      uint32_t sum = 0;
+      for (int q = 0; q < n; ++q) put(&hist[(size_t)d * n + q], sum += hist[(size_t)d * n + q]);
+    }
+    return;
+  }
+  for (int d = (int)(threadIdx.x / DYN_WAVE) * n + m.block; d < (1 << bits); d += WAVES * n) {
     uint32_t* row = hist + (size_t)d * n;
     uint32_t carry = 0;
     for (int base = 0; base < n; base += 4 * DYN_WAVE) {
@@ -433,13 +448,14 @@ __device__ __forceinline__ void radix_scan(uint32_t* hist, int bits, RadixTeam m
   }
 }
 
-// Stable move of one tile of `count` requests (FULL: kRadixTile).  What is missing to kRadixTile takes part as requests of
+// Stable move of one tile of `count` requests (FULL: a whole one).  What is missing to a whole one takes part as requests of
 // the last digit, behind all others, and is not written.  Every wave owns a contiguous run of rows of 64 requests and
 // walks them in order; a request's rank among the row's requests with its digit comes from wave ballots.  `next`: output
-// position of the next request of each digit that the thread owns (threadIdx.x * kRadixOwn ...), moved on.
-template <bool FULL>
+// position of the next request of each digit that the thread owns (threadIdx.x * kOwn ...), moved on.
+template <int WAVES, bool FULL>
 __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_t* in_in, const int32_t* out_in, uint32_t* keys_out,
-                                           int32_t* in_out, int32_t* out_out, int count, int shift, int bits, uint32_t* next, RadixLds& s) {
+                                           int32_t* in_out, int32_t* out_out, int count, int shift, int bits, uint32_t* next, RadixLds<WAVES>& s) {
+  constexpr int kThreads = RadixLds<WAVES>::kThreads, kOwn = RadixLds<WAVES>::kOwn;
   const int nbins = 1 << bits;
   const uint32_t mask = (uint32_t)nbins - 1u;
   const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
@@ -455,7 +471,7 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
     if (!FULL && at + r * DYN_WAVE >= count) key[r] = ~0u;
   }
 #pragma unroll
-  for (int q = 0; q < kRadixItems; ++q) s.move2[q * kRadixThreads + threadIdx.x] = 0;   // the wave counters
+  for (int q = 0; q < kRadixItems; ++q) s.move2[q * kThreads + threadIdx.x] = 0;   // the wave counters
   __syncthreads();
   uint16_t* my = s.wcnt[wave];
 #pragma unroll
@@ -477,22 +493,22 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
   }
   __syncthreads();
   // per digit: where its requests start in the tile, and where each wave's among them do
-  uint32_t total[kRadixOwn], sum = 0;
+  uint32_t total[kOwn], sum = 0;
 #pragma unroll
-  for (int q = 0; q < kRadixOwn; ++q) {
+  for (int q = 0; q < kOwn; ++q) {
     total[q] = 0;
 #pragma unroll
-    for (int w = 0; w < kRadixWaves; ++w) total[q] += s.wcnt[w][threadIdx.x * kRadixOwn + q];
+    for (int w = 0; w < WAVES; ++w) total[q] += s.wcnt[w][threadIdx.x * kOwn + q];
     sum += total[q];
   }
-  uint32_t start = block_exclusive_sum<kRadixWaves>(sum, s.wave_sum);
+  uint32_t start = block_exclusive_sum<WAVES>(sum, s.wave_sum);
 #pragma unroll
-  for (int q = 0; q < kRadixOwn; ++q) {
-    const int d = threadIdx.x * kRadixOwn + q;
+  for (int q = 0; q < kOwn; ++q) {
+    const int d = threadIdx.x * kOwn + q;
     s.to[d] = next[q] - start;
     next[q] += total[q];
 #pragma unroll
-    for (int w = 0; w < kRadixWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
       const uint32_t c = s.wcnt[w][d];
       s.wcnt[w][d] = (uint16_t)start;
       start += c;
@@ -511,7 +527,7 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
   uint32_t dst[kRadixItems];
 #pragma unroll
   for (int r = 0; r < kRadixItems; ++r) {
-    const int i = r * kRadixThreads + threadIdx.x;
+    const int i = r * kThreads + threadIdx.x;
     const uint32_t k = s.move[i];
     dst[r] = s.to[(k >> shift) & mask] + (uint32_t)i;
     if (FULL || i < count) {
@@ -525,38 +541,40 @@ __device__ __forceinline__ void radix_tile(const uint32_t* keys_in, const int32_
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kRadixItems; ++r) {
-    const int i = r * kRadixThreads + threadIdx.x;
+    const int i = r * kThreads + threadIdx.x;
     if (FULL || i < count) put(out_out + dst[r], (int32_t)s.move[i]);
   }
 }
 
 // Stable move of the requests [beg, end).
+template <int WAVES>
 __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_t* in_in, const int32_t* out_in, uint32_t* keys_out,
                                            int32_t* in_out, int32_t* out_out, int64_t beg, int64_t end, int shift, int bits,
-                                           const uint32_t* hist, RadixTeam m, RadixLds& s) {
+                                           const uint32_t* hist, RadixTeam m, RadixLds<WAVES>& s) {
+  constexpr int kTile = RadixLds<WAVES>::kTile, kOwn = RadixLds<WAVES>::kOwn;
   const int nbins = 1 << bits;
-  uint32_t next[kRadixOwn];                             // output position of the next request of each owned digit
+  uint32_t next[kOwn];                             // output position of the next request of each owned digit
   {
-    uint32_t total[kRadixOwn], sum = 0;
+    uint32_t total[kOwn], sum = 0;
 #pragma unroll
-    for (int q = 0; q < kRadixOwn; ++q) {
-      const int d = threadIdx.x * kRadixOwn + q;
+    for (int q = 0; q < kOwn; ++q) {
+      const int d = threadIdx.x * kOwn + q;
       const uint32_t* row = hist + (size_t)d * m.blocks;
       total[q] = d < nbins ? row[m.blocks - 1] : 0u;
       next[q] = d < nbins && m.block > 0 ? row[m.block - 1] : 0u;
       sum += total[q];
     }
-    uint32_t base = block_exclusive_sum<kRadixWaves>(sum, s.wave_sum);
+    uint32_t base = block_exclusive_sum<WAVES>(sum, s.wave_sum);
 #pragma unroll
-    for (int q = 0; q < kRadixOwn; ++q) {
+    for (int q = 0; q < kOwn; ++q) {
       next[q] += base;
       base += total[q];
     }
   }
   int64_t at = beg;
-  for (; at + kRadixTile <= end; at += kRadixTile)
-    radix_tile<true>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, kRadixTile, shift, bits, next, s);
-  if (at < end) radix_tile<false>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, (int)(end - at), shift, bits, next, s);
+  for (; at + kTile <= end; at += kTile)
+    radix_tile<WAVES, true>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, kTile, shift, bits, next, s);
+  if (at < end) radix_tile<WAVES, false>(keys_in + at, in_in + at, out_in + at, keys_out, in_out, out_out, (int)(end - at), shift, bits, next, s);
 }
 
 // ---- a trace in window order ----------------------------------------------------------------
@@ -593,7 +611,6 @@ struct RunLds {
   uint32_t piece_add[DYN_WS_MAX_BREAKS + 1];
   uint32_t out[2];
 };
-constexpr int kRunEdges = 2048;
 
 // Element i of a run of 4-byte values, i * 4 < 2^32: one 32-bit offset instead of a 64-bit address.
 template <typename T>
@@ -876,47 +893,50 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
 
 // The windows of a trace of a few runs (RUNS), or the `n` windows that window_sort_kernel left: a list, each of them one
 // piece.  The blocks share them.
-template <bool RUNS>
-__device__ __forceinline__ void shared_windows(const IngestArgs& a, double r_window, int n, WinLds<kRadixWaves, kRadixItems>& s, RunLds& p, int32_t* s_edge) {
-  const ClassEdges edges = stage_edges(a, s_edge, kRunEdges);
+template <int WAVES, bool RUNS>
+__device__ __forceinline__ void shared_windows(const IngestArgs& a, double r_window, int n, WinLds<WAVES, kRadixItems>& s, RunLds& p, int32_t* s_edge, int edge_room) {
+  const ClassEdges edges = stage_edges(a, s_edge, edge_room);
   if (RUNS && blockIdx.x == 0 && threadIdx.x == 0) a.cell_off[(int64_t)a.n_window * a.n_model * a.n_in_bin * a.n_out_bin] = a.n_req;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     if (RUNS) {
-      find_pieces<kRadixThreads>(a, r_window, i, p);
-      window_move<kRadixWaves, kRadixItems, true>(a, i, p.out[0], (int)p.out[1], edges, s, &p);
+      find_pieces<WAVES * DYN_WAVE>(a, r_window, i, p);
+      window_move<WAVES, kRadixItems, true>(a, i, p.out[0], (int)p.out[1], edges, s, &p);
     } else {
       const int w = (int)a.key_a[i];
       const int64_t beg = a.win_off[w];
-      window_move<kRadixWaves, kRadixItems, false>(a, w, beg, (int)(a.win_off[w + 1] - beg), edges, s);
+      window_move<WAVES, kRadixItems, false>(a, w, beg, (int)(a.win_off[w + 1] - beg), edges, s);
     }
     __syncthreads();
   }
 }
 
 // A trace that is not in window order, and the long windows of one that is.
-__global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void unordered_kernel(RadixArgs g) {
+  constexpr int kThreads = RadixLds<WAVES>::kThreads, kTile = RadixLds<WAVES>::kTile;
+  constexpr int kRunEdges = WAVES >= 8 ? 2048 : 256;
   const IngestArgs& a = g.t;
   const Route route = route_of(a);               // the same for every block
   const int n_left = route == kByWindow ? (int)a.unsorted[DYN_WS_HEADER_LEFT_WORD - DYN_WS_HEADER_ORDER_WORD] : 0;
   if (route == kByWindow && (int)blockIdx.x >= n_left) return;
   __shared__ union {
-    RadixLds radix;
+    RadixLds<WAVES> radix;
     struct {
-      WinLds<kRadixWaves, kRadixItems> win;
+      WinLds<WAVES, kRadixItems> win;
       RunLds run;
       int32_t edge[kRunEdges];
     } runs;
   } lds;
   if (route == kByWindow) {
-    shared_windows<false>(a, g.r_window, n_left, lds.runs.win, lds.runs.run, lds.runs.edge);
+    shared_windows<WAVES, false>(a, g.r_window, n_left, lds.runs.win, lds.runs.run, lds.runs.edge, kRunEdges);
     return;
   }
   if (route == kByRuns) {
-    shared_windows<true>(a, g.r_window, a.n_window, lds.runs.win, lds.runs.run, lds.runs.edge);
+    shared_windows<WAVES, true>(a, g.r_window, a.n_window, lds.runs.win, lds.runs.run, lds.runs.edge, kRunEdges);
     return;
   }
   if ((int)blockIdx.x >= g.blocks) return;
-  RadixLds& s = lds.radix;
+  RadixLds<WAVES>& s = lds.radix;
   const RadixTeam m = join_team(g.join, g.members, g.passed, (uint32_t)g.blocks, (float)a.n_req * 0.012f * (float)g.passes, a.status, &s.wave_sum[0], &s.flag);
   if (m.blocks == 0) return;
   uint32_t passed = 0;                           // barriers behind this block
@@ -926,10 +946,10 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
     if (!ok && threadIdx.x == 0) atomicOr(a.status, DYN_WS_SORT_ABANDONED);
     return ok;
   };
-  const int n_tile = (int)((a.n_req + kRadixTile - 1) / kRadixTile);
+  const int n_tile = (int)((a.n_req + kTile - 1) / kTile);
   const int tiles = n_tile / m.blocks, more = n_tile % m.blocks;   // the first `more` blocks take one tile more
-  const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kRadixTile;
-  const int64_t end = std::min<int64_t>(a.n_req, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kRadixTile);
+  const int64_t beg = (int64_t)(m.block * tiles + min(m.block, more)) * kTile;
+  const int64_t end = std::min<int64_t>(a.n_req, beg + (int64_t)(tiles + (m.block < more ? 1 : 0)) * kTile);
   radix_keys(a, g.r_window, beg, end, s);
   const uint32_t* k_src = a.key_a;
   uint32_t* k_dst = a.key_b;
@@ -941,7 +961,7 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
     const int shift = p * g.bits;
     radix_count(k_src, beg, end, shift, g.bits, a.block_hist, m, s);
     if (!sync()) return;
-    radix_scan(a.block_hist, g.bits, m);
+    radix_scan<WAVES>(a.block_hist, g.bits, m);
     if (!sync()) return;
     radix_move(k_src, i_src, o_src, k_dst, i_dst, o_dst, beg, end, shift, g.bits, a.block_hist, m, s);
     if (!sync()) return;
@@ -952,19 +972,19 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
     k_dst = old_src;
   }
   if (a.n_req == 0)
-    for (int64_t c = threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = 0;
+    for (int64_t c = threadIdx.x; c <= g.cells; c += kThreads) a.cell_off[c] = 0;
   // The offsets (cell_off[c] = number of requests with key < c), a tile of sorted keys in LDS at a time: a request fills
   // the cells from the key before it on (by one thread the 35 000 empty cells before the log of a grid's last minutes took 1.1 ms).
   // What is left behind the last request is its block's.
   uint32_t left = 0;                             // one more than the key before the tile
-  for (int64_t at = beg; at < end; at += kRadixTile) {
-    const int count = (int)std::min<int64_t>(kRadixTile, end - at);
+  for (int64_t at = beg; at < end; at += kTile) {
+    const int count = (int)std::min<int64_t>(kTile, end - at);
     left = at > 0 ? __hip_atomic_load(k_src + at - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u : 0u;
 #pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) s.move[r * kRadixThreads + threadIdx.x] = k_src[std::min<int64_t>(at + r * kRadixThreads + threadIdx.x, end - 1)];
+    for (int r = 0; r < kRadixItems; ++r) s.move[r * kThreads + threadIdx.x] = k_src[std::min<int64_t>(at + r * kThreads + threadIdx.x, end - 1)];
     __syncthreads();
 #pragma unroll 1
-    for (int i = threadIdx.x; i - (int)threadIdx.x < count; i += kRadixThreads) {
+    for (int i = threadIdx.x; i - (int)threadIdx.x < count; i += kThreads) {
       const uint32_t from = i > 0 ? s.move[min(i, count) - 1] + 1u : left, to = s.move[min(i, count - 1)] + 1u;   // beyond the tile: equal
       fill_runs(a.cell_off, from, to, at + i);
     }
@@ -972,12 +992,30 @@ __global__ __launch_bounds__(kRadixThreads) void unordered_kernel(RadixArgs g) {
     __syncthreads();
   }
   if (end == a.n_req && beg < end)
-    for (int64_t c = (int64_t)left + threadIdx.x; c <= g.cells; c += kRadixThreads) a.cell_off[c] = a.n_req;
+    for (int64_t c = (int64_t)left + threadIdx.x; c <= g.cells; c += kThreads) a.cell_off[c] = a.n_req;
 }
 
 }  // namespace
 
-int64_t dyn_ingest_blocks(int64_t n_req) { return n_req > 0 ? (n_req + kRadixTile - 1) / kRadixTile : 1; }
+// Which logs are sorted, and have their runs and long windows moved, by small blocks: four waves, 128 registers and 22 KB of LDS.
+// A kernel's blocks have to fit beside what runs on other streams, also where they return at once: beside an evaluation,
+// which fills every compute unit, blocks of more than 28 KB, or of more registers than four waves of 128, wait until it is
+// through (empty kernels, us: 4 waves of 128 registers and 20 KB 9, 28 KB 35, 40 KB 830; 8 waves of 64 registers and
+// 16 KB 9, of 128 840; 16 waves 830).  Ingests beside an evaluation, large blocks and small (us): 20 000 requests 780, 45;
+// 1 M 840, 81; 1 M in six runs 907, 142; 300 000 unordered 947, 168.  Alone: 20 000 16, 16; 1 M in six runs 74, 48;
+// unordered 20 000 86, 75, 300 000 78, 81, 600 000 93, 122, 1 M 102, 128.  Larger logs take large blocks all the same,
+// whose tiles write longer runs (six million unordered 280), and so do logs of long windows: theirs move as quickly
+// only there (500 000 in nine runs and 60 windows 38, 63).  Two small blocks to a unit: four are quicker alone (1 M in six
+// runs 48, 38) and wait longer for their places (700 000 in time order beside a kernel that fills the device 79, 96).
+constexpr int64_t kSmallLog = 1 << 20;
+bool small_blocks(int64_t n_req, int32_t n_window) { return n_req <= kSmallLog && 1.75 * (double)n_req / n_window <= 4096.0; }
+constexpr int64_t kSmallTile = RadixLds<kSmallWaves>::kTile, kLargeTile = RadixLds<kLargeWaves>::kTile;
+
+// Blocks that the digit counts have room for at ten bits a digit (grows with n_req).
+int64_t dyn_ingest_blocks(int64_t n_req) {
+  const int64_t n = std::max<int64_t>(n_req, 1);
+  return std::max((n + kLargeTile - 1) / kLargeTile, (std::min(n, kSmallLog) + kSmallTile - 1) / kSmallTile);
+}
 
 hipError_t dyn_launch_edges(const int32_t* in_edge, size_t n_in, const int32_t* out_edge, size_t n_out, int32_t* d_in,
                             int32_t* d_out, WsHeader* header, uint32_t order_word, uint32_t* counters, hipStream_t s) {
@@ -1011,12 +1049,15 @@ bool dyn_ingest_always_sorts(int64_t n_req, int32_t n_window, int64_t n_class, i
 }
 
 // Samples of one window (order_kernel) after which the log is sorted: those of the longest window that one block moves while
-// the device sorts everything.  The block 8 us and 1.5 us a thousand requests, the sort 50 us and 16 us a pass and million.
+// the device sorts everything.  The block 8 us and 1.5 us a thousand requests, the sort 50 us and 16 us a pass and million; in a
+// small log 8 and 4, and 70 and 45.
 // Measured (us; the window routes and the sort): ordered, 10 M requests in 3 of 2016 windows 6750, 378; 6 M in 10 of
 // 1440 1266, 276; 500 000 in 5 of 2016 (by 64 threads) 1575, 102; six runs, 10 M in 3 of 2016 5100, 373.
-uint32_t dyn_ingest_many(int64_t n_req, int32_t key_bits) {
-  const double longest = (42.0 + 16e-6 * sort_passes(key_bits) * (double)n_req) / 1.5e-3;
-  return (double)n_req > longest ? (uint32_t)(longest / kSampleStep) + 1u : 0u;
+uint32_t dyn_ingest_many(int64_t n_req, int32_t n_window, int32_t key_bits) {
+  const bool small = small_blocks(n_req, n_window);
+  const double passes = sort_passes(key_bits) * (double)n_req;
+  const double longest = small ? (62.0 + 45e-6 * passes) / 4e-3 : (42.0 + 16e-6 * passes) / 1.5e-3;
+  return (double)n_req > longest ? (uint32_t)(longest / (small ? kSampleStep : 4 * kSampleStep)) + 1u : 0u;
 }
 
 hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
@@ -1028,7 +1069,7 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   if (!a.force_sort) {        // in window order: one block per window moves its requests to their cells
     // the order kernel ORs into the flag word, which the header kernel before it set to 0
     const int64_t per_block = 256 * kOrderRows;
-    hipLaunchKernelGGL(order_kernel, dim3((unsigned)std::max<int64_t>(1, (n + per_block - 1) / per_block)), dim3(256), 0, s, a, r_window);
+    hipLaunchKernelGGL(order_kernel, dim3((unsigned)std::max<int64_t>(1, (n + per_block - 1) / per_block)), dim3(256), 0, s, a, r_window, small_blocks(n, a.n_window) ? 0u : 3u);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const size_t n_edge = (size_t)a.n_model * ((a.n_in_bin - 1) + (a.n_out_bin - 1));
     const size_t room = n_edge <= kWinEdges ? n_edge : 0;
@@ -1069,10 +1110,12 @@ hipError_t dyn_launch_ingest(const IngestArgs& a, hipStream_t s) {
   r.passed = a.unsorted + (DYN_WS_HEADER_BREAK_WORD + DYN_WS_MAX_BREAKS - 1 - DYN_WS_HEADER_ORDER_WORD);   // the last break's word: a log that is sorted needs no breaks
   // a block for every tile, as far as they fit the device and the digit counts (a word per digit and block) the workspace
   const int64_t room = ((int64_t)DYN_INGEST_MAX_BINS * a.n_block) >> bits;
-  const int64_t n_tile = (n + kRadixTile - 1) / kRadixTile;
+  const bool small = small_blocks(n, a.n_window);
+  const int64_t n_tile = small ? (n + kSmallTile - 1) / kSmallTile : (n + kLargeTile - 1) / kLargeTile, at_once = (int64_t)n_cu * (small ? 2 : 1);
   const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>({(int64_t)n_cu, n_tile, room}));
   r.blocks = (int32_t)blocks;
-  const int64_t grid = a.force_sort ? blocks : std::max<int64_t>(blocks, std::min<int64_t>(n_cu, a.n_window));
-  hipLaunchKernelGGL(unordered_kernel, dim3((unsigned)grid), dim3(kRadixThreads), 0, s, r);
+  const int64_t grid = a.force_sort ? blocks : std::max<int64_t>(blocks, std::min<int64_t>(at_once, a.n_window));
+  if (small) hipLaunchKernelGGL(unordered_kernel<kSmallWaves>, dim3((unsigned)grid), dim3(kSmallWaves * DYN_WAVE), 0, s, r);
+  else hipLaunchKernelGGL(unordered_kernel<kLargeWaves>, dim3((unsigned)grid), dim3(kLargeWaves * DYN_WAVE), 0, s, r);
   return hipGetLastError();
 }

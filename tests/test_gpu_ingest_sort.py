@@ -185,7 +185,7 @@ def _counted(seed, counts, n_run=1, n_model=1):
 # 4 x 12 288 requests, and one more; several of them; all but one), one that alone takes longer than the sort has the log sorted
 @pytest.mark.parametrize("counts,n_run,left,sorts", [
     ([512, 513] + [100] * 20, 1, 1, False), ([500] * 20 + [2048, 2049], 1, 1, False), ([1500] * 20 + [4097, 4096], 1, 1, False),
-    ([6000] * 400 + [4 * WINDOW + 1, 4 * WINDOW], 1, 1, False), ([4000] * 20 + [4 * WINDOW], 1, None, True), ([0] * 600 + [520] * 300, 1, 300, False), ([0] * 99 + [25_000], 1, 1, False),
+    ([6000] * 400 + [4 * WINDOW + 1, 4 * WINDOW], 1, 1, False), ([4000] * 20 + [4 * WINDOW], 1, None, True), ([0] * 600 + [520] * 300, 1, 300, False), ([0] * 99 + [12_000], 1, 1, False), ([0] * 99 + [25_000], 1, None, True),
     ([200] * 2000 + [20_000, 100], 1, 1, False), ([200] * 2000 + [60_000, 100], 1, None, True), ([0] * 2000 + [90_000] * 2, 1, None, True),
     ([200] * 2000 + [60_000, 100], 2, None, True), ([0] * 2000 + [90_000] * 2, 6, None, True), ([200] * 200 + [15_000, 100], 6, 0, False)])
 @pytest.mark.parametrize("n_model", [1, 4])
@@ -228,3 +228,35 @@ def test_sort_beside_another_kernel_is_not_left_to_a_few_blocks(dyn):
     assert dyn.dyn_workspace_status(got[3]) == 0
     _check(got, tr, edges, 1440, 10.0)
     assert int(got[3][:256].view(torch.int32)[11]) >= 64         # blocks that sorted
+
+
+# in time order, of six runs, of long windows that are left, unordered
+@pytest.mark.parametrize("counts,n_run,shuffled", [([300] * 60, 1, False), ([700] * 1000, 1, False), ([60] * 100, 6, False), ([0] * 99 + [9000], 1, False), ([200] * 1000, 1, True)])
+def test_small_log_does_not_wait_for_another_stream(dyn, counts, n_run, shuffled):
+    """A kernel on another stream fills the device: the ingest's blocks fit beside it, and it is through long before that kernel."""
+    edges = _edges(5, 5)
+    tr = _counted(9, counts, n_run)
+    if shuffled:
+        p = np.random.default_rng(9).permutation(len(tr["t_s"]))
+        tr = {k: v[p] for k, v in tr.items()}
+    d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
+    call = lambda: dyn.dyn_trace_ingest(*d, None, edges, len(counts), 10.0)
+    full = torch.rand(1 << 29, device="cuda")
+    out = torch.empty_like(full)
+    call()
+    torch.erfinv(full, out=out)
+    torch.cuda.synchronize()
+    early = 0
+    for _ in range(8):                                           # streams share a few hardware queues: one that shares none with this
+        other, done, end = torch.cuda.Stream(), torch.cuda.Event(), torch.cuda.Event()
+        with torch.cuda.stream(other):
+            torch.erfinv(full, out=out)
+            end.record()
+        torch.cuda._sleep(30_000)                                # until that kernel has filled the device
+        got = call()
+        done.record()
+        done.synchronize()
+        early += not end.query()
+        torch.cuda.synchronize()
+    _check(got, tr, edges, len(counts), 10.0)
+    assert early >= 2, early
