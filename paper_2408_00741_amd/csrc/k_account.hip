@@ -74,31 +74,38 @@ __global__ __launch_bounds__(5 * DYN_WAVE) void account_totals_kernel(AccountArg
   if (lane == 0) a.totals[wave] = t;
 }
 
-// Everything in one block, header included, where the cells are few: the launches would cost more than the work.  487 windows of
-// 15 classes: 13 us in one launch, 50 in three.
-constexpr int kOneBlock = 1024;                  // threads, and windows at a time
+// Everything in one block, header included, where the cells are few: the launches would cost more than the work.  Four waves and
+// 13 KB, so that the block fits beside what other streams run (16 waves and 49 KB waited until an evaluation was through: 60
+// windows of 9 classes 792 us beside one, 23 so).  What bounds it: the latency of the selections, eight in flight per thread,
+// and the chain of additions, five of them in five lanes.  Beyond 1024 windows the chain alone is as long as the
+// kernels below take.  Measured (us; one launch, three without their gaps): 60 windows of 9 classes 3.2, 7.6; 487 of 15 12.9, 14.0;
+// 1 of 16 384 17, 2757; 1440 of 9 28.6, 23.4; 1820 of 9 36.1, 27.7.
+constexpr int kOneBlock = 256;                   // threads, and windows at a time
 constexpr int64_t kOneBlockCells = 16384;
+constexpr int32_t kOneBlockWindows = 1024;
 __global__ __launch_bounds__(kOneBlock) void account_one_kernel(AccountArgs a, WsHeader* header) {
+  constexpr int kAhead = 8, kRow = kOneBlock + 1;   // a row's first value lies in another bank than the next one's
   __shared__ unsigned long long s_used[kOneBlock];
-  __shared__ double s_v[5][kOneBlock];
+  __shared__ double s_v[5 * kRow];
   __shared__ uint32_t s_bad;
-  const int tid = threadIdx.x, lane = tid & (DYN_WAVE - 1), wave = tid / DYN_WAVE;
+  const int tid = threadIdx.x;
   if (tid == 0) s_bad = 0u;
   double t = 0.0;
   for (int w0 = 0; w0 < a.n_window; w0 += kOneBlock) {
     const int n = min(kOneBlock, a.n_window - w0), cells = n * a.G;
-    __syncthreads();
     s_used[tid] = 0ull;
+    const bool in = tid < n;
+    const double energy = in ? a.window_energy[w0 + tid] : 0.0, carbon = in ? a.carbon[w0 + tid] : 0.0;
     __syncthreads();
     const int32_t* sel = a.sel + (size_t)w0 * a.G;
-    for (int c0 = tid; c0 < cells; c0 += 8 * kOneBlock) {
-      int32_t k[8], gpus[8];
+    for (int c0 = tid; c0 < cells; c0 += kAhead * kOneBlock) {
+      int32_t k[kAhead], gpus[kAhead];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) k[q] = sel[min(c0 + q * kOneBlock, cells - 1)];
+      for (int q = 0; q < kAhead; ++q) k[q] = sel[min(c0 + q * kOneBlock, cells - 1)];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) gpus[q] = a.cfg[k[q] >= 0 && k[q] < a.K ? k[q] : 0].gpus;
+      for (int q = 0; q < kAhead; ++q) gpus[q] = a.cfg[k[q] >= 0 && k[q] < a.K ? k[q] : 0].gpus;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < kAhead; ++q) {
         const int c = c0 + q * kOneBlock;
         if (c >= cells) continue;
         if (k[q] >= a.K) s_bad = 1u;               // not a candidate of the list: counted as no selection
@@ -106,22 +113,22 @@ __global__ __launch_bounds__(kOneBlock) void account_one_kernel(AccountArgs a, W
       }
     }
     __syncthreads();
-    if (tid < n) {
+    if (in) {
       const int w = w0 + tid;
       const int64_t used = (int64_t)s_used[tid];
       const double hours = ((double)used * a.window_s) / 3600.0;
-      const double kwh = a.window_energy[w] / 3.6e6;
+      const double kwh = energy / 3.6e6;
       a.gpus[w] = used;
-      a.gpu_cost[w] = s_v[1][tid] = hours * a.gpu_hour_price;
-      a.energy_cost[w] = s_v[2][tid] = kwh * a.kwh_price;
-      a.carbon_g[w] = s_v[3][tid] = kwh * a.carbon[w];
-      s_v[0][tid] = hours;
-      s_v[4][tid] = (double)((used + a.gpus_per_server - 1) / a.gpus_per_server);
+      a.gpu_cost[w] = s_v[1 * kRow + tid] = hours * a.gpu_hour_price;
+      a.energy_cost[w] = s_v[2 * kRow + tid] = kwh * a.kwh_price;
+      a.carbon_g[w] = s_v[3 * kRow + tid] = kwh * carbon;
+      s_v[tid] = hours;
+      s_v[4 * kRow + tid] = (double)((used + a.gpus_per_server - 1) / a.gpus_per_server);
     }
     __syncthreads();
-    if (wave < 5) t = add_in_order(t, s_v[wave], n);
+    if (tid < 5) t = add_in_order(t, s_v + tid * kRow, n);
   }
-  if (wave < 5 && lane == 0) a.totals[wave] = t;
+  if (tid < 5) a.totals[tid] = t;
   if (tid == 0) {
     header->status = s_bad ? DYN_WS_BAD_REQUEST : 0u;
     header->kind = DYN_WS_KIND_WORD;
@@ -139,7 +146,7 @@ __global__ void account_header_kernel(WsHeader* header) {
 
 hipError_t dyn_launch_account(const AccountArgs& a, WsHeader* header, hipStream_t s) {
   DynTimed timed(DYN_K_TOTALS, s);
-  if ((int64_t)a.n_window * a.G <= kOneBlockCells) {
+  if (a.n_window <= kOneBlockWindows && (int64_t)a.n_window * a.G <= kOneBlockCells) {
     hipLaunchKernelGGL(account_one_kernel, dim3(1), dim3(kOneBlock), 0, s, a, header);
     return hipGetLastError();
   }

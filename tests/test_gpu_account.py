@@ -56,10 +56,10 @@ def test_account_matches_oracle(dyn, idx, n_req, n_win):
     prof.free()
 
 
-@pytest.mark.parametrize("n_win", [1, 2, 63, 64, 65, 546, 547, 1024, 1025, 2049])
+@pytest.mark.parametrize("n_win", [1, 2, 63, 64, 65, 255, 256, 257, 546, 547, 1024, 1025, 2049])
 @pytest.mark.parametrize("G", [1, 9, 30])
 def test_totals_in_window_order(dyn, n_win, G):
-    """One block (up to 16 384 cells, 1024 windows at a time) and several, with windows that end inside a group of 64."""
+    """One block (up to 16 384 cells and 1024 windows, 256 at a time) and several, with windows that end inside a group of 64."""
     w = make(SPECS[2].scaled(1000, 2))
     prof = dyn.dyn_profile_load({k: (np.repeat(v[:1], G, axis=0) if v.ndim >= 3 else v) for k, v in w["profile"].items()})
     plan = dyn.Plan(w["configs"], {k: np.repeat(v[:1], G) for k, v in w["slos"].items()}, w["pct"], None, 0.0)

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 
 import oracle
+from tests.beside import calls_through_early
 
 pytestmark = pytest.mark.gpu
 
@@ -241,22 +242,6 @@ def test_small_log_does_not_wait_for_another_stream(dyn, counts, n_run, shuffled
         tr = {k: v[p] for k, v in tr.items()}
     d = [torch.from_numpy(np.ascontiguousarray(tr[k])).cuda() for k in ("t_s", "in_tok", "out_tok")]
     call = lambda: dyn.dyn_trace_ingest(*d, None, edges, len(counts), 10.0)
-    full = torch.rand(1 << 29, device="cuda")
-    out = torch.empty_like(full)
-    call()
-    torch.erfinv(full, out=out)
-    torch.cuda.synchronize()
-    early = 0
-    for _ in range(8):                                           # streams share a few hardware queues: one that shares none with this
-        other, done, end = torch.cuda.Stream(), torch.cuda.Event(), torch.cuda.Event()
-        with torch.cuda.stream(other):
-            torch.erfinv(full, out=out)
-            end.record()
-        torch.cuda._sleep(30_000)                                # until that kernel has filled the device
-        got = call()
-        done.record()
-        done.synchronize()
-        early += not end.query()
-        torch.cuda.synchronize()
+    early, got = calls_through_early(call)
     _check(got, tr, edges, len(counts), 10.0)
     assert early >= 2, early

@@ -1,0 +1,36 @@
+"""Calls on small problems beside a kernel of another stream that fills the device: their blocks fit beside it."""
+import numpy as np
+import pytest
+
+from tests.beside import calls_through_early
+from workloads import SPECS, make
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def dyn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2408_00741_amd as d
+    return d
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("n_win", [60, 487])
+def test_account(dyn, n_win):
+    w = make(SPECS[1].scaled(1000, 2))
+    G = w["n_class"]
+    prof = dyn.dyn_profile_load(w["profile"])
+    plan = dyn.Plan(w["configs"], w["slos"], w["pct"], None, 0.0)
+    rng = np.random.default_rng(n_win)
+    sel = _dev(rng.integers(-1, w["configs"]["n_inst"].size, n_win * G).astype(np.int32))
+    e, ci = _dev(rng.uniform(0.0, 1e9, n_win)), _dev(rng.uniform(80.0, 700.0, n_win))
+    early, _ = calls_through_early(lambda: dyn.dyn_account(prof, sel, e, plan, n_win, 300.0, 11.06, 0.0832, ci, 8))
+    prof.free()
+    assert early >= 2, early
