@@ -8,7 +8,9 @@
 
 namespace {
 
-constexpr int kWavesPerBlock = 16;
+// Four waves: blocks of 16 (10 us instead of 11 at 487 windows of 15 classes) waited until the kernels of other streams that
+// fill the device were through (the plan beside an evaluation 949 us, 204 so).
+constexpr int kWavesPerBlock = 4;
 constexpr int32_t kNone = 0x7FFFFFFF;
 
 // In the place of an energy: no feasible configuration (a NaN with bits of its own, so that an energy that is NaN still counts as one).
@@ -85,10 +87,11 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void select_window_kernel
   if (threadIdx.x == 0) window_total(s_e, a.G, &a.win_energy[w], &a.win_inf[w]);
 }
 
-// A block per class and run of windows, a wave per window.  The idle terms of the class's candidates are the same in every
+// A block per class and four windows, a wave per window.  The idle terms of the class's candidates are the same in every
 // window: the block forms them once, a chunk of candidates at a time, in LDS (formed by every lane of every cell they
-// were most of what the kernel loaded: 487 windows, 15 classes, 429 candidates 19 us, 11 us so).
-constexpr int kIdleChunk = 4096;
+// were most of what the kernel loaded: 487 windows, 15 classes, 429 candidates 19 us,
+// 11 us so).
+constexpr int kIdleChunk = 2048;
 template <bool IDLE>
 __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void select_kernel(SelectArgs a) {
   extern __shared__ double s_idle[];       // [min(K, kIdleChunk)]
@@ -273,11 +276,12 @@ hipError_t dyn_launch_finish(const FinishArgs& a, hipStream_t s) {
   return dyn_launch_window_totals(a.sel, a.sel_energy, a.n_window, a.G, a.win_energy, a.win_inf, s);
 }
 
-// Without an idle term a block per window sums up as it selects, which saves a launch; with one, or with too few windows to
-// fill the device, a block takes one class of several windows.
+// Without an idle term a block per window sums up as it selects, which saves a launch, where its waves have few classes each or
+// the windows fill the device all the same.  Measured (us of the whole plan, a block per window and two kernels): 2016 windows of 20
+// classes 364, 377; 300 of 25 298, 292; 256 of 100 281, 254.  With an idle term a block takes one class of several windows.
 hipError_t dyn_launch_select(const SelectArgs& a, hipStream_t s) {
   const bool idle = a.idle_w != 0.0;
-  if (!idle && a.G <= 4096 && (a.n_window >= 256 || a.G <= kWavesPerBlock)) {
+  if (!idle && a.G <= 4096 && (a.n_window >= 1024 || a.G <= 2 * kWavesPerBlock)) {
     DynTimed timed(DYN_K_SELECT, s);
     hipLaunchKernelGGL(select_window_kernel, dim3((unsigned)a.n_window), dim3(kWavesPerBlock * DYN_WAVE), (size_t)a.G * sizeof(double), s, a);
     return hipGetLastError();

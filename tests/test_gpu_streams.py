@@ -34,3 +34,18 @@ def test_account(dyn, n_win):
     early, _ = calls_through_early(lambda: dyn.dyn_account(prof, sel, e, plan, n_win, 300.0, 11.06, 0.0832, ci, 8))
     prof.free()
     assert early >= 2, early
+
+
+@pytest.mark.parametrize("n_win", [1, 60])
+@pytest.mark.parametrize("idle", [0.0, 0.1])
+def test_evaluate_and_select(dyn, n_win, idle):
+    w = make(SPECS[1].scaled(2500 * n_win, n_win))
+    tr = w["trace"]
+    ins, outs, off, _ = dyn.dyn_trace_ingest(_dev(tr["t_s"]), _dev(tr["in_tok"]), _dev(tr["out_tok"]), _dev(tr["model"]), w["edges"], n_win, w["window_s"])
+    prof = dyn.dyn_profile_load(w["profile"])
+    plan = dyn.Plan(w["configs"], w["slos"], w["pct"], None, idle)
+    early, (space, ws) = calls_through_early(lambda: dyn.dyn_eval_space(prof, ins, outs, off, n_win, w["window_s"], plan))
+    assert early >= 2, early
+    early, sel = calls_through_early(lambda: dyn.dyn_select_config(prof, space, n_win, w["window_s"], plan))
+    assert early >= 2, early
+    prof.free()
