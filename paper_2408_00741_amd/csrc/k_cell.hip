@@ -145,11 +145,11 @@ __device__ __forceinline__ void group_sync() {
 // global memory once for the sums and once per 10-bit digit of the selection (radix select through one LDS histogram).
 // Every thread returns the same result.  `hist` (kHistBins counters) and `xch` (kXchWords) are LDS scratch of the
 // group; the caller guarantees nobody else uses them.
-constexpr int kXchWords = 24;
+constexpr int kXchWords = 16;
 template <int U, int WAVES>   // U independent loads per array in flight
 __device__ __forceinline__ CellOut cell_by_group(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg,
                                  int64_t m, int64_t rank, uint32_t* hist, int64_t* xch) {
-  static_assert(WAVES * 3 <= kXchWords, "one wave or the block");
+  static_assert(WAVES * 3 <= 12, "words 12 and 13 pass the digit on");
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int tid = WAVES == 1 ? lane : (int)threadIdx.x, wave = tid / DYN_WAVE;
   constexpr int nthr = WAVES * DYN_WAVE;
@@ -576,18 +576,23 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     }
 }
 
-// ---- few cells: a block per cell --------------------------------------------------------------
+// ---- few cells: a block per long cell -----------------------------------------------------------
 // With no more cells than compute units hold blocks, a wave per cell leaves most of the device idle while the longest cell
-// decides the time.  Here eight waves share a cell: up to kBlockRows values in each thread's registers, the bit-wise search with
-// the waves' counts added up through LDS (a barrier a bit); longer cells are streamed.  What bounds it is latency: offsets,
-// requests, the bits of the search.  It pays where the longest cell is beyond a wave's plain registers (2048 requests), which
-// classes of uneven traffic reach at a mean of about 1000.  Measured (us, a wave per cell and a block): 9 cells of 10 000 requests
-// together 12.4, 9.4; 540 of 1 M 18.8, 13.1; 1000 of 10 M 105, 40; but 40 even ones of 100 000 7.3, 9.0; 1000 of 100 000 3.8, 13.6;
-// and beyond the cells that are resident at once 2500 of 1 M 7.3, 21.6; 36 000 of 20 M 34, 271.
-constexpr int kBlockWaves = 8;
-constexpr int kBlockRows = 16;                     // register path: m <= 512 * kBlockRows
+// decides the time.  Here cells of up to kWaveCell requests have a wave each and four waves share a longer one: up to kBlockRows
+// values in each thread's registers, the bit-wise search with the waves' counts added up through LDS (a barrier a bit); beyond
+// that the cell is streamed.  What bounds it is latency: offsets, requests, the bits of the search.  Four waves and not eight: a
+// block of eight does not find its place beside other streams' kernels until they are through (nine cells of a minute
+// 844 us beside an evaluation, 79 so, 46 with a wave per cell).
+// Measured (us; a wave per cell, a block of eight waves each, this): 9 cells of 10 000 requests together 12.4, 9.3, 10.5; 180 of 300 000
+// 18.0, 9.3, 10.5; 540 of 1 M 22.1, 13.2, 15.6; 1000 of 10 M 106, 41, 52; even cells: 40 of 2500 7.2, 8.9, 6.2; 1000 of 1024 5.4,
+// 12.0, 5.9; 1000 of 3072 11.0, 16.4, 9.5; 1000 of 6144 19.1, 24.0, 23.0; 256 of 8000 21.5, 9.3, 10.8.  Few requests a cell, or
+// more cells than are resident at once, are better with a wave per cell: 2500 of 1 M 7.3, 21.6 with a block each.
+constexpr int kBlockWaves = 4;
+constexpr int kBlockRows = 32;                     // register path: m <= 256 * kBlockRows
+constexpr int kWaveCell = 3072;                    // up to here a wave on its own: 24 packed registers
 constexpr int64_t kBlockCells = 1024;              // cells that the device holds at once this way
 constexpr int64_t kBlockMean = 1000;               // requests per cell
+static_assert(kWaveCell <= 128 * 24, "the packed form below");
 
 template <int R>
 __device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int m, int rank, int64_t* xch, uint32_t* s_n) {
@@ -651,18 +656,25 @@ __device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in,
   return r;
 }
 
-__global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_aggregate_block_kernel(
+__global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) void cell_aggregate_block_kernel(
     const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells,
     double window_s, double r_window, int32_t pct_num, int32_t pct_den, int64_t* __restrict__ tin, int64_t* __restrict__ tout,
     int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header) {
-  __shared__ uint32_t s_hist[kHistBins];
-  __shared__ int64_t s_xch[kXchWords];
+  __shared__ uint32_t s_hist[kBlockWaves][kHistBins];
+  __shared__ int64_t s_xch[kBlockWaves][kXchWords];
   __shared__ uint32_t s_n[2 * kBlockWaves];
-  const int64_t c = blockIdx.x;
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
+  // the first blocks take a cell per wave, one block for every cell follows
+  const int64_t shared = (cells + kBlockWaves - 1) / kBlockWaves;
+  const bool alone = (int64_t)blockIdx.x < shared;
+  const int64_t c = alone ? (int64_t)blockIdx.x * kBlockWaves + wave : (int64_t)blockIdx.x - shared;
+  if (c >= cells) return;
   int64_t beg = cell_off[c], end = cell_off[c + 1];
   uint32_t bad = (beg < 0 || end < beg || end > n_req) ? DYN_WS_BAD_OFFSETS : 0u;
   if (bad) beg = end = 0;                          // never read outside the trace
   const int64_t m = end - beg;
+  if (alone != (m <= kWaveCell)) return;           // uniform over the wave, and over a block that takes one cell
   CellOut r;
   r.tin = r.tout = 0;
   r.p99 = 0;
@@ -671,15 +683,16 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_aggregate_block_ke
     const int64_t rank = ((int64_t)pct_num * m + pct_den - 1) / pct_den;
     constexpr int kThreads = kBlockWaves * DYN_WAVE;
     const int32_t *ci = in + beg, *co = out + beg;
-    if (m <= kThreads) r = cell_by_block<1>(ci, co, (int)m, (int)rank, s_xch, s_n);
-    else if (m <= 2 * kThreads) r = cell_by_block<2>(ci, co, (int)m, (int)rank, s_xch, s_n);
-    else if (m <= 4 * kThreads) r = cell_by_block<4>(ci, co, (int)m, (int)rank, s_xch, s_n);
-    else if (m <= 8 * kThreads) r = cell_by_block<8>(ci, co, (int)m, (int)rank, s_xch, s_n);
-    else if (m <= kBlockRows * kThreads) r = cell_by_block<kBlockRows>(ci, co, (int)m, (int)rank, s_xch, s_n);
-    else r = cell_by_group<8, kBlockWaves>(in, out, beg, m, rank, s_hist, s_xch);
+    if (alone) {
+      if (m <= DYN_WAVE * kRegRowsMax) r = cell_by_wave(in, out, beg, (int)m, (int)rank, lane);
+      else if (!(m <= 128 * 24 && cell_in_registers_packed<24>(ci, co, (int)m, (int)rank, lane, &r)))   // the bound spares the search 3 of 11 us
+        r = cell_by_group<8, 1>(in, out, beg, m, rank, s_hist[wave], s_xch[wave]);
+    } else if (m <= kBlockRows / 2 * kThreads) r = cell_by_block<kBlockRows / 2>(ci, co, (int)m, (int)rank, s_xch[0], s_n);
+    else if (m <= kBlockRows * kThreads) r = cell_by_block<kBlockRows>(ci, co, (int)m, (int)rank, s_xch[0], s_n);
+    else r = cell_by_group<8, kBlockWaves>(in, out, beg, m, rank, s_hist[0], s_xch[0]);
     if (r.orv >> 31) bad |= DYN_WS_BAD_REQUEST;    // a negative token count
   }
-  if (threadIdx.x == 0) write_cell(c, r, m, bad, window_s, r_window, cells, tin, tout, in_p99, rec, cstat, header);
+  if (alone ? lane == 0 : threadIdx.x == 0) write_cell(c, r, m, bad, window_s, r_window, cells, tin, tout, in_p99, rec, cstat, header);
 }
 
 }  // namespace
@@ -691,7 +704,7 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                                      uint8_t* cstat, WsHeader* header, hipStream_t s) {
   DynTimed timed(DYN_K_CELL, s);
   if (cells <= kBlockCells && n_req > kBlockMean * cells) {
-    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)cells), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
+    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)(cells + (cells + kBlockWaves - 1) / kBlockWaves)), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
                        window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header);
     return hipGetLastError();
   }

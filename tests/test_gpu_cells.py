@@ -1,5 +1,5 @@
-"""Token sums and percentile length of single cells at the sizes where the reduction changes its form, in few cells (a block each)
-and in many (a wave each)."""
+"""Token sums and percentile length of single cells at the sizes where the reduction changes its form: few cells of many requests (a
+wave each, a block for a long one), more cells or fewer requests (a wave each), many small ones."""
 import numpy as np
 import pytest
 
@@ -18,17 +18,19 @@ def dyn():
     return d
 
 
-SIZES = [0, 1, 2, 63, 64, 65, 100, 101, 256, 511, 512, 513, 1024, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 20_001, 0, 3]
+SIZES = [0, 1, 2, 63, 64, 65, 100, 101, 256, 511, 512, 513, 1024, 1025, 2047, 2048, 2049, 3072, 3073, 4096, 4097, 8191, 8192, 8193, 20_001, 0, 3]
 
 
-@pytest.mark.parametrize("cells", [len(SIZES), 1024, 1025, 3000])
+# (cells, requests in those that SIZES does not name): the block form asks for at most 1024 cells and more than 1000 requests a cell
+@pytest.mark.parametrize("cells,each", [(len(SIZES), 0), (1024, 1010), (1024, 930), (1025, 1010), (1025, 5), (3000, 400)])
 @pytest.mark.parametrize("pct", [(99, 100), (1, 2), (1, 1000), (1, 1)])
 @pytest.mark.parametrize("kind", ["tokens", "equal", "wide", "negative"])
-def test_cell_statistics(dyn, cells, pct, kind):
+def test_cell_statistics(dyn, cells, each, pct, kind):
     rng = np.random.default_rng(cells + pct[0])
-    m = np.concatenate([SIZES, rng.integers(0, 5 if cells < 2000 else 400, cells - len(SIZES))]).astype(np.int64)
+    m = np.concatenate([SIZES, rng.integers(each - each // 20 if each > 900 else 0, each + 1 if each < 900 else each + each // 20, cells - len(SIZES))]).astype(np.int64)
     off = np.concatenate([[0], np.cumsum(m)])
     n = int(off[-1])
+    assert (cells <= 1024 and n > 1000 * cells) == ((cells, each) in ((len(SIZES), 0), (1024, 1010)))
     x, y = (rng.integers(0, {"tokens": 8193, "equal": 3, "wide": 1 << 31, "negative": 8193}[kind], n).astype(np.int32) for _ in range(2))
     if kind == "negative":
         x[off[20]] = -5                            # cell 20 holds one: its sums count it, its status says so

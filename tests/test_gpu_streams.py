@@ -46,6 +46,8 @@ def test_evaluate_and_select(dyn, n_win, idle):
     plan = dyn.Plan(w["configs"], w["slos"], w["pct"], None, idle)
     early, (space, ws) = calls_through_early(lambda: dyn.dyn_eval_space(prof, ins, outs, off, n_win, w["window_s"], plan))
     assert early >= 2, early
+    early, _ = calls_through_early(lambda: dyn.dyn_eval_select(prof, ins, outs, off, n_win, w["window_s"], plan))
+    assert early >= 2, early
     early, sel = calls_through_early(lambda: dyn.dyn_select_config(prof, space, n_win, w["window_s"], plan))
     assert early >= 2, early
     prof.free()
