@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     flags = tbt_route(cnt_l, j64, lane);
     const int rpt = ((int)wave_max_u32((uint32_t)cnt_l) + DYN_WAVE - 1) / DYN_WAVE;   // rows per tick
     const int rows = T * rpt;
-    // with few cells on the whole device a cell of many rows is quicker with a block's four waves: it goes on the list
+    // with few cells on the whole device a cell of many rows is quicker with a block's waves: it goes on the list
     if (rows <= 128 && !(a.few_cells && rows > 8)) {
       const float theta = a.theta[g];
       const int m = (int)m_cell, rk = (int)rank;
@@ -330,18 +330,18 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 }
 
 // The same for the listed cells whose ticks do not fit one wave's registers: a block per cell, wave w takes the ticks
-// w, w + 8, ...; x_j by the bit-wise search with the waves' counts added up through LDS (one barrier per bit).  A cell
+// w, w + WAVES, ...; x_j by the bit-wise search with the waves' counts added up through LDS (one barrier per bit).  A cell
 // it settles is taken off the list (its entry becomes DYN_LIST_DONE).
 #define DYN_LIST_DONE 0xFFFFFFFFu
-constexpr int kTightWaves = 8;
-constexpr int kTightBlocks = 512;              // what the device holds at once (registers: two to a compute unit)
+constexpr int kTightWaves = 4, kTightManyWaves = 8;   // of a block: dyn_launch_tick_cell says where the line lies
+constexpr int kTightUnits = 4096;              // waves that the device holds at once (registers)
 
 enum BlockCell { kNotTaken, kSettled, kBoundFails };   // kBoundFails: token sums and x_j are known, the ticks' lists are needed
-template <int P>   // P registers = 2P rows per wave
+template <int WAVES, int P>   // P registers = 2P rows per wave
 __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
                                                  int64_t beg_l, int32_t cnt_l, int T, int rpt, int m, int rank, float theta,
-                                                 int lane, int wave, uint32_t* s_x /* [2][kTightWaves] */,
-                                                 uint32_t* s_m /* [4 * kTightWaves] */, TightCell* res) {
+                                                 int lane, int wave, uint32_t* s_x /* [2][WAVES] */,
+                                                 uint32_t* s_m /* [4 * WAVES] */, TightCell* res) {
   uint32_t v[P];
   uint32_t orv = 0, vmax = 0, tok_acc = 0, tok_l = 0;
   constexpr int CH = 4;
@@ -366,7 +366,7 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
       const int64_t row_q = beg_q + (int64_t)(r * DYN_WAVE);   // one scalar offset for both arrays
       a[u] = ok ? (uint32_t)in[row_q + lane] : 0u;
       b[u] = ok ? (uint32_t)out[row_q + lane] : 0u;
-      if (++r == rpt) { r = 0; q += kTightWaves; }
+      if (++r == rpt) { r = 0; q += WAVES; }
     }
 #pragma unroll
     for (int u = 0; u < 2 * CH; ++u) {
@@ -389,26 +389,26 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
   // sums over the block: every wave writes its word, a barrier, every wave reads all of them (two buffers in turn)
   int turn = 0;
   auto block_or = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
+    if (lane == 0) s_x[turn * WAVES + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kTightWaves; ++w) all |= s_x[turn * kTightWaves + w];
+    for (int w = 0; w < WAVES; ++w) all |= s_x[turn * WAVES + w];
     turn ^= 1;
     return all;
   };
   auto block_max = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
+    if (lane == 0) s_x[turn * WAVES + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kTightWaves; ++w) all = max(all, s_x[turn * kTightWaves + w]);
+    for (int w = 0; w < WAVES; ++w) all = max(all, s_x[turn * WAVES + w]);
     turn ^= 1;
     return all;
   };
   auto block_sum = [&](uint32_t x) {
-    if (lane == 0) s_x[turn * kTightWaves + wave] = x;
+    if (lane == 0) s_x[turn * WAVES + wave] = x;
     __syncthreads();
     uint32_t all = 0;
-    for (int w = 0; w < kTightWaves; ++w) all += s_x[turn * kTightWaves + w];
+    for (int w = 0; w < WAVES; ++w) all += s_x[turn * WAVES + w];
     turn ^= 1;
     return all;
   };
@@ -449,11 +449,11 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
         if (lane == q) eq_l = (uint32_t)eq_acc;
         n_eq += eq_acc;
         eq_acc = 0;
-        r = 0; q += kTightWaves;
+        r = 0; q += WAVES;
       }
     }
   }
-  n_gt = (int)block_sum((uint32_t)n_gt) - (2 * P * DYN_WAVE * kTightWaves - m);
+  n_gt = (int)block_sum((uint32_t)n_gt) - (2 * P * DYN_WAVE * WAVES - m);
   n_eq = (int)block_sum((uint32_t)n_eq);
   const int need = j - n_gt;
   uint32_t place = (uint32_t)need;
@@ -466,7 +466,7 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
     if (lane < 4) s_m[wave * 4 + lane] = lane == 0 ? m4[0] : lane == 1 ? m4[1] : lane == 2 ? m4[2] : m4[3];
     __syncthreads();
     uint32_t best[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-    for (int i = 0; i < 4 * kTightWaves; ++i) {
+    for (int i = 0; i < 4 * WAVES; ++i) {
       uint32_t x = s_m[i];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {        // insertion into the ascending four
@@ -491,7 +491,7 @@ __device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict_
 // wave in LDS: the n_top-th largest by a bit-wise search, what is above it gathered in place, the rest of the places
 // filled with it, a bitonic sort of that many.
 constexpr int kListTick = 2048;
-__device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int cnt, int n_top, int32_t* dst, int32_t* buf, int lane) {
+__device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int cnt, int n_top, int32_t* dst, uint16_t* buf, int lane) {
   auto wave_sync = [] {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -504,7 +504,7 @@ __device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int c
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       mx = max(mx, x[u]);
-      if (i0 + u * DYN_WAVE + lane < cnt) buf[i0 + u * DYN_WAVE + lane] = x[u];
+      if (i0 + u * DYN_WAVE + lane < cnt) buf[i0 + u * DYN_WAVE + lane] = (uint16_t)x[u];
     }
   }
   wave_sync();
@@ -528,15 +528,15 @@ __device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int c
       const bool take = i0 + lane < cnt && x > thr;
       const uint64_t who = __ballot(take);
       wave_sync();                                 // the row is read before places in it are written
-      if (take) buf[got + __popcll(who & ((1ull << lane) - 1ull))] = x;
+      if (take) buf[got + __popcll(who & ((1ull << lane) - 1ull))] = (uint16_t)x;
       got += __popcll(who);
     }
     wave_sync();
-    for (int i = got + lane; i < n_top; i += DYN_WAVE) buf[i] = thr;
+    for (int i = got + lane; i < n_top; i += DYN_WAVE) buf[i] = (uint16_t)thr;
   }
   int n2 = 2;
   while (n2 < n_top) n2 <<= 1;                     // at most kListTick
-  for (int i = n_top + lane; i < n2; i += DYN_WAVE) buf[i] = -1;
+  for (int i = n_top + lane; i < n2; i += DYN_WAVE) buf[i] = 0;   // as short as any: behind the n_top
   wave_sync();
   for (int k = 2; k <= n2; k <<= 1)
     for (int d = k >> 1; d > 0; d >>= 1) {
@@ -544,7 +544,7 @@ __device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int c
         const int i = ((p & ~(d - 1)) << 1) | (p & (d - 1)), o = i | d;   // the pair's places
         const int32_t u = buf[i], v = buf[o];
         const bool down = (i & k) == 0;            // descending runs first: the whole ends descending
-        if (down ? u < v : u > v) { buf[i] = v; buf[o] = u; }
+        if (down ? u < v : u > v) { buf[i] = (uint16_t)v; buf[o] = (uint16_t)u; }
       }
       wave_sync();
     }
@@ -552,10 +552,11 @@ __device__ __forceinline__ void tick_list(const int32_t* __restrict__ src, int c
   wave_sync();                                     // buf is reused
 }
 
-__global__ __launch_bounds__(kTightWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_tight_block_kernel(TickCellArgs a) {
-  __shared__ uint32_t s_x[2 * kTightWaves];
-  __shared__ uint32_t s_m[4 * kTightWaves];
-  __shared__ int32_t s_list[kTightWaves][kListTick];
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_tight_block_kernel(TickCellArgs a) {
+  __shared__ uint32_t s_x[2 * WAVES];
+  __shared__ uint32_t s_m[4 * WAVES];
+  __shared__ uint16_t s_list[WAVES][kListTick];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int T = a.n_tick, G = a.G;
@@ -578,17 +579,17 @@ __global__ __launch_bounds__(kTightWaves* DYN_WAVE) __attribute__((amdgpu_waves_
     const int64_t rank = (a.pct_num * m_cell + a.pct_den - 1) / a.pct_den;
     const int64_t j64 = m_cell > 0 ? m_cell - rank + 1 : 0;
     const int rpt = ((int)wave_max_u32((uint32_t)cnt_l) + DYN_WAVE - 1) / DYN_WAVE;
-    const int rows = ((T + kTightWaves - 1) / kTightWaves) * rpt;   // rows of the wave with most ticks
+    const int rows = ((T + WAVES - 1) / WAVES) * rpt;   // rows of the wave with most ticks
     TightCell tc;
     tc.tok_l = 0; tc.eq_l = 0; tc.xj = 0; tc.place = 0; tc.need = 0; tc.walk = true;
     BlockCell done = kNotTaken;                  // block-uniform from here on
     if (m_cell > 0 && m_cell < (1 << 24) && rows <= 128) {
       const float theta = a.theta[g];
       const int m = (int)m_cell, rk = (int)rank;
-      if (rows <= 16) done = tight_cell_block<8>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
-      else if (rows <= 32) done = tight_cell_block<16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
-      else if (rows <= 64) done = tight_cell_block<32>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
-      else done = tight_cell_block<64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      if (rows <= 16) done = tight_cell_block<WAVES, 8>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      else if (rows <= 32) done = tight_cell_block<WAVES, 16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      else if (rows <= 64) done = tight_cell_block<WAVES, 32>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
+      else done = tight_cell_block<WAVES, 64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
     }
     __syncthreads();                             // s_x is reused by the next item
     if (done == kNotTaken) continue;
@@ -602,9 +603,10 @@ __global__ __launch_bounds__(kTightWaves* DYN_WAVE) __attribute__((amdgpu_waves_
     } else {
       // Its lists, a tick per wave at a time, where that is better than what follows: few cells on the whole device, or a
       // list beyond the 64 entries that one wave keeps sorted (a block per cell, tick after tick).  540 cells of up to
-      // 6800 requests and 12 ticks: 73 us in this kernel (84 with four waves a block); 26, then 227 in tick_cell_kernel and 462 in tick_deep_kernel without.
-      if (!(a.few_cells || j64 > DYN_TICK_WAVE) || j64 > DYN_TICK_DEPTH || wave_max_u32((uint32_t)cnt_l) > kListTick) continue;
-      for (int q = wave; q < T; q += kTightWaves) {
+      // 6800 requests and 12 ticks: 83 us in this kernel (74 with eight waves a block); 26, then 227 in tick_cell_kernel and 462 in
+      // tick_deep_kernel without.  A single tick is one wave's work here, and all four of the deep kernel's there.
+      if (T < 2 || !(a.few_cells || j64 > DYN_TICK_WAVE) || j64 > DYN_TICK_DEPTH || wave_max_u32((uint32_t)cnt_l) > kListTick) continue;
+      for (int q = wave; q < T; q += WAVES) {
         const int64_t beg_q = readlane_i64(beg_l, q);
         const int cnt_q = __builtin_amdgcn_readlane(cnt_l, q);
         if (cnt_q > 0) tick_list(a.in + beg_q, cnt_q, j64 < cnt_q ? (int)j64 : cnt_q, a.top + beg_q, s_list[wave], lane);
@@ -613,7 +615,7 @@ __global__ __launch_bounds__(kTightWaves* DYN_WAVE) __attribute__((amdgpu_waves_
       flags |= walks_with_lists(flags, j64) ? 0u : DYN_TP_GENERAL;
       tc.eq_l = (uint32_t)beg_l;                 // where the tick's list is (n_req < 2^31)
     }
-    if (lane < T && (lane % kTightWaves) == wave) {   // the wave that walked the tick
+    if (lane < T && (lane % WAVES) == wave) {   // the wave that walked the tick
       TickRec r;
       r.load = div_by((double)tc.tok_l, a.tick_s, a.r_tick);
       r.off = tc.eq_l;
@@ -1729,7 +1731,17 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   DynTimed timed(DYN_K_TICK_TOP, s);
   hipLaunchKernelGGL(tick_init_kernel, dim3(1), dim3(1), 0, s, a.counters);
   hipLaunchKernelGGL(tick_tight_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
-  hipLaunchKernelGGL(tick_tight_block_kernel, dim3(kTightBlocks), dim3(kTightWaves * DYN_WAVE), 0, s, a);
+  // Eight waves where that halves the rows a wave holds and the cells are long enough to share, or where cells are too long for
+  // four; such a block (33 KB of LDS) waits beside kernels of other streams that fill the device, one of four finds its place.
+  // Measured (us of the call; four waves, eight): 4 M requests, 12 500 cells of 30 ticks, prefill by load 988, 1113; 1500 cells of 1
+  // tick 630, 684, of 3 819, 852, of 5 flat 142, 114; 1000 of 10 360, 366; 540 cells of 1 M and 12 ticks 266, 256; long cells: 500 of
+  // 8000 and 30 ticks flat 2649, 162; 240 of 16 700 and 6 ticks 2758, 126; 100 of 20 000 and 10 ticks 102, 119.
+  const int T = a.n_tick;
+  const int64_t mean = a.n_req / cells;
+  const int64_t rows = (T + 3) / 4 * (mean * 5 / 4 / T / DYN_WAVE + 1);   // of a wave of four in a cell somewhat longer than the mean
+  const bool many = T > 4 && ((mean > 1000 && 2 * ((T + 7) / 8) <= (T + 3) / 4) || rows > 128);
+  if (many) hipLaunchKernelGGL(tick_tight_block_kernel<kTightManyWaves>, dim3(kTightUnits / kTightManyWaves), dim3(kTightManyWaves * DYN_WAVE), 0, s, a);
+  else hipLaunchKernelGGL(tick_tight_block_kernel<kTightWaves>, dim3(kTightUnits / kTightWaves), dim3(kTightWaves * DYN_WAVE), 0, s, a);
   hipLaunchKernelGGL(tick_cell_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
   hipLaunchKernelGGL(tick_deep_kernel, dim3(kDeepBlocks), dim3(256), 0, s, a);
   return hipGetLastError();

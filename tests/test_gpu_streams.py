@@ -51,3 +51,15 @@ def test_evaluate_and_select(dyn, n_win, idle):
     early, sel = calls_through_early(lambda: dyn.dyn_select_config(prof, space, n_win, w["window_s"], plan))
     assert early >= 2, early
     prof.free()
+
+
+def test_ticks(dyn):
+    """An hour of 540 cells whose lists the block kernel builds."""
+    w = make(SPECS[1].scaled(60_000, 60))
+    tr, T = w["trace"], 12
+    ins, outs, off, _ = dyn.dyn_trace_ingest(_dev(tr["t_s"]), _dev(tr["in_tok"]), _dev(tr["out_tok"]), _dev(tr["model"]), w["edges"], 60 * T, w["window_s"] / T)
+    prof = dyn.dyn_profile_load(w["profile"])
+    plan = dyn.Plan({k: v[:8] for k, v in w["configs"].items()}, w["slos"], w["pct"], None, 0.0)
+    early, _ = calls_through_early(lambda: dyn.dyn_eval_select_ticks(prof, ins, outs, off, 60, T, w["window_s"] / T, plan))
+    prof.free()
+    assert early >= 2, early

@@ -203,7 +203,8 @@ def test_deep_percentiles_with_load_dependent_prefill(dyn, n_req, NW, T, crowd):
     assert j.max() > 16
 
 
-@pytest.mark.parametrize("n_req,NW,T,crowd", [(2048, 1, 1, None), (2049, 1, 1, None), (2047 * 3, 1, 3, None), (6600, 1, 3, 2300), (64 * 12, 1, 12, None), (13_000, 1, 12, None), (130, 2, 5, None)])
+@pytest.mark.parametrize("n_req,NW,T,crowd", [(2048, 1, 1, None), (2049, 1, 1, None), (2047 * 3, 1, 3, None), (6600, 1, 3, 2300), (64 * 12, 1, 12, None), (13_000, 1, 12, None), (130, 2, 5, None),
+                                             (9_000, 1, 6, None), (30_000, 1, 30, 1500), (2100, 1, 2, None)])
 @pytest.mark.parametrize("pct", [(99, 100), (1, 2), (1, 100), (1, 1)])
 def test_lists_of_a_few_cells(dyn, n_req, NW, T, crowd, pct):
     """Cells whose lists a block builds, a tick per wave: ticks of up to 2048 requests and one more, lists of whole ticks, of
