@@ -938,9 +938,12 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
   ta.G = p->G; ta.n_tp = p->n_tp; ta.n_f = p->n_f; ta.n_rho = p->n_rho;
   ta.slo_ttft = p->d_slo_ttft; ta.slo_tbt = p->d_slo_tbt;
   ta.rec = (const CellRec*)(base + w.cell.rec); ta.n_window = t->n_window; ta.window_s = t->window_s;
-  // About 8192 blocks: the blocks of a type with few instances end early, and of longer blocks the last ones run alone, of
-  // shorter ones the set-up counts (36 000 cells, three types; 4096, 6000, 8192, 12 288, 20 000 blocks: 231, 208, 204, 213, 216 us).
-  ta.win_per_block = (int32_t)std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, (cells * p->n_tp + 8191) / 8192));
+  // About 8192 blocks where a cell has many entries: the blocks of a type with few instances end early, and of longer blocks
+  // the last ones run alone (36 000 cells of 224 entries; 4096, 6000, 8192, 12 288, 20 000 blocks: 231, 208, 204, 213, 216 us).  With
+  // few entries, or few windows a block, the set-up counts (10 000 cells of 24 entries 13, 20 us; 3600 of 96 27, 41): 4096 then.
+  const int64_t by4 = (cells * p->n_tp + 4095) / 4096, by8 = (cells * p->n_tp + 8191) / 8192;
+  const int64_t wanted = mp.types.off[p->n_tp] >= 192 ? std::max(by8, std::min<int64_t>(8, by4)) : by4;
+  ta.win_per_block = (int32_t)std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, wanted));
   ta.n_share = m->n_share; ta.r_share = 1.0 / (double)m->n_share;
   ta.types = mp.types;
   ta.type_energy = (double*)(base + w.type_energy); ta.type_f = (int8_t*)(base + w.type_f);
