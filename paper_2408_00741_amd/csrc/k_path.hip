@@ -345,40 +345,35 @@ __global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
   for (int i = 0; i < 4; ++i) put[i] = r == i ? &s_v[(i & 1) ^ 1][d] : &s_dump[threadIdx.x];
   if (r == 0) s_v[0][d] = inf;                               // before the first window: as after a window without a feasible candidate
   __syncthreads();
-  auto run = [&](int u, int w0) {                            // the windows w0 + 4 u ...
-    const int w = w0 + 4 * u + r;                          // this row's window
-    c[(u + kRuns - 1) % kRuns] = cost(w + 4 * (kRuns - 1));
-    const bool has = on && w < NW;
-    const double cw = has ? c[u] : inf;
-    double keep = inf;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const double v = s_v[i & 1][src];
-      const bool alive = __ballot((int)(__double_as_longlong(v) >> 32) < 0x7FF00000) != 0;   // any total below +inf (the wave holds all of them)
-      double m[SPL];
-      add_sources<0, SPL>(v, t, m);
-#pragma unroll
-      for (int k = 1; k < SPL; k *= 2)
-#pragma unroll
-        for (int q = 0; q + k < SPL; q += 2 * k) m[q] = __builtin_fmin(m[q], m[q + k]);   // sums are never NaN here
-      const double arrive = rows_min_f64(m[0]);
-      // least total of the sequences that end in this window in this destination (row i: its window)
-      const double now = (!alive || !(cw < inf)) ? cw : arrive + cw;
-      *put[i] = now;                                       // the other rows' lanes write to a place of their own that nobody reads
-      keep = r == i ? now : keep;
-      lds_barrier();                                       // the window's only block barrier
-    }
-    if (has) col[(size_t)w * step] = keep;
-  };
-  int w0 = 0;
 #pragma unroll 1
-  for (; w0 + 4 * (kRuns - 1) < NW; w0 += 4 * kRuns) {
+  for (int w0 = 0; w0 < NW; w0 += 4 * kRuns) {
 #pragma unroll
-    for (int u = 0; u < kRuns; ++u) run(u, w0);
+    for (int u = 0; u < kRuns; ++u) {
+      const int w = w0 + 4 * u + r;                          // this row's window
+      c[(u + kRuns - 1) % kRuns] = cost(w + 4 * (kRuns - 1));
+      const bool has = on && w < NW;
+      const double cw = has ? c[u] : inf;
+      double keep = inf;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double v = s_v[i & 1][src];
+        const bool alive = __ballot((int)(__double_as_longlong(v) >> 32) < 0x7FF00000) != 0;   // any total below +inf (the wave holds all of them)
+        double m[SPL];
+        add_sources<0, SPL>(v, t, m);
+#pragma unroll
+        for (int k = 1; k < SPL; k *= 2)
+#pragma unroll
+          for (int q = 0; q + k < SPL; q += 2 * k) m[q] = __builtin_fmin(m[q], m[q + k]);   // sums are never NaN here
+        const double arrive = rows_min_f64(m[0]);
+        // least total of the sequences that end in this window in this destination (row i: its window)
+        const double now = (!alive || !(cw < inf)) ? cw : arrive + cw;
+        *put[i] = now;                                       // the other rows' lanes write to a place of their own that nobody reads
+        keep = r == i ? now : keep;
+        lds_barrier();                                       // the window's only block barrier
+      }
+      if (has) col[(size_t)w * step] = keep;
+    }
   }
-#pragma unroll
-  for (int u = 0; u + 1 < kRuns; ++u)                        // what is left: no more runs than there are windows
-    if (w0 + 4 * u < NW) run(u, w0);
 }
 
 // One wave per (window, class), lane = destination layout, the lane's column of the table in registers: where
