@@ -5,10 +5,10 @@
 // A trace that is already in window order (a request log is in time order) does not need the
 // general sort: the order kernel notices it (a word in the workspace header stays 0; it also
 // writes where every window starts), and one block per window then moves its requests, stably,
-// to their cells (window_sort_kernel).  So does a trace of a few such runs.  Any other trace takes
-// the radix sort.  The host does not read the word: all routes are enqueued and the kernels of a
-// route not taken return at their first instruction.  Runs and the general sort are one launch, so
-// what is not taken costs one empty launch.
+// to their cells (window_sort_kernel).  So does a trace of a few such runs, while no window of it is too long.  Any other
+// trace takes the radix sort.  The host does not read the word: all routes are enqueued and the kernels of a
+// route not taken return at their first instruction.  Runs, the long windows that window_sort_kernel leaves and the general sort
+// are one launch: a route that is not taken costs one empty launch (4 to 5 us), of unordered_kernel or of window_sort_kernel.
 #include <string.h>
 
 #include <algorithm>
@@ -229,7 +229,8 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* wa
 //   fence by all 8 waves of 256 blocks costs 17 us a barrier, by one wave 2.  Data for other blocks is stored
 //   through the L2 (put), so the write-back finds it clean; scattered runs cost the same either way.
 // - A tile is ordered by digit in LDS before it is written, so that a digit's requests leave as one run: 8 M single words
-//   scattered cost 93 us, runs of 16 words 13 us, of 32 words 9.5 us.  So the tile is 8192 requests: 32 to a digit.
+//   scattered cost 93 us, runs of 16 words 13 us, of 32 words 9.5 us.  So the tile of the large
+//   blocks is 8192 requests: 32 to a digit.
 // - All loads of a thread's eight requests are in flight together, also where only keys are counted or compared.
 // 523 us with separate scan phases, all waves fencing and single words scattered; 225 us so.
 //
@@ -586,6 +587,8 @@ __device__ __forceinline__ void radix_move(const uint32_t* keys_in, const int32_
 // a thread): a window of one tile needs no counting and no look-up of where a class goes.  Ten million requests in 1440
 // windows: 47 us; 62 with 16 requests a thread, 75 with 8; 72 with keys read twice and single words scattered (and
 // 53 us for the kernel that wrote the keys, where order_kernel takes 19).
+// Of the variants the compiler spills <8, 24, 4> 24 vector registers (72 bytes of scratch a thread) and <4, 8, 6> 40; the
+// others none.  With fewer requests a thread nothing is spilled and the day's log takes longer (above).
 constexpr size_t kWinEdges = 2048;               // class edges that a block stages in LDS
 
 template <int WAVES, int ITEMS>

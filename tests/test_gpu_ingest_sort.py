@@ -9,7 +9,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-TILE = 8192          # requests a block of the general sort moves at a time
+TILE = 8192          # requests a large block of the general sort moves at a time, a small one (logs of up to a million) SMALL
+SMALL = 2048
+MILLION = 1 << 20
 WINDOW = 12288       # requests a block of the window route moves at a time (512, 2048 or 4096 where windows are short)
 
 
@@ -44,9 +46,10 @@ def _check(got, tr, edges, n_window, window_s):
     np.testing.assert_array_equal(got[1].cpu().numpy(), want["out_tok"])
 
 
-# one, two and three passes; digits of 1 to 10 bits; less than a wave, a tile and one more, many tiles a block
-@pytest.mark.parametrize("n,n_window,n_in,n_out", [(1, 1, 1, 1), (2, 2, 1, 1), (63, 5, 2, 2), (TILE - 1, 9, 5, 5), (TILE, 40, 5, 5), (TILE + 1, 41, 5, 5),
-                                                   (2 * TILE + 65, 1000, 5, 5), (100_000, 3, 40, 30), (300_001, 2000, 16, 20), (2_500_000, 1440, 5, 5)])
+# one, two and three passes; digits of 5 to 10 bits; less than a wave (1200 classes: the sort is forced), a tile and one more, many
+# tiles a block; the longest log that small blocks sort and one more
+@pytest.mark.parametrize("n,n_window,n_in,n_out", [(1, 1, 40, 30), (2, 2, 40, 30), (63, 5, 40, 30), (SMALL - 1, 9, 5, 5), (SMALL, 40, 5, 5), (SMALL + 1, 300, 2, 1), (TILE - 1, 9, 5, 5), (TILE, 40, 5, 5), (TILE + 1, 41, 5, 5),
+                                                   (2 * TILE + 65, 1000, 5, 5), (100_000, 3, 40, 30), (300_001, 2000, 16, 20), (MILLION, 1440, 5, 5), (MILLION + 1, 1440, 5, 5), (2_500_000, 1440, 5, 5)])
 def test_general_sort_is_stable(dyn, n, n_window, n_in, n_out):
     edges = _edges(n_in, n_out)
     tr = _log(n, n, n_window * 10.0)
