@@ -89,3 +89,11 @@ def test_binding_refuses_host_tensors(dyn):
     import torch
     with pytest.raises(ValueError):
         dyn.binding._dp(torch.zeros(4, dtype=torch.int32), torch.int32, "x")
+
+
+def test_ingest_workspace_grows_with_the_log():
+    """A workspace for a longer log serves a shorter one, also across the length up to which small blocks sort."""
+    import paper_2408_00741_amd as dyn
+    n = [0, 1, 2047, 2048, 2049, 8191, 8192, 8193, 100_000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 8193, 4 << 20, (4 << 20) + 1, 20_000_000]
+    size = [dyn.dyn_trace_ingest_workspace(q, 1440, 25) for q in n]
+    assert size == sorted(size)
