@@ -114,8 +114,8 @@ size_t dyn_trace_ingest_workspace(int64_t n_req, int32_t n_window, int32_t n_cla
  *   in_sorted, out_sorted       : DEVICE [n_req] outputs; must not alias the inputs.
  *   cell_off                    : DEVICE [n_window*G + 1] output, cell_off[last] = n_req.
  *   workspace                   : DEVICE, 256-byte aligned, >= dyn_trace_ingest_workspace.
- * A trace already in window order, or of a few runs that each are, is moved window by window,
- * any other by a general stable sort; the route is picked on the device (the call does not wait for it), both give the same
+ * A trace already in window order, or of a few runs that each are, is moved window by window while
+ * no window of it is too long, any other by a general stable sort; the route is picked on the device (the call does not wait for it), both give the same
  * bytes.  The edge lists travel in kernel arguments, so the HOST arrays are free on return.
  * A request whose timestamp falls outside [0, n_window*window_s) or whose model index is
  * outside [0, n_model) raises DYN_WS_BAD_REQUEST in the workspace status and is filed
