@@ -242,7 +242,7 @@ IngestWs ingest_ws_layout(int64_t n_req, int32_t n_model, int32_t n_in_bin, int3
 // One array per GPU the library runs on, held until the process ends.  In host code the array's
 // name is only a handle for hipGetSymbolAddress: kernels and copies get the address that call
 // returns for the current device, never the name.
-static __device__ __align__(256) unsigned char scratch[DYN_STATIC_WORKSPACE_BYTES];
+static __device__ __align__(256) unsigned char scratch[DYN_STATIC_WORKSPACE_BYTES + DYN_CELL_MANY_MAX];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -318,6 +318,8 @@ EvalWs dyn_eval_ws_layout(int64_t cells, int32_t K) {
   w.cstat = off; off += align256(c);
   w.part = off; off += align256(c * (size_t)w.n_wslot * sizeof(SelPart));
   w.total = off;
+  w.many = off; off += align256(dyn_cell_many_bytes(cells));
+  w.all = off;
   return w;
 }
 
@@ -401,7 +403,8 @@ int eval_impl(dyn_profile* p, const dyn_trace_view* t, const dyn_config* cfg, in
   if (!hip_ok(dyn_launch_cell_aggregate(t->in_tok, t->out_tok, t->cell_off, t->n_req, cells, t->window_s, o->pct_num,
                                         o->pct_den, (int64_t*)(base + w.tin), (int64_t*)(base + w.tout),
                                         (int32_t*)(base + w.in_p99), (CellRec*)(base + w.rec),
-                                        (uint8_t*)(base + w.cstat), (WsHeader*)(base + w.header), s),
+                                        (uint8_t*)(base + w.cstat), (WsHeader*)(base + w.header),
+                                        workspace_bytes >= w.all ? base + w.many : nullptr, s),   // a workspace of the size without it still does
               "cell aggregate launch"))
     return DYN_E_DEVICE;
 
@@ -662,7 +665,7 @@ int dyn_trace_ingest(const double* t_s, const int32_t* in_tok, const int32_t* ou
 
 size_t dyn_eval_space_workspace(int32_t n_window, int32_t n_class, int32_t n_config) {
   if (n_window < 1 || n_class < 1 || n_config < 1) return 0;
-  return dyn_eval_ws_layout((int64_t)n_window * n_class, n_config).total;
+  return dyn_eval_ws_layout((int64_t)n_window * n_class, n_config).all;
 }
 
 int dyn_eval_space(dyn_profile* p, const dyn_trace_view* t, const dyn_config* cfg, int32_t K,
@@ -748,7 +751,7 @@ int dyn_eval_select_static(dyn_profile* p, const dyn_trace_view* t, const dyn_co
   if ((rc = check_device(p)) != DYN_OK) return rc;
   void* ws = nullptr;
   if ((rc = scratch_address(&ws)) != DYN_OK) return rc;
-  if ((rc = eval_impl(p, t, cfg, K, o, out, sel, ws, (size_t)DYN_STATIC_WORKSPACE_BYTES, hip_stream)) != DYN_OK) return rc;
+  if ((rc = eval_impl(p, t, cfg, K, o, out, sel, ws, (size_t)DYN_STATIC_WORKSPACE_BYTES + DYN_CELL_MANY_MAX, hip_stream)) != DYN_OK) return rc;
   if (status) {
     hipLaunchKernelGGL(cell_status_word_kernel, dim3(1), dim3(1024), 0, (hipStream_t)hip_stream,
                        (const uint8_t*)((const char*)ws + w.cstat), cells, status);
@@ -837,7 +840,7 @@ namespace {
 
 struct MixedWs {
   EvalWs cell;       // header .. cstat (per-cell aggregates); cell.part is where type_energy starts
-  size_t type_energy, type_f, ok, total;
+  size_t type_energy, type_f, ok, total, many, all;
 };
 struct MixedPlan {
   MixedTypes types;
@@ -878,6 +881,8 @@ MixedWs mixed_ws_layout(int64_t cells, int32_t n_entry) {
   w.type_f = off; off += align256(c * (size_t)n_entry);
   w.ok = off; off += align256(c * sizeof(int32_t));
   w.total = off;
+  w.many = off; off += align256(dyn_cell_many_bytes(cells));
+  w.all = off;
   return w;
 }
 
@@ -886,7 +891,7 @@ MixedWs mixed_ws_layout(int64_t cells, int32_t n_entry) {
 size_t dyn_mixed_workspace(const dyn_profile* p, int32_t n_window, const dyn_mixed_space* m) {
   MixedPlan mp;
   if (!p || n_window < 1 || plan_mixed(p, m, &mp) != DYN_OK) return 0;
-  return mixed_ws_layout((int64_t)n_window * p->G, mp.n_entry).total;
+  return mixed_ws_layout((int64_t)n_window * p->G, mp.n_entry).all;
 }
 
 int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mixed_space* m, const dyn_objective* o,
@@ -928,7 +933,8 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
   if (!hip_ok(dyn_launch_cell_aggregate(t->in_tok, t->out_tok, t->cell_off, t->n_req, cells, t->window_s, o->pct_num,
                                         o->pct_den, (int64_t*)(base + w.cell.tin), (int64_t*)(base + w.cell.tout),
                                         (int32_t*)(base + w.cell.in_p99), (CellRec*)(base + w.cell.rec),
-                                        (uint8_t*)(base + w.cell.cstat), (WsHeader*)(base + w.cell.header), s),
+                                        (uint8_t*)(base + w.cell.cstat), (WsHeader*)(base + w.cell.header),
+                                        workspace_bytes >= w.all ? base + w.many : nullptr, s),
               "cell aggregate launch"))
     return DYN_E_DEVICE;
 
@@ -1121,7 +1127,7 @@ HierWs hier_ws_layout(int64_t cells, int32_t n_tick, int32_t n_tp, int32_t n_lay
 size_t dyn_hierarchy_workspace(int32_t n_window, int32_t n_tick, int32_t n_class, int32_t n_layout) {
   if (n_window < 1 || n_tick < 1 || n_class < 1 || n_layout < 1) return 0;
   return hier_ws_layout((int64_t)n_window * n_class, n_tick, 64, n_layout).total +
-         path_ws_layout(n_window, n_class, n_layout, n_layout).total;
+         path_ws_layout(n_window, n_class, n_layout, n_layout).total + align256(dyn_cell_many_bytes((int64_t)n_window * n_class * n_tick));
 }
 
 int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view* tf, int32_t n_tick, const dyn_controllers* c,
@@ -1172,13 +1178,14 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
       (rc = cache_upload(p->lay_tp_host, p->d_lay_tp, c->lay_tp_index, (size_t)c->n_layout, s, "copy layouts")) != DYN_OK)
     return rc;
   const double window_s = (double)n_tick * tf->window_s;
+  void* many = workspace_bytes >= w.total + pw.total + align256(dyn_cell_many_bytes(fine_cells)) ? base + w.total + pw.total : nullptr;   // of both levels in turn
   // tick level first: the window-level aggregation then (re)writes the workspace's header
   if (!hip_ok(dyn_launch_cell_aggregate(tf->in_tok, tf->out_tok, tf->cell_off, tf->n_req, fine_cells, tf->window_s, o->pct_num, o->pct_den,
                                         (int64_t*)(fb + w.fine.tin), (int64_t*)(fb + w.fine.tout), (int32_t*)(fb + w.fine.in_p99),
-                                        (CellRec*)(fb + w.fine.rec), (uint8_t*)(fb + w.fine.cstat), (WsHeader*)(fb + w.fine.header), s), "cell aggregate launch") ||
+                                        (CellRec*)(fb + w.fine.rec), (uint8_t*)(fb + w.fine.cstat), (WsHeader*)(fb + w.fine.header), many, s), "cell aggregate launch") ||
       !hip_ok(dyn_launch_cell_aggregate(tc->in_tok, tc->out_tok, tc->cell_off, tc->n_req, cells, window_s, o->pct_num, o->pct_den,
                                         (int64_t*)(base + w.coarse.tin), (int64_t*)(base + w.coarse.tout), (int32_t*)(base + w.coarse.in_p99),
-                                        (CellRec*)(base + w.coarse.rec), (uint8_t*)(base + w.coarse.cstat), (WsHeader*)(base + w.coarse.header), s), "cell aggregate launch"))
+                                        (CellRec*)(base + w.coarse.rec), (uint8_t*)(base + w.coarse.cstat), (WsHeader*)(base + w.coarse.header), many, s), "cell aggregate launch"))
     return DYN_E_DEVICE;
   HierArgs a;
   a.tab = p->d_tab; a.ml = p->d_ml; a.gridpack = p->d_gridpack; a.jstart = p->d_jstart; a.tstart = p->d_tstart; a.thr = p->d_thr; a.n_bucket = p->n_bucket; a.bucket_scale = p->bucket_scale;

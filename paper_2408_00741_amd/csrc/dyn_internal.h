@@ -127,6 +127,7 @@ struct WsHeader {
 // Layout of the evaluation workspace (offsets in bytes, all multiples of 256).
 struct EvalWs {
   size_t header, tin, tout, in_p99, rec, cstat, part, total;
+  size_t many, all;  // after `total`: scratch of dyn_launch_cell_aggregate, and the end of that
   int32_t n_wslot;   // partial records per cell
 };
 EvalWs dyn_eval_ws_layout(int64_t cells, int32_t K);
@@ -136,7 +137,10 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                                      const int64_t* cell_off, int64_t n_req, int64_t cells,
                                      double window_s, int32_t pct_num, int32_t pct_den,
                                      int64_t* tin, int64_t* tout, int32_t* in_p99, CellRec* rec,
-                                     uint8_t* cstat, WsHeader* header, hipStream_t s);
+                                     uint8_t* cstat, WsHeader* header, void* many, hipStream_t s);
+// Bytes of `many`, 256-byte aligned; with a null pointer a block keeps every long cell.
+size_t dyn_cell_many_bytes(int64_t cells);
+#define DYN_CELL_MANY_MAX ((8u << 20) + 16384u)   // the most it can be
 
 struct SpaceArgs {
   const double* tab; const double* ml; const double* gridpack;

@@ -13,6 +13,8 @@
 // the cell, so the j-th largest element cannot be below it): for a high percentile only a
 // few bits are left.  Larger cells are streamed from global memory by the whole block,
 // once for the sums and once per 10-bit digit, through an LDS histogram (radix select).
+#include <algorithm>
+
 #include "dyn_device.h"
 
 namespace {
@@ -141,53 +143,15 @@ __device__ __forceinline__ void group_sync() {
   }
 }
 
-// Large cell, by a group of WAVES waves (the whole block, or one wave on its own): the group streams the cell from
-// global memory once for the sums and once per 10-bit digit of the selection (radix select through one LDS histogram).
-// Every thread returns the same result.  `hist` (kHistBins counters) and `xch` (kXchWords) are LDS scratch of the
-// group; the caller guarantees nobody else uses them.
+// The value of rank `need` (counted from the bottom) among those of the cell's values whose bits from hi_bit on are `prefix`, 10 bits a
+// pass over the cell.  `hist` and `xch` as below.
 constexpr int kXchWords = 16;
-template <int U, int WAVES>   // U independent loads per array in flight
-__device__ __forceinline__ CellOut cell_by_group(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg,
-                                 int64_t m, int64_t rank, uint32_t* hist, int64_t* xch) {
-  static_assert(WAVES * 3 <= 12, "words 12 and 13 pass the digit on");
+template <int U, int WAVES>   // U independent loads in flight
+__device__ __forceinline__ uint32_t rank_by_group(const int32_t* __restrict__ in, int64_t beg, int64_t m, int hi_bit, uint32_t prefix,
+                                                  int64_t need, uint32_t* hist, int64_t* xch) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int tid = WAVES == 1 ? lane : (int)threadIdx.x, wave = tid / DYN_WAVE;
   constexpr int nthr = WAVES * DYN_WAVE;
-  int64_t sin = 0, sout = 0;
-  uint32_t orv = 0;
-  for (int64_t i0 = 0; i0 < m; i0 += U * nthr) {
-    int a[U], b[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + u * nthr + tid;
-      a[u] = i < m ? in[beg + i] : 0;
-      b[u] = i < m ? out[beg + i] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      sin += a[u];
-      sout += b[u];
-      orv |= (uint32_t)(a[u] | b[u]);
-    }
-  }
-  sin = wave_sum_i64(sin);
-  sout = wave_sum_i64(sout);
-  orv = wave_or_u32(orv);
-  group_sync<WAVES>();
-  if (lane == 0) { xch[wave * 3 + 0] = sin; xch[wave * 3 + 1] = sout; xch[wave * 3 + 2] = (int64_t)orv; }
-  group_sync<WAVES>();
-  CellOut r;
-  r.tin = r.tout = 0;
-  r.orv = 0;
-  for (int w = 0; w < WAVES; ++w) {
-    r.tin += xch[w * 3 + 0];
-    r.tout += xch[w * 3 + 1];
-    r.orv |= (uint32_t)xch[w * 3 + 2];
-  }
-
-  int hi_bit = 32 - __builtin_clz(r.orv | 1u);  // bits >= hi_bit of the answer are `prefix`
-  uint32_t prefix = 0;
-  int64_t need = rank;
   while (hi_bit > 0) {
     const int w = hi_bit < kHistBits ? hi_bit : kHistBits;
     const int shift = hi_bit - w;
@@ -251,7 +215,54 @@ __device__ __forceinline__ CellOut cell_by_group(const int32_t* __restrict__ in,
     hi_bit = shift;
   }
   group_sync<WAVES>();
-  r.p99 = prefix;
+  return prefix;
+}
+
+// Large cell, by a group of WAVES waves (the whole block, or one wave on its own): the group streams the cell from
+// global memory once for the sums and once per 10-bit digit of the selection (radix select through one LDS histogram).
+// Every thread returns the same result.  `hist` (kHistBins counters) and `xch` (kXchWords) are LDS scratch of the
+// group; the caller guarantees nobody else uses them.
+template <int U, int WAVES>   // U independent loads per array in flight
+__device__ __forceinline__ CellOut cell_by_group(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg,
+                                 int64_t m, int64_t rank, uint32_t* hist, int64_t* xch) {
+  static_assert(WAVES * 3 <= 12, "words 12 and 13 pass the digit on");
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const int tid = WAVES == 1 ? lane : (int)threadIdx.x, wave = tid / DYN_WAVE;
+  constexpr int nthr = WAVES * DYN_WAVE;
+  int64_t sin = 0, sout = 0;
+  uint32_t orv = 0;
+  for (int64_t i0 = 0; i0 < m; i0 += U * nthr) {
+    int a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * nthr + tid;
+      a[u] = i < m ? in[beg + i] : 0;
+      b[u] = i < m ? out[beg + i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      sin += a[u];
+      sout += b[u];
+      orv |= (uint32_t)(a[u] | b[u]);
+    }
+  }
+  sin = wave_sum_i64(sin);
+  sout = wave_sum_i64(sout);
+  orv = wave_or_u32(orv);
+  group_sync<WAVES>();
+  if (lane == 0) { xch[wave * 3 + 0] = sin; xch[wave * 3 + 1] = sout; xch[wave * 3 + 2] = (int64_t)orv; }
+  group_sync<WAVES>();
+  CellOut r;
+  r.tin = r.tout = 0;
+  r.orv = 0;
+  for (int w = 0; w < WAVES; ++w) {
+    r.tin += xch[w * 3 + 0];
+    r.tout += xch[w * 3 + 1];
+    r.orv |= (uint32_t)xch[w * 3 + 2];
+  }
+
+  // bits >= 32 - clz of the answer are zero
+  r.p99 = rank_by_group<U, WAVES>(in, beg, m, 32 - __builtin_clz(r.orv | 1u), 0u, rank, hist, xch);
   return r;
 }
 
@@ -576,6 +587,96 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
     }
 }
 
+// ---- long cells: many blocks share a cell --------------------------------------------------------
+// A block streams a cell at about 16 GB/s (a memory latency for every 16 KB), so a few cells of many requests leave the device
+// idle.  Here a cell beyond what a block holds in registers is cut into pieces, a block each.  The first pass takes the sums and counts
+// the lengths by exponent and the six bits below it (exact below 64, otherwise a bin is at most 1/64 of its value wide) in LDS and adds
+// the counts to the cell's counters in the workspace; in the second every block finds the bin that holds the rank, counts the lengths
+// in it by its 256 parts, and the last block of the cell to be done finds the answer.  Lengths below 2^15 are exact then; what is left
+// of a wider bin that block searches alone.  Bounds: the launches (3 us each), then reading 8 and 4 bytes a request.
+// Measured (us of dyn_eval_select; a block per cell, this): 20 M requests in one cell 22 090, 71 (the first pass 28: 5.7 TB/s, the second 25);
+// in 48 cells 1109, 72; in 500 174, 88; 3.8 M in 3 cells 2817, 39; 12.8 M in 8 cells of mixed pools 3194, 61.  The line: 9 cells of mean
+// 4500 37, 40, of 8000 48, 40; 500 of 4500 45, 52, of 8000 57, 51; 1000 of 8000 67, 71, of 12 000 87, 78; one of 9000 30, 37, of 16 000 35, 37.
+constexpr int64_t kLongCell = 8192;                // what a block still holds in registers
+constexpr int kLongSlots = 1024;                   // slots of the workspace: several copies a cell where cells are few
+constexpr int kLongCopies = 4;                     // at most: blocks that add to one counter hold each other up (28 us against 11 for 900 blocks and 3 cells)
+constexpr int64_t kLongMean = 9000, kLongLeast = 20000;   // requests per cell, and in all, from which the two launches are worth it
+constexpr int kLongBlocks = 512;                   // pieces of a whole trace, two blocks to a compute unit
+constexpr int64_t kLongShare = 32;                  // pieces of a mean cell that one copy of its counters takes
+constexpr int64_t kLongPiece = 4096;               // least requests of a piece: 16 a thread
+constexpr int kCoarseBins = 64 + 26 * 64;          // exponents 6 .. 31
+constexpr int kFineBins = 256;
+constexpr int kSlotsPerBlock = 8;                  // cleared by one block of long_prepare
+// words of the workspace: long cells, pieces; the cells [kBlockCells at most]; every slot's first piece and the end; the slots
+constexpr int kLongCellsAt = 64, kLongFirstAt = kLongCellsAt + 1024, kLongHeadWords = kLongFirstAt + 1088;
+// words of a slot: the counts, the two sums (64 bits), the OR of all token counts, blocks done
+constexpr int kFineAt = kCoarseBins, kSumsAt = kFineAt + kFineBins, kOrAt = kSumsAt + 4, kDoneAt = kOrAt + 1;
+constexpr int kLongSlotWords = 2048;
+static_assert((kLongHeadWords + (size_t)kLongSlots * kLongSlotWords) * sizeof(uint32_t) <= DYN_CELL_MANY_MAX && kLongSlots + 1 <= 1088 && kLongHeadWords % 64 == 0, "the workspace");
+static_assert(kDoneAt < kLongSlotWords && kSumsAt % 2 == 0, "the slot");
+
+struct LongArgs {
+  int64_t from;      // cells of more requests are long
+  int64_t piece;     // requests of a piece
+  int32_t n_cell, copies;  // cells (each may be long); slots of a cell, a power of two
+  uint32_t* work;
+};
+
+__device__ __forceinline__ int coarse_bin(uint32_t v) {
+  const int e = 31 - __builtin_clz(v | 32u);         // 5 below 64
+  return e < 6 ? (int)v : (e - 5) * 64 + (int)((v >> (e - 6)) & 63u);
+}
+// The least value of a bin, and how many bits the values in it differ by.
+__device__ __forceinline__ uint32_t coarse_low(int bin, int* bits) {
+  const int e = bin / 64 + 5;
+  *bits = bin < 64 ? 0 : e - 6;
+  return bin < 64 ? (uint32_t)bin : (64u + (uint32_t)(bin & 63)) << (e - 6);
+}
+
+// Block 0 of these lists the long cells and their pieces, the others clear the slots.  `s` is LDS scratch of kHistBins words.
+__device__ __forceinline__ void long_prepare(const LongArgs& a, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells, int part, uint32_t* s) {
+  if (part > 0) {
+    const int s0 = (part - 1) * kSlotsPerBlock, s1 = min(s0 + kSlotsPerBlock, a.n_cell * a.copies);
+    uint4* at = (uint4*)(a.work + kLongHeadWords + (size_t)s0 * kLongSlotWords);
+    for (int i = threadIdx.x; i < (s1 - s0) * (kLongSlotWords / 4); i += blockDim.x) at[i] = make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  int n = 0;                                         // long cells so far, block-uniform
+  uint32_t pieces = 0;
+  for (int64_t c0 = 0; c0 < cells; c0 += blockDim.x) {
+    const int64_t c = c0 + threadIdx.x;
+    const int64_t beg = c < cells ? cell_off[c] : 0, end = c < cells ? cell_off[c + 1] : 0;
+    const bool is = beg >= 0 && end <= n_req && end - beg > a.from;
+    const uint32_t mine = is ? (uint32_t)((end - beg + a.piece - 1) / a.piece) : 0u;
+    const uint64_t who = __ballot(is);
+    uint32_t incl = mine;
+#pragma unroll
+    for (int d = 1; d < DYN_WAVE; d <<= 1) {
+      const uint32_t up = __shfl_up(incl, d, DYN_WAVE);
+      if (lane >= d) incl += up;
+    }
+    if (lane == DYN_WAVE - 1) { s[2 * wave] = (uint32_t)__popcll(who); s[2 * wave + 1] = incl; }
+    __syncthreads();
+    int at = n + __popcll(who & ((1ull << lane) - 1ull));
+    uint32_t first = pieces + incl - mine;
+    for (int w = 0; w < (int)blockDim.x / DYN_WAVE; ++w) {
+      if (w < wave) { at += (int)s[2 * w]; first += s[2 * w + 1]; }
+      n += (int)s[2 * w];
+      pieces += s[2 * w + 1];
+    }
+    __syncthreads();                                 // s is written again
+    if (is) {
+      a.work[kLongCellsAt + at] = (uint32_t)c;
+      a.work[kLongFirstAt + at] = first;
+    }
+  }
+  if (threadIdx.x == 0) {
+    a.work[0] = (uint32_t)n;
+    a.work[kLongFirstAt + n] = pieces;
+  }
+}
+
 // ---- few cells: a block per long cell -----------------------------------------------------------
 // With no more cells than compute units hold blocks, a wave per cell leaves most of the device idle while the longest cell
 // decides the time.  Here cells of up to kWaveCell requests have a wave each and four waves share a longer one: up to kBlockRows
@@ -592,6 +693,7 @@ constexpr int kBlockRows = 32;                     // register path: m <= 256 * 
 constexpr int kWaveCell = 3072;                    // up to here a wave on its own: 24 packed registers
 constexpr int64_t kBlockCells = 1024;              // cells that the device holds at once this way
 constexpr int64_t kBlockMean = 1000;               // requests per cell
+static_assert(kBlockCells <= kLongSlots, "a slot for every cell");
 static_assert(kWaveCell <= 128 * 24, "the packed form below");
 
 template <int R>
@@ -659,7 +761,7 @@ __device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in,
 __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) void cell_aggregate_block_kernel(
     const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells,
     double window_s, double r_window, int32_t pct_num, int32_t pct_den, int64_t* __restrict__ tin, int64_t* __restrict__ tout,
-    int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header) {
+    int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header, LongArgs lg) {
   __shared__ uint32_t s_hist[kBlockWaves][kHistBins];
   __shared__ int64_t s_xch[kBlockWaves][kXchWords];
   __shared__ uint32_t s_n[2 * kBlockWaves];
@@ -667,6 +769,10 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   // the first blocks take a cell per wave, one block for every cell follows
   const int64_t shared = (cells + kBlockWaves - 1) / kBlockWaves;
+  if ((int64_t)blockIdx.x >= cells + shared) {     // the blocks after those make the many blocks' kernels ready
+    long_prepare(lg, cell_off, n_req, cells, (int)((int64_t)blockIdx.x - cells - shared), s_hist[0]);
+    return;
+  }
   const bool alone = (int64_t)blockIdx.x < shared;
   const int64_t c = alone ? (int64_t)blockIdx.x * kBlockWaves + wave : (int64_t)blockIdx.x - shared;
   if (c >= cells) return;
@@ -674,6 +780,7 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_
   uint32_t bad = (beg < 0 || end < beg || end > n_req) ? DYN_WS_BAD_OFFSETS : 0u;
   if (bad) beg = end = 0;                          // never read outside the trace
   const int64_t m = end - beg;
+  if (m > lg.from) return;                         // the many blocks' (lg.from >= kWaveCell)
   if (alone != (m <= kWaveCell)) return;           // uniform over the wave, and over a block that takes one cell
   CellOut r;
   r.tin = r.tout = 0;
@@ -695,17 +802,245 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_
   if (alone ? lane == 0 : threadIdx.x == 0) write_cell(c, r, m, bad, window_s, r_window, cells, tin, tout, in_p99, rec, cstat, header);
 }
 
+// The slots' first pieces into LDS (kLongSlots + 1 words); returns how many slots are used, *n_item the pieces.
+__device__ __forceinline__ int long_table(const LongArgs& a, uint32_t* s_first, uint32_t* n_item) {
+  const int n = (int)a.work[0];
+  for (int i = threadIdx.x; i <= n; i += blockDim.x) s_first[i] = a.work[kLongFirstAt + i];
+  __syncthreads();
+  *n_item = n > 0 ? s_first[n] : 0u;
+  return n;
+}
+__device__ __forceinline__ int long_slot(const uint32_t* s_first, int n, uint32_t item) {
+  int l = 0, h = n - 1;                              // the last slot that starts at or before the item
+  while (l < h) {
+    const int mid = (l + h + 1) >> 1;
+    if (s_first[mid] <= item) l = mid; else h = mid - 1;
+  }
+  return l;
+}
+
+// First pass: sums and coarse counts.
+__global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_count_kernel(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
+                                                                                const int64_t* __restrict__ cell_off, LongArgs a) {
+  __shared__ uint32_t s_first[kLongSlots + 1];
+  __shared__ uint32_t s_bin[kCoarseBins];
+  __shared__ int64_t s_sum[kBlockWaves][2];
+  __shared__ uint32_t s_or[kBlockWaves];
+  constexpr int kThreads = kBlockWaves * DYN_WAVE, U = 8;
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t n_item;
+  const int n = long_table(a, s_first, &n_item);
+  for (uint32_t item = blockIdx.x; item < n_item; item += gridDim.x) {
+    const int slot = long_slot(s_first, n, item);
+    const int64_t c = a.work[kLongCellsAt + slot];
+    const int64_t end = cell_off[c + 1], beg = cell_off[c] + (int64_t)(item - s_first[slot]) * a.piece;
+    const int m = (int)(end - beg < a.piece ? end - beg : a.piece);
+    for (int b = threadIdx.x; b < kCoarseBins; b += kThreads) s_bin[b] = 0u;
+    __syncthreads();
+    const int32_t *pi = in + beg, *po = out + beg;
+    int64_t sin = 0, sout = 0;
+    uint32_t orv = 0;
+    for (int i0 = 0; i0 < m; i0 += U * kThreads) {
+      uint32_t x[U], y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = min(i0 + u * kThreads + (int)threadIdx.x, m - 1);
+        x[u] = (uint32_t)pi[i];
+        y[u] = (uint32_t)po[i];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool ok = i0 + u * kThreads + (int)threadIdx.x < m;
+        sin += ok ? (int32_t)x[u] : 0;
+        sout += ok ? (int32_t)y[u] : 0;
+        orv |= x[u] | y[u];                          // beyond the piece: its last request again
+        if (ok) atomicAdd(&s_bin[coarse_bin(x[u])], 1u);
+      }
+    }
+    sin = wave_sum_i64(sin);
+    sout = wave_sum_i64(sout);
+    orv = wave_or_u32(orv);
+    if (lane == 0) { s_sum[wave][0] = sin; s_sum[wave][1] = sout; s_or[wave] = orv; }
+    __syncthreads();
+    uint32_t* at = a.work + kLongHeadWords + ((size_t)slot * a.copies + (item & (uint32_t)(a.copies - 1))) * kLongSlotWords;
+    for (int b = threadIdx.x; b < kCoarseBins; b += kThreads) {
+      const uint32_t k = s_bin[b];
+      if (k) atomicAdd(&at[b], k);
+    }
+    if (threadIdx.x == 0) {
+      int64_t t0 = 0, t1 = 0;
+      uint32_t o = 0;
+      for (int w = 0; w < kBlockWaves; ++w) { t0 += s_sum[w][0]; t1 += s_sum[w][1]; o |= s_or[w]; }
+      atomicAdd((unsigned long long*)(at + kSumsAt), (unsigned long long)t0);
+      atomicAdd((unsigned long long*)(at + kSumsAt) + 1, (unsigned long long)t1);
+      atomicOr(&at[kOrAt], o);
+    }
+    __syncthreads();                                 // LDS is reused by the next item
+  }
+}
+
+// The bin where the running count of `bins` counters (a thread holds PER consecutive ones, zeroes beyond) reaches `need`; *below = the
+// count before it.  Block-uniform; `s` is LDS scratch of kBlockWaves + 2 words.
+template <int PER>
+__device__ __forceinline__ int find_bin(const uint32_t (&k)[PER], int64_t need, uint32_t* s, int64_t* below) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t mine = 0;                                 // a cell has fewer than 2^31 requests
+#pragma unroll
+  for (int q = 0; q < PER; ++q) mine += k[q];
+  uint32_t incl = mine;
+#pragma unroll
+  for (int d = 1; d < DYN_WAVE; d <<= 1) {
+    const uint32_t up = __shfl_up(incl, d, DYN_WAVE);
+    if (lane >= d) incl += up;
+  }
+  if (lane == DYN_WAVE - 1) s[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - mine;
+  for (int w = 0; w < wave; ++w) run += s[w];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if ((int64_t)run < need && need <= (int64_t)run + k[q]) {   // one thread, one bin
+      s[kBlockWaves] = (uint32_t)((int)threadIdx.x * PER + q);
+      s[kBlockWaves + 1] = run;
+    }
+    run += k[q];
+  }
+  __syncthreads();
+  const int bin = (int)s[kBlockWaves];
+  *below = s[kBlockWaves + 1];
+  __syncthreads();
+  return bin;
+}
+
+// Second pass: the bin that holds the rank, its parts counted, and the cell's outputs from the last block to be done with it.
+__global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_rank_kernel(
+    const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t cells, double window_s,
+    double r_window, int32_t pct_num, int32_t pct_den, int64_t* __restrict__ tin, int64_t* __restrict__ tout, int32_t* __restrict__ in_p99,
+    CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header, LongArgs a) {
+  constexpr int kThreads = kBlockWaves * DYN_WAVE, U = 8, kPer = (kCoarseBins + kThreads - 1) / kThreads;
+  __shared__ uint32_t s_first[kLongSlots + 1];
+  __shared__ uint32_t s_bin[kPer * kThreads];
+  __shared__ int64_t s_xch[kXchWords];
+  __shared__ uint32_t s_find[kBlockWaves + 2];
+  __shared__ uint32_t s_last;
+  static_assert(kFineBins == kThreads && kHistBins <= kPer * kThreads, "a thread per part of a bin");
+  uint32_t n_item;
+  const int n = long_table(a, s_first, &n_item);
+  for (uint32_t item = blockIdx.x; item < n_item; item += gridDim.x) {
+    const int slot = long_slot(s_first, n, item);
+    const int64_t c = a.work[kLongCellsAt + slot];
+    const int64_t beg = cell_off[c], m = cell_off[c + 1] - beg;
+    const int64_t rank = ((int64_t)pct_num * m + pct_den - 1) / pct_den;
+    uint32_t* at = a.work + kLongHeadWords + (size_t)slot * a.copies * kLongSlotWords;   // the cell's first copy
+    {                                                // the copies' counts, coalesced, then a thread's consecutive bins through LDS
+      uint32_t t[kLongCopies][kPer];
+#pragma unroll
+      for (int y = 0; y < kLongCopies; ++y)          // all loads in flight: a copy that is not there is read as the first, then left out
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          t[y][q] = at[(size_t)(y < a.copies ? y : 0) * kLongSlotWords + min(q * kThreads + (int)threadIdx.x, kCoarseBins)];
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int y = 0; y < kLongCopies; ++y) all += y < a.copies ? t[y][q] : 0u;
+        s_bin[q * kThreads + threadIdx.x] = q * kThreads + (int)threadIdx.x < kCoarseBins ? all : 0u;
+      }
+    }
+    __syncthreads();
+    uint32_t k[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) k[q] = s_bin[(int)threadIdx.x * kPer + q];
+    int64_t below;
+    int bits;
+    const uint32_t low = coarse_low(find_bin(k, rank, s_find, &below), &bits);
+    const int shift = bits > 8 ? bits - 8 : 0;       // of a value in the bin to its part
+    const uint32_t pieces = s_first[slot + 1] - s_first[slot];
+    bool last = item == s_first[slot];
+    if (bits > 0) {
+      s_bin[threadIdx.x] = 0u;
+      __syncthreads();
+      const int64_t p0 = (int64_t)(item - s_first[slot]) * a.piece;
+      const int32_t* pi = in + beg + p0;
+      const int mp = (int)(m - p0 < a.piece ? m - p0 : a.piece);
+      for (int i0 = 0; i0 < mp; i0 += U * kThreads) {
+        uint32_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = (uint32_t)pi[min(i0 + u * kThreads + (int)threadIdx.x, mp - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i0 + u * kThreads + (int)threadIdx.x < mp && (x[u] - low) >> bits == 0u) atomicAdd(&s_bin[(x[u] - low) >> shift], 1u);
+      }
+      __syncthreads();
+      // The counts are added at the device's coherence point, and the block has every one of its old values back before it says that
+      // it is done: whoever is last finds all counts there.
+      uint32_t old = 0;
+      const uint32_t mine = s_bin[threadIdx.x];
+      if (mine) old = __hip_atomic_fetch_add(&at[(size_t)(item & (uint32_t)(a.copies - 1)) * kLongSlotWords + kFineAt + threadIdx.x], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("" ::"v"(old) : "memory");
+      __syncthreads();
+      if (threadIdx.x == 0) s_last = __hip_atomic_fetch_add(&at[kDoneAt], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == pieces ? 1u : 0u;
+      __syncthreads();
+      last = s_last != 0u;
+    }
+    if (last) {                                      // block-uniform
+      CellOut r;
+      r.p99 = low;
+      if (bits > 0) {
+        uint32_t f[1] = {0u};
+#pragma unroll
+        for (int y = 0; y < kLongCopies; ++y) {
+          const uint32_t x = __hip_atomic_load(&at[(size_t)(y < a.copies ? y : 0) * kLongSlotWords + kFineAt + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          f[0] += y < a.copies ? x : 0u;
+        }
+        int64_t less;
+        const int part = find_bin(f, rank - below, s_find, &less);
+        r.p99 = low + ((uint32_t)part << shift);
+        if (shift > 0) r.p99 = rank_by_group<U, kBlockWaves>(in, beg, m, shift, r.p99 >> shift, rank - below - less, s_bin, s_xch);
+      }
+      r.tin = r.tout = 0;
+      r.orv = 0;
+      for (int y = 0; y < a.copies; ++y) {
+        const uint32_t* ay = at + (size_t)y * kLongSlotWords;
+        r.tin += (int64_t)((const uint64_t*)(ay + kSumsAt))[0];
+        r.tout += (int64_t)((const uint64_t*)(ay + kSumsAt))[1];
+        r.orv |= ay[kOrAt];
+      }
+      const uint32_t bad = (r.orv >> 31) ? DYN_WS_BAD_REQUEST : 0u;   // a negative token count
+      if (threadIdx.x == 0) write_cell(c, r, m, bad, window_s, r_window, cells, tin, tout, in_p99, rec, cstat, header);
+    }
+    __syncthreads();                                 // LDS is reused by the next item
+  }
+}
+
 }  // namespace
 
 hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_tok,
                                      const int64_t* cell_off, int64_t n_req, int64_t cells,
                                      double window_s, int32_t pct_num, int32_t pct_den,
                                      int64_t* tin, int64_t* tout, int32_t* in_p99, CellRec* rec,
-                                     uint8_t* cstat, WsHeader* header, hipStream_t s) {
+                                     uint8_t* cstat, WsHeader* header, void* many, hipStream_t s) {
   DynTimed timed(DYN_K_CELL, s);
   if (cells <= kBlockCells && n_req > kBlockMean * cells) {
-    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)(cells + (cells + kBlockWaves - 1) / kBlockWaves)), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
-                       window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header);
+    LongArgs lg;
+    lg.from = INT64_MAX; lg.piece = 0; lg.n_cell = 0; lg.copies = 1; lg.work = nullptr;
+    unsigned prepare = 0, items = 0;
+    if (many && n_req > kLongMean * cells && n_req > kLongLeast) {
+      lg.from = kLongCell;
+      lg.n_cell = (int32_t)cells;
+      lg.piece = std::max<int64_t>(kLongPiece, ((n_req + kLongBlocks - 1) / kLongBlocks + 255) / 256 * 256);
+      while (lg.copies < kLongCopies && 2 * lg.copies * cells <= kLongSlots && n_req > (kLongShare * lg.copies) * cells * lg.piece) lg.copies *= 2;
+      lg.work = (uint32_t*)many;
+      prepare = 1 + (unsigned)(cells * lg.copies + kSlotsPerBlock - 1) / kSlotsPerBlock;
+      items = (unsigned)((n_req + lg.piece - 1) / lg.piece + std::min<int64_t>(cells, n_req / kLongCell));   // every long cell's last piece may be a short one
+    }
+    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)(cells + (cells + kBlockWaves - 1) / kBlockWaves) + prepare), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
+                       window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, lg);
+    if (items) {
+      hipLaunchKernelGGL(cell_long_count_kernel, dim3(items), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, lg);
+      hipLaunchKernelGGL(cell_long_rank_kernel, dim3(items), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, cells, window_s, 1.0 / window_s,
+                         pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, lg);
+    }
     return hipGetLastError();
   }
   if (n_req / 48 <= cells) {                     // a few dozen requests per cell on average
@@ -720,4 +1055,8 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                      0, s, in_tok, out_tok, cell_off, n_req, cells, window_s, 1.0 / window_s, pct_num, pct_den, tin,
                      tout, in_p99, rec, cstat, header);
   return hipGetLastError();
+}
+
+size_t dyn_cell_many_bytes(int64_t cells) {
+  return (kLongHeadWords + kLongSlotWords * (size_t)std::min<int64_t>(kLongSlots, kLongCopies * std::max<int64_t>(cells, 1))) * sizeof(uint32_t);
 }
