@@ -337,6 +337,11 @@ TickWs dyn_tick_ws_layout(int64_t n_req, int64_t coarse_cells, int32_t n_tick, i
   w.slow_list = off; off += align256(c * sizeof(uint32_t));
   w.list_cells = off; off += align256(c * sizeof(uint32_t));
   w.total = off;
+  w.n_slot = (int32_t)std::min<int64_t>(n_req / DYN_TICK_LONG, DYN_TICK_SLOTS_MAX);
+  w.pool_words = w.n_slot > 0 ? (uint32_t)std::min<int64_t>(n_req + 16384, DYN_TICK_POOL_MAX) : 0u;
+  w.slots = off; off += (size_t)w.n_slot * DYN_TICK_SLOT_WORDS * sizeof(uint32_t);
+  w.pool = off; off += align256((size_t)w.pool_words * sizeof(uint32_t));
+  w.all = off;
   return w;
 }
 
@@ -549,6 +554,7 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
       theta[g] = (float)th * 0.999999f;
     }
   }
+  p->prefill_flat = *std::min_element(theta.begin(), theta.end()) >= 0.98f;
 
   void* fixed_ws = nullptr;
   (void)scratch_address(&fixed_ws);   // set-up of dyn_eval_select_static on this device; that call reports a failure itself
@@ -762,7 +768,7 @@ int dyn_eval_select_static(dyn_profile* p, const dyn_trace_view* t, const dyn_co
 
 size_t dyn_eval_ticks_workspace(int64_t n_req, int32_t n_window, int32_t n_tick, int32_t n_class, int32_t n_config) {
   if (n_req < 0 || n_window < 1 || n_tick < 1 || n_tick > DYN_TICK_LIMIT || n_class < 1 || n_config < 1) return 0;
-  return dyn_tick_ws_layout(n_req, (int64_t)n_window * n_class, n_tick, n_config).total;
+  return dyn_tick_ws_layout(n_req, (int64_t)n_window * n_class, n_tick, n_config).all;
 }
 
 int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tick, const dyn_config* cfg, int32_t K,
@@ -800,8 +806,13 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ca.rec = (TickRec*)(base + w.fine.rec); ca.plan = (TickPlan*)(base + w.plan); ca.top = (int32_t*)(base + w.top);
   ca.cstat = (uint8_t*)(base + w.fine.cstat); ca.header = (WsHeader*)(base + w.fine.header);
   ca.counters = (uint32_t*)(base + w.counters); ca.deep_list = (uint32_t*)(base + w.deep_list); ca.slow_list = (uint32_t*)(base + w.slow_list);
-  ca.list_cells = (uint32_t*)(base + w.list_cells); ca.theta = p->d_theta;
+  ca.list_cells = (uint32_t*)(base + w.list_cells); ca.theta = p->d_theta; ca.flat = p->prefill_flat;
   ca.few_cells = cells <= 4 * (int64_t)p->n_cu ? 1 : 0;   // every cell's block of four waves is resident at once (four to a compute unit)
+  ca.slots = (uint32_t*)(base + w.slots); ca.pool = (uint32_t*)(base + w.pool); ca.pool_words = w.pool_words;
+  ca.n_slot = workspace_bytes >= w.all ? w.n_slot : 0;    // a workspace of the size without them still does
+  ca.sure = ca.n_slot > 0 && t->n_req / DYN_TICK_LONG <= ca.n_slot;
+  ca.cfg = p->d_cfg; ca.K = K; ca.ml = p->d_ml; ca.tab = p->d_tab; ca.gridpack = p->d_gridpack;
+  ca.jstart = p->d_jstart; ca.bucket_scale = p->bucket_scale; ca.n_tp_f = p->n_tp * p->n_f; ca.n_rho = p->n_rho;
   if (!hip_ok(dyn_launch_tick_cell(ca, s), "tick cell launch")) return DYN_E_DEVICE;
 
   TickArgs ta;
@@ -821,7 +832,7 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   a.part = (SelPart*)(base + w.part); a.n_wslot = w.n_wslot;
   ta.n_tick = n_tick; ta.tick_s = t->window_s; ta.window_s = (double)n_tick * t->window_s;
   ta.rec = (const TickRec*)(base + w.fine.rec); ta.plan = (const TickPlan*)(base + w.plan); ta.top = (const int32_t*)(base + w.top);
-  ta.in = t->in_tok;
+  ta.in = t->in_tok; ta.pool = ca.pool;
   ta.counters = (const uint32_t*)(base + w.counters); ta.slow_list = (const uint32_t*)(base + w.slow_list);
   ta.tstart = p->d_tstart; ta.thr = p->d_thr; ta.single_point = p->single_point; ta.any_two_rows = p->any_two_rows;
   ta.pfspan = p->d_pfspan; ta.n_cu = p->n_cu;

@@ -90,6 +90,52 @@ __device__ __forceinline__ double div_by(double a, double b, double rb) {
   return __builtin_fma(e1, rb, q1);
 }
 
+// Lengths counted by exponent and the six bits below it: exact below 64, otherwise a bin is at most 1/64 of its value wide.
+constexpr int kCoarseBins = 64 + 26 * 64;          // exponents 6 .. 31
+__device__ __forceinline__ int coarse_bin(uint32_t v) {
+  const int e = 31 - __builtin_clz(v | 32u);         // 5 below 64
+  return e < 6 ? (int)v : (e - 5) * 64 + (int)((v >> (e - 6)) & 63u);
+}
+// The least value of a bin, and how many bits the values in it differ by.
+__device__ __forceinline__ uint32_t coarse_low(int bin, int* bits) {
+  const int e = bin / 64 + 5;
+  *bits = bin < 64 ? 0 : e - 6;
+  return bin < 64 ? (uint32_t)bin : (64u + (uint32_t)(bin & 63)) << (e - 6);
+}
+
+// The bin where the running count of `bins` counters (a thread holds PER consecutive ones, zeroes beyond) reaches `need`; *below = the
+// count before it.  Block-uniform; `s` is LDS scratch of WAVES + 2 words.
+template <int WAVES, int PER>
+__device__ __forceinline__ int find_bin(const uint32_t (&k)[PER], int64_t need, uint32_t* s, int64_t* below) {
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
+  uint32_t mine = 0;                                 // a cell has fewer than 2^31 requests
+#pragma unroll
+  for (int q = 0; q < PER; ++q) mine += k[q];
+  uint32_t incl = mine;
+#pragma unroll
+  for (int d = 1; d < DYN_WAVE; d <<= 1) {
+    const uint32_t up = __shfl_up(incl, d, DYN_WAVE);
+    if (lane >= d) incl += up;
+  }
+  if (lane == DYN_WAVE - 1) s[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - mine;
+  for (int w = 0; w < wave; ++w) run += s[w];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if ((int64_t)run < need && need <= (int64_t)run + k[q]) {   // one thread, one bin
+      s[WAVES] = (uint32_t)((int)threadIdx.x * PER + q);
+      s[WAVES + 1] = run;
+    }
+    run += k[q];
+  }
+  __syncthreads();
+  const int bin = (int)s[WAVES];
+  *below = s[WAVES + 1];
+  __syncthreads();
+  return bin;
+}
+
 struct Lookup {          // per-thread constants of the table look-up
   double den, rden, rho_max, bucket_scale, omu, u;
   const double *lo, *hi;         // the configuration's two table rows: [3][n_rho] prefill, TBT, power

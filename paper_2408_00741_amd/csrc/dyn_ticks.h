@@ -6,6 +6,11 @@
 
 #define DYN_TICK_MAX 64     // ticks per window: a wave's lane holds a tick in the cell kernel
 #define DYN_TICK_FAST 16    // percentile depth j up to which the evaluation kernel keeps a sorted list in registers
+#define DYN_TICK_LONG 4096  // requests of a cell from which many blocks share it
+#define DYN_TICK_SLOT_WORDS 2048
+#define DYN_TICK_SLOTS_MAX 2048
+#define DYN_TICK_TABLE_HEAD 4   // words before a cell's tables: first length, lengths, stride, the first length's place in a row
+#define DYN_TICK_POOL_MAX (4u << 20)   // words
 #define DYN_TICK_WAVE 64    // depth up to which one wave of the cell kernel extracts the per-tick lists
 static_assert(DYN_TICK_MAX == DYN_TICK_LIMIT && DYN_TICK_MAX == DYN_WAVE && DYN_TICK_WAVE == DYN_WAVE,
               "the ABI's limits are the kernels' limits");
@@ -30,6 +35,7 @@ struct TickPlan {
 #define DYN_TP_RAW 8u     // j > DYN_TICK_DEPTH: the lists are whole ticks, sorted
 #define DYN_TICK_PIECES 0x80000000u   // in TickRec.off of a tick of such a cell that is too long to sort in LDS: its list is sorted in pieces of DYN_TICK_DEPTH (offsets stay below 2^31)
 #define DYN_TP_GENERAL 16u  // left to the general kernel: j beyond the walk's register list, or a TBT percentile that needs all ticks
+#define DYN_TP_TABLE 64u   // no lists: per tick a table of how many requests are at least so long (TickPlan.place: where in TickArgs.pool)
 #define DYN_TP_TIGHT 32u   // settled by the ticks' requests of length xj (TickRec.off then holds their number, not a list offset)
 
 struct TickCellArgs {
@@ -44,12 +50,20 @@ struct TickCellArgs {
   int32_t* top;              // [n_req]: per tick its min(j, cnt) largest input lengths, descending, at rec.off
   uint8_t* cstat;            // [fine cells] status bytes
   WsHeader* header;
-  uint32_t* counters;        // [0] cells on deep_list, [1] cells on slow_list, [2] cells on list_cells, [3] cells walked with lists; zeroed before the cell kernels
+  uint32_t* counters;        // [0] cells on deep_list, [1] cells on slow_list, [2] cells on list_cells, [3] cells walked with lists, [4] long cells, [5] words of the pool given away; zeroed before the cell kernels
   uint32_t* deep_list;       // [cells]
   uint32_t* slow_list;       // [cells] cells left to the general kernel
   uint32_t* list_cells;      // [cells] cells that need per-tick lists
   const float* theta;        // [G] per class: least (smallest / largest prefill time of a table row), rounded down
+  bool flat;                 // all of them are 0.98 or more
   int32_t few_cells;         // so few cells that a block per cell leaves no compute unit short of work
+  // long cells, which many blocks share: a slot of DYN_TICK_SLOT_WORDS each, and the words their tables are cut from
+  uint32_t* slots; int32_t n_slot;   // n_slot 0: none, a block keeps every long cell
+  uint32_t* pool; uint32_t pool_words;
+  bool sure;                 // there is a slot for every long cell of this trace
+  // how far a cell's prefill times lie apart
+  const DevCfg* cfg; int32_t K; const double* ml; const double* tab; const double* gridpack;
+  const int32_t* jstart; double bucket_scale; int32_t n_tp_f, n_rho;
 };
 
 struct TickArgs {
@@ -61,6 +75,7 @@ struct TickArgs {
   const TickPlan* plan;    // [cells]
   const int32_t* top;      // [n_req]
   const int32_t* in;       // [n_req] input lengths of the trace sorted by tick (DYN_TP_RAW cells)
+  const uint32_t* pool;    // the tables of DYN_TP_TABLE cells
   const int32_t* tstart; const double* thr; bool single_point;   // threshold form of the bucket index
   bool any_two_rows;
   int32_t n_cu;               // compute units of the device (0: unknown)
@@ -74,7 +89,9 @@ struct TickArgs {
 struct TickWs {
   EvalWs fine;      // header, rec (as TickRec) and cstat are used; fine.part is where `plan` starts
   size_t plan, top, part, counters, deep_list, slow_list, list_cells, total;
-  int32_t n_wslot;
+  size_t slots, pool, all;   // after `total`: the long cells' slots and tables, and the end of that
+  int32_t n_wslot, n_slot;
+  uint32_t pool_words;
 };
 TickWs dyn_tick_ws_layout(int64_t n_req, int64_t coarse_cells, int32_t n_tick, int32_t K);
 

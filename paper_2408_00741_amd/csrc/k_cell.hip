@@ -604,7 +604,6 @@ constexpr int64_t kLongMean = 9000, kLongLeast = 20000;   // requests per cell, 
 constexpr int kLongBlocks = 512;                   // pieces of a whole trace, two blocks to a compute unit
 constexpr int64_t kLongShare = 32;                  // pieces of a mean cell that one copy of its counters takes
 constexpr int64_t kLongPiece = 4096;               // least requests of a piece: 16 a thread
-constexpr int kCoarseBins = 64 + 26 * 64;          // exponents 6 .. 31
 constexpr int kFineBins = 256;
 constexpr int kSlotsPerBlock = 8;                  // cleared by one block of long_prepare
 // words of the workspace: long cells, pieces; the cells [kBlockCells at most]; every slot's first piece and the end; the slots
@@ -621,17 +620,6 @@ struct LongArgs {
   int32_t n_cell, copies;  // cells (each may be long); slots of a cell, a power of two
   uint32_t* work;
 };
-
-__device__ __forceinline__ int coarse_bin(uint32_t v) {
-  const int e = 31 - __builtin_clz(v | 32u);         // 5 below 64
-  return e < 6 ? (int)v : (e - 5) * 64 + (int)((v >> (e - 6)) & 63u);
-}
-// The least value of a bin, and how many bits the values in it differ by.
-__device__ __forceinline__ uint32_t coarse_low(int bin, int* bits) {
-  const int e = bin / 64 + 5;
-  *bits = bin < 64 ? 0 : e - 6;
-  return bin < 64 ? (uint32_t)bin : (64u + (uint32_t)(bin & 63)) << (e - 6);
-}
 
 // Block 0 of these lists the long cells and their pieces, the others clear the slots.  `s` is LDS scratch of kHistBins words.
 __device__ __forceinline__ void long_prepare(const LongArgs& a, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells, int part, uint32_t* s) {
@@ -879,39 +867,6 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_count_kernel(
   }
 }
 
-// The bin where the running count of `bins` counters (a thread holds PER consecutive ones, zeroes beyond) reaches `need`; *below = the
-// count before it.  Block-uniform; `s` is LDS scratch of kBlockWaves + 2 words.
-template <int PER>
-__device__ __forceinline__ int find_bin(const uint32_t (&k)[PER], int64_t need, uint32_t* s, int64_t* below) {
-  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = threadIdx.x / DYN_WAVE;
-  uint32_t mine = 0;                                 // a cell has fewer than 2^31 requests
-#pragma unroll
-  for (int q = 0; q < PER; ++q) mine += k[q];
-  uint32_t incl = mine;
-#pragma unroll
-  for (int d = 1; d < DYN_WAVE; d <<= 1) {
-    const uint32_t up = __shfl_up(incl, d, DYN_WAVE);
-    if (lane >= d) incl += up;
-  }
-  if (lane == DYN_WAVE - 1) s[wave] = incl;
-  __syncthreads();
-  uint32_t run = incl - mine;
-  for (int w = 0; w < wave; ++w) run += s[w];
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    if ((int64_t)run < need && need <= (int64_t)run + k[q]) {   // one thread, one bin
-      s[kBlockWaves] = (uint32_t)((int)threadIdx.x * PER + q);
-      s[kBlockWaves + 1] = run;
-    }
-    run += k[q];
-  }
-  __syncthreads();
-  const int bin = (int)s[kBlockWaves];
-  *below = s[kBlockWaves + 1];
-  __syncthreads();
-  return bin;
-}
-
 // Second pass: the bin that holds the rank, its parts counted, and the cell's outputs from the last block to be done with it.
 __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_rank_kernel(
     const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t cells, double window_s,
@@ -953,7 +908,7 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_rank_kernel(
     for (int q = 0; q < kPer; ++q) k[q] = s_bin[(int)threadIdx.x * kPer + q];
     int64_t below;
     int bits;
-    const uint32_t low = coarse_low(find_bin(k, rank, s_find, &below), &bits);
+    const uint32_t low = coarse_low(find_bin<kBlockWaves>(k, rank, s_find, &below), &bits);
     const int shift = bits > 8 ? bits - 8 : 0;       // of a value in the bin to its part
     const uint32_t pieces = s_first[slot + 1] - s_first[slot];
     bool last = item == s_first[slot];
@@ -994,7 +949,7 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) void cell_long_rank_kernel(
           f[0] += y < a.copies ? x : 0u;
         }
         int64_t less;
-        const int part = find_bin(f, rank - below, s_find, &less);
+        const int part = find_bin<kBlockWaves>(f, rank - below, s_find, &less);
         r.p99 = low + ((uint32_t)part << shift);
         if (shift > 0) r.p99 = rank_by_group<U, kBlockWaves>(in, beg, m, shift, r.p99 >> shift, rank - below - less, s_bin, s_xch);
       }

@@ -10,6 +10,8 @@
 // The request stream is read once, independent of the configurations:
 //   tick_tight_kernel, tick_tight_block_kernel  the cells whose percentile is settled without lists (below), and the lists
 //                      of long cells and of few ones;
+//   long_count, long_rank   cells of more than 4096 requests, a block for every piece of a tick (at the head of tick_cell_kernel
+//                      and of tick_deep_kernel, so that a trace without such cells pays for no launch)
 //   tick_cell_kernel   of the cells left, per cell every tick's load, its min(j, count) largest input lengths in
 //                      descending order (j <= 64: kept sorted in a wave's lanes) and the cell's
 //                      j-th largest input length x_j; what the later kernels do with the cell;
@@ -38,6 +40,7 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kFastDepth = DYN_TICK_FAST;
 constexpr int kDeepCap = DYN_TICK_DEPTH;     // largest j, and the largest tick the deep-cell kernel sorts in one go
 constexpr int kDeepBlocks = 512;
+constexpr int kListBlocks = 2048;            // of the cell kernel: eight to a compute unit; with a wave for every cell of a day the empty ones took 10 us
 constexpr int kGeneralBlocks = 1024;          // grid of the general kernel when the device cannot be asked what fits
 constexpr int kListCap = 2048;               // list entries of one cell the general kernel stages in LDS
 constexpr int kStripBytes = 32 * 1024;       // per-tick values of a block's configurations in the general kernel
@@ -51,6 +54,8 @@ __global__ void tick_init_kernel(uint32_t* counters) {
   counters[1] = 0u;
   counters[2] = 0u;
   counters[3] = 0u;
+  counters[4] = 0u;
+  counters[5] = 0u;
 }
 
 // How the TBT percentile of a cell can be found (lane q holds tick q's request count, 0 beyond the ticks): from the
@@ -98,6 +103,12 @@ struct TightCell {
   uint32_t need;      // the rank from the top
   bool walk;          // the rank is within reach of the walk's four ticks from one end
 };
+enum Settled { kNotTaken, kSettled, kBoundFails, kListed };   // kBoundFails: token sums and x_j are known, the ticks' lists are needed; kListed: those are written too
+constexpr int kListedDepth = 4;                // largest j whose lists tight_cell takes out of its registers
+constexpr int kListedRegs = 16;                // and how many of those at most: more would spill
+
+// The bound of a cell: of its class, except that a cell whose requests are all of one tick has one prefill time.
+__device__ __forceinline__ float cell_theta(float theta, int32_t cnt_l) { return __popcll(__ballot(cnt_l > 0)) <= 1 ? 1.0f : theta; }
 #define DYN_TIGHT_FROM_BELOW 0x80000000u
 
 // The up to four smallest positive per-tick counts of a wave (e_l: lane q holds tick q's count, 0 elsewhere), ascending,
@@ -129,10 +140,10 @@ __device__ __forceinline__ bool tight_place(int need, int n_eq, int npos, uint32
   return false;
 }
 
-template <int P>   // P registers = 2P rows
-__device__ __forceinline__ bool tight_cell(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg_l,
-                                           int32_t cnt_l, int T, int rpt, int m, int rank, float theta, int lane,
-                                           TightCell* res) {
+template <int P, bool LISTS>   // P registers = 2P rows; LISTS: cells with short lists are listed here
+__device__ __forceinline__ Settled tight_cell(const int32_t* __restrict__ in, const int32_t* __restrict__ out, int64_t beg_l,
+                                              int32_t cnt_l, int T, int rpt, int m, int rank, float theta, int lane,
+                                              int32_t* __restrict__ list, TightCell* res) {
   uint32_t v[P];
   uint32_t orv = 0, lmax = 0, lmax2 = 0, tok_acc = 0, tok_l = 0;
   constexpr int CH = P < 4 ? P : 4;      // registers per round: up to 8 + 8 loads in flight
@@ -180,9 +191,9 @@ __device__ __forceinline__ bool tight_cell(const int32_t* __restrict__ in, const
                    "+v"(v[p0 + 2]), "+v"(v[p0 + 3])::"memory");
   }
   orv = wave_or_u32(orv);
-  if (orv >= (1u << 16)) return false;   // wave-uniform
+  if (orv >= (1u << 16)) return kNotTaken;   // wave-uniform
   const uint32_t top = wave_max_u32(max(lmax, lmax2));
-  if (top == 0xFFFFu) return false;      // the padding value itself; the search's candidates (up to top + 1) must fit 16 bits
+  if (top == 0xFFFFu) return kNotTaken;  // the padding value itself; the search's candidates (up to top + 1) must fit 16 bits
   uint32_t xj = top;
   const int j = m - rank + 1;
   if (rank != m) {
@@ -210,7 +221,61 @@ __device__ __forceinline__ bool tight_cell(const int32_t* __restrict__ in, const
   }
   // the bound: theta * (x_j + 1) > x_j, with theta below the true ratio by 2^-21 at least (so that no rounding of the
   // scaled lengths can turn the order around)
-  if (!((double)theta * ((double)xj + 1.0) > (double)xj)) return false;
+  res->tok_l = tok_l;
+  res->xj = xj;
+  if (!((double)theta * ((double)xj + 1.0) > (double)xj)) {
+    if (!LISTS || P > kListedRegs || j > kListedDepth) return kBoundFails;
+    // The lists of a cell with few places in them, from the registers: a lane keeps the largest lengths of its tick in
+    // order, and at the tick's end the wave takes the largest of all lanes j times.  As a launch of their own these lists cost
+    // as much as this kernel, which had read the same requests (11 000 cells of 9 and 24 requests: 107 and 122 us).
+    if constexpr (LISTS && P <= kListedRegs) {
+    int32_t best[kListedDepth], take[kListedDepth];
+#pragma unroll
+    for (int p = 0; p < kListedDepth; ++p) { best[p] = -1; take[p] = -1; }
+    q = 0; r = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int32_t x = (int32_t)(h ? v[i] >> 16 : v[i] & 0xFFFFu);
+        x = x == 0xFFFF ? -1 : x;        // padding
+        if (j == 1) best[0] = max(best[0], x);   // wave-uniform
+        else {
+#pragma unroll
+          for (int p = 0; p < kListedDepth; ++p) {
+            const int32_t hi = max(best[p], x);
+            x = min(best[p], x);
+            best[p] = hi;
+          }
+        }
+        if (++r == rpt) {
+#pragma unroll
+          for (int p = 0; p < kListedDepth; ++p) {
+            if (p < j && q < T) {        // wave-uniform
+              const int32_t mx = wave_max_i32(best[0]);
+              if (lane == q) take[p] = mx;
+              if (j > 1) {
+                const uint64_t who = __ballot(best[0] == mx);
+                if (lane == __builtin_ctzll(who)) {
+#pragma unroll
+                  for (int u = 0; u + 1 < kListedDepth; ++u) best[u] = best[u + 1];
+                  best[kListedDepth - 1] = -1;
+                }
+              }
+            }
+          }
+#pragma unroll
+          for (int p = 0; p < kListedDepth; ++p) best[p] = -1;
+          r = 0; ++q;
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < kListedDepth; ++p)
+      if (p < j && p < cnt_l) list[beg_l + p] = take[p];
+    }
+    return kListed;
+  }
   // longer requests, and per tick the requests of length x_j.  The padding (0xFFFF in every slot beyond a tick's
   // requests) counts as longer: it is taken off afterwards.
   int n_gt = -(2 * P * DYN_WAVE - m), n_eq = 0, eq_acc = 0;
@@ -244,13 +309,27 @@ __device__ __forceinline__ bool tight_cell(const int32_t* __restrict__ in, const
     place = (uint32_t)(n_eq - need + 1) | DYN_TIGHT_FROM_BELOW;
   }
   res->need = (uint32_t)need;
-  res->tok_l = tok_l;
   res->eq_l = eq_l;
-  res->xj = xj;
   res->place = place;
-  return true;
+  return kSettled;
 }
 
+// A long cell goes to the blocks that share it without being read first where its bound fails for any x_j of 50 or more, or where a
+// wave of its block would hold more than 64 rows.  Measured (us of the call; a block per cell, shared): 60 cells of 65 000 requests and
+// 12 ticks 140, 117; 288 of 13 900 and 30 ticks 254, 209; 12 of 4700 and 30 ticks (at most 24 rows) 96, 117.
+constexpr int kLongRows = 64;
+__device__ __forceinline__ bool long_at_once(const TickCellArgs& a, int64_t m, int g, int32_t cnt_l, int rows) {
+  if (!a.sure || m <= DYN_TICK_LONG) return false;   // most cells, before the class's bound is there
+  return rows > kLongRows || cell_theta(a.theta[g], cnt_l) < 0.98f;
+}
+
+// An entry of list_cells: the cell, with DYN_LIST_SKIP set for one that the block kernel leaves to tick_cell_kernel unseen (fewer than 2^30 cells).
+#define DYN_LIST_DONE 0xFFFFFFFFu
+#define DYN_LIST_SKIP 0x80000000u
+
+// LISTS: for profiles whose prefill times depend on the load; the other form is smaller (ticks of a day 79 against 87 us, 8000 cells of
+// 11 requests 8.8 against 12.7).
+template <bool LISTS>
 __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(6, 8))) void tick_tight_kernel(TickCellArgs a) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
@@ -281,22 +360,26 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
   TightCell tc;
   tc.tok_l = 0; tc.eq_l = 0; tc.xj = 0; tc.place = 0; tc.need = 0; tc.walk = true;
   uint32_t flags = 0;
-  bool done = m_cell == 0;                       // an empty cell: loads 0, nothing else
-  if (!done) {
+  Settled done = m_cell == 0 ? kSettled : kNotTaken;   // an empty cell: loads 0, nothing else
+  if (m_cell > 0) {
     flags = tbt_route(cnt_l, j64, lane);
     const int rpt = ((int)wave_max_u32((uint32_t)cnt_l) + DYN_WAVE - 1) / DYN_WAVE;   // rows per tick
     const int rows = T * rpt;
     // with few cells on the whole device a cell of many rows is quicker with a block's waves: it goes on the list
-    if (rows <= 128 && !(a.few_cells && rows > 8)) {
-      const float theta = a.theta[g];
+    if (rows <= 128 && !(a.few_cells && rows > 8) && !long_at_once(a, m_cell, g, cnt_l, 0)) {
+      const float theta = cell_theta(a.theta[g], cnt_l);
       const int m = (int)m_cell, rk = (int)rank;
-      if (rows <= 4) done = tight_cell<2>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      else if (rows <= 8) done = tight_cell<4>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      else if (rows <= 16) done = tight_cell<8>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      else if (rows <= 32) done = tight_cell<16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      else if (rows <= 64) done = tight_cell<32>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      else done = tight_cell<64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, &tc);
-      if (done) {
+      if (rows <= 4) done = tight_cell<2, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      else if (rows <= 8) done = tight_cell<4, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      else if (rows <= 16) done = tight_cell<8, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      else if (rows <= 32) done = tight_cell<16, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      else if (rows <= 64) done = tight_cell<32, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      else done = tight_cell<64, LISTS>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, a.top, &tc);
+      if (done == kListed) {                     // j <= 4: any four non-empty ticks hold as many requests, so the walk takes it
+        tc.eq_l = (uint32_t)beg_l;               // where the tick's list is (n_req < 2^31)
+        if (lane == 0) atomicAdd(&a.counters[3], 1u);
+      }
+      if (done == kSettled) {
         flags |= DYN_TP_TIGHT;
         // the walk keeps four ticks and finds the TBT percentile from the largest tick TBT or the four largest
         if (!tc.walk || !(flags & (DYN_TP_DENSE | DYN_TP_SMALL))) {
@@ -306,8 +389,9 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
       }
     }
   }
-  if (!done) {                                   // the kernel that builds per-tick lists writes everything about this cell
-    if (lane == 0) a.list_cells[atomicAdd(&a.counters[2], 1u)] = (uint32_t)c;
+  if (done != kSettled && done != kListed) {     // the kernel that builds per-tick lists writes everything about this cell
+    const bool skip = done == kBoundFails && !a.few_cells && j64 <= DYN_TICK_WAVE;   // the next kernel would find out the same and leave it
+    if (lane == 0) a.list_cells[atomicAdd(&a.counters[2], 1u)] = (uint32_t)c | (skip ? DYN_LIST_SKIP : 0u);
     return;
   }
   if (lane < T) {
@@ -329,16 +413,414 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
   }
 }
 
+// ---- long cells: many blocks share a cell --------------------------------------------------------
+// A block streams a cell at about 16 GB/s, and sorts a tick's lengths in hundreds of barriers; few cells of many requests left the
+// device idle for milliseconds.  Here a cell's ticks are cut into pieces, a block each, and nothing is sorted:
+//   long_count  token sums per tick, and the cell's lengths counted by exponent and six bits (coarse_bin).  The cell's last block
+//               finds the bin that holds x_j, how far apart the prefill times of its ticks lie under any configuration (theta, from
+//               the least and the largest tick load), and so which lengths can decide: those of the bin where
+//               theta * (x + 1) > x (as above, the ties at x_j settle the cell), else those from theta * bin to bin / theta;
+//   long_rank   every such length counted per tick.  The cell's last block turns the counts into "how many are at least so
+//               long", reads x_j off them, and the ties or the tables are the general kernel's and the walk's.
+// Cells it cannot take (lengths of 2^16 and more at the rank, negative token counts, a theta that leaves more than kLongRange lengths, no
+// room in the pool) go to the lists as before.  Bound: two reads of the lengths and the two launches.
+constexpr int kLongBlocks = 1024;              // at most: four to a compute unit
+constexpr int64_t kLongPiece = 4096;           // requests of a piece, about
+constexpr int kLongRange = 4096;               // lengths of a table
+// words of a slot: the coarse counts, per tick the token sum (64 bits) and the OR of the token counts, then
+constexpr int kSlotSum = kCoarseBins, kSlotOr = kSlotSum + 2 * DYN_TICK_MAX, kSlotCell = kSlotOr + DYN_TICK_MAX, kSlotDone = kSlotCell + 1,
+              kSlotDone2 = kSlotCell + 2, kSlotFrom = kSlotCell + 3, kSlotN = kSlotCell + 4, kSlotLow = kSlotCell + 5, kSlotBits = kSlotCell + 6,
+              kSlotTheta = kSlotCell + 7, kSlotPool = kSlotCell + 8;   // kSlotN: lengths counted, 0: the cell went to the lists
+static_assert(kSlotPool < DYN_TICK_SLOT_WORDS && kSlotSum % 2 == 0 && kSlotCell % 4 == 0, "the slot");
+constexpr int kLongPer = (kCoarseBins + 255) / 256;
+constexpr int kLongWords = kLongPer * 256 + 64;   // LDS of long_count
+static_assert(kLongWords >= kWavesPerBlock * DYN_WAVE && kLongRange + 1 + 520 + 64 <= kDeepCap, "LDS");
+static_assert(kWavesPerBlock * DYN_WAVE == 256, "blocks of 256 threads");
+
+// Pieces of a tick, so that the cells' pieces keep the device busy and are not too small.
+__device__ __forceinline__ int long_split(const TickCellArgs& a, int n_long) {
+  const int64_t units = (int64_t)n_long * a.n_tick;
+  const int64_t want = a.n_req / (units * kLongPiece) + 1, most = 2 * kLongBlocks / units;
+  return (int)max((int64_t)1, min(want, most));
+}
+__host__ __device__ __forceinline__ int long_blocks(const TickCellArgs& a) {   // no more than there can be pieces
+  const int64_t most = a.n_req / kLongPiece + (int64_t)a.n_slot * a.n_tick;
+  return a.n_slot > 0 ? (int)(most < kLongBlocks ? most : kLongBlocks) : 0;
+}
+struct LongUnit {
+  int slot, q;
+  int64_t c, beg;    // the cell; first request of the piece
+  int n;             // its requests
+};
+__device__ __forceinline__ LongUnit long_unit(const TickCellArgs& a, uint32_t unit, int split) {
+  LongUnit u;
+  const uint32_t per = (uint32_t)(a.n_tick * split);
+  u.slot = (int)(unit / per);
+  const uint32_t in_cell = unit - (uint32_t)u.slot * per, s = in_cell % (uint32_t)split;
+  u.q = (int)(in_cell / (uint32_t)split);
+  u.c = a.slots[(size_t)u.slot * DYN_TICK_SLOT_WORDS + kSlotCell];
+  const int64_t f = ((u.c / a.G) * a.n_tick + u.q) * a.G + u.c % a.G;
+  const int64_t b = a.fine_off[f], e = a.fine_off[f + 1];
+  const int64_t cnt = (b < 0 || e < b || e > a.n_req) ? 0 : e - b;   // such a tick is treated as empty
+  u.beg = b + cnt * s / split;
+  u.n = (int)(cnt * (s + 1) / split - cnt * s / split);
+  return u;
+}
+__device__ __forceinline__ uint32_t seen(const uint32_t* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Adds at the device's coherence point; the old value comes back, so a block that has waited for it knows that the sum is there.
+__device__ __forceinline__ uint32_t add_seen(uint32_t* at, uint32_t v) { return __hip_atomic_fetch_add(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// A cell's ticks in a wave's lanes, as in the kernels above.
+struct CellTicks {
+  int64_t beg_l, m, j, rank;
+  int32_t cnt_l;
+  uint32_t bad_l;
+};
+__device__ __forceinline__ CellTicks cell_ticks(const TickCellArgs& a, int64_t c, int lane) {
+  CellTicks t;
+  t.beg_l = 0; t.cnt_l = 0; t.bad_l = 0;
+  if (lane < a.n_tick) {
+    const int64_t f = ((c / a.G) * a.n_tick + lane) * a.G + c % a.G;
+    const int64_t b = a.fine_off[f], e = a.fine_off[f + 1];
+    if (b < 0 || e < b || e > a.n_req) t.bad_l = DYN_WS_BAD_OFFSETS;
+    else { t.beg_l = b; t.cnt_l = (int32_t)(e - b); }
+  }
+  t.m = (int64_t)wave_sum_u64((uint64_t)(uint32_t)t.cnt_l);
+  t.rank = (a.pct_num * t.m + a.pct_den - 1) / a.pct_den;
+  t.j = t.m > 0 ? t.m - t.rank + 1 : 0;
+  return t;
+}
+
+// This thread's part of: the least ratio (smallest / largest) of a configuration's prefill times at loads from lmin to lmax.  A row is
+// linear between its load points, so its extremes are at the ends or at the points between them.
+__device__ __forceinline__ float theta_between(const TickCellArgs& a, int g, double lmin, double lmax) {
+  const double* rg = a.gridpack + 1;             // the load points
+  const double top = rg[a.n_rho - 1];
+  const int R = a.n_rho;
+  float theta = 1.0f;
+#pragma unroll 1
+  for (int k = threadIdx.x; k < a.K; k += 256) {
+    const DevCfg cf = a.cfg[k];
+    const size_t row = (size_t)g * a.n_tp_f;
+    const bool two = cf.u != 0.0;
+    const double ml = two ? (1.0 - cf.u) * a.ml[row + cf.row_lo] + cf.u * a.ml[row + cf.row_hi] : a.ml[row + cf.row_lo];
+    const double *lo = a.tab + (row + cf.row_lo) * 3 * R, *hi = a.tab + (row + cf.row_hi) * 3 * R;
+    auto point = [&](int i) { return two ? (1.0 - cf.u) * lo[i] + cf.u * hi[i] : lo[i]; };
+    const double den = cf.nd * ml;
+    double mn = __builtin_inf(), mx = -__builtin_inf();
+    int from = 0;
+#pragma unroll 1
+    for (int e = 0; e < 2; ++e) {                // the lower end, the upper end and the points between them
+      const double rho = fmin((e ? lmax : lmin) / den, top);
+      int jj = a.jstart[(int)(fmax(rho, 0.0) * a.bucket_scale)];
+      while (jj > 0 && rg[jj] > rho) --jj;
+      while (jj < R - 2 && rg[jj + 1] <= rho) ++jj;
+      const double t = (rho - rg[jj]) / (rg[jj + 1] - rg[jj]);
+      double v = (1.0 - t) * point(jj) + t * point(jj + 1);
+      mn = fmin(mn, v);
+      mx = fmax(mx, v);
+#pragma unroll 1
+      for (int i = e ? from + 1 : jj + 1; i <= jj; ++i) {
+        v = point(i);
+        mn = fmin(mn, v);
+        mx = fmax(mx, v);
+      }
+      from = jj;
+    }
+    theta = fminf(theta, (mx > 0.0 && mn > 0.0) ? (float)(mn / mx) * 0.999999f : 0.0f);   // below mn / mx by 2^-21 at least
+  }
+  return theta;
+}
+
+// First pass, and what the cell's last block decides.  `s`: kLongWords words of LDS.
+__device__ __forceinline__ void long_count(const TickCellArgs& a, int n_share, uint32_t* s) {
+  const int n_long = (int)min(a.counters[4], (uint32_t)a.n_slot);   // complete: written by the kernel before this one
+  if (n_long == 0) return;
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE), tid = threadIdx.x;
+  const int T = a.n_tick, split = long_split(a, n_long);
+  const uint32_t n_unit = (uint32_t)(n_long * T * split);
+  uint32_t* s_x = s + kLongPer * 256;            // [64]
+  for (uint32_t unit = blockIdx.x; unit < n_unit; unit += n_share) {
+    const LongUnit u = long_unit(a, unit, split);
+    uint32_t* at = a.slots + (size_t)u.slot * DYN_TICK_SLOT_WORDS;
+    uint32_t old = 0;
+    if (u.n > 0) {                               // block-uniform
+#pragma unroll
+      for (int b = 0; b < kLongPer; ++b) s[b * 256 + tid] = 0u;
+      __syncthreads();
+      const int32_t *pi = a.in + u.beg, *po = a.out + u.beg;
+      uint64_t acc = 0;
+      uint32_t orv = 0;
+      constexpr int U = 8;
+      for (int i0 = 0; i0 < u.n; i0 += U * 256) {
+        int32_t x[U], y[U];
+#pragma unroll
+        for (int v = 0; v < U; ++v) {
+          const uint32_t i = (uint32_t)min(i0 + v * 256 + tid, u.n - 1);
+          x[v] = pi[i];
+          y[v] = po[i];
+        }
+#pragma unroll
+        for (int v = 0; v < U; ++v) {
+          const bool ok = i0 + v * 256 + tid < u.n;
+          acc += ok ? (uint64_t)((int64_t)x[v] + (int64_t)y[v]) : 0;
+          orv |= (uint32_t)(x[v] | y[v]);        // beyond the piece: its last request again
+          if (ok) atomicAdd(&s[coarse_bin((uint32_t)x[v])], 1u);
+        }
+      }
+      acc = wave_sum_u64(acc);
+      orv = wave_or_u32(orv);
+      if (lane == 0) {
+        old += (uint32_t)__hip_atomic_fetch_add((unsigned long long*)(at + kSlotSum) + u.q, (unsigned long long)acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        old += __hip_atomic_fetch_or(&at[kSlotOr + u.q], orv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int b = 0; b < kLongPer; ++b) {
+        const uint32_t k = b * 256 + tid < kCoarseBins ? s[b * 256 + tid] : 0u;
+        if (k) old += add_seen(&at[b * 256 + tid], k);
+      }
+    }
+    asm volatile("" ::"v"(old) : "memory");
+    __syncthreads();
+    if (tid == 0) s_x[0] = add_seen(&at[kSlotDone], 1u) + 1u == (uint32_t)(T * split) ? 1u : 0u;
+    __syncthreads();
+    const bool last = s_x[0] != 0u;
+    __syncthreads();
+    if (!last) continue;                         // block-uniform
+    // the cell's last block
+    const int64_t c = u.c;
+    const int g = (int)(c % a.G);
+    const CellTicks ct = cell_ticks(a, c, lane);
+#pragma unroll
+    for (int b = 0; b < kLongPer; ++b) s[b * 256 + tid] = b * 256 + tid < kCoarseBins ? seen(&at[b * 256 + tid]) : 0u;
+    uint64_t tok = 0;
+    uint32_t or_l = 0;
+    if (lane < T) {
+      tok = (uint64_t)seen(&at[kSlotSum + 2 * lane]) | ((uint64_t)seen(&at[kSlotSum + 2 * lane + 1]) << 32);
+      or_l = seen(&at[kSlotOr + lane]);
+    }
+    const double load = div_by((double)tok, a.tick_s, a.r_tick);
+    __syncthreads();
+    uint32_t k[kLongPer];
+#pragma unroll
+    for (int b = 0; b < kLongPer; ++b) k[b] = s[tid * kLongPer + b];
+    int64_t below;
+    int bits;
+    const uint32_t low = coarse_low(find_bin<kWavesPerBlock>(k, ct.rank, s_x, &below), &bits);
+    const uint32_t high = low + ((1u << bits) - 1u);
+    bool ok = low < 65536u && (wave_or_u32(or_l) >> 31) == 0u;   // wave-uniform, the same in every wave
+    float theta = cell_theta(a.theta[g], ct.cnt_l);
+    const bool by_class = (double)theta * ((double)high + 1.0) > (double)high;
+    if (!by_class) {                             // block-uniform: the loads of this cell
+      double lmin = ct.cnt_l > 0 ? load : __builtin_inf(), lmax = ct.cnt_l > 0 ? load : 0.0;
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) {
+        lmin = fmin(lmin, __shfl_xor(lmin, d, DYN_WAVE));
+        lmax = fmax(lmax, __shfl_xor(lmax, d, DYN_WAVE));
+      }
+      const uint32_t th = wave_min_u32(__float_as_uint(ok ? theta_between(a, g, lmin, lmax) : 0.0f));   // floats >= 0 order like their bits
+      if (lane == 0) s_x[wave] = th;
+      __syncthreads();
+      theta = __uint_as_float(min(min(s_x[0], s_x[1]), min(s_x[2], s_x[3])));
+      __syncthreads();
+    }
+    const bool tight = (double)theta * ((double)high + 1.0) > (double)high;
+    int from = (int)low, n = (int)(high - low) + 1;
+    if (ok && !tight) {
+      ok = theta > 0.25f;
+      if (ok) {
+        from = max(0, (int)((double)low * (double)theta) - 1);
+        n = (int)((double)high / (double)theta) + 3 - from;
+        ok = n <= kLongRange;
+      }
+    }
+    const uint32_t words = (uint32_t)(DYN_TICK_TABLE_HEAD + T * (n + 1) + 3) & ~3u;
+    uint32_t pool = 0;
+    if (ok) {                                    // block-uniform
+      if (tid == 0) s_x[4] = atomicAdd(&a.counters[5], words);
+      __syncthreads();
+      pool = s_x[4];
+      __syncthreads();
+      ok = pool <= a.pool_words && words <= a.pool_words - pool;
+    }
+    if (ok)
+      for (uint32_t i = tid; i < words / 4; i += 256) ((uint4*)(a.pool + pool))[i] = make_uint4(0u, 0u, 0u, 0u);
+    const bool raw = ct.j > DYN_TICK_DEPTH;
+    if (wave == 0 && lane < T) {
+      TickRec r;
+      r.load = load;
+      r.off = (uint32_t)ct.beg_l;
+      r.cnt = ct.cnt_l;
+      a.rec[c * T + lane] = r;
+      a.cstat[((c / a.G) * T + lane) * a.G + g] = (uint8_t)(ct.bad_l | (or_l >> 31 ? DYN_WS_BAD_REQUEST : 0u));
+    }
+    const uint32_t route = tbt_route(ct.cnt_l, ct.j, lane);
+    if (tid == 0) {
+      at[kSlotFrom] = (uint32_t)from;
+      at[kSlotN] = ok ? (uint32_t)n : 0u;
+      at[kSlotLow] = low;
+      at[kSlotBits] = (uint32_t)bits | (tight ? 0x100u : 0u);
+      at[kSlotTheta] = __float_as_uint(theta);
+      at[kSlotPool] = pool;
+      if (!ok) {                                 // lists, by one block
+        TickPlan p;
+        p.j = (int32_t)ct.j;
+        p.xj = 0;
+        p.flags = route | (raw ? DYN_TP_RAW : ct.j > DYN_TICK_WAVE ? DYN_TP_DEEP : 0u);
+        p.place = 0;
+        if (raw || !walks_with_lists(route, ct.j)) {
+          p.flags |= DYN_TP_GENERAL;
+          a.slow_list[atomicAdd(&a.counters[1], 1u)] = (uint32_t)c;
+        } else {
+          atomicAdd(&a.counters[3], 1u);
+        }
+        a.plan[c] = p;
+        a.deep_list[atomicAdd(&a.counters[0], 1u)] = (uint32_t)c;
+      }
+    }
+    __syncthreads();                             // LDS is reused by the next unit
+  }
+}
+
+// Second pass: the lengths from `from` on, counted per tick, and the plan from the cell's last block.  `s`: kDeepCap words of LDS.
+__device__ __forceinline__ void long_rank(const TickCellArgs& a, uint32_t* s) {
+  const int n_long = (int)min(a.counters[4], (uint32_t)a.n_slot);
+  if (n_long == 0) return;
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE), tid = threadIdx.x;
+  const int T = a.n_tick, split = long_split(a, n_long);
+  const uint32_t n_unit = (uint32_t)(n_long * T * split);
+  uint32_t* s_all = s + kLongRange + 1;          // [513] the cell's requests of at least every length of the bin
+  uint32_t* s_x = s_all + 520;
+  for (uint32_t unit = blockIdx.x; unit < n_unit; unit += gridDim.x) {
+    const LongUnit u = long_unit(a, unit, split);
+    uint32_t* at = a.slots + (size_t)u.slot * DYN_TICK_SLOT_WORDS;
+    const int from = (int)at[kSlotFrom], n = (int)at[kSlotN];
+    if (n == 0) continue;                        // block-uniform
+    const int stride = n + 1;
+    uint32_t* table = a.pool + at[kSlotPool] + DYN_TICK_TABLE_HEAD;
+    uint32_t old = 0;
+    if (u.n > 0) {
+      for (int i = tid; i <= n; i += 256) s[i] = 0u;
+      __syncthreads();
+      const int32_t* pi = a.in + u.beg;
+      constexpr int U = 8;
+      uint32_t above = 0;
+      for (int i0 = 0; i0 < u.n; i0 += U * 256) {
+        int32_t x[U];
+#pragma unroll
+        for (int v = 0; v < U; ++v) x[v] = pi[(uint32_t)min(i0 + v * 256 + tid, u.n - 1)];
+#pragma unroll
+        for (int v = 0; v < U; ++v) {
+          if (i0 + v * 256 + tid < u.n && x[v] >= from) {
+            if (x[v] - from < n) atomicAdd(&s[x[v] - from], 1u);
+            else ++above;
+          }
+        }
+      }
+      above = wave_sum_u32(above);
+      if (lane == 0 && above) atomicAdd(&s[n], above);
+      __syncthreads();
+      for (int i = tid; i <= n; i += 256)
+        if (s[i]) old += add_seen(&table[(size_t)u.q * stride + i], s[i]);
+    }
+    asm volatile("" ::"v"(old) : "memory");
+    __syncthreads();
+    if (tid == 0) s_x[0] = add_seen(&at[kSlotDone2], 1u) + 1u == (uint32_t)(T * split) ? 1u : 0u;
+    __syncthreads();
+    const bool last = s_x[0] != 0u;
+    __syncthreads();
+    if (!last) continue;                         // block-uniform
+    // the cell's last block: how many are at least so long, per tick (a wave each) and for the lengths of the bin in all
+    const int64_t c = u.c;
+    const int low = (int)at[kSlotLow], bits = (int)(at[kSlotBits] & 0xFFu), in_bin = 1 << bits;
+    const bool tight = (at[kSlotBits] & 0x100u) != 0u;
+    const CellTicks ct = cell_ticks(a, c, lane);
+    for (int i = tid; i <= in_bin; i += 256) s_all[i] = 0u;
+    __syncthreads();
+    for (int q = wave; q < T; q += kWavesPerBlock) {
+      uint32_t* row = table + (size_t)q * stride;
+      uint32_t more = 0;                         // of at least the length after the chunk
+      for (int top = (n / 512) * 512; top >= 0; top -= 512) {   // the last entry counts what is longer than the table's lengths
+        uint32_t x[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) x[v] = top + lane * 8 + v <= n ? seen(&row[top + lane * 8 + v]) : 0u;
+#pragma unroll
+        for (int v = 6; v >= 0; --v) x[v] += x[v + 1];
+        uint32_t after = x[0];                   // of this lane's entries and all after them
+#pragma unroll
+        for (int d = 1; d < DYN_WAVE; d <<= 1) {
+          const uint32_t o = __shfl_down(after, d, DYN_WAVE);
+          if (lane + d < DYN_WAVE) after += o;
+        }
+        const uint32_t rest = more + after - x[0];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          const int i = top + lane * 8 + v, b = from + i - low;
+          if (i <= n) {
+            row[i] = x[v] + rest;
+            if (b >= 0 && b <= in_bin) atomicAdd(&s_all[b], x[v] + rest);
+          }
+        }
+        more += (uint32_t)__builtin_amdgcn_readlane((int)after, 0);
+      }
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (tid == 0) s_x[0] = 0u;
+    __syncthreads();
+    for (int b = tid; b < in_bin; b += 256)      // the largest length that j requests reach: exactly one, the counts descend
+      if (s_all[b] >= (uint32_t)ct.j && (b + 1 == in_bin || s_all[b + 1] < (uint32_t)ct.j)) s_x[0] = (uint32_t)b;
+    __syncthreads();
+    const int b = (int)s_x[0], xj = low + b;
+    const int n_gt = (int)s_all[b + 1], n_eq = (int)s_all[b] - n_gt, need = (int)ct.j - n_gt;
+    const uint32_t* row = table + (size_t)min(lane, T - 1) * stride + (xj - from);
+    const uint32_t eq_l = lane < T && ct.cnt_l > 0 ? row[0] - row[1] : 0u;
+    uint32_t flags = tbt_route(ct.cnt_l, ct.j, lane), place;
+    if (tight) {
+      uint32_t m4[4];
+      const int npos = smallest_four(eq_l, lane, m4);
+      const uint64_t s4 = npos >= 4 ? (uint64_t)m4[0] + m4[1] + m4[2] + m4[3] : 0u;
+      flags |= DYN_TP_TIGHT;
+      if (!tight_place(need, n_eq, npos, (uint32_t)min(s4, (uint64_t)0xFFFFFFFFu), &place) || !(flags & (DYN_TP_DENSE | DYN_TP_SMALL))) {
+        flags |= DYN_TP_GENERAL;
+        place = (uint32_t)need;
+      }
+    } else {
+      flags |= DYN_TP_TABLE | DYN_TP_GENERAL;
+      place = at[kSlotPool];
+    }
+    if (wave == 0 && tight && lane < T) a.rec[c * T + lane].off = eq_l;
+    if (tid == 0) {
+      if (!tight) {                              // with x_j known fewer lengths can decide
+        const double theta = (double)__uint_as_float(at[kSlotTheta]);
+        const int lo = max(from, (int)((double)xj * theta) - 1), hi = min(from + n - 1, (int)((double)xj / theta) + 2);
+        table[-DYN_TICK_TABLE_HEAD] = (uint32_t)lo;
+        table[-DYN_TICK_TABLE_HEAD + 1] = (uint32_t)(hi - lo + 1);
+        table[-DYN_TICK_TABLE_HEAD + 2] = (uint32_t)stride;
+        table[-DYN_TICK_TABLE_HEAD + 3] = (uint32_t)(lo - from);
+      }
+      TickPlan p;
+      p.j = (int32_t)ct.j;
+      p.xj = xj;
+      p.flags = flags;
+      p.place = place;
+      a.plan[c] = p;
+      if (flags & DYN_TP_GENERAL) a.slow_list[atomicAdd(&a.counters[1], 1u)] = (uint32_t)c;
+    }
+    __syncthreads();                             // LDS is reused by the next unit
+  }
+}
+
+
 // The same for the listed cells whose ticks do not fit one wave's registers: a block per cell, wave w takes the ticks
 // w, w + WAVES, ...; x_j by the bit-wise search with the waves' counts added up through LDS (one barrier per bit).  A cell
 // it settles is taken off the list (its entry becomes DYN_LIST_DONE).
-#define DYN_LIST_DONE 0xFFFFFFFFu
 constexpr int kTightWaves = 4, kTightManyWaves = 8;   // of a block: dyn_launch_tick_cell says where the line lies
 constexpr int kTightUnits = 4096;              // waves that the device holds at once (registers)
 
-enum BlockCell { kNotTaken, kSettled, kBoundFails };   // kBoundFails: token sums and x_j are known, the ticks' lists are needed
 template <int WAVES, int P>   // P registers = 2P rows per wave
-__device__ __forceinline__ BlockCell tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
+__device__ __forceinline__ Settled tight_cell_block(const int32_t* __restrict__ in, const int32_t* __restrict__ out,
                                                  int64_t beg_l, int32_t cnt_l, int T, int rpt, int m, int rank, float theta,
                                                  int lane, int wave, uint32_t* s_x /* [2][WAVES] */,
                                                  uint32_t* s_m /* [4 * WAVES] */, TightCell* res) {
@@ -562,7 +1044,9 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
   const int T = a.n_tick, G = a.G;
   const uint32_t n_item = a.counters[2];         // complete: written by the kernel before this one
   for (uint32_t item = blockIdx.x; item < n_item; item += gridDim.x) {
-    const int64_t c = a.list_cells[item];
+    const uint32_t entry = a.list_cells[item];
+    if (entry & DYN_LIST_SKIP) continue;         // block-uniform
+    const int64_t c = entry;
     const int64_t w = c / G;
     const int g = (int)(c % G);
     const int64_t f0 = (w * T) * G + g;
@@ -582,9 +1066,9 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
     const int rows = ((T + WAVES - 1) / WAVES) * rpt;   // rows of the wave with most ticks
     TightCell tc;
     tc.tok_l = 0; tc.eq_l = 0; tc.xj = 0; tc.place = 0; tc.need = 0; tc.walk = true;
-    BlockCell done = kNotTaken;                  // block-uniform from here on
-    if (m_cell > 0 && m_cell < (1 << 24) && rows <= 128) {
-      const float theta = a.theta[g];
+    Settled done = kNotTaken;                    // block-uniform from here on
+    if (m_cell > 0 && m_cell < (1 << 24) && rows <= 128 && !long_at_once(a, m_cell, g, cnt_l, rows)) {
+      const float theta = cell_theta(a.theta[g], cnt_l);
       const int m = (int)m_cell, rk = (int)rank;
       if (rows <= 16) done = tight_cell_block<WAVES, 8>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
       else if (rows <= 32) done = tight_cell_block<WAVES, 16>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
@@ -592,6 +1076,19 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
       else done = tight_cell_block<WAVES, 64>(a.in, a.out, beg_l, cnt_l, T, rpt, m, rk, theta, lane, wave, s_x, s_m, &tc);
     }
     __syncthreads();                             // s_x is reused by the next item
+    if (done != kSettled && m_cell > DYN_TICK_LONG && a.n_slot > 0) {   // block-uniform: to the blocks that share it, if a slot is left
+      if (threadIdx.x == 0) s_x[0] = atomicAdd(&a.counters[4], 1u);
+      __syncthreads();
+      const uint32_t slot = s_x[0];
+      __syncthreads();
+      if (slot < (uint32_t)a.n_slot) {
+        uint4* at = (uint4*)(a.slots + (size_t)slot * DYN_TICK_SLOT_WORDS);
+        for (int i = threadIdx.x; i < DYN_TICK_SLOT_WORDS / 4; i += WAVES * DYN_WAVE)
+          at[i] = make_uint4(i == kSlotCell / 4 ? (uint32_t)c : 0u, 0u, 0u, 0u);
+        if (threadIdx.x == 0) a.list_cells[item] = DYN_LIST_DONE;
+        continue;
+      }
+    }
     if (done == kNotTaken) continue;
     uint32_t flags = tbt_route(cnt_l, j64, lane);
     if (done == kSettled) {
@@ -647,15 +1144,21 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
 // (kept values win ties against new ones, lower lanes against higher ones), and the merged
 // order is written through a 64-word LDS buffer.  A second list, merged with every finished
 // tick's list, holds the j largest lengths of the whole cell: its last entry is x_j.
-__global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_cell_kernel(TickCellArgs a) {
-  __shared__ int32_t s_buf[kWavesPerBlock][DYN_WAVE];
+__global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(6, 8))) void tick_cell_kernel(TickCellArgs a) {
+  __shared__ uint32_t s_long[kLongWords];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int T = a.n_tick, G = a.G;
-  const int64_t item = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-  if (item >= (int64_t)a.counters[2]) return;   // complete: written by the kernel before this one
-  if (a.list_cells[item] == DYN_LIST_DONE) return;   // settled by the kernel before this one
-  const int64_t c = a.list_cells[item];
+  const int n_share = long_blocks(a);
+  if ((int)blockIdx.x < n_share) {              // block-uniform: the first blocks share the long cells
+    long_count(a, n_share, s_long);
+    return;
+  }
+  int32_t (*s_buf)[DYN_WAVE] = (int32_t (*)[DYN_WAVE])s_long;
+  const uint32_t n_item = a.counters[2];        // complete: written by the kernel before this one
+  for (uint32_t item = (blockIdx.x - n_share) * kWavesPerBlock + wave; item < n_item; item += (gridDim.x - n_share) * kWavesPerBlock) {
+  if (a.list_cells[item] == DYN_LIST_DONE) continue;   // settled by the kernel before this one
+  const int64_t c = a.list_cells[item] & ~DYN_LIST_SKIP;
   const int64_t w = c / G;
   const int g = (int)(c % G);
   const int64_t f0 = (w * T) * G + g;           // fine cell of tick 0; tick q is q*G further
@@ -811,6 +1314,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) void tick_cell_kernel(Tic
     if (flags & DYN_TP_GENERAL) a.slow_list[atomicAdd(&a.counters[1], 1u)] = (uint32_t)c;
     else if (j64 > 0) atomicAdd(&a.counters[3], 1u);   // a cell the walk takes with its lists
   }
+  }
 }
 
 // ---- cells whose percentile lies more than 64 deep ------------------------------------------------
@@ -826,6 +1330,7 @@ __global__ __launch_bounds__(256) void tick_deep_kernel(TickCellArgs a) {
   const int tid = threadIdx.x, lane = tid & (DYN_WAVE - 1), wave = tid / DYN_WAVE;
   const int T = a.n_tick;
   const uint32_t n_deep = a.counters[0];         // complete: written by the kernel before this one
+  long_rank(a, (uint32_t*)s_val);
   auto block_sum = [&](uint32_t v) -> uint32_t {
     const uint32_t ws = wave_sum_u32(v);
     __syncthreads();
@@ -1339,7 +1844,8 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
     const int xmin = (int)((double)pl.xj * theta);
     WalkOut o;
     if (pl.flags & DYN_TP_DENSE) {
-      if (j <= 4) o = walk_ticks<4, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      if (j == 1) o = walk_ticks<1, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      else if (j <= 4) o = walk_ticks<4, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
       else if (j <= 8) o = walk_ticks<8, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
       else o = walk_ticks<kFastDepth, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
     } else {
@@ -1458,7 +1964,8 @@ __device__ __forceinline__ double weighted_from_top(const double* strip, const i
 // lengths equal to x_j.  Otherwise the bracket is bisected: a probe value v is ranked in every tick's list
 // (binary search on the scaled entries), and either at least j scaled entries are >= v, then the least
 // of them is a new lower end, or fewer, then the largest one below v is a new upper end.  Both ends are
-// values of the lists from then on, so the search ends with the percentile itself.
+// values of the lists from then on, so the search ends with the percentile itself.  A cell with tables (DYN_TP_TABLE) is searched the same way
+// over all lengths, a probe ranked by one entry of every tick's table.
 // LDS: [load grid] [reciprocal spacings] [SINGLE: grid point per bucket] [strip NT x n_tick]
 //      [per tick: load] [per tick: count] [per tick: entries listed] [per tick: entries equal to x_j]
 //      [per tick: start of its list, then two words] [the cell's lists when they fit] [bucket index]
@@ -1495,6 +2002,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
     const int j = pl.j;
     const bool dense = (pl.flags & DYN_TP_DENSE) != 0;
     const bool tight = (pl.flags & DYN_TP_TIGHT) != 0;   // no lists: per tick the number of requests of length x_j, and the rank among them
+    const bool tabled = (pl.flags & DYN_TP_TABLE) != 0;  // no lists: how many requests are at least so long, per tick
     const bool raw = (pl.flags & DYN_TP_RAW) != 0;       // the lists are whole ticks; a tick marked DYN_TICK_PIECES is sorted in pieces of DYN_TICK_DEPTH
     const TickRec* rec = a.rec + cell * T;
     if (tid < DYN_WAVE) {                      // the first wave, a tick per lane: where each tick's list is read from
@@ -1503,7 +2011,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
       if (tid < T) r = rec[tid];
       const bool pieces = raw && (r.off & DYN_TICK_PIECES) != 0u;
       const uint32_t off = raw ? (r.off & ~DYN_TICK_PIECES) : r.off;
-      const int len = (tid < T && !tight) ? (raw ? r.cnt : min(r.cnt, j)) : 0;
+      const int len = (tid < T && !tight && !tabled) ? (raw ? r.cnt : min(r.cnt, j)) : 0;
       int incl = len;                          // inclusive prefix over the ticks
 #pragma unroll
       for (int d = 1; d < DYN_WAVE; d <<= 1) {
@@ -1541,8 +2049,28 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
       __syncthreads();
     }
     const int32_t* lists = staged ? s_lists : a.top;
-    if (tid < T && !tight && s_len[tid] < 0) s_neq[tid] = 0;
-    if (tid < T && !tight && s_len[tid] >= 0) {        // per tick: listed lengths above x_j and equal to it (the list is descending)
+    // the table of a tick: entry i counts its requests of at least t_from + i, 0 <= i <= t_n
+    const uint32_t* t_at = a.pool + (tabled ? pl.place : 0u);
+    int t_from = 0, t_n = 0, t_stride = 0;
+    if (tabled) {                              // block-uniform
+      t_from = (int)t_at[0];
+      t_n = (int)t_at[1];
+      t_stride = (int)t_at[2];
+      t_at += DYN_TICK_TABLE_HEAD + t_at[3];
+      if (T * (t_n + 1) <= kListCap) {
+        for (int i = tid; i < T * (t_n + 1); i += NT) s_lists[i] = (int32_t)t_at[(size_t)(i / (t_n + 1)) * t_stride + i % (t_n + 1)];
+        __syncthreads();
+        t_at = (const uint32_t*)s_lists;
+        t_stride = t_n + 1;
+      }
+      if (tid < T) {
+        const uint32_t* row = t_at + (size_t)tid * t_stride + (pl.xj - t_from);
+        s_neq[tid] = (int32_t)(row[0] - row[1]);
+        if (row[1]) atomicAdd(&s_lbase[T + 1], row[1]);
+      }
+    }
+    if (tid < T && !tight && !tabled && s_len[tid] < 0) s_neq[tid] = 0;
+    if (tid < T && !tight && !tabled && s_len[tid] >= 0) {        // per tick: listed lengths above x_j and equal to it (the list is descending)
       const int len = s_len[tid];
       const int32_t* lq = lists + s_lbase[tid];
       int l = 0, h = len;                      // first entry <= x_j
@@ -1623,7 +2151,18 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
         if (!(v > lo)) v = hi;
         int n_ge = 0;
         double a_min = __builtin_inf(), b_max = -__builtin_inf();
-        for (int q = 0; q < T; ++q) {
+        if (tabled) {                          // the ends are lengths, held by a request or not: the last one standing is
+          for (int q = 0; q < T; ++q) {
+            if (s_cnt[q] == 0) continue;
+            const double pf = s_strip[q * NT + tid];   // above 0, like theta
+            int x = (int)(v / pf);             // the least length with x * pf >= v
+            while ((double)x * pf < v) ++x;
+            while (x > 0 && (double)(x - 1) * pf >= v) --x;
+            n_ge += (int)t_at[(size_t)q * t_stride + min(max(x - t_from, 0), t_n)];
+            a_min = min_num(a_min, (double)x * pf);
+            b_max = max_num(b_max, (double)(x - 1) * pf);
+          }
+        } else for (int q = 0; q < T; ++q) {
           int len = s_len[q];
           if (len == 0) continue;
           const double pf = s_strip[q * NT + tid];
@@ -1709,6 +2248,7 @@ void launch_general(const TickArgs& a, size_t lds, hipStream_t s) {
   if (a.n_cu > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tick_general_kernel<SINGLE, TWO>, nt, lds) == hipSuccess &&
       per_cu > 0)
     blocks = per_cu * a.n_cu;
+  blocks = (int)std::min<int64_t>(blocks, (int64_t)a.s.n_window * a.s.G * a.s.n_tile);
   hipLaunchKernelGGL((tick_general_kernel<SINGLE, TWO>), dim3(blocks), dim3(nt), lds, s, a);
 }
 
@@ -1730,7 +2270,8 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   const int64_t blocks = (cells + kWavesPerBlock - 1) / kWavesPerBlock;
   DynTimed timed(DYN_K_TICK_TOP, s);
   hipLaunchKernelGGL(tick_init_kernel, dim3(1), dim3(1), 0, s, a.counters);
-  hipLaunchKernelGGL(tick_tight_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
+  if (a.flat) hipLaunchKernelGGL(tick_tight_kernel<false>, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
+  else hipLaunchKernelGGL(tick_tight_kernel<true>, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
   // Eight waves where that halves the rows a wave holds and the cells are long enough to share, or where cells are too long for
   // four; such a block (33 KB of LDS) waits beside kernels of other streams that fill the device, one of four finds its place.
   // Measured (us of the call; four waves, eight): 4 M requests, 12 500 cells of 30 ticks, prefill by load 988, 1113; 1500 cells of 1
@@ -1740,9 +2281,9 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   const int64_t mean = a.n_req / cells;
   const int64_t rows = (T + 3) / 4 * (mean * 5 / 4 / T / DYN_WAVE + 1);   // of a wave of four in a cell somewhat longer than the mean
   const bool many = T > 4 && ((mean > 1000 && 2 * ((T + 7) / 8) <= (T + 3) / 4) || rows > 128);
-  if (many) hipLaunchKernelGGL(tick_tight_block_kernel<kTightManyWaves>, dim3(kTightUnits / kTightManyWaves), dim3(kTightManyWaves * DYN_WAVE), 0, s, a);
-  else hipLaunchKernelGGL(tick_tight_block_kernel<kTightWaves>, dim3(kTightUnits / kTightWaves), dim3(kTightWaves * DYN_WAVE), 0, s, a);
-  hipLaunchKernelGGL(tick_cell_kernel, dim3((unsigned)blocks), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
+  if (many) hipLaunchKernelGGL(tick_tight_block_kernel<kTightManyWaves>, dim3((unsigned)std::min<int64_t>(cells, kTightUnits / kTightManyWaves)), dim3(kTightManyWaves * DYN_WAVE), 0, s, a);
+  else hipLaunchKernelGGL(tick_tight_block_kernel<kTightWaves>, dim3((unsigned)std::min<int64_t>(cells, kTightUnits / kTightWaves)), dim3(kTightWaves * DYN_WAVE), 0, s, a);
+  hipLaunchKernelGGL(tick_cell_kernel, dim3((unsigned)std::min<int64_t>(blocks, kListBlocks) + long_blocks(a)), dim3(kWavesPerBlock * DYN_WAVE), 0, s, a);
   hipLaunchKernelGGL(tick_deep_kernel, dim3(kDeepBlocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
