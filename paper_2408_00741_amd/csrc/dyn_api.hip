@@ -824,9 +824,6 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   a.tile_rows = p->d_tile_rows;
   a.slo_ttft = p->d_slo_ttft; a.slo_tbt = p->d_slo_tbt; a.budget = p->d_budget;
   a.rec = nullptr; a.n_window = n_window; a.window_s = t->window_s;
-  const int64_t cell_tiles = cells * p->n_tile;
-  // about 8192 blocks; beyond 16 windows a block gains nothing more from its staged rows (measured: 10 .. 20 alike)
-  a.win_per_block = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, (cell_tiles + 8191) / 8192));
   a.energy = out->energy_j; a.p99_ttft = out->p99_ttft_ms; a.p99_tbt = out->p99_tbt_ms; a.flags = out->flags;
   a.pw0 = p->d_pw0; a.idle_w = o->idle_cost_weight;
   a.part = (SelPart*)(base + w.part); a.n_wslot = w.n_wslot;

@@ -2288,12 +2288,21 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Windows a block of the evaluation kernel walks: as for the window-level kernel, less where the per-tick
-// records of that many windows would not fit beside the table rows.
-int32_t dyn_tick_win_per_block(const TickArgs& a, int32_t wanted) {
+// Windows a block of the evaluation kernels walks.  About 8192 blocks keep cells that differ apart from each other; beyond 16
+// windows a block gains nothing more from its staged rows (a day of 12 ticks: 10 .. 20 alike).  With few ticks a window is soon
+// walked (0.6 us a tick, the chain of one look-up) and the staging (3 us, and 0.12 for every value a thread stages) would be most of a
+// block's life: such blocks walk until it is 15 % of it, as long as the blocks fill three quarters of the device.  Measured (us of
+// the call; 8192 blocks, this): 8000 cells of 1 tick and 252 candidates 68, 47; 2800 of 5 ticks 55, 43; 2300 of 6 and 60 candidates 72,
+// 56; 10 800 of 6 and lists 259, 238.  Less again where the per-tick records would not fit beside the table rows.
+int32_t dyn_tick_win_per_block(const TickArgs& a) {
   const SpaceArgs& sa = a.s;
   const size_t tab = (size_t)sa.n_slot * DYN_SLOT_STRIDE(sa.n_rho) * sizeof(double);
-  int32_t wpb = wanted;
+  const int64_t cell_tiles = (int64_t)sa.n_window * sa.G * sa.n_tile;
+  const double stage = 3.0 + 0.12 * (double)sa.n_slot * (3 * sa.n_rho) / sa.tile;
+  const int64_t for_stage = (int64_t)(stage / (0.15 * 0.6 * a.n_tick)) + 1;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(20 * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 8192)));
+  const int64_t for_device = cell_tiles / std::max<int64_t>(1, per_cu * a.n_cu * 3 / 4);
+  int32_t wpb = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, std::max((cell_tiles + 8191) / 8192, std::min(for_stage, for_device))));
   while (wpb > 1 && tab + tick_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, wpb, a.single_point) > DYN_LDS_BUDGET) wpb /= 2;
   return wpb;
 }
@@ -2301,7 +2310,7 @@ int32_t dyn_tick_win_per_block(const TickArgs& a, int32_t wanted) {
 hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
   TickArgs a = a_in;
   SpaceArgs& sa = a.s;
-  sa.win_per_block = dyn_tick_win_per_block(a, sa.win_per_block);
+  sa.win_per_block = dyn_tick_win_per_block(a);
   const int n_chunk = (sa.n_window + sa.win_per_block - 1) / sa.win_per_block;
   const dim3 grid((unsigned)((size_t)n_chunk * sa.G * sa.n_tile)), block(sa.tile);
   const size_t tab = (size_t)sa.n_slot * DYN_SLOT_STRIDE(sa.n_rho) * sizeof(double);
