@@ -978,7 +978,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
 }
 
 namespace {
-struct PathWs { size_t layout, order, seg, transition, pred, kend, end_total, min_cost, min_k, exits, total; };
+struct PathWs { size_t layout, order, seg, transition, pred, kend, end_total, min_cost, min_k, exits, total, totals, near, wrong, all; };
 PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) {
   PathWs w;
   size_t off = 0;
@@ -994,13 +994,25 @@ PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) 
   w.min_k = off; off += align256(per_layout * sizeof(int32_t));
   w.exits = off; off += align256((size_t)G * dyn_path_runs(n_window) * DYN_PATH_STATES * sizeof(int32_t));
   w.total = off;
+  const size_t near = n_window >= DYN_PATH_NEAR_LEAST ? per_layout : 0;
+  w.totals = off; off += align256(near * sizeof(double));
+  w.near = off; off += align256(near * sizeof(uint64_t));
+  w.wrong = off; off += near ? align256(((size_t)G + 1) * sizeof(uint32_t)) : 0;
+  w.all = off;
   return w;
+}
+// The parts after `total`, at `more` (null: a workspace of the size without them, which still does).
+void path_near(PathArgs* a, char* more, const PathWs& w) {
+  const bool near = more && w.all > w.total;
+  a->totals = near ? (double*)(more + (w.totals - w.total)) : a->min_cost;
+  a->near = near ? (uint64_t*)(more + (w.near - w.total)) : nullptr;
+  a->wrong = near ? (uint32_t*)(more + (w.wrong - w.total)) : nullptr;
 }
 }  // namespace
 
 size_t dyn_select_path_workspace(int32_t n_window, int32_t n_class, int32_t n_config, int32_t n_layout) {
   if (n_window < 1 || n_class < 1 || n_config < 1 || n_layout < 1) return 0;
-  return path_ws_layout(n_window, n_class, n_config, n_layout).total;
+  return path_ws_layout(n_window, n_class, n_config, n_layout).all;
 }
 
 int dyn_select_path(dyn_profile* p, const dyn_space* space, const dyn_config* cfg, int32_t K, const dyn_objective* o,
@@ -1059,6 +1071,7 @@ int dyn_select_path(dyn_profile* p, const dyn_space* space, const dyn_config* cf
   a.order = p->d_path_order; a.seg_start = p->d_path_seg;
   a.pred = (int32_t*)(base + w.pred); a.kend = (int32_t*)(base + w.kend); a.end_total = (double*)(base + w.end_total);
   a.min_cost = (double*)(base + w.min_cost); a.min_k = (int32_t*)(base + w.min_k); a.exits = (int32_t*)(base + w.exits);
+  path_near(&a, workspace_bytes >= w.all ? base + w.total : nullptr, w);
   a.sel = out->sel; a.sel_energy = out->sel_energy_j; a.path_cost = out->path_cost;
   if (!hip_ok(dyn_launch_path(a, s), "path launch")) return DYN_E_DEVICE;
   if (!hip_ok(dyn_launch_window_totals(out->sel, out->sel_energy_j, n_window, p->G, out->window_energy_j,
@@ -1135,7 +1148,7 @@ HierWs hier_ws_layout(int64_t cells, int32_t n_tick, int32_t n_tp, int32_t n_lay
 size_t dyn_hierarchy_workspace(int32_t n_window, int32_t n_tick, int32_t n_class, int32_t n_layout) {
   if (n_window < 1 || n_tick < 1 || n_class < 1 || n_layout < 1) return 0;
   return hier_ws_layout((int64_t)n_window * n_class, n_tick, 64, n_layout).total +
-         path_ws_layout(n_window, n_class, n_layout, n_layout).total + align256(dyn_cell_many_bytes((int64_t)n_window * n_class * n_tick));
+         path_ws_layout(n_window, n_class, n_layout, n_layout).all + align256(dyn_cell_many_bytes((int64_t)n_window * n_class * n_tick));
 }
 
 int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view* tf, int32_t n_tick, const dyn_controllers* c,
@@ -1226,6 +1239,8 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     pa.order = p->d_ident; pa.seg_start = p->d_ident;
     pa.pred = (int32_t*)(pb + pw.pred); pa.kend = (int32_t*)(pb + pw.kend); pa.end_total = (double*)(pb + pw.end_total);
     pa.min_cost = (double*)(pb + pw.min_cost); pa.min_k = (int32_t*)(pb + pw.min_k); pa.exits = (int32_t*)(pb + pw.exits);
+    const size_t more = w.total + pw.total + align256(dyn_cell_many_bytes(fine_cells));
+    path_near(&pa, workspace_bytes >= more + (pw.all - pw.total) ? base + more : nullptr, pw);
     pa.sel = out->layout_sel; pa.sel_energy = (double*)(base + w.sel_energy); pa.path_cost = out->path_cost;
     if (!hip_ok(dyn_launch_path(pa, s), "path launch")) return DYN_E_DEVICE;
   }

@@ -313,9 +313,11 @@ __device__ __forceinline__ void add_sources(double v, const double (&t)[N], doub
 // times in a row on the one-day workload; nothing of the chip's rates applies.  Sources split over waves, their totals
 // by lane reads and the partial minima through LDS atomics: 0.41 us a window; sources read from LDS by every lane
 // (n_layout^2 values a window through the LDS port): 0.27 us; this, with 48 layouts: 0.22 us (596 to 323 us for the day).
-// min_cost[window][layout] is overwritten by the least total of the sequences that end there (+inf: none).
+// totals[window][layout] (which may be min_cost itself) takes the least total of the sequences that end there (+inf: none).
+// Where `near` is set only classes with wrong totals are walked (below).
 template <int LMAX>
 __global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
+  if (a.near && a.wrong[blockIdx.x] == 0u) return;           // block-uniform
   constexpr int SPL = LMAX / 4;                              // sources per row
   static_assert(LMAX % 16 == 0 && LMAX <= 64, "a row of 16 lanes broadcasts its sources");
   __shared__ double s_v[2][LMAX];                            // least totals of the window before, two buffers in turn
@@ -332,7 +334,8 @@ __global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
     const int ls = r * SPL + q;
     t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + d] : inf;   // layouts beyond NL never win
   }
-  double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);  // this destination in window w: col[w * step]
+  const double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);   // this destination in window w: col[w * step]
+  double* tot = a.totals + (size_t)g * NL + (on ? d : 0);
   const size_t step = (size_t)G * NL;
   // loaded by every lane, from the last window beyond the end: behind a branch the waits would take in later loads too
   auto cost = [&](int w) { return col[(size_t)min(w, NW - 1) * step]; };
@@ -371,17 +374,219 @@ __global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
         keep = r == i ? now : keep;
         lds_barrier();                                       // the window's only block barrier
       }
-      if (has) col[(size_t)w * step] = keep;
+      if (has) tot[(size_t)w * step] = keep;
     }
   }
 }
+
+// Many windows: the walk of a class in pieces.  What a sequence cost long ago moves all totals of a window alike, so which sources can be
+// the cheapest is known from a walk that starts a few windows before (path_near_kernel, a block for every piece of every class, the
+// step of path_chain_kernel): those whose sum is within 2^-30 of the least, a bit each.  path_sum_kernel then takes the totals from the
+// first window on: of the named sources only, nearly always one, so a step is a lane exchange and two additions.  path_pred_kernel, which
+// forms all sums anyway, compares: a total that is not what the recurrence says marks its class, and path_chain_kernel walks
+// that class as a whole (overheads so large that a choice of 16 windows ago still matters).  By induction over the windows the
+// totals are those of the whole walk to the last bit.
+// Bounds: the issue of NL^2 sums a window and the walk of 64 windows (45 us for the day of 25 classes and 48 layouts), then the latency of
+// a lane exchange and two additions, 0.09 us a window in place of 0.22 (134 and 325 us).  Measured (us of dyn_select_path; the whole
+// walk, this): the day 486, 335; 95 680 cells of 38 layouts and 1196 windows 556, 503; 517 windows of 64 layouts, most without requests, so
+// that many sources tie, 219, 172; 320 windows of 51 163, 138; 259 of 25 116, 120.
+template <int LMAX>
+__global__ __launch_bounds__(LMAX * 4) void path_near_kernel(PathArgs a) {
+  constexpr int SPL = LMAX / 4, kBefore = DYN_PATH_BEFORE;
+  static_assert(SPL <= 16, "a row's bits");
+  __shared__ double s_v[2][LMAX];
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const int r = lane >> 4, p = lane & 15, d = (int)(threadIdx.x / DYN_WAVE) * 16 + p;
+  const int src = r * SPL + min(p, SPL - 1);
+  const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.y;
+  const double inf = __builtin_inf();
+  const bool on = d < NL;
+  double t[SPL];
+#pragma unroll
+  for (int q = 0; q < SPL; ++q) {
+    const int ls = r * SPL + q;
+    t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + d] : inf;
+  }
+  const int w0 = (int)blockIdx.x * DYN_PATH_PIECE, w1 = min(NW, w0 + DYN_PATH_PIECE), wb = max(0, w0 - kBefore);
+  const double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);
+  const size_t step = (size_t)G * NL;
+  uint16_t* bits = (uint16_t*)(a.near + (size_t)g * NL + (on ? d : 0)) + r;   // of this row in window w: bits[w * step * 4]
+  constexpr int kAhead = 8;                                  // costs in flight, in registers of their own
+  double c[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) c[u] = col[(size_t)min(wb + u, NW - 1) * step];
+  if (r == 0) s_v[0][d] = inf;
+  __syncthreads();
+#pragma unroll 1
+  for (int wa = wb; wa < w1; wa += kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int w = wa + u;
+      const double cw = on && w < NW ? c[u] : inf;
+      c[u] = col[(size_t)min(w + kAhead, NW - 1) * step];
+      const double v = s_v[u & 1][src];
+      const bool alive = __ballot((int)(__double_as_longlong(v) >> 32) < 0x7FF00000) != 0;
+      double m[SPL], x[SPL];
+      add_sources<0, SPL>(v, t, m);
+#pragma unroll
+      for (int q = 0; q < SPL; ++q) x[q] = m[q];
+#pragma unroll
+      for (int k = 1; k < SPL; k *= 2)
+#pragma unroll
+        for (int q = 0; q + k < SPL; q += 2 * k) x[q] = __builtin_fmin(x[q], x[q + k]);
+      const double arrive = rows_min_f64(x[0]);
+      const double now = (!alive || !(cw < inf)) ? cw : arrive + cw;
+      if (r == 0) s_v[(u & 1) ^ 1][d] = now;
+      if (w >= w0 && w < w1) {                               // block-uniform
+        const double near = arrive + arrive * 0x1p-30;
+        uint32_t b = 0;
+#pragma unroll
+        for (int q = 0; q < SPL; ++q) b |= m[q] <= near ? 1u << q : 0u;
+        if (!(arrive < inf)) b = 0u;                         // no sequence arrives
+        if (on) bits[(size_t)w * step * 4] = (uint16_t)b;
+      }
+      lds_barrier();
+    }
+  }
+}
+
+// Source layout of a bit of `near`: a row's 16 bits hold the SPL sources of the row.
+__device__ __forceinline__ int near_source(uint64_t bits, int SPL, int NL) {
+  const int b = __builtin_ctzll(bits | (1ull << 63));
+  return min((b >> 4) * SPL + (b & 15), NL - 1);
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {       // of any lane
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(lane * 4, (int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(lane * 4, (int)(uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// A block per class.  Its first wave adds, lane = destination layout; the others fetch the next windows' costs and sources and look
+// the overheads up, everything that does not need the totals.  One wave alone waited for its loads (0.16 us a window), and a step of 50
+// instructions took 0.15: a step with one source everywhere has a path of its own.
+constexpr int kSumWindows = 16, kSumThreads = 256, kSumGroup = 8;
+constexpr int kSumRows = 2 * kSumWindows + kSumGroup;
+__global__ __launch_bounds__(kSumThreads) void path_sum_kernel(PathArgs a) {
+  extern __shared__ double smem[];
+  const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.x;
+  double* s_t = smem;                                        // [NL][NL]
+  double2* s_c = (double2*)(s_t + ((NL * NL + 1) & ~1));     // [2][kSumWindows][64] cost, overhead from the first source
+  uint64_t* s_r = (uint64_t*)(s_c + kSumRows * DYN_WAVE);    // the same: the sources after the first
+  int32_t* s_f = (int32_t*)(s_r + kSumRows * DYN_WAVE);      // the same: four times the first source, -4: none
+  __shared__ uint32_t s_odd[2];                              // a bit for every window where a destination has no source, or several, or that is beyond the last
+  const int SPL = (NL + 15) / 16 * 4;                        // sources of a row in path_near_kernel
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  const double inf = __builtin_inf();
+  const size_t step = (size_t)G * NL;
+  for (int i = threadIdx.x; i < NL * NL; i += kSumThreads) s_t[i] = a.transition[i];
+  if (threadIdx.x == 0) {
+    a.wrong[g] = 0u;                                         // path_pred_kernel marks
+    if (g == 0) a.wrong[G] = 0u;
+    s_odd[0] = s_odd[1] = 0u;
+  }
+  __syncthreads();
+  const bool on = lane < NL;
+  const int d = on ? lane : 0;
+  auto fetch = [&](int w0, int buf, int wave, int n) {       // windows w0 .. w0 + kSumWindows - 1 by n waves
+    constexpr int U = 8;
+    for (int i0 = wave; i0 < kSumWindows; i0 += U * n) {
+      double c[U];
+      uint64_t b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const size_t at = (size_t)min(w0 + i0 + u * n, NW - 1) * step + (size_t)g * NL + d;
+        c[u] = a.min_cost[at];
+        b[u] = a.near[at];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * n, at = (buf * kSumWindows + i) * DYN_WAVE + lane;
+        if (i >= kSumWindows) break;
+        const bool has = on && c[u] < inf && w0 + i < NW;
+        const int l = near_source(b[u], SPL, NL);
+        const uint64_t rest = has ? b[u] & (b[u] - 1) : 0ull;
+        s_c[at] = make_double2(has ? c[u] : inf, s_t[l * NL + d]);
+        s_r[at] = rest;
+        s_f[at] = has && b[u] == 0 ? -4 : 4 * l;
+        if ((__ballot(has && (b[u] == 0 || rest != 0)) != 0 || w0 + i >= NW) && lane == 0) atomicOr(&s_odd[buf], 1u << i);
+      }
+    }
+  };
+  auto from = [&](double v, int l4) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(l4, (int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(l4, (int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+  };
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
+  fetch(0, 0, wave, kSumThreads / DYN_WAVE);
+  __syncthreads();
+  double v = inf;                                            // lanes beyond the layouts stay there
+  double* tot = a.totals + (size_t)g * NL + d;
+  int buf = 0;
+  for (int w0 = 0; w0 < NW; w0 += kSumWindows, buf ^= 1) {
+    if (wave > 0) {
+      if (w0 + kSumWindows < NW) fetch(w0 + kSumWindows, buf ^ 1, wave - 1, kSumThreads / DYN_WAVE - 1);
+    } else if (on) {                                         // a lane's source is a layout: one of these
+      const uint32_t odd = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_odd[buf]);
+      double2 c[kSumGroup];
+      int l4[kSumGroup];
+      const double2* pc = s_c + buf * kSumWindows * DYN_WAVE + lane;
+      const int32_t* pf = s_f + buf * kSumWindows * DYN_WAVE + lane;
+#pragma unroll
+      for (int u = 0; u < kSumGroup; ++u) { c[u] = pc[u * DYN_WAVE]; l4[u] = pf[u * DYN_WAVE]; }
+#pragma unroll 1
+      for (int i0 = 0; i0 < kSumWindows; i0 += kSumGroup) {
+        pc += kSumGroup * DYN_WAVE;                          // past the last group: read and not used
+        pf += kSumGroup * DYN_WAVE;
+        if (((odd >> i0) & ((1u << kSumGroup) - 1u)) == 0u) {   // wave-uniform
+#pragma unroll
+          for (int u = 0; u < kSumGroup; ++u) {
+            v = (from(v, l4[u]) + c[u].y) + c[u].x;
+            *tot = v;
+            tot += step;
+            c[u] = pc[u * DYN_WAVE];
+            l4[u] = pf[u * DYN_WAVE];
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < kSumGroup; ++u) {
+            double arrive = from(v, l4[u]) + c[u].y;
+            uint64_t rest = s_r[(buf * kSumWindows + i0 + u) * DYN_WAVE + lane];
+            while (__ballot(rest != 0) != 0) {
+              const int q = near_source(rest, SPL, NL);
+              const double x = from(v, q * 4) + s_t[q * NL + d];
+              if (rest != 0) arrive = __builtin_fmin(arrive, x);
+              rest &= rest - 1;
+            }
+            if (l4[u] < 0) arrive = 0.0;                     // the first window of a sequence
+            v = arrive + c[u].x;
+            if (w0 + i0 + u < NW) *tot = v;
+            tot += step;
+            c[u] = pc[u * DYN_WAVE];
+            l4[u] = pf[u * DYN_WAVE];
+          }
+        }
+      }
+      if (lane == 0) s_odd[buf] = 0u;                        // filled again after the barrier
+    }
+    __syncthreads();
+  }
+}
+size_t sum_lds(int NL) { return ((size_t)NL * NL + 1) / 2 * 16 + (size_t)kSumRows * DYN_WAVE * (16 + 8 + 4); }
 
 // One wave per (window, class), lane = destination layout, the lane's column of the table in registers: where
 // the cheapest arrival in every layout of the next window comes from (least total + overhead, then the lowest
 // candidate among the sources that reach it), as (candidate << 6) | its layout, -1: none; and the best end and the total
 // of a sequence that ends in this window.  The sums are those of the walk, from the same operands.
-template <int LMAX>
-__global__ __launch_bounds__(256) void path_pred_kernel(PathArgs a) {
+// kAll: of the whole walk's totals.  kNamed: of path_sum_kernel's, with `near`; checks them.  kAgain: after the classes with wrong totals
+// were walked as a whole, for those.
+enum PredMode { kAll, kNamed, kAgain };
+template <int LMAX, PredMode MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LMAX <= 32 ? 4 : 3, 8))) void path_pred_kernel(PathArgs a) {
+  extern __shared__ double s_t[];                            // [NL][NL], with `near`
+  if (MODE == kAgain && a.wrong[a.G] == 0u) return;
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int NL = a.n_layout, NW = a.n_window, G = a.G;
   const double inf = __builtin_inf();
@@ -389,14 +594,20 @@ __global__ __launch_bounds__(256) void path_pred_kernel(PathArgs a) {
   double t[LMAX];
 #pragma unroll
   for (int l = 0; l < LMAX; ++l) t[l] = (on && l < NL) ? a.transition[(size_t)l * NL + lane] : inf;
+  if (MODE == kNamed) {
+    for (int i = threadIdx.x; i < NL * NL; i += 256) s_t[i] = a.transition[i];
+    __syncthreads();
+  }
   const int64_t cells = (int64_t)NW * G;
   const int64_t n_wave = (int64_t)gridDim.x * (blockDim.x / DYN_WAVE);
   for (int64_t cell = (int64_t)blockIdx.x * (blockDim.x / DYN_WAVE) + threadIdx.x / DYN_WAVE; cell < cells; cell += n_wave) {
     const int w = (int)(cell / G), g = (int)(cell % G);
-    const double v = on ? a.min_cost[(size_t)cell * NL + lane] : inf;
+    if (MODE == kAgain && a.wrong[g] == 0u) continue;                 // wave-uniform
+    const double v = on ? a.totals[(size_t)cell * NL + lane] : inf;
     const int k = on ? a.min_k[(size_t)cell * NL + lane] : 0;
     const uint32_t pk = (v < inf) ? (((uint32_t)k << 6) | (uint32_t)lane) : 0xFFFFFFFFu;
-    const double nv = (on && w + 1 < NW) ? a.min_cost[((size_t)cell + G) * NL + lane] : inf;
+    const double nv = (on && w + 1 < NW) ? a.totals[((size_t)cell + G) * NL + lane] : inf;
+    const double nc = (MODE == kNamed && on && w + 1 < NW) ? a.min_cost[((size_t)cell + G) * NL + lane] : inf;
     const bool gap = __ballot(v < inf) == 0;                 // no feasible candidate in this window
     const bool ends = !gap && __ballot(nv < inf) == 0;       // the next window has none, or does not exist
     double ev = inf;
@@ -416,15 +627,49 @@ __global__ __launch_bounds__(256) void path_pred_kernel(PathArgs a) {
     if (w + 1 >= NW) continue;
     double m = inf;
     uint32_t p = 0xFFFFFFFFu;                                // all ones: nothing arrives (then m is +inf)
+    if (MODE == kNamed) {                                  // the two least of all, then the source among those named: half of the instructions
+      double m2[2] = {inf, inf}, s2[2] = {inf, inf};
 #pragma unroll
-    for (int l = 0; l < LMAX; ++l) {
-      const double arr = readlane_f64(v, l) + t[l];
-      const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)pk, l);
-      const bool better = arr < m || (arr == m && sp < p);
-      m = better ? arr : m;
-      p = better ? sp : p;
+      for (int l = 0; l < LMAX; ++l) {
+        const double arr = readlane_f64(v, l) + t[l];
+        s2[l % 2] = min_num(s2[l % 2], max_num(m2[l % 2], arr));   // sums are never NaN here
+        m2[l % 2] = min_num(m2[l % 2], arr);
+        if (l % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // all sums at once would not fit the registers
+      }
+      m = __builtin_fmin(m2[0], m2[1]);
+      const double next = __builtin_fmin(__builtin_fmin(s2[0], s2[1]), __builtin_fmax(m2[0], m2[1]));
+      uint64_t named = on && m < inf ? a.near[((size_t)cell + G) * NL + lane] : 0ull;
+      while (__ballot(named != 0) != 0) {
+        const int q = near_source(named, LMAX / 4, NL);
+        const double arr = lane_f64(v, q) + s_t[q * NL + (on ? lane : 0)];
+        const uint32_t sp = (uint32_t)__builtin_amdgcn_ds_bpermute(q * 4, (int)pk);
+        if (named != 0 && arr == m) p = sp;
+        named &= named - 1;
+      }
+      // where two reach the least, or none of the named does, all are looked at for the lowest candidate
+      if (__ballot(on && m < inf && (next == m || p == 0xFFFFFFFFu)) != 0) {
+        p = 0xFFFFFFFFu;
+#pragma unroll 1
+        for (int l = 0; l < NL; ++l) {
+          const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)pk, l);
+          if (readlane_f64(v, l) + s_t[l * NL + (on ? lane : 0)] == m) p = min(p, sp);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int l = 0; l < LMAX; ++l) {
+        const double arr = readlane_f64(v, l) + t[l];
+        const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)pk, l);
+        const bool better = arr < m || (arr == m && sp < p);
+        m = better ? arr : m;
+        p = better ? sp : p;
+      }
     }
     if (on) a.pred[((size_t)g * NW + w + 1) * NL + lane] = (int32_t)p;
+    if (MODE == kNamed) {                                  // the next window's totals by the recurrence, from this window's
+      const double now = (gap || !(nc < inf)) ? nc : m + nc;
+      if (__ballot(on && __double_as_longlong(now) != __double_as_longlong(nv)) != 0 && lane == 0) { a.wrong[g] = 1u; a.wrong[G] = 1u; }
+    }
   }
 }
 
@@ -446,7 +691,16 @@ __device__ __forceinline__ void trace_stage(const PathArgs& a, int g, int lo, in
   const int32_t* bp = a.pred + (size_t)g * NW * NL;          // [NW][NL]: where the cheapest arrival in layout l at window w comes from
   const int32_t* kend = a.kend + (size_t)g * NW;             // [NW]: -1 gap, best end where a sequence ends, 0 otherwise
   const int n_row = (hi < NW ? hi : NW - 1) - lo;            // predecessor records of the windows lo+1 .. hi
-  for (int i = threadIdx.x; i < n_row * NL; i += blockDim.x) s_bp[i] = bp[(size_t)(lo + 1) * NL + i];
+  constexpr int U = 16;                                      // records in flight per thread: a load at a time took 12 us of a run's 25
+  const int32_t* from = bp + (size_t)(lo + 1) * NL;
+  for (int i0 = threadIdx.x; i0 < n_row * NL; i0 += U * (int)blockDim.x) {
+    int32_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = from[min(i0 + u * (int)blockDim.x, n_row * NL - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * (int)blockDim.x < n_row * NL) s_bp[i0 + u * (int)blockDim.x] = x[u];
+  }
   for (int i = n_row * NL + threadIdx.x; i < (hi - lo) * NL; i += blockDim.x) s_bp[i] = -1;   // nothing follows the last window
   for (int i = threadIdx.x; i < hi - lo; i += blockDim.x) s_ke[i] = kend[lo + i];
   __syncthreads();
@@ -543,9 +797,17 @@ void launch_layout_route(const PathArgs& a, hipStream_t s) {
   const int64_t cells = (int64_t)a.n_window * a.G;
   const int64_t n = cells * a.n_layout;
   hipLaunchKernelGGL(path_min_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
-  const int64_t pred_blocks = std::min<int64_t>((cells + 3) / 4, 2048);
-  hipLaunchKernelGGL(path_pred_kernel<LMAX>, dim3((unsigned)pred_blocks), dim3(256), 0, s, a);
+  const dim3 pred((unsigned)std::min<int64_t>((cells + 3) / 4, 2048));
+  if (a.near) {
+    hipLaunchKernelGGL(path_near_kernel<LMAX>, dim3((unsigned)((a.n_window + DYN_PATH_PIECE - 1) / DYN_PATH_PIECE), (unsigned)a.G), dim3(LMAX * 4), 0, s, a);
+    hipLaunchKernelGGL(path_sum_kernel, dim3((unsigned)a.G), dim3(kSumThreads), sum_lds(a.n_layout), s, a);
+    hipLaunchKernelGGL((path_pred_kernel<LMAX, kNamed>), pred, dim3(256), (size_t)a.n_layout * a.n_layout * sizeof(double), s, a);
+    hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
+    hipLaunchKernelGGL((path_pred_kernel<LMAX, kAgain>), pred, dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
+    hipLaunchKernelGGL((path_pred_kernel<LMAX, kAll>), pred, dim3(256), 0, s, a);
+  }
   const dim3 runs((unsigned)dyn_path_runs(a.n_window), (unsigned)a.G);
   hipLaunchKernelGGL(path_trace_runs_kernel, dim3(runs.x + 1, runs.y), dim3(128), 0, s, a);
   hipLaunchKernelGGL(path_trace_write_kernel, runs, dim3(DYN_WAVE), 0, s, a);
