@@ -960,6 +960,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
   ta.win_per_block = (int32_t)std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, wanted));
   ta.n_share = m->n_share; ta.r_share = 1.0 / (double)m->n_share;
   ta.types = mp.types;
+  ta.win_per_block = dyn_mixed_even_windows(ta);
   ta.type_energy = (double*)(base + w.type_energy); ta.type_f = (int8_t*)(base + w.type_f);
   if (!hip_ok(dyn_launch_mixed_types(ta, p->single_point, s), "mixed types launch")) return DYN_E_DEVICE;
 

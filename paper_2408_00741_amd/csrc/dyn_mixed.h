@@ -24,6 +24,7 @@ struct MixedTypeArgs {            // per-type least energies over the admissible
   double* type_energy;                    // [cells][n_entry]
   int8_t* type_f;                         // [cells][n_entry]
 };
+int32_t dyn_mixed_even_windows(const MixedTypeArgs& a);   // win_per_block, or up to a quarter more where that leaves fewer lanes idle
 hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, bool single_point, hipStream_t s);
 
 struct MixedCombineArgs {         // least total energy over the assignments of instances and shares

@@ -120,11 +120,17 @@ __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
   }
 }
 
+// Entries of a type that are not twice another.
+__host__ __device__ __forceinline__ int own_entries(int n_max, int S) { return n_max / 2 * (S + (S + 1) / 2) + (n_max & 1) * S; }
+
 // The same per-type energies with the frequencies walked by the thread: a thread is (entry, window), takes its
 // share of the window's load once and keeps the least admissible energy over the frequencies in ascending order
 // (strictly less replaces: the lowest frequency among equals), so nothing crosses lanes and every lane stores.
 // The capacities n x max load and their reciprocals, which the other kernel forms per lane and pass, come from an
 // LDS table [n_max][n_f] built once per block.  Chosen when that table fits beside the rows.
+// 2n instances with 2a shares run at the utilization of n with a: load and capacity are both exactly twice as much, so every
+// quotient, table value and comparison is the same to the last bit and the energy exactly twice.  Only the entries that are not twice
+// another are looked up, three of four with 8 shares: 36 000 cells, 28 instances and 8 shares 282 us a call, 255 so.
 // LDS: as above, then [capacity n_max*n_f] [its reciprocal n_max*n_f]
 template <bool SINGLE>
 __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
@@ -178,10 +184,12 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
   L.bucket_scale = a.bucket_scale;
   L.rgp = s_rgp; L.rinv = s_rinv; L.js = s_js; L.thr = s_thr; L.n_rho = n_rho;
   const double sd = (double)S;
-  const int64_t n_pair = (int64_t)n_ent * (w1 - w0);              // (window, entry), entry fastest
-  for (int64_t idx = threadIdx.x; idx < n_pair; idx += blockDim.x) {
-    const int dw = (int)(idx / n_ent), e = (int)(idx - (int64_t)dw * n_ent);
-    const int n = e / S + 1, sh = e - (n - 1) * S + 1;
+  // entries that are not twice another: of every two instance counts all shares of the odd one, the odd shares of the even one
+  const int per_two = S + (S + 1) / 2, n_own = own_entries(n_max, S);
+  const int n_pair = n_own * (w1 - w0);                           // (window, entry), entry fastest
+  for (int idx = threadIdx.x; idx < n_pair; idx += blockDim.x) {
+    const int dw = idx / n_own, e = idx - dw * n_own, two = e / per_two, in_two = e - two * per_two;
+    const int n = 2 * two + (in_two < S ? 1 : 2), sh = in_two < S ? in_two + 1 : 2 * (in_two - S) + 1;
     const double nd = (double)n, ad = (double)sh;
     const CellRec rec = s_rec[dw];
     const double ls = div_by(rec.load * ad, sd, a.r_share);      // the part of the load this type takes
@@ -205,9 +213,11 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
       const double pf = omt * tab[0] + t * tab[1], tb = omt * tab[n_rho] + t * tab[n_rho + 1];
       if (live && !(rec.xp99 * pf > slo_ttft) && !(tb * rec.nonempty > slo_tbt)) { best = en; bf = f; }
     }
-    const size_t o = ((size_t)(w0 + dw) * a.G + g) * n_entry + a.types.off[i] + e;
-    a.type_energy[o] = best;
-    a.type_f[o] = (int8_t)bf;
+    const size_t o = ((size_t)(w0 + dw) * a.G + g) * n_entry + a.types.off[i];
+    for (int q = 1; q * n <= n_max && q * sh <= S; q *= 2) {      // twice the instances under twice the load: the same utilization to the last bit
+      a.type_energy[o + (q * n - 1) * S + (q * sh - 1)] = (double)q * best;
+      a.type_f[o + (q * n - 1) * S + (q * sh - 1)] = (int8_t)bf;
+    }
   }
 }
 
@@ -448,6 +458,19 @@ size_t type_walk_lds(const MixedTypeArgs& a, bool single) {   // plus the capaci
 size_t dyn_mixed_combine_lds(int32_t n_tp, int32_t n_entry, int32_t u_max, int32_t n_share) {
   const size_t n_state = (size_t)(u_max + 1) * (n_share + 1);
   return ((size_t)n_entry + 2 * n_state) * sizeof(double) + (size_t)n_tp * n_state * sizeof(uint16_t) + 8;
+}
+
+// A type's block takes 256 of its (window, entry) pairs at a time, and the last time what is left.  36 000 cells of 96, 48 and 24 entries
+// of their own: 14 windows 260 us (2816 places for 2352 pairs), 16 windows 255 (2816 for 2688).
+int32_t dyn_mixed_even_windows(const MixedTypeArgs& a) {
+  int32_t best = a.win_per_block;
+  int64_t least = INT64_MAX, of = 1;
+  for (int32_t w = a.win_per_block; w <= std::min(DYN_MAX_WIN_PER_BLOCK, a.win_per_block + a.win_per_block / 4); ++w) {
+    int64_t rounds = 0;
+    for (int i = 0; i < a.n_tp; ++i) rounds += ((int64_t)own_entries(a.types.n_max[i], a.n_share) * w + 255) / 256;
+    if (least == INT64_MAX || rounds * of < least * w) { least = rounds; of = w; best = w; }
+  }
+  return best;
 }
 
 hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, bool single_point, hipStream_t s) {
