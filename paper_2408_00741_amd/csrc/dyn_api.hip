@@ -242,7 +242,7 @@ IngestWs ingest_ws_layout(int64_t n_req, int32_t n_model, int32_t n_in_bin, int3
 // One array per GPU the library runs on, held until the process ends.  In host code the array's
 // name is only a handle for hipGetSymbolAddress: kernels and copies get the address that call
 // returns for the current device, never the name.
-static __device__ __align__(256) unsigned char scratch[DYN_STATIC_WORKSPACE_BYTES + DYN_CELL_MANY_MAX];
+static __device__ __align__(256) unsigned char scratch[DYN_STATIC_WORKSPACE_BYTES];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -318,8 +318,11 @@ EvalWs dyn_eval_ws_layout(int64_t cells, int32_t K) {
   w.cstat = off; off += align256(c);
   w.part = off; off += align256(c * (size_t)w.n_wslot * sizeof(SelPart));
   w.total = off;
-  w.many = off; off += align256(dyn_cell_many_bytes(cells));
-  w.all = off;
+  // The aggregation is through before the evaluation writes its first partial record.  What fits the fixed workspace without
+  // this scratch fits it with it: the part before the records is a third of `total` at most, and the scratch 8 MB.
+  static_assert(DYN_STATIC_WORKSPACE_BYTES / 5 * 2 + DYN_CELL_MANY_MAX <= DYN_STATIC_WORKSPACE_BYTES, "the rule of dyn_eval_select_static");
+  w.many = w.part;
+  w.all = std::max(w.total, w.many + align256(dyn_cell_many_bytes(cells)));
   return w;
 }
 
@@ -762,7 +765,7 @@ int dyn_eval_select_static(dyn_profile* p, const dyn_trace_view* t, const dyn_co
   if ((rc = check_device(p)) != DYN_OK) return rc;
   void* ws = nullptr;
   if ((rc = scratch_address(&ws)) != DYN_OK) return rc;
-  if ((rc = eval_impl(p, t, cfg, K, o, out, sel, ws, (size_t)DYN_STATIC_WORKSPACE_BYTES + DYN_CELL_MANY_MAX, hip_stream)) != DYN_OK) return rc;
+  if ((rc = eval_impl(p, t, cfg, K, o, out, sel, ws, (size_t)DYN_STATIC_WORKSPACE_BYTES, hip_stream)) != DYN_OK) return rc;
   if (status) {
     hipLaunchKernelGGL(cell_status_word_kernel, dim3(1), dim3(1024), 0, (hipStream_t)hip_stream,
                        (const uint8_t*)((const char*)ws + w.cstat), cells, status);

@@ -128,7 +128,7 @@ struct WsHeader {
 // Layout of the evaluation workspace (offsets in bytes, all multiples of 256).
 struct EvalWs {
   size_t header, tin, tout, in_p99, rec, cstat, part, total;
-  size_t many, all;  // after `total`: scratch of dyn_launch_cell_aggregate, and the end of that
+  size_t many, all;  // scratch of dyn_launch_cell_aggregate, over the partial records; the end of both
   int32_t n_wslot;   // partial records per cell
 };
 EvalWs dyn_eval_ws_layout(int64_t cells, int32_t K);

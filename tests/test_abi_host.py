@@ -97,3 +97,17 @@ def test_ingest_workspace_grows_with_the_log():
     n = [0, 1, 2047, 2048, 2049, 8191, 8192, 8193, 100_000, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, (1 << 20) + 8193, 4 << 20, (4 << 20) + 1, 20_000_000]
     size = [dyn.dyn_trace_ingest_workspace(q, 1440, 25) for q in n]
     assert size == sorted(size)
+
+
+def test_eval_workspace_and_the_fixed_one(dyn):
+    """The header's example fits the fixed workspace by the header's own rule; a workspace for more cells or candidates serves fewer."""
+    assert dyn.dyn_eval_space_workspace(1440, 25, 576) == 13_140_480 <= dyn.DYN_STATIC_WORKSPACE_BYTES
+    for K in (1, 63, 576, 2048, 20_000, 65_536):
+        cells = [1, 2, 9, 100, 255, 256, 257, 680, 1023, 1024, 1025, 2000, 5000, 36_000, 75_000, 112_000, 200_000]
+        size = [dyn.dyn_eval_space_workspace(n, 1, K) for n in cells]
+        assert size == sorted(size)
+        # 24 bytes a record, a record for every 64 candidates and four more; 53 bytes a cell before them
+        need = [256 + 53 * n + 24 * (K // 64 + 4) * n for n in cells]
+        for got, at_least in zip(size, need):
+            assert got >= at_least
+            assert (got <= dyn.DYN_STATIC_WORKSPACE_BYTES) == (at_least + 6 * 256 <= dyn.DYN_STATIC_WORKSPACE_BYTES)

@@ -93,3 +93,34 @@ def test_static_workspace_refuses_what_does_not_fit(dyn):
                                                C.byref(se), None, None), "dyn_eval_select_static")
     assert e.value.status == -6 and "fixed" in str(e.value)
     prof.free()
+
+
+@pytest.mark.parametrize("K", [1, 576, 20_000, 40_000])
+def test_static_workspace_takes_what_the_query_says(dyn, K):
+    """The most windows whose workspace the query puts within the fixed one, and one more."""
+    w = make(SPECS[0].scaled(100, 1), with_trace=False)
+    prof = dyn.dyn_profile_load({k: (v[:1] if v.ndim >= 3 else v) for k, v in w["profile"].items()})
+    cfg = {k: np.resize(v, K) for k, v in w["configs"].items()}
+    plan = dyn.Plan(cfg, {k: v[:1] for k, v in w["slos"].items()}, w["pct"], None, 0.0)
+    lo, hi = 1, 1 << 20
+    while lo < hi:
+        mid = (lo + hi + 1) // 2
+        lo, hi = (mid, hi) if dyn.dyn_eval_space_workspace(mid, 1, K) <= dyn.DYN_STATIC_WORKSPACE_BYTES else (lo, mid - 1)
+    x = torch.zeros(0, dtype=torch.int32, device="cuda")
+    big = (lo + 1) * K
+    space = {"energy_j": torch.empty(big, dtype=torch.float64, device="cuda"), "p99_ttft_ms": torch.empty(big, dtype=torch.float64, device="cuda"),
+             "p99_tbt_ms": torch.empty(big, dtype=torch.float64, device="cuda"), "flags": torch.empty(big, dtype=torch.uint8, device="cuda")}
+    for n, fits in ((lo, True), (lo + 1, False)):
+        sel = {"sel": torch.empty(n, dtype=torch.int32, device="cuda"), **{k: torch.empty(n, dtype=torch.float64, device="cuda") for k in ("sel_energy_j", "sel_cost", "window_energy_j")},
+               "window_infeasible": torch.empty(n, dtype=torch.int32, device="cuda")}
+        out = {k: v[:n * K].view(n, K) for k, v in space.items()}
+        off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+        if fits:
+            dyn.dyn_eval_select_static(prof, x, x, off, n, 60.0, plan, out, sel)
+            torch.cuda.synchronize()
+            assert bool((sel["sel"] >= 0).all())
+        else:
+            with pytest.raises(dyn.DynError) as e:
+                dyn.dyn_eval_select_static(prof, x, x, off, n, 60.0, plan, out, sel)
+            assert e.value.status == -6
+    prof.free()
