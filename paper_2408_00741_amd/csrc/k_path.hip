@@ -468,9 +468,9 @@ __device__ __forceinline__ double lane_f64(double v, int lane) {       // of any
 constexpr int kSumWindows = 16, kSumThreads = 256, kSumGroup = 8;
 constexpr int kSumRows = 2 * kSumWindows + kSumGroup;
 __global__ __launch_bounds__(kSumThreads) void path_sum_kernel(PathArgs a) {
-  extern __shared__ double smem[];
+  extern __shared__ __attribute__((aligned(16))) double sum_smem[];   // the static words are before it
   const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.x;
-  double* s_t = smem;                                        // [NL][NL]
+  double* s_t = sum_smem;                                       // [NL][NL]
   double2* s_c = (double2*)(s_t + ((NL * NL + 1) & ~1));     // [2][kSumWindows][64] cost, overhead from the first source
   uint64_t* s_r = (uint64_t*)(s_c + kSumRows * DYN_WAVE);    // the same: the sources after the first
   int32_t* s_f = (int32_t*)(s_r + kSumRows * DYN_WAVE);      // the same: four times the first source, -4: none
