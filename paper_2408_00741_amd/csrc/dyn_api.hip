@@ -543,6 +543,8 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
     memcpy(&packed[(3 * r + 1) * d->n_rho], d->tbt_ms + r * d->n_rho, (size_t)d->n_rho * 8);
     memcpy(&packed[(3 * r + 2) * d->n_rho], d->power_w + r * d->n_rho, (size_t)d->n_rho * 8);
   }
+  p->mean_power.assign(d->n_tp, 0.0);
+  for (size_t i = 0; i < n_tab; ++i) p->mean_power[(i / ((size_t)d->n_f * d->n_rho)) % d->n_tp] += d->power_w[i] / (double)(n_tab / d->n_tp);
   std::vector<double> pw0(n_row);
   for (size_t r = 0; r < n_row; ++r) pw0[r] = d->power_w[r * d->n_rho];
   std::vector<double> pfspan(2 * n_row);
@@ -987,7 +989,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
 }
 
 namespace {
-struct PathWs { size_t layout, order, seg, transition, pred, kend, end_total, min_cost, min_k, exits, total, totals, near, wrong, all; };
+struct PathWs { size_t layout, order, seg, transition, pred, kend, end_total, min_cost, min_k, exits, total, totals, near, whole, all; };
 PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) {
   PathWs w;
   size_t off = 0;
@@ -1006,17 +1008,22 @@ PathWs path_ws_layout(int32_t n_window, int32_t G, int32_t K, int32_t n_layout) 
   const size_t near = n_window >= DYN_PATH_NEAR_LEAST ? per_layout : 0;
   w.totals = off; off += align256(near * sizeof(double));
   w.near = off; off += align256(near * sizeof(uint64_t));
-  w.wrong = off; off += near ? align256(((size_t)G + 1) * sizeof(uint32_t)) : 0;
+  w.whole = off; off += near ? align256((size_t)G * sizeof(uint32_t)) : 0;
   w.all = off;
   return w;
 }
-// The parts after `total`, at `more` (null: a workspace of the size without them, which still does).
+// The parts after `total`, at `more` (null: none, the walk takes every window as a whole).
 void path_near(PathArgs* a, char* more, const PathWs& w) {
   const bool near = more && w.all > w.total;
   a->totals = near ? (double*)(more + (w.totals - w.total)) : a->min_cost;
   a->near = near ? (uint64_t*)(more + (w.near - w.total)) : nullptr;
-  a->wrong = near ? (uint32_t*)(more + (w.wrong - w.total)) : nullptr;
+  a->whole = near ? (uint32_t*)(more + (w.whole - w.total)) : nullptr;
 }
+// Whether the walk in pieces pays: `over` is the mean overhead of a change, `watts` the mean candidate's power by the profile.  The dearer
+// changes are, the more often what was chosen 16 windows ago still decides, and such pieces are walked as a whole after all.  Measured
+// (us of dyn_select_path, the whole walk 450, by mean overhead in windows of that power; a day of 25 classes and 48 layouts): 0.02 272, 0.4 297,
+// 1.0 366, 1.4 393, 2.0 487, 20 528.
+bool path_pieces_pay(double over, double watts, double window_s) { return over <= 1.5 * watts * window_s; }
 }  // namespace
 
 size_t dyn_select_path_workspace(int32_t n_window, int32_t n_class, int32_t n_config, int32_t n_layout) {
@@ -1044,7 +1051,9 @@ int dyn_select_path(dyn_profile* p, const dyn_space* space, const dyn_config* cf
   }
   for (int k = 0; k < K; ++k)
     if (tr->layout[k] < 0 || tr->layout[k] >= tr->n_layout) { dyn_set_error("layout[%d]=%d outside [0, %d)", k, tr->layout[k], tr->n_layout); return DYN_E_RANGE; }
+  double over = 0.0;                                         // mean
   for (int64_t i = 0; i < (int64_t)tr->n_layout * tr->n_layout; ++i) {
+    over += tr->transition_j[i] / ((double)tr->n_layout * tr->n_layout);
     if (!isfinite(tr->transition_j[i])) { dyn_set_error("transition_j[%lld] is not finite", (long long)i); return DYN_E_NOTFINITE; }
     if (tr->transition_j[i] < 0.0) { dyn_set_error("transition_j[%lld] < 0", (long long)i); return DYN_E_RANGE; }
   }
@@ -1080,7 +1089,9 @@ int dyn_select_path(dyn_profile* p, const dyn_space* space, const dyn_config* cf
   a.order = p->d_path_order; a.seg_start = p->d_path_seg;
   a.pred = (int32_t*)(base + w.pred); a.kend = (int32_t*)(base + w.kend); a.end_total = (double*)(base + w.end_total);
   a.min_cost = (double*)(base + w.min_cost); a.min_k = (int32_t*)(base + w.min_k); a.exits = (int32_t*)(base + w.exits);
-  path_near(&a, workspace_bytes >= w.all ? base + w.total : nullptr, w);
+  double watts = 0.0;
+  for (int k = 0; k < K; ++k) watts += (double)cfg[k].n_inst * p->mean_power[cfg[k].tp_index] / K;
+  path_near(&a, workspace_bytes >= w.all && path_pieces_pay(over, watts, window_s) ? base + w.total : nullptr, w);   // a workspace of the size without it still does
   a.sel = out->sel; a.sel_energy = out->sel_energy_j; a.path_cost = out->path_cost;
   if (!hip_ok(dyn_launch_path(a, s), "path launch")) return DYN_E_DEVICE;
   if (!hip_ok(dyn_launch_window_totals(out->sel, out->sel_energy_j, n_window, p->G, out->window_energy_j,
@@ -1249,7 +1260,10 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     pa.pred = (int32_t*)(pb + pw.pred); pa.kend = (int32_t*)(pb + pw.kend); pa.end_total = (double*)(pb + pw.end_total);
     pa.min_cost = (double*)(pb + pw.min_cost); pa.min_k = (int32_t*)(pb + pw.min_k); pa.exits = (int32_t*)(pb + pw.exits);
     const size_t more = w.total + pw.total + align256(dyn_cell_many_bytes(fine_cells));
-    path_near(&pa, workspace_bytes >= more + (pw.all - pw.total) ? base + more : nullptr, pw);
+    double over = 0.0, watts = 0.0;                          // means
+    for (int64_t i = 0; i < (int64_t)c->n_layout * c->n_layout; ++i) over += c->transition_j[i] / ((double)c->n_layout * c->n_layout);
+    for (int l = 0; l < c->n_layout; ++l) watts += (double)c->lay_n[l] * p->mean_power[c->lay_tp_index[l]] / c->n_layout;
+    path_near(&pa, workspace_bytes >= more + (pw.all - pw.total) && path_pieces_pay(over, watts, window_s) ? base + more : nullptr, pw);
     pa.sel = out->layout_sel; pa.sel_energy = (double*)(base + w.sel_energy); pa.path_cost = out->path_cost;
     if (!hip_ok(dyn_launch_path(pa, s), "path launch")) return DYN_E_DEVICE;
   }

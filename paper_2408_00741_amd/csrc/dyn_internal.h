@@ -51,6 +51,7 @@ struct dyn_profile {
   double* d_pw0;  // [G][n_tp][n_f]  power at load 0 (first column of d_pw)
   double* d_pfspan;  // [G][n_tp][n_f][2]  smallest and largest prefill time of the row over the load axis
   float* d_theta;    // [G]  least ratio smallest / largest prefill time over the class's rows, rounded down
+  std::vector<double> mean_power;   // [n_tp] watts of an instance, over classes, frequencies and loads
   bool prefill_flat; // that ratio is 0.98 or more in every class
   // load grid for the kernels: [-inf, rho[0..n_rho-1], +inf] followed by
   // [0, 1/(rho[1]-rho[0]), ..., 1/(rho[n_rho-1]-rho[n_rho-2]), 0]

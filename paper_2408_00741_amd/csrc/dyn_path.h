@@ -8,7 +8,7 @@
 #define DYN_PATH_RUN 64             // windows the trace-back follows per block
 #define DYN_PATH_PIECE 48           // windows of a piece of path_near_kernel
 #define DYN_PATH_BEFORE 16          // windows before it that the piece's walk starts
-#define DYN_PATH_NEAR_LEAST 300     // windows from which its two kernels are worth it
+#define DYN_PATH_NEAR_LEAST 300     // windows from which they are worth it
 #define DYN_PATH_STATES 65          // what a run can be entered with: a layout of the window after it, or (64) none
 inline int32_t dyn_path_runs(int32_t n_window) { return (n_window + DYN_PATH_RUN - 1) / DYN_PATH_RUN; }
 
@@ -21,13 +21,13 @@ struct PathArgs {
   const int32_t* order;         // DEVICE [K] candidates sorted by (layout, index)
   const int32_t* seg_start;     // DEVICE [n_layout + 1] first sorted position of every layout
   const double* transition;     // DEVICE [n_layout][n_layout] (from, to)
-  int32_t* pred;                // workspace [G][n_window][n_layout]
+  int32_t* pred;                // workspace [G][n_window][n_layout]; with `near`, until the predecessors are taken, the totals that the pieces start from (doubles [pieces][G][n_layout])
   int32_t* kend;                // workspace [G][n_window]
   double* end_total;            // workspace [G][n_window] (n_layout <= 64): total of the sequence that ends in the window, +inf where none does
   double* min_cost;             // workspace [cells][n_layout] (n_layout <= 64): least cost of a layout's candidates
   double* totals;               // workspace [cells][n_layout]: least total of the sequences ending there; min_cost itself where `near` is null
   uint64_t* near;               // workspace [cells][n_layout]: the sources that may be the cheapest (path_near_kernel); null: the walk takes all
-  uint32_t* wrong;              // workspace [G + 1]: totals that are not what the recurrence says: of a class, of any
+  uint32_t* whole;              // workspace [G]: windows of a class that path_walk_kernel took all sums of
   int32_t* min_k;               // workspace [cells][n_layout]: the candidate that has it
   int32_t* exits;               // workspace [G][runs][DYN_PATH_STATES] (n_layout <= 64): state a run of windows is left with, by the state it is entered with
   int32_t* sel; double* sel_energy; double* path_cost;

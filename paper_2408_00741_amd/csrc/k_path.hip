@@ -314,46 +314,54 @@ __device__ __forceinline__ void add_sources(double v, const double (&t)[N], doub
 // by lane reads and the partial minima through LDS atomics: 0.41 us a window; sources read from LDS by every lane
 // (n_layout^2 values a window through the LDS port): 0.27 us; this, with 48 layouts: 0.22 us (596 to 323 us for the day).
 // totals[window][layout] (which may be min_cost itself) takes the least total of the sequences that end there (+inf: none).
-// Where `near` is set only classes with wrong totals are walked (below).
-template <int LMAX>
-__global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
-  if (a.near && a.wrong[blockIdx.x] == 0u) return;           // block-uniform
+// Begins at window w0 (a multiple of 16) with s_v[0] set; after every 16 windows `more` says whether to go on, and the windows walked come back.
+// s_dump: a word for every one of the THREADS threads; waves beyond the layouts only keep step.
+struct WalkOn {                                              // to the last window
+  __device__ __forceinline__ bool more(int) { return true; }
+};
+template <int LMAX, int THREADS, typename More>
+__device__ __forceinline__ int walk_whole(const PathArgs& a, int g, int w0, double (*s_v)[LMAX], double* s_dump, More& more) {
   constexpr int SPL = LMAX / 4;                              // sources per row
   static_assert(LMAX % 16 == 0 && LMAX <= 64, "a row of 16 lanes broadcasts its sources");
-  __shared__ double s_v[2][LMAX];                            // least totals of the window before, two buffers in turn
-  __shared__ double s_dump[LMAX * 4];
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
-  const int g = blockIdx.x, r = lane >> 4, p = lane & 15, d = (int)(threadIdx.x / DYN_WAVE) * 16 + p;   // row, place in it, destination
+  int lane = threadIdx.x & (DYN_WAVE - 1), NL = a.n_layout;
+  asm volatile("" : "+v"(lane), "+s"(NL));                   // inside a caller's loop: its addresses are not worth registers outside of it
+  lane &= DYN_WAVE - 1;
+  const int r = lane >> 4, p = lane & 15, d = (int)(threadIdx.x / DYN_WAVE) * 16 + p;   // row, place in it, destination
   const int src = r * SPL + min(p, SPL - 1);                 // the source whose total this lane reads
-  const int NL = a.n_layout, NW = a.n_window, G = a.G;
+  const int NW = a.n_window, G = a.G;
   const double inf = __builtin_inf();
   const bool on = d < NL;
   double t[SPL];                                             // overhead of going from the row's source q to this lane's destination
 #pragma unroll
   for (int q = 0; q < SPL; ++q) {
     const int ls = r * SPL + q;
-    t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + d] : inf;   // layouts beyond NL never win
+    const double over = a.transition[(size_t)min(ls, NL - 1) * NL + (on ? d : 0)];
+    t[q] = on && ls < NL ? over : inf;                       // layouts beyond NL never win
   }
-  const double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);   // this destination in window w: col[w * step]
-  double* tot = a.totals + (size_t)g * NL + (on ? d : 0);
-  const size_t step = (size_t)G * NL;
+  const size_t step = (size_t)G * NL, mine = (size_t)g * NL + (on ? d : 0);   // this destination in window w: [w * step + mine]
+  double* tot = a.totals + mine + (size_t)(w0 + r) * step;   // of this row's window
+  const double *next = a.min_cost + mine + (size_t)(w0 + r) * step, *last = a.min_cost + mine + (size_t)(NW - 1) * step;
+  int next_w = w0 + r;
   // loaded by every lane, from the last window beyond the end: behind a branch the waits would take in later loads too
-  auto cost = [&](int w) { return col[(size_t)min(w, NW - 1) * step]; };
+  auto cost = [&]() {
+    const double x = *(next_w < NW ? next : last);
+    next += 4 * step;
+    next_w += 4;
+    return x;
+  };
   constexpr int kRuns = 4;                                   // runs per loop pass: their costs sit in registers of their own, since
   double c[kRuns];                                           // handing a value on that is still being loaded would wait for it
 #pragma unroll
-  for (int u = 0; u + 1 < kRuns; ++u) c[u] = cost(4 * u + r);
+  for (int u = 0; u + 1 < kRuns; ++u) c[u] = cost();
   double* put[4];                                            // where a lane writes in window i of a run: no branch in the walk
 #pragma unroll
-  for (int i = 0; i < 4; ++i) put[i] = r == i ? &s_v[(i & 1) ^ 1][d] : &s_dump[threadIdx.x];
-  if (r == 0) s_v[0][d] = inf;                               // before the first window: as after a window without a feasible candidate
-  __syncthreads();
+  for (int i = 0; i < 4; ++i) put[i] = r == i && (THREADS == LMAX * 4 || d < LMAX) ? &s_v[(i & 1) ^ 1][d] : &s_dump[threadIdx.x];
 #pragma unroll 1
-  for (int w0 = 0; w0 < NW; w0 += 4 * kRuns) {
+  for (; w0 < NW; w0 += 4 * kRuns) {
 #pragma unroll
     for (int u = 0; u < kRuns; ++u) {
       const int w = w0 + 4 * u + r;                          // this row's window
-      c[(u + kRuns - 1) % kRuns] = cost(w + 4 * (kRuns - 1));
+      c[(u + kRuns - 1) % kRuns] = cost();
       const bool has = on && w < NW;
       const double cw = has ? c[u] : inf;
       double keep = inf;
@@ -374,40 +382,78 @@ __global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
         keep = r == i ? now : keep;
         lds_barrier();                                       // the window's only block barrier
       }
-      if (has) tot[(size_t)w * step] = keep;
+      if (has) *tot = keep;
+      tot += 4 * step;
     }
+    if (!more.more(w0 + 4 * kRuns)) return min(w0 + 4 * kRuns, NW);   // block-uniform
   }
+  return NW;
+}
+template <int LMAX>
+__global__ __launch_bounds__(LMAX * 4) void path_chain_kernel(PathArgs a) {
+  __shared__ double s_v[2][LMAX];                            // least totals of the window before, two buffers in turn
+  __shared__ double s_dump[LMAX * 4];
+  if (threadIdx.x < LMAX) s_v[0][threadIdx.x] = __builtin_inf();   // before the first window: as after a window without a feasible candidate
+  __syncthreads();
+  WalkOn on;
+  walk_whole<LMAX, LMAX * 4>(a, (int)blockIdx.x, 0, s_v, s_dump, on);
 }
 
 // Many windows: the walk of a class in pieces.  What a sequence cost long ago moves all totals of a window alike, so which sources can be
-// the cheapest is known from a walk that starts a few windows before (path_near_kernel, a block for every piece of every class, the
-// step of path_chain_kernel): those whose sum is within 2^-30 of the least, a bit each.  path_sum_kernel then takes the totals from the
-// first window on: of the named sources only, nearly always one, so a step is a lane exchange and two additions.  path_pred_kernel, which
-// forms all sums anyway, compares: a total that is not what the recurrence says marks its class, and path_chain_kernel walks
-// that class as a whole (overheads so large that a choice of 16 windows ago still matters).  By induction over the windows the
-// totals are those of the whole walk to the last bit.
-// Bounds: the issue of NL^2 sums a window and the walk of 64 windows (45 us for the day of 25 classes and 48 layouts), then the latency of
-// a lane exchange and two additions, 0.09 us a window in place of 0.22 (134 and 325 us).  Measured (us of dyn_select_path; the whole
-// walk, this): the day 486, 335; 95 680 cells of 38 layouts and 1196 windows 556, 503; 517 windows of 64 layouts, most without requests, so
-// that many sources tie, 219, 172; 320 windows of 51 163, 138; 259 of 25 116, 120.
+// the cheapest is mostly known from a walk that starts a few windows before (path_near_kernel, a block for every piece of every class, the
+// step of path_chain_kernel): those whose sum is within 2^-30 of the least, a bit each.  path_walk_kernel then takes the totals: of the
+// named source only, so a step is a lane exchange and two additions.  Where a piece begins it knows whether the piece's walk began from the
+// same totals but for a constant (`alike`).  If not (overheads so large that a choice of 16 windows ago still matters), and where many windows
+// of the piece have several sources named (ties), it walks the piece as path_chain_kernel does: what is lost then is path_near_kernel's time.
+// Totals are those of the whole walk to the last bit.  With costs >= 0 (a piece with others is never alike), m the least total that a piece
+// starts from, D the constant and e = 100 * 2^-53 * (D + sum) the rounding of both walks in 50 windows, a source whose sum is more than 2^-30 of the
+// least beyond it in the piece is beyond it by more than 2^-30 m - 2 * 2^-33 m - 2 e > 0 in the whole walk, as D <= 2^13 m.
+// Bounds: the issue of NL^2 sums and comparisons a window (the pieces, 51 us for the day of 25 classes and 48 layouts), then the latency of a
+// lane exchange and two additions, 0.096 us a window (138) in place of 0.225 (324).  Measured (us of dyn_select_path; the whole walk, this):
+// the day 450, 271; with ten times its overheads 450, 277, fifty times 450, 364, five times (joining and re-sharding then cost the same, and
+// a fifth of the windows have ties) 450, 480; 95 680 cells of 38 layouts and 1196 windows 543, 416; 517 windows of 64 layouts, most without
+// requests, 204, 140; 320 of 51 148, 116, with many ties 148, 171.
+constexpr int kWalkGroup = 8, kWalkRing = 3, kWalkAhead = 4;
+constexpr int kWalkThreads = 256;
+static_assert(DYN_PATH_PIECE % kWalkGroup == 0 && DYN_PATH_PIECE % 16 == 0, "pieces begin where groups and the whole walk's passes do");
+
+// What path_near_kernel leaves of a piece, in the space of the predecessors: the totals it starts from, then for every piece and class
+constexpr int kPieceEmpty = 1;                               // a window where a destination has no source (a sequence starts), or is beyond the last
+constexpr int kPieceBelow = 2;                               // a cost below zero: never alike
+constexpr int kPieceTie = 4;                                 // times the windows where a destination has several sources
+constexpr int kTies = 4;                                     // so many are taken one by one, a microsecond each; a piece of more is walked as a whole, 7 us more
+__device__ __forceinline__ double* piece_start(const PathArgs& a, int piece, int g) { return (double*)a.pred + ((size_t)piece * a.G + g) * a.n_layout; }
+__device__ __forceinline__ int* piece_flags(const PathArgs& a, int piece, int g) {
+  const int n_piece = (a.n_window + DYN_PATH_PIECE - 1) / DYN_PATH_PIECE;
+  return (int*)piece_start(a, n_piece, 0) + (size_t)piece * a.G + g;
+}
+static_assert(((DYN_PATH_NEAR_LEAST + DYN_PATH_PIECE - 1) / DYN_PATH_PIECE) * (sizeof(double) + sizeof(int)) <= DYN_PATH_NEAR_LEAST * sizeof(int32_t), "they fit");
+
 template <int LMAX>
 __global__ __launch_bounds__(LMAX * 4) void path_near_kernel(PathArgs a) {
   constexpr int SPL = LMAX / 4, kBefore = DYN_PATH_BEFORE;
   static_assert(SPL <= 16, "a row's bits");
+  static_assert(kBefore % 8 == 0 && DYN_PATH_PIECE % 8 == 0, "the passes below");
   __shared__ double s_v[2][LMAX];
+  __shared__ int s_flag;
+  const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.y;
+  const double inf = __builtin_inf();
+  if (threadIdx.x < LMAX) s_v[0][threadIdx.x] = inf;
+  if (threadIdx.x == 0) s_flag = 0;
+  __syncthreads();
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int r = lane >> 4, p = lane & 15, d = (int)(threadIdx.x / DYN_WAVE) * 16 + p;
   const int src = r * SPL + min(p, SPL - 1);
-  const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.y;
-  const double inf = __builtin_inf();
   const bool on = d < NL;
   double t[SPL];
 #pragma unroll
   for (int q = 0; q < SPL; ++q) {
     const int ls = r * SPL + q;
-    t[q] = (on && ls < NL) ? a.transition[(size_t)ls * NL + d] : inf;
+    const double over = a.transition[(size_t)min(ls, NL - 1) * NL + (on ? d : 0)];
+    t[q] = on && ls < NL ? over : inf;
   }
-  const int w0 = (int)blockIdx.x * DYN_PATH_PIECE, w1 = min(NW, w0 + DYN_PATH_PIECE), wb = max(0, w0 - kBefore);
+  const int piece = (int)blockIdx.x;
+  const int w0 = piece * DYN_PATH_PIECE, w1 = min(NW, w0 + DYN_PATH_PIECE), wb = max(0, w0 - kBefore);
   const double* col = a.min_cost + (size_t)g * NL + (on ? d : 0);
   const size_t step = (size_t)G * NL;
   uint16_t* bits = (uint16_t*)(a.near + (size_t)g * NL + (on ? d : 0)) + r;   // of this row in window w: bits[w * step * 4]
@@ -415,14 +461,16 @@ __global__ __launch_bounds__(LMAX * 4) void path_near_kernel(PathArgs a) {
   double c[kAhead];
 #pragma unroll
   for (int u = 0; u < kAhead; ++u) c[u] = col[(size_t)min(wb + u, NW - 1) * step];
-  if (r == 0) s_v[0][d] = inf;
-  __syncthreads();
+  uint32_t signs = 0;                                        // the upper bit: a cost below zero
+  uint32_t several = 0, empty = w1 < w0 + DYN_PATH_PIECE ? 1u : 0u;   // wave-uniform
+  double start = inf;
 #pragma unroll 1
   for (int wa = wb; wa < w1; wa += kAhead) {
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       const int w = wa + u;
       const double cw = on && w < NW ? c[u] : inf;
+      signs |= (uint32_t)((uint64_t)__double_as_longlong(cw) >> 32);
       c[u] = col[(size_t)min(w + kAhead, NW - 1) * step];
       const double v = s_v[u & 1][src];
       const bool alive = __ballot((int)(__double_as_longlong(v) >> 32) < 0x7FF00000) != 0;
@@ -437,17 +485,30 @@ __global__ __launch_bounds__(LMAX * 4) void path_near_kernel(PathArgs a) {
       const double arrive = rows_min_f64(x[0]);
       const double now = (!alive || !(cw < inf)) ? cw : arrive + cw;
       if (r == 0) s_v[(u & 1) ^ 1][d] = now;
-      if (w >= w0 && w < w1) {                               // block-uniform
-        const double near = arrive + arrive * 0x1p-30;
+      if (wa >= w0 && w < w1) {                              // block-uniform
+        const double near = arrive + __builtin_fabs(arrive) * 0x1p-30;
         uint32_t b = 0;
 #pragma unroll
         for (int q = 0; q < SPL; ++q) b |= m[q] <= near ? 1u << q : 0u;
-        if (!(arrive < inf)) b = 0u;                         // no sequence arrives
+        if (!(arrive < inf)) b = alive ? (1u << SPL) - 1u : 0u;   // the sums overflow: all are asked for; or no sequence arrives
         if (on) bits[(size_t)w * step * 4] = (uint16_t)b;
+        // of the wave's destinations (a bit each, the same in all rows): with several sources, and with none
+        const uint64_t who = __ballot(b != 0), twice = __ballot((b & (b - 1)) != 0);
+        const uint32_t lo = (uint32_t)who, hi = (uint32_t)(who >> 32), any = lo | hi, rows = (uint32_t)twice | (uint32_t)(twice >> 32) | (lo & hi);
+        const uint32_t has = (uint32_t)__ballot(cw < inf) & 0xFFFFu;
+        several += ((rows | (rows >> 16) | (any & (any >> 16))) & has) != 0 ? 1u : 0u;
+        empty |= has & ~(any | (any >> 16));
       }
+      if (u == kAhead - 1 && wa + kAhead == w0) start = now;
       lds_barrier();
     }
   }
+  const int flags = (empty ? kPieceEmpty : 0) | (__ballot((signs >> 31) != 0) != 0 ? kPieceBelow : 0);
+  if (lane == 0 && flags) atomicOr(&s_flag, flags);
+  if (lane == 0 && several) atomicAdd(&s_flag, (int)several * kPieceTie);   // of all waves: a window may count more than once
+  __syncthreads();
+  if (r == 0 && on) piece_start(a, piece, g)[d] = start;
+  if (threadIdx.x == 0) *piece_flags(a, piece, g) = s_flag;
 }
 
 // Source layout of a bit of `near`: a row's 16 bits hold the SPL sources of the row.
@@ -455,159 +516,266 @@ __device__ __forceinline__ int near_source(uint64_t bits, int SPL, int NL) {
   const int b = __builtin_ctzll(bits | (1ull << 63));
   return min((b >> 4) * SPL + (b & 15), NL - 1);
 }
-__device__ __forceinline__ double lane_f64(double v, int lane) {       // of any lane
+__device__ __forceinline__ double exchange_f64(double v, int lane4) {  // of the lane lane4 / 4, which must be active
   const uint64_t u = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(lane * 4, (int)(uint32_t)u);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(lane * 4, (int)(uint32_t)(u >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(lane4, (int)(uint32_t)u);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(lane4, (int)(uint32_t)(u >> 32));
   return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// A block per class.  Its first wave adds, lane = destination layout; the others fetch the next windows' costs and sources and look
-// the overheads up, everything that does not need the totals.  One wave alone waited for its loads (0.16 us a window), and a step of 50
-// instructions took 0.15: a step with one source everywhere has a path of its own.
-constexpr int kSumWindows = 16, kSumThreads = 256, kSumGroup = 8;
-constexpr int kSumRows = 2 * kSumWindows + kSumGroup;
-__global__ __launch_bounds__(kSumThreads) void path_sum_kernel(PathArgs a) {
-  extern __shared__ __attribute__((aligned(16))) double sum_smem[];   // the static words are before it
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  return __longlong_as_double((long long)(((uint64_t)(uint32_t)dpp_mov<CTRL>((int)(uint32_t)(u >> 32)) << 32) | (uint32_t)dpp_mov<CTRL>((int)(uint32_t)u)));
+}
+__device__ __forceinline__ double wave_min_f64(double v) {   // least of a full wave, in every lane
+  v = __builtin_fmin(v, dpp_f64<0x121>(v));                  // row_ror 1, 2, 4, 8
+  v = __builtin_fmin(v, dpp_f64<0x122>(v));
+  v = __builtin_fmin(v, dpp_f64<0x124>(v));
+  v = __builtin_fmin(v, dpp_f64<0x128>(v));
+  return rows_min_f64(v);
+}
+
+// Whether a piece's walk started from the totals v but for a constant (a lane per layout, +inf on lanes beyond them; a full wave).
+__device__ __forceinline__ bool alike(double v, double start) {
+  const double inf = __builtin_inf();
+  const bool has = v < inf;
+  if (__ballot(has != (start < inf)) != 0) return false;     // a NaN start too
+  const uint64_t who = __ballot(has);
+  if (who == 0) return true;                                 // a new sequence starts with the piece
+  const double least = wave_min_f64(has ? start : inf);
+  const double by = has ? v - start : 0.0, first = readlane_f64(by, __builtin_ctzll(who));
+  return __ballot(has && !(__builtin_fabs(by - first) <= least * 0x1p-33)) == 0 && __builtin_fabs(first) <= least * 0x1p13;
+}
+
+// Where a piece begins, the first wave says how it is walked: lane = layout, v = the totals of the window before.
+struct PieceStart {
+  const PathArgs& a;
+  int g, next;                                               // the next piece to say it of
+  int* s_how;                                                // [2], pieces in turn: all waves have read a word long before it is written again
+  double start;
+  int flags;
+  static __device__ __forceinline__ int own_lane() {         // opaque: no addresses of these rare steps in registers during the walk
+    int lane = threadIdx.x & (DYN_WAVE - 1);
+    asm volatile("" : "+v"(lane));
+    return lane;
+  }
+  __device__ __forceinline__ void fetch() {
+    const int lane = own_lane();
+    const bool in = next * DYN_PATH_PIECE < a.n_window;
+    start = in && lane < a.n_layout ? piece_start(a, next, g)[lane] : __builtin_inf();
+    flags = in ? *piece_flags(a, next, g) : 0;
+  }
+  // Where the sources are not right path_pred_kernel is told to look at all.
+  __device__ __forceinline__ void say(double v) {
+    const int lane = own_lane();
+    const bool same = next == 0 || (alike(v, start) && (flags & kPieceBelow) == 0);
+    if (!same && lane < DYN_PATH_PIECE && next * DYN_PATH_PIECE + lane < a.n_window)
+      a.near[((size_t)(next * DYN_PATH_PIECE + lane) * a.G + g) * a.n_layout] = ~0ull;
+    if (lane == 0) s_how[next & 1] = !same || flags >= (kTies + 1) * kPieceTie ? kWhole : flags >= kPieceTie ? kSeveral : flags != 0 ? kEmpty : kPlain;
+    ++next;
+    fetch();
+  }
+  __device__ __forceinline__ int how(int w) const { return __builtin_amdgcn_readfirstlane(s_how[(w / DYN_PATH_PIECE) & 1]); }   // of the piece of window w
+  static constexpr int kPlain = 0, kEmpty = 1, kSeveral = 2, kWhole = 3;   // one source everywhere; or none; or in few windows several; all sums
+};
+static_assert(DYN_PATH_PIECE <= DYN_WAVE, "a lane marks a window");
+template <int LMAX>
+struct WalkWholePieces {                                     // until a piece that need not be walked as a whole
+  PieceStart& at;
+  double (*s_v)[LMAX];
+  __device__ __forceinline__ bool more(int w) {
+    if (w % DYN_PATH_PIECE != 0 || w >= at.a.n_window) return true;   // block-uniform
+    if (threadIdx.x < DYN_WAVE) at.say(threadIdx.x < LMAX ? s_v[0][threadIdx.x] : __builtin_inf());
+    lds_barrier();
+    return at.how(w) == PieceStart::kWhole;
+  }
+};
+
+// A block per class.  Of pieces with one source everywhere (or none) the first wave adds, lane = destination layout; the others fetch the costs,
+// sources and overheads of the group of eight windows after the next, which need no totals: three groups in LDS, so that the block finds
+// room beside another stream's kernel (20 KB with 48 layouts; 90 KB were held by rows of 64 lanes, the overhead table and the further sources).
+template <int LMAX>
+__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void path_walk_kernel(PathArgs a) {
+  constexpr int SPL = LMAX / 4, kHelpers = kWalkThreads / DYN_WAVE - 1, kEach = (kWalkGroup + kHelpers - 1) / kHelpers;
+  constexpr int kRows = kWalkRing * kWalkGroup;
+  constexpr uint32_t kNone = 255u;                           // others are four times the source, and one more where there are several
+  __shared__ double2 s_c[kRows][LMAX];                       // cost, overhead from the source
+  __shared__ uint8_t s_l[kRows][LMAX];
+  __shared__ double s_v[2][LMAX];
+  __shared__ int s_how[2];
   const int NL = a.n_layout, NW = a.n_window, G = a.G, g = blockIdx.x;
-  double* s_t = sum_smem;                                       // [NL][NL]
-  double2* s_c = (double2*)(s_t + ((NL * NL + 1) & ~1));     // [2][kSumWindows][64] cost, overhead from the first source
-  uint64_t* s_r = (uint64_t*)(s_c + kSumRows * DYN_WAVE);    // the same: the sources after the first
-  int32_t* s_f = (int32_t*)(s_r + kSumRows * DYN_WAVE);      // the same: four times the first source, -4: none
-  __shared__ uint32_t s_odd[2];                              // a bit for every window where a destination has no source, or several, or that is beyond the last
-  const int SPL = (NL + 15) / 16 * 4;                        // sources of a row in path_near_kernel
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
+  double* s_dump = (double*)s_c;                             // the whole walk needs no rows
+  static_assert(kRows * LMAX * sizeof(double2) >= kWalkThreads * sizeof(double), "a word for every thread");
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const double inf = __builtin_inf();
   const size_t step = (size_t)G * NL;
-  for (int i = threadIdx.x; i < NL * NL; i += kSumThreads) s_t[i] = a.transition[i];
-  if (threadIdx.x == 0) {
-    a.wrong[g] = 0u;                                         // path_pred_kernel marks
-    if (g == 0) a.wrong[G] = 0u;
-    s_odd[0] = s_odd[1] = 0u;
+  const bool lay = lane < NL;
+  PieceStart at{a, g, 0, s_how, inf, 0};
+  double v = inf;                                            // of the first wave: before the first window as after one without a feasible candidate
+  if (wave == 0) {
+    at.fetch();
+    at.say(v);
   }
   __syncthreads();
-  const bool on = lane < NL;
-  const int d = on ? lane : 0;
-  auto fetch = [&](int w0, int buf, int wave, int n) {       // windows w0 .. w0 + kSumWindows - 1 by n waves
-    constexpr int U = 8;
-    for (int i0 = wave; i0 < kSumWindows; i0 += U * n) {
-      double c[U];
-      uint64_t b[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const size_t at = (size_t)min(w0 + i0 + u * n, NW - 1) * step + (size_t)g * NL + d;
-        c[u] = a.min_cost[at];
-        b[u] = a.near[at];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * n, at = (buf * kSumWindows + i) * DYN_WAVE + lane;
-        if (i >= kSumWindows) break;
-        const bool has = on && c[u] < inf && w0 + i < NW;
-        const int l = near_source(b[u], SPL, NL);
-        const uint64_t rest = has ? b[u] & (b[u] - 1) : 0ull;
-        s_c[at] = make_double2(has ? c[u] : inf, s_t[l * NL + d]);
-        s_r[at] = rest;
-        s_f[at] = has && b[u] == 0 ? -4 : 4 * l;
-        if ((__ballot(has && (b[u] == 0 || rest != 0)) != 0 || w0 + i >= NW) && lane == 0) atomicOr(&s_odd[buf], 1u << i);
-      }
-    }
-  };
-  auto from = [&](double v, int l4) {
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(l4, (int)(uint32_t)u);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(l4, (int)(uint32_t)(u >> 32));
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-  };
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
-  fetch(0, 0, wave, kSumThreads / DYN_WAVE);
-  __syncthreads();
-  double v = inf;                                            // lanes beyond the layouts stay there
-  double* tot = a.totals + (size_t)g * NL + d;
-  int buf = 0;
-  for (int w0 = 0; w0 < NW; w0 += kSumWindows, buf ^= 1) {
-    if (wave > 0) {
-      if (w0 + kSumWindows < NW) fetch(w0 + kSumWindows, buf ^ 1, wave - 1, kSumThreads / DYN_WAVE - 1);
-    } else if (on) {                                         // a lane's source is a layout: one of these
-      const uint32_t odd = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_odd[buf]);
-      double2 c[kSumGroup];
-      int l4[kSumGroup];
-      const double2* pc = s_c + buf * kSumWindows * DYN_WAVE + lane;
-      const int32_t* pf = s_f + buf * kSumWindows * DYN_WAVE + lane;
-#pragma unroll
-      for (int u = 0; u < kSumGroup; ++u) { c[u] = pc[u * DYN_WAVE]; l4[u] = pf[u * DYN_WAVE]; }
+
+  int w = 0, n_whole = 0;
 #pragma unroll 1
-      for (int i0 = 0; i0 < kSumWindows; i0 += kSumGroup) {
-        pc += kSumGroup * DYN_WAVE;                          // past the last group: read and not used
-        pf += kSumGroup * DYN_WAVE;
-        if (((odd >> i0) & ((1u << kSumGroup) - 1u)) == 0u) {   // wave-uniform
+  while (w < NW) {
+    int how = at.how(w);                                     // block-uniform
+    if (how == PieceStart::kWhole) {
+      if (wave == 0 && lane < LMAX) s_v[0][lane] = v;
+      lds_barrier();
+      WalkWholePieces<LMAX> more{at, s_v};
+      const int from = w;
+      w = walk_whole<LMAX, kWalkThreads>(a, g, w, s_v, s_dump, more);
+      n_whole += w - from;
+      if (wave == 0) v = lane < LMAX ? s_v[0][lane] : inf;
+      continue;
+    }
+    int ld = lay ? lane : 0;
+    asm volatile("" : "+v"(ld));                             // no addresses of this part in registers during the other one
+    int buf = 0;
+    auto after = [&]() {                                     // the group is done; false: the last one of this kind
+      w += kWalkGroup;
+      buf = buf + 1 == kWalkRing ? 0 : buf + 1;
+      lds_barrier();
+      if (w % DYN_PATH_PIECE == 0 && w < NW) how = at.how(w);
+      return w < NW && how != PieceStart::kWhole;
+    };
+    // Both kinds of waves in loops of their own: registers of loads in flight would make the other kind wait.
+    if (wave > 0) {                                          // a helper's windows of a group: wave - 1, + kHelpers, ...
+      double c[kEach], over[kEach];
+      uint64_t b[kEach];
+      auto load = [&](int w) {
 #pragma unroll
-          for (int u = 0; u < kSumGroup; ++u) {
-            v = (from(v, l4[u]) + c[u].y) + c[u].x;
-            *tot = v;
+        for (int u = 0; u < kEach; ++u) {
+          const size_t at_w = (size_t)min(w + wave - 1 + u * kHelpers, NW - 1) * step + (size_t)g * NL + ld;
+          c[u] = a.min_cost[at_w];
+          b[u] = a.near[at_w];
+        }
+      };
+      auto look_up = [&](int w, int buf) {                   // of the windows loaded before
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+          const int i = wave - 1 + u * kHelpers;
+          const bool has = w + i < NW && c[u] < inf;
+          const int l = near_source(b[u], SPL, NL);
+          over[u] = a.transition[(size_t)l * NL + ld];
+          if (i < kWalkGroup && lay) {
+            s_c[buf * kWalkGroup + i][ld].x = has ? c[u] : inf;
+            s_l[buf * kWalkGroup + i][ld] = (uint8_t)(b[u] == 0 ? kNone : 4u * (uint32_t)l + (has && (b[u] & (b[u] - 1)) != 0 ? 1u : 0u));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);                   // the next loads go to the same registers: nothing to hand on
+      };
+      auto put = [&](int buf) {                              // the overheads, which took a while
+#pragma unroll
+        for (int u = 0; u < kEach; ++u) {
+          const int i = wave - 1 + u * kHelpers;
+          if (i < kWalkGroup && lay) s_c[buf * kWalkGroup + i][ld].y = over[u];
+        }
+      };
+      load(w); look_up(w, 0); put(0);
+      load(w + kWalkGroup); look_up(w + kWalkGroup, 1); put(1);
+      load(w + 2 * kWalkGroup);
+      lds_barrier();
+      do {
+        const int b2 = buf + 2 < kWalkRing ? buf + 2 : buf + 2 - kWalkRing;   // nobody reads that buffer now
+        look_up(w + 2 * kWalkGroup, b2);
+        load(w + 3 * kWalkGroup);
+        put(b2);
+      } while (after());
+    } else {                                                 // a lane's source is a layout
+      double* tot_l = a.totals + (size_t)g * NL + ld;
+      double2 rc[kWalkAhead];
+      uint32_t rl[kWalkAhead];
+      lds_barrier();
+#pragma unroll
+      for (int u = 0; u < kWalkAhead; ++u) { rc[u] = s_c[u][ld]; rl[u] = s_l[u][ld]; }
+      do {
+        const int b1 = buf + 1 == kWalkRing ? 0 : buf + 1;
+        auto next = [&](int u) {                             // window u + kWalkAhead of this group, or of the next one
+          const int row = u + kWalkAhead < kWalkGroup ? buf * kWalkGroup + u + kWalkAhead : b1 * kWalkGroup + u + kWalkAhead - kWalkGroup;
+          rc[u % kWalkAhead] = s_c[row][ld];
+          rl[u % kWalkAhead] = s_l[row][ld];
+        };
+        double* tot = tot_l + (size_t)w * step;
+        if (how == PieceStart::kPlain) {                     // block-uniform
+#pragma unroll
+          for (int u = 0; u < kWalkGroup; ++u) {
+            const int i = u % kWalkAhead;
+            const double x = (exchange_f64(v, (int)rl[i]) + rc[i].y) + rc[i].x;
+            v = lay ? x : inf;
+            if (lay) *tot = v;
             tot += step;
-            c[u] = pc[u * DYN_WAVE];
-            l4[u] = pf[u * DYN_WAVE];
+            next(u);
+          }
+        } else if (how == PieceStart::kEmpty) {
+#pragma unroll
+          for (int u = 0; u < kWalkGroup; ++u) {
+            const int i = u % kWalkAhead;
+            const bool none = rl[i] == kNone;                // the first window of a sequence
+            const double arrive = exchange_f64(v, none ? 0 : (int)rl[i]) + rc[i].y;
+            v = lay ? (none ? rc[i].x : arrive + rc[i].x) : inf;
+            if (lay && w + u < NW) *tot = v;
+            tot += step;
+            next(u);
           }
         } else {
 #pragma unroll
-          for (int u = 0; u < kSumGroup; ++u) {
-            double arrive = from(v, l4[u]) + c[u].y;
-            uint64_t rest = s_r[(buf * kSumWindows + i0 + u) * DYN_WAVE + lane];
-            while (__ballot(rest != 0) != 0) {
-              const int q = near_source(rest, SPL, NL);
-              const double x = from(v, q * 4) + s_t[q * NL + d];
-              if (rest != 0) arrive = __builtin_fmin(arrive, x);
-              rest &= rest - 1;
+          for (int u = 0; u < kWalkGroup; ++u) {
+            const int i = u % kWalkAhead;
+            const bool none = rl[i] == kNone, more = lay && (rl[i] & 3u) == 1u;
+            double arrive = exchange_f64(v, none ? 0 : (int)(rl[i] & ~3u)) + rc[i].y;
+            if (__ballot(more) != 0) {                       // wave-uniform
+              const uint64_t b = a.near[(size_t)(w + u) * step + (size_t)g * NL + ld];
+              for (uint64_t rest = more ? b & (b - 1) : 0ull; __ballot(rest != 0) != 0; rest &= rest - 1) {
+                const int q = near_source(rest, SPL, NL);
+                const double x = exchange_f64(v, 4 * q) + a.transition[(size_t)q * NL + ld];
+                if (rest != 0) arrive = __builtin_fmin(arrive, x);
+              }
             }
-            if (l4[u] < 0) arrive = 0.0;                     // the first window of a sequence
-            v = arrive + c[u].x;
-            if (w0 + i0 + u < NW) *tot = v;
+            v = lay ? (none ? rc[i].x : arrive + rc[i].x) : inf;
+            if (lay && w + u < NW) *tot = v;
             tot += step;
-            c[u] = pc[u * DYN_WAVE];
-            l4[u] = pf[u * DYN_WAVE];
+            next(u);
           }
         }
-      }
-      if (lane == 0) s_odd[buf] = 0u;                        // filled again after the barrier
+        if ((w + kWalkGroup) % DYN_PATH_PIECE == 0 && w + kWalkGroup < NW) at.say(v);
+      } while (after());
     }
-    __syncthreads();
   }
+  if (threadIdx.x == 0) a.whole[g] = (uint32_t)n_whole;
 }
-size_t sum_lds(int NL) { return ((size_t)NL * NL + 1) / 2 * 16 + (size_t)kSumRows * DYN_WAVE * (16 + 8 + 4); }
 
-// One wave per (window, class), lane = destination layout, the lane's column of the table in registers: where
+// One wave per (window, class), lane = destination layout: where
 // the cheapest arrival in every layout of the next window comes from (least total + overhead, then the lowest
 // candidate among the sources that reach it), as (candidate << 6) | its layout, -1: none; and the best end and the total
 // of a sequence that ends in this window.  The sums are those of the walk, from the same operands.
-// kAll: of the whole walk's totals.  kNamed: of path_sum_kernel's, with `near`; checks them.  kAgain: after the classes with wrong totals
-// were walked as a whole, for those.
-enum PredMode { kAll, kNamed, kAgain };
-template <int LMAX, PredMode MODE>
+// NEAR: of the named sources only, which hold every source that reaches the least sum; of all where more than four are named (also
+// where path_walk_kernel found that they are not right).
+template <int LMAX, bool NEAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LMAX <= 32 ? 4 : 3, 8))) void path_pred_kernel(PathArgs a) {
-  extern __shared__ double s_t[];                            // [NL][NL], with `near`
-  if (MODE == kAgain && a.wrong[a.G] == 0u) return;
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int NL = a.n_layout, NW = a.n_window, G = a.G;
   const double inf = __builtin_inf();
   const bool on = lane < NL;
-  double t[LMAX];
+  const int ld = on ? lane : 0;
+  double t[NEAR ? 1 : LMAX];                                 // the lane's column of the table
+  if constexpr (!NEAR) {
 #pragma unroll
-  for (int l = 0; l < LMAX; ++l) t[l] = (on && l < NL) ? a.transition[(size_t)l * NL + lane] : inf;
-  if (MODE == kNamed) {
-    for (int i = threadIdx.x; i < NL * NL; i += 256) s_t[i] = a.transition[i];
-    __syncthreads();
+    for (int l = 0; l < LMAX; ++l) t[l] = (on && l < NL) ? a.transition[(size_t)l * NL + lane] : inf;
   }
   const int64_t cells = (int64_t)NW * G;
   const int64_t n_wave = (int64_t)gridDim.x * (blockDim.x / DYN_WAVE);
   for (int64_t cell = (int64_t)blockIdx.x * (blockDim.x / DYN_WAVE) + threadIdx.x / DYN_WAVE; cell < cells; cell += n_wave) {
     const int w = (int)(cell / G), g = (int)(cell % G);
-    if (MODE == kAgain && a.wrong[g] == 0u) continue;                 // wave-uniform
     const double v = on ? a.totals[(size_t)cell * NL + lane] : inf;
     const int k = on ? a.min_k[(size_t)cell * NL + lane] : 0;
     const uint32_t pk = (v < inf) ? (((uint32_t)k << 6) | (uint32_t)lane) : 0xFFFFFFFFu;
     const double nv = (on && w + 1 < NW) ? a.totals[((size_t)cell + G) * NL + lane] : inf;
-    const double nc = (MODE == kNamed && on && w + 1 < NW) ? a.min_cost[((size_t)cell + G) * NL + lane] : inf;
+    uint64_t named = (NEAR && on && w + 1 < NW) ? a.near[((size_t)cell + G) * NL + lane] : 0ull;
     const bool gap = __ballot(v < inf) == 0;                 // no feasible candidate in this window
     const bool ends = !gap && __ballot(nv < inf) == 0;       // the next window has none, or does not exist
     double ev = inf;
@@ -627,32 +795,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LMAX <= 32 
     if (w + 1 >= NW) continue;
     double m = inf;
     uint32_t p = 0xFFFFFFFFu;                                // all ones: nothing arrives (then m is +inf)
-    if (MODE == kNamed) {                                  // the two least of all, then the source among those named: half of the instructions
-      double m2[2] = {inf, inf}, s2[2] = {inf, inf};
-#pragma unroll
-      for (int l = 0; l < LMAX; ++l) {
-        const double arr = readlane_f64(v, l) + t[l];
-        s2[l % 2] = min_num(s2[l % 2], max_num(m2[l % 2], arr));   // sums are never NaN here
-        m2[l % 2] = min_num(m2[l % 2], arr);
-        if (l % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // all sums at once would not fit the registers
+    if (NEAR && __ballot(__popcll(named) > 4) == 0) {        // wave-uniform
+      if (__ballot((named & (named - 1)) != 0) == 0) {
+        const uint32_t sp = (uint32_t)__builtin_amdgcn_ds_bpermute(near_source(named, LMAX / 4, NL) * 4, (int)pk);
+        if (named != 0) p = sp;
+      } else {
+        while (__ballot(named != 0) != 0) {
+          const int q = near_source(named, LMAX / 4, NL);
+          const double arr = exchange_f64(v, 4 * q) + a.transition[(size_t)q * NL + ld];
+          const uint32_t sp = (uint32_t)__builtin_amdgcn_ds_bpermute(q * 4, (int)pk);
+          const bool better = named != 0 && (arr < m || (arr == m && sp < p));
+          m = better ? arr : m;
+          p = better ? sp : p;
+          named &= named - 1;
+        }
       }
-      m = __builtin_fmin(m2[0], m2[1]);
-      const double next = __builtin_fmin(__builtin_fmin(s2[0], s2[1]), __builtin_fmax(m2[0], m2[1]));
-      uint64_t named = on && m < inf ? a.near[((size_t)cell + G) * NL + lane] : 0ull;
-      while (__ballot(named != 0) != 0) {
-        const int q = near_source(named, LMAX / 4, NL);
-        const double arr = lane_f64(v, q) + s_t[q * NL + (on ? lane : 0)];
-        const uint32_t sp = (uint32_t)__builtin_amdgcn_ds_bpermute(q * 4, (int)pk);
-        if (named != 0 && arr == m) p = sp;
-        named &= named - 1;
-      }
-      // where two reach the least, or none of the named does, all are looked at for the lowest candidate
-      if (__ballot(on && m < inf && (next == m || p == 0xFFFFFFFFu)) != 0) {
-        p = 0xFFFFFFFFu;
+    } else if constexpr (NEAR) {                             // rare: the column stays in the cache
 #pragma unroll 1
-        for (int l = 0; l < NL; ++l) {
-          const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)pk, l);
-          if (readlane_f64(v, l) + s_t[l * NL + (on ? lane : 0)] == m) p = min(p, sp);
+      for (int l0 = 0; l0 < LMAX; l0 += 8) {                 // lanes beyond the layouts hold +inf
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = a.transition[(size_t)min(l0 + u, NL - 1) * NL + ld];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const double arr = readlane_f64(v, l0 + u) + x[u];
+          const uint32_t sp = (uint32_t)__builtin_amdgcn_readlane((int)pk, l0 + u);
+          const bool better = arr < m || (arr == m && sp < p);
+          m = better ? arr : m;
+          p = better ? sp : p;
         }
       }
     } else {
@@ -666,10 +836,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LMAX <= 32 
       }
     }
     if (on) a.pred[((size_t)g * NW + w + 1) * NL + lane] = (int32_t)p;
-    if (MODE == kNamed) {                                  // the next window's totals by the recurrence, from this window's
-      const double now = (gap || !(nc < inf)) ? nc : m + nc;
-      if (__ballot(on && __double_as_longlong(now) != __double_as_longlong(nv)) != 0 && lane == 0) { a.wrong[g] = 1u; a.wrong[G] = 1u; }
-    }
   }
 }
 
@@ -800,13 +966,11 @@ void launch_layout_route(const PathArgs& a, hipStream_t s) {
   const dim3 pred((unsigned)std::min<int64_t>((cells + 3) / 4, 2048));
   if (a.near) {
     hipLaunchKernelGGL(path_near_kernel<LMAX>, dim3((unsigned)((a.n_window + DYN_PATH_PIECE - 1) / DYN_PATH_PIECE), (unsigned)a.G), dim3(LMAX * 4), 0, s, a);
-    hipLaunchKernelGGL(path_sum_kernel, dim3((unsigned)a.G), dim3(kSumThreads), sum_lds(a.n_layout), s, a);
-    hipLaunchKernelGGL((path_pred_kernel<LMAX, kNamed>), pred, dim3(256), (size_t)a.n_layout * a.n_layout * sizeof(double), s, a);
-    hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
-    hipLaunchKernelGGL((path_pred_kernel<LMAX, kAgain>), pred, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(path_walk_kernel<LMAX>, dim3((unsigned)a.G), dim3(kWalkThreads), 0, s, a);
+    hipLaunchKernelGGL((path_pred_kernel<LMAX, true>), pred, dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL(path_chain_kernel<LMAX>, dim3((unsigned)a.G), dim3(LMAX * 4), 0, s, a);
-    hipLaunchKernelGGL((path_pred_kernel<LMAX, kAll>), pred, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((path_pred_kernel<LMAX, false>), pred, dim3(256), 0, s, a);
   }
   const dim3 runs((unsigned)dyn_path_runs(a.n_window), (unsigned)a.G);
   hipLaunchKernelGGL(path_trace_runs_kernel, dim3(runs.x + 1, runs.y), dim3(128), 0, s, a);

@@ -63,3 +63,19 @@ def test_ticks(dyn):
     early, _ = calls_through_early(lambda: dyn.dyn_eval_select_ticks(prof, ins, outs, off, 60, T, w["window_s"] / T, plan))
     prof.free()
     assert early >= 2, early
+
+
+@pytest.mark.parametrize("n_layout", [12, 48, 64])
+def test_path(dyn, n_layout):
+    """Sequences over enough windows for the walk in pieces."""
+    n_win = 320
+    w = make(SPECS[1].scaled(1000, 2))
+    G, rng = w["n_class"], np.random.default_rng(n_layout)
+    cfg = {"n_inst": rng.integers(1, 5, n_layout).astype(np.int32), "tp_index": np.zeros(n_layout, np.int32), "f_mhz": np.full(n_layout, w["profile"]["f_mhz"][0])}
+    prof = dyn.dyn_profile_load(w["profile"])
+    plan = dyn.Plan(cfg, w["slos"], w["pct"], None, 0.0)
+    space = {"energy_j": _dev(rng.uniform(1e4, 5e4, (n_win * G, n_layout))), "flags": _dev(np.ones((n_win * G, n_layout), np.uint8))}
+    tr = rng.uniform(0.0, 1e4, (n_layout, n_layout))
+    early, _ = calls_through_early(lambda: dyn.dyn_select_path(prof, space, n_win, 60.0, plan, np.arange(n_layout, dtype=np.int32), tr))
+    prof.free()
+    assert early >= 2, early

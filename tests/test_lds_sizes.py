@@ -1,5 +1,5 @@
-"""Where a kernel's dynamic LDS holds 16-byte elements, it begins at a multiple of 16: behind the static part, whose size the code
-object's metadata gives."""
+"""Static LDS of kernels that have to find room beside a kernel of another stream that fills the device: about 20 KB find it at once, 40
+wait for that kernel's end.  From the code objects' metadata, no GPU needed."""
 import os
 import re
 import struct
@@ -8,7 +8,8 @@ import subprocess
 import pytest
 
 READELF = "/opt/rocm/llvm/bin/llvm-readelf"
-SIXTEEN = ["path_sum_kernel"]                     # kernels with double2 (or wider) in their dynamic LDS
+# The walk of a path call of some hundred windows; its rows hold 16-byte elements and are static, so that the compiler places them.
+AT_MOST = {"path_walk_kernelILi16E": 8192, "path_walk_kernelILi32E": 16384, "path_walk_kernelILi48E": 20480, "path_walk_kernelILi64E": 28672}
 
 
 def _static_lds(path, tmp):
@@ -19,7 +20,6 @@ def _static_lds(path, tmp):
             continue
         obj = os.path.join(tmp, "obj")
         open(obj, "wb").write(lib[at:])
-        name = None
         for line in subprocess.run([READELF, "--notes", obj], capture_output=True, text=True).stdout.splitlines():
             if m := re.match(r"\s+(?:- )?\.group_segment_fixed_size:\s+(\d+)", line):
                 size = int(m[1])
@@ -28,12 +28,12 @@ def _static_lds(path, tmp):
     return out
 
 
-def test_dynamic_lds_of_wide_elements(tmp_path):
+def test_room_beside_other_streams(tmp_path):
     import paper_2408_00741_amd as dyn
     if not os.path.exists(READELF):
         pytest.skip("no llvm-readelf")
     lds = _static_lds(dyn.lib_path(), str(tmp_path))
     assert len(lds) > 50
-    for kernel in SIXTEEN:
-        found = {k: v for k, v in lds.items() if kernel in k}
-        assert found and all(v % 16 == 0 for v in found.values()), found
+    for kernel, most in AT_MOST.items():
+        found = [v for k, v in lds.items() if kernel in k]
+        assert len(found) == 1 and found[0] <= most, (kernel, found)
