@@ -843,6 +843,7 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ta.counters = (const uint32_t*)(base + w.counters); ta.slow_list = (const uint32_t*)(base + w.slow_list);
   ta.tstart = p->d_tstart; ta.thr = p->d_thr; ta.single_point = p->single_point; ta.any_two_rows = p->any_two_rows;
   ta.pfspan = p->d_pfspan; ta.n_cu = p->n_cu;
+  ta.mean_depth = t->n_req * (o->pct_den - o->pct_num) / o->pct_den / cells;   // n_req and the percentile's numbers are below 2^31
   if (!hip_ok(dyn_launch_tick_space(ta, s), "tick space launch")) return DYN_E_DEVICE;
 
   FinishArgs f;
