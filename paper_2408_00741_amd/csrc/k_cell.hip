@@ -14,6 +14,7 @@
 // few bits are left.  Larger cells are streamed from global memory by the whole block,
 // once for the sums and once per 10-bit digit, through an LDS histogram (radix select).
 #include <algorithm>
+#include <type_traits>
 
 #include "dyn_device.h"
 
@@ -746,10 +747,14 @@ __device__ __forceinline__ CellOut cell_by_block(const int32_t* __restrict__ in,
   return r;
 }
 
+// LONG: cells beyond lg.from are left to the many blocks' kernels, which this one makes ready; the other form is what small calls were before those
+// came in (a minute of 9 cells: 19.0 us a call against 19.15, of 25 cells 28.95, 29.3).
+struct NoLong {};
+template <bool LONG>
 __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(4, 8))) void cell_aggregate_block_kernel(
     const int32_t* __restrict__ in, const int32_t* __restrict__ out, const int64_t* __restrict__ cell_off, int64_t n_req, int64_t cells,
     double window_s, double r_window, int32_t pct_num, int32_t pct_den, int64_t* __restrict__ tin, int64_t* __restrict__ tout,
-    int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header, LongArgs lg) {
+    int32_t* __restrict__ in_p99, CellRec* __restrict__ rec, uint8_t* __restrict__ cstat, WsHeader* __restrict__ header, std::conditional_t<LONG, LongArgs, NoLong> lg) {
   __shared__ uint32_t s_hist[kBlockWaves][kHistBins];
   __shared__ int64_t s_xch[kBlockWaves][kXchWords];
   __shared__ uint32_t s_n[2 * kBlockWaves];
@@ -757,9 +762,11 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   // the first blocks take a cell per wave, one block for every cell follows
   const int64_t shared = (cells + kBlockWaves - 1) / kBlockWaves;
-  if ((int64_t)blockIdx.x >= cells + shared) {     // the blocks after those make the many blocks' kernels ready
-    long_prepare(lg, cell_off, n_req, cells, (int)((int64_t)blockIdx.x - cells - shared), s_hist[0]);
-    return;
+  if constexpr (LONG) {
+    if ((int64_t)blockIdx.x >= cells + shared) {   // the blocks after those make the many blocks' kernels ready
+      long_prepare(lg, cell_off, n_req, cells, (int)((int64_t)blockIdx.x - cells - shared), s_hist[0]);
+      return;
+    }
   }
   const bool alone = (int64_t)blockIdx.x < shared;
   const int64_t c = alone ? (int64_t)blockIdx.x * kBlockWaves + wave : (int64_t)blockIdx.x - shared;
@@ -768,7 +775,9 @@ __global__ __launch_bounds__(kBlockWaves* DYN_WAVE) __attribute__((amdgpu_waves_
   uint32_t bad = (beg < 0 || end < beg || end > n_req) ? DYN_WS_BAD_OFFSETS : 0u;
   if (bad) beg = end = 0;                          // never read outside the trace
   const int64_t m = end - beg;
-  if (m > lg.from) return;                         // the many blocks' (lg.from >= kWaveCell)
+  if constexpr (LONG) {
+    if (m > lg.from) return;                       // the many blocks' (lg.from >= kWaveCell)
+  }
   if (alone != (m <= kWaveCell)) return;           // uniform over the wave, and over a block that takes one cell
   CellOut r;
   r.tin = r.tout = 0;
@@ -977,24 +986,25 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
                                      uint8_t* cstat, WsHeader* header, void* many, hipStream_t s) {
   DynTimed timed(DYN_K_CELL, s);
   if (cells <= kBlockCells && n_req > kBlockMean * cells) {
-    LongArgs lg;
-    lg.from = INT64_MAX; lg.piece = 0; lg.n_cell = 0; lg.copies = 1; lg.work = nullptr;
-    unsigned prepare = 0, items = 0;
+    const unsigned blocks = (unsigned)(cells + (cells + kBlockWaves - 1) / kBlockWaves);
     if (many && n_req > kLongMean * cells && n_req > kLongLeast) {
+      LongArgs lg;
       lg.from = kLongCell;
       lg.n_cell = (int32_t)cells;
       lg.piece = std::max<int64_t>(kLongPiece, ((n_req + kLongBlocks - 1) / kLongBlocks + 255) / 256 * 256);
+      lg.copies = 1;
       while (lg.copies < kLongCopies && 2 * lg.copies * cells <= kLongSlots && n_req > (kLongShare * lg.copies) * cells * lg.piece) lg.copies *= 2;
       lg.work = (uint32_t*)many;
-      prepare = 1 + (unsigned)(cells * lg.copies + kSlotsPerBlock - 1) / kSlotsPerBlock;
-      items = (unsigned)((n_req + lg.piece - 1) / lg.piece + std::min<int64_t>(cells, n_req / kLongCell));   // every long cell's last piece may be a short one
-    }
-    hipLaunchKernelGGL(cell_aggregate_block_kernel, dim3((unsigned)(cells + (cells + kBlockWaves - 1) / kBlockWaves) + prepare), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
-                       window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, lg);
-    if (items) {
+      const unsigned prepare = 1 + (unsigned)(cells * lg.copies + kSlotsPerBlock - 1) / kSlotsPerBlock;
+      const unsigned items = (unsigned)((n_req + lg.piece - 1) / lg.piece + std::min<int64_t>(cells, n_req / kLongCell));   // every long cell's last piece may be a short one
+      hipLaunchKernelGGL(cell_aggregate_block_kernel<true>, dim3(blocks + prepare), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
+                         window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, lg);
       hipLaunchKernelGGL(cell_long_count_kernel, dim3(items), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, lg);
       hipLaunchKernelGGL(cell_long_rank_kernel, dim3(items), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, cells, window_s, 1.0 / window_s,
                          pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, lg);
+    } else {
+      hipLaunchKernelGGL(cell_aggregate_block_kernel<false>, dim3(blocks), dim3(kBlockWaves * DYN_WAVE), 0, s, in_tok, out_tok, cell_off, n_req, cells,
+                         window_s, 1.0 / window_s, pct_num, pct_den, tin, tout, in_p99, rec, cstat, header, NoLong{});
     }
     return hipGetLastError();
   }
