@@ -320,3 +320,43 @@ def test_argument_errors(dyn):
     torch.cuda.synchronize()
     assert out["nodes"].min().item() >= 1
     prof.free()
+
+
+def test_workspaces_of_every_size_that_is_taken(dyn):
+    """The path's pieces and the long cells' scratch follow the least workspace, in this order of need: without either, with the
+    scratch alone, a word short of the pieces, with all.  Outputs are the same; a word short of the least is refused."""
+    NW, T, n_lay, G = 300, 1, 9, 1
+    prof, _, _, slo, lay_n, lay_tp, _, _, tick = _random_case(2, 3, 3, 600, 6)
+    prof = {k: (v[:G] if v.ndim >= 3 else v) for k, v in prof.items()}
+    slo = {k: np.full(G, 1e9) for k in slo}
+    rng = np.random.default_rng(17)
+    n = 9001 * NW * T + 1                                  # long cells at both levels
+    off = np.concatenate([[0], np.sort(rng.integers(0, n + 1, NW - 1)), [n]]).astype(np.int64)
+    x, y = (_dev(rng.integers(1, 4000, n).astype(np.int32)) for _ in range(2))
+    trace = (x, y, _dev(off))
+    tok = np.diff(np.concatenate([[0], np.cumsum(x.cpu().numpy().astype(np.int64) + y.cpu().numpy())])[off]) / tick
+    prof["max_load_tps"] = prof["max_load_tps"] * (tok.max() / prof["max_load_tps"].mean() / 3.0)      # some windows need several instances
+    h = dyn.dyn_profile_load(prof)
+    trans = rng.uniform(0.0, 1.0, (n_lay, n_lay)) * 0.05 * 300.0 * tick
+    np.fill_diagonal(trans, 0.0)
+    up = lambda b: (b + 255) // 256 * 256   # noqa: E731
+    full = dyn.dyn_hierarchy_workspace(NW, T, G, n_lay)
+    pieces = 2 * up(NW * G * n_lay * 8) + up(G * 4)
+    scratch = up(4 * (64 + 1024 + 1088 + 2048 * min(1024, 4 * NW * G * T)))
+    sizes = {"least": full - pieces - scratch, "no pieces": full - pieces, "almost": full - 256, "all": full}
+    call = lambda b: dyn.dyn_hierarchy(h, trace, trace, NW, T, tick, 4, 2, 2, 8, lay_n[:n_lay], lay_tp[:n_lay], slo, transition_j=trans,   # noqa: E731
+                                       workspace=torch.empty(b, dtype=torch.uint8, device="cuda"))
+    out = {}
+    for k, b in sizes.items():
+        out[k], ws = call(b)
+        assert dyn.dyn_workspace_status(ws) == 0
+        for q in out[k]:
+            assert torch.equal(out[k][q], out["least"][q]), (k, q)
+    st = {"in_tok": x.cpu().numpy(), "out_tok": y.cpu().numpy(), "cell_off": off}
+    o = oracle.hierarchy(prof, st, st, NW, T, tick, 4, 2, 2, 8, lay_n[:n_lay], lay_tp[:n_lay], slo, transition=trans)
+    assert_same({**{k: v.cpu().numpy() for k, v in out["all"].items()}, "status": 0}, o, NW, G)
+    np.testing.assert_array_equal(out["all"]["path_cost"].cpu().numpy(), o["path_cost"])
+    assert (o["layout_sel"] >= 0).any()
+    with pytest.raises(dyn.DynError):
+        call(sizes["least"] - 256)
+    h.free()
