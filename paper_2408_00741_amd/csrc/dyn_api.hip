@@ -779,6 +779,19 @@ int dyn_eval_select_static(dyn_profile* p, const dyn_trace_view* t, const dyn_co
   return DYN_OK;
 }
 
+// Requests of a long cell from which blocks share it and make tables of its lengths although its block could make its ticks' lists.  A table
+// pays where ticks are long, as the loads of short ones differ so much that it holds thousands of lengths, and where there are few: a cell
+// costs its blocks T of them, and the pool holds so many.  Measured (us by lists, by tables) at requests of a mean tick : cells: of 12 ticks
+// 360:90 292 231 (an hour's load, 300:126: 229 875), 420:45 214 204, 500:126 256 231, 1000:45 328 240, 1000:360 387 400, 1000:540 419 479; of 16
+// 360:45 336 617, 420:45 368 249, 500:180 417 325, 1000:180 382 367, 1000:360 476 537, 1000:540 556 3387; of 20 360:45 354 948, 440:45 419
+// 332, 420:180 412 457, 500:180 512 446, 1000:180 429 516, 1000:360 605 3707; of 24 420:45 424 1210, 440:45 458 360, 500:360 608 715, 1000:360
+// 727 3923; of 48 440:45 1533 2610, 500:45 1609 1265, 1000:90 1550 1522, 1000:126 1713 4261; of 50 470:18 1567 1189.
+constexpr int kTablesMost = 5500, kTablesMostLarge = 4400;   // long cells x ticks, up to 16 ticks and beyond
+static int64_t tick_tables_from(int64_t T, int64_t cells) {
+  if (cells * T > (T <= 16 ? kTablesMost : kTablesMostLarge)) return INT64_MAX;
+  return (T <= 16 ? 400 : 460) * T + 1;
+}
+
 size_t dyn_eval_ticks_workspace(int64_t n_req, int32_t n_window, int32_t n_tick, int32_t n_class, int32_t n_config) {
   if (n_req < 0 || n_window < 1 || n_tick < 1 || n_tick > DYN_TICK_LIMIT || n_class < 1 || n_config < 1) return 0;
   return dyn_tick_ws_layout(n_req, (int64_t)n_window * n_class, n_tick, n_config).all;
@@ -824,6 +837,8 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ca.slots = (uint32_t*)(base + w.slots); ca.pool = (uint32_t*)(base + w.pool); ca.pool_words = w.pool_words;
   ca.n_slot = workspace_bytes >= w.all ? w.n_slot : 0;    // a workspace of the size without them still does
   ca.sure = ca.n_slot > 0 && t->n_req / DYN_TICK_LONG <= ca.n_slot;
+  // how many cells are long is not known here: no more than there are, and rarely more than the trace holds of twice the least long one
+  ca.table_from = tick_tables_from(n_tick, std::min<int64_t>(cells, t->n_req / (2 * DYN_TICK_LONG)));
   ca.cfg = p->d_cfg; ca.K = K; ca.ml = p->d_ml; ca.tab = p->d_tab; ca.gridpack = p->d_gridpack;
   ca.jstart = p->d_jstart; ca.bucket_scale = p->bucket_scale; ca.n_tp_f = p->n_tp * p->n_f; ca.n_rho = p->n_rho;
   if (!hip_ok(dyn_launch_tick_cell(ca, s), "tick cell launch")) return DYN_E_DEVICE;

@@ -61,6 +61,7 @@ struct TickCellArgs {
   uint32_t* slots; int32_t n_slot;   // n_slot 0: none, a block keeps every long cell
   uint32_t* pool; uint32_t pool_words;
   bool sure;                 // there is a slot for every long cell of this trace
+  int64_t table_from;        // requests of a long cell from which tables are made although its ticks' lists could be
   // how far a cell's prefill times lie apart
   const DevCfg* cfg; int32_t K; const double* ml; const double* tab; const double* gridpack;
   const int32_t* jstart; double bucket_scale; int32_t n_tp_f, n_rho;

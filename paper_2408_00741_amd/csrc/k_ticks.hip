@@ -318,12 +318,9 @@ __device__ __forceinline__ Settled tight_cell(const int32_t* __restrict__ in, co
 // wave of its block would hold more than 64 rows.  Measured (us of the call; a block per cell, shared): 60 cells of 65 000 requests and
 // 12 ticks 140, 117; 288 of 13 900 and 30 ticks 254, 209; 12 of 4700 and 30 ticks (at most 24 rows) 96, 117.
 constexpr int kLongRows = 64;
-// Requests of a mean tick from which tables are better than lists: the loads of shorter ticks differ so much that a table holds
-// thousands of lengths (45 cells of 1960 requests and 30 ticks, some beyond 4096: 836 us by lists, 943 by tables; 540 of 1850 and 12 ticks 257, 248).
-constexpr int kLongTick = 340;
 __device__ __forceinline__ bool long_at_once(const TickCellArgs& a, int64_t m, int g, int32_t cnt_l, int rows) {
   if (!a.sure || m <= DYN_TICK_LONG) return false;   // most cells, before the class's bound is there
-  return rows > kLongRows || (m > (int64_t)kLongTick * a.n_tick && cell_theta(a.theta[g], cnt_l) < 0.98f);
+  return rows > kLongRows || (m >= a.table_from && cell_theta(a.theta[g], cnt_l) < 0.98f);
 }
 
 // An entry of list_cells: the cell, with DYN_LIST_SKIP set for one that the block kernel leaves to tick_cell_kernel unseen (fewer than 2^30 cells).
@@ -1080,7 +1077,7 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
     }
     __syncthreads();                             // s_x is reused by the next item
     const bool lists = T >= 2 && (a.few_cells || j64 > DYN_TICK_WAVE) && j64 <= DYN_TICK_DEPTH && wave_max_u32((uint32_t)cnt_l) <= kListTick;   // can be made here
-    if (done != kSettled && m_cell > DYN_TICK_LONG && a.n_slot > 0 && !(done == kBoundFails && lists && m_cell <= (int64_t)kLongTick * T)) {   // block-uniform: to the blocks that share it, if a slot is left
+    if (done != kSettled && m_cell > DYN_TICK_LONG && a.n_slot > 0 && !(done == kBoundFails && lists && m_cell < a.table_from)) {   // block-uniform: to the blocks that share it, if a slot is left
       if (threadIdx.x == 0) s_x[0] = atomicAdd(&a.counters[4], 1u);
       __syncthreads();
       const uint32_t slot = s_x[0];

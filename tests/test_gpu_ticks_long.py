@@ -104,3 +104,14 @@ def test_lists_from_registers(dyn, n_req, T, pct):   # noqa: F811
     """1200 cells of a few to 50 requests with lists of 1 to 6 places: up to 4 are taken from the registers of the wave that read the cell."""
     w = _case(n_req, 1200, "load", stride=41)
     _check(dyn, w, T, pct)
+
+
+@pytest.mark.parametrize("T,m,windows,rest", [(12, 4800, 1, 0), (12, 4801, 1, 0), (16, 6400, 1, 0), (16, 6401, 2, 0), (17, 7820, 1, 0), (17, 7821, 2, 0),
+                                              (64, 29_441, 68, 530_000), (64, 29_441, 69, 535_900)])
+def test_lists_and_tables_of_long_cells(dyn, T, m, windows, rest):   # noqa: F811
+    """The longest cell whose ticks' lists are made and the shortest that gets tables, up to 16 ticks and beyond; 68 and 69 cells of 64 ticks in
+    a trace of more than 69 times 8192 requests, where tables are made and where all lists are: one long cell, the rest of `rest` requests."""
+    n = m + rest
+    w = _case(n, windows, "load", stride=41)
+    w["trace"]["t_s"] = np.concatenate([(np.arange(m) + 0.5) * (w["window_s"] / m), w["window_s"] * (1.0 + (windows - 1) * (np.arange(rest) + 0.5) / max(rest, 1))])
+    _check(dyn, w, T)
