@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 //   long_rank   every such length counted per tick.  The cell's last block turns the counts into "how many are at least so
 //               long", reads x_j off them, and the ties or the tables are the general kernel's and the walk's.
 // Cells it cannot take (lengths of 2^16 and more at the rank, negative token counts, a theta that leaves more than kLongRange lengths, no
-// room in the pool) go to the lists as before.  Bound: two reads of the lengths and the two launches.
+// room in the pool: 4 M words, sixteen cells of 64 ticks at the widest) go to the lists as before; which of many get room is the order of an atomic.  Bound: two reads of the lengths and the two launches.
 constexpr int kLongBlocks = 1024;              // at most: four to a compute unit
 constexpr int64_t kLongPiece = 4096;           // requests of a piece, about
 constexpr int kLongRange = 4096;               // lengths of a table
@@ -1145,6 +1145,9 @@ __global__ __launch_bounds__(WAVES* DYN_WAVE) __attribute__((amdgpu_waves_per_eu
 // (kept values win ties against new ones, lower lanes against higher ones), and the merged
 // order is written through a 64-word LDS buffer.  A second list, merged with every finished
 // tick's list, holds the j largest lengths of the whole cell: its last entry is x_j.
+// The first blocks take the long cells (long_count), in the registers and LDS of this kernel: spills are long_count's, the loop over listed cells has
+// none.  What sharing the launch costs that loop (us of the kernel without, with it; thousands of listed cells): 316 322, 124 126, 241 250; a launch of its
+// own would cost every call 2 to 4.5.  With eight waves a SIMD for the loop 296, but long_count on long cells 22.7 and 26.1.
 __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_waves_per_eu(6, 8))) void tick_cell_kernel(TickCellArgs a) {
   __shared__ uint32_t s_long[kLongWords];
   const int lane = threadIdx.x & (DYN_WAVE - 1);
