@@ -779,17 +779,16 @@ int dyn_eval_select_static(dyn_profile* p, const dyn_trace_view* t, const dyn_co
   return DYN_OK;
 }
 
-// Requests of a long cell from which blocks share it and make tables of its lengths although its block could make its ticks' lists.  A table
-// pays where ticks are long, as the loads of short ones differ so much that it holds thousands of lengths, and where there are few: a cell
-// costs its blocks T of them, and the pool holds so many.  Measured (us by lists, by tables) at requests of a mean tick : cells: of 12 ticks
-// 360:90 292 231 (an hour's load, 300:126: 229 875), 420:45 214 204, 500:126 256 231, 1000:45 328 240, 1000:360 387 400, 1000:540 419 479; of 16
-// 360:45 336 617, 420:45 368 249, 500:180 417 325, 1000:180 382 367, 1000:360 476 537, 1000:540 556 3387; of 20 360:45 354 948, 440:45 419
-// 332, 420:180 412 457, 500:180 512 446, 1000:180 429 516, 1000:360 605 3707; of 24 420:45 424 1210, 440:45 458 360, 500:360 608 715, 1000:360
-// 727 3923; of 48 440:45 1533 2610, 500:45 1609 1265, 1000:90 1550 1522, 1000:126 1713 4261; of 50 470:18 1567 1189.
-constexpr int kTablesMost = 5500, kTablesMostLarge = 4400;   // long cells x ticks, up to 16 ticks and beyond
-static int64_t tick_tables_from(int64_t T, int64_t cells) {
-  if (cells * T > (T <= 16 ? kTablesMost : kTablesMostLarge)) return INT64_MAX;
-  return (T <= 16 ? 400 : 460) * T + 1;
+// Requests of a long cell from which blocks share it and make tables of its lengths although its block could make its ticks' lists: the loads
+// of short ticks differ so much that a table holds thousands of lengths.  Where most of many cells are long, all have lists: the pool holds
+// so many tables, and one block makes the lists of a cell that finds it full.  Measured, us by lists and by tables, at requests of a mean tick : cells,
+// of 12 ticks 160:90 207 172, 300:126 273 231, 400:270 297 256, 1000:90 330 218, 1000:360 378 364, 300:900 355 396, 600:900 365 449; of 16 300:126 314 262,
+// 400:126 376 259, 1000:540 544 625; of 24 160:540 505 430, 300:126 528 435, 600:540 680 768, 400:900 867 2868; of 32 200:900 1027 793, 300:540 807 993,
+// 300:900 1206 3577; of 48 160:540 1672 1460, 300:126 1367 1574, 600:126 1669 1519, 300:540 1742 4193; of 64 160:360 2365 1996, 400:180 2656 2133,
+// 300:360 2475 6203.  Still full: of 48 1000:180 2284 5049, of 64 400:270 2811 4612.  From 250 requests of a mean tick in place of 340 (T 24, 250:63) 355 852.
+constexpr int64_t kTablesMost = 17000, kTablesMean = 220;   // cells x ticks, of so many requests a tick
+static int64_t tick_tables_from(int64_t T, int64_t cells, int64_t n_req) {
+  return cells * T > kTablesMost && n_req >= kTablesMean * T * cells ? INT64_MAX : 340 * T + 1;
 }
 
 size_t dyn_eval_ticks_workspace(int64_t n_req, int32_t n_window, int32_t n_tick, int32_t n_class, int32_t n_config) {
@@ -837,8 +836,7 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ca.slots = (uint32_t*)(base + w.slots); ca.pool = (uint32_t*)(base + w.pool); ca.pool_words = w.pool_words;
   ca.n_slot = workspace_bytes >= w.all ? w.n_slot : 0;    // a workspace of the size without them still does
   ca.sure = ca.n_slot > 0 && t->n_req / DYN_TICK_LONG <= ca.n_slot;
-  // how many cells are long is not known here: no more than there are, and rarely more than the trace holds of twice the least long one
-  ca.table_from = tick_tables_from(n_tick, std::min<int64_t>(cells, t->n_req / (2 * DYN_TICK_LONG)));
+  ca.table_from = tick_tables_from(n_tick, cells, t->n_req);
   ca.cfg = p->d_cfg; ca.K = K; ca.ml = p->d_ml; ca.tab = p->d_tab; ca.gridpack = p->d_gridpack;
   ca.jstart = p->d_jstart; ca.bucket_scale = p->bucket_scale; ca.n_tp_f = p->n_tp * p->n_f; ca.n_rho = p->n_rho;
   if (!hip_ok(dyn_launch_tick_cell(ca, s), "tick cell launch")) return DYN_E_DEVICE;

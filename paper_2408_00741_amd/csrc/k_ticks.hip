@@ -419,7 +419,9 @@ __global__ __launch_bounds__(kWavesPerBlock* DYN_WAVE) __attribute__((amdgpu_wav
 //   long_count  token sums per tick, and the cell's lengths counted by exponent and six bits (coarse_bin).  The cell's last block
 //               finds the bin that holds x_j, how far apart the prefill times of its ticks lie under any configuration (theta, from
 //               the least and the largest tick load), and so which lengths can decide: those of the bin where
-//               theta * (x + 1) > x (as above, the ties at x_j settle the cell), else those from theta * bin to bin / theta;
+//               theta * (x + 1) > x (as above, the ties at x_j settle the cell), else those from theta * bin to bin / theta and no longer than the
+//               cell's longest (540 cells of 12 ticks, an hour's load, 246 us without that, 238 with it; 63 of 14 ticks and 4200 requests, whose
+//               tables to bin / theta were too wide, so that one block made the lists, 859, 223);
 //   long_rank   every such length counted per tick.  The cell's last block turns the counts into "how many are at least so
 //               long", reads x_j off them, and the ties or the tables are the general kernel's and the walk's.
 // Cells it cannot take (lengths of 2^16 and more at the rank, negative token counts, a theta that leaves more than kLongRange lengths, no
@@ -605,6 +607,11 @@ __device__ __forceinline__ void long_count(const TickCellArgs& a, int n_share, u
     uint32_t k[kLongPer];
 #pragma unroll
     for (int b = 0; b < kLongPer; ++b) k[b] = s[tid * kLongPer + b];
+    uint32_t longest = 0;                        // the last bin that holds a request
+#pragma unroll
+    for (int b = 0; b < kLongPer; ++b) longest = k[b] ? (uint32_t)(tid * kLongPer + b) : longest;
+    longest = wave_max_u32(longest);
+    if (lane == 0) s_x[8 + wave] = longest;      // find_bin's barriers are between this and its use
     int64_t below;
     int bits;
     const uint32_t low = coarse_low(find_bin<kWavesPerBlock>(k, ct.rank, s_x, &below), &bits);
@@ -632,6 +639,9 @@ __device__ __forceinline__ void long_count(const TickCellArgs& a, int n_share, u
       if (ok) {
         from = max(0, (int)((double)low * (double)theta) - 1);
         n = (int)((double)high / (double)theta) + 3 - from;
+        int bits_l;
+        const uint32_t low_l = coarse_low((int)max(max(s_x[8], s_x[9]), max(s_x[10], s_x[11])), &bits_l);
+        if (low_l < 65536u) n = min(n, (int)(low_l + (1u << bits_l)) - from);   // beyond the longest request there is nothing to count
         ok = n <= kLongRange;
       }
     }

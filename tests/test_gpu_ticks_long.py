@@ -106,12 +106,26 @@ def test_lists_from_registers(dyn, n_req, T, pct):   # noqa: F811
     _check(dyn, w, T, pct)
 
 
-@pytest.mark.parametrize("T,m,windows,rest", [(12, 4800, 1, 0), (12, 4801, 1, 0), (16, 6400, 1, 0), (16, 6401, 2, 0), (17, 7820, 1, 0), (17, 7821, 2, 0),
-                                              (64, 29_441, 68, 530_000), (64, 29_441, 69, 535_900)])
+@pytest.mark.parametrize("T,m,windows,rest", [(13, 4420, 1, 0), (13, 4421, 2, 0), (64, 21_760, 2, 0), (64, 21_761, 1, 0), (64, 21_761, 265, 264 * 14_100), (64, 21_761, 266, 265 * 14_100)])
 def test_lists_and_tables_of_long_cells(dyn, T, m, windows, rest):   # noqa: F811
-    """The longest cell whose ticks' lists are made and the shortest that gets tables, up to 16 ticks and beyond; 68 and 69 cells of 64 ticks in
-    a trace of more than 69 times 8192 requests, where tables are made and where all lists are: one long cell, the rest of `rest` requests."""
-    n = m + rest
-    w = _case(n, windows, "load", stride=41)
+    """The longest cell whose ticks' lists are made and the shortest that gets tables, of few ticks and of most; 265 and 266 cells of 64 ticks and 220
+    requests a tick, where tables are made and where all lists are: one long cell, and `rest` requests in the others."""
+    w = _case(m + rest, windows, "load", stride=61)
     w["trace"]["t_s"] = np.concatenate([(np.arange(m) + 0.5) * (w["window_s"] / m), w["window_s"] * (1.0 + (windows - 1) * (np.arange(rest) + 0.5) / max(rest, 1))])
     _check(dyn, w, T)
+
+
+@pytest.mark.parametrize("prefill", ["load", "wild"])
+@pytest.mark.parametrize("longest", [63, 64, 127, 128, 8191, 8192, 8319, 65_535, 65_536, 70_000])
+def test_tables_end_at_the_longest_request(dyn, longest, prefill):   # noqa: F811
+    """The percentile among the longest requests, which many share, at the ends of the counted ranges of lengths and beyond those that are counted;
+    the first tick has twice the load of the others."""
+    w = _case(30_000, 1, prefill)
+    tr, rng = w["trace"], np.random.default_rng(7)
+    tr["in_tok"] = np.minimum(rng.integers(1, max(2, 2 * longest), 30_000), longest).astype(np.int32)
+    tr["in_tok"][rng.random(30_000) < 0.7] = 1 + longest // 3
+    tr["t_s"][:4000] = 0.05 * w["window_s"]
+    tr["t_s"].sort()
+    _check(dyn, w, 7)
+    tr["in_tok"][rng.integers(0, 30_000, 40)] = longest + 300     # fewer than the percentile's rank: longer than all that counts
+    _check(dyn, w, 7)
