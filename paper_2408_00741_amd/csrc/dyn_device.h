@@ -74,20 +74,22 @@ __device__ __forceinline__ int64_t readlane_i64(int64_t x, int lane) {   // lane
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
-// a / b, correctly rounded, given rb = RN(1 / b): the one division routine of the library.
-// q0 = RN(a * rb) is within 3/2 ulp of a / b; one residual step (the residual a - b*q0 is exact
-// in a fused multiply-add) brings q1 within 1/2 ulp + a relative 2^-52 of it, i.e. q1 is a
-// faithful rounding; for a faithful q1 and a correctly rounded reciprocal a second residual
-// step returns RN(a / b) (Markstein's theorem on the final step of a Newton-Raphson division).
-// Holds while nothing under- or overflows: the host keeps window lengths, capacities and grid
+// a / b, correctly rounded, given rb = RN(1 / b): the one division routine of the library.  One multiplication and two fused
+// operations are enough for a divisor known beforehand (Brisebarre, Muller, Raina, "Accelerating correctly rounded floating-point division
+// when the divisor is known in advance", IEEE Trans. Computers 53, 2004).  Why: scale a and b to [1, 2) and let u = 2^-53, n = rb - 1/b,
+// |n| <= u / 2.  If q0 = RN(a * rb) is one of the two doubles around a / b, the residual is exact and Markstein's theorem gives RN(a / b).
+// It always is for a >= b: |a * n| < u, half an ulp of the quotient, and the rounding adds no more than the other half.  For a < b (ulp
+// u, and |a * n| < u) it can be the next but one.  Let m be the midpoint of two doubles nearest to a / b; a - m * b = k u^2 for an
+// integer k, not 0.  Up to |k| = 4, a * rb = m + a * n + k u^2 / b is less than u from m, so q0 is a neighbour of m and with that of
+// a / b.  Beyond, a / b is 5 u^2 / b or more from m, and what the last rounding is given is off by less: by |q0 - a / b| * b * |n|, at most
+// (a + 1) b u^2 / 4 < 3 u^2 / b, and by the residual's own rounding, at most 2 u^2 / b.  (All pairs of up to 13 bits, and the hardest of 53:
+// tests/test_division.py.)  Holds while nothing under- or overflows: the host keeps window lengths, capacities and grid
 // spacings within [1e-100, 1e100], which leaves every operand, residual and quotient normal
 // (a == 0 gives 0 exactly).
 __device__ __forceinline__ double div_by(double a, double b, double rb) {
   const double q0 = a * rb;
   const double e0 = __builtin_fma(-b, q0, a);
-  const double q1 = __builtin_fma(e0, rb, q0);
-  const double e1 = __builtin_fma(-b, q1, a);
-  return __builtin_fma(e1, rb, q1);
+  return __builtin_fma(e0, rb, q0);
 }
 
 // Lengths counted by exponent and the six bits below it: exact below 64, otherwise a bin is at most 1/64 of its value wide.

@@ -12,7 +12,7 @@
 // The two divisions per entry (load / capacity, position inside the load bracket) have
 // divisors that do not depend on the window: their correctly rounded reciprocals are
 // computed once (per thread, per grid interval) and each quotient is then formed from the
-// reciprocal with two residual steps (div_by), which returns the correctly rounded a/b.
+// reciprocal with one residual step (div_by), which returns the correctly rounded a/b.
 //
 // With the fused selection, each wave also reduces the least cost among its feasible
 // configurations (Section IV-B "Scale-up/down") and one lane writes a partial record.
