@@ -58,11 +58,15 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
   const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)x, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
   return min(min(a, b), min(c, d));
 }
+// x, which is the same in every lane.  The builtin returns an int: as a half of 64 bits it must not be sign-extended.
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, DYN_WAVE);
-  return __builtin_amdgcn_readfirstlane((uint32_t)x) |
-         ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32);
+  return uniform_u64(x);
 }
 __device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {   // every lane ends with the total
 #pragma unroll

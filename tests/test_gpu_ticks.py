@@ -401,3 +401,18 @@ def test_full_size_traces_sampled_windows(dyn, idx, n_run):
     # a window's energy under tick-level load: never below the least energy any configuration has at zero load
     assert np.isfinite(g["energy_j"]).all() and (g["energy_j"] > 0).all()
     assert np.isfinite(g["p99_ttft_ms"]).all()
+
+
+@pytest.mark.parametrize("tokens", [(1 << 31) - 64, 1 << 31, 3 << 30, (1 << 32) - 64, 1 << 32, 5 << 30])
+def test_token_sums_around_32_bits(dyn, tokens):
+    """A tick of 64 requests whose tokens add up to about 2^31 and 2^32: the halves of the 64-bit sum."""
+    w = _one_class(make(SPECS[1].scaled(640, 2)))
+    n = 640
+    w["trace"]["t_s"] = np.sort(np.repeat((np.arange(10) + 0.5) * (w["window_s"] / 5), n // 10))
+    w["trace"]["in_tok"] = np.full(n, tokens // 64 - 3, np.int32)
+    w["trace"]["out_tok"] = np.full(n, 3, np.int32)
+    w["profile"]["max_load_tps"] = w["profile"]["max_load_tps"] * 0.0 + tokens / (w["window_s"] / 5)
+    w["configs"] = {k: v[::7].copy() for k, v in w["configs"].items()}
+    g, fine = gpu_ticks(dyn, w, 5)
+    assert g["status"] == 0
+    assert_same(w, g, ora_ticks(w, fine, 5))
