@@ -48,7 +48,7 @@ hipError_t dev_alloc(T** p, size_t count) {
 }
 
 void free_profile_device(dyn_profile* p) {
-  void* ptrs[] = {p->d_tab, p->d_ml, p->d_pw0, p->d_pfspan, p->d_theta, p->d_gridpack, p->d_jstart, p->d_tstart, p->d_thr, p->d_cfg,
+  void* ptrs[] = {p->d_tab, p->d_ml, p->d_pw0, p->d_pfspan, p->d_steep, p->d_theta, p->d_gridpack, p->d_even_grid, p->d_jstart, p->d_tstart, p->d_thr, p->d_cfg,
                   p->d_tile_rows, p->d_slo_ttft, p->d_slo_tbt, p->d_budget, p->d_path_layout, p->d_path_order,
                   p->d_path_seg, p->d_path_trans, p->d_hier_trans, p->d_lay_n, p->d_lay_tp, p->d_tp, p->d_ident};
   for (void* q : ptrs)
@@ -169,6 +169,15 @@ int prepare_configs(dyn_profile* p, const dyn_config* cfg, int32_t K, hipStream_
   for (int k = 0; k < K; ++k) p->any_two_rows = p->any_two_rows || dc[k].u != 0.0;
   p->cfg_host.assign(cfg, cfg + K);
   return DYN_OK;
+}
+
+AxisArgs axis_args(const dyn_profile* p) {
+  AxisArgs a;
+  a.gridpack = p->d_gridpack; a.even_grid = p->d_even_grid;
+  a.jstart = p->d_jstart; a.tstart = p->d_tstart; a.thr = p->d_thr;
+  a.n_rho = p->n_rho; a.n_bucket = p->n_bucket; a.bucket_scale = p->bucket_scale; a.even_scale = p->even_scale; a.rho_max = p->rho_max;
+  a.single_point = p->single_point; a.even = p->even;
+  return a;
 }
 
 // Uploads `n` values to a device array of the handle unless the handle already holds the same values there.  A
@@ -374,6 +383,7 @@ int32_t space_windows_per_block(dyn_profile* p, const SpaceArgs& a_in, int32_t n
   int64_t wpb = std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, (cell_tiles + 8191) / 8192));
   SpaceArgs a = a_in;
   a.win_per_block = 8;
+  a.axis.even = false;                       // the rule's figures are of the other form's blocks; 10 windows in place of 8, which the even form's occupancy gives: 2325 us, 2023 (201 600 cells of 2048)
   const int per_cu = dyn_space_blocks_per_cu(a);
   if (per_cu > 0 && p->n_cu > 0) wpb = std::min<int64_t>(wpb, std::max<int64_t>(4, 16384 / ((int64_t)per_cu * p->n_cu)));
   const int64_t staged = (int64_t)p->n_slot * 3 * p->n_rho;        // values of a block
@@ -425,8 +435,7 @@ int eval_impl(dyn_profile* p, const dyn_trace_view* t, const dyn_config* cfg, in
     return DYN_E_DEVICE;
 
   SpaceArgs a;
-  a.tab = p->d_tab; a.ml = p->d_ml; a.gridpack = p->d_gridpack;
-  a.jstart = p->d_jstart; a.n_bucket = p->n_bucket; a.bucket_scale = p->bucket_scale; a.one_step = p->one_step;
+  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step;
   a.G = p->G; a.n_tp_f = p->n_tp * p->n_f; a.n_rho = p->n_rho;
   a.cfg = p->d_cfg; a.K = K; a.tile = p->tile; a.n_tile = p->n_tile; a.n_slot = p->n_slot;
   a.tile_rows = p->d_tile_rows;
@@ -493,7 +502,7 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   p->G = d->n_class; p->n_tp = d->n_tp; p->n_f = d->n_f; p->n_rho = d->n_rho;
   p->tp.assign(d->tp, d->tp + d->n_tp);
   p->fg.assign(d->f_mhz, d->f_mhz + d->n_f);
-  p->d_tab = p->d_ml = p->d_pw0 = p->d_pfspan = p->d_gridpack = nullptr;
+  p->d_tab = p->d_ml = p->d_pw0 = p->d_pfspan = p->d_steep = p->d_gridpack = p->d_even_grid = nullptr;
   p->d_theta = nullptr;
   p->d_jstart = nullptr; p->d_tstart = nullptr; p->d_thr = nullptr; p->d_cfg = nullptr; p->d_tile_rows = nullptr;
   p->d_slo_ttft = p->d_slo_tbt = nullptr; p->d_budget = nullptr;
@@ -539,12 +548,26 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   for (int q = 0; q < d->n_rho; ++q) gridpack[1 + q] = d->rho[q];
   gridpack[d->n_rho + 1] = INFINITY;
   for (int q = 0; q + 1 < d->n_rho; ++q) gridpack[d->n_rho + 3 + q] = 1.0 / (d->rho[q + 1] - d->rho[q]);
-  // one packed row per (class, TP, f): prefill | TBT | power
+  // Evenly spaced load points: with buckets a little narrower than the spacing every point opens its own bucket, and what precedes it
+  // by a rounding may share it.  A product by a constant is monotone, so nothing else can.
+  p->rho_max = rho_max;
+  p->even_scale = (double)(d->n_rho - 1) / rho_max * (1.0 + 0x1p-40);
+  p->even = true;                            // rho[0] is 0
+  for (int q = 1; q < d->n_rho && p->even; ++q) p->even = (int)(d->rho[q] * p->even_scale) == q;
+  std::vector<double> even_grid(3 * (size_t)(d->n_rho - 1));
+  for (int q = 0; q + 1 < d->n_rho; ++q) {
+    even_grid[3 * (size_t)q] = d->rho[q];
+    even_grid[3 * (size_t)q + 1] = d->rho[q + 1] - d->rho[q];
+    even_grid[3 * (size_t)q + 2] = gridpack[d->n_rho + 3 + q];
+  }
+  // one packed row per (class, TP, f): (prefill, TBT, power) per load point
   std::vector<double> packed(3 * n_tab);
   for (size_t r = 0; r < n_row; ++r) {
-    memcpy(&packed[(3 * r + 0) * d->n_rho], d->prefill_ms_per_tok + r * d->n_rho, (size_t)d->n_rho * 8);
-    memcpy(&packed[(3 * r + 1) * d->n_rho], d->tbt_ms + r * d->n_rho, (size_t)d->n_rho * 8);
-    memcpy(&packed[(3 * r + 2) * d->n_rho], d->power_w + r * d->n_rho, (size_t)d->n_rho * 8);
+    for (size_t i = r * d->n_rho; i < (r + 1) * d->n_rho; ++i) {
+      packed[3 * i + 0] = d->prefill_ms_per_tok[i];
+      packed[3 * i + 1] = d->tbt_ms[i];
+      packed[3 * i + 2] = d->power_w[i];
+    }
   }
   p->mean_power.assign(d->n_tp, 0.0);
   for (size_t i = 0; i < n_tab; ++i) p->mean_power[(i / ((size_t)d->n_f * d->n_rho)) % d->n_tp] += d->power_w[i] / (double)(n_tab / d->n_tp);
@@ -555,6 +578,14 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
     const double* row = d->prefill_ms_per_tok + r * d->n_rho;
     pfspan[2 * r] = *std::min_element(row, row + d->n_rho);
     pfspan[2 * r + 1] = *std::max_element(row, row + d->n_rho);
+  }
+  std::vector<double> steep(n_row);
+  for (size_t r = 0; r < n_row; ++r) {
+    const double* v = d->tbt_ms + r * d->n_rho;
+    double slope = INFINITY;
+    for (int q = 0; q + 1 < d->n_rho; ++q)
+      slope = v[q + 1] - v[q] >= v[q + 1] * 0x1p-49 && v[q] > 0.0 ? std::min(slope, (v[q + 1] - v[q]) / (d->rho[q + 1] - d->rho[q])) : 0.0;
+    steep[r] = slope > 0.0 ? 0x1p-28 * v[d->n_rho - 1] / slope : INFINITY;
   }
   // per class the least ratio over its rows, as a float below the quotient by 2^-21 at least (0: no bound)
   std::vector<float> theta(p->G, 0.0f);
@@ -574,10 +605,10 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   bool ok = hip_ok(hipGetDevice(&p->device), "hipGetDevice") &&
             hip_ok(hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device), "hipDeviceGetAttribute") &&
             hip_ok(dev_alloc(&p->d_tab, 3 * n_tab), "hipMalloc") && hip_ok(dev_alloc(&p->d_ml, n_row), "hipMalloc") &&
-            hip_ok(dev_alloc(&p->d_pw0, n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_pfspan, 2 * n_row), "hipMalloc") &&
+            hip_ok(dev_alloc(&p->d_pw0, n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_pfspan, 2 * n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_steep, n_row), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_theta, (size_t)p->G), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_gridpack, gridpack.size()), "hipMalloc") &&
-            hip_ok(dev_alloc(&p->d_jstart, js.size()), "hipMalloc") &&
+            hip_ok(dev_alloc(&p->d_even_grid, even_grid.size()), "hipMalloc") && hip_ok(dev_alloc(&p->d_jstart, js.size()), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_tstart, tstart.size()), "hipMalloc") && hip_ok(dev_alloc(&p->d_thr, thr.size()), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_cfg, DYN_MAX_CONFIGS), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_tile_rows, 2 * DYN_MAX_CONFIGS + 1024), "hipMalloc") &&
@@ -595,8 +626,10 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
        hip_ok(hipMemcpyAsync(p->d_ml, d->max_load_tps, n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_pw0, pw0.data(), n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_pfspan, pfspan.data(), 2 * n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
+       hip_ok(hipMemcpyAsync(p->d_steep, steep.data(), n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_theta, theta.data(), (size_t)p->G * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_gridpack, gridpack.data(), gridpack.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
+       hip_ok(hipMemcpyAsync(p->d_even_grid, even_grid.data(), even_grid.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_jstart, js.data(), js.size() * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_tstart, tstart.data(), tstart.size() * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_thr, thr.data(), thr.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
@@ -843,8 +876,7 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
 
   TickArgs ta;
   SpaceArgs& a = ta.s;
-  a.tab = p->d_tab; a.ml = p->d_ml; a.gridpack = p->d_gridpack;
-  a.jstart = p->d_jstart; a.n_bucket = p->n_bucket; a.bucket_scale = p->bucket_scale; a.one_step = p->one_step;
+  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step;
   a.G = p->G; a.n_tp_f = p->n_tp * p->n_f; a.n_rho = p->n_rho;
   a.cfg = p->d_cfg; a.K = K; a.tile = p->tile; a.n_tile = p->n_tile; a.n_slot = p->n_slot;
   a.tile_rows = p->d_tile_rows;
@@ -857,8 +889,8 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ta.rec = (const TickRec*)(base + w.fine.rec); ta.plan = (const TickPlan*)(base + w.plan); ta.top = (const int32_t*)(base + w.top);
   ta.in = t->in_tok; ta.pool = ca.pool;
   ta.counters = (const uint32_t*)(base + w.counters); ta.slow_list = (const uint32_t*)(base + w.slow_list);
-  ta.tstart = p->d_tstart; ta.thr = p->d_thr; ta.single_point = p->single_point; ta.any_two_rows = p->any_two_rows;
-  ta.pfspan = p->d_pfspan; ta.n_cu = p->n_cu;
+  ta.any_two_rows = p->any_two_rows;
+  ta.pfspan = p->d_pfspan; ta.steep = p->d_steep; ta.n_cu = p->n_cu;
   ta.mean_depth = t->n_req * (o->pct_den - o->pct_num) / o->pct_den / cells;   // n_req and the percentile's numbers are below 2^31
   if (!hip_ok(dyn_launch_tick_space(ta, s), "tick space launch")) return DYN_E_DEVICE;
 
@@ -974,8 +1006,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
     return DYN_E_DEVICE;
 
   MixedTypeArgs ta;
-  ta.tab = p->d_tab; ta.ml = p->d_ml; ta.gridpack = p->d_gridpack;
-  ta.jstart = p->d_jstart; ta.tstart = p->d_tstart; ta.thr = p->d_thr; ta.n_bucket = p->n_bucket; ta.bucket_scale = p->bucket_scale;
+  ta.tab = p->d_tab; ta.ml = p->d_ml; ta.axis = axis_args(p);
   ta.G = p->G; ta.n_tp = p->n_tp; ta.n_f = p->n_f; ta.n_rho = p->n_rho;
   ta.slo_ttft = p->d_slo_ttft; ta.slo_tbt = p->d_slo_tbt;
   ta.rec = (const CellRec*)(base + w.cell.rec); ta.n_window = t->n_window; ta.window_s = t->window_s;
@@ -989,7 +1020,7 @@ int dyn_eval_select_mixed(dyn_profile* p, const dyn_trace_view* t, const dyn_mix
   ta.types = mp.types;
   ta.win_per_block = dyn_mixed_even_windows(ta);
   ta.type_energy = (double*)(base + w.type_energy); ta.type_f = (int8_t*)(base + w.type_f);
-  if (!hip_ok(dyn_launch_mixed_types(ta, p->single_point, s), "mixed types launch")) return DYN_E_DEVICE;
+  if (!hip_ok(dyn_launch_mixed_types(ta, s), "mixed types launch")) return DYN_E_DEVICE;
 
   MixedCombineArgs ca;
   ca.type_energy = ta.type_energy; ca.type_f = ta.type_f; ca.budget = p->d_budget;
@@ -1246,7 +1277,7 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
                                         (CellRec*)(base + w.coarse.rec), (uint8_t*)(base + w.coarse.cstat), (WsHeader*)(base + w.coarse.header), many, s), "cell aggregate launch"))
     return DYN_E_DEVICE;
   HierArgs a;
-  a.tab = p->d_tab; a.ml = p->d_ml; a.gridpack = p->d_gridpack; a.jstart = p->d_jstart; a.tstart = p->d_tstart; a.thr = p->d_thr; a.n_bucket = p->n_bucket; a.bucket_scale = p->bucket_scale;
+  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p);
   a.G = p->G; a.n_tp = p->n_tp; a.n_f = p->n_f; a.n_rho = p->n_rho; a.tp = p->d_tp;
   a.slo_ttft = p->d_slo_ttft; a.slo_tbt = p->d_slo_tbt;
   a.rec_c = (const CellRec*)(base + w.coarse.rec); a.rec_f = (const CellRec*)(fb + w.fine.rec);
@@ -1266,7 +1297,7 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     a.keep = out->keep ? out->keep : (double*)(base + w.keep); a.fwd = (double*)(base + w.fwd);
     if (!hip_ok(dyn_launch_hier_spill(a, s), "hierarchy launch")) return DYN_E_DEVICE;
   }
-  if (!hip_ok(dyn_launch_hier_shard(a, p->single_point, s), "hierarchy launch")) return DYN_E_DEVICE;
+  if (!hip_ok(dyn_launch_hier_shard(a, s), "hierarchy launch")) return DYN_E_DEVICE;
   if (c->transition_j) {        // the windows' layouts chosen together; overwrites layout_sel
     PathArgs pa;
     pa.energy = a.lay_energy; pa.flags = a.lay_flags; pa.cfg = nullptr; pa.K = c->n_layout; pa.pw0 = p->d_pw0;
@@ -1284,7 +1315,7 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     pa.sel = out->layout_sel; pa.sel_energy = (double*)(base + w.sel_energy); pa.path_cost = out->path_cost;
     if (!hip_ok(dyn_launch_path(pa, s), "path launch")) return DYN_E_DEVICE;
   }
-  if (!hip_ok(dyn_launch_hier_ticks(a, p->single_point, s), "hierarchy launch")) return DYN_E_DEVICE;
+  if (!hip_ok(dyn_launch_hier_ticks(a, s), "hierarchy launch")) return DYN_E_DEVICE;
   return DYN_OK;
 }
 

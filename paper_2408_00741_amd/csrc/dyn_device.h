@@ -78,6 +78,7 @@ __device__ __forceinline__ int64_t readlane_i64(int64_t x, int lane) {   // lane
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
+__device__ __forceinline__ double lane_f64(double x, int lane) { return __longlong_as_double((long long)readlane_i64(__double_as_longlong(x), lane)); }
 // a / b, correctly rounded, given rb = RN(1 / b): the one division routine of the library.  One multiplication and two fused
 // operations are enough for a divisor known beforehand (Brisebarre, Muller, Raina, "Accelerating correctly rounded floating-point division
 // when the divisor is known in advance", IEEE Trans. Computers 53, 2004).  Why: scale a and b to [1, 2) and let u = 2^-53, n = rb - 1/b,
@@ -143,11 +144,12 @@ __device__ __forceinline__ int find_bin(const uint32_t (&k)[PER], int64_t need, 
 }
 
 struct Lookup {          // per-thread constants of the table look-up
-  double den, rden, rho_max, bucket_scale, omu, u;
-  const double *lo, *hi;         // the configuration's two table rows: [3][n_rho] prefill, TBT, power
-  const double *rgp, *rinv;      // padded load grid and reciprocal spacings
+  double den, rden, rho_max, scale, omu, u;   // scale: buckets (DYN_AXIS_EVEN: load points) per unit of the load axis
+  const double *lo, *hi;         // the configuration's two table rows: [n_rho][3] prefill, TBT, power
+  const double* grid;            // DYN_AXIS_EVEN: [n_rho - 1][3] load point, spacing, its reciprocal; else the padded load grid
+  const double* rinv;            // reciprocal spacings
   const uint16_t* js;            // bucket index
-  const double* thr;             // SINGLE: the grid point inside each bucket
+  const double* thr;             // DYN_AXIS_SINGLE: the grid point inside each bucket
   int n_rho;
 };
 
@@ -163,50 +165,176 @@ __device__ __forceinline__ double min_num(double a, double b) {
   return r;
 }
 
-// SINGLE: every bucket of the load axis holds at most one interior grid point, so the bracket
-// is the bucket's start index plus one comparison; otherwise the bracket is searched from the
-// bucket's index.
-// The bracket of the load axis that rc = min(rho, rho_max) lies in, and its weight there.
-template <bool SINGLE>
-__device__ __forceinline__ int table_bracket(const Lookup& L, double rc, double* t) {
-  int jj;
-  if (SINGLE) {
-    const int b = (int)(rc * L.bucket_scale);
-    jj = (int)L.js[b] + (rc >= L.thr[b] ? 1 : 0);
-  } else {
-    jj = L.js[(int)(fmax(rc, 0.0) * L.bucket_scale)];
-    while (jj > 0 && L.rgp[jj + 1] > rc) --jj;
-    while (jj < L.n_rho - 2 && L.rgp[jj + 2] <= rc) ++jj;
+// A block's copy of the load axis in LDS, doubles first, then the bucket index.
+struct Axis {
+  double *grid, *rinv, *thr;     // grid: DYN_AXIS_EVEN [3 * (n_rho - 1)], else [n_rho + 2] and after it rinv [n_rho + 1]; thr: SINGLE [n_bucket + 1]
+  double* end;                   // the first double after them
+};
+template <int AXIS>
+__device__ __forceinline__ Axis place_axis(double* at, int n_rho, int n_bucket) {
+  Axis x;
+  x.grid = at;
+  x.rinv = at + (n_rho + 2);
+  x.thr = x.rinv + (n_rho + 1);
+  x.end = AXIS == DYN_AXIS_EVEN ? at + 3 * (n_rho - 1) : x.thr + (AXIS == DYN_AXIS_SINGLE ? n_bucket + 1 : 0);
+  return x;
+}
+template <int AXIS>
+__device__ __forceinline__ void stage_axis(const AxisArgs& a, const Axis& x, uint16_t* js) {
+  if (AXIS == DYN_AXIS_EVEN) {
+    for (int i = threadIdx.x; i < 3 * (a.n_rho - 1); i += blockDim.x) x.grid[i] = a.even_grid[i];
+    return;
   }
-  const double r0 = L.rgp[jj + 1], r1 = L.rgp[jj + 2];
-  *t = div_by(rc - r0, r1 - r0, L.rinv[jj + 1]);
-  return jj;
+  for (int i = threadIdx.x; i < 2 * a.n_rho + 3; i += blockDim.x) x.grid[i] = a.gridpack[i];
+  for (int i = threadIdx.x; i <= a.n_bucket; i += blockDim.x) {
+    js[i] = (uint16_t)(AXIS == DYN_AXIS_SINGLE ? a.tstart[i] : a.jstart[i]);
+    if (AXIS == DYN_AXIS_SINGLE) x.thr[i] = a.thr[i];
+  }
+}
+template <int AXIS>
+__device__ __forceinline__ void use_axis(const AxisArgs& a, const Axis& x, const uint16_t* js, Lookup* L) {
+  L->rho_max = a.rho_max;
+  L->scale = AXIS == DYN_AXIS_EVEN ? a.even_scale : a.bucket_scale;
+  L->grid = x.grid; L->rinv = x.rinv; L->thr = x.thr; L->js = js; L->n_rho = a.n_rho;
 }
 
-// Tables at (f, min(rho, rho_max)) for load `load` (>= 0): the window-level kernel's arithmetic.
+// The lesser of v and the wave-uniform s.
+__device__ __forceinline__ double min_uniform(double v, double s) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(v), "s"(s));
+  return r;
+}
+// Values that are read by here: the compiler otherwise moves their loads behind the next branch, a memory latency later.
+__device__ __forceinline__ void read_now(double& a) { asm volatile("" : "+v"(a)); }
+__device__ __forceinline__ void read_now(double& a, double& b) { asm volatile("" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void read_now(double& a, double& b, double& c, double& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+
+// The bracket of a load by the bucket index.
+template <int AXIS>
+__device__ __forceinline__ int find_index(const Lookup& L, double rc) {
+  if (AXIS == DYN_AXIS_SINGLE) {
+    const int b = (int)(rc * L.scale);
+    return (int)L.js[b] + (rc >= L.thr[b] ? 1 : 0);
+  }
+  int j = L.js[(int)(fmax(rc, 0.0) * L.scale)];
+  while (j > 0 && L.grid[j + 1] > rc) --j;
+  while (j < L.n_rho - 2 && L.grid[j + 2] <= rc) ++j;
+  return j;
+}
+// The bracket of the load axis that rc = min(rho, rho_max) lies in and its weight there; load(j) reads from the table rows what
+// the caller wants of load points j and j + 1, read() waits for it.
+// EVEN: the bracket is one multiplication away, or one less where rc is a rounding below the load point (dyn_internal.h), which a
+// wave hardly ever meets: everything is read at once and read again in that case.  SINGLE: every bucket holds at most one
+// interior grid point, so the bracket is the bucket's start index plus one comparison.  SEARCH: searched from the bucket's index.
+// Vector instructions of a look-up of three columns: 50 by SINGLE from three tables side by side, 33 by EVEN from one of triples.
+template <int AXIS, typename Load, typename Read>
+__device__ __forceinline__ double find_bracket(const Lookup& L, double rc, Load&& load, Read&& read) {
+  if (AXIS == DYN_AXIS_EVEN) {
+    int j = (int)min((uint32_t)(int)(rc * L.scale), (uint32_t)(L.n_rho - 2));   // a load below 0 goes through the search
+    const double* g = L.grid + 3 * j;
+    double r0 = g[0], d = g[1], ri = g[2];
+    load(j);
+    read_now(r0, d);
+    read_now(ri);
+    read();
+    if (__builtin_expect(__ballot(rc < r0) != 0, 0)) {
+      while (j > 0 && L.grid[3 * j] > rc) --j;
+      g = L.grid + 3 * j;
+      r0 = g[0]; d = g[1]; ri = g[2];
+      load(j);
+    }
+    return div_by(rc - r0, d, ri);
+  }
+  const int j = find_index<AXIS>(L, rc);
+  const double r0 = L.grid[j + 1], r1 = L.grid[j + 2];
+  load(j);
+  return div_by(rc - r0, r1 - r0, L.rinv[j + 1]);
+}
+
+// Tables at (f, min(rho, rho_max)) for N loads (>= 0) at once: the window-level kernel's arithmetic.  What the loads wait for in LDS
+// they wait for together.  COLUMNS: which of them.
 // TWO: both frequency rows are combined (weight 0 on the upper row leaves
 // the lower row's value unchanged, so lanes with a profiled frequency may run it too).
-template <bool SINGLE, bool TWO>
-__device__ __forceinline__ bool table_lookup(const Lookup& L, double load, double* pf, double* tb, double* pw) {
-  const double rho = div_by(load, L.den, L.rden);
-  const bool ov = rho > L.rho_max;
-  double t;
-  const int jj = table_bracket<SINGLE>(L, ov ? L.rho_max : rho, &t);
-  const double omt = 1.0 - t;
-  const int n_rho = L.n_rho;
-  double x_pf = omt * L.lo[jj] + t * L.lo[jj + 1];
-  double x_tb = omt * L.lo[n_rho + jj] + t * L.lo[n_rho + jj + 1];
-  double x_pw = omt * L.lo[2 * n_rho + jj] + t * L.lo[2 * n_rho + jj + 1];
-  if (TWO) {
-    const double b_pf = omt * L.hi[jj] + t * L.hi[jj + 1];
-    const double b_tb = omt * L.hi[n_rho + jj] + t * L.hi[n_rho + jj + 1];
-    const double b_pw = omt * L.hi[2 * n_rho + jj] + t * L.hi[2 * n_rho + jj + 1];
-    x_pf = L.omu * x_pf + L.u * b_pf;
-    x_tb = L.omu * x_tb + L.u * b_tb;
-    x_pw = L.omu * x_pw + L.u * b_pw;
+constexpr int kPrefill = 1, kTbt = 2, kPower = 4, kAllColumns = 7;
+struct Looked {
+  double v[3];                   // prefill, TBT, power: those asked for
+  bool ov;
+};
+__device__ __forceinline__ const double* at_point(const double* base, int j) { return (const double*)((const char*)base + __umul24((uint32_t)j, 24u)); }
+template <int AXIS, bool TWO, int COLUMNS, int N>
+__device__ __forceinline__ void table_lookups(const Lookup& L, const double (&load)[N], Looked (&r)[N]) {
+  double rc[N], r0[N], d[N], ri[N], a[N][6], b[N][6];
+  auto read = [&](int i, int j) {
+    if (AXIS == DYN_AXIS_EVEN) {
+      const double* g = at_point(L.grid, j);
+      r0[i] = g[0]; d[i] = g[1]; ri[i] = g[2];
+    } else {
+      r0[i] = L.grid[j + 1]; d[i] = L.grid[j + 2] - r0[i]; ri[i] = L.rinv[j + 1];
+    }
+    const double* lo = at_point(L.lo, j);
+    const double* hi = at_point(L.hi, j);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (!(COLUMNS >> c & 1)) continue;
+      a[i][2 * c] = lo[c]; a[i][2 * c + 1] = lo[c + 3];
+      if (TWO) { b[i][2 * c] = hi[c]; b[i][2 * c + 1] = hi[c + 3]; }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double rho = div_by(load[i], L.den, L.rden);
+    r[i].ov = rho > L.rho_max;
+    rc[i] = min_uniform(rho, L.rho_max);
   }
-  *pf = x_pf; *tb = x_tb; *pw = x_pw;
-  return ov;
+  if (AXIS == DYN_AXIS_EVEN) {
+    int j[N];
+    bool low = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      j[i] = (int)min((uint32_t)(int)(rc[i] * L.scale), (uint32_t)(L.n_rho - 2));
+      read(i, j[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      read_now(r0[i], d[i]);
+      read_now(ri[i]);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        if (!(COLUMNS >> c & 1)) continue;
+        read_now(a[i][2 * c], a[i][2 * c + 1]);
+        if (TWO) read_now(b[i][2 * c], b[i][2 * c + 1]);
+      }
+      low = low || rc[i] < r0[i];
+    }
+    if (__builtin_expect(__ballot(low) != 0, 0)) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        while (j[i] > 0 && L.grid[3 * j[i]] > rc[i]) --j[i];
+        read(i, j[i]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) read(i, find_index<AXIS>(L, rc[i]));
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double t = div_by(rc[i] - r0[i], d[i], ri[i]);
+    const double omt = 1.0 - t;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (!(COLUMNS >> c & 1)) continue;
+      r[i].v[c] = omt * a[i][2 * c] + t * a[i][2 * c + 1];
+      if (TWO) r[i].v[c] = L.omu * r[i].v[c] + L.u * (omt * b[i][2 * c] + t * b[i][2 * c + 1]);
+    }
+  }
+}
+template <int AXIS, bool TWO, int COLUMNS = kAllColumns>
+__device__ __forceinline__ Looked table_lookup(const Lookup& L, double load) {
+  const double one[1] = {load};
+  Looked r[1];
+  table_lookups<AXIS, TWO, COLUMNS, 1>(L, one, r);
+  return r[0];
 }
 
 }  // namespace

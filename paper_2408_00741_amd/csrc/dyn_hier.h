@@ -6,8 +6,7 @@
 
 struct HierArgs {
   // profile
-  const double* tab; const double* ml; const double* gridpack; const int32_t* jstart; const int32_t* tstart; const double* thr;
-  int32_t n_bucket; double bucket_scale;
+  const double* tab; const double* ml; AxisArgs axis;
   int32_t G, n_tp, n_f, n_rho;
   const int32_t* tp;            // DEVICE [n_tp] GPUs per instance
   const double* slo_ttft; const double* slo_tbt;
@@ -37,8 +36,8 @@ struct HierArgs {
 // fragmentation rule: node counts, kept fractions and served loads of every window and tick (before the shard level)
 hipError_t dyn_launch_hier_spill(const HierArgs& a, hipStream_t s);
 // window level: node counts, per-window layouts and (lay_energy != NULL) every layout's energy and admissibility
-hipError_t dyn_launch_hier_shard(const HierArgs& a, bool single_point, hipStream_t s);
+hipError_t dyn_launch_hier_shard(const HierArgs& a, hipStream_t s);
 // tick level: frequencies under layout_sel, energies, window totals
-hipError_t dyn_launch_hier_ticks(const HierArgs& a, bool single_point, hipStream_t s);
+hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s);
 
 #endif  // DYN_HIER_H_

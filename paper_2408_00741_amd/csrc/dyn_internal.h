@@ -45,12 +45,20 @@ struct dyn_profile {
   std::vector<double> fg;
   int device;
   // device copy of the tables, one packed row per (class, TP, f):
-  // [G][n_tp*n_f][3][n_rho] with the three tables (prefill, TBT, power) side by side
+  // [G][n_tp*n_f][n_rho][3], the three tables (prefill, TBT, power) of a load point side by side: what a look-up reads is two
+  // points, 48 bytes from one address
   double* d_tab;
   double* d_ml;   // [G][n_tp][n_f]
   double* d_pw0;  // [G][n_tp][n_f]  power at load 0 (first column of d_pw)
   double* d_pfspan;  // [G][n_tp][n_f][2]  smallest and largest prefill time of the row over the load axis
   float* d_theta;    // [G]  least ratio smallest / largest prefill time over the class's rows, rounded down
+  // [G][n_tp][n_f]: the utilization from which TBT at a load is surely above TBT at any load smaller by a part of DYN_TICK_NEAR, roundings
+  // and the clamp at the last load point included (+inf: a row that does not rise everywhere).  Two values of an interpolation are off
+  // by 6 u v each (u = 2^-53, v the larger table value), so a row whose least slope is s tells loads x and x (1 - 2^-20) apart where
+  // s x 2^-20 > 12 u v; 2^-28 v / s leaves a factor of two.  At the last load point the weights are 0 and 1 and the value is the
+  // table's; below it no value passes that: with a weight of 1/2 or more on the upper point the other weight is exact and the sum stays
+  // short of half an ulp above the table's value, with less it is 12 u v below where the points differ by 16 u v.
+  double* d_steep;
   std::vector<double> mean_power;   // [n_tp] watts of an instance, over classes, frequencies and loads
   bool prefill_flat; // that ratio is 0.98 or more in every class
   // load grid for the kernels: [-inf, rho[0..n_rho-1], +inf] followed by
@@ -69,6 +77,12 @@ struct dyn_profile {
   int32_t* d_tstart;  // [n_bucket + 1]
   double* d_thr;      // [n_bucket + 1]
   bool single_point;
+  // Load points that lie (almost) evenly from 0 on: (int)(rho[i] * even_scale) == i for every one, so that for any load x the
+  // largest i with rho[i] <= x is (int)(x * even_scale), or one less where x is a rounding below the next point.
+  bool even;
+  double even_scale;
+  double* d_even_grid;  // [n_rho - 1][3] load point, spacing, its reciprocal
+  double rho_max;       // the last load point
   // plan: candidate list
   std::vector<dyn_config> cfg_host;   // what d_cfg currently holds
   DevCfg* d_cfg;                      // [DYN_MAX_CONFIGS]
@@ -144,9 +158,23 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
 size_t dyn_cell_many_bytes(int64_t cells);
 #define DYN_CELL_MANY_MAX ((8u << 20) + 16384u)   // the most it can be
 
+// How a kernel finds the bracket of a load: the load axis and which of its forms hold.
+enum { DYN_AXIS_SEARCH = 0, DYN_AXIS_SINGLE = 1, DYN_AXIS_EVEN = 2 };
+struct AxisArgs {
+  const double* gridpack; const double* even_grid;
+  const int32_t* jstart; const int32_t* tstart; const double* thr;
+  int32_t n_rho, n_bucket; double bucket_scale, even_scale, rho_max;
+  bool single_point, even;
+};
+inline int dyn_axis(const AxisArgs& a) { return a.even ? DYN_AXIS_EVEN : a.single_point ? DYN_AXIS_SINGLE : DYN_AXIS_SEARCH; }
+// LDS of a block's copy of the axis: doubles, and the bucket index at the end of the block's LDS
+inline size_t dyn_axis_lds(const AxisArgs& a, int axis) {
+  if (axis == DYN_AXIS_EVEN) return (size_t)3 * (a.n_rho - 1) * sizeof(double);
+  return ((size_t)2 * a.n_rho + 3 + (axis == DYN_AXIS_SINGLE ? a.n_bucket + 1 : 0)) * sizeof(double) + ((size_t)a.n_bucket + 1) * sizeof(uint16_t) + 8;
+}
+
 struct SpaceArgs {
-  const double* tab; const double* ml; const double* gridpack;
-  const int32_t* jstart; int32_t n_bucket; double bucket_scale; bool one_step;
+  const double* tab; const double* ml; AxisArgs axis; bool one_step;
   int32_t G, n_tp_f /* n_tp*n_f */, n_rho;
   const DevCfg* cfg; int32_t K;
   int32_t tile, n_tile, n_slot;       // configurations per tile, tiles, LDS slots per tile

@@ -14,8 +14,7 @@ struct MixedTypes {               // by value in the kernel arguments
 };
 
 struct MixedTypeArgs {            // per-type least energies over the admissible frequencies
-  const double* tab; const double* ml; const double* gridpack;
-  const int32_t* jstart; const int32_t* tstart; const double* thr; int32_t n_bucket; double bucket_scale;
+  const double* tab; const double* ml; AxisArgs axis;
   int32_t G, n_tp, n_f, n_rho;
   const double* slo_ttft; const double* slo_tbt;
   const CellRec* rec; int32_t n_window; int32_t win_per_block; double window_s;
@@ -25,7 +24,7 @@ struct MixedTypeArgs {            // per-type least energies over the admissible
   int8_t* type_f;                         // [cells][n_entry]
 };
 int32_t dyn_mixed_even_windows(const MixedTypeArgs& a);   // win_per_block, or up to a quarter more where that leaves fewer lanes idle
-hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, bool single_point, hipStream_t s);
+hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, hipStream_t s);
 
 struct MixedCombineArgs {         // least total energy over the assignments of instances and shares
   const double* type_energy; const int8_t* type_f;

@@ -6,6 +6,7 @@
 
 #define DYN_TICK_MAX 64     // ticks per window: a wave's lane holds a tick in the cell kernel
 #define DYN_TICK_FAST 16    // percentile depth j up to which the evaluation kernel keeps a sorted list in registers
+#define DYN_TICK_NEAR 0x1p-20   // ticks whose loads come within this part of the cell's largest are near it (dyn_profile.d_steep)
 #define DYN_TICK_LONG 4096  // requests of a cell from which many blocks share it
 #define DYN_TICK_SLOT_WORDS 2048
 #define DYN_TICK_SLOTS_MAX 2048
@@ -77,10 +78,11 @@ struct TickArgs {
   const int32_t* top;      // [n_req]
   const int32_t* in;       // [n_req] input lengths of the trace sorted by tick (DYN_TP_RAW cells)
   const uint32_t* pool;    // the tables of DYN_TP_TABLE cells
-  const int32_t* tstart; const double* thr; bool single_point;   // threshold form of the bucket index
   bool any_two_rows;
+  int32_t win_long, n_long;   // of the walk without lists: its first n_long blocks of a (class, tile) take win_long windows each
   int32_t n_cu;               // compute units of the device (0: unknown)
   int64_t mean_depth;         // the percentile's rank from the top in a cell of mean length
+  const double* steep;        // [G][n_tp_f] dyn_profile.d_steep
   const double* pfspan;       // [G][n_tp_f][2] smallest and largest prefill time of every table row
   const uint32_t* counters;   // [1]: number of cells on slow_list, [3]: number of cells walked with lists
   const uint32_t* slow_list;  // [cells] cells left to the general kernel

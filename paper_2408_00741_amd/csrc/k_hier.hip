@@ -27,47 +27,48 @@ constexpr int kShardWaves = 4;          // (window, class) cells per block of th
 constexpr int kFreqThreads = 256;
 constexpr int kFreqChunk = 4;           // look-ups a thread of the frequency kernel has in flight
 constexpr int kSpillLds = 48 * 1024;    // an epoch's window loads are staged in LDS when they fit in this
+constexpr size_t kAxisLds = 32 * 1024;  // evenly spaced points are staged in triples up to this
 constexpr int kSpillRun = 8;            // classes whose tick loads a thread fetches ahead of the chain
 
-struct Looked { double pf, tb, pw; bool ov; };
+struct Row { double pf, tb, pw; bool ov; };
 
 // The load axis (grid points, reciprocal spacings, bucket index) is the same for every class and small.  The
-// frequency kernel keeps a copy in LDS, which takes six of a look-up's thirteen gathers off the vector memory
+// frequency kernel keeps a copy in LDS, which takes half of a look-up's gathers off the vector memory
 // path (37 -> 30 us for a day of ticks); the shard kernel, whose blocks live for one look-up per lane, reads it
 // from global memory (with the copy its blocks start a memory round trip later: 30 us instead of 26 us).
-// LDS: [padded grid and reciprocal spacings 2 n_rho + 3] [SINGLE: grid point per bucket n_bucket + 1] [bucket index, 16-bit]
-struct Axis { const double* pack; const double* thr; const uint16_t* js; const int32_t* js_global; };   // js == nullptr: js_global
-template <bool SINGLE>
-__device__ __forceinline__ Axis global_axis(const HierArgs& a) {
-  Axis x;
-  x.pack = a.gridpack; x.thr = a.thr; x.js = nullptr; x.js_global = SINGLE ? a.tstart : a.jstart;
+struct LoadAxis { const double *grid, *rinv, *thr; const uint16_t* js; const int32_t* js_global; };   // js == nullptr: js_global
+template <int AXIS>
+__device__ __forceinline__ LoadAxis global_axis(const HierArgs& a) {
+  LoadAxis x;
+  x.grid = AXIS == DYN_AXIS_EVEN ? a.axis.even_grid : a.axis.gridpack; x.rinv = a.axis.gridpack + a.n_rho + 2; x.thr = a.axis.thr;
+  x.js = nullptr; x.js_global = AXIS == DYN_AXIS_SINGLE ? a.axis.tstart : a.axis.jstart;
   return x;
 }
-template <bool SINGLE>
-__device__ __forceinline__ Axis stage_axis(const HierArgs& a, double* smem) {
-  double* s_pack = smem;
-  double* s_thr = s_pack + 2 * a.n_rho + 3;
-  uint16_t* s_js = (uint16_t*)(s_thr + (SINGLE ? a.n_bucket + 1 : 0));
-  for (int i = threadIdx.x; i < 2 * a.n_rho + 3; i += blockDim.x) s_pack[i] = a.gridpack[i];
-  for (int i = threadIdx.x; i <= a.n_bucket; i += blockDim.x) {
-    s_js[i] = (uint16_t)(SINGLE ? a.tstart[i] : a.jstart[i]);
-    if (SINGLE) s_thr[i] = a.thr[i];
-  }
+template <int AXIS>
+__device__ __forceinline__ LoadAxis lds_axis(const HierArgs& a, double* smem) {
+  const Axis s = place_axis<AXIS>(smem, a.n_rho, a.axis.n_bucket);
+  uint16_t* s_js = (uint16_t*)s.end;
+  stage_axis<AXIS>(a.axis, s, s_js);
   __syncthreads();
-  Axis x;
-  x.pack = s_pack; x.thr = s_thr; x.js = s_js; x.js_global = nullptr;
+  LoadAxis x;
+  x.grid = s.grid; x.rinv = s.rinv; x.thr = s.thr; x.js = s_js; x.js_global = nullptr;
   return x;
 }
 
 // Bracket of a clamped load fraction rc: largest grid index i <= n_rho-2 with grid[i] <= rc.
-// SINGLE: no bucket holds more than one interior grid point; the index is then the number of interior
-// points in lower buckets plus one comparison with the bucket's own point.
-template <bool SINGLE>
-__device__ __forceinline__ int bracket(const HierArgs& a, const Axis& x, double rc) {
-  const double* grid = x.pack + 1;
-  const int b = min((int)(fmax(rc, 0.0) * a.bucket_scale), a.n_bucket);
+// EVEN: one multiplication, or one less where rc is a rounding below the point.  SINGLE: no bucket holds more than one interior
+// grid point; the index is then the number of interior points in lower buckets plus one comparison with the bucket's own point.
+template <int AXIS>
+__device__ __forceinline__ int bracket(const HierArgs& a, const LoadAxis& x, double rc) {
+  if (AXIS == DYN_AXIS_EVEN) {
+    int j = (int)min((uint32_t)(int)(rc * a.axis.even_scale), (uint32_t)(a.n_rho - 2));
+    while (j > 0 && x.grid[3 * j] > rc) --j;
+    return j;
+  }
+  const double* grid = x.grid + 1;
+  const int b = min((int)(fmax(rc, 0.0) * a.axis.bucket_scale), a.axis.n_bucket);
   const int j0 = x.js ? (int)x.js[b] : x.js_global[b];
-  if (SINGLE) return j0 + (rc >= x.thr[b] ? 1 : 0);
+  if (AXIS == DYN_AXIS_SINGLE) return j0 + (rc >= x.thr[b] ? 1 : 0);
   int j = j0;
   while (j > 0 && grid[j] > rc) --j;
   while (j < a.n_rho - 2 && grid[j + 1] <= rc) ++j;
@@ -75,28 +76,34 @@ __device__ __forceinline__ int bracket(const HierArgs& a, const Axis& x, double 
 }
 
 // Linear interpolation in table row `row` (class, TP, frequency) between grid points j and j+1.
-__device__ __forceinline__ void interpolate(const HierArgs& a, const Axis& x, size_t row, int j, double rc, Looked* r) {
-  const double* grid = x.pack + 1;
-  const double* rinv = x.pack + a.n_rho + 3;                 // RN(1 / spacing)
-  const double g0 = grid[j], g1 = grid[j + 1];
-  const double t = div_by(rc - g0, g1 - g0, rinv[j]);
+template <int AXIS>
+__device__ __forceinline__ void interpolate(const HierArgs& a, const LoadAxis& x, size_t row, int j, double rc, Row* r) {
+  double t;
+  if (AXIS == DYN_AXIS_EVEN) {
+    const double* g = x.grid + 3 * j;
+    t = div_by(rc - g[0], g[1], g[2]);
+  } else {
+    const double* grid = x.grid + 1;
+    const double g0 = grid[j], g1 = grid[j + 1];
+    t = div_by(rc - g0, g1 - g0, x.rinv[j + 1]);             // RN(1 / spacing)
+  }
   const double omt = 1.0 - t;
-  const double* v = a.tab + row * 3 * a.n_rho;
-  r->pf = omt * v[j] + t * v[j + 1];
-  r->tb = omt * v[a.n_rho + j] + t * v[a.n_rho + j + 1];
-  r->pw = omt * v[2 * a.n_rho + j] + t * v[2 * a.n_rho + j + 1];
+  const double* v = a.tab + (row * a.n_rho + j) * 3;
+  r->pf = omt * v[0] + t * v[3];
+  r->tb = omt * v[1] + t * v[4];
+  r->pw = omt * v[2] + t * v[5];
 }
 
 // Row (g, ti, f) at per-instance load `load / n`; values at the last grid point when the load is beyond it.
-template <bool SINGLE>
-__device__ __forceinline__ Looked look_up(const HierArgs& a, const Axis& x, int g, int ti, int f, double load, double n) {
+template <int AXIS>
+__device__ __forceinline__ Row look_up(const HierArgs& a, const LoadAxis& x, int g, int ti, int f, double load, double n) {
   const size_t row = ((size_t)g * a.n_tp + ti) * a.n_f + f;
   const double rho = load / (n * a.ml[row]);
-  const double rho_max = x.pack[a.n_rho];
-  Looked r;
+  const double rho_max = a.axis.rho_max;
+  Row r;
   r.ov = rho > rho_max;
   const double rc = r.ov ? rho_max : rho;
-  interpolate(a, x, row, bracket<SINGLE>(a, x, rc), rc, &r);
+  interpolate<AXIS>(a, x, row, bracket<AXIS>(a, x, rc), rc, &r);
   return r;
 }
 
@@ -122,9 +129,9 @@ __device__ __forceinline__ double row_max_f64(double v) {
 }
 
 // One wave per (window, class); lanes stride the layouts; the lowest index wins equal energies.
-template <bool SINGLE>
+template <int AXIS>
 __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierArgs a) {
-  const Axis x = global_axis<SINGLE>(a);
+  const LoadAxis x = global_axis<AXIS>(a);
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int64_t cell = (int64_t)blockIdx.x * kShardWaves + threadIdx.x / DYN_WAVE;
   if (cell >= (int64_t)a.n_window * a.G) return;
@@ -144,7 +151,7 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
     for (int i = e0 + lane; i < e1; i += DYN_WAVE) peak = fmax(peak, a.rec_c[(size_t)i * a.G + g].load);
     peak = wave_max_f64(peak);
     const int inst = max(1, a.gpus_per_node / a.tp[a.tp_ref]);
-    const double ml_node = ((double)inst * a.ml[((size_t)g * a.n_tp + a.tp_ref) * a.n_f + a.f_ref]) * a.gridpack[a.n_rho];
+    const double ml_node = ((double)inst * a.ml[((size_t)g * a.n_tp + a.tp_ref) * a.n_f + a.f_ref]) * a.axis.rho_max;
     const double q = ceil(peak / ml_node);
     nodes = q < 1.0 ? 1 : (q > 2147483647.0 ? 2147483647 : (int32_t)q);
     if (w == e0 && lane == 0) a.nodes[(size_t)e * a.G + g] = nodes;
@@ -159,7 +166,7 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
     bool ok = (int64_t)n * a.tp[ti] <= budget;
     double en = __builtin_inf();
     if (ok) {
-      const Looked r = look_up<SINGLE>(a, x, g, ti, a.f_ref, load, (double)n);
+      const Row r = look_up<AXIS>(a, x, g, ti, a.f_ref, load, (double)n);
       ok = !(r.ov || rec.xp99 * r.pf > slo_t || r.tb * rec.nonempty > slo_b);
       en = ((double)n * r.pw) * a.window_s;
     }
@@ -180,10 +187,10 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
 
 // One thread per (window, tick, class).  A block stays within one class: its threads then read the same
 // few table rows, and a wave's look-up touches a handful of cache lines instead of one per lane.
-template <bool SINGLE>
+template <int AXIS>
 __global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a) {
   extern __shared__ double s_axis[];
-  const Axis x = stage_axis<SINGLE>(a, s_axis);
+  const LoadAxis x = lds_axis<AXIS>(a, s_axis);
   const int g = blockIdx.x % a.G;
   const int64_t wt = (int64_t)(blockIdx.x / a.G) * kFreqThreads + threadIdx.x;   // window * n_tick + tick
   if (wt >= (int64_t)a.n_window * a.n_tick) return;
@@ -202,7 +209,7 @@ __global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a) {
   const int n = a.lay_n[l], ti = a.lay_tp[l];
   const double nd = (double)n;
   const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
-  const double rho_max = x.pack[a.n_rho];
+  const double rho_max = a.axis.rho_max;
   const size_t row0 = ((size_t)g * a.n_tp + ti) * a.n_f;
   int bf = -1;
   double bp = __builtin_inf(), pw_ref = 0.0;
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a) {
     double rc[kFreqChunk];
     bool ov[kFreqChunk];
     int j[kFreqChunk];
-    Looked r[kFreqChunk];
+    Row r[kFreqChunk];
 #pragma unroll
     for (int c = 0; c < kFreqChunk; ++c) {                   // level 1: capacities
       const int fi = min(f0 + c, a.n_f - 1);
@@ -219,10 +226,10 @@ __global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a) {
       rc[c] = ov[c] ? rho_max : rho;
     }
 #pragma unroll
-    for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<SINGLE>(a, x, rc[c]);   // level 2: bucket index
+    for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(a, x, rc[c]);   // level 2: bucket index
 #pragma unroll
     for (int c = 0; c < kFreqChunk; ++c)                     // level 3: grid points and table values
-      interpolate(a, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
+      interpolate<AXIS>(a, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
 #pragma unroll
     for (int c = 0; c < kFreqChunk; ++c) {                   // ascending frequency: the lowest wins equal powers
       const int fi = f0 + c;
@@ -255,7 +262,7 @@ __global__ __launch_bounds__(DYN_WAVE) void hier_spill_epoch_kernel(HierArgs a) 
   const int e0 = e * a.epoch_windows, e1 = min(a.n_window, e0 + a.epoch_windows);
   const int G = a.G;
   const int inst = max(1, a.gpus_per_node / a.tp[a.tp_ref]);
-  const double rho_max = a.gridpack[a.n_rho];
+  const double rho_max = a.axis.rho_max;
   const double guard = 1.0 - 0x1p-40;
   double* s_load = s_spill;
   double* s_cap = s_spill + (size_t)min(a.epoch_windows, a.n_window) * G;
@@ -389,8 +396,16 @@ __global__ __launch_bounds__(64) void hier_sum_kernel(HierArgs a) {
   }
 }
 
-size_t axis_lds(const HierArgs& a, bool single) {         // at most 4097 buckets: 42 KB
-  return ((size_t)2 * a.n_rho + 3 + (single ? a.n_bucket + 1 : 0)) * sizeof(double) + ((size_t)a.n_bucket + 1) * sizeof(uint16_t) + 8;
+// Evenly spaced points beyond what LDS holds in triples keep the other forms (at most 4097 buckets: 42 KB and the points).
+int hier_axis(const HierArgs& a) {
+  const int axis = dyn_axis(a.axis);
+  return axis != DYN_AXIS_EVEN || dyn_axis_lds(a.axis, axis) <= kAxisLds ? axis : a.axis.single_point ? DYN_AXIS_SINGLE : DYN_AXIS_SEARCH;
+}
+template <typename F>
+void with_axis(int axis, F&& f) {
+  if (axis == DYN_AXIS_EVEN) f(std::integral_constant<int, DYN_AXIS_EVEN>());
+  else if (axis == DYN_AXIS_SINGLE) f(std::integral_constant<int, DYN_AXIS_SINGLE>());
+  else f(std::integral_constant<int, DYN_AXIS_SEARCH>());
 }
 
 }  // namespace
@@ -407,21 +422,24 @@ hipError_t dyn_launch_hier_spill(const HierArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t dyn_launch_hier_shard(const HierArgs& a, bool single_point, hipStream_t s) {
+hipError_t dyn_launch_hier_shard(const HierArgs& a, hipStream_t s) {
   const int64_t cells = (int64_t)a.n_window * a.G;
   const unsigned shard_blocks = (unsigned)((cells + kShardWaves - 1) / kShardWaves);
   DynTimed timed(DYN_K_HIER, s);
-  if (single_point) hipLaunchKernelGGL(hier_shard_kernel<true>, dim3(shard_blocks), dim3(kShardWaves * DYN_WAVE), 0, s, a);
-  else hipLaunchKernelGGL(hier_shard_kernel<false>, dim3(shard_blocks), dim3(kShardWaves * DYN_WAVE), 0, s, a);
+  with_axis(dyn_axis(a.axis), [&](auto x) {
+    hipLaunchKernelGGL(hier_shard_kernel<decltype(x)::value>, dim3(shard_blocks), dim3(kShardWaves * DYN_WAVE), 0, s, a);
+  });
   return hipGetLastError();
 }
 
-hipError_t dyn_launch_hier_ticks(const HierArgs& a, bool single_point, hipStream_t s) {
+hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s) {
   const int64_t ticks = (int64_t)a.n_window * a.n_tick;
   const unsigned freq_blocks = (unsigned)(((ticks + kFreqThreads - 1) / kFreqThreads) * a.G);
   DynTimed timed(DYN_K_HIER, s);
-  if (single_point) hipLaunchKernelGGL(hier_freq_kernel<true>, dim3(freq_blocks), dim3(kFreqThreads), axis_lds(a, true), s, a);
-  else hipLaunchKernelGGL(hier_freq_kernel<false>, dim3(freq_blocks), dim3(kFreqThreads), axis_lds(a, false), s, a);
+  const int axis = hier_axis(a);
+  with_axis(axis, [&](auto x) {
+    hipLaunchKernelGGL(hier_freq_kernel<decltype(x)::value>, dim3(freq_blocks), dim3(kFreqThreads), dyn_axis_lds(a.axis, axis), s, a);
+  });
   hipLaunchKernelGGL(hier_sum_kernel, dim3((unsigned)a.n_window), dim3(64), (size_t)a.G * sizeof(double), s, a);
   return hipGetLastError();
 }

@@ -32,9 +32,8 @@ __device__ __forceinline__ uint32_t row_min_u32(uint32_t x) {
 // Block = (run of windows, class, type).  A thread is (entry, frequency): 16 entries of 16
 // frequency lanes per pass over the type's entries.  The type's table rows (all frequencies)
 // sit in LDS.
-// LDS: [rows n_f*3*n_rho] [padded load grid n_rho+2] [reciprocal spacings n_rho+1]
-//      [SINGLE: grid point per bucket n_bucket+1] [cell records win_per_block] [bucket index (16-bit)]
-template <bool SINGLE>
+// LDS: [rows n_f*3*n_rho] [load axis] [cell records win_per_block] [bucket index (16-bit)]
+template <int AXIS>
 __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
   extern __shared__ double smem[];
   const int n_rho = a.n_rho, n_f = a.n_f, S = a.n_share;
@@ -50,11 +49,9 @@ __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
   // rows one double apart from a multiple of the bank width: the 16 frequency lanes of an entry read
   // the same load bracket of 16 different rows, which would otherwise fall into one LDS bank
   const int row_stride = (3 * n_rho) | 1;
-  double* s_tab = smem;                                        // [n_f][row_stride]: prefill, TBT, power
-  double* s_rgp = s_tab + (size_t)n_f * row_stride;
-  double* s_rinv = s_rgp + (n_rho + 2);
-  double* s_thr = s_rinv + (n_rho + 1);
-  CellRec* s_rec = (CellRec*)(s_thr + (SINGLE ? a.n_bucket + 1 : 0));
+  double* s_tab = smem;                                        // [n_f][row_stride]: prefill, TBT, power of every load point
+  const Axis axis = place_axis<AXIS>(s_tab + (size_t)n_f * row_stride, n_rho, a.axis.n_bucket);
+  CellRec* s_rec = (CellRec*)axis.end;
   uint16_t* s_js = (uint16_t*)(s_rec + a.win_per_block);
 
   {
@@ -64,11 +61,7 @@ __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
       s_tab[r * row_stride + (q - r * 3 * n_rho)] = src[q];
     }
   }
-  for (int q = threadIdx.x; q < 2 * n_rho + 3; q += blockDim.x) s_rgp[q] = a.gridpack[q];
-  for (int q = threadIdx.x; q <= a.n_bucket; q += blockDim.x) {
-    s_js[q] = (uint16_t)(SINGLE ? a.tstart[q] : a.jstart[q]);
-    if (SINGLE) s_thr[q] = a.thr[q];
-  }
+  stage_axis<AXIS>(a.axis, axis, s_js);
   for (int q = threadIdx.x; q < w1 - w0; q += blockDim.x) s_rec[q] = a.rec[(size_t)(w0 + q) * a.G + g];
   __syncthreads();
 
@@ -80,9 +73,7 @@ __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
   const double slo_ttft = a.slo_ttft[g], slo_tbt = a.slo_tbt[g];
   Lookup L;
   L.u = 0.0; L.omu = 1.0;
-  L.rho_max = s_rgp[n_rho];
-  L.bucket_scale = a.bucket_scale;
-  L.rgp = s_rgp; L.rinv = s_rinv; L.js = s_js; L.thr = s_thr; L.n_rho = n_rho;
+  use_axis<AXIS>(a.axis, axis, s_js, &L);
   L.lo = s_tab + (size_t)fc * row_stride;
   L.hi = L.lo;
   const double sd = (double)S;
@@ -98,12 +89,11 @@ __global__ __launch_bounds__(256) void mixed_type_kernel(MixedTypeArgs a) {
     for (int w = w0; w < w1; ++w) {
       const CellRec rec = s_rec[w - w0];
       const double ls = div_by(rec.load * ad, sd, a.r_share);      // the part of the load this type takes
-      double pf, tb, pw;
-      const bool ov = table_lookup<SINGLE, false>(L, ls, &pf, &tb, &pw);
-      const double en = (nd * pw) * a.window_s;
-      const double p_ttft = rec.xp99 * pf;
-      const double p_tbt = tb * rec.nonempty;
-      const bool ok = f_ok && !ov && !(p_ttft > slo_ttft) && !(p_tbt > slo_tbt);
+      const Looked r = table_lookup<AXIS, false>(L, ls);
+      const double en = (nd * r.v[2]) * a.window_s;
+      const double p_ttft = rec.xp99 * r.v[0];
+      const double p_tbt = r.v[1] * rec.nonempty;
+      const bool ok = f_ok && !r.ov && !(p_ttft > slo_ttft) && !(p_tbt > slo_tbt);
       // least energy of the row's admissible lanes (energies are >= +0: their bits order as integers),
       // lowest frequency among equals; +inf when no lane is admissible
       const uint64_t bits = ok ? (uint64_t)__double_as_longlong(en) : 0x7FF0000000000000ull;
@@ -132,7 +122,7 @@ __host__ __device__ __forceinline__ int own_entries(int n_max, int S) { return n
 // quotient, table value and comparison is the same to the last bit and the energy exactly twice.  Only the entries that are not twice
 // another are looked up, three of four with 8 shares: 36 000 cells, 28 instances and 8 shares 282 us a call, 255 so.
 // LDS: as above, then [capacity n_max*n_f] [its reciprocal n_max*n_f]
-template <bool SINGLE>
+template <int AXIS>
 __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
   extern __shared__ double smem[];
   const int n_rho = a.n_rho, n_f = a.n_f, S = a.n_share;
@@ -148,10 +138,8 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
 
   const int row_stride = (3 * n_rho) | 1;          // see mixed_type_kernel
   double* s_tab = smem;
-  double* s_rgp = s_tab + (size_t)n_f * row_stride;
-  double* s_rinv = s_rgp + (n_rho + 2);
-  double* s_thr = s_rinv + (n_rho + 1);
-  CellRec* s_rec = (CellRec*)(s_thr + (SINGLE ? a.n_bucket + 1 : 0));
+  const Axis axis = place_axis<AXIS>(s_tab + (size_t)n_f * row_stride, n_rho, a.axis.n_bucket);
+  CellRec* s_rec = (CellRec*)axis.end;
   double* s_den = (double*)(s_rec + a.win_per_block);            // [n_max][n_f]
   double* s_rden = s_den + (size_t)n_max * n_f;
   uint16_t* s_js = (uint16_t*)(s_rden + (size_t)n_max * n_f);
@@ -163,11 +151,7 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
       s_tab[r * row_stride + (q - r * 3 * n_rho)] = src[q];
     }
   }
-  for (int q = threadIdx.x; q < 2 * n_rho + 3; q += blockDim.x) s_rgp[q] = a.gridpack[q];
-  for (int q = threadIdx.x; q <= a.n_bucket; q += blockDim.x) {
-    s_js[q] = (uint16_t)(SINGLE ? a.tstart[q] : a.jstart[q]);
-    if (SINGLE) s_thr[q] = a.thr[q];
-  }
+  stage_axis<AXIS>(a.axis, axis, s_js);
   for (int q = threadIdx.x; q < w1 - w0; q += blockDim.x) s_rec[q] = a.rec[(size_t)(w0 + q) * a.G + g];
   for (int q = threadIdx.x; q < n_max * n_f; q += blockDim.x) {
     const int n = q / n_f + 1, f = q - (n - 1) * n_f;
@@ -180,9 +164,7 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
   const double slo_ttft = a.slo_ttft[g], slo_tbt = a.slo_tbt[g];
   Lookup L;
   L.u = 0.0; L.omu = 1.0;
-  L.rho_max = s_rgp[n_rho];
-  L.bucket_scale = a.bucket_scale;
-  L.rgp = s_rgp; L.rinv = s_rinv; L.js = s_js; L.thr = s_thr; L.n_rho = n_rho;
+  use_axis<AXIS>(a.axis, axis, s_js, &L);
   const double sd = (double)S;
   // entries that are not twice another: of every two instance counts all shares of the odd one, the odd shares of the even one
   const int per_two = S + (S + 1) / 2, n_own = own_entries(n_max, S);
@@ -203,14 +185,17 @@ __global__ __launch_bounds__(256) void mixed_type_walk_kernel(MixedTypeArgs a) {
       const double rho = div_by(ls, den[f], rden[f]);
       bool live = !(rho > L.rho_max);
       if (__ballot(live) == 0) continue;
-      double t;
-      const int jj = table_bracket<SINGLE>(L, live ? rho : L.rho_max, &t);
+      double p0, p1;
+      const double* tab;
+      const double t = find_bracket<AXIS>(L, min_uniform(rho, L.rho_max), [&](int j) {
+        tab = s_tab + (size_t)f * row_stride + 3 * j;
+        p0 = tab[2]; p1 = tab[5];
+      }, [&] { read_now(p0, p1); });
       const double omt = 1.0 - t;
-      const double* tab = s_tab + (size_t)f * row_stride + jj;
-      const double en = (nd * (omt * tab[2 * n_rho] + t * tab[2 * n_rho + 1])) * a.window_s;
+      const double en = (nd * (omt * p0 + t * p1)) * a.window_s;
       live = live && en < best;
       if (__ballot(live) == 0) continue;
-      const double pf = omt * tab[0] + t * tab[1], tb = omt * tab[n_rho] + t * tab[n_rho + 1];
+      const double pf = omt * tab[0] + t * tab[3], tb = omt * tab[1] + t * tab[4];
       if (live && !(rec.xp99 * pf > slo_ttft) && !(tb * rec.nonempty > slo_tbt)) { best = en; bf = f; }
     }
     const size_t o = ((size_t)(w0 + dw) * a.G + g) * n_entry + a.types.off[i];
@@ -443,14 +428,13 @@ __global__ __launch_bounds__(DYN_WAVE) void mixed_rows_kernel(MixedCombineArgs a
   }
 }
 
-size_t type_lds(const MixedTypeArgs& a, bool single) {
-  return ((size_t)a.n_f * ((3 * a.n_rho) | 1) + 2 * a.n_rho + 3 + (single ? a.n_bucket + 1 : 0)) * sizeof(double) +
-         (size_t)a.win_per_block * sizeof(CellRec) + ((size_t)a.n_bucket + 1) * sizeof(uint16_t) + 8;
+size_t type_lds(const MixedTypeArgs& a, int axis) {
+  return (size_t)a.n_f * ((3 * a.n_rho) | 1) * sizeof(double) + dyn_axis_lds(a.axis, axis) + (size_t)a.win_per_block * sizeof(CellRec);
 }
-size_t type_walk_lds(const MixedTypeArgs& a, bool single) {   // plus the capacities of the type with most instances
+size_t type_walk_lds(const MixedTypeArgs& a, int axis) {   // plus the capacities of the type with most instances
   int n_max = 0;
   for (int i = 0; i < a.n_tp; ++i) n_max = std::max(n_max, a.types.n_max[i]);
-  return type_lds(a, single) + (size_t)2 * n_max * a.n_f * sizeof(double);
+  return type_lds(a, axis) + (size_t)2 * n_max * a.n_f * sizeof(double);
 }
 
 }  // namespace
@@ -473,22 +457,24 @@ int32_t dyn_mixed_even_windows(const MixedTypeArgs& a) {
   return best;
 }
 
-hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, bool single_point, hipStream_t s) {
+hipError_t dyn_launch_mixed_types(const MixedTypeArgs& a, hipStream_t s) {
   const int n_chunk = (a.n_window + a.win_per_block - 1) / a.win_per_block;
   const dim3 grid((unsigned)((size_t)n_chunk * a.G * a.n_tp)), block(256);
-  bool single = single_point;
-  if (single && type_lds(a, true) > DYN_LDS_BUDGET) single = false;
-  const size_t lds = type_lds(a, single);
+  int axis = dyn_axis(a.axis);
+  if (type_lds(a, axis) > DYN_LDS_BUDGET) axis = DYN_AXIS_SEARCH;
+  const size_t lds = type_lds(a, axis);
   if (lds > DYN_LDS_BUDGET) return hipErrorInvalidValue;
   DynTimed timed(DYN_K_MIXED_TYPES, s);
-  const size_t lds_walk = type_walk_lds(a, single);
+  const size_t lds_walk = type_walk_lds(a, axis);
   if (lds_walk <= DYN_LDS_BUDGET) {
-    if (single) hipLaunchKernelGGL(mixed_type_walk_kernel<true>, grid, block, lds_walk, s, a);
-    else hipLaunchKernelGGL(mixed_type_walk_kernel<false>, grid, block, lds_walk, s, a);
+    if (axis == DYN_AXIS_EVEN) hipLaunchKernelGGL(mixed_type_walk_kernel<DYN_AXIS_EVEN>, grid, block, lds_walk, s, a);
+    else if (axis == DYN_AXIS_SINGLE) hipLaunchKernelGGL(mixed_type_walk_kernel<DYN_AXIS_SINGLE>, grid, block, lds_walk, s, a);
+    else hipLaunchKernelGGL(mixed_type_walk_kernel<DYN_AXIS_SEARCH>, grid, block, lds_walk, s, a);
     return hipGetLastError();
   }
-  if (single) hipLaunchKernelGGL(mixed_type_kernel<true>, grid, block, lds, s, a);
-  else hipLaunchKernelGGL(mixed_type_kernel<false>, grid, block, lds, s, a);
+  if (axis == DYN_AXIS_EVEN) hipLaunchKernelGGL(mixed_type_kernel<DYN_AXIS_EVEN>, grid, block, lds, s, a);
+  else if (axis == DYN_AXIS_SINGLE) hipLaunchKernelGGL(mixed_type_kernel<DYN_AXIS_SINGLE>, grid, block, lds, s, a);
+  else hipLaunchKernelGGL(mixed_type_kernel<DYN_AXIS_SEARCH>, grid, block, lds, s, a);
   return hipGetLastError();
 }
 

@@ -20,9 +20,9 @@
 
 namespace {
 
-// LDS: [table rows n_slot*3*n_rho] [padded load grid n_rho+2] [padded reciprocal spacings n_rho+1]
-//      [cell records win_per_block] [bucket index n_bucket+1 (16-bit)]
-template <bool LDS, bool SEL, bool ONE_STEP>
+// LDS: [table rows n_slot*3*n_rho] [load axis] [cell records win_per_block] [bucket index n_bucket+1 (16-bit)]
+enum { kSearch = 0, kOneStep = 1, kEven = 2 };   // how the bracket is found; kOneStep: it is at most one from the bucket's index
+template <bool LDS, bool SEL, int FORM>
 __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   extern __shared__ double smem[];
   // block -> (window chunk, class, tile); tile fastest
@@ -31,10 +31,12 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   const int chunk = blockIdx.x / (a.n_tile * a.G);
   const int n_rho = a.n_rho;
 
-  double* s_tab = smem;                                              // [n_slot][3][n_rho]
-  double* s_rgp = smem + (LDS ? (size_t)a.n_slot * 3 * n_rho : 0);   // s_rgp[i+1] = rho[i]; -inf, +inf pads
-  double* s_rinv = s_rgp + (n_rho + 2);                              // s_rinv[i+1] = 1/(rho[i+1]-rho[i]); 0 pads
-  CellRec* s_rec = (CellRec*)(s_rinv + (n_rho + 1));                 // [win_per_block]
+  double* s_tab = smem;                                              // [n_slot][n_rho][3]
+  constexpr int AXIS = FORM == kEven ? DYN_AXIS_EVEN : DYN_AXIS_SEARCH;
+  const Axis axis = place_axis<AXIS>(smem + (LDS ? (size_t)a.n_slot * 3 * n_rho : 0), n_rho, a.axis.n_bucket);
+  double* s_rgp = axis.grid;                                         // not kEven: s_rgp[i+1] = rho[i]; -inf, +inf pads
+  double* s_rinv = axis.rinv;                                        // not kEven: s_rinv[i+1] = 1/(rho[i+1]-rho[i]); 0 pads
+  CellRec* s_rec = (CellRec*)axis.end;                               // [win_per_block]
   uint16_t* s_js = (uint16_t*)(s_rec + a.win_per_block);             // [n_bucket + 1]
 
   const int w0 = chunk * a.win_per_block;
@@ -47,8 +49,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
       for (int i = threadIdx.x; i < per_slot; i += blockDim.x) s_tab[slot * per_slot + i] = src[i];
     }
   }
-  for (int i = threadIdx.x; i < 2 * n_rho + 3; i += blockDim.x) s_rgp[i] = a.gridpack[i];
-  for (int i = threadIdx.x; i <= a.n_bucket; i += blockDim.x) s_js[i] = (uint16_t)a.jstart[i];
+  stage_axis<AXIS>(a.axis, axis, s_js);
   // the cells of this block's run of windows (load, P99 input length)
   for (int i = threadIdx.x; i < w1 - w0; i += blockDim.x) s_rec[i] = a.rec[(size_t)(w0 + i) * a.G + g];
   __syncthreads();
@@ -67,7 +68,9 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   const double ml = two_rows ? omu * mlrow[c.row_lo] + c.u * mlrow[c.row_hi] : mlrow[c.row_lo];
   const double den = c.nd * ml;
   const double rden = 1.0 / den;
-  const double rho_max = s_rgp[n_rho];
+  Lookup L;
+  use_axis<AXIS>(a.axis, axis, s_js, &L);
+  const double rho_max = L.rho_max;
   const double slo_ttft = a.slo_ttft[g], slo_tbt = a.slo_tbt[g];
   const int32_t bud = a.budget[g];
   const uint32_t fl_budget = (bud > 0 && c.gpus > bud) ? DYN_F_BUDGET : 0u;
@@ -80,13 +83,13 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   const int lane = threadIdx.x & (DYN_WAVE - 1);
   const int wslot = tile * (a.tile / DYN_WAVE) + (int)(threadIdx.x / DYN_WAVE);
 
-  const double *lo_pf, *lo_tb, *lo_pw, *hi_pf, *hi_tb, *hi_pw;
+  const double *row_lo, *row_hi;            // (prefill, TBT, power) per load point
   if (LDS) {
-    lo_pf = s_tab + (size_t)c.slot_lo * 3 * n_rho; lo_tb = lo_pf + n_rho; lo_pw = lo_tb + n_rho;
-    hi_pf = s_tab + (size_t)c.slot_hi * 3 * n_rho; hi_tb = hi_pf + n_rho; hi_pw = hi_tb + n_rho;
+    row_lo = s_tab + (size_t)c.slot_lo * 3 * n_rho;
+    row_hi = s_tab + (size_t)c.slot_hi * 3 * n_rho;
   } else {
-    lo_pf = a.tab + ((size_t)g * a.n_tp_f + c.row_lo) * 3 * n_rho; lo_tb = lo_pf + n_rho; lo_pw = lo_tb + n_rho;
-    hi_pf = a.tab + ((size_t)g * a.n_tp_f + c.row_hi) * 3 * n_rho; hi_tb = hi_pf + n_rho; hi_pw = hi_tb + n_rho;
+    row_lo = a.tab + ((size_t)g * a.n_tp_f + c.row_lo) * 3 * n_rho;
+    row_hi = a.tab + ((size_t)g * a.n_tp_f + c.row_hi) * 3 * n_rho;
   }
   const uint32_t koff = (uint32_t)k * 8u;   // byte offset of this lane inside an output row
 
@@ -99,31 +102,43 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
     const double rc = ov ? rho_max : rho;
     // bracket: largest j with rho[j] <= rc, at most n_rho-2; start from the bucket index
     // (rc <= rho_max keeps the bucket at or below n_bucket; a negative load maps to bucket 0)
-    const int b = (int)(fmax(rc, 0.0) * a.bucket_scale);
-    int j = s_js[b];                                   // <= n_rho-2 by construction
-    double r0, r1, ri;
-    if (ONE_STEP) {
+    double t, v[6], u[6];                       // the two load points of the lower and the upper row
+    auto load = [&](int j) {
+      const double* lo = row_lo + 3 * j;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) v[i] = lo[i];
+      if (two_rows) {
+        const double* hi = row_hi + 3 * j;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) u[i] = hi[i];
+      }
+    };
+    if (FORM == kOneStep) {
+      const int b = (int)(fmax(rc, 0.0) * L.scale);
+      int j = s_js[b];                                   // <= n_rho-2 by construction
       // the grid is coarse against the buckets: the bracket is j-1, j or j+1
       const double g0 = s_rgp[j + 1], g1 = s_rgp[j + 2];
       const bool down = g0 > rc && j > 0;
       const bool up = !down && g1 <= rc && j < n_rho - 2;
       j += up ? 1 : (down ? -1 : 0);
-      r0 = s_rgp[j + 1]; r1 = s_rgp[j + 2]; ri = s_rinv[j + 1];
+      const double r0 = s_rgp[j + 1], r1 = s_rgp[j + 2];
+      load(j);
+      t = div_by(rc - r0, r1 - r0, s_rinv[j + 1]);
     } else {
-      while (j > 0 && s_rgp[j + 1] > rc) --j;
-      while (j < n_rho - 2 && s_rgp[j + 2] <= rc) ++j;
-      r0 = s_rgp[j + 1]; r1 = s_rgp[j + 2]; ri = s_rinv[j + 1];
+      t = find_bracket<AXIS>(L, rc, load, [&] {
+        read_now(v[0], v[1], v[2], v[3]);
+        read_now(v[4], v[5]);
+      });
     }
-    const double t = div_by(rc - r0, r1 - r0, ri);
     const double omt = 1.0 - t;
 
-    double pf = omt * lo_pf[j] + t * lo_pf[j + 1];
-    double tb = omt * lo_tb[j] + t * lo_tb[j + 1];
-    double pw = omt * lo_pw[j] + t * lo_pw[j + 1];
+    double pf = omt * v[0] + t * v[3];
+    double tb = omt * v[1] + t * v[4];
+    double pw = omt * v[2] + t * v[5];
     if (two_rows) {
-      const double pf_b = omt * hi_pf[j] + t * hi_pf[j + 1];
-      const double tb_b = omt * hi_tb[j] + t * hi_tb[j + 1];
-      const double pw_b = omt * hi_pw[j] + t * hi_pw[j + 1];
+      const double pf_b = omt * u[0] + t * u[3];
+      const double tb_b = omt * u[1] + t * u[4];
+      const double pw_b = omt * u[2] + t * u[5];
       pf = omu * pf + c.u * pf_b;
       tb = omu * tb + c.u * tb_b;
       pw = omu * pw + c.u * pw_b;
@@ -175,10 +190,22 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   }
 }
 
+size_t rows_lds(const SpaceArgs& a) { return (size_t)a.n_slot * 3 * a.n_rho * sizeof(double); }
+size_t even_lds(const SpaceArgs& a) {
+  return rows_lds(a) + dyn_axis_lds(a.axis, DYN_AXIS_EVEN) + (size_t)a.win_per_block * sizeof(CellRec);
+}
+// Grids of more points than fit in LDS in triples keep the search (the host's tiles are cut for its LDS).
+int space_form(const SpaceArgs& a) { return a.axis.even && even_lds(a) <= DYN_LDS_BUDGET ? kEven : a.one_step ? kOneStep : kSearch; }
+size_t space_lds(const SpaceArgs& a) {
+  return space_form(a) == kEven ? even_lds(a) : rows_lds(a) + dyn_space_lds_tail(a.n_rho, a.axis.n_bucket, a.win_per_block);   // host keeps this <= 64 KB
+}
+
 template <bool LDS, bool SEL>
-void launch_one_step(const SpaceArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
-  if (a.one_step) hipLaunchKernelGGL((space_kernel<LDS, SEL, true>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((space_kernel<LDS, SEL, false>), grid, block, lds, s, a);
+void launch_form(const SpaceArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  const int form = space_form(a);
+  if (form == kEven) hipLaunchKernelGGL((space_kernel<LDS, SEL, kEven>), grid, block, lds, s, a);
+  else if (form == kOneStep) hipLaunchKernelGGL((space_kernel<LDS, SEL, kOneStep>), grid, block, lds, s, a);
+  else hipLaunchKernelGGL((space_kernel<LDS, SEL, kSearch>), grid, block, lds, s, a);
 }
 
 }  // namespace
@@ -190,16 +217,18 @@ size_t dyn_space_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t win_per_block
 
 // Blocks of the evaluation kernel that one compute unit holds at a time for this shape (0 if the query fails).
 int dyn_space_blocks_per_cu(const SpaceArgs& a) {
-  const size_t lds_tab = (size_t)a.n_slot * 3 * a.n_rho * sizeof(double);
-  const size_t lds = (a.n_slot > 0 ? lds_tab : 0) + dyn_space_lds_tail(a.n_rho, a.n_bucket, a.win_per_block);
+  const size_t lds = space_lds(a);
+  const int form = space_form(a);
   int n = 0;
   hipError_t e;
   if (a.n_slot > 0) {
-    if (a.one_step) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, true>, a.tile, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, false>, a.tile, lds);
+    if (form == kEven) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kEven>, a.tile, lds);
+    else if (form == kOneStep) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kOneStep>, a.tile, lds);
+    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kSearch>, a.tile, lds);
   } else {
-    if (a.one_step) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, true>, a.tile, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, false>, a.tile, lds);
+    if (form == kEven) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kEven>, a.tile, lds);
+    else if (form == kOneStep) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kOneStep>, a.tile, lds);
+    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kSearch>, a.tile, lds);
   }
   if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
   return n;
@@ -208,16 +237,15 @@ int dyn_space_blocks_per_cu(const SpaceArgs& a) {
 hipError_t dyn_launch_space(const SpaceArgs& a, hipStream_t s) {
   const int n_chunk = (a.n_window + a.win_per_block - 1) / a.win_per_block;
   const size_t blocks = (size_t)n_chunk * a.G * a.n_tile;
-  const size_t lds_tab = (size_t)a.n_slot * 3 * a.n_rho * sizeof(double);
   DynTimed timed(DYN_K_SPACE, s);
-  const size_t lds = (a.n_slot > 0 ? lds_tab : 0) + dyn_space_lds_tail(a.n_rho, a.n_bucket, a.win_per_block);  // host keeps this <= 64 KB
+  const size_t lds = space_lds(a);
   const dim3 grid((unsigned)blocks), block(a.tile);
   if (a.n_slot > 0) {
-    if (a.part) launch_one_step<true, true>(a, grid, block, lds, s);
-    else launch_one_step<true, false>(a, grid, block, lds, s);
+    if (a.part) launch_form<true, true>(a, grid, block, lds, s);
+    else launch_form<true, false>(a, grid, block, lds, s);
   } else {
-    if (a.part) launch_one_step<false, true>(a, grid, block, lds, s);
-    else launch_one_step<false, false>(a, grid, block, lds, s);
+    if (a.part) launch_form<false, true>(a, grid, block, lds, s);
+    else launch_form<false, false>(a, grid, block, lds, s);
   }
   return hipGetLastError();
 }

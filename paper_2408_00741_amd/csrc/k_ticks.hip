@@ -507,7 +507,7 @@ __device__ __forceinline__ float theta_between(const TickCellArgs& a, int g, dou
     const bool two = cf.u != 0.0;
     const double ml = two ? (1.0 - cf.u) * a.ml[row + cf.row_lo] + cf.u * a.ml[row + cf.row_hi] : a.ml[row + cf.row_lo];
     const double *lo = a.tab + (row + cf.row_lo) * 3 * R, *hi = a.tab + (row + cf.row_hi) * 3 * R;
-    auto point = [&](int i) { return two ? (1.0 - cf.u) * lo[i] + cf.u * hi[i] : lo[i]; };
+    auto point = [&](int i) { return two ? (1.0 - cf.u) * lo[3 * i] + cf.u * hi[3 * i] : lo[3 * i]; };
     const double den = cf.nd * ml;
     double mn = __builtin_inf(), mx = -__builtin_inf();
     int from = 0;
@@ -1468,8 +1468,8 @@ __device__ __forceinline__ void offer_tick(double (&s)[JF], const int32_t* s_top
 // Power of the configuration at load 0: what table_lookup returns for it (bracket 0, weight 0 on the second load point).
 template <bool TWO>
 __device__ __forceinline__ double idle_power(const Lookup& L) {
-  const double a = L.lo[2 * L.n_rho];
-  return TWO ? L.omu * a + L.u * L.hi[2 * L.n_rho] : a;
+  const double a = L.lo[2];
+  return TWO ? L.omu * a + L.u * L.hi[2] : a;
 }
 
 // The four largest tick TBTs with their request counts (descending; ties keep the earlier tick first).
@@ -1512,77 +1512,46 @@ struct WalkOut {
   bool ov;
 };
 
-// One walk over the ticks of a cell, in time order, two look-ups in flight (PAIR; one at a time leaves registers for
-// a fifth wave per SIMD in the kernel without lists, which gains more than the second look-up in flight).  The cell's j <= JF largest scaled
+// One walk over the ticks of a cell with lists, in time order, two look-ups in flight.  The cell's j <= JF largest scaled
 // candidates go through a sorted list that starts with JF - j copies of +inf, so that its last entry is the j-th
-// largest of what was inserted (j == 0: nothing is inserted).  SPARSE: the TBT percentile from the four largest
-// tick TBTs, else the largest tick TBT.
-// TIGHT: the TTFT percentile is x_j times the prefill time of rank `place` (bit 31: from below) among the ticks, each
-// counted as often as it holds requests of length x_j (`s_top`: that number per tick; `xmin` carries x_j): the four
-// largest (smallest) prefill times are kept with their counts.
-template <int JF, bool SPARSE, bool SINGLE, bool TWO, bool TIGHT = false, bool PAIR = true>
+// largest of what was inserted.  SPARSE: the TBT percentile from the four largest tick TBTs, else the largest tick TBT.
+template <int JF, bool SPARSE, int AXIS, bool TWO>
 __device__ __forceinline__ WalkOut walk_ticks(const Lookup& L, int T, int j, const double* s_load, const int32_t* s_cnt,
-                                              const int32_t* s_top, int xmin, double nd, double tick_s, uint32_t place = 0) {
+                                              const int32_t* s_top, int xmin, double nd, double tick_s) {
   double s[JF];
-  int wt[TIGHT ? JF : 1];
-  const double sign = (place & DYN_TIGHT_FROM_BELOW) ? -1.0 : 1.0;
 #pragma unroll
-  for (int i = 0; i < JF; ++i) s[i] = (!TIGHT && i < JF - j) ? __builtin_inf() : -__builtin_inf();
-  if (TIGHT) {
-#pragma unroll
-    for (int i = 0; i < JF; ++i) wt[i] = 0;
-  }
+  for (int i = 0; i < JF; ++i) s[i] = i < JF - j ? __builtin_inf() : -__builtin_inf();
   double e = 0.0, tbmax = -__builtin_inf();
   TbtTop tt;
   if (SPARSE) tt.clear();
   bool ov = false;
-  auto one = [&](int q, int c0, double pf0, double tb0) {
-    if (c0 > 0 && j > 0) {                       // block-uniform
-      if (SPARSE) tt.offer(tb0, c0); else tbmax = max_num(tbmax, tb0);
-      if (TIGHT) {
-        const int eq = __builtin_amdgcn_readfirstlane(s_top[q]);
-        double key = pf0 * sign;
-        if (eq > 0 && __ballot(key > s[JF - 1]) != 0) {
-          int w_in = eq;
-#pragma unroll
-          for (int i = 0; i < JF; ++i) {
-            const bool gt = key > s[i];
-            const double tk = s[i];
-            const int tw = wt[i];
-            s[i] = gt ? key : tk;
-            wt[i] = gt ? w_in : tw;
-            key = gt ? tk : key;
-            w_in = gt ? tw : w_in;
-          }
-        }
-      } else {
-        offer_tick<JF>(s, s_top, T, q, c0 < j ? c0 : j, xmin, pf0);
-      }
-    }
+  auto one = [&](int q, int c, const Looked& r) {
+    if (SPARSE) tt.offer(r.v[1], c); else tbmax = max_num(tbmax, r.v[1]);
+    offer_tick<JF>(s, s_top, T, q, c < j ? c : j, xmin, r.v[0]);
   };
   // a tick without requests has load 0: the tables at their first load point, no look-up
   const double e_idle = (nd * idle_power<TWO>(L)) * tick_s;
   int q = 0;
   for (; q + 2 <= T; q += 2) {
     const int c0 = s_cnt[q], c1 = s_cnt[q + 1];                 // block-uniform
-    if (PAIR && c0 > 0 && c1 > 0) {
-      double pf0, tb0, pw0, pf1, tb1, pw1;
-      const bool o0 = table_lookup<SINGLE, TWO>(L, s_load[q], &pf0, &tb0, &pw0);
-      const bool o1 = table_lookup<SINGLE, TWO>(L, s_load[q + 1], &pf1, &tb1, &pw1);
-      ov = ov | o0 | o1;
-      e += (nd * pw0) * tick_s;                  // ticks in time order
-      e += (nd * pw1) * tick_s;
-      one(q, c0, pf0, tb0);
-      one(q + 1, c1, pf1, tb1);
+    if (c0 > 0 && c1 > 0) {
+      const double load[2] = {s_load[q], s_load[q + 1]};
+      Looked r[2];
+      table_lookups<AXIS, TWO, kAllColumns, 2>(L, load, r);
+      ov = ov | r[0].ov | r[1].ov;
+      e += (nd * r[0].v[2]) * tick_s;                // ticks in time order
+      e += (nd * r[1].v[2]) * tick_s;
+      one(q, c0, r[0]);
+      one(q + 1, c1, r[1]);
     } else {
 #pragma unroll
       for (int d = 0; d < 2; ++d) {
         const int cd = d ? c1 : c0;
         if (cd > 0) {
-          double pf0, tb0, pw0;
-          ov = ov | table_lookup<SINGLE, TWO>(L, s_load[q + d], &pf0, &tb0, &pw0);
-          e += (nd * pw0) * tick_s;
-          one(q + d, cd, pf0, tb0);
+          const Looked r = table_lookup<AXIS, TWO>(L, s_load[q + d]);
+          ov = ov | r.ov;
+          e += (nd * r.v[2]) * tick_s;
+          one(q + d, cd, r);
         } else {
           e += e_idle;
         }
@@ -1590,21 +1559,123 @@ __device__ __forceinline__ WalkOut walk_ticks(const Lookup& L, int T, int j, con
     }
   }
   if (q < T) {
-    const int c0 = s_cnt[q];
-    if (c0 > 0) {
-      double pf0, tb0, pw0;
-      ov = ov | table_lookup<SINGLE, TWO>(L, s_load[q], &pf0, &tb0, &pw0);
-      e += (nd * pw0) * tick_s;
-      one(q, c0, pf0, tb0);
+    const int c = s_cnt[q];
+    if (c > 0) {
+      const Looked r = table_lookup<AXIS, TWO>(L, s_load[q]);
+      ov = ov | r.ov;
+      e += (nd * r.v[2]) * tick_s;
+      one(q, c, r);
     } else {
       e += e_idle;
     }
   }
   WalkOut r;
   r.e = e; r.ov = ov; r.ttft = s[JF - 1];
-  if (TIGHT) {
-    const int want = (int)(place & ~DYN_TIGHT_FROM_BELOW);
-    double pick = s[JF - 1];
+  r.tbt = SPARSE ? tt.jth(j) : tbmax;
+  return r;
+}
+
+// A plan read by scalar loads: it is the same for the wave, and written by an earlier kernel.
+typedef __attribute__((address_space(4))) TickPlan ScalarPlan;
+__device__ __forceinline__ TickPlan load_plan(const TickPlan* at) {
+  const ScalarPlan* p = (const ScalarPlan*)at;
+  TickPlan r;
+  r.j = p->j; r.xj = p->xj; r.flags = p->flags; r.place = p->place;
+  return r;
+}
+
+typedef const __attribute__((address_space(4))) TickRec ScalarRec;   // the same of its ticks
+
+// Of a cell that needs no lists, as bits: which ticks hold requests, which hold requests of length x_j and whose loads come near the
+// largest; the largest load, 0 if no tick holds requests.
+struct TickMask {
+  uint64_t some, eq, top;
+  double top_load;
+};
+// A tick per lane.  Loads are compared by their high words (loads >= 0 order like their bits): a step is 2^-20 of the load or less, and
+// half of that at least, so a load within DYN_TICK_NEAR of the largest is two steps away at most.
+__device__ __forceinline__ TickMask tick_mask(const TickRec& r, bool asks, int T, int lane) {
+  static_assert(DYN_TICK_NEAR == 0x1p-20, "a step of the high word");
+  TickMask m;
+  const bool some = lane < T && r.cnt > 0;
+  m.some = __ballot(some);
+  m.eq = __ballot(some && asks && (int32_t)r.off > 0);
+  const int32_t hi = some ? (int32_t)((uint64_t)__double_as_longlong(r.load) >> 32) : -0x7FFFFFFF;
+  const int32_t most = wave_max_i32(hi);
+  m.top = __ballot(some && hi >= most - 2);
+  m.top_load = 0.0;
+  uint64_t left = __ballot(some && hi == most);
+  if (left) m.top_load = lane_f64(r.load, __builtin_ctzll(left));
+  for (left &= left - 1; left; left &= left - 1) m.top_load = fmax(m.top_load, lane_f64(r.load, __builtin_ctzll(left)));
+  return m;
+}
+
+// The walk without lists, in time order.  The TBT percentile is the largest tick TBT, which only ticks whose loads come near the
+// largest can have (dyn_profile.d_steep; where a candidate's row does not say so, and with rows between two frequencies, all are
+// asked); SPARSE: it comes from the four largest tick TBTs.  The TTFT percentile is x_j times the prefill time of rank `place` (bit
+// 31: from below) among the ticks, each counted as often as it holds requests of length x_j (`off`): where that is one tick its
+// own, else the four largest (smallest) are kept with their counts.  So most ticks are asked for their power only: they go through a loop
+// of their own that touches nothing but the energy.  What a tick is asked about itself is a bit of a mask in scalar registers, and
+// whether any is overloaded is asked of the largest load (a rounded quotient is monotone).
+template <bool SPARSE, int AXIS, bool TWO>
+__device__ __forceinline__ WalkOut walk_masked(const Lookup& L, int T, const TickPlan& pl, const TickRec& rec, ScalarRec* at,
+                                               double nd, double tick_s, double e_idle, double steep, int lane) {
+  const TickMask m = tick_mask(rec, pl.j > 0, T, lane);
+  constexpr int JF = 4;
+  double s[JF];
+  int wt[JF];
+  const double sign = (pl.place & DYN_TIGHT_FROM_BELOW) ? -1.0 : 1.0;
+#pragma unroll
+  for (int i = 0; i < JF; ++i) { s[i] = -__builtin_inf(); wt[i] = 0; }
+  double e = 0.0, tbmax = -__builtin_inf();
+  TbtTop tt;
+  if (SPARSE) tt.clear();
+  const double top_rho = div_by(m.top_load, L.den, L.rden);
+  const bool one_eq = (m.eq & (m.eq - 1)) == 0;  // of the cell's j-th largest length there is one, or several in one tick
+  uint64_t asked = m.eq | (SPARSE || TWO || __ballot(top_rho < steep) != 0 ? m.some : m.top);
+  uint64_t some = m.some;
+  double next = at[0].load;
+  for (int q = 0;;) {
+    const int stop = asked ? __builtin_ctzll(asked) : T;
+    for (; q < stop; ++q, some >>= 1) {
+      const double load = next;
+      next = at[min(q + 1, T - 1)].load;
+      if (some & 1) e += (nd * table_lookup<AXIS, TWO, kPower>(L, load).v[2]) * tick_s;
+      else e += e_idle;                          // load 0: the tables at their first load point, no look-up
+    }
+    if (!asked) break;
+    const Looked r = table_lookup<AXIS, TWO, kAllColumns>(L, next);
+    next = at[min(q + 1, T - 1)].load;
+    e += (nd * r.v[2]) * tick_s;
+    if (SPARSE) tt.offer(r.v[1], __builtin_amdgcn_readlane(rec.cnt, q)); else tbmax = max_num(tbmax, r.v[1]);
+    if (m.eq >> q & 1) {
+      double key = r.v[0] * sign;
+      if (one_eq) {
+        s[0] = key;
+      } else if (__ballot(key > s[JF - 1]) != 0) {
+        int w_in = __builtin_amdgcn_readlane((int)rec.off, q);
+#pragma unroll
+        for (int i = 0; i < JF; ++i) {
+          const bool gt = key > s[i];
+          const double tk = s[i];
+          const int tw = wt[i];
+          s[i] = gt ? key : tk;
+          wt[i] = gt ? w_in : tw;
+          key = gt ? tk : key;
+          w_in = gt ? tw : w_in;
+        }
+      }
+    }
+    ++q; some >>= 1;
+    asked &= asked - 1;
+  }
+  WalkOut o;
+  o.e = e;
+  o.ov = top_rho > L.rho_max;
+  double pick = s[0];
+  if (!one_eq) {
+    const int want = (int)(pl.place & ~DYN_TIGHT_FROM_BELOW);
+    pick = s[JF - 1];
     int cum = 0;
     bool found = false;
 #pragma unroll
@@ -1614,10 +1685,10 @@ __device__ __forceinline__ WalkOut walk_ticks(const Lookup& L, int T, int j, con
       pick = hit ? s[i] : pick;
       found = found || hit;
     }
-    r.ttft = (double)xmin * (pick * sign);
   }
-  r.tbt = SPARSE ? tt.jth(j) : tbmax;
-  return r;
+  o.ttft = (double)pl.xj * (pick * sign);
+  o.tbt = SPARSE ? tt.jth(pl.j) : tbmax;
+  return o;
 }
 
 // Per-thread state of one configuration inside a (class, tile) block.
@@ -1625,22 +1696,20 @@ struct CfgState {
   Lookup L;
   double nd, slo_ttft, slo_tbt, idle_term;
   uint32_t fl_budget, koff;
-  int k, k_raw, lane, wslot;
+  int row_lo, k0;                // k0: the wave's first configuration
   bool live;
 };
 
 // The constants of configuration k_raw (>= K: a copy of the last one that stores nothing): `g` is
 // block-uniform; the table rows are either the block's LDS copy (LDS) or global memory.
-template <bool LDS>
-__device__ __forceinline__ void load_config(const TickArgs& a, int g, int k_raw, const double* s_tab, const double* s_rgp,
-                                            const double* s_rinv, const double* s_thr, const uint16_t* s_js,
-                                            CfgState* st) {
+template <bool LDS, int AXIS>
+__device__ __forceinline__ void load_config(const TickArgs& a, int g, int k_raw, const double* s_tab, const Axis& axis,
+                                            const uint16_t* s_js, CfgState* st) {
   const SpaceArgs& sa = a.s;
   const int n_rho = sa.n_rho;
-  st->k_raw = k_raw;
-  st->live = st->k_raw < sa.K;            // every lane stays alive for the wave reduction
-  st->k = st->live ? st->k_raw : sa.K - 1;
-  const DevCfg c = sa.cfg[st->k];
+  st->live = k_raw < sa.K;                // every lane stays alive for the wave reduction
+  const DevCfg c = sa.cfg[st->live ? k_raw : sa.K - 1];
+  st->row_lo = c.row_lo;
   const size_t grow = (size_t)g * sa.n_tp_f;
   const double ml_lo = sa.ml[grow + c.row_lo], ml_hi = sa.ml[grow + c.row_hi];
   const double p0_lo = sa.pw0[grow + c.row_lo], p0_hi = sa.pw0[grow + c.row_hi];
@@ -1651,9 +1720,7 @@ __device__ __forceinline__ void load_config(const TickArgs& a, int g, int k_raw,
   const double ml = two_rows ? L.omu * ml_lo + c.u * ml_hi : ml_lo;
   L.den = c.nd * ml;
   L.rden = 1.0 / L.den;
-  L.rho_max = s_rgp[n_rho];
-  L.bucket_scale = sa.bucket_scale;
-  L.rgp = s_rgp; L.rinv = s_rinv; L.js = s_js; L.thr = s_thr; L.n_rho = n_rho;
+  use_axis<AXIS>(sa.axis, axis, s_js, &L);
   if (LDS) {      // kept apart so that the address space of the rows is known at compile time
     L.lo = s_tab + (size_t)c.slot_lo * DYN_SLOT_STRIDE(n_rho);
     L.hi = s_tab + (size_t)c.slot_hi * DYN_SLOT_STRIDE(n_rho);
@@ -1668,31 +1735,38 @@ __device__ __forceinline__ void load_config(const TickArgs& a, int g, int k_raw,
   st->fl_budget = (bud > 0 && c.gpus > bud) ? DYN_F_BUDGET : 0u;
   const double pw0 = two_rows ? L.omu * p0_lo + c.u * p0_hi : p0_lo;
   st->idle_term = sa.idle_w * ((c.nd * pw0) * a.window_s);
-  st->lane = threadIdx.x & (DYN_WAVE - 1);
-  st->wslot = st->k_raw / DYN_WAVE;       // tiles are multiples of 64 configurations wide
-  st->koff = (uint32_t)st->k * 8u;
+  st->k0 = __builtin_amdgcn_readfirstlane(k_raw);   // tiles are multiples of 64 configurations wide
+  st->koff = (uint32_t)k_raw * 8u;        // where it is live
 }
 
-// One flat loop over the rows a tile needs: the loads of different rows are in flight together.
+// The rows a tile needs, a wave a row: which row it is comes by a scalar load, and the loads of several are in flight together.
 __device__ __forceinline__ void stage_rows(const SpaceArgs& sa, int g, int tile, double* s_tab) {
-  const int per_slot = 3 * sa.n_rho, total = sa.n_slot * per_slot;
+  const int per_slot = 3 * sa.n_rho, lane = threadIdx.x & (DYN_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE), waves = blockDim.x / DYN_WAVE;
   const int32_t* rows = sa.tile_rows + tile * sa.n_slot;
   const double* base = sa.tab + (size_t)g * sa.n_tp_f * per_slot;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    const int slot = i / per_slot;
-    const int row = rows[slot];
-    s_tab[slot * DYN_SLOT_STRIDE(sa.n_rho) + (i - slot * per_slot)] = base[(size_t)(row < 0 ? 0 : row) * per_slot + (i - slot * per_slot)];
+#pragma unroll 2
+  for (int slot = wave; slot < sa.n_slot; slot += waves) {
+    const double* src = base + (size_t)max(rows[slot], 0) * per_slot;
+    double* dst = s_tab + slot * DYN_SLOT_STRIDE(sa.n_rho);
+    double v[4];
+    for (int i0 = 0; i0 < per_slot; i0 += 4 * DYN_WAVE) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) if (i0 + q * DYN_WAVE + lane < per_slot) v[q] = src[i0 + q * DYN_WAVE + lane];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) if (i0 + q * DYN_WAVE + lane < per_slot) dst[i0 + q * DYN_WAVE + lane] = v[q];
+    }
   }
 }
-template <bool SINGLE>
-__device__ __forceinline__ void stage_grid(const TickArgs& a, double* s_rgp, double* s_thr, uint16_t* s_js) {
-  const SpaceArgs& sa = a.s;
-  for (int i = threadIdx.x; i < 2 * sa.n_rho + 3; i += blockDim.x) s_rgp[i] = sa.gridpack[i];
-  for (int i = threadIdx.x; i <= sa.n_bucket; i += blockDim.x) {
-    s_js[i] = (uint16_t)(SINGLE ? a.tstart[i] : sa.jstart[i]);
-    if (SINGLE) s_thr[i] = a.thr[i];
-  }
+
+// A wave-uniform address that stays in scalar registers: the compiler otherwise adds the lane's offset to the array's start once, outside
+// the loop over the cells, and keeps a 64-bit address per array in vector registers it does not have (the reloads then wait for the
+// stores before them).
+template <typename T>
+__device__ __forceinline__ auto row_start(T* p) {
+  uint64_t at = uniform_u64((uint64_t)(uintptr_t)p);
+  asm("" : "+s"(at));
+  return (__attribute__((address_space(1))) char*)at;
 }
 
 // Flags, streaming stores of the four outputs and the wave's partial selection for one cell.
@@ -1704,16 +1778,18 @@ __device__ __forceinline__ void emit_cell(const SpaceArgs& sa, const CfgState& s
   if (p_tbt > st.slo_tbt) fl |= DYN_F_TBT;
   if (!fl) fl = DYN_F_FEASIBLE;
   if (empty) fl |= DYN_F_EMPTY;
+  const double cost = e + st.idle_term;
   if (st.live) {
     const size_t row = cell * (size_t)sa.K;
-    __builtin_nontemporal_store(e, (double*)((char*)(sa.energy + row) + st.koff));
-    __builtin_nontemporal_store(p_ttft, (double*)((char*)(sa.p99_ttft + row) + st.koff));
-    __builtin_nontemporal_store(p_tbt, (double*)((char*)(sa.p99_tbt + row) + st.koff));
-    __builtin_nontemporal_store((uint8_t)fl, (sa.flags + row) + (uint32_t)st.k);
+    uint32_t koff = st.koff;
+    asm("" : "+v"(koff));                    // 32 bits up to the store, which widens it itself
+    __builtin_nontemporal_store(e, (__attribute__((address_space(1))) double*)(row_start(sa.energy + row) + koff));
+    __builtin_nontemporal_store(p_ttft, (__attribute__((address_space(1))) double*)(row_start(sa.p99_ttft + row) + koff));
+    __builtin_nontemporal_store(p_tbt, (__attribute__((address_space(1))) double*)(row_start(sa.p99_tbt + row) + koff));
+    __builtin_nontemporal_store((uint8_t)fl, (__attribute__((address_space(1))) uint8_t*)(row_start(sa.flags + row) + (koff >> 3)));
   }
   // least cost among this wave's feasible configurations (costs >= +0 order like their bits)
   const bool feas = st.live && (fl & DYN_F_FEASIBLE);
-  const double cost = e + st.idle_term;
   const uint64_t bits = (uint64_t)__double_as_longlong(cost);
   const uint32_t hi = feas ? (uint32_t)(bits >> 32) : 0xFFFFFFFFu;
   const uint32_t lo = feas ? (uint32_t)bits : 0xFFFFFFFFu;
@@ -1724,24 +1800,22 @@ __device__ __forceinline__ void emit_cell(const SpaceArgs& sa, const CfgState& s
     win = __ballot(feas && hi == mh && lo == mlo);
   }
   const int wl = win ? __builtin_ctzll(win) : 0;
-  if (st.lane == wl) {
-    SelPart p;
-    p.cost = win ? cost : __builtin_inf();
-    p.energy = win ? e : __builtin_inf();
-    p.k = win ? st.k_raw : -1;
-    p.pad = 0;
-    sa.part[cell * (size_t)sa.n_wslot + st.wslot] = p;
+  if ((int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == wl) {
+    auto* p = (__attribute__((address_space(1))) SelPart*)row_start(sa.part + (cell * (size_t)sa.n_wslot + st.k0 / DYN_WAVE));
+    p->cost = win ? cost : __builtin_inf();
+    p->energy = win ? e : __builtin_inf();
+    p->k = win ? st.k0 + wl : -1;
+    p->pad = 0;
   }
 }
 
 // A block walks a run of windows of one (class, tile): the empty cells, the cells that are not evaluated and
 // the cells the cell kernel left to this kernel (the others are the general kernel's).  The next cell's
 // candidate lists are kept in flight (NPRE registers per thread) while the current one is evaluated.
-// LDS: [table rows n_slot*3*n_rho] [padded load grid n_rho+2] [reciprocal spacings n_rho+1]
-//      [SINGLE: grid point per bucket, n_bucket+1]
+// LDS: [table rows n_slot*3*n_rho] [load axis]
 //      [per window of the block, per tick: load] [the same: request count] [the same: list offset]
 //      [per window: plan] [two buffers of candidate lists, [position][tick]] [bucket index (16-bit)]
-template <int TB, bool LDS, bool SINGLE, bool TWO>
+template <int TB, bool LDS, int AXIS, bool TWO>
 __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4, 4))) void tick_space_kernel(TickArgs a) {
   constexpr int NPRE = kFastDepth * TB / DYN_WAVE;   // blocks have at least 64 threads; n_tick <= TB
   extern __shared__ double smem[];
@@ -1754,10 +1828,8 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
   const int w1 = min(w0 + sa.win_per_block, sa.n_window);
 
   double* s_tab = smem;
-  double* s_rgp = smem + (LDS ? (size_t)sa.n_slot * DYN_SLOT_STRIDE(n_rho) : 0);
-  double* s_rinv = s_rgp + (n_rho + 2);
-  double* s_thr = s_rinv + (n_rho + 1);                         // [n_bucket + 1] when SINGLE
-  uint32_t* s_ratio = (uint32_t*)(s_thr + (SINGLE ? sa.n_bucket + 1 : 0));   // [4] per wave (two doubles' room)
+  const Axis axis = place_axis<AXIS>(smem + (LDS ? (size_t)sa.n_slot * DYN_SLOT_STRIDE(n_rho) : 0), n_rho, sa.axis.n_bucket);
+  uint32_t* s_ratio = (uint32_t*)axis.end;                      // [4] per wave (two doubles' room)
   double* s_load = (double*)s_ratio + 2;                        // [win_per_block][T]
   TickPlan* s_plan = (TickPlan*)(s_load + sa.win_per_block * T);   // [win_per_block]
   int32_t* s_cnt = (int32_t*)(s_plan + sa.win_per_block);       // [win_per_block][T] requests per tick
@@ -1775,7 +1847,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
   if (!any) return;                                             // block-uniform
 
   if (LDS) stage_rows(sa, g, tile, s_tab);
-  stage_grid<SINGLE>(a, s_rgp, s_thr, s_js);
+  stage_axis<AXIS>(sa.axis, axis, s_js);
   for (int i = threadIdx.x; i < (w1 - w0) * T; i += blockDim.x) {   // the ticks of this block's cells
     const int dw = i / T, q = i - dw * T;
     const TickRec r = a.rec[((size_t)(w0 + dw) * sa.G + g) * T + q];
@@ -1801,7 +1873,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
   }
   __syncthreads();
   CfgState st;
-  load_config<LDS>(a, g, tile * sa.tile + (int)threadIdx.x, s_tab, s_rgp, s_rinv, s_thr, s_js, &st);
+  load_config<LDS, AXIS>(a, g, tile * sa.tile + (int)threadIdx.x, s_tab, axis, s_js, &st);
   uint32_t ratio_bits = s_ratio[0];
   for (int i = 1; i < (int)blockDim.x / DYN_WAVE; ++i) ratio_bits = min(ratio_bits, s_ratio[i]);
   const double theta = (double)__uint_as_float(ratio_bits);
@@ -1858,82 +1930,79 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
     const int xmin = (int)((double)pl.xj * theta);
     WalkOut o;
     if (pl.flags & DYN_TP_DENSE) {
-      if (j == 1) o = walk_ticks<1, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
-      else if (j <= 4) o = walk_ticks<4, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
-      else if (j <= 8) o = walk_ticks<8, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
-      else o = walk_ticks<kFastDepth, false, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      if (j == 1) o = walk_ticks<1, false, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      else if (j <= 4) o = walk_ticks<4, false, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      else if (j <= 8) o = walk_ticks<8, false, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      else o = walk_ticks<kFastDepth, false, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
     } else {
-      if (j <= 4) o = walk_ticks<4, true, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
-      else o = walk_ticks<kFastDepth / 2, true, SINGLE, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      if (j <= 4) o = walk_ticks<4, true, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
+      else o = walk_ticks<kFastDepth / 2, true, AXIS, TWO>(st.L, T, j, load_w, cnt_w, top_w, xmin, st.nd, a.tick_s);
     }
     emit_cell(sa, st, cell, false, o.ov, o.e, o.ttft, o.tbt);
   }
 }
 
 // The same block mapping for the cells that need no lists: empty cells, cells that are not evaluated, and the cells
-// settled by their ticks' requests of length x_j (DYN_TP_TIGHT).  Nothing is staged per cell and the block has no
-// barrier after its set-up.
-// LDS: [table rows] [padded load grid] [reciprocal spacings] [SINGLE: grid point per bucket]
-//      [per window of the block, per tick: load] [per window: plan] [per window and tick: request count, requests of length x_j]
-//      [bucket index (16-bit)]
-template <bool LDS, bool SINGLE, bool TWO>
-__global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(5, 5))) void tick_tight_walk_kernel(TickArgs a) {
+// settled by their ticks' requests of length x_j (DYN_TP_TIGHT).  A wave takes a cell's ticks from global memory into its lanes, the
+// next cell's while it walks this one; nothing is staged per cell and the block has no barrier after its set-up.
+// LDS: [load axis] [table rows] [bucket index (16-bit)]
+template <bool LDS, int AXIS, bool TWO>
+__global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(TWO ? 5 : 6, TWO ? 5 : 6))) void tick_tight_walk_kernel(TickArgs a) {
   extern __shared__ double smem[];
   const SpaceArgs& sa = a.s;
   const int tile = blockIdx.x % sa.n_tile;
   const int g = (blockIdx.x / sa.n_tile) % sa.G;
   const int chunk = blockIdx.x / (sa.n_tile * sa.G);
   const int n_rho = sa.n_rho, T = a.n_tick;
-  const int w0 = chunk * sa.win_per_block;
-  const int w1 = min(w0 + sa.win_per_block, sa.n_window);
+  // the first n_long chunks are of win_long windows, the rest of win_per_block
+  const int w0 = min(chunk, a.n_long) * a.win_long + max(chunk - a.n_long, 0) * sa.win_per_block;
+  const int w1 = min(w0 + (chunk < a.n_long ? a.win_long : sa.win_per_block), sa.n_window);
+  const int lane = threadIdx.x & (DYN_WAVE - 1);
 
-  double* s_tab = smem;
-  double* s_rgp = smem + (LDS ? (size_t)sa.n_slot * DYN_SLOT_STRIDE(n_rho) : 0);
-  double* s_rinv = s_rgp + (n_rho + 2);
-  double* s_thr = s_rinv + (n_rho + 1);                         // [n_bucket + 1] when SINGLE
-  double* s_load = s_thr + (SINGLE ? sa.n_bucket + 1 : 0);      // [win_per_block][T]
-  TickPlan* s_plan = (TickPlan*)(s_load + sa.win_per_block * T);   // [win_per_block]
-  int32_t* s_cnt = (int32_t*)(s_plan + sa.win_per_block);       // [win_per_block][T] requests per tick
-  int32_t* s_eq = s_cnt + sa.win_per_block * T;                 // [win_per_block][T] requests of length x_j per tick
-  uint16_t* s_js = (uint16_t*)(s_eq + sa.win_per_block * T);    // [n_bucket + 1]
+  const Axis axis = place_axis<AXIS>(smem, n_rho, sa.axis.n_bucket);   // at the start: its place is an offset in the instruction
+  double* s_tab = axis.end;
+  uint16_t* s_js = (uint16_t*)(s_tab + (LDS ? (size_t)sa.n_slot * DYN_SLOT_STRIDE(n_rho) : 0));   // [n_bucket + 1]
 
   auto mine = [](const TickPlan& p) {
     return p.j == 0 || ((p.flags & DYN_TP_TIGHT) && !(p.flags & DYN_TP_GENERAL));
   };
   bool any = false;
-  for (int w = w0; w < w1; ++w) any = any || mine(a.plan[(size_t)w * sa.G + g]);
+  for (int w = w0; w < w1 && !any; ++w) any = mine(load_plan(a.plan + (size_t)w * sa.G + g));
   if (!any) return;                                             // block-uniform
 
   if (LDS) stage_rows(sa, g, tile, s_tab);
-  stage_grid<SINGLE>(a, s_rgp, s_thr, s_js);
-  for (int i = threadIdx.x; i < (w1 - w0) * T; i += blockDim.x) {   // the ticks of this block's cells
-    const int dw = i / T, q = i - dw * T;
-    const TickRec r = a.rec[((size_t)(w0 + dw) * sa.G + g) * T + q];
-    s_load[i] = r.load;
-    s_cnt[i] = r.cnt;
-    s_eq[i] = (int32_t)r.off;
-  }
-  for (int i = threadIdx.x; i < w1 - w0; i += blockDim.x) s_plan[i] = a.plan[(size_t)(w0 + i) * sa.G + g];
-  __syncthreads();
+  stage_axis<AXIS>(sa.axis, axis, s_js);
   CfgState st;
-  load_config<LDS>(a, g, tile * sa.tile + (int)threadIdx.x, s_tab, s_rgp, s_rinv, s_thr, s_js, &st);
+  load_config<LDS, AXIS>(a, g, tile * sa.tile + (int)threadIdx.x, s_tab, axis, s_js, &st);
+  // the least utilization from which a tick's TBT is above every other's when its load is, over the wave's candidates
+  // (by the high word, one up: infinity stays)
+  const uint32_t steep_hi = wave_max_u32((uint32_t)((uint64_t)__double_as_longlong(a.steep[(size_t)g * sa.n_tp_f + st.row_lo]) >> 32));
+  const double steep = __longlong_as_double((long long)((uint64_t)min(steep_hi + 1u, 0x7FF00000u) << 32));
+  const size_t cell0 = (size_t)w0 * sa.G + g;
+  const TickRec* rec = a.rec + cell0 * T + min(lane, T - 1);
+  const TickPlan* plan = a.plan + cell0;
+  TickRec next = *rec;
+  TickPlan next_plan = load_plan(plan);
+  __syncthreads();
+  const double e_idle = (st.nd * idle_power<TWO>(st.L)) * a.tick_s;
   for (int w = w0; w < w1; ++w) {
-    const TickPlan pl = s_plan[w - w0];
+    const TickRec r = next;
+    const TickPlan pl = next_plan;
+    if (w + 1 < w1) {
+      rec += (size_t)sa.G * T;
+      plan += sa.G;
+      next = *rec;
+      next_plan = load_plan(plan);
+    }
     if (!mine(pl)) continue;                     // block-uniform
+    const bool empty = pl.j == 0;
     const size_t cell = (size_t)w * sa.G + g;
-    const int32_t* cnt_w = s_cnt + (w - w0) * T;
-    const double* load_w = s_load + (w - w0) * T;
-    const int32_t* eq_w = s_eq + (w - w0) * T;
-    const int j = pl.j;
-    const bool empty = j == 0;
     WalkOut o;
-    if (empty) {
-      o = walk_ticks<4, false, SINGLE, TWO, false, false>(st.L, T, 0, load_w, cnt_w, eq_w, 0, st.nd, a.tick_s);
-      o.ttft = o.tbt = 0.0;
-    } else if (pl.flags & DYN_TP_DENSE) {
-      o = walk_ticks<4, false, SINGLE, TWO, true, false>(st.L, T, j, load_w, cnt_w, eq_w, pl.xj, st.nd, a.tick_s, pl.place);
+    if (empty || (pl.flags & DYN_TP_DENSE)) {
+      o = walk_masked<false, AXIS, TWO>(st.L, T, pl, r, (ScalarRec*)(a.rec + cell * T), st.nd, a.tick_s, e_idle, steep, lane);
+      if (empty) o.ttft = o.tbt = 0.0;           // its ticks' power at load 0 remains
     } else {
-      o = walk_ticks<4, true, SINGLE, TWO, true, false>(st.L, T, j, load_w, cnt_w, eq_w, pl.xj, st.nd, a.tick_s, pl.place);
+      o = walk_masked<true, AXIS, TWO>(st.L, T, pl, r, (ScalarRec*)(a.rec + cell * T), st.nd, a.tick_s, e_idle, steep, lane);
     }
     emit_cell(sa, st, cell, empty, o.ov, o.e, o.ttft, o.tbt);
   }
@@ -1980,10 +2049,10 @@ __device__ __forceinline__ double weighted_from_top(const double* strip, const i
 // of them is a new lower end, or fewer, then the largest one below v is a new upper end.  Both ends are
 // values of the lists from then on, so the search ends with the percentile itself.  A cell with tables (DYN_TP_TABLE) is searched the same way
 // over all lengths, a probe ranked by one entry of every tick's table.
-// LDS: [load grid] [reciprocal spacings] [SINGLE: grid point per bucket] [strip NT x n_tick]
+// LDS: [load axis] [strip NT x n_tick]
 //      [per tick: load] [per tick: count] [per tick: entries listed] [per tick: entries equal to x_j]
 //      [per tick: start of its list, then two words] [the cell's lists when they fit] [bucket index]
-template <bool SINGLE, bool TWO>
+template <int AXIS, bool TWO>
 __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) {
   extern __shared__ double smem[];
   const SpaceArgs& sa = a.s;
@@ -1991,10 +2060,8 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
   const int tid = threadIdx.x, NT = blockDim.x;
   // The table rows stay in global memory (they are read through the caches): consecutive items of a block belong to
   // different classes, and staging a class's rows per item cost more than the look-ups of the item.
-  double* s_rgp = smem;
-  double* s_rinv = s_rgp + (n_rho + 2);
-  double* s_thr = s_rinv + (n_rho + 1);
-  double* s_strip = s_thr + (SINGLE ? sa.n_bucket + 1 : 0);     // [T][NT]
+  const Axis axis = place_axis<AXIS>(smem, n_rho, sa.axis.n_bucket);
+  double* s_strip = axis.end;                                   // [T][NT]
   double* s_load = s_strip + (size_t)T * NT;                    // [T]
   int32_t* s_cnt = (int32_t*)(s_load + T);                      // [T]
   int32_t* s_len = s_cnt + T;                                   // [T] min(j, count)
@@ -2006,7 +2073,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
 
   const uint64_t n_item = (uint64_t)a.counters[1] * (uint64_t)sa.n_tile;   // complete: written by the cell kernel
   if (blockIdx.x >= n_item) return;                              // block-uniform
-  stage_grid<SINGLE>(a, s_rgp, s_thr, s_js);
+  stage_axis<AXIS>(sa.axis, axis, s_js);
   for (uint64_t item = blockIdx.x; item < n_item; item += gridDim.x) {
     const size_t cell = a.slow_list[item / (uint64_t)sa.n_tile];
     const int tile = (int)(item % (uint64_t)sa.n_tile);
@@ -2125,7 +2192,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
     for (int sub = 0; sub < sa.tile; sub += NT) {
       const bool in_tile = sub + (tid & ~(DYN_WAVE - 1)) < sa.tile;   // wave-uniform: a wave past the tile's end stores nothing
       CfgState st;
-      load_config<false>(a, g, tile * sa.tile + (in_tile ? sub + tid : 0), nullptr, s_rgp, s_rinv, s_thr, s_js, &st);
+      load_config<false, AXIS>(a, g, tile * sa.tile + (in_tile ? sub + tid : 0), nullptr, axis, s_js, &st);
       double e = 0.0, pf_min = __builtin_inf(), pf_max = -__builtin_inf(), tb_max = -__builtin_inf();
       bool ov = false;
       const double e_idle = (st.nd * idle_power<TWO>(st.L)) * a.tick_s;
@@ -2134,22 +2201,21 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
           e += e_idle;
           continue;
         }
-        double pf, tb, pw;
-        ov = table_lookup<SINGLE, TWO>(st.L, s_load[q], &pf, &tb, &pw) | ov;
-        e += (st.nd * pw) * a.tick_s;
-        s_strip[q * NT + tid] = dense ? pf : tb;
+        const Looked r = table_lookup<AXIS, TWO>(st.L, s_load[q]);
+        const double pf = r.v[0];
+        ov = r.ov | ov;
+        e += (st.nd * r.v[2]) * a.tick_s;
+        s_strip[q * NT + tid] = dense ? pf : r.v[1];
         pf_min = min_num(pf_min, pf);
         pf_max = max_num(pf_max, pf);
-        tb_max = max_num(tb_max, tb);
+        tb_max = max_num(tb_max, r.v[1]);
       }
       double p_tbt = tb_max;
       if (!dense) {                            // block-uniform
         p_tbt = weighted_from_top(s_strip, s_cnt, T, NT, j, tid);
         for (int q = 0; q < T; ++q) {
           if (s_cnt[q] == 0) continue;
-          double pf, tb, pw;
-          table_lookup<SINGLE, TWO>(st.L, s_load[q], &pf, &tb, &pw);
-          s_strip[q * NT + tid] = pf;
+          s_strip[q * NT + tid] = table_lookup<AXIS, TWO, kPrefill>(st.L, s_load[q]).v[0];
         }
       }
       // TTFT percentile
@@ -2219,20 +2285,13 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void tick_general_kernel(TickArgs a) 
   }
 }
 
-size_t tick_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t n_tick, int32_t win_per_block, bool single) {
-  return (size_t)(2 * n_rho + 3) * sizeof(double) + (single ? ((size_t)n_bucket + 1) * sizeof(double) : 0) +
-         2 * sizeof(double) + (size_t)win_per_block * (n_tick * (sizeof(double) + 2 * sizeof(int32_t)) + sizeof(TickPlan)) +
-         (size_t)2 * n_tick * kFastDepth * sizeof(int32_t) + ((size_t)n_bucket + 1) * sizeof(uint16_t) + 8;
+size_t tick_lds_tail(const TickArgs& a, int32_t n_tick, int32_t win_per_block, int axis) {
+  return dyn_axis_lds(a.s.axis, axis) + 2 * sizeof(double) + (size_t)win_per_block * (n_tick * (sizeof(double) + 2 * sizeof(int32_t)) + sizeof(TickPlan)) +
+         (size_t)2 * n_tick * kFastDepth * sizeof(int32_t);
 }
-size_t tight_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t n_tick, int32_t win_per_block, bool single) {
-  return (size_t)(2 * n_rho + 3) * sizeof(double) + (single ? ((size_t)n_bucket + 1) * sizeof(double) : 0) +
-         (size_t)win_per_block * (n_tick * (sizeof(double) + 2 * sizeof(int32_t)) + sizeof(TickPlan)) +
-         ((size_t)n_bucket + 1) * sizeof(uint16_t) + 8;
-}
-size_t general_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t n_tick, int nt, bool single) {
-  return (size_t)(2 * n_rho + 3) * sizeof(double) + (single ? ((size_t)n_bucket + 1) * sizeof(double) : 0) +
-         (size_t)n_tick * nt * sizeof(double) + (size_t)n_tick * (sizeof(double) + 5 * sizeof(int32_t)) +
-         2 * sizeof(uint32_t) + (size_t)kListCap * sizeof(int32_t) + ((size_t)n_bucket + 1) * sizeof(uint16_t) + 8;
+size_t general_lds_tail(const TickArgs& a, int32_t n_tick, int nt, int axis) {
+  return dyn_axis_lds(a.s.axis, axis) + (size_t)n_tick * nt * sizeof(double) + (size_t)n_tick * (sizeof(double) + 5 * sizeof(int32_t)) +
+         2 * sizeof(uint32_t) + (size_t)kListCap * sizeof(int32_t);
 }
 // Threads of a block of the general kernel: the tile's width, less where the strip (one double per tick and
 // thread) would pass 32 KB.
@@ -2244,37 +2303,46 @@ static_assert(256 * 16 * sizeof(double) <= kStripBytes && 128 * 32 * sizeof(doub
                   64 * DYN_TICK_MAX * sizeof(double) <= kStripBytes,
               "the strip of the general kernel");
 
-template <bool LDS, bool SINGLE, bool TWO>
+template <bool LDS, int AXIS, bool TWO>
 void launch_tight_walk(const TickArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL((tick_tight_walk_kernel<LDS, SINGLE, TWO>), grid, block, lds, s, a);
+  hipLaunchKernelGGL((tick_tight_walk_kernel<LDS, AXIS, TWO>), grid, block, lds, s, a);
 }
-template <bool LDS, bool SINGLE, bool TWO>
+template <bool LDS, int AXIS, bool TWO>
 void launch_space(const TickArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
-  if (a.n_tick <= 16) hipLaunchKernelGGL((tick_space_kernel<16, LDS, SINGLE, TWO>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((tick_space_kernel<DYN_TICK_MAX, LDS, SINGLE, TWO>), grid, block, lds, s, a);
+  if (a.n_tick <= 16) hipLaunchKernelGGL((tick_space_kernel<16, LDS, AXIS, TWO>), grid, block, lds, s, a);
+  else hipLaunchKernelGGL((tick_space_kernel<DYN_TICK_MAX, LDS, AXIS, TWO>), grid, block, lds, s, a);
 }
-template <bool SINGLE, bool TWO>
+template <int AXIS, bool TWO>
 void launch_general(const TickArgs& a, size_t lds, hipStream_t s) {
   DynTimed timed(DYN_K_TICK_MERGE, s);
   // The items are dealt round-robin to the grid: as many blocks as the device holds at once, so that none starts late.
   const int nt = general_threads(a);
   int per_cu = 0, blocks = kGeneralBlocks;
-  if (a.n_cu > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tick_general_kernel<SINGLE, TWO>, nt, lds) == hipSuccess &&
+  if (a.n_cu > 0 && hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, tick_general_kernel<AXIS, TWO>, nt, lds) == hipSuccess &&
       per_cu > 0)
     blocks = per_cu * a.n_cu;
   blocks = (int)std::min<int64_t>(blocks, (int64_t)a.s.n_window * a.s.G * a.s.n_tile);
-  hipLaunchKernelGGL((tick_general_kernel<SINGLE, TWO>), dim3(blocks), dim3(nt), lds, s, a);
+  hipLaunchKernelGGL((tick_general_kernel<AXIS, TWO>), dim3(blocks), dim3(nt), lds, s, a);
 }
 
+template <int V> using Int = std::integral_constant<int, V>;
+template <typename L, typename F>
+void dispatch_axis(L lds, int axis, bool two, F&& f) {
+  auto with = [&](auto x) { if (two) f(lds, x, std::true_type()); else f(lds, x, std::false_type()); };
+  if (axis == DYN_AXIS_EVEN) with(Int<DYN_AXIS_EVEN>());
+  else if (axis == DYN_AXIS_SINGLE) with(Int<DYN_AXIS_SINGLE>());
+  else with(Int<DYN_AXIS_SEARCH>());
+}
 template <typename F>
-void dispatch(bool lds, bool single, bool two, F&& f) {
-  if (lds) {
-    if (single) { if (two) f(std::true_type(), std::true_type(), std::true_type()); else f(std::true_type(), std::true_type(), std::false_type()); }
-    else { if (two) f(std::true_type(), std::false_type(), std::true_type()); else f(std::true_type(), std::false_type(), std::false_type()); }
-  } else {
-    if (single) { if (two) f(std::false_type(), std::true_type(), std::true_type()); else f(std::false_type(), std::true_type(), std::false_type()); }
-    else { if (two) f(std::false_type(), std::false_type(), std::true_type()); else f(std::false_type(), std::false_type(), std::false_type()); }
-  }
+void dispatch(bool lds, int axis, bool two, F&& f) {
+  if (lds) dispatch_axis(std::true_type(), axis, two, f); else dispatch_axis(std::false_type(), axis, two, f);
+}
+// Preferences when LDS is short: keep the table rows in LDS first, the quicker form of the load axis second (without it the bracket is
+// searched; without the rows the tables are read from global memory).
+template <typename Tail>
+int axis_that_fits(const TickArgs& a, size_t tab, Tail&& tail) {
+  const int axis = dyn_axis(a.s.axis);
+  return tail(axis) + tab <= DYN_LDS_BUDGET ? axis : DYN_AXIS_SEARCH;
 }
 
 }  // namespace
@@ -2302,23 +2370,45 @@ hipError_t dyn_launch_tick_cell(const TickCellArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Windows over which the staging (3 us, and 0.12 for every value a thread stages) is 15 % of a block's life, at 0.6 us a tick.
+static int64_t stage_windows(const TickArgs& a) {
+  const double stage = 3.0 + 0.12 * (double)a.s.n_slot * (3 * a.s.n_rho) / a.s.tile;
+  return (int64_t)(stage / (0.15 * 0.6 * a.n_tick)) + 1;
+}
+
 // Windows a block of the evaluation kernels walks.  About 8192 blocks keep cells that differ apart from each other; beyond 16
 // windows a block gains nothing more from its staged rows (a day of 12 ticks: 10 .. 20 alike).  With few ticks a window is soon
-// walked (0.6 us a tick, the chain of one look-up) and the staging (3 us, and 0.12 for every value a thread stages) would be most of a
-// block's life: such blocks walk until it is 15 % of it, as long as the blocks fill three quarters of the device.  Measured (us of
+// walked (0.6 us a tick, the chain of one look-up) and the staging would be most of a block's life: such blocks walk until it is 15 % of it, as long as the blocks fill three quarters of the device.  Measured (us of
 // the call; 8192 blocks, this): 8000 cells of 1 tick and 252 candidates 68, 47; 2800 of 5 ticks 55, 43; 2300 of 6 and 60 candidates 72,
 // 56; 10 800 of 6 and lists 259, 238.  Less again where the per-tick records would not fit beside the table rows.
 int32_t dyn_tick_win_per_block(const TickArgs& a) {
   const SpaceArgs& sa = a.s;
   const size_t tab = (size_t)sa.n_slot * DYN_SLOT_STRIDE(sa.n_rho) * sizeof(double);
   const int64_t cell_tiles = (int64_t)sa.n_window * sa.G * sa.n_tile;
-  const double stage = 3.0 + 0.12 * (double)sa.n_slot * (3 * sa.n_rho) / sa.tile;
-  const int64_t for_stage = (int64_t)(stage / (0.15 * 0.6 * a.n_tick)) + 1;
+  const int64_t for_stage = stage_windows(a);
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(20 * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 8192)));
   const int64_t for_device = cell_tiles / std::max<int64_t>(1, per_cu * a.n_cu * 3 / 4);
   int32_t wpb = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, std::max((cell_tiles + 8191) / 8192, std::min(for_stage, for_device))));
-  while (wpb > 1 && tab + tick_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, wpb, a.single_point) > DYN_LDS_BUDGET) wpb /= 2;
+  while (wpb > 1 && tab + tick_lds_tail(a, a.n_tick, wpb, dyn_axis(sa.axis)) > DYN_LDS_BUDGET) wpb /= 2;
   return wpb;
+}
+
+// How the walk without lists cuts a (class, tile)'s windows.  A block spends 7 us on its set-up where the device is full, 0.43 on a tick:
+// long blocks lose the least by it, but one that begins last runs alone to its end, and the classes differ (22 to 48 us for the same
+// windows, by how many ticks hold requests of the percentile's length).  So where every place on the device has windows enough, blocks of
+// many windows come first and leave four rounds of blocks of few.  36 000 cells of 576 candidates and 12 ticks, us of the call: 14
+// windows a block 441, 10 436, 20 first and then 7 417, 20 and 5 410, 16 and 5 410, 24 and 8 424.
+static void tight_chunks(TickArgs& a, size_t tab) {
+  SpaceArgs& sa = a.s;
+  const int64_t few = std::max<int64_t>(2, std::min<int64_t>(16, stage_windows(a))), many = 4 * few;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((a.any_two_rows ? 20 : 24) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
+  const int64_t places = per_cu * std::max(1, a.n_cu), columns = (int64_t)sa.G * sa.n_tile;
+  const int64_t kept = (4 * few * places + columns - 1) / columns;   // windows left to the blocks of few
+  a.win_long = (int32_t)many;
+  a.n_long = 0;
+  if (columns * sa.n_window < 2 * many * places || sa.n_window - kept < many) return;
+  a.n_long = (int32_t)((sa.n_window - kept) / many);
+  sa.win_per_block = (int32_t)few;
 }
 
 hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
@@ -2328,24 +2418,22 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
   const int n_chunk = (sa.n_window + sa.win_per_block - 1) / sa.win_per_block;
   const dim3 grid((unsigned)((size_t)n_chunk * sa.G * sa.n_tile)), block(sa.tile);
   const size_t tab = (size_t)sa.n_slot * DYN_SLOT_STRIDE(sa.n_rho) * sizeof(double);
-  // Preferences when LDS is short: keep the table rows in LDS first, the per-bucket grid
-  // points second (without them the bracket is searched; without the rows the tables are
-  // read from global memory).
   {
     DynTimed timed(DYN_K_TICK_SPACE, s);         // both walks
     {
-    bool single = a.single_point;
-    size_t tail = tight_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, sa.win_per_block, single);
-    if (single && tail + tab > DYN_LDS_BUDGET) {
-      single = false;
-      tail = tight_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, sa.win_per_block, false);
-    }
+    const int32_t wpb_list = sa.win_per_block;
+    tight_chunks(a, tab);
+    const int64_t chunks = a.n_long + (sa.n_window - (int64_t)a.n_long * a.win_long + sa.win_per_block - 1) / sa.win_per_block;
+    const dim3 grid_t((unsigned)(chunks * sa.G * sa.n_tile));
+    const int axis = axis_that_fits(a, tab, [&](int x) { return dyn_axis_lds(sa.axis, x); });
+    const size_t tail = dyn_axis_lds(sa.axis, axis);
     const bool lds = sa.n_slot > 0 && tab + tail <= DYN_LDS_BUDGET;
     if (!lds && tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
     const size_t bytes = (lds ? tab : 0) + tail;
-    dispatch(lds, single, a.any_two_rows, [&](auto L, auto S, auto W) {
-      launch_tight_walk<decltype(L)::value, decltype(S)::value, decltype(W)::value>(a, grid, block, bytes, s);
+    dispatch(lds, axis, a.any_two_rows, [&](auto L, auto S, auto W) {
+      launch_tight_walk<decltype(L)::value, decltype(S)::value, decltype(W)::value>(a, grid_t, block, bytes, s);
     });
+    sa.win_per_block = wpb_list;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -2359,16 +2447,12 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
       sa.win_per_block = std::min(sa.win_per_block, (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, (cell_tiles + 8191) / 8192)));
       grid_l.x = (unsigned)((size_t)((sa.n_window + sa.win_per_block - 1) / sa.win_per_block) * sa.G * sa.n_tile);
     }
-    bool single = a.single_point;
-    size_t tail = tick_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, sa.win_per_block, single);
-    if (single && tail + tab > DYN_LDS_BUDGET) {
-      single = false;
-      tail = tick_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, sa.win_per_block, false);
-    }
+    const int axis = axis_that_fits(a, tab, [&](int x) { return tick_lds_tail(a, a.n_tick, sa.win_per_block, x); });
+    const size_t tail = tick_lds_tail(a, a.n_tick, sa.win_per_block, axis);
     const bool lds = sa.n_slot > 0 && tab + tail <= DYN_LDS_BUDGET;
     if (!lds && tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
     const size_t bytes = (lds ? tab : 0) + tail;
-    dispatch(lds, single, a.any_two_rows, [&](auto L, auto S, auto W) {
+    dispatch(lds, axis, a.any_two_rows, [&](auto L, auto S, auto W) {
       launch_space<decltype(L)::value, decltype(S)::value, decltype(W)::value>(a, grid_l, block, bytes, s);
     });
     hipError_t e = hipGetLastError();
@@ -2377,14 +2461,10 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
   }
   {
     const int nt = general_threads(a);
-    bool single = a.single_point;
-    size_t tail = general_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, nt, single);
-    if (single && tail > DYN_LDS_BUDGET) {
-      single = false;
-      tail = general_lds_tail(sa.n_rho, sa.n_bucket, a.n_tick, nt, false);
-    }
+    const int axis = axis_that_fits(a, 0, [&](int x) { return general_lds_tail(a, a.n_tick, nt, x); });
+    const size_t tail = general_lds_tail(a, a.n_tick, nt, axis);
     if (tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
-    dispatch(false, single, a.any_two_rows, [&](auto, auto S, auto W) {
+    dispatch(false, axis, a.any_two_rows, [&](auto, auto S, auto W) {
       launch_general<decltype(S)::value, decltype(W)::value>(a, tail, s);
     });
   }
