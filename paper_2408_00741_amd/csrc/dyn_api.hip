@@ -1184,7 +1184,7 @@ namespace {
 struct HierWs {
   EvalWs coarse;                 // header .. cstat of the window-level aggregation (first: its header is the workspace's)
   size_t fine_base; EvalWs fine; // the tick-level aggregation, offsets relative to fine_base
-  size_t tp, lay_n, lay_tp, tick_energy, tick_viol, served_c, served_f, keep, fwd, lay_energy, lay_flags, sel_energy, path, total;
+  size_t tp, lay_n, lay_tp, served_c, served_f, keep, fwd, lay_energy, lay_flags, sel_energy, path, total;
 };
 HierWs hier_ws_layout(int64_t cells, int32_t n_tick, int32_t n_tp, int32_t n_layout) {
   HierWs w;
@@ -1196,8 +1196,6 @@ HierWs hier_ws_layout(int64_t cells, int32_t n_tick, int32_t n_tp, int32_t n_lay
   w.tp = off; off += align256((size_t)n_tp * 4);
   w.lay_n = off; off += align256((size_t)n_layout * 4);
   w.lay_tp = off; off += align256((size_t)n_layout * 4);
-  w.tick_energy = off; off += align256(c * n_tick * 8);
-  w.tick_viol = off; off += align256(c * n_tick);
   // only used with the fragmentation rule (keep holds at most one entry per cell)
   w.served_c = off; off += align256(c * 8);
   w.served_f = off; off += align256(c * n_tick * 8);
@@ -1290,7 +1288,6 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
   a.win_energy = out->window_energy_j; a.win_inf = out->window_infeasible;
   a.lay_energy = c->transition_j ? (double*)(base + w.lay_energy) : nullptr;
   a.lay_flags = c->transition_j ? (uint8_t*)(base + w.lay_flags) : nullptr;
-  a.tick_energy = (double*)(base + w.tick_energy); a.tick_viol = (uint8_t*)(base + w.tick_viol);
   a.served_c = a.served_f = a.keep = a.fwd = nullptr;
   if (c->spill) {
     a.served_c = (double*)(base + w.served_c); a.served_f = (double*)(base + w.served_f);

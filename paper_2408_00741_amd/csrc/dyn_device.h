@@ -213,7 +213,7 @@ __device__ __forceinline__ void read_now(double& a, double& b, double& c, double
 template <int AXIS>
 __device__ __forceinline__ int find_index(const Lookup& L, double rc) {
   if (AXIS == DYN_AXIS_SINGLE) {
-    const int b = (int)(rc * L.scale);
+    const int b = (int)(fmax(rc, 0.0) * L.scale);
     return (int)L.js[b] + (rc >= L.thr[b] ? 1 : 0);
   }
   int j = L.js[(int)(fmax(rc, 0.0) * L.scale)];

@@ -25,8 +25,6 @@ struct HierArgs {
   double* win_energy; int32_t* win_inf;   // [n_window] totals over the classes
   double* lay_energy;           // workspace [cells][n_layout] or NULL: every layout's energy at the reference frequency
   uint8_t* lay_flags;           // workspace [cells][n_layout]: DYN_F_FEASIBLE where the layout fits and meets the SLO
-  double* tick_energy;          // workspace [fine cells]
-  uint8_t* tick_viol;           // workspace [fine cells]
   // fragmentation rule (all NULL without it): loads the pools serve after forwarding, kept fractions
   double* served_c;             // workspace [cells]
   double* served_f;             // workspace [fine cells]

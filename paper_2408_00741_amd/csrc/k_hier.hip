@@ -6,25 +6,30 @@
 //                       and meet the SLO;
 //   hier_freq_kernel    scale-up/down: per tick the frequency of least power among those that meet the
 //                       SLO under the tick's load (the reference frequency, counted, if none does);
-//   hier_sum_kernel     energy of a (window, class) = its ticks' energies added in time order; window
+//                       energy of a (window, class) = its ticks' energies added in time order; window
 //                       totals = the classes' energies added in class order.
 //   hier_spill_*        (fragmentation rule only) before the others: per epoch, classes in ascending order,
 //                       the node counts, the fraction of its arriving load every pool keeps and the loads the
 //                       pools serve in every window and tick once the rest has been forwarded to the next class.
-// The tables stay in global memory (they are a few hundred KB and live in L2; copying a class's tables
+// The frequency kernel's tables stay in global memory (they are a few hundred KB and live in L2; copying a class's tables
 // to LDS per block was measured to cost more than the look-ups it serves).  Two things matter instead:
-// threads of a block share the class, so that a wave's gathers fall into a few table rows, and the
-// frequency kernel takes its look-ups four at a time, level by level (capacity -> bucket -> grid points
-// and table values), so that a thread waits for three rounds of loads per four frequencies, not twelve.
+// neighbouring lanes share the class and the layout, so that a wave's gathers fall into a few table rows, and the
+// kernel takes its look-ups four at a time, level by level (capacity -> grid points -> table values), so that a
+// thread waits for a few rounds of loads per four frequencies, not twelve.
 #include <algorithm>
 
 #include "dyn_hier.h"
+#include "dyn_mixed.h"
 #include "dyn_device.h"
 
 namespace {
 
-constexpr int kShardWaves = 4;          // (window, class) cells per block of the shard kernel, one wave each
+constexpr int kShardWaves = 4;          // of a block of the shard kernel
+constexpr size_t kRowsLds = 16 * 1024;  // rows at the reference frequency are staged in LDS up to this
 constexpr int kFreqThreads = 256;
+constexpr int kTickChunk = 64;          // ticks of a class in LDS at a time
+constexpr int kFreqTabled = 128;        // frequencies up to which the capacities are tabled
+constexpr size_t kFreqLds = 16 * 1024;  // of the results and capacities: blocks beside another stream's kernel find room
 constexpr int kFreqChunk = 4;           // look-ups a thread of the frequency kernel has in flight
 constexpr int kSpillLds = 48 * 1024;    // an epoch's window loads are staged in LDS when they fit in this
 constexpr size_t kAxisLds = 32 * 1024;  // evenly spaced points are staged in triples up to this
@@ -32,28 +37,9 @@ constexpr int kSpillRun = 8;            // classes whose tick loads a thread fet
 
 struct Row { double pf, tb, pw; bool ov; };
 
-// The load axis (grid points, reciprocal spacings, bucket index) is the same for every class and small.  The
-// frequency kernel keeps a copy in LDS, which takes half of a look-up's gathers off the vector memory
-// path (37 -> 30 us for a day of ticks); the shard kernel, whose blocks live for one look-up per lane, reads it
-// from global memory (with the copy its blocks start a memory round trip later: 30 us instead of 26 us).
-struct LoadAxis { const double *grid, *rinv, *thr; const uint16_t* js; const int32_t* js_global; };   // js == nullptr: js_global
-template <int AXIS>
-__device__ __forceinline__ LoadAxis global_axis(const HierArgs& a) {
-  LoadAxis x;
-  x.grid = AXIS == DYN_AXIS_EVEN ? a.axis.even_grid : a.axis.gridpack; x.rinv = a.axis.gridpack + a.n_rho + 2; x.thr = a.axis.thr;
-  x.js = nullptr; x.js_global = AXIS == DYN_AXIS_SINGLE ? a.axis.tstart : a.axis.jstart;
-  return x;
-}
-template <int AXIS>
-__device__ __forceinline__ LoadAxis lds_axis(const HierArgs& a, double* smem) {
-  const Axis s = place_axis<AXIS>(smem, a.n_rho, a.axis.n_bucket);
-  uint16_t* s_js = (uint16_t*)s.end;
-  stage_axis<AXIS>(a.axis, s, s_js);
-  __syncthreads();
-  LoadAxis x;
-  x.grid = s.grid; x.rinv = s.rinv; x.thr = s.thr; x.js = s_js; x.js_global = nullptr;
-  return x;
-}
+// The load axis (grid points, reciprocal spacings, bucket index) is the same for every class and small: a copy in LDS takes half of
+// a look-up's gathers off the vector memory path.
+struct LoadAxis { const double *grid, *rinv, *thr; const uint16_t* js; };
 
 // Bracket of a clamped load fraction rc: largest grid index i <= n_rho-2 with grid[i] <= rc.
 // EVEN: one multiplication, or one less where rc is a rounding below the point.  SINGLE: no bucket holds more than one interior
@@ -67,7 +53,7 @@ __device__ __forceinline__ int bracket(const HierArgs& a, const LoadAxis& x, dou
   }
   const double* grid = x.grid + 1;
   const int b = min((int)(fmax(rc, 0.0) * a.axis.bucket_scale), a.axis.n_bucket);
-  const int j0 = x.js ? (int)x.js[b] : x.js_global[b];
+  const int j0 = (int)x.js[b];
   if (AXIS == DYN_AXIS_SINGLE) return j0 + (rc >= x.thr[b] ? 1 : 0);
   int j = j0;
   while (j > 0 && grid[j] > rc) --j;
@@ -94,19 +80,6 @@ __device__ __forceinline__ void interpolate(const HierArgs& a, const LoadAxis& x
   r->pw = omt * v[2] + t * v[5];
 }
 
-// Row (g, ti, f) at per-instance load `load / n`; values at the last grid point when the load is beyond it.
-template <int AXIS>
-__device__ __forceinline__ Row look_up(const HierArgs& a, const LoadAxis& x, int g, int ti, int f, double load, double n) {
-  const size_t row = ((size_t)g * a.n_tp + ti) * a.n_f + f;
-  const double rho = load / (n * a.ml[row]);
-  const double rho_max = a.axis.rho_max;
-  Row r;
-  r.ov = rho > rho_max;
-  const double rc = r.ov ? rho_max : rho;
-  interpolate<AXIS>(a, x, row, bracket<AXIS>(a, x, rc), rc, &r);
-  return r;
-}
-
 __device__ __forceinline__ double wave_max_f64(double v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v = fmax(v, __shfl_xor(v, d, DYN_WAVE));
@@ -128,126 +101,230 @@ __device__ __forceinline__ double row_max_f64(double v) {
   return fmax(v, dpp_f64<0x128>(v));
 }
 
-// One wave per (window, class); lanes stride the layouts; the lowest index wins equal energies.
-template <int AXIS>
-__global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierArgs a) {
-  const LoadAxis x = global_axis<AXIS>(a);
-  const int lane = threadIdx.x & (DYN_WAVE - 1);
-  const int64_t cell = (int64_t)blockIdx.x * kShardWaves + threadIdx.x / DYN_WAVE;
-  if (cell >= (int64_t)a.n_window * a.G) return;
-  const int w = (int)(cell / a.G), g = (int)(cell % a.G);
-  const CellRec rec = a.rec_c[cell];
-  if (lane == 0 && a.cstat_c[cell]) atomicOr(a.status, (uint32_t)a.cstat_c[cell]);
-  // scale-out/in: the epoch's peak load over the capacity of one node at the reference configuration
-  const int e = w / a.epoch_windows;
+// The node count of epoch e for class g (a wave's work; the same in every lane).
+__device__ __forceinline__ int32_t epoch_nodes(const HierArgs& a, int e, int g, int lane) {
   const int e0 = e * a.epoch_windows, e1 = min(a.n_window, e0 + a.epoch_windows);
-  int32_t nodes;
-  double load = rec.load;
-  if (a.served_c) {                                          // fragmentation rule: both come from the spill kernels
-    nodes = a.nodes[(size_t)e * a.G + g];
-    load = a.served_c[cell];
-  } else {
-    double peak = 0.0;
-    for (int i = e0 + lane; i < e1; i += DYN_WAVE) peak = fmax(peak, a.rec_c[(size_t)i * a.G + g].load);
-    peak = wave_max_f64(peak);
-    const int inst = max(1, a.gpus_per_node / a.tp[a.tp_ref]);
-    const double ml_node = ((double)inst * a.ml[((size_t)g * a.n_tp + a.tp_ref) * a.n_f + a.f_ref]) * a.axis.rho_max;
-    const double q = ceil(peak / ml_node);
-    nodes = q < 1.0 ? 1 : (q > 2147483647.0 ? 2147483647 : (int32_t)q);
-    if (w == e0 && lane == 0) a.nodes[(size_t)e * a.G + g] = nodes;
-  }
-  const int64_t budget = (int64_t)nodes * a.gpus_per_node;
-  // shard-up/down at the reference frequency
-  const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
-  double best_e = __builtin_inf();
-  int best = 0x7FFFFFFF;
-  for (int l = lane; l < a.n_layout; l += DYN_WAVE) {
-    const int n = a.lay_n[l], ti = a.lay_tp[l];
-    bool ok = (int64_t)n * a.tp[ti] <= budget;
-    double en = __builtin_inf();
-    if (ok) {
-      const Row r = look_up<AXIS>(a, x, g, ti, a.f_ref, load, (double)n);
-      ok = !(r.ov || rec.xp99 * r.pf > slo_t || r.tb * rec.nonempty > slo_b);
-      en = ((double)n * r.pw) * a.window_s;
-    }
-    if (a.lay_energy) {                                      // the sequence selection takes it from here
-      a.lay_energy[(size_t)cell * a.n_layout + l] = en;
-      a.lay_flags[(size_t)cell * a.n_layout + l] = ok ? (uint8_t)DYN_F_FEASIBLE : (uint8_t)0;
-    }
-    if (ok && (best == 0x7FFFFFFF || en < best_e)) { best_e = en; best = l; }   // l ascends per lane
-  }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    const double oe = __shfl_xor(best_e, d, DYN_WAVE);
-    const int ol = __shfl_xor(best, d, DYN_WAVE);
-    if (ol != 0x7FFFFFFF && (best == 0x7FFFFFFF || oe < best_e || (oe == best_e && ol < best))) { best_e = oe; best = ol; }
-  }
-  if (lane == 0) a.layout_sel[cell] = best == 0x7FFFFFFF ? -1 : best;
+  double peak = 0.0;
+  for (int i = e0 + lane; i < e1; i += DYN_WAVE) peak = fmax(peak, a.rec_c[(size_t)i * a.G + g].load);
+  peak = row_max_f64(peak);                                  // of 16 lanes, then of the four rows
+  peak = fmax(fmax(lane_f64(peak, 0), lane_f64(peak, 16)), fmax(lane_f64(peak, 32), lane_f64(peak, 48)));
+  const int inst = max(1, a.gpus_per_node / a.tp[a.tp_ref]);
+  const double ml_node = ((double)inst * a.ml[((size_t)g * a.n_tp + a.tp_ref) * a.n_f + a.f_ref]) * a.axis.rho_max;
+  const double q = ceil(peak / ml_node);
+  return q < 1.0 ? 1 : (q > 2147483647.0 ? 2147483647 : (int32_t)q);
 }
 
-// One thread per (window, tick, class).  A block stays within one class: its threads then read the same
-// few table rows, and a wave's look-up touches a handful of cache lines instead of one per lane.
-template <int AXIS>
-__global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a) {
-  extern __shared__ double s_axis[];
-  const LoadAxis x = lds_axis<AXIS>(a, s_axis);
+// Block = (run of windows, class), one wave per `per_wave` windows after each other.  A lane is a layout; what depends on the class and the
+// layout only (capacity and its reciprocal, the rows at the reference frequency, which a block keeps in LDS) is formed once, a wave's
+// records and statuses are read together, and the nodes are counted where an epoch begins.  A wave a cell, which did all of that
+// for one look-up per lane, took 28 us for 36 000 cells of 48 layouts, bound by its chain of loads.
+// LDS: [load axis] [rows at f_ref n_tp*3*n_rho (ROWS)] [bucket index (16-bit)]
+template <bool ROWS, int AXIS>
+__global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierArgs a, int per_wave) {
+  extern __shared__ double s_shard[];
+  const int lane = threadIdx.x & (DYN_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int g = blockIdx.x % a.G;
-  const int64_t wt = (int64_t)(blockIdx.x / a.G) * kFreqThreads + threadIdx.x;   // window * n_tick + tick
-  if (wt >= (int64_t)a.n_window * a.n_tick) return;
-  const int64_t f = wt * a.G + g;
-  const int w = (int)(wt / a.n_tick);
-  if (a.cstat_f[f]) atomicOr(a.status, (uint32_t)a.cstat_f[f]);
-  const int l = a.layout_sel[(size_t)w * a.G + g];
-  if (l < 0) {
-    a.f_sel[f] = -1;
-    a.tick_energy[f] = 0.0;
-    a.tick_viol[f] = 0;
-    return;
+  const int w0 = ((int)(blockIdx.x / a.G) * kShardWaves + wave) * per_wave, w1 = min(w0 + per_wave, a.n_window);
+  const Axis axis = place_axis<AXIS>(s_shard, a.n_rho, a.axis.n_bucket);
+  double* s_rows = axis.end;
+  uint16_t* s_js = (uint16_t*)(s_rows + (ROWS ? (size_t)a.n_tp * 3 * a.n_rho : 0));
+  const size_t row_ref = ((size_t)g * a.n_tp) * a.n_f + a.f_ref;   // of the first TP degree; the next is n_f rows on
+
+  CellRec mine;                                              // lane i: the wave's window i (per_wave <= 64)
+  mine.load = mine.xp99 = mine.nonempty = 0.0;
+  if (w0 + lane < w1) {
+    const size_t cell = (size_t)(w0 + lane) * a.G + g;
+    mine = a.rec_c[cell];
+    if (a.served_c) mine.load = a.served_c[cell];            // fragmentation rule: loads and node counts come from the spill kernels
+    if (a.cstat_c[cell]) atomicOr(a.status, (uint32_t)a.cstat_c[cell]);
   }
-  const CellRec rec = a.rec_f[f];
-  const double load = a.served_f ? a.served_f[f] : rec.load;
-  const int n = a.lay_n[l], ti = a.lay_tp[l];
-  const double nd = (double)n;
+  if (ROWS)
+    for (int t = wave; t < a.n_tp; t += kShardWaves)
+      for (int i = lane; i < 3 * a.n_rho; i += DYN_WAVE) s_rows[t * 3 * a.n_rho + i] = a.tab[(row_ref + (size_t)t * a.n_f) * 3 * a.n_rho + i];
+  stage_axis<AXIS>(a.axis, axis, s_js);
+
+  struct Layout { int64_t gpus; double nd; };
+  Lookup L;
+  Layout y;
+  auto take = [&](int l) {                                   // the constants of layout l
+    const int n = a.lay_n[l], ti = a.lay_tp[l];
+    y.gpus = (int64_t)n * a.tp[ti];
+    y.nd = (double)n;
+    L.den = y.nd * a.ml[row_ref + (size_t)ti * a.n_f];
+    L.rden = 1.0 / L.den;
+    L.lo = ROWS ? s_rows + ti * 3 * a.n_rho : a.tab + (row_ref + (size_t)ti * a.n_f) * 3 * a.n_rho;
+    L.hi = L.lo;
+  };
+  use_axis<AXIS>(a.axis, axis, s_js, &L);
+  L.u = 0.0; L.omu = 1.0;
+  take(min(lane, a.n_layout - 1));
   const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
+  __syncthreads();
+  int e_now = -1;
+  int64_t budget = 0;
+  for (int w = w0; w < w1; ++w) {
+    const int at = w - w0;
+    const double load = lane_f64(mine.load, at), xp99 = lane_f64(mine.xp99, at), nonempty = lane_f64(mine.nonempty, at);
+    const size_t cell = (size_t)w * a.G + g;
+    const int e = w / a.epoch_windows;
+    if (e != e_now) {
+      e_now = e;
+      const int32_t nodes = a.served_c ? a.nodes[(size_t)e * a.G + g] : epoch_nodes(a, e, g, lane);
+      if (!a.served_c && w == e * a.epoch_windows && lane == 0) a.nodes[(size_t)e * a.G + g] = nodes;
+      budget = (int64_t)nodes * a.gpus_per_node;
+    }
+    double best_e = __builtin_inf();
+    int best = 0x7FFFFFFF;
+    for (int l0 = 0; l0 < a.n_layout; l0 += DYN_WAVE) {
+      const int l = l0 + lane;
+      if (a.n_layout > DYN_WAVE) take(min(l, a.n_layout - 1));
+      const Looked r = table_lookup<AXIS, false>(L, load);
+      const bool fits = l < a.n_layout && y.gpus <= budget;
+      const bool ok = fits && !(r.ov || xp99 * r.v[0] > slo_t || r.v[1] * nonempty > slo_b);
+      const double en = fits ? (y.nd * r.v[2]) * a.window_s : __builtin_inf();
+      if (a.lay_energy && l < a.n_layout) {                  // the sequence selection takes it from here
+        a.lay_energy[cell * a.n_layout + l] = en;
+        a.lay_flags[cell * a.n_layout + l] = ok ? (uint8_t)DYN_F_FEASIBLE : (uint8_t)0;
+      }
+      if (ok && (best == 0x7FFFFFFF || en < best_e)) { best_e = en; best = l; }   // l ascends per lane
+    }
+    // least energy, the lowest index among equals; energies are >= +0, so their bits order as integers
+    const uint64_t bits = (uint64_t)__double_as_longlong(best_e);
+    const bool has = best != 0x7FFFFFFF;
+    const uint32_t hi = has ? (uint32_t)(bits >> 32) : 0xFFFFFFFFu;
+    const uint32_t most = wave_min_u32(hi);
+    const uint32_t lo = has && hi == most ? (uint32_t)bits : 0xFFFFFFFFu;
+    const uint32_t least = wave_min_u32(lo);
+    const uint32_t l = wave_min_u32(has && hi == most && lo == least ? (uint32_t)best : 0xFFFFFFFFu);
+    if (lane == 0) a.layout_sel[cell] = (int32_t)l;          // -1 where no lane has one
+  }
+}
+
+// Block = (window, run of classes); a thread takes (class, tick) pairs, ticks fastest, so that the ticks of a cell, which share the layout and
+// mostly the bracket, are neighbouring lanes and read the same few lines of the tables.  The cells' capacities per frequency and their
+// reciprocals come from a table in LDS (TABLED; a division and a gather less per look-up).  Frequencies and energies meet in LDS: they
+// leave it with the classes side by side, and a thread per class adds its ticks in time order, in chunks of kTickChunk.  With one run of
+// classes the window's totals are added here too, in class order.  With a block per class and 256 ticks, results written a class apart
+// and a kernel of its own for the sums: 31 + 7.6 us for 432 000 ticks.
+// LDS: [load axis] [energy chunk*run] [capacities, reciprocals run*n_f each (TABLED)] [instances run] [frequency chunk*run] [TP run] [bucket index]
+template <bool TABLED, int AXIS>
+__global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a, int run, int n_run, int chunk) {
+  extern __shared__ double s_freq[];
+  const int w = blockIdx.x / n_run, g0 = (int)(blockIdx.x % n_run) * run, n_g = min(run, a.G - g0);
+  const Axis axis = place_axis<AXIS>(s_freq, a.n_rho, a.axis.n_bucket);
+  double* s_e = axis.end;                                    // [chunk][run]
+  double* s_den = s_e + (size_t)chunk * run;                 // [run][n_f]
+  double* s_rden = s_den + (TABLED ? (size_t)run * a.n_f : 0);
+  double* s_nd = s_rden + (TABLED ? (size_t)run * a.n_f : 0);
+  int32_t* s_f = (int32_t*)(s_nd + run);                     // [chunk][run]; bit 30: no frequency was admissible
+  int32_t* s_ti = s_f + chunk * run;                         // -1: no layout
+  uint16_t* s_js = (uint16_t*)(s_ti + run);
+  stage_axis<AXIS>(a.axis, axis, s_js);
+  for (int i = threadIdx.x; i < n_g; i += blockDim.x) {
+    const int l = a.layout_sel[(size_t)w * a.G + g0 + i];
+    s_ti[i] = l < 0 ? -1 : a.lay_tp[l];
+    s_nd[i] = l < 0 ? 1.0 : (double)a.lay_n[l];
+  }
+  __syncthreads();
+  if (TABLED) {
+    for (int i = threadIdx.x; i < n_g * a.n_f; i += blockDim.x) {
+      const int g = i / a.n_f, f = i - g * a.n_f;
+      const double den = s_nd[g] * a.ml[((size_t)(g0 + g) * a.n_tp + max(s_ti[g], 0)) * a.n_f + f];
+      s_den[i] = den;
+      s_rden[i] = 1.0 / den;
+    }
+    __syncthreads();
+  }
+  LoadAxis x;
+  x.grid = axis.grid; x.rinv = axis.rinv; x.thr = axis.thr; x.js = s_js;
   const double rho_max = a.axis.rho_max;
-  const size_t row0 = ((size_t)g * a.n_tp + ti) * a.n_f;
-  int bf = -1;
-  double bp = __builtin_inf(), pw_ref = 0.0;
-  for (int f0 = 0; f0 < a.n_f; f0 += kFreqChunk) {
-    double rc[kFreqChunk];
-    bool ov[kFreqChunk];
-    int j[kFreqChunk];
-    Row r[kFreqChunk];
+  double sum = 0.0;                                          // thread i: of class g0 + i (run <= kFreqThreads)
+  int32_t viol = 0;
+  for (int q0 = 0; q0 < a.n_tick; q0 += chunk) {
+    const int n_q = min(chunk, a.n_tick - q0);
+    for (int i = threadIdx.x; i < n_g * n_q; i += blockDim.x) {
+      const int gl = i / n_q, q = i - gl * n_q, g = g0 + gl, ti = s_ti[gl];
+      const size_t f = ((size_t)w * a.n_tick + q0 + q) * a.G + g;
+      if (a.cstat_f[f]) atomicOr(a.status, (uint32_t)a.cstat_f[f]);
+      if (ti < 0) {
+        s_f[q * run + gl] = -1;
+        s_e[q * run + gl] = 0.0;
+        continue;
+      }
+      const CellRec rec = a.rec_f[f];
+      const double load = a.served_f ? a.served_f[f] : rec.load;
+      const double nd = s_nd[gl];
+      const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
+      const size_t row0 = ((size_t)g * a.n_tp + ti) * a.n_f;
+      int bf = -1;
+      double bp = __builtin_inf(), pw_ref = 0.0;
+      for (int f0 = 0; f0 < a.n_f; f0 += kFreqChunk) {
+        double rc[kFreqChunk];
+        bool ov[kFreqChunk];
+        int j[kFreqChunk];
+        Row r[kFreqChunk];
 #pragma unroll
-    for (int c = 0; c < kFreqChunk; ++c) {                   // level 1: capacities
-      const int fi = min(f0 + c, a.n_f - 1);
-      const double rho = load / (nd * a.ml[row0 + fi]);
-      ov[c] = rho > rho_max;
-      rc[c] = ov[c] ? rho_max : rho;
+        for (int c = 0; c < kFreqChunk; ++c) {               // level 1: capacities
+          const int fi = min(f0 + c, a.n_f - 1);
+          const double rho = TABLED ? div_by(load, s_den[gl * a.n_f + fi], s_rden[gl * a.n_f + fi]) : load / (nd * a.ml[row0 + fi]);
+          ov[c] = rho > rho_max;
+          rc[c] = ov[c] ? rho_max : rho;
+        }
+#pragma unroll
+        for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(a, x, rc[c]);   // level 2: the load axis
+#pragma unroll
+        for (int c = 0; c < kFreqChunk; ++c)                 // level 3: table values
+          interpolate<AXIS>(a, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
+#pragma unroll
+        for (int c = 0; c < kFreqChunk; ++c) {               // ascending frequency: the lowest wins equal powers
+          const int fi = f0 + c;
+          if (fi >= a.n_f) break;
+          if (fi == a.f_ref) pw_ref = r[c].pw;
+          if (ov[c] || rec.xp99 * r[c].pf > slo_t || r[c].tb * rec.nonempty > slo_b) continue;
+          if (bf < 0 || r[c].pw < bp) { bf = fi; bp = r[c].pw; }
+        }
+      }
+      int32_t none = 0;
+      if (bf < 0) {                                          // nothing admissible: the reference frequency, counted
+        bp = pw_ref;
+        bf = a.f_ref;
+        none = 1 << 30;
+      }
+      s_f[q * run + gl] = bf | none;
+      s_e[q * run + gl] = (nd * bp) * a.tick_s;
     }
-#pragma unroll
-    for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(a, x, rc[c]);   // level 2: bucket index
-#pragma unroll
-    for (int c = 0; c < kFreqChunk; ++c)                     // level 3: grid points and table values
-      interpolate<AXIS>(a, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
-#pragma unroll
-    for (int c = 0; c < kFreqChunk; ++c) {                   // ascending frequency: the lowest wins equal powers
-      const int fi = f0 + c;
-      if (fi >= a.n_f) break;
-      if (fi == a.f_ref) pw_ref = r[c].pw;
-      if (ov[c] || rec.xp99 * r[c].pf > slo_t || r[c].tb * rec.nonempty > slo_b) continue;
-      if (bf < 0 || r[c].pw < bp) { bf = fi; bp = r[c].pw; }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n_g * n_q; i += blockDim.x) {
+      const int q = i / n_g, gl = i - q * n_g;
+      const int32_t v = s_f[q * run + gl];
+      a.f_sel[((size_t)w * a.n_tick + q0 + q) * a.G + g0 + gl] = v < 0 ? -1 : v & ~(1 << 30);
     }
+    if ((int)threadIdx.x < n_g)
+      for (int q = 0; q < n_q; ++q) {                        // time order
+        sum += s_e[q * run + threadIdx.x];
+        const int32_t v = s_f[q * run + threadIdx.x];
+        viol += v >= 0 ? v >> 30 : 0;
+      }
+    __syncthreads();
   }
-  uint8_t viol = 0;
-  if (bf < 0) {                                              // nothing admissible: the reference frequency, counted
-    bp = pw_ref;
-    bf = a.f_ref;
-    viol = 1;
+  if ((int)threadIdx.x < n_g) {
+    const size_t cell = (size_t)w * a.G + g0 + threadIdx.x;
+    const bool has = s_ti[threadIdx.x] >= 0;
+    a.energy[cell] = has ? sum : __builtin_inf();
+    a.violations[cell] = has ? viol : 0;
+    s_e[threadIdx.x] = sum;
   }
-  a.f_sel[f] = bf;
-  a.tick_energy[f] = (nd * bp) * a.tick_s;
-  a.tick_viol[f] = viol;
+  if (n_run > 1) return;                                     // the totals are another kernel's
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double e = 0.0;
+    int32_t ninf = 0;
+    for (int g = 0; g < n_g; ++g) {
+      if (s_ti[g] >= 0) e += s_e[g]; else ++ninf;
+    }
+    a.win_energy[w] = e;
+    a.win_inf[w] = ninf;
+  }
 }
 
 // Fragmentation rule, window level.  One wave per epoch, lanes stride the epoch's windows, classes one after the
@@ -364,38 +441,6 @@ __global__ __launch_bounds__(DYN_WAVE) void hier_spill_tick_kernel(HierArgs a) {
   }
 }
 
-// One block per window: thread g adds the ticks of (window, g) in time order; thread 0 then adds the
-// classes in class order.
-__global__ __launch_bounds__(64) void hier_sum_kernel(HierArgs a) {
-  extern __shared__ double s_e[];                            // [G] energy, NaN marks "no layout"
-  const int w = blockIdx.x;
-  for (int g = threadIdx.x; g < a.G; g += blockDim.x) {
-    const size_t cell = (size_t)w * a.G + g;
-    const bool has = a.layout_sel[cell] >= 0;
-    double e = 0.0;
-    int32_t v = 0;
-    for (int q = 0; q < a.n_tick; ++q) {                     // time order
-      const size_t f = ((size_t)w * a.n_tick + q) * a.G + g;
-      e += a.tick_energy[f];
-      v += a.tick_viol[f];
-    }
-    a.energy[cell] = has ? e : __builtin_inf();
-    a.violations[cell] = has ? v : 0;
-    s_e[g] = has ? e : __builtin_nan("");
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double e = 0.0;
-    int32_t ninf = 0;
-    for (int g = 0; g < a.G; ++g) {
-      const double x = s_e[g];
-      if (x == x) e += x; else ++ninf;
-    }
-    a.win_energy[w] = e;
-    a.win_inf[w] = ninf;
-  }
-}
-
 // Evenly spaced points beyond what LDS holds in triples keep the other forms (at most 4097 buckets: 42 KB and the points).
 int hier_axis(const HierArgs& a) {
   const int axis = dyn_axis(a.axis);
@@ -423,23 +468,47 @@ hipError_t dyn_launch_hier_spill(const HierArgs& a, hipStream_t s) {
 }
 
 hipError_t dyn_launch_hier_shard(const HierArgs& a, hipStream_t s) {
+  // Windows a wave: as many as leave the device its waves (8192), and no more than 8; the blocks' set-up is by then a small part.
   const int64_t cells = (int64_t)a.n_window * a.G;
-  const unsigned shard_blocks = (unsigned)((cells + kShardWaves - 1) / kShardWaves);
+  const int per_wave = (int)std::max<int64_t>(1, std::min<int64_t>(8, cells / 6144));
+  const int64_t runs = (a.n_window + (int64_t)per_wave * kShardWaves - 1) / ((int64_t)per_wave * kShardWaves);
+  const int axis = hier_axis(a);
+  const size_t rows = (size_t)a.n_tp * 3 * a.n_rho * sizeof(double);
+  const bool in_lds = rows <= kRowsLds && dyn_axis_lds(a.axis, axis) + rows <= DYN_LDS_BUDGET;
+  const size_t lds = dyn_axis_lds(a.axis, axis) + (in_lds ? rows : 0);
   DynTimed timed(DYN_K_HIER, s);
-  with_axis(dyn_axis(a.axis), [&](auto x) {
-    hipLaunchKernelGGL(hier_shard_kernel<decltype(x)::value>, dim3(shard_blocks), dim3(kShardWaves * DYN_WAVE), 0, s, a);
+  with_axis(axis, [&](auto x) {
+    if (in_lds) hipLaunchKernelGGL((hier_shard_kernel<true, decltype(x)::value>), dim3((unsigned)(runs * a.G)), dim3(kShardWaves * DYN_WAVE), lds, s, a, per_wave);
+    else hipLaunchKernelGGL((hier_shard_kernel<false, decltype(x)::value>), dim3((unsigned)(runs * a.G)), dim3(kShardWaves * DYN_WAVE), lds, s, a, per_wave);
   });
   return hipGetLastError();
 }
 
 hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s) {
-  const int64_t ticks = (int64_t)a.n_window * a.n_tick;
-  const unsigned freq_blocks = (unsigned)(((ticks + kFreqThreads - 1) / kFreqThreads) * a.G);
-  DynTimed timed(DYN_K_HIER, s);
-  const int axis = hier_axis(a);
-  with_axis(axis, [&](auto x) {
-    hipLaunchKernelGGL(hier_freq_kernel<decltype(x)::value>, dim3(freq_blocks), dim3(kFreqThreads), dyn_axis_lds(a.axis, axis), s, a);
-  });
-  hipLaunchKernelGGL(hier_sum_kernel, dim3((unsigned)a.n_window), dim3(64), (size_t)a.G * sizeof(double), s, a);
+  // A long load axis keeps its place in LDS: then fewer classes, no table of capacities, in the end tick by tick.
+  int axis = hier_axis(a);
+  if (dyn_axis_lds(a.axis, axis) + kFreqLds > DYN_LDS_BUDGET) axis = DYN_AXIS_SEARCH;
+  const size_t axis_lds = dyn_axis_lds(a.axis, axis), room = axis_lds < DYN_LDS_BUDGET ? std::min(kFreqLds, DYN_LDS_BUDGET - axis_lds) : 0;
+  int chunk = std::min(a.n_tick, kTickChunk);
+  bool tabled = a.n_f <= kFreqTabled;
+  auto of_class = [&] { return (size_t)chunk * (sizeof(double) + sizeof(int32_t)) + (tabled ? (size_t)a.n_f * 2 * sizeof(double) : 0) + sizeof(double) + sizeof(int32_t); };
+  if (of_class() > room) tabled = false;
+  if (of_class() > room) chunk = 1;
+  const size_t per_class = of_class();
+  const int run = (int)std::max<size_t>(1, std::min<size_t>(std::min(a.G, kFreqThreads), room / per_class));
+  const int n_run = (a.G + run - 1) / run;
+  const size_t lds = axis_lds + (size_t)run * per_class;
+  {
+    DynTimed timed(DYN_K_HIER, s);
+    const dim3 grid((unsigned)((int64_t)a.n_window * n_run));
+    with_axis(axis, [&](auto x) {
+      if (tabled) hipLaunchKernelGGL((hier_freq_kernel<true, decltype(x)::value>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+      else hipLaunchKernelGGL((hier_freq_kernel<false, decltype(x)::value>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+    });
+  }
+  if (n_run > 1) {
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : dyn_launch_window_totals(a.layout_sel, a.energy, a.n_window, a.G, a.win_energy, a.win_inf, s);
+  }
   return hipGetLastError();
 }
