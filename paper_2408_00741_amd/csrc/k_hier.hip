@@ -14,8 +14,8 @@
 // The frequency kernel's tables stay in global memory (they are a few hundred KB and live in L2; copying a class's tables
 // to LDS per block was measured to cost more than the look-ups it serves).  Two things matter instead:
 // neighbouring lanes share the class and the layout, so that a wave's gathers fall into a few table rows, and the
-// kernel takes its look-ups four at a time, level by level (capacity -> grid points -> table values), so that a
-// thread waits for a few rounds of loads per four frequencies, not twelve.
+// kernel takes its look-ups three at a time, level by level (capacity -> grid points -> table values), so that a
+// thread waits for a few rounds of loads per three frequencies, not nine.
 #include <algorithm>
 
 #include "dyn_hier.h"
@@ -30,7 +30,7 @@ constexpr int kFreqThreads = 256;
 constexpr int kTickChunk = 64;          // ticks of a class in LDS at a time
 constexpr int kFreqTabled = 128;        // frequencies up to which the capacities are tabled
 constexpr size_t kFreqLds = 16 * 1024;  // of the results and capacities: blocks beside another stream's kernel find room
-constexpr int kFreqChunk = 4;           // look-ups a thread of the frequency kernel has in flight
+constexpr int kFreqChunk = 3;           // look-ups a thread of the frequency kernel has in flight: four need the registers of a third of the waves (35 us, 27)
 constexpr int kSpillLds = 48 * 1024;    // an epoch's window loads are staged in LDS when they fit in this
 constexpr size_t kAxisLds = 32 * 1024;  // evenly spaced points are staged in triples up to this
 constexpr int kSpillRun = 8;            // classes whose tick loads a thread fetches ahead of the chain
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
 // and a kernel of its own for the sums: 31 + 7.6 us for 432 000 ticks.
 // LDS: [load axis] [energy chunk*run] [capacities, reciprocals run*n_f each (TABLED)] [instances run] [frequency chunk*run] [TP run] [bucket index]
 template <bool TABLED, int AXIS>
-__global__ __launch_bounds__(kFreqThreads) void hier_freq_kernel(HierArgs a, int run, int n_run, int chunk) {
+__global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void hier_freq_kernel(HierArgs a, int run, int n_run, int chunk) {
   extern __shared__ double s_freq[];
   const int w = blockIdx.x / n_run, g0 = (int)(blockIdx.x % n_run) * run, n_g = min(run, a.G - g0);
   const Axis axis = place_axis<AXIS>(s_freq, a.n_rho, a.axis.n_bucket);
