@@ -48,7 +48,7 @@ hipError_t dev_alloc(T** p, size_t count) {
 }
 
 void free_profile_device(dyn_profile* p) {
-  void* ptrs[] = {p->d_tab, p->d_ml, p->d_pw0, p->d_pfspan, p->d_steep, p->d_theta, p->d_gridpack, p->d_even_grid, p->d_jstart, p->d_tstart, p->d_thr, p->d_cfg,
+  void* ptrs[] = {p->d_tab, p->d_ml, p->d_pw0, p->d_pfspan, p->d_theta, p->d_gridpack, p->d_jstart, p->d_tstart, p->d_thr, p->d_cfg,
                   p->d_tile_rows, p->d_slo_ttft, p->d_slo_tbt, p->d_budget, p->d_path_layout, p->d_path_order,
                   p->d_path_seg, p->d_path_trans, p->d_hier_trans, p->d_lay_n, p->d_lay_tp, p->d_tp, p->d_ident};
   for (void* q : ptrs)
@@ -554,12 +554,9 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   p->even_scale = (double)(d->n_rho - 1) / rho_max * (1.0 + 0x1p-40);
   p->even = true;                            // rho[0] is 0
   for (int q = 1; q < d->n_rho && p->even; ++q) p->even = (int)(d->rho[q] * p->even_scale) == q;
-  std::vector<double> even_grid(3 * (size_t)(d->n_rho - 1));
-  for (int q = 0; q + 1 < d->n_rho; ++q) {
-    even_grid[3 * (size_t)q] = d->rho[q];
-    even_grid[3 * (size_t)q + 1] = d->rho[q + 1] - d->rho[q];
-    even_grid[3 * (size_t)q + 2] = gridpack[d->n_rho + 3 + q];
-  }
+  const size_t even_at = gridpack.size();       // the triples follow the padded grid in its allocation
+  for (int q = 0; q + 1 < d->n_rho; ++q)
+    for (double v : {d->rho[q], d->rho[q + 1] - d->rho[q], gridpack[d->n_rho + 3 + q]}) gridpack.push_back(v);
   // one packed row per (class, TP, f): (prefill, TBT, power) per load point
   std::vector<double> packed(3 * n_tab);
   for (size_t r = 0; r < n_row; ++r) {
@@ -579,7 +576,8 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
     pfspan[2 * r] = *std::min_element(row, row + d->n_rho);
     pfspan[2 * r + 1] = *std::max_element(row, row + d->n_rho);
   }
-  std::vector<double> steep(n_row);
+  pfspan.resize(3 * n_row);                      // d_steep follows the spans in their allocation
+  double* steep = pfspan.data() + 2 * n_row;
   for (size_t r = 0; r < n_row; ++r) {
     const double* v = d->tbt_ms + r * d->n_rho;
     double slope = INFINITY;
@@ -605,10 +603,10 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   bool ok = hip_ok(hipGetDevice(&p->device), "hipGetDevice") &&
             hip_ok(hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device), "hipDeviceGetAttribute") &&
             hip_ok(dev_alloc(&p->d_tab, 3 * n_tab), "hipMalloc") && hip_ok(dev_alloc(&p->d_ml, n_row), "hipMalloc") &&
-            hip_ok(dev_alloc(&p->d_pw0, n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_pfspan, 2 * n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_steep, n_row), "hipMalloc") &&
+            hip_ok(dev_alloc(&p->d_pw0, n_row), "hipMalloc") && hip_ok(dev_alloc(&p->d_pfspan, pfspan.size()), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_theta, (size_t)p->G), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_gridpack, gridpack.size()), "hipMalloc") &&
-            hip_ok(dev_alloc(&p->d_even_grid, even_grid.size()), "hipMalloc") && hip_ok(dev_alloc(&p->d_jstart, js.size()), "hipMalloc") &&
+            hip_ok(dev_alloc(&p->d_jstart, js.size()), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_tstart, tstart.size()), "hipMalloc") && hip_ok(dev_alloc(&p->d_thr, thr.size()), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_cfg, DYN_MAX_CONFIGS), "hipMalloc") &&
             hip_ok(dev_alloc(&p->d_tile_rows, 2 * DYN_MAX_CONFIGS + 1024), "hipMalloc") &&
@@ -622,14 +620,16 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
             hip_ok(dev_alloc(&p->d_tp, p->n_tp), "hipMalloc") && hip_ok(dev_alloc(&p->d_ident, DYN_MAX_CONFIGS + 1), "hipMalloc");
   std::vector<int32_t> ident(DYN_MAX_CONFIGS + 1);
   std::iota(ident.begin(), ident.end(), 0);
+  if (ok) {
+    p->d_even_grid = p->d_gridpack + even_at;
+    p->d_steep = p->d_pfspan + 2 * n_row;
+  }
   ok = ok && hip_ok(hipMemcpyAsync(p->d_tab, packed.data(), 3 * n_tab * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_ml, d->max_load_tps, n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_pw0, pw0.data(), n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
-       hip_ok(hipMemcpyAsync(p->d_pfspan, pfspan.data(), 2 * n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
-       hip_ok(hipMemcpyAsync(p->d_steep, steep.data(), n_row * 8, hipMemcpyHostToDevice, s), "copy") &&
+       hip_ok(hipMemcpyAsync(p->d_pfspan, pfspan.data(), pfspan.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_theta, theta.data(), (size_t)p->G * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_gridpack, gridpack.data(), gridpack.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
-       hip_ok(hipMemcpyAsync(p->d_even_grid, even_grid.data(), even_grid.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_jstart, js.data(), js.size() * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_tstart, tstart.data(), tstart.size() * 4, hipMemcpyHostToDevice, s), "copy") &&
        hip_ok(hipMemcpyAsync(p->d_thr, thr.data(), thr.size() * 8, hipMemcpyHostToDevice, s), "copy") &&
