@@ -557,19 +557,18 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   const size_t even_at = gridpack.size();       // the triples follow the padded grid in its allocation
   for (int q = 0; q + 1 < d->n_rho; ++q)
     for (double v : {d->rho[q], d->rho[q + 1] - d->rho[q], gridpack[d->n_rho + 3 + q]}) gridpack.push_back(v);
-  // one packed row per (class, TP, f): (prefill, TBT, power) per load point
+  // one packed row per (class, TP, f): (prefill, TBT, power) per load point.  A zero with a sign (which passes as >= 0) loses it: the
+  // kernels order energies and costs by their bits, where -0.0 is the largest
   std::vector<double> packed(3 * n_tab);
-  for (size_t r = 0; r < n_row; ++r) {
-    for (size_t i = r * d->n_rho; i < (r + 1) * d->n_rho; ++i) {
-      packed[3 * i + 0] = d->prefill_ms_per_tok[i];
-      packed[3 * i + 1] = d->tbt_ms[i];
-      packed[3 * i + 2] = d->power_w[i];
-    }
+  for (size_t i = 0; i < n_tab; ++i) {
+    packed[3 * i + 0] = d->prefill_ms_per_tok[i] + 0.0;
+    packed[3 * i + 1] = d->tbt_ms[i] + 0.0;
+    packed[3 * i + 2] = d->power_w[i] + 0.0;
   }
   p->mean_power.assign(d->n_tp, 0.0);
   for (size_t i = 0; i < n_tab; ++i) p->mean_power[(i / ((size_t)d->n_f * d->n_rho)) % d->n_tp] += d->power_w[i] / (double)(n_tab / d->n_tp);
   std::vector<double> pw0(n_row);
-  for (size_t r = 0; r < n_row; ++r) pw0[r] = d->power_w[r * d->n_rho];
+  for (size_t r = 0; r < n_row; ++r) pw0[r] = packed[3 * r * d->n_rho + 2];
   std::vector<double> pfspan(2 * n_row);
   for (size_t r = 0; r < n_row; ++r) {
     const double* row = d->prefill_ms_per_tok + r * d->n_rho;

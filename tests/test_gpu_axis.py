@@ -111,3 +111,31 @@ def test_blocks_of_many_windows_and_of_few(dyn):
     g, fine = gpu_ticks(dyn, w, 12)
     assert g["status"] == 0
     assert_same(w, g, ora_ticks(w, fine, 12))
+
+
+def test_powers_of_zero_with_a_sign(dyn):
+    """-0.0 passes as a power: its energy is the least, equal to that of +0.0, for every entry point that selects."""
+    w, st = _case(GRIDS["even"], "rising")
+    P, NW, G = w["profile"], w["n_window"], w["n_class"]
+    P["power_w"][:, 1] = -0.0
+    P["power_w"][:, 2, ::2] = 0.0
+    P["max_load_tps"] *= 4.0
+    prof = dyn.dyn_profile_load(P)
+    for idle in (0.0, 0.1):
+        _, sel, _ = dyn.dyn_eval_select(prof, _dev(st["in_tok"]), _dev(st["out_tok"]), _dev(st["cell_off"]), NW, w["window_s"], dyn.Plan(w["configs"], w["slos"], w["pct"], None, idle))
+        o = oracle.evaluate(P, st, NW, w["window_s"], w["configs"], w["slos"], w["pct"], None, idle)
+        np.testing.assert_array_equal(sel["sel"].cpu().numpy(), o["sel"])
+    prof.free()
+    g, fine = gpu_ticks(dyn, w, 5)
+    assert_same(w, g, ora_ticks(w, fine, 5))
+    n_max = [3] * P["tp"].size
+    g, s = gpu_mixed(dyn, w, 4, n_max)
+    same_mixed(w, g, oracle.mixed(P, s, NW, w["window_s"], 4, n_max, w["slos"], w["pct"], None, want_types=True), 4, n_max, None)
+    tick = w["window_s"] / 5
+    st_f = oracle.ingest(w["trace"], w["edges"], NW * 5, tick)
+    lay_n, lay_tp = _layouts(w, 4)
+    for keep in (lay_tp != 2, lay_tp >= 0):
+        g, _, _ = gpu_hier(dyn, P, w["trace"], w["edges"], NW, 5, tick, 2, 0, 3, 64, lay_n[keep], lay_tp[keep], w["slos"], w["pct"])
+        o = oracle.hierarchy(P, st, st_f, NW, 5, tick, 2, 0, 3, 64, lay_n[keep], lay_tp[keep], w["slos"], w["pct"])
+        same_hierarchy(g, o, NW, G)
+        assert (o["energy_j"] == 0.0).any()
