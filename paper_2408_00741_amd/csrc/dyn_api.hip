@@ -548,12 +548,9 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   for (int q = 0; q < d->n_rho; ++q) gridpack[1 + q] = d->rho[q];
   gridpack[d->n_rho + 1] = INFINITY;
   for (int q = 0; q + 1 < d->n_rho; ++q) gridpack[d->n_rho + 3 + q] = 1.0 / (d->rho[q + 1] - d->rho[q]);
-  // Evenly spaced load points: with buckets a little narrower than the spacing every point opens its own bucket, and what precedes it
-  // by a rounding may share it.  A product by a constant is monotone, so nothing else can.
   p->rho_max = rho_max;
-  p->even_scale = (double)(d->n_rho - 1) / rho_max * (1.0 + 0x1p-40);
-  p->even = true;                            // rho[0] is 0
-  for (int q = 1; q < d->n_rho && p->even; ++q) p->even = (int)(d->rho[q] * p->even_scale) == q;
+  p->even_scale = dyn_even_scale(d->rho, d->n_rho);
+  p->even = p->even_scale > 0.0;
   const size_t even_at = gridpack.size();       // the triples follow the padded grid in its allocation
   for (int q = 0; q + 1 < d->n_rho; ++q)
     for (double v : {d->rho[q], d->rho[q + 1] - d->rho[q], gridpack[d->n_rho + 3 + q]}) gridpack.push_back(v);

@@ -42,7 +42,7 @@ struct Row { double pf, tb, pw; bool ov; };
 struct LoadAxis { const double *grid, *rinv, *thr; const uint16_t* js; };
 
 // Bracket of a clamped load fraction rc: largest grid index i <= n_rho-2 with grid[i] <= rc.
-// EVEN: one multiplication, or one less where rc is a rounding below the point.  SINGLE: no bucket holds more than one interior
+// EVEN: one multiplication, or one less where rc is just below the point.  SINGLE: no bucket holds more than one interior
 // grid point; the index is then the number of interior points in lower buckets plus one comparison with the bucket's own point.
 template <int AXIS>
 __device__ __forceinline__ int bracket(const HierArgs& a, const LoadAxis& x, double rc) {

@@ -1,0 +1,56 @@
+"""The host's rules on sizes and tables (csrc/dyn_rules.h), compiled here for the CPU."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHIM = """
+#include "dyn_rules.h"
+extern "C" double even_scale(const double* rho, int n) { return dyn_even_scale(rho, n); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "shim.cpp").write_text(SHIM)
+    lib = str(d / "librules.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-ffp-contract=off", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "paper_2408_00741_amd", "csrc"),
+                    str(d / "shim.cpp"), "-o", lib], check=True)
+    r = C.CDLL(lib)
+    r.even_scale.restype = C.c_double
+    return r
+
+
+def _even_scale(rules, rho):
+    rho = np.ascontiguousarray(rho, np.float64)
+    return rules.even_scale(rho.ctypes.data_as(C.c_void_p), rho.size)
+
+
+@pytest.mark.parametrize("n", [2, 3, 16, 33, 64, 900, 2000])
+def test_even_load_points(rules, n):
+    """Points that are even up to their roundings; a look-up starts at a point above the load only a rounding beside a point."""
+    for rho in (np.linspace(0.0, 0.95, n), np.cumsum(np.r_[0.0, np.full(n - 1, 0.95 / (n - 1))]), 3.0e7 * np.arange(n)):
+        s = _even_scale(rules, rho)
+        assert s > 0.0
+        load = np.random.default_rng(n).uniform(0.0, rho[-1], 100_000)
+        first = np.minimum((load * s).astype(np.int64), n - 2)
+        assert (rho[first] <= load).all()
+        for side in (-np.inf, np.inf):               # a rounding beside every point: the start is the bracket or the one above
+            x = np.clip(np.nextafter(rho, side), 0.0, rho[-1])
+            true = np.clip(np.searchsorted(rho, x, side="right") - 1, 0, n - 2)
+            first = np.minimum((x * s).astype(np.int64), n - 2)
+            assert ((first == true) | (first == true + 1)).all()
+
+
+@pytest.mark.parametrize("by", [0.3, 0.9, 1e-3, 1e-5, -1e-9])
+def test_displaced_load_points(rules, by):
+    """Points displaced within their buckets, for which most loads (or many) would start at a point above them, keep the other forms."""
+    rho = np.linspace(0.0, 0.95, 33)
+    one = rho.copy()
+    one[7] += by * rho[1]
+    rho[1:-1] += by * rho[1]
+    assert _even_scale(rules, rho) == 0.0 and _even_scale(rules, one) == 0.0
