@@ -367,29 +367,13 @@ __global__ __launch_bounds__(256) void or_cell_status_kernel(const uint8_t* __re
   if (v) atomicOr(status, v);
 }
 
-// Windows one block of the evaluation kernel walks.  Long runs amortise the staging of the table rows in LDS, but
-// the blocks a chip holds at a time then write that many more separate streams; measured on the one-day and the two
-// one-week workloads the kernel is fastest when about 16K (block, window) rows are in flight at a time (8, 6 and 8
-// windows; 14 to 32 cost 8 to 22 % more), and no run should leave the chip with fewer than ~8192 blocks in all.
-// How much a block stages moves that: up to 7 table values a thread leave little to amortise, more than 14 much.  Over 50 traces of 300 000
-// requests (13 000 to 313 000 tiles of cells, 0.4 to 40 million results) at 1 to 16 windows, the call is 8.8 % above its best without these two
-// lines, 6.4 % with them.  Up to 7, 4 windows in place of 5 to 8: 128 us 121, 113 100, 86 76, 79 76, 64 56, 139 127, 107 105, 58 58 and 61 66 (50 400
-// cells of 1152 candidates, beyond 250 000 tiles, 314 at 6, 338); beyond 14, 8 in place of 4: 107 80, 77 66, 71 63, 79 75, 76 74 and 79 81 (the fewest
-// tiles 91 000; 31 800 at 4 and 6 windows 66, 61).  Between, 4 in place of 6 is as often better as worse: 237 195, 341 317, 94 89, 125 123, 68 73, 241 279; the
-// one-day workload stages 12.  Blocks that stage nothing keep the first rule.  dyn_eval_tune replaces the rule's value by a measured one.
+// Windows a block of the evaluation kernel walks: the rule's, or what dyn_eval_tune measured.
 int32_t space_windows_per_block(dyn_profile* p, const SpaceArgs& a_in, int32_t n_window) {
   if (p->wpb > 0 && p->wpb_windows == n_window) return p->wpb;
-  const int64_t cell_tiles = (int64_t)n_window * p->G * p->n_tile;
-  int64_t wpb = std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, (cell_tiles + 8191) / 8192));
   SpaceArgs a = a_in;
   a.win_per_block = 8;
-  a.axis.even = false;                       // the rule's figures are of the other form's blocks; 10 windows in place of 8, which the even form's occupancy gives: 2325 us, 2023 (201 600 cells of 2048)
-  const int per_cu = dyn_space_blocks_per_cu(a);
-  if (per_cu > 0 && p->n_cu > 0) wpb = std::min<int64_t>(wpb, std::max<int64_t>(4, 16384 / ((int64_t)per_cu * p->n_cu)));
-  const int64_t staged = (int64_t)p->n_slot * 3 * p->n_rho;        // values of a block
-  if (staged > 0 && staged <= 7 * (int64_t)p->tile && cell_tiles <= 250000) wpb = std::min<int64_t>(wpb, 4);
-  else if (staged > 14 * (int64_t)p->tile && cell_tiles >= 8 * 4096) wpb = std::max<int64_t>(wpb, 8);   // at least 4096 blocks
-  p->wpb = (int32_t)wpb; p->wpb_windows = n_window; p->wpb_tuned = false;
+  p->wpb = dyn_space_windows((int64_t)n_window * p->G * p->n_tile, p->tile, (int64_t)p->n_slot * 3 * p->n_rho, dyn_space_lds(a), p->n_cu);
+  p->wpb_windows = n_window; p->wpb_tuned = false;
   return p->wpb;
 }
 

@@ -35,7 +35,6 @@ struct CellRec {  // what the space kernel needs from a cell (32 bytes)
 #define DYN_MAX_CONFIGS 65536     // capacity of a profile handle's configuration table
 #define DYN_MAX_TILE 256          // configurations per tile of the space kernel
 #define DYN_LDS_BUDGET (64 * 1024)
-#define DYN_MAX_WIN_PER_BLOCK 32  // windows one block of the space kernel walks
 
 // ---- host-side profile handle -----------------------------------------------------------
 // Besides the tables it owns the device copies of the last candidate list and objective
@@ -187,7 +186,7 @@ struct SpaceArgs {
   const double* pw0; double idle_w; SelPart* part; int32_t n_wslot;
 };
 hipError_t dyn_launch_space(const SpaceArgs& a, hipStream_t s);
-int dyn_space_blocks_per_cu(const SpaceArgs& a);   // resident blocks of the evaluation kernel per compute unit (0: unknown)
+size_t dyn_space_lds(const SpaceArgs& a);   // LDS of a block
 size_t dyn_space_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t win_per_block);   // LDS bytes besides the table rows
 
 struct FinishArgs {   // reduces the partial records of every cell, then the window totals

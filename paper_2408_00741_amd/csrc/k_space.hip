@@ -218,24 +218,7 @@ size_t dyn_space_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t win_per_block
          ((size_t)n_bucket + 1) * sizeof(uint16_t);
 }
 
-// Blocks of the evaluation kernel that one compute unit holds at a time for this shape (0 if the query fails).
-int dyn_space_blocks_per_cu(const SpaceArgs& a) {
-  const size_t lds = space_lds(a);
-  const int form = space_form(a);
-  int n = 0;
-  hipError_t e;
-  if (a.n_slot > 0) {
-    if (form == kEven) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kEven>, a.tile, lds);
-    else if (form == kOneStep) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kOneStep>, a.tile, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<true, true, kSearch>, a.tile, lds);
-  } else {
-    if (form == kEven) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kEven>, a.tile, lds);
-    else if (form == kOneStep) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kOneStep>, a.tile, lds);
-    else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, space_kernel<false, true, kSearch>, a.tile, lds);
-  }
-  if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
-  return n;
-}
+size_t dyn_space_lds(const SpaceArgs& a) { return space_lds(a); }
 
 hipError_t dyn_launch_space(const SpaceArgs& a, hipStream_t s) {
   const int n_chunk = (a.n_window + a.win_per_block - 1) / a.win_per_block;

@@ -10,6 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "dyn_rules.h"
 extern "C" double even_scale(const double* rho, int n) { return dyn_even_scale(rho, n); }
+extern "C" int space_windows(long long cell_tiles, int tile, long long staged, long long lds, int n_cu) { return dyn_space_windows(cell_tiles, tile, staged, (size_t)lds, n_cu); }
 """
 
 
@@ -54,3 +55,13 @@ def test_displaced_load_points(rules, by):
     one[7] += by * rho[1]
     rho[1:-1] += by * rho[1]
     assert _even_scale(rules, rho) == 0.0 and _even_scale(rules, one) == 0.0
+
+
+@pytest.mark.parametrize("tile,rows,n_rho,want", [(256, 8, 64, 8), (192, 12, 64, 8), (128, 8, 64, 5), (64, 4, 64, 4), (256, 8, 72, 8), (192, 12, 200, 32)])
+def test_windows_a_block_of_a_large_space(rules, tile, rows, n_rho, want):
+    """About 16 384 rows in flight of the blocks that LDS and threads leave room for, on 256 compute units: the registers of the form that
+    runs do not come into it (by them 256-wide tiles got 9 or 10 windows)."""
+    lds = 8 * (3 * rows * n_rho + 3 * (n_rho - 1)) + 8 * 24
+    got = rules.space_windows(C.c_longlong(1_600_000), tile, C.c_longlong(3 * rows * n_rho), C.c_longlong(lds), 256)
+    room = max(1, min(160 * 1024 // ((lds + 511) // 512 * 512), 2048 // tile))
+    assert got == want == max(min(32, max(4, 16384 // (256 * room))), 8 if 3 * rows * n_rho > 14 * tile else 1)
