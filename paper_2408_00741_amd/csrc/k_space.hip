@@ -16,8 +16,6 @@
 //
 // With the fused selection, each wave also reduces the least cost among its feasible
 // configurations (Section IV-B "Scale-up/down") and one lane writes a partial record.
-#include <algorithm>
-
 #include "dyn_device.h"
 
 namespace {
@@ -192,7 +190,6 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   }
 }
 
-constexpr double kManyBytes = 4e9;
 size_t rows_lds(const SpaceArgs& a) { return (size_t)a.n_slot * 3 * a.n_rho * sizeof(double); }
 size_t even_lds(const SpaceArgs& a) {
   return rows_lds(a) + dyn_axis_lds(a.axis, DYN_AXIS_EVEN) + (size_t)a.win_per_block * sizeof(CellRec);
@@ -224,14 +221,7 @@ hipError_t dyn_launch_space(const SpaceArgs& a, hipStream_t s) {
   const int n_chunk = (a.n_window + a.win_per_block - 1) / a.win_per_block;
   const size_t blocks = (size_t)n_chunk * a.G * a.n_tile;
   DynTimed timed(DYN_K_SPACE, s);
-  size_t lds = space_lds(a);
-  // Spaces of many gigabytes: no more than 20 waves on a compute unit, by LDS that is not used.  With the 24 that the registers allow the
-  // stores fall into one of two states from run to run: 201 600 cells of 2048 candidates (11 GB) 2031, 2058, 2255, 2276, 2317 us; with 20 waves
-  // 2028, 2029; with 16, 2123, 2128.  A space of 0.5 GB loses by it (130 us, 142); between 0.5 and 11 GB it was not measured.
-  if (25.0 * (double)a.n_window * a.G * a.K >= kManyBytes) {
-    const size_t resident = std::max(1, 20 * DYN_WAVE / a.tile);
-    lds = std::max(lds, (size_t)(160 * 1024) / (resident + 1) + 512);
-  }
+  const size_t lds = space_lds(a);
   const dim3 grid((unsigned)blocks), block(a.tile);
   if (a.n_slot > 0) {
     if (a.part) launch_form<true, true>(a, grid, block, lds, s);
