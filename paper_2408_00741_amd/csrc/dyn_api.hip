@@ -1256,7 +1256,7 @@ int dyn_hierarchy(dyn_profile* p, const dyn_trace_view* tc, const dyn_trace_view
     return DYN_E_DEVICE;
   HierArgs a;
   a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p);
-  a.G = p->G; a.n_tp = p->n_tp; a.n_f = p->n_f; a.n_rho = p->n_rho; a.tp = p->d_tp;
+  a.G = p->G; a.n_tp = p->n_tp; a.n_f = p->n_f; a.n_rho = p->n_rho; a.n_cu = p->n_cu; a.tp = p->d_tp;
   a.slo_ttft = p->d_slo_ttft; a.slo_tbt = p->d_slo_tbt;
   a.rec_c = (const CellRec*)(base + w.coarse.rec); a.rec_f = (const CellRec*)(fb + w.fine.rec);
   a.cstat_c = (const uint8_t*)(base + w.coarse.cstat); a.cstat_f = (const uint8_t*)(fb + w.fine.cstat); a.status = &((WsHeader*)(base + w.coarse.header))->status;

@@ -149,6 +149,7 @@ struct Lookup {          // per-thread constants of the table look-up
   const double* grid;            // DYN_AXIS_EVEN: [n_rho - 1][3] load point, spacing, its reciprocal; else the padded load grid
   const double* rinv;            // reciprocal spacings
   const uint16_t* js;            // bucket index
+  const int32_t* js_global;      // DYN_AXIS_GLOBAL: the same
   const double* thr;             // DYN_AXIS_SINGLE: the grid point inside each bucket
   int n_rho;
 };
@@ -176,11 +177,12 @@ __device__ __forceinline__ Axis place_axis(double* at, int n_rho, int n_bucket) 
   x.grid = at;
   x.rinv = at + (n_rho + 2);
   x.thr = x.rinv + (n_rho + 1);
-  x.end = AXIS == DYN_AXIS_EVEN ? at + 3 * (n_rho - 1) : x.thr + (AXIS == DYN_AXIS_SINGLE ? n_bucket + 1 : 0);
+  x.end = AXIS & DYN_AXIS_GLOBAL ? at : AXIS == DYN_AXIS_EVEN ? at + 3 * (n_rho - 1) : x.thr + (AXIS == DYN_AXIS_SINGLE ? n_bucket + 1 : 0);
   return x;
 }
 template <int AXIS>
 __device__ __forceinline__ void stage_axis(const AxisArgs& a, const Axis& x, uint16_t* js) {
+  if (AXIS & DYN_AXIS_GLOBAL) return;
   if (AXIS == DYN_AXIS_EVEN) {
     for (int i = threadIdx.x; i < 3 * (a.n_rho - 1); i += blockDim.x) x.grid[i] = a.even_grid[i];
     return;
@@ -193,9 +195,18 @@ __device__ __forceinline__ void stage_axis(const AxisArgs& a, const Axis& x, uin
 }
 template <int AXIS>
 __device__ __forceinline__ void use_axis(const AxisArgs& a, const Axis& x, const uint16_t* js, Lookup* L) {
+  constexpr int FORM = AXIS & ~DYN_AXIS_GLOBAL;
   L->rho_max = a.rho_max;
-  L->scale = AXIS == DYN_AXIS_EVEN ? a.even_scale : a.bucket_scale;
-  L->grid = x.grid; L->rinv = x.rinv; L->thr = x.thr; L->js = js; L->n_rho = a.n_rho;
+  L->scale = FORM == DYN_AXIS_EVEN ? a.even_scale : a.bucket_scale;
+  L->n_rho = a.n_rho;
+  if (AXIS & DYN_AXIS_GLOBAL) {
+    L->grid = FORM == DYN_AXIS_EVEN ? a.even_grid : a.gridpack;
+    L->rinv = a.gridpack + a.n_rho + 2;
+    L->thr = a.thr;
+    L->js_global = FORM == DYN_AXIS_SINGLE ? a.tstart : a.jstart;
+  } else {
+    L->grid = x.grid; L->rinv = x.rinv; L->thr = x.thr; L->js = js;
+  }
 }
 
 // The lesser of v and the wave-uniform s.
@@ -212,11 +223,9 @@ __device__ __forceinline__ void read_now(double& a, double& b, double& c, double
 // The bracket of a load by the bucket index.
 template <int AXIS>
 __device__ __forceinline__ int find_index(const Lookup& L, double rc) {
-  if (AXIS == DYN_AXIS_SINGLE) {
-    const int b = (int)(fmax(rc, 0.0) * L.scale);
-    return (int)L.js[b] + (rc >= L.thr[b] ? 1 : 0);
-  }
-  int j = L.js[(int)(fmax(rc, 0.0) * L.scale)];
+  const int b = (int)(fmax(rc, 0.0) * L.scale);
+  int j = AXIS & DYN_AXIS_GLOBAL ? L.js_global[b] : (int)L.js[b];
+  if ((AXIS & ~DYN_AXIS_GLOBAL) == DYN_AXIS_SINGLE) return j + (rc >= L.thr[b] ? 1 : 0);
   while (j > 0 && L.grid[j + 1] > rc) --j;
   while (j < L.n_rho - 2 && L.grid[j + 2] <= rc) ++j;
   return j;
@@ -263,9 +272,10 @@ struct Looked {
 __device__ __forceinline__ const double* at_point(const double* base, int j) { return (const double*)((const char*)base + __umul24((uint32_t)j, 24u)); }
 template <int AXIS, bool TWO, int COLUMNS, int N>
 __device__ __forceinline__ void table_lookups(const Lookup& L, const double (&load)[N], Looked (&r)[N]) {
+  constexpr int FORM = AXIS & ~DYN_AXIS_GLOBAL;
   double rc[N], r0[N], d[N], ri[N], a[N][6], b[N][6];
   auto read = [&](int i, int j) {
-    if (AXIS == DYN_AXIS_EVEN) {
+    if (FORM == DYN_AXIS_EVEN) {
       const double* g = at_point(L.grid, j);
       r0[i] = g[0]; d[i] = g[1]; ri[i] = g[2];
     } else {
@@ -286,7 +296,7 @@ __device__ __forceinline__ void table_lookups(const Lookup& L, const double (&lo
     r[i].ov = rho > L.rho_max;
     rc[i] = min_uniform(rho, L.rho_max);
   }
-  if (AXIS == DYN_AXIS_EVEN) {
+  if (FORM == DYN_AXIS_EVEN) {
     int j[N];
     bool low = false;
 #pragma unroll

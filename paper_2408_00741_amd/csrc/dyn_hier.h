@@ -7,7 +7,7 @@
 struct HierArgs {
   // profile
   const double* tab; const double* ml; AxisArgs axis;
-  int32_t G, n_tp, n_f, n_rho;
+  int32_t G, n_tp, n_f, n_rho, n_cu;
   const int32_t* tp;            // DEVICE [n_tp] GPUs per instance
   const double* slo_ttft; const double* slo_tbt;
   // trace aggregates

@@ -158,8 +158,9 @@ hipError_t dyn_launch_cell_aggregate(const int32_t* in_tok, const int32_t* out_t
 size_t dyn_cell_many_bytes(int64_t cells);
 #define DYN_CELL_MANY_MAX ((8u << 20) + 16384u)   // the most it can be
 
-// How a kernel finds the bracket of a load: the load axis and which of its forms hold.
-enum { DYN_AXIS_SEARCH = 0, DYN_AXIS_SINGLE = 1, DYN_AXIS_EVEN = 2 };
+// How a kernel finds the bracket of a load: the load axis and which of its forms hold.  With DYN_AXIS_GLOBAL it is read from global memory,
+// else from a copy in the block's LDS.
+enum { DYN_AXIS_SEARCH = 0, DYN_AXIS_SINGLE = 1, DYN_AXIS_EVEN = 2, DYN_AXIS_GLOBAL = 4 };
 struct AxisArgs {
   const double* gridpack; const double* even_grid;
   const int32_t* jstart; const int32_t* tstart; const double* thr;
@@ -169,6 +170,7 @@ struct AxisArgs {
 inline int dyn_axis(const AxisArgs& a) { return a.even ? DYN_AXIS_EVEN : a.single_point ? DYN_AXIS_SINGLE : DYN_AXIS_SEARCH; }
 // LDS of a block's copy of the axis: doubles, and the bucket index at the end of the block's LDS
 inline size_t dyn_axis_lds(const AxisArgs& a, int axis) {
+  if (axis & DYN_AXIS_GLOBAL) return 0;
   if (axis == DYN_AXIS_EVEN) return (size_t)3 * (a.n_rho - 1) * sizeof(double);
   return ((size_t)2 * a.n_rho + 3 + (axis == DYN_AXIS_SINGLE ? a.n_bucket + 1 : 0)) * sizeof(double) + ((size_t)a.n_bucket + 1) * sizeof(uint16_t) + 8;
 }

@@ -47,4 +47,12 @@ inline int32_t dyn_space_windows(int64_t cell_tiles, int32_t tile, int64_t stage
   return (int32_t)w;
 }
 
+// Whether the hierarchy's frequency kernel keeps a block's copy of the load axis (`axis_lds` of the block's `lds` bytes) in LDS or reads it
+// from global memory.  A copy of up to 40 KB, which leaves room for three blocks, is quicker (64 even points: 95 us a call of 1440 blocks, 103);
+// a longer one only while all blocks are resident at once: 1000 uneven points (46 KB) 35 us and 38 with 60 blocks, 52 and 60 with 360, 145 and 139 with
+// 1440; 4000 (72 KB) 179 and 149 with 1440.
+inline bool dyn_freq_axis_staged(size_t axis_lds, size_t lds, int64_t blocks, int32_t n_cu) {
+  return axis_lds <= 40 * 1024 || (lds <= 160 * 1024 && blocks <= (int64_t)(160 * 1024 / lds) * n_cu);
+}
+
 #endif  // DYN_RULES_H_

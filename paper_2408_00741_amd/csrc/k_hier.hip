@@ -32,49 +32,33 @@ constexpr int kFreqTabled = 128;        // frequencies up to which the capacitie
 constexpr size_t kFreqLds = 16 * 1024;  // of the results and capacities: blocks beside another stream's kernel find room
 constexpr int kFreqChunk = 3;           // look-ups a thread of the frequency kernel has in flight: four need the registers of a third of the waves (35 us, 27)
 constexpr int kSpillLds = 48 * 1024;    // an epoch's window loads are staged in LDS when they fit in this
-constexpr size_t kAxisLds = 32 * 1024;  // evenly spaced points are staged in triples up to this
 constexpr int kSpillRun = 8;            // classes whose tick loads a thread fetches ahead of the chain
 
 struct Row { double pf, tb, pw; bool ov; };
 
-// The load axis (grid points, reciprocal spacings, bucket index) is the same for every class and small: a copy in LDS takes half of
-// a look-up's gathers off the vector memory path.
-struct LoadAxis { const double *grid, *rinv, *thr; const uint16_t* js; };
-
 // Bracket of a clamped load fraction rc: largest grid index i <= n_rho-2 with grid[i] <= rc.
-// EVEN: one multiplication, or one less where rc is just below the point.  SINGLE: no bucket holds more than one interior
-// grid point; the index is then the number of interior points in lower buckets plus one comparison with the bucket's own point.
+// EVEN: one multiplication, or one less where rc is just below the point.
 template <int AXIS>
-__device__ __forceinline__ int bracket(const HierArgs& a, const LoadAxis& x, double rc) {
-  if (AXIS == DYN_AXIS_EVEN) {
-    int j = (int)min((uint32_t)(int)(rc * a.axis.even_scale), (uint32_t)(a.n_rho - 2));
-    while (j > 0 && x.grid[3 * j] > rc) --j;
-    return j;
-  }
-  const double* grid = x.grid + 1;
-  const int b = min((int)(fmax(rc, 0.0) * a.axis.bucket_scale), a.axis.n_bucket);
-  const int j0 = (int)x.js[b];
-  if (AXIS == DYN_AXIS_SINGLE) return j0 + (rc >= x.thr[b] ? 1 : 0);
-  int j = j0;
-  while (j > 0 && grid[j] > rc) --j;
-  while (j < a.n_rho - 2 && grid[j + 1] <= rc) ++j;
+__device__ __forceinline__ int bracket(const Lookup& L, double rc) {
+  if ((AXIS & ~DYN_AXIS_GLOBAL) != DYN_AXIS_EVEN) return find_index<AXIS>(L, rc);
+  int j = (int)min((uint32_t)(int)(rc * L.scale), (uint32_t)(L.n_rho - 2));
+  while (j > 0 && L.grid[3 * j] > rc) --j;
   return j;
 }
 
 // Linear interpolation in table row `row` (class, TP, frequency) between grid points j and j+1.
 template <int AXIS>
-__device__ __forceinline__ void interpolate(const HierArgs& a, const LoadAxis& x, size_t row, int j, double rc, Row* r) {
+__device__ __forceinline__ void interpolate(const double* tab, const Lookup& L, size_t row, int j, double rc, Row* r) {
   double t;
-  if (AXIS == DYN_AXIS_EVEN) {
-    const double* g = x.grid + 3 * j;
+  if ((AXIS & ~DYN_AXIS_GLOBAL) == DYN_AXIS_EVEN) {
+    const double* g = L.grid + 3 * j;
     t = div_by(rc - g[0], g[1], g[2]);
   } else {
-    const double* grid = x.grid + 1;
-    const double g0 = grid[j], g1 = grid[j + 1];
-    t = div_by(rc - g0, g1 - g0, x.rinv[j + 1]);             // RN(1 / spacing)
+    const double g0 = L.grid[j + 1], g1 = L.grid[j + 2];
+    t = div_by(rc - g0, g1 - g0, L.rinv[j + 1]);             // RN(1 / spacing)
   }
   const double omt = 1.0 - t;
-  const double* v = a.tab + (row * a.n_rho + j) * 3;
+  const double* v = tab + (row * L.n_rho + j) * 3;
   r->pf = omt * v[0] + t * v[3];
   r->tb = omt * v[1] + t * v[4];
   r->pw = omt * v[2] + t * v[5];
@@ -118,16 +102,16 @@ __device__ __forceinline__ int32_t epoch_nodes(const HierArgs& a, int e, int g, 
 // layout only (capacity and its reciprocal, the rows at the reference frequency, which a block keeps in LDS) is formed once, a wave's
 // records and statuses are read together, and the nodes are counted where an epoch begins.  A wave a cell, which did all of that
 // for one look-up per lane, took 28 us for 36 000 cells of 48 layouts, bound by its chain of loads.
-// LDS: [load axis] [rows at f_ref n_tp*3*n_rho (ROWS)] [bucket index (16-bit)]
-template <bool ROWS, int AXIS>
+// The load axis is read from global memory, at most five words a look-up: copies in LDS are no faster where they are small (36 000 cells, 64 even points
+// 95.1 us, 95.2) and cost waves where they are not (9000 cells, 64 uneven points, 38 KB: 49 us, 61; 4000 points 64, more than 300).
+// LDS: [rows at f_ref n_tp*3*n_rho (ROWS)]
+template <bool ROWS, int FORM>
 __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierArgs a, int per_wave) {
-  extern __shared__ double s_shard[];
+  constexpr int AXIS = FORM | DYN_AXIS_GLOBAL;
+  extern __shared__ double s_rows[];
   const int lane = threadIdx.x & (DYN_WAVE - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DYN_WAVE);
   const int g = blockIdx.x % a.G;
   const int w0 = ((int)(blockIdx.x / a.G) * kShardWaves + wave) * per_wave, w1 = min(w0 + per_wave, a.n_window);
-  const Axis axis = place_axis<AXIS>(s_shard, a.n_rho, a.axis.n_bucket);
-  double* s_rows = axis.end;
-  uint16_t* s_js = (uint16_t*)(s_rows + (ROWS ? (size_t)a.n_tp * 3 * a.n_rho : 0));
   const size_t row_ref = ((size_t)g * a.n_tp) * a.n_f + a.f_ref;   // of the first TP degree; the next is n_f rows on
 
   CellRec mine;                                              // lane i: the wave's window i (per_wave <= 64)
@@ -141,7 +125,6 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
   if (ROWS)
     for (int t = wave; t < a.n_tp; t += kShardWaves)
       for (int i = lane; i < 3 * a.n_rho; i += DYN_WAVE) s_rows[t * 3 * a.n_rho + i] = a.tab[(row_ref + (size_t)t * a.n_f) * 3 * a.n_rho + i];
-  stage_axis<AXIS>(a.axis, axis, s_js);
 
   struct Layout { int64_t gpus; double nd; };
   Lookup L;
@@ -155,7 +138,7 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
     L.lo = ROWS ? s_rows + ti * 3 * a.n_rho : a.tab + (row_ref + (size_t)ti * a.n_f) * 3 * a.n_rho;
     L.hi = L.lo;
   };
-  use_axis<AXIS>(a.axis, axis, s_js, &L);
+  use_axis<AXIS>(a.axis, Axis(), nullptr, &L);
   L.u = 0.0; L.omu = 1.0;
   take(min(lane, a.n_layout - 1));
   const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
@@ -235,8 +218,8 @@ __global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6,
     }
     __syncthreads();
   }
-  LoadAxis x;
-  x.grid = axis.grid; x.rinv = axis.rinv; x.thr = axis.thr; x.js = s_js;
+  Lookup x;
+  use_axis<AXIS>(a.axis, axis, s_js, &x);
   const double rho_max = a.axis.rho_max;
   double sum = 0.0;                                          // thread i: of class g0 + i (run <= kFreqThreads)
   int32_t viol = 0;
@@ -271,10 +254,10 @@ __global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6,
           rc[c] = ov[c] ? rho_max : rho;
         }
 #pragma unroll
-        for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(a, x, rc[c]);   // level 2: the load axis
+        for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(x, rc[c]);   // level 2: the load axis
 #pragma unroll
         for (int c = 0; c < kFreqChunk; ++c)                 // level 3: table values
-          interpolate<AXIS>(a, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
+          interpolate<AXIS>(a.tab, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
 #pragma unroll
         for (int c = 0; c < kFreqChunk; ++c) {               // ascending frequency: the lowest wins equal powers
           const int fi = f0 + c;
@@ -441,11 +424,6 @@ __global__ __launch_bounds__(DYN_WAVE) void hier_spill_tick_kernel(HierArgs a) {
   }
 }
 
-// Evenly spaced points beyond what LDS holds in triples keep the other forms (at most 4097 buckets: 42 KB and the points).
-int hier_axis(const HierArgs& a) {
-  const int axis = dyn_axis(a.axis);
-  return axis != DYN_AXIS_EVEN || dyn_axis_lds(a.axis, axis) <= kAxisLds ? axis : a.axis.single_point ? DYN_AXIS_SINGLE : DYN_AXIS_SEARCH;
-}
 template <typename F>
 void with_axis(int axis, F&& f) {
   if (axis == DYN_AXIS_EVEN) f(std::integral_constant<int, DYN_AXIS_EVEN>());
@@ -468,42 +446,41 @@ hipError_t dyn_launch_hier_spill(const HierArgs& a, hipStream_t s) {
 }
 
 hipError_t dyn_launch_hier_shard(const HierArgs& a, hipStream_t s) {
-  // Windows a wave: as many as leave the device its waves (8192), and no more than 8; the blocks' set-up is by then a small part.
+  // Windows a wave: as many as leave the device about 6000 waves, and no more than 8; the blocks' set-up is by then a small part.
   const int64_t cells = (int64_t)a.n_window * a.G;
   const int per_wave = (int)std::max<int64_t>(1, std::min<int64_t>(8, cells / 6144));
   const int64_t runs = (a.n_window + (int64_t)per_wave * kShardWaves - 1) / ((int64_t)per_wave * kShardWaves);
-  const int axis = hier_axis(a);
   const size_t rows = (size_t)a.n_tp * 3 * a.n_rho * sizeof(double);
-  const bool in_lds = rows <= kRowsLds && dyn_axis_lds(a.axis, axis) + rows <= DYN_LDS_BUDGET;
-  const size_t lds = dyn_axis_lds(a.axis, axis) + (in_lds ? rows : 0);
+  // a load axis beyond a compute unit's LDS is refused
+  if (dyn_axis_lds(a.axis, a.axis.single_point ? DYN_AXIS_SINGLE : DYN_AXIS_SEARCH) > 160 * 1024) return hipErrorInvalidValue;
   DynTimed timed(DYN_K_HIER, s);
-  with_axis(axis, [&](auto x) {
-    if (in_lds) hipLaunchKernelGGL((hier_shard_kernel<true, decltype(x)::value>), dim3((unsigned)(runs * a.G)), dim3(kShardWaves * DYN_WAVE), lds, s, a, per_wave);
-    else hipLaunchKernelGGL((hier_shard_kernel<false, decltype(x)::value>), dim3((unsigned)(runs * a.G)), dim3(kShardWaves * DYN_WAVE), lds, s, a, per_wave);
+  with_axis(dyn_axis(a.axis), [&](auto x) {
+    const dim3 grid((unsigned)(runs * a.G)), block(kShardWaves * DYN_WAVE);
+    if (rows <= kRowsLds) hipLaunchKernelGGL((hier_shard_kernel<true, decltype(x)::value>), grid, block, rows, s, a, per_wave);
+    else hipLaunchKernelGGL((hier_shard_kernel<false, decltype(x)::value>), grid, block, 0, s, a, per_wave);
   });
   return hipGetLastError();
 }
 
 hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s) {
-  // A long load axis keeps its place in LDS: then fewer classes, no table of capacities, in the end tick by tick.
-  int axis = hier_axis(a);
-  if (dyn_axis_lds(a.axis, axis) + kFreqLds > DYN_LDS_BUDGET) axis = DYN_AXIS_SEARCH;
-  const size_t axis_lds = dyn_axis_lds(a.axis, axis), room = axis_lds < DYN_LDS_BUDGET ? std::min(kFreqLds, DYN_LDS_BUDGET - axis_lds) : 0;
-  int chunk = std::min(a.n_tick, kTickChunk);
-  bool tabled = a.n_f <= kFreqTabled;
-  auto of_class = [&] { return (size_t)chunk * (sizeof(double) + sizeof(int32_t)) + (tabled ? (size_t)a.n_f * 2 * sizeof(double) : 0) + sizeof(double) + sizeof(int32_t); };
-  if (of_class() > room) tabled = false;
-  if (of_class() > room) chunk = 1;
-  const size_t per_class = of_class();
-  const int run = (int)std::max<size_t>(1, std::min<size_t>(std::min(a.G, kFreqThreads), room / per_class));
+  const int axis = dyn_axis(a.axis);
+  const int chunk = std::min(a.n_tick, kTickChunk);
+  const bool tabled = a.n_f <= kFreqTabled;
+  const size_t per_class = (size_t)chunk * (sizeof(double) + sizeof(int32_t)) + (tabled ? (size_t)a.n_f * 2 * sizeof(double) : 0) + sizeof(double) + sizeof(int32_t);
+  const int run = (int)std::max<size_t>(1, std::min<size_t>(std::min(a.G, kFreqThreads), kFreqLds / per_class));
   const int n_run = (a.G + run - 1) / run;
-  const size_t lds = axis_lds + (size_t)run * per_class;
+  const size_t axis_lds = dyn_axis_lds(a.axis, axis);
+  size_t lds = axis_lds + (size_t)run * per_class;
+  const bool staged = tabled && dyn_freq_axis_staged(axis_lds, lds, (int64_t)a.n_window * n_run, a.n_cu);
+  if (!staged) lds -= axis_lds;
   {
     DynTimed timed(DYN_K_HIER, s);
     const dim3 grid((unsigned)((int64_t)a.n_window * n_run));
     with_axis(axis, [&](auto x) {
-      if (tabled) hipLaunchKernelGGL((hier_freq_kernel<true, decltype(x)::value>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
-      else hipLaunchKernelGGL((hier_freq_kernel<false, decltype(x)::value>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+      constexpr int FORM = decltype(x)::value;
+      if (staged) hipLaunchKernelGGL((hier_freq_kernel<true, FORM>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+      else if (tabled) hipLaunchKernelGGL((hier_freq_kernel<true, FORM | DYN_AXIS_GLOBAL>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+      else hipLaunchKernelGGL((hier_freq_kernel<false, FORM | DYN_AXIS_GLOBAL>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
     });
   }
   if (n_run > 1) {

@@ -233,6 +233,51 @@ def test_random_profiles_and_layouts(dyn, seed, n_tick, n_f, R, NW, epoch):
     assert o["nodes"].min() >= 1
 
 
+def _on_grid(prof, rg, seed):
+    """The profile's capacities with random tables over the load points `rg`."""
+    rng = np.random.default_rng(seed)
+    shape = prof["max_load_tps"].shape + (rg.size,)
+    return dict(prof, rho=rg, prefill_ms_per_tok=rng.uniform(0.02, 0.1, shape), tbt_ms=np.sort(rng.uniform(10, 150, shape), axis=-1),
+                power_w=np.sort(rng.uniform(100, 3000, shape), axis=-1))
+
+
+@pytest.mark.parametrize("kind,n_rho,NW", [("even", 1500, 5), ("even", 1800, 5), ("even", 1800, 800), ("jitter", 1000, 5), ("jitter", 1000, 800), ("uneven", 300, 9),
+                                           ("uneven", 3000, 5), ("uneven", 3000, 700), ("even", 4500, 3), ("uneven", 9700, 3)])
+def test_long_load_axes(dyn, kind, n_rho, NW):
+    """Axes that a block keeps in LDS, and that it reads from global memory because they are long or the blocks many, in every form."""
+    prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(n_rho, 2, 3, 400 + 8 * NW, NW)
+    rg = np.linspace(0.0, 0.95, n_rho)
+    if kind == "jitter":
+        rg = rg * (1.0 + 1e-9 * np.sin(np.arange(n_rho)))
+    if kind == "uneven":
+        rg = np.r_[0.0, np.geomspace(0.01, 0.95, n_rho - 1)]
+    prof = _on_grid(prof, rg, n_rho)
+    slo = {k: v * 2.0 for k, v in slo.items()}          # so that every axis has windows with a layout
+    g, coarse, fine = gpu_hier(dyn, prof, tr, edges, NW, T, tick, 3, 2, 2, 8, lay_n, lay_tp, slo)
+    o = oracle.hierarchy(prof, coarse, fine, NW, T, tick, 3, 2, 2, 8, lay_n, lay_tp, slo)
+    assert_same(g, o, NW, 2)
+    assert (o["layout_sel"] >= 0).any()
+
+
+def test_load_axes_beyond_what_is_taken(dyn):
+    """9730 points, with their bucket index, are the longest axis that fits a compute unit's LDS; more are refused."""
+    prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(0, 2, 3, 300, 3)
+    prof = _on_grid(prof, np.linspace(0.0, 0.95, 9800), 1)
+    with pytest.raises(dyn.DynError):
+        gpu_hier(dyn, prof, tr, edges, NW, T, tick, 3, 2, 2, 8, lay_n, lay_tp, slo)
+
+
+@pytest.mark.parametrize("n_tick,n_f", [(64, 3), (65, 3), (130, 2), (3, 128), (3, 129), (70, 150)])
+def test_many_ticks_and_many_frequencies(dyn, n_tick, n_f):
+    """More ticks than a block keeps at a time, whose sums and violations run on, and more frequencies than it tables."""
+    prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(11, n_tick, n_f, 40 * n_tick, 4)
+    prof = dict(prof, max_load_tps=prof["max_load_tps"] * 0.3)
+    g, coarse, fine = gpu_hier(dyn, prof, tr, edges, NW, T, tick, 2, 2, n_f - 1, 8, lay_n, lay_tp, slo)
+    o = oracle.hierarchy(prof, coarse, fine, NW, T, tick, 2, 2, n_f - 1, 8, lay_n, lay_tp, slo)
+    assert_same(g, o, NW, 2)
+    assert (o["layout_sel"] >= 0).any() and o["violations"].sum() > 0
+
+
 def test_more_than_64_layouts_and_ties(dyn):
     """Layout list longer than a wave with repeated entries: the lowest index of equal energies is chosen."""
     prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(5, 4, 3, 4000, 6)

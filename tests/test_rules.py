@@ -11,6 +11,7 @@ SHIM = """
 #include "dyn_rules.h"
 extern "C" double even_scale(const double* rho, int n) { return dyn_even_scale(rho, n); }
 extern "C" int space_windows(long long cell_tiles, int tile, long long staged, long long lds, int n_cu) { return dyn_space_windows(cell_tiles, tile, staged, (size_t)lds, n_cu); }
+extern "C" int freq_axis_staged(long long axis_lds, long long lds, long long blocks, int n_cu) { return dyn_freq_axis_staged((size_t)axis_lds, (size_t)lds, blocks, n_cu); }
 """
 
 
@@ -65,3 +66,9 @@ def test_windows_a_block_of_a_large_space(rules, tile, rows, n_rho, want):
     got = rules.space_windows(C.c_longlong(1_600_000), tile, C.c_longlong(3 * rows * n_rho), C.c_longlong(lds), 256)
     room = max(1, min(160 * 1024 // ((lds + 511) // 512 * 512), 2048 // tile))
     assert got == want == max(min(32, max(4, 16384 // (256 * room))), 8 if 3 * rows * n_rho > 14 * tile else 1)
+
+
+@pytest.mark.parametrize("axis,lds,blocks,staged", [(1512, 10_000, 10_000, 1), (40 * 1024, 56 * 1024, 10_000, 1), (46 * 1024, 54 * 1024, 512, 1), (46 * 1024, 54 * 1024, 513, 0),
+                                                    (72 * 1024, 80 * 1024, 512, 1), (72 * 1024, 80 * 1024, 513, 0), (152 * 1024, 168 * 1024, 1, 0)])
+def test_where_the_frequency_kernel_keeps_a_long_axis(rules, axis, lds, blocks, staged):
+    assert rules.freq_axis_staged(C.c_longlong(axis), C.c_longlong(lds), C.c_longlong(blocks), 256) == staged
