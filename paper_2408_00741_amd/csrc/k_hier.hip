@@ -26,10 +26,6 @@ namespace {
 
 constexpr int kShardWaves = 4;          // of a block of the shard kernel
 constexpr size_t kRowsLds = 16 * 1024;  // rows at the reference frequency are staged in LDS up to this
-constexpr int kFreqThreads = 256;
-constexpr int kTickChunk = 64;          // ticks of a class in LDS at a time
-constexpr int kFreqTabled = 128;        // frequencies up to which the capacities are tabled
-constexpr size_t kFreqLds = 16 * 1024;  // of the results and capacities: blocks beside another stream's kernel find room
 constexpr int kFreqChunk = 3;           // look-ups a thread of the frequency kernel has in flight: four need the registers of a third of the waves (35 us, 27)
 constexpr int kSpillLds = 48 * 1024;    // an epoch's window loads are staged in LDS when they fit in this
 constexpr int kSpillRun = 8;            // classes whose tick loads a thread fetches ahead of the chain
@@ -183,36 +179,44 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
   }
 }
 
-// Block = (window, run of classes); a thread takes (class, tick) pairs, ticks fastest, so that the ticks of a cell, which share the layout and
-// mostly the bracket, are neighbouring lanes and read the same few lines of the tables.  The cells' capacities per frequency and their
-// reciprocals come from a table in LDS (TABLED; a division and a gather less per look-up).  Frequencies and energies meet in LDS: they
-// leave it with the classes side by side, and a thread per class adds its ticks in time order, in chunks of kTickChunk.  With one run of
-// classes the window's totals are added here too, in class order.  With a block per class and 256 ticks, results written a class apart
+// Block = (run of windows, run of classes); its cells are its windows' classes, one window after the other.  A thread takes (cell, tick) pairs, ticks fastest, so that
+// the ticks of a cell, which share the layout and mostly the bracket, are neighbouring lanes and read the same few lines of the tables.  The cells' capacities per
+// frequency and their reciprocals come from a table in LDS (TABLED; a division and a gather less per look-up).  Frequencies and energies meet in LDS: they
+// leave it with the classes side by side, and a thread per cell adds its ticks in time order, in chunks of DYN_FREQ_CHUNK.  With one run of
+// classes the windows' totals are added here too, in class order.  With a block per class and 256 ticks, results written a class apart
 // and a kernel of its own for the sums: 31 + 7.6 us for 432 000 ticks.
-// LDS: [load axis] [energy chunk*run] [capacities, reciprocals run*n_f each (TABLED)] [instances run] [frequency chunk*run] [TP run] [bucket index]
+// LDS: [load axis] [energy chunk*cells] [capacities, reciprocals cells*n_f each (TABLED)] [instances cells] [frequency chunk*cells] [table row cells] [first tick cells]
+//      [class cells] [bucket index]
 template <bool TABLED, int AXIS>
-__global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void hier_freq_kernel(HierArgs a, int run, int n_run, int chunk) {
+__global__ __launch_bounds__(DYN_FREQ_MOST) __attribute__((amdgpu_waves_per_eu(6, 6))) void hier_freq_kernel(HierArgs a, DynFreqShape f) {
   extern __shared__ double s_freq[];
-  const int w = blockIdx.x / n_run, g0 = (int)(blockIdx.x % n_run) * run, n_g = min(run, a.G - g0);
+  const int run = f.run, chunk = f.chunk, most = f.wins * run;
+  const int w0 = (int)(blockIdx.x / f.n_run) * f.wins, g0 = (int)(blockIdx.x % f.n_run) * run;
+  const int n_g = min(run, a.G - g0), n_w = min(f.wins, a.n_window - w0), n_c = n_w * n_g;
   const Axis axis = place_axis<AXIS>(s_freq, a.n_rho, a.axis.n_bucket);
-  double* s_e = axis.end;                                    // [chunk][run]
-  double* s_den = s_e + (size_t)chunk * run;                 // [run][n_f]
-  double* s_rden = s_den + (TABLED ? (size_t)run * a.n_f : 0);
-  double* s_nd = s_rden + (TABLED ? (size_t)run * a.n_f : 0);
-  int32_t* s_f = (int32_t*)(s_nd + run);                     // [chunk][run]; bit 30: no frequency was admissible
-  int32_t* s_ti = s_f + chunk * run;                         // -1: no layout
-  uint16_t* s_js = (uint16_t*)(s_ti + run);
+  double* s_e = axis.end;                                    // [chunk][most]
+  double* s_den = s_e + (size_t)chunk * most;                // [most][n_f]
+  double* s_rden = s_den + (TABLED ? (size_t)most * a.n_f : 0);
+  double* s_nd = s_rden + (TABLED ? (size_t)most * a.n_f : 0);
+  int32_t* s_f = (int32_t*)(s_nd + most);                    // [chunk][most]; bit 30: no frequency was admissible
+  int32_t* s_row = s_f + chunk * most;                       // first table row of the cell's layout; -1: no layout
+  int32_t* s_at = s_row + most;                              // the cell's first tick
+  int32_t* s_g = s_at + most;                                // the cell's class
+  uint16_t* s_js = (uint16_t*)(s_g + most);
   stage_axis<AXIS>(a.axis, axis, s_js);
-  for (int i = threadIdx.x; i < n_g; i += blockDim.x) {
-    const int l = a.layout_sel[(size_t)w * a.G + g0 + i];
-    s_ti[i] = l < 0 ? -1 : a.lay_tp[l];
+  for (int i = threadIdx.x; i < n_c; i += blockDim.x) {
+    const int dw = i / n_g, g = g0 + (i - dw * n_g), w = w0 + dw;
+    const int l = a.layout_sel[(size_t)w * a.G + g];
+    s_row[i] = l < 0 ? -1 : (g * a.n_tp + a.lay_tp[l]) * a.n_f;
     s_nd[i] = l < 0 ? 1.0 : (double)a.lay_n[l];
+    s_at[i] = w * a.n_tick * a.G + g;                        // below 2^30
+    s_g[i] = g;
   }
   __syncthreads();
   if (TABLED) {
-    for (int i = threadIdx.x; i < n_g * a.n_f; i += blockDim.x) {
-      const int g = i / a.n_f, f = i - g * a.n_f;
-      const double den = s_nd[g] * a.ml[((size_t)(g0 + g) * a.n_tp + max(s_ti[g], 0)) * a.n_f + f];
+    for (int i = threadIdx.x; i < n_c * a.n_f; i += blockDim.x) {
+      const int c = i / a.n_f;
+      const double den = s_nd[c] * a.ml[(size_t)max(s_row[c], 0) + (i - c * a.n_f)];
       s_den[i] = den;
       s_rden[i] = 1.0 / den;
     }
@@ -221,24 +225,26 @@ __global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6,
   Lookup x;
   use_axis<AXIS>(a.axis, axis, s_js, &x);
   const double rho_max = a.axis.rho_max;
-  double sum = 0.0;                                          // thread i: of class g0 + i (run <= kFreqThreads)
+  double sum = 0.0;                                          // thread i: of cell i (at most as many as threads)
   int32_t viol = 0;
   for (int q0 = 0; q0 < a.n_tick; q0 += chunk) {
     const int n_q = min(chunk, a.n_tick - q0);
-    for (int i = threadIdx.x; i < n_g * n_q; i += blockDim.x) {
-      const int gl = i / n_q, q = i - gl * n_q, g = g0 + gl, ti = s_ti[gl];
-      const size_t f = ((size_t)w * a.n_tick + q0 + q) * a.G + g;
-      if (a.cstat_f[f]) atomicOr(a.status, (uint32_t)a.cstat_f[f]);
-      if (ti < 0) {
-        s_f[q * run + gl] = -1;
-        s_e[q * run + gl] = 0.0;
+    int stride = most;                                       // not known to stay the same: the addresses of the sums below are not kept over the look-ups
+    asm volatile("" : "+s"(stride));
+    for (int i = threadIdx.x; i < n_c * n_q; i += blockDim.x) {
+      const int c = i / n_q, q = i - c * n_q;
+      const int row0 = s_row[c], at = s_at[c] + (q0 + q) * a.G;
+      if (a.cstat_f[at]) atomicOr(a.status, (uint32_t)a.cstat_f[at]);
+      if (row0 < 0) {
+        s_f[q * stride + c] = -1;
+        s_e[q * stride + c] = 0.0;
         continue;
       }
-      const CellRec rec = a.rec_f[f];
-      const double load = a.served_f ? a.served_f[f] : rec.load;
-      const double nd = s_nd[gl];
+      const CellRec rec = a.rec_f[at];
+      const double load = a.served_f ? a.served_f[at] : rec.load;
+      const double nd = s_nd[c];
+      const int g = s_g[c];
       const double slo_t = a.slo_ttft[g], slo_b = a.slo_tbt[g];
-      const size_t row0 = ((size_t)g * a.n_tp + ti) * a.n_f;
       int bf = -1;
       double bp = __builtin_inf(), pw_ref = 0.0;
       for (int f0 = 0; f0 < a.n_f; f0 += kFreqChunk) {
@@ -247,24 +253,24 @@ __global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6,
         int j[kFreqChunk];
         Row r[kFreqChunk];
 #pragma unroll
-        for (int c = 0; c < kFreqChunk; ++c) {               // level 1: capacities
-          const int fi = min(f0 + c, a.n_f - 1);
-          const double rho = TABLED ? div_by(load, s_den[gl * a.n_f + fi], s_rden[gl * a.n_f + fi]) : load / (nd * a.ml[row0 + fi]);
-          ov[c] = rho > rho_max;
-          rc[c] = ov[c] ? rho_max : rho;
+        for (int k = 0; k < kFreqChunk; ++k) {               // level 1: capacities
+          const int fi = min(f0 + k, a.n_f - 1);
+          const double rho = TABLED ? div_by(load, s_den[c * a.n_f + fi], s_rden[c * a.n_f + fi]) : load / (nd * a.ml[row0 + fi]);
+          ov[k] = rho > rho_max;
+          rc[k] = ov[k] ? rho_max : rho;
         }
 #pragma unroll
-        for (int c = 0; c < kFreqChunk; ++c) j[c] = bracket<AXIS>(x, rc[c]);   // level 2: the load axis
+        for (int k = 0; k < kFreqChunk; ++k) j[k] = bracket<AXIS>(x, rc[k]);   // level 2: the load axis
 #pragma unroll
-        for (int c = 0; c < kFreqChunk; ++c)                 // level 3: table values
-          interpolate<AXIS>(a.tab, x, row0 + min(f0 + c, a.n_f - 1), j[c], rc[c], &r[c]);
+        for (int k = 0; k < kFreqChunk; ++k)                 // level 3: table values
+          interpolate<AXIS>(a.tab, x, (size_t)(row0 + min(f0 + k, a.n_f - 1)), j[k], rc[k], &r[k]);
 #pragma unroll
-        for (int c = 0; c < kFreqChunk; ++c) {               // ascending frequency: the lowest wins equal powers
-          const int fi = f0 + c;
+        for (int k = 0; k < kFreqChunk; ++k) {               // ascending frequency: the lowest wins equal powers
+          const int fi = f0 + k;
           if (fi >= a.n_f) break;
-          if (fi == a.f_ref) pw_ref = r[c].pw;
-          if (ov[c] || rec.xp99 * r[c].pf > slo_t || r[c].tb * rec.nonempty > slo_b) continue;
-          if (bf < 0 || r[c].pw < bp) { bf = fi; bp = r[c].pw; }
+          if (fi == a.f_ref) pw_ref = r[k].pw;
+          if (ov[k] || rec.xp99 * r[k].pf > slo_t || r[k].tb * rec.nonempty > slo_b) continue;
+          if (bf < 0 || r[k].pw < bp) { bf = fi; bp = r[k].pw; }
         }
       }
       int32_t none = 0;
@@ -273,40 +279,44 @@ __global__ __launch_bounds__(kFreqThreads) __attribute__((amdgpu_waves_per_eu(6,
         bf = a.f_ref;
         none = 1 << 30;
       }
-      s_f[q * run + gl] = bf | none;
-      s_e[q * run + gl] = (nd * bp) * a.tick_s;
+      s_f[q * stride + c] = bf | none;
+      s_e[q * stride + c] = (nd * bp) * a.tick_s;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n_g * n_q; i += blockDim.x) {
-      const int q = i / n_g, gl = i - q * n_g;
-      const int32_t v = s_f[q * run + gl];
-      a.f_sel[((size_t)w * a.n_tick + q0 + q) * a.G + g0 + gl] = v < 0 ? -1 : v & ~(1 << 30);
+    for (int i = threadIdx.x; i < n_c * n_q; i += blockDim.x) {
+      const int q = i / n_c, c = i - q * n_c;
+      const int32_t v = s_f[q * stride + c];
+      a.f_sel[s_at[c] + (q0 + q) * a.G] = v < 0 ? -1 : v & ~(1 << 30);
     }
-    if ((int)threadIdx.x < n_g)
+    if ((int)threadIdx.x < n_c)
       for (int q = 0; q < n_q; ++q) {                        // time order
-        sum += s_e[q * run + threadIdx.x];
-        const int32_t v = s_f[q * run + threadIdx.x];
+        sum += s_e[q * stride + threadIdx.x];
+        const int32_t v = s_f[q * stride + threadIdx.x];
         viol += v >= 0 ? v >> 30 : 0;
       }
     __syncthreads();
   }
-  if ((int)threadIdx.x < n_g) {
-    const size_t cell = (size_t)w * a.G + g0 + threadIdx.x;
-    const bool has = s_ti[threadIdx.x] >= 0;
+  if ((int)threadIdx.x < n_c) {
+    const int dw = threadIdx.x / n_g;
+    const size_t cell = (size_t)(w0 + dw) * a.G + g0 + ((int)threadIdx.x - dw * n_g);
+    const bool has = s_row[threadIdx.x] >= 0;
     a.energy[cell] = has ? sum : __builtin_inf();
     a.violations[cell] = has ? viol : 0;
     s_e[threadIdx.x] = sum;
   }
-  if (n_run > 1) return;                                     // the totals are another kernel's
+  if (f.n_run > 1) return;                                   // the totals are another kernel's
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if ((int)threadIdx.x < n_w) {                              // thread i: window i
+    const double* e_w = s_e + threadIdx.x * n_g;
+    const int32_t* row_w = s_row + threadIdx.x * n_g;
     double e = 0.0;
     int32_t ninf = 0;
+#pragma unroll 4
     for (int g = 0; g < n_g; ++g) {
-      if (s_ti[g] >= 0) e += s_e[g]; else ++ninf;
+      if (row_w[g] >= 0) e += e_w[g]; else ++ninf;
     }
-    a.win_energy[w] = e;
-    a.win_inf[w] = ninf;
+    a.win_energy[w0 + threadIdx.x] = e;
+    a.win_inf[w0 + threadIdx.x] = ninf;
   }
 }
 
@@ -464,26 +474,18 @@ hipError_t dyn_launch_hier_shard(const HierArgs& a, hipStream_t s) {
 
 hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s) {
   const int axis = dyn_axis(a.axis);
-  const int chunk = std::min(a.n_tick, kTickChunk);
-  const bool tabled = a.n_f <= kFreqTabled;
-  const size_t per_class = (size_t)chunk * (sizeof(double) + sizeof(int32_t)) + (tabled ? (size_t)a.n_f * 2 * sizeof(double) : 0) + sizeof(double) + sizeof(int32_t);
-  const int run = (int)std::max<size_t>(1, std::min<size_t>(std::min(a.G, kFreqThreads), kFreqLds / per_class));
-  const int n_run = (a.G + run - 1) / run;
-  const size_t axis_lds = dyn_axis_lds(a.axis, axis);
-  size_t lds = axis_lds + (size_t)run * per_class;
-  const bool staged = tabled && dyn_freq_axis_staged(axis_lds, lds, (int64_t)a.n_window * n_run, a.n_cu);
-  if (!staged) lds -= axis_lds;
+  const DynFreqShape f = dyn_freq_shape(a.n_window, a.G, a.n_tick, a.n_f, dyn_axis_lds(a.axis, axis), a.n_cu);
   {
     DynTimed timed(DYN_K_HIER, s);
-    const dim3 grid((unsigned)((int64_t)a.n_window * n_run));
+    const dim3 grid((unsigned)f.blocks), block(f.threads);
     with_axis(axis, [&](auto x) {
       constexpr int FORM = decltype(x)::value;
-      if (staged) hipLaunchKernelGGL((hier_freq_kernel<true, FORM>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
-      else if (tabled) hipLaunchKernelGGL((hier_freq_kernel<true, FORM | DYN_AXIS_GLOBAL>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
-      else hipLaunchKernelGGL((hier_freq_kernel<false, FORM | DYN_AXIS_GLOBAL>), grid, dim3(kFreqThreads), lds, s, a, run, n_run, chunk);
+      if (f.staged) hipLaunchKernelGGL((hier_freq_kernel<true, FORM>), grid, block, f.lds, s, a, f);
+      else if (f.tabled) hipLaunchKernelGGL((hier_freq_kernel<true, FORM | DYN_AXIS_GLOBAL>), grid, block, f.lds, s, a, f);
+      else hipLaunchKernelGGL((hier_freq_kernel<false, FORM | DYN_AXIS_GLOBAL>), grid, block, f.lds, s, a, f);
     });
   }
-  if (n_run > 1) {
+  if (f.n_run > 1) {
     const hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : dyn_launch_window_totals(a.layout_sel, a.energy, a.n_window, a.G, a.win_energy, a.win_inf, s);
   }

@@ -278,6 +278,23 @@ def test_many_ticks_and_many_frequencies(dyn, n_tick, n_f):
     assert (o["layout_sel"] >= 0).any() and o["violations"].sum() > 0
 
 
+@pytest.mark.parametrize("G,n_tick,NW", [(1, 1, 5003), (1, 5, 1030), (1, 12, 2017), (1, 65, 600), (3, 5, 2000), (9, 12, 1025), (25, 12, 7), (48, 12, 3), (100, 12, 5)])
+def test_windows_and_classes_packed_into_blocks(dyn, G, n_tick, NW):
+    """Blocks of several windows (the last not full), of more than 256 threads, and runs of classes; some cells without a layout, some without requests."""
+    prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(G, n_tick, 3, 40 * n_tick * G + 6 * NW * n_tick, NW)
+    rng = np.random.default_rng(G)
+    a = 1 if G in (1, 3) else {9: 3, 25: 5, 48: 6, 100: 10}[G]
+    edges = {"in_edge": np.linspace(1, 500, a + 1)[1:-1].astype(np.int32).reshape(1, -1), "out_edge": np.linspace(1, 300, G // a + 1)[1:-1].astype(np.int32).reshape(1, -1)}
+    shape = (G,) + prof["tbt_ms"].shape[1:]
+    prof = dict(prof, prefill_ms_per_tok=rng.uniform(0.02, 0.1, shape), tbt_ms=np.sort(rng.uniform(10, 150, shape), axis=-1), power_w=np.sort(rng.uniform(100, 3000, shape), axis=-1),
+                max_load_tps=rng.uniform(300, 1500, shape[:3]) * (0.3 / min(G, 2)))
+    slo = {"slo_ttft_ms": rng.uniform(25, 70, G), "slo_tbt_ms": rng.uniform(80, 150, G)}
+    g, coarse, fine = gpu_hier(dyn, prof, tr, edges, NW, T, tick, 5, 2, 2, 8, lay_n, lay_tp, slo)
+    o = oracle.hierarchy(prof, coarse, fine, NW, T, tick, 5, 2, 2, 8, lay_n, lay_tp, slo)
+    assert_same(g, o, NW, G)
+    assert (o["layout_sel"] >= 0).any() and (o["layout_sel"] < 0).any()
+
+
 def test_more_than_64_layouts_and_ties(dyn):
     """Layout list longer than a wave with repeated entries: the lowest index of equal energies is chosen."""
     prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(5, 4, 3, 4000, 6)
