@@ -372,7 +372,7 @@ int32_t space_windows_per_block(dyn_profile* p, const SpaceArgs& a_in, int32_t n
   if (p->wpb > 0 && p->wpb_windows == n_window) return p->wpb;
   SpaceArgs a = a_in;
   a.win_per_block = 8;
-  p->wpb = dyn_space_windows((int64_t)n_window * p->G * p->n_tile, p->tile, (int64_t)p->n_slot * 3 * p->n_rho, dyn_space_lds(a), p->n_cu);
+  p->wpb = dyn_space_windows((int64_t)n_window * p->G * p->n_tile, p->tile, (int64_t)p->n_slot * 3 * p->n_rho, dyn_space_waves_per_cu(a));
   p->wpb_windows = n_window; p->wpb_tuned = false;
   return p->wpb;
 }

@@ -20,28 +20,30 @@ inline double dyn_even_scale(const double* rho, int32_t n_rho) {
   return scale;
 }
 
-// Blocks of `threads` threads and `lds` bytes that a compute unit of 2048 threads and 160 KB (in pieces of 512 bytes) has room for.
-inline int32_t dyn_blocks_in_room(int32_t threads, size_t lds) {
-  return (int32_t)std::max<size_t>(1, std::min((size_t)(160 * 1024) / std::max<size_t>(512, (lds + 511) / 512 * 512), (size_t)(2048 / threads)));
-}
-
 #define DYN_MAX_WIN_PER_BLOCK 32  // windows one block of the space kernel walks
 
+#define DYN_SPACE_IN_FLIGHT 224   // (wave, window) pairs of a compute unit
+
 // Windows one block of the evaluation kernel walks.  Long runs amortise the staging of the table rows in LDS, but
-// the blocks a chip holds at a time then write that many more separate streams; measured on the one-day and the two
-// one-week workloads the kernel is fastest when about 16K (block, window) rows are in flight at a time (8, 6 and 8
-// windows; 14 to 32 cost 8 to 22 % more), and no run should leave the chip with fewer than ~8192 blocks in all.  The rows are those of
-// the blocks that LDS and threads leave room for: by the blocks that the registers of each form leave (6 or 7 of 8 waves) 256-wide tiles got 9 or 10
-// windows in place of 8, 2.0 GB of results (2048 candidates) 371 and 377 us, 354; 10.3 GB 1835, 1787, 1755; with 10^8 requests 2050, 2190, 2010.
+// the blocks a chip holds at a time then write that many more separate streams; and no run should leave the chip with fewer than ~8192
+// blocks in all.  What decides is how many rows of 64 results a compute unit writes over a block's life, its resident waves times the windows of a block: about
+// 224.  us by windows a block, even load points (GB of results; candidates in tiles of, resident waves):
+//   2 GB, 256, 32 waves:  6 365, 7 366, 8 385, 10 403      2 GB, 256, 24 waves:  6 370, 7 365, 8 365, 9 376, 10 395
+//   4 GB, 256, 32 waves:  6 708, 7 700, 8 700, 10 744      4 GB, 256, 24 waves:  6 725, 8 691, 9 694, 10 700, 12 738
+//   8 GB, 256, 32 waves:  6 1391, 7 1361, 8 1368, 10 1435  10.3 GB and 10^8 requests, 32 waves:  6 2034, 7 1997, 8 2054, 10 2220
+//   4 GB, 192, 24 waves:  6 802, 8 744, 9 740, 10 783      1 GB, 192, 24 waves:  6 223, 8 211, 9 216, 10 225
+//   4 GB, 128, 22 waves:  5 887, 8 760, 9 755, 10 737, 12 715    4 GB, 64, 20 waves:  4 1002, 8 789, 9 765, 10 748, 12 750
+// The former rule counted 64 rows of blocks a compute unit whatever their width: 5 and 4 windows in the last line, and with uneven points (64 wide, 10 waves
+// beside their bucket index) 2 GB in 1218 us, 634 now.
 // How much a block stages moves that: up to 7 table values a thread leave little to amortise, more than 14 much.  Over 50 traces of 300 000
 // requests (13 000 to 313 000 tiles of cells, 0.4 to 40 million results) at 1 to 16 windows, the call is 8.8 % above its best without these two
 // lines, 6.4 % with them.  Up to 7, 4 windows in place of 5 to 8: 128 us 121, 113 100, 86 76, 79 76, 64 56, 139 127, 107 105, 58 58 and 61 66 (50 400
 // cells of 1152 candidates, beyond 250 000 tiles, 314 at 6, 338); beyond 14, 8 in place of 4: 107 80, 77 66, 71 63, 79 75, 76 74 and 79 81 (the fewest
 // tiles 91 000; 31 800 at 4 and 6 windows 66, 61).  Between, 4 in place of 6 is as often better as worse: 237 195, 341 317, 94 89, 125 123, 68 73, 241 279; the
 // one-day workload stages 12.  Blocks that stage nothing keep the first rule.  dyn_eval_tune replaces the rule's value by a measured one.
-inline int32_t dyn_space_windows(int64_t cell_tiles, int32_t tile, int64_t staged /* table values of a block */, size_t lds, int32_t n_cu) {
+inline int32_t dyn_space_windows(int64_t cell_tiles, int32_t tile, int64_t staged /* table values of a block */, int32_t waves /* of a compute unit */) {
   int64_t w = std::max<int64_t>(1, std::min<int64_t>(DYN_MAX_WIN_PER_BLOCK, (cell_tiles + 8191) / 8192));
-  if (n_cu > 0) w = std::min<int64_t>(w, std::max<int64_t>(4, 16384 / ((int64_t)dyn_blocks_in_room(tile, lds) * n_cu)));
+  if (waves > 0) w = std::min<int64_t>(w, std::max<int64_t>(4, DYN_SPACE_IN_FLIGHT / waves));
   if (staged > 0 && staged <= 7 * (int64_t)tile && cell_tiles <= 250000) w = std::min<int64_t>(w, 4);
   else if (staged > 14 * (int64_t)tile && cell_tiles >= 8 * 4096) w = std::max<int64_t>(w, 8);   // at least 4096 blocks
   return (int32_t)w;

@@ -200,12 +200,15 @@ size_t space_lds(const SpaceArgs& a) {
   return space_form(a) == kEven ? even_lds(a) : rows_lds(a) + dyn_space_lds_tail(a.n_rho, a.axis.n_bucket, a.win_per_block);   // host keeps this <= 64 KB
 }
 
+using SpaceKernel = void (*)(SpaceArgs);
 template <bool LDS, bool SEL>
-void launch_form(const SpaceArgs& a, dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+SpaceKernel of_form(const SpaceArgs& a) {
   const int form = space_form(a);
-  if (form == kEven) hipLaunchKernelGGL((space_kernel<LDS, SEL, kEven>), grid, block, lds, s, a);
-  else if (form == kOneStep) hipLaunchKernelGGL((space_kernel<LDS, SEL, kOneStep>), grid, block, lds, s, a);
-  else hipLaunchKernelGGL((space_kernel<LDS, SEL, kSearch>), grid, block, lds, s, a);
+  return form == kEven ? space_kernel<LDS, SEL, kEven> : form == kOneStep ? space_kernel<LDS, SEL, kOneStep> : space_kernel<LDS, SEL, kSearch>;
+}
+SpaceKernel kernel_of(const SpaceArgs& a) {
+  if (a.n_slot > 0) return a.part ? of_form<true, true>(a) : of_form<true, false>(a);
+  return a.part ? of_form<false, true>(a) : of_form<false, false>(a);
 }
 
 }  // namespace
@@ -215,20 +218,17 @@ size_t dyn_space_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t win_per_block
          ((size_t)n_bucket + 1) * sizeof(uint16_t);
 }
 
-size_t dyn_space_lds(const SpaceArgs& a) { return space_lds(a); }
+// Waves of the fused kernel of this form on a compute unit (0 if the query fails); the kernel without the selection has the same windows.
+int dyn_space_waves_per_cu(const SpaceArgs& a) {
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, a.n_slot > 0 ? of_form<true, true>(a) : of_form<false, true>(a), a.tile, space_lds(a)) != hipSuccess) { (void)hipGetLastError(); return 0; }
+  return n * (a.tile / DYN_WAVE);
+}
 
 hipError_t dyn_launch_space(const SpaceArgs& a, hipStream_t s) {
   const int n_chunk = (a.n_window + a.win_per_block - 1) / a.win_per_block;
   const size_t blocks = (size_t)n_chunk * a.G * a.n_tile;
   DynTimed timed(DYN_K_SPACE, s);
-  const size_t lds = space_lds(a);
-  const dim3 grid((unsigned)blocks), block(a.tile);
-  if (a.n_slot > 0) {
-    if (a.part) launch_form<true, true>(a, grid, block, lds, s);
-    else launch_form<true, false>(a, grid, block, lds, s);
-  } else {
-    if (a.part) launch_form<false, true>(a, grid, block, lds, s);
-    else launch_form<false, false>(a, grid, block, lds, s);
-  }
+  hipLaunchKernelGGL(kernel_of(a), dim3((unsigned)blocks), dim3(a.tile), space_lds(a), s, a);
   return hipGetLastError();
 }

@@ -11,7 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "dyn_rules.h"
 extern "C" double even_scale(const double* rho, int n) { return dyn_even_scale(rho, n); }
-extern "C" int space_windows(long long cell_tiles, int tile, long long staged, long long lds, int n_cu) { return dyn_space_windows(cell_tiles, tile, staged, (size_t)lds, n_cu); }
+extern "C" int space_windows(long long cell_tiles, int tile, long long staged, int waves) { return dyn_space_windows(cell_tiles, tile, staged, waves); }
 extern "C" int freq_axis_staged(long long axis_lds, long long lds, long long blocks, int n_cu) { return dyn_freq_axis_staged((size_t)axis_lds, (size_t)lds, blocks, n_cu); }
 extern "C" void freq_shape(int n_window, int G, int n_tick, int n_f, long long axis_lds, int n_cu, long long* o) {
   const DynFreqShape f = dyn_freq_shape(n_window, G, n_tick, n_f, (size_t)axis_lds, n_cu);
@@ -64,14 +64,12 @@ def test_displaced_load_points(rules, by):
     assert _even_scale(rules, rho) == 0.0 and _even_scale(rules, one) == 0.0
 
 
-@pytest.mark.parametrize("tile,rows,n_rho,want", [(256, 8, 64, 8), (192, 12, 64, 8), (128, 8, 64, 5), (64, 4, 64, 4), (256, 8, 72, 8), (192, 12, 200, 32)])
-def test_windows_a_block_of_a_large_space(rules, tile, rows, n_rho, want):
-    """About 16 384 rows in flight of the blocks that LDS and threads leave room for, on 256 compute units: the registers of the form that
-    runs do not come into it (by them 256-wide tiles got 9 or 10 windows)."""
-    lds = 8 * (3 * rows * n_rho + 3 * (n_rho - 1)) + 8 * 24
-    got = rules.space_windows(C.c_longlong(1_600_000), tile, C.c_longlong(3 * rows * n_rho), C.c_longlong(lds), 256)
-    room = max(1, min(160 * 1024 // ((lds + 511) // 512 * 512), 2048 // tile))
-    assert got == want == max(min(32, max(4, 16384 // (256 * room))), 8 if 3 * rows * n_rho > 14 * tile else 1)
+@pytest.mark.parametrize("tiles,tile,staged,waves,want", [(1_600_000, 256, 1536, 32, 7), (1_600_000, 256, 1536, 24, 9), (830_000, 192, 2304, 24, 9), (1_250_000, 128, 1536, 22, 10),
+                                                          (2_500_000, 64, 768, 20, 11), (1_250_000, 64, 768, 10, 22), (1_600_000, 256, 1536, 0, 32), (60_000, 256, 3600, 32, 8),
+                                                          (250_000, 256, 1536, 32, 4), (8192, 64, 700, 32, 1), (20_000, 256, 2048, 32, 3)])
+def test_windows_a_block(rules, tiles, tile, staged, waves, want):
+    """Resident waves times windows stay at about 224 where the device is full, whatever the width of the tiles; few tiles keep 8192 blocks."""
+    assert rules.space_windows(C.c_longlong(tiles), tile, C.c_longlong(staged), waves) == want
 
 
 @pytest.mark.parametrize("axis,lds,blocks,staged", [(1512, 10_000, 10_000, 1), (40 * 1024, 56 * 1024, 10_000, 1), (46 * 1024, 54 * 1024, 512, 1), (46 * 1024, 54 * 1024, 513, 0),
