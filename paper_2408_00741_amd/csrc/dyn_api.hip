@@ -419,7 +419,7 @@ int eval_impl(dyn_profile* p, const dyn_trace_view* t, const dyn_config* cfg, in
     return DYN_E_DEVICE;
 
   SpaceArgs a;
-  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step;
+  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step; a.two_rows = p->any_two_rows;
   a.G = p->G; a.n_tp_f = p->n_tp * p->n_f; a.n_rho = p->n_rho;
   a.cfg = p->d_cfg; a.K = K; a.tile = p->tile; a.n_tile = p->n_tile; a.n_slot = p->n_slot;
   a.tile_rows = p->d_tile_rows;
@@ -856,7 +856,7 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
 
   TickArgs ta;
   SpaceArgs& a = ta.s;
-  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step;
+  a.tab = p->d_tab; a.ml = p->d_ml; a.axis = axis_args(p); a.one_step = p->one_step; a.two_rows = p->any_two_rows;
   a.G = p->G; a.n_tp_f = p->n_tp * p->n_f; a.n_rho = p->n_rho;
   a.cfg = p->d_cfg; a.K = K; a.tile = p->tile; a.n_tile = p->n_tile; a.n_slot = p->n_slot;
   a.tile_rows = p->d_tile_rows;
@@ -869,7 +869,6 @@ int dyn_eval_select_ticks(dyn_profile* p, const dyn_trace_view* t, int32_t n_tic
   ta.rec = (const TickRec*)(base + w.fine.rec); ta.plan = (const TickPlan*)(base + w.plan); ta.top = (const int32_t*)(base + w.top);
   ta.in = t->in_tok; ta.pool = ca.pool;
   ta.counters = (const uint32_t*)(base + w.counters); ta.slow_list = (const uint32_t*)(base + w.slow_list);
-  ta.any_two_rows = p->any_two_rows;
   ta.pfspan = p->d_pfspan; ta.steep = p->d_steep; ta.n_cu = p->n_cu;
   ta.mean_depth = t->n_req * (o->pct_den - o->pct_num) / o->pct_den / cells;   // n_req and the percentile's numbers are below 2^31
   if (!hip_ok(dyn_launch_tick_space(ta, s), "tick space launch")) return DYN_E_DEVICE;

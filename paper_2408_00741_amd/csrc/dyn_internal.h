@@ -177,6 +177,7 @@ inline size_t dyn_axis_lds(const AxisArgs& a, int axis) {
 
 struct SpaceArgs {
   const double* tab; const double* ml; AxisArgs axis; bool one_step;
+  bool two_rows;                      // some candidate lies between two profiled frequencies
   int32_t G, n_tp_f /* n_tp*n_f */, n_rho;
   const DevCfg* cfg; int32_t K;
   int32_t tile, n_tile, n_slot;       // configurations per tile, tiles, LDS slots per tile

@@ -78,7 +78,6 @@ struct TickArgs {
   const int32_t* top;      // [n_req]
   const int32_t* in;       // [n_req] input lengths of the trace sorted by tick (DYN_TP_RAW cells)
   const uint32_t* pool;    // the tables of DYN_TP_TABLE cells
-  bool any_two_rows;
   int32_t win_long, n_long;   // of the walk without lists: its first n_long blocks of a (class, tile) take win_long windows each
   int32_t n_cu;               // compute units of the device (0: unknown)
   int64_t mean_depth;         // the percentile's rank from the top in a cell of mean length

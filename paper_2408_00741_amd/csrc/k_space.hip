@@ -22,7 +22,9 @@ namespace {
 
 // LDS: [table rows n_slot*3*n_rho] [load axis] [cell records win_per_block] [bucket index n_bucket+1 (16-bit)]
 enum { kSearch = 0, kOneStep = 1, kEven = 2 };   // how the bracket is found; kOneStep: it is at most one from the bucket's index
-template <bool LDS, bool SEL, int FORM>
+// TWO: some candidate lies between two profiled frequencies.  Without, the second row's code takes no registers: 58 in the even form with the
+// selection (76), 50 in kOneStep (68), 60 in kSearch (78), and 32 waves a compute unit in place of 24 or 28.
+template <bool LDS, bool SEL, int FORM, bool TWO>
 __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   extern __shared__ double smem[];
   // block -> (window chunk, class, tile); tile fastest
@@ -62,7 +64,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
   const int k = live ? k_raw : a.K - 1;
 
   const DevCfg c = a.cfg[k];
-  const bool two_rows = c.u != 0.0;
+  const bool two_rows = TWO && c.u != 0.0;
   const double omu = 1.0 - c.u;
   const double* mlrow = a.ml + (size_t)g * a.n_tp_f;
   const double ml = two_rows ? omu * mlrow[c.row_lo] + c.u * mlrow[c.row_hi] : mlrow[c.row_lo];
@@ -201,14 +203,15 @@ size_t space_lds(const SpaceArgs& a) {
 }
 
 using SpaceKernel = void (*)(SpaceArgs);
-template <bool LDS, bool SEL>
-SpaceKernel of_form(const SpaceArgs& a) {
-  const int form = space_form(a);
-  return form == kEven ? space_kernel<LDS, SEL, kEven> : form == kOneStep ? space_kernel<LDS, SEL, kOneStep> : space_kernel<LDS, SEL, kSearch>;
+template <bool LDS, bool SEL, bool TWO>
+SpaceKernel of_form(int form) {
+  return form == kEven ? space_kernel<LDS, SEL, kEven, TWO> : form == kOneStep ? space_kernel<LDS, SEL, kOneStep, TWO> : space_kernel<LDS, SEL, kSearch, TWO>;
 }
+template <bool LDS, bool SEL>
+SpaceKernel of_rows(const SpaceArgs& a) { return a.two_rows ? of_form<LDS, SEL, true>(space_form(a)) : of_form<LDS, SEL, false>(space_form(a)); }
 SpaceKernel kernel_of(const SpaceArgs& a) {
-  if (a.n_slot > 0) return a.part ? of_form<true, true>(a) : of_form<true, false>(a);
-  return a.part ? of_form<false, true>(a) : of_form<false, false>(a);
+  if (a.n_slot > 0) return a.part ? of_rows<true, true>(a) : of_rows<true, false>(a);
+  return a.part ? of_rows<false, true>(a) : of_rows<false, false>(a);
 }
 
 }  // namespace
@@ -221,7 +224,7 @@ size_t dyn_space_lds_tail(int32_t n_rho, int32_t n_bucket, int32_t win_per_block
 // Waves of the fused kernel of this form on a compute unit (0 if the query fails); the kernel without the selection has the same windows.
 int dyn_space_waves_per_cu(const SpaceArgs& a) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, a.n_slot > 0 ? of_form<true, true>(a) : of_form<false, true>(a), a.tile, space_lds(a)) != hipSuccess) { (void)hipGetLastError(); return 0; }
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, a.n_slot > 0 ? of_rows<true, true>(a) : of_rows<false, true>(a), a.tile, space_lds(a)) != hipSuccess) { (void)hipGetLastError(); return 0; }
   return n * (a.tile / DYN_WAVE);
 }
 

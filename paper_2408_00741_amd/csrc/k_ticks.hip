@@ -2401,7 +2401,7 @@ int32_t dyn_tick_win_per_block(const TickArgs& a) {
 static void tight_chunks(TickArgs& a, size_t tab) {
   SpaceArgs& sa = a.s;
   const int64_t few = std::max<int64_t>(2, std::min<int64_t>(16, stage_windows(a))), many = 4 * few;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((a.any_two_rows ? 20 : 24) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((a.s.two_rows ? 20 : 24) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
   const int64_t places = per_cu * std::max(1, a.n_cu), columns = (int64_t)sa.G * sa.n_tile;
   const int64_t kept = (4 * few * places + columns - 1) / columns;   // windows left to the blocks of few
   a.win_long = (int32_t)many;
@@ -2430,7 +2430,7 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
     const bool lds = sa.n_slot > 0 && tab + tail <= DYN_LDS_BUDGET;
     if (!lds && tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
     const size_t bytes = (lds ? tab : 0) + tail;
-    dispatch(lds, axis, a.any_two_rows, [&](auto L, auto S, auto W) {
+    dispatch(lds, axis, a.s.two_rows, [&](auto L, auto S, auto W) {
       launch_tight_walk<decltype(L)::value, decltype(S)::value, decltype(W)::value>(a, grid_t, block, bytes, s);
     });
     sa.win_per_block = wpb_list;
@@ -2452,7 +2452,7 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
     const bool lds = sa.n_slot > 0 && tab + tail <= DYN_LDS_BUDGET;
     if (!lds && tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
     const size_t bytes = (lds ? tab : 0) + tail;
-    dispatch(lds, axis, a.any_two_rows, [&](auto L, auto S, auto W) {
+    dispatch(lds, axis, a.s.two_rows, [&](auto L, auto S, auto W) {
       launch_space<decltype(L)::value, decltype(S)::value, decltype(W)::value>(a, grid_l, block, bytes, s);
     });
     hipError_t e = hipGetLastError();
@@ -2464,7 +2464,7 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
     const int axis = axis_that_fits(a, 0, [&](int x) { return general_lds_tail(a, a.n_tick, nt, x); });
     const size_t tail = general_lds_tail(a, a.n_tick, nt, axis);
     if (tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;
-    dispatch(false, axis, a.any_two_rows, [&](auto, auto S, auto W) {
+    dispatch(false, axis, a.s.two_rows, [&](auto, auto S, auto W) {
       launch_general<decltype(S)::value, decltype(W)::value>(a, tail, s);
     });
   }
