@@ -23,9 +23,10 @@ namespace {
 // LDS: [table rows n_slot*3*n_rho] [load axis] [cell records win_per_block] [bucket index n_bucket+1 (16-bit)]
 enum { kSearch = 0, kOneStep = 1, kEven = 2 };   // how the bracket is found; kOneStep: it is at most one from the bucket's index
 // TWO: some candidate lies between two profiled frequencies.  Without, the second row's code takes no registers: 58 in the even form with the
-// selection (76), 50 in kOneStep (68), 60 in kSearch (78), and 32 waves a compute unit in place of 24 or 28.
+// selection, 50 in kOneStep, 60 in kSearch.  With, its values are read after the first row's are used, and 64 registers do: both rows at once take 68 to 78, and blocks that fit
+// the device with 8 waves a SIMD then need a second round (6741 cells of 231 candidates 37.6 us, 34.4).
 template <bool LDS, bool SEL, int FORM, bool TWO>
-__global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
+__global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(LDS && SEL && TWO && FORM != kOneStep ? 8 : 1))) void space_kernel(SpaceArgs a) {
   extern __shared__ double smem[];
   // block -> (window chunk, class, tile); tile fastest
   const int tile = blockIdx.x % a.n_tile;
@@ -104,16 +105,13 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
     const double rc = ov ? rho_max : rho;
     // bracket: largest j with rho[j] <= rc, at most n_rho-2; start from the bucket index
     // (rc <= rho_max keeps the bucket at or below n_bucket; a negative load maps to bucket 0)
-    double t, v[6], u[6];                       // the two load points of the lower and the upper row
+    int at;
+    double t, v[6];                             // the two load points of the lower row
     auto load = [&](int j) {
       const double* lo = row_lo + 3 * j;
 #pragma unroll
       for (int i = 0; i < 6; ++i) v[i] = lo[i];
-      if (two_rows) {
-        const double* hi = row_hi + 3 * j;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) u[i] = hi[i];
-      }
+      at = j;
     };
     if (FORM == kOneStep) {
       const int b = (int)(fmax(rc, 0.0) * L.scale);
@@ -138,6 +136,7 @@ __global__ __launch_bounds__(DYN_MAX_TILE) void space_kernel(SpaceArgs a) {
     double tb = omt * v[1] + t * v[4];
     double pw = omt * v[2] + t * v[5];
     if (two_rows) {
+      const double* u = row_hi + 3 * at;
       const double pf_b = omt * u[0] + t * u[3];
       const double tb_b = omt * u[1] + t * u[4];
       const double pw_b = omt * u[2] + t * u[5];
