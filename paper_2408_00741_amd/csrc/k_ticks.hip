@@ -1946,8 +1946,11 @@ __global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(4,
 // settled by their ticks' requests of length x_j (DYN_TP_TIGHT).  A wave takes a cell's ticks from global memory into its lanes, the
 // next cell's while it walks this one; nothing is staged per cell and the block has no barrier after its set-up.
 // LDS: [load axis] [table rows] [bucket index (16-bit)]
+// Waves a SIMD: six leave 80 registers, which do for the even form; the others lack five there, and their reloads wait for the stores before them (36 000 cells of 576
+// candidates on uneven points, 12 ticks 920 us, with five waves 870; one tick 445, 394).
+constexpr int tight_waves(int axis, bool two) { return axis == DYN_AXIS_EVEN && !two ? 6 : 5; }
 template <bool LDS, int AXIS, bool TWO>
-__global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(TWO ? 5 : 6, TWO ? 5 : 6))) void tick_tight_walk_kernel(TickArgs a) {
+__global__ __launch_bounds__(DYN_MAX_TILE) __attribute__((amdgpu_waves_per_eu(tight_waves(AXIS, TWO), tight_waves(AXIS, TWO)))) void tick_tight_walk_kernel(TickArgs a) {
   extern __shared__ double smem[];
   const SpaceArgs& sa = a.s;
   const int tile = blockIdx.x % sa.n_tile;
@@ -2398,10 +2401,10 @@ int32_t dyn_tick_win_per_block(const TickArgs& a) {
 // windows, by how many ticks hold requests of the percentile's length).  So where every place on the device has windows enough, blocks of
 // many windows come first and leave four rounds of blocks of few.  36 000 cells of 576 candidates and 12 ticks, us of the call: 14
 // windows a block 441, 10 436, 20 first and then 7 417, 20 and 5 410, 16 and 5 410, 24 and 8 424.
-static void tight_chunks(TickArgs& a, size_t tab) {
+static void tight_chunks(TickArgs& a, size_t tab, int axis) {
   SpaceArgs& sa = a.s;
   const int64_t few = std::max<int64_t>(2, std::min<int64_t>(16, stage_windows(a))), many = 4 * few;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>((a.s.two_rows ? 20 : 24) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4 * tight_waves(axis, sa.two_rows) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
   const int64_t places = per_cu * std::max(1, a.n_cu), columns = (int64_t)sa.G * sa.n_tile;
   const int64_t kept = (4 * few * places + columns - 1) / columns;   // windows left to the blocks of few
   a.win_long = (int32_t)many;
@@ -2422,10 +2425,10 @@ hipError_t dyn_launch_tick_space(const TickArgs& a_in, hipStream_t s) {
     DynTimed timed(DYN_K_TICK_SPACE, s);         // both walks
     {
     const int32_t wpb_list = sa.win_per_block;
-    tight_chunks(a, tab);
+    const int axis = axis_that_fits(a, tab, [&](int x) { return dyn_axis_lds(sa.axis, x); });
+    tight_chunks(a, tab, axis);
     const int64_t chunks = a.n_long + (sa.n_window - (int64_t)a.n_long * a.win_long + sa.win_per_block - 1) / sa.win_per_block;
     const dim3 grid_t((unsigned)(chunks * sa.G * sa.n_tile));
-    const int axis = axis_that_fits(a, tab, [&](int x) { return dyn_axis_lds(sa.axis, x); });
     const size_t tail = dyn_axis_lds(sa.axis, axis);
     const bool lds = sa.n_slot > 0 && tab + tail <= DYN_LDS_BUDGET;
     if (!lds && tail > DYN_LDS_BUDGET) return hipErrorInvalidValue;

@@ -72,7 +72,7 @@ def test_every_form_of_the_axis(dyn, grid, tbt):
         np.testing.assert_array_equal(space[k].cpu().numpy(), o[k], err_msg=k)
     np.testing.assert_array_equal(sel["sel"].cpu().numpy(), o["sel"])
     prof.free()
-    for n_tick in (1, 5, 40):
+    for n_tick in (1, 2, 5, 40):
         g, fine = gpu_ticks(dyn, w, n_tick)
         assert g["status"] == 0
         assert_same(w, g, ora_ticks(w, fine, n_tick))
