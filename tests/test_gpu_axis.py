@@ -90,7 +90,8 @@ def test_every_form_of_the_axis(dyn, grid, tbt):
 
 @pytest.mark.parametrize("apart", [0, 1, 3, 1 << 10, 1 << 20])
 def test_ticks_whose_loads_are_close(dyn, apart):
-    """One class, ticks of the same number of tokens or `apart` more in one: which tick has the largest TBT is then a matter of roundings."""
+    """One class, ticks of the same number of tokens or `apart` more in one: which tick has the largest TBT is then a matter of roundings.  Lengths of
+    2^16 and more: the cell is walked with lists, which asks every tick."""
     w, _ = _case(GRIDS["even"], "rising", 2000, 1)
     n_tick, per = 8, 12
     n = n_tick * per
@@ -104,6 +105,58 @@ def test_ticks_whose_loads_are_close(dyn, apart):
     g, fine = gpu_ticks(dyn, w, n_tick, pct=(90, 100))
     assert g["status"] == 0
     assert_same(w, g, ora_ticks(w, fine, n_tick, pct=(90, 100)))
+
+
+DENSE, GENERAL, TIGHT = 1, 16, 32               # of a cell's plan
+
+
+def _close_case(tokens, seed):
+    """One populated cell of 6 ticks of 680 requests whose loads are `tokens`, the same again, and 1 to 400 fewer (2^-20 is 32 to 38 of them), and TBT
+    rows that rise by so little that a token is about a rounding, or less, with utilizations on both sides of the rows' bounds; capacities put the
+    largest load on, below and above grid points and the last one."""
+    w, _ = _case(GRIDS["even"], "rising", 2000, 1)
+    rng = np.random.default_rng(seed)
+    n_tick, per, P = 6, 680, w["profile"]
+    w["window_s"] = float(n_tick)               # a tick of one second: loads are token counts
+    x = rng.integers(tokens // per - 2500, tokens // per + 2500, (n_tick, per))
+    lack = tokens - np.asarray([0, 0, 1, 40, 200, 400])[rng.permutation(n_tick)] - per - x.sum(1)      # an output token each
+    x += (lack // per)[:, None]
+    x[:, 0] += lack % per
+    x = x[:, rng.permutation(per)]
+    assert x.min() > 1000 and x.max() < 65535
+    w["trace"] = {"t_s": np.repeat(np.arange(n_tick), per) + 0.5, "in_tok": x.ravel().astype(np.int32), "out_tok": np.ones(n_tick * per, np.int32), "model": np.zeros(n_tick * per, np.int32)}
+    n_tp, n_f, rho = P["tp"].size, 16, P["rho"]
+    w["configs"] = {"n_inst": np.tile(np.arange(1, 9), n_tp * n_f).astype(np.int32), "tp_index": np.repeat(np.arange(n_tp), 8 * n_f).astype(np.int32),
+                    "f_mhz": np.tile(np.repeat(1000.0 + np.arange(n_f), 8), n_tp)}
+    shape = (w["n_class"], n_tp, n_f)
+    at = np.r_[rho[-1] * np.asarray([1.0, 1.0 - 2.0 ** -21, 1.0 + 2.0 ** -21, 1.0 + 1e-9, 1.2]), 0.7, 0.3, rho[rng.integers(1, 32, 5)]]
+    rise = rng.choice([1e-3, 0.1, 1.0, 1.1, 2.0, 5.0, 100.0, 1e4], shape)[..., None]      # the bound is near 1 / rise
+    w["profile"] = {"tp": P["tp"], "f_mhz": 1000.0 + np.arange(n_f), "rho": rho, "max_load_tps": tokens / (rng.choice(at, shape) * rng.integers(1, 4, shape)),
+                    "prefill_ms_per_tok": rng.uniform(0.005, 0.02, shape)[..., None] + 0.0 * rho, "power_w": rng.uniform(100.0, 200.0, shape)[..., None] * (1.0 + rho),
+                    "tbt_ms": rng.uniform(5.0, 40.0, shape)[..., None] * (1.0 + rise * 2.0 ** -28 * rho)}
+    return w, n_tick
+
+
+@pytest.mark.parametrize("tokens", [1 << 25, (1 << 25) + 1, (1 << 25) + 33, 40_000_003])
+def test_walk_without_lists_and_close_loads(dyn, tokens):
+    """Which tick has the largest TBT is then a matter of roundings, and the walk without lists asks only ticks near the largest load."""
+    for seed in range(6):
+        w, n_tick = _close_case(tokens, seed)
+        prof = dyn.dyn_profile_load(w["profile"])
+        ins, outs, off, _ = dyn.dyn_trace_ingest(*(_dev(w["trace"][k]) for k in ("t_s", "in_tok", "out_tok", "model")), w["edges"], n_tick, 1.0)
+        space, sel, ws = dyn.dyn_eval_select_ticks(prof, ins, outs, off, 1, n_tick, 1.0, dyn.Plan(w["configs"], w["slos"], (90, 100), None, 0.0))
+        torch.cuda.synchronize()
+        fine = {"in_tok": ins.cpu().numpy(), "out_tok": outs.cpu().numpy(), "cell_off": off.cpu().numpy()}
+        o = oracle.evaluate_ticks(w["profile"], fine, 1, n_tick, 1.0, w["configs"], w["slos"], (90, 100), None, 0.0)
+        for k in ("energy_j", "p99_ttft_ms", "p99_tbt_ms", "flags"):
+            np.testing.assert_array_equal(space[k].cpu().numpy(), o[k], err_msg=k)
+        np.testing.assert_array_equal(sel["sel"].cpu().numpy(), o["sel"])
+        # the cell's plan in the workspace: j, x_j, flags
+        j = fine["in_tok"].size - -(-90 * fine["in_tok"].size // 100) + 1
+        words = ws[: ws.numel() // 4 * 4].view(torch.int32).cpu().numpy()
+        i = np.flatnonzero((words[:-3] == j) & (words[1:-2] == np.sort(fine["in_tok"])[-j]))
+        assert i.size == 1 and words[i[0] + 2] & (DENSE | GENERAL | TIGHT) == DENSE | TIGHT
+        prof.free()
 
 
 def test_blocks_of_many_windows_and_of_few(dyn):
