@@ -87,7 +87,7 @@ __device__ __forceinline__ double lane_f64(double x, int lane) { return __longlo
 // u, and |a * n| < u) it can be the next but one.  Let m be the midpoint of two doubles nearest to a / b; a - m * b = k u^2 for an
 // integer k, not 0.  Up to |k| = 4, a * rb = m + a * n + k u^2 / b is less than u from m, so q0 is a neighbour of m and with that of
 // a / b.  Beyond, a / b is 5 u^2 / b or more from m, and what the last rounding is given is off by less: by |q0 - a / b| * b * |n|, at most
-// (a + 1) b u^2 / 4 < 3 u^2 / b, and by the residual's own rounding, at most 2 u^2 / b.  (All pairs of up to 13 bits, and the hardest of 53:
+// (a + 1) b u^2 / 4 < 3 u^2 / b, and by the residual's own rounding, at most 2 u^2 / b.  (All pairs of up to 10 bits, and the hardest of 53:
 // tests/test_division.py.)  Holds while nothing under- or overflows: the host keeps window lengths, capacities and grid
 // spacings within [1e-100, 1e100], which leaves every operand, residual and quotient normal
 // (a == 0 gives 0 exactly).
