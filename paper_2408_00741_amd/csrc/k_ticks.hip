@@ -2412,11 +2412,13 @@ int32_t dyn_tick_win_per_block(const TickArgs& a) {
 // long blocks lose the least by it, but one that begins last runs alone to its end, and the classes differ (22 to 48 us for the same
 // windows, by how many ticks hold requests of the percentile's length).  So where every place on the device has windows enough, blocks of
 // many windows come first and leave four rounds of blocks of few.  36 000 cells of 576 candidates and 12 ticks, us of the call: 14
-// windows a block 441, 10 436, 20 first and then 7 417, 20 and 5 410, 16 and 5 410, 24 and 8 424.
+// windows a block 441, 10 436, 20 first and then 7 417, 20 and 5 410, 16 and 5 410, 24 and 8 424.  Other shapes, blocks of one size and of two: 30 ticks 772, 685; 40 ticks
+// and 256 candidates 603, 566; 6 ticks and 100 classes 898, 869; 5 ticks and 2048 candidates 697, 672; 12 ticks and 1152 630, 602, and 320 651, 629, and 192 515, 489; 200 load
+// points 1019, 868; mostly cells with lists 905, 902.  A block's LDS is its rows and its axis (uneven points 956 without the axis, 918).
 static void tight_chunks(TickArgs& a, size_t tab, int axis) {
   SpaceArgs& sa = a.s;
   const int64_t few = std::max<int64_t>(2, std::min<int64_t>(16, stage_windows(a))), many = 4 * few;
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4 * tight_waves(axis, sa.two_rows) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + 2048)));
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4 * tight_waves(axis, sa.two_rows) * DYN_WAVE / sa.tile, (160 * 1024) / (int64_t)(tab + dyn_axis_lds(sa.axis, axis))));
   const int64_t places = per_cu * std::max(1, a.n_cu), columns = (int64_t)sa.G * sa.n_tile;
   const int64_t kept = (4 * few * places + columns - 1) / columns;   // windows left to the blocks of few
   a.win_long = (int32_t)many;
