@@ -60,16 +60,18 @@ inline bool dyn_freq_axis_staged(size_t axis_lds, size_t lds, int64_t blocks, in
 // How the hierarchy's frequency kernel is cut: blocks of `wins` windows and `run` classes, `chunk` ticks in LDS at a time.  A block's chain (layouts, capacities, four
 // rounds of look-ups, sums) is 9 us whatever it holds, so a block takes the windows that give its threads work, as long as every compute unit has a
 // block: 20 160 windows of one class and 12 ticks 50 us a call, a window a block 150; 2016 windows 42.6, 50.8; 10 000 windows of 4 classes and 5 ticks 60, 107.
-// Classes beyond one run are cut into runs alike: 100 classes (300 windows, 12 ticks) by 34, 34, 32 78 us, by 47, 47, 6 84.  Where the device has a place for every block
-// anyway, a block gets the threads to look everything up in one round: an hour of 25 classes 26.7 us, 31.1 with 256.
+// Classes beyond one run are cut into runs alike: 100 classes (300 windows, 12 ticks) by 34, 34, 32 78 us, by 47, 47, 6 84.  A round of a block's threads is
+// 4.8 us: where twice as many blocks as compute units or fewer hold every look-up in one round, classes are cut for that, though the totals are then a launch of
+// their own.  An hour of 25 classes and 12 ticks 37.1 us a call (one run, two rounds 40.5), 30 ticks 34.6 (43.8), 90 classes 36.7 (47.5), 240 windows of 25
+// 40.3 (44.4).  Larger blocks do as well alone, but those of more than four waves wait for the end of another stream's kernel: beside an
+// element-wise one the hour takes 160 us, 2000 to 3000 by blocks of 320 threads.
 struct DynFreqShape {
-  int32_t wins, run, n_run, chunk, threads;
+  int32_t wins, run, n_run, chunk;
   bool tabled, staged;           // capacities tabled; load axis in LDS
   int64_t blocks;
   size_t lds;
 };
 #define DYN_FREQ_THREADS 256
-#define DYN_FREQ_MOST 512        // threads of a block at most
 #define DYN_FREQ_CHUNK 64
 #define DYN_FREQ_TABLED 128      // frequencies up to which the capacities are tabled
 #define DYN_FREQ_LDS (16 * 1024) // of results and capacities: blocks beside another stream's kernel find room
@@ -78,15 +80,15 @@ inline DynFreqShape dyn_freq_shape(int32_t n_window, int32_t G, int32_t n_tick, 
   f.chunk = std::min(n_tick, DYN_FREQ_CHUNK);
   f.tabled = n_f <= DYN_FREQ_TABLED;
   const size_t per_cell = (size_t)f.chunk * 12 + (f.tabled ? (size_t)n_f * 16 : 0) + 20;
-  const int32_t most = std::min(DYN_FREQ_THREADS, (int32_t)std::max<size_t>(1, DYN_FREQ_LDS / per_cell));   // cells
+  int32_t most = std::min(DYN_FREQ_THREADS, (int32_t)std::max<size_t>(1, DYN_FREQ_LDS / per_cell));   // cells
+  const int32_t one = DYN_FREQ_THREADS / f.chunk;            // cells of one round
+  if ((int64_t)n_window * ((G + one - 1) / one) <= 2 * (int64_t)n_cu) most = std::min(most, one);
   f.n_run = (G + most - 1) / most;
   f.run = (G + f.n_run - 1) / f.n_run;                       // alike: the last block is as full as the others
   const int32_t items = f.run * f.chunk;
   f.wins = 1;
   if (f.n_run == 1) f.wins = std::max(1, std::min({most / G, DYN_FREQ_THREADS / items, n_window / std::max(1, n_cu)}));
   f.blocks = (int64_t)((n_window + f.wins - 1) / f.wins) * f.n_run;
-  f.threads = DYN_FREQ_THREADS;
-  if (items > f.threads && f.blocks <= n_cu) f.threads = std::min(DYN_FREQ_MOST, (items + 63) / 64 * 64);
   f.lds = (size_t)f.wins * f.run * per_cell;
   f.staged = f.tabled && dyn_freq_axis_staged(axis_lds, f.lds + axis_lds, f.blocks, n_cu);
   if (f.staged) f.lds += axis_lds;

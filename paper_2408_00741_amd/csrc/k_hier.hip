@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kShardWaves* DYN_WAVE) void hier_shard_kernel(HierA
 // LDS: [load axis] [energy chunk*cells] [capacities, reciprocals cells*n_f each (TABLED)] [instances cells] [frequency chunk*cells] [table row cells] [first tick cells]
 //      [class cells] [bucket index]
 template <bool TABLED, int AXIS>
-__global__ __launch_bounds__(DYN_FREQ_MOST) __attribute__((amdgpu_waves_per_eu(6, 6))) void hier_freq_kernel(HierArgs a, DynFreqShape f) {
+__global__ __launch_bounds__(DYN_FREQ_THREADS) __attribute__((amdgpu_waves_per_eu(6, 6))) void hier_freq_kernel(HierArgs a, DynFreqShape f) {
   extern __shared__ double s_freq[];
   const int run = f.run, chunk = f.chunk, most = f.wins * run;
   const int w0 = (int)(blockIdx.x / f.n_run) * f.wins, g0 = (int)(blockIdx.x % f.n_run) * run;
@@ -477,7 +477,7 @@ hipError_t dyn_launch_hier_ticks(const HierArgs& a, hipStream_t s) {
   const DynFreqShape f = dyn_freq_shape(a.n_window, a.G, a.n_tick, a.n_f, dyn_axis_lds(a.axis, axis), a.n_cu);
   {
     DynTimed timed(DYN_K_HIER, s);
-    const dim3 grid((unsigned)f.blocks), block(f.threads);
+    const dim3 grid((unsigned)f.blocks), block(DYN_FREQ_THREADS);
     with_axis(axis, [&](auto x) {
       constexpr int FORM = decltype(x)::value;
       if (f.staged) hipLaunchKernelGGL((hier_freq_kernel<true, FORM>), grid, block, f.lds, s, a, f);

@@ -280,7 +280,7 @@ def test_many_ticks_and_many_frequencies(dyn, n_tick, n_f):
 
 @pytest.mark.parametrize("G,n_tick,NW", [(1, 1, 5003), (1, 5, 1030), (1, 12, 2017), (1, 65, 600), (3, 5, 2000), (9, 12, 1025), (25, 12, 7), (48, 12, 3), (100, 12, 5)])
 def test_windows_and_classes_packed_into_blocks(dyn, G, n_tick, NW):
-    """Blocks of several windows (the last not full), of more than 256 threads, and runs of classes; some cells without a layout, some without requests."""
+    """Blocks of several windows (the last not full), of more look-ups than threads, and runs of classes; some cells without a layout, some without requests."""
     prof, tr, edges, slo, lay_n, lay_tp, NW, T, tick = _random_case(G, n_tick, 3, 40 * n_tick * G + 6 * NW * n_tick, NW)
     rng = np.random.default_rng(G)
     a = 1 if G in (1, 3) else {9: 3, 25: 5, 48: 6, 100: 10}[G]

@@ -79,3 +79,18 @@ def test_path(dyn, n_layout):
     early, _ = calls_through_early(lambda: dyn.dyn_select_path(prof, space, n_win, 60.0, plan, np.arange(n_layout, dtype=np.int32), tr))
     prof.free()
     assert early >= 2, early
+
+
+@pytest.mark.parametrize("n_win,n_tick", [(60, 12), (240, 12), (20, 30)])
+def test_hierarchy(dyn, n_win, n_tick):
+    """Windows of 25 classes with more ticks than a block of four waves has threads."""
+    w = make(SPECS[2].scaled(400 * n_win, n_win))
+    raw = [_dev(w["trace"][k]) for k in ("t_s", "in_tok", "out_tok", "model")]
+    coarse = dyn.dyn_trace_ingest(*raw, w["edges"], n_win, w["window_s"])[:3]
+    fine = dyn.dyn_trace_ingest(*raw, w["edges"], n_win * n_tick, w["window_s"] / n_tick)[:3]
+    prof = dyn.dyn_profile_load(w["profile"])
+    n, t = np.meshgrid(np.arange(1, 17, dtype=np.int32), np.arange(3, dtype=np.int32))
+    early, _ = calls_through_early(lambda: dyn.dyn_hierarchy(prof, coarse, fine, n_win, n_tick, w["window_s"] / n_tick, 6, 2, w["profile"]["f_mhz"].size - 1, 8,
+                                                             n.ravel(), t.ravel(), w["slos"], w["pct"]))
+    prof.free()
+    assert early >= 2, early

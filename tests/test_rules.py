@@ -15,8 +15,8 @@ extern "C" int space_windows(long long cell_tiles, int tile, long long staged, i
 extern "C" int freq_axis_staged(long long axis_lds, long long lds, long long blocks, int n_cu) { return dyn_freq_axis_staged((size_t)axis_lds, (size_t)lds, blocks, n_cu); }
 extern "C" void freq_shape(int n_window, int G, int n_tick, int n_f, long long axis_lds, int n_cu, long long* o) {
   const DynFreqShape f = dyn_freq_shape(n_window, G, n_tick, n_f, (size_t)axis_lds, n_cu);
-  const long long v[] = {f.wins, f.run, f.n_run, f.chunk, f.threads, f.tabled, f.staged, f.blocks, (long long)f.lds};
-  for (int i = 0; i < 9; ++i) o[i] = v[i];
+  const long long v[] = {f.wins, f.run, f.n_run, f.chunk, f.tabled, f.staged, f.blocks, (long long)f.lds};
+  for (int i = 0; i < 8; ++i) o[i] = v[i];
 }
 """
 
@@ -82,25 +82,25 @@ def test_where_the_frequency_kernel_keeps_a_long_axis(rules, axis, lds, blocks, 
 def test_cut_of_the_frequency_kernel(rules, G):
     """Every cell in one block, a thread for every cell, the LDS that a block is given room for, and no block of a few lanes where windows could fill it."""
     for n_window, n_tick, n_f, axis in itertools.product((1, 60, 511, 2016, 20160), (1, 5, 12, 64, 65, 1000), (1, 12, 128, 129), (1512, 60_000, 150_000)):
-        o = (C.c_longlong * 9)()
+        o = (C.c_longlong * 8)()
         rules.freq_shape(n_window, G, n_tick, n_f, C.c_longlong(axis), 256, o)
-        wins, run, n_run, chunk, threads, tabled, staged, blocks, lds = o
+        wins, run, n_run, chunk, tabled, staged, blocks, lds = o
         assert wins >= 1 and run >= 1 and chunk == min(n_tick, 64) and tabled == (n_f <= 128)
         assert run * n_run >= G > run * (n_run - 1) and (wins == 1 or n_run == 1)
         assert blocks == -(-n_window // wins) * n_run
         cells = wins * run
-        assert cells <= 256 <= threads <= 512 and threads % 64 == 0
+        assert cells <= 256
         need = cells * (chunk * 12 + (16 * n_f if tabled else 0) + 20)
         assert lds == need + (axis if staged else 0) <= 160 * 1024 and need <= 16 * 1024
         assert G - run * (n_run - 1) > run - n_run                   # runs alike: the last lacks less than one class a run
         if n_run == 1 and blocks >= 2 * 256:                        # more blocks than places: they are half full, or as full as LDS lets them
             assert 2 * cells * chunk > 256 or 2 * need > 16 * 1024 - need // cells * G
-        if blocks <= 256:
-            assert threads >= min(512, run * chunk)
+        if n_window * -(-G // (256 // chunk)) <= 2 * 256:            # few: every look-up of a block in one round
+            assert run * chunk <= 256
 
 
 def test_few_classes_share_a_block(rules):
     for n_window, G, n_tick, wins in ((20160, 1, 12, 21), (2016, 1, 12, 7), (2016, 1, 1, 7), (60, 1, 12, 1), (10000, 4, 5, 12), (1440, 9, 12, 2), (1440, 25, 12, 1)):
-        o = (C.c_longlong * 9)()
+        o = (C.c_longlong * 8)()
         rules.freq_shape(n_window, G, n_tick, 12, C.c_longlong(1512), 256, o)
         assert o[0] == wins, (n_window, G, n_tick)
