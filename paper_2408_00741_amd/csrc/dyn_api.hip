@@ -533,7 +533,7 @@ int dyn_profile_load(const dyn_profile_desc* d, void* hip_stream, dyn_profile** 
   gridpack[d->n_rho + 1] = INFINITY;
   for (int q = 0; q + 1 < d->n_rho; ++q) gridpack[d->n_rho + 3 + q] = 1.0 / (d->rho[q + 1] - d->rho[q]);
   p->rho_max = rho_max;
-  p->even_scale = dyn_even_scale(d->rho, d->n_rho);
+  p->even_scale = dyn_even_scale(d->rho, d->n_rho, p->n_bucket);
   p->even = p->even_scale > 0.0;
   const size_t even_at = gridpack.size();       // the triples follow the padded grid in its allocation
   for (int q = 0; q + 1 < d->n_rho; ++q)

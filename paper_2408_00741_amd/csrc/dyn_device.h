@@ -232,8 +232,8 @@ __device__ __forceinline__ int find_index(const Lookup& L, double rc) {
 }
 // The bracket of the load axis that rc = min(rho, rho_max) lies in and its weight there; load(j) reads from the table rows what
 // the caller wants of load points j and j + 1, read() waits for it.
-// EVEN: the bracket is one multiplication away, or one less where rc is just below the load point (dyn_even_scale), which a
-// wave hardly ever meets: everything is read at once and read again in that case.  SINGLE: every bucket holds at most one
+// EVEN: the bracket is one multiplication away, or one less where rc is just below the load point (dyn_even_scale), which few
+// waves meet: everything is read at once and read again in that case.  SINGLE: every bucket holds at most one
 // interior grid point, so the bracket is the bucket's start index plus one comparison.  SEARCH: searched from the bucket's index.
 // Vector instructions of a look-up of three columns: 50 by SINGLE from three tables side by side, 33 by EVEN from one of triples.
 template <int AXIS, typename Load, typename Read>

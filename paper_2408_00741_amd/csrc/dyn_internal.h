@@ -77,8 +77,8 @@ struct dyn_profile {
   int32_t* d_tstart;  // [n_bucket + 1]
   double* d_thr;      // [n_bucket + 1]
   bool single_point;
-  // Load points that lie evenly from 0 on up to roundings (dyn_even_scale): rho[i] * even_scale is i or up to 2^-20 more for every one, so
-  // that for any load x the largest i with rho[i] <= x is (int)(x * even_scale), or one less where x is that little below the next point.
+  // Load points that lie one in each of n_rho - 1 even steps from 0 on (dyn_even_scale says how near its start): (int)(rho[i] * even_scale) is i for
+  // every one, so that for any load x the largest i with rho[i] <= x is (int)(x * even_scale), or one less where x lies below its step's point.
   bool even;
   double even_scale;
   double* d_even_grid;  // [n_rho - 1][3] load point, spacing, its reciprocal

@@ -7,15 +7,22 @@
 #include <cstdint>
 
 // Evenly spaced load points: buckets a little narrower than the spacing, of which every point opens its own and fills at most the first
-// 2^-20 (the points' own roundings and the 2^-40 take far less).  A product by a constant is monotone, so only loads in that part of a
-// bucket can lie below its point: a wave hardly ever meets one.  Points anywhere in their buckets would do as well for the result, but with
-// points 0.3 to 0.9 of a spacing late most loads then are asked twice: 36 000 cells of mixed pools 294 us, 248 by the buckets' index; ticks 562, 486.
-// Returns buckets per unit of the load axis, 0 where the points do not lie so.
-inline double dyn_even_scale(const double* rho, int32_t n_rho) {
+// 2^-10 (the points' own roundings and the 2^-40 take far less).  A product by a constant is monotone, so only loads in that part of a
+// bucket can lie below its point: one wave in sixteen meets one.  Points anywhere in their buckets do as well for the result, but with points 0.3 to 0.9 of a
+// spacing late most loads are asked twice; with the buckets' index instead they cost what room it takes in LDS (10 bytes a bucket, three
+// buckets to the least spacing).  us a call by the index, by the even form (36 000 cells; 12 ticks; mixed pools; evaluation; hierarchy):
+//   64 points, 0.3 late, 269 buckets:   464 572   239 291   134 141    97 101       33 points, 0.9 late, 960 buckets:  461 544   235 265   153 160    96 100
+//   64 points, 0.8 late, 945 buckets:   522 576   263 291   133 140    98 100       33 points, 0.95, 1920 buckets:     524 544   260 265   158 160   107 100
+//   64 points, 0.9 late, 1890 buckets:  586 577   296 291   140 138   109 100       64 points, 0.95, 3780 buckets:     944 577   379 292   154 137   112 100
+//   128 points, 0.6 late, 952 buckets:  700 824   314 406   191 180   102 106      128 points, 0.8, 1905 buckets:      942 826   402 406   198 179   112 105
+// So beyond DYN_EVEN_BUCKETS buckets the points may lie anywhere in theirs.  Returns buckets per unit of the load axis, 0 where the points do not lie so.
+#define DYN_EVEN_BUCKETS 1500
+inline double dyn_even_scale(const double* rho, int32_t n_rho, int32_t n_bucket /* of the index */) {
   const double scale = (double)(n_rho - 1) / rho[n_rho - 1] * (1.0 + 0x1p-40);
+  const double late = n_bucket > DYN_EVEN_BUCKETS ? 1.0 : 0x1p-10;
   for (int32_t q = 1; q < n_rho; ++q) {
     const double x = rho[q] * scale - (double)q;
-    if (!(x >= 0.0 && x < 0x1p-20)) return 0.0;
+    if (!(x >= 0.0 && x < late)) return 0.0;
   }
   return scale;
 }

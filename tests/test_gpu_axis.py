@@ -33,6 +33,7 @@ GRIDS = {
     "many": np.linspace(0.0, 0.95, 900),                                           # a row of 21 KB
     "jitter": np.linspace(0.0, 0.95, 33) * (1.0 + 1e-9 * np.sin(np.arange(33.0))),    # more than the even form allows
     "late": np.linspace(0.0, 0.95, 33) + np.r_[0.0, np.linspace(0.3, 0.9, 31), 0.0] * (0.95 / 32),    # points late in their buckets
+    "crowded": np.linspace(0.0, 0.95, 33) + np.r_[0.0, np.full(31, 0.95), 0.0] * (0.95 / 32),      # so late that the even form takes them
     "uneven": np.r_[0.0, np.geomspace(0.01, 0.95, 20)],
 }
 
