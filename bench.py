@@ -34,7 +34,7 @@ def kernel_source_hash():
     reported while it still describes the kernel as it stands."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("k_space.hip", "dyn_internal.h"):
+    for name in ("k_space.hip", "dyn_device.h", "dyn_internal.h", "dyn_rules.h"):
         with open(os.path.join(ROOT, "paper_2408_00741_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

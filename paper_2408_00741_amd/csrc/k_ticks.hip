@@ -1597,7 +1597,7 @@ struct TickMask {
 __device__ __forceinline__ TickMask tick_mask(const TickRec& r, bool asks, int T, int lane) {
   static_assert(DYN_TICK_NEAR == 0x1p-20, "a step of the high word");
   TickMask m;
-  if (T <= 2) {                                  // not worth the exchange between the lanes: 60 000 cells of one tick and 2048 candidates 148 us, 142
+  if (T <= 2) {                                  // not worth the exchange between the lanes: 7500 cells of one tick and 2048 candidates 148 us, 142
     m.some = m.eq = 0;
     m.top_load = 0.0;
     for (int q = 0; q < T; ++q) {
